@@ -1,89 +1,223 @@
-// a6 for fp32 layers (correctness configuration): Y = (X Vt_S^T) Ut_S with plain fp32 FMA tiles.
-// Two launches of one LDS-tiled kernel; the r_S-wide intermediate goes through the workspace.
-// Each 64-row block of the flat token axis is cut into the segments that belong to one prompt, and a
-// segment uses the packed factors of that prompt's pattern.
+// a6 for fp32 layers: Y = (X Vt_S^T) Ut_S on the fp32 matrix instructions (16x16x4, full fp32 products and sums), two
+// launches; the r_S-wide intermediate goes through the workspace.
+//
+// What bounds it: the fp32 layers are small (256 tokens x 1024 x 128 ranks: 0.13 GFLOP, 3 MB), so what counts is how much of
+// the chip works at once and how many dependent memory round trips a wavefront makes.  Hence small output tiles (16 or 32
+// token rows), the reduction cut over the wavefronts of a workgroup (added in wavefront order through LDS), and operands
+// fetched straight into registers, several 16-deep reduction chunks at a time: lane (i = l % 16, g = l / 16) takes 16
+// bytes of its row at reduction index 4 g, and the four matrix instructions of a chunk use element e of every lane, i.e.
+// reduction indices {e, 4 + e, 8 + e, 12 + e} -- the same for both operands, so the order within a chunk does not matter.
+// Measured at that size: first product 150.7 -> 7.7 us, second 26.9 -> 4.8 us (before: 64 x 64 tiles of plain FMA through
+// LDS, 8 workgroups for the first product).
+//
+// Each block of token rows is cut into the segments that belong to one prompt, and a segment uses the packed factors of
+// that prompt's pattern.
 #include "common.hpp"
 
 namespace parse {
 
-constexpr int TM = 64, TN = 64, TK = 16;
+__device__ __forceinline__ f32x4 mfma_f32_16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
-// C[rows][N] = A[rows][K] * op(B_p).  B_NT: B_p is [N][K] (Vt_S);  else B_p is [K][N] (Ut_S).
-template <bool B_NT>
-__global__ __launch_bounds__(256) void sgemm_segments(const float *__restrict__ A, const float *__restrict__ Bbase,
-                                                      size_t pattern_stride, int n_patterns, int rows, int N, int K,
-                                                      const int32_t *__restrict__ tok_offsets,
-                                                      const int32_t *__restrict__ pattern_id, int P,
-                                                      float *__restrict__ C) {
-  __shared__ float As[TK][TM + 1];
-  __shared__ float Bs[TK][TN + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int row0 = blockIdx.x * TM, col0 = blockIdx.y * TN;
-  const int row_end = min(row0 + TM, rows);
+// one block of token rows: calls body(valid, pattern, seg_lo, seg_hi) for every prompt segment of rows [row0, row_end)
+template <typename F>
+__device__ __forceinline__ void for_segments(int row0, int row_end, int rows, const int32_t *__restrict__ tok_offsets,
+                                             const int32_t *__restrict__ pattern_id, int P, int n_patterns, F body) {
   int seg_lo = row0;
   while (seg_lo < row_end) {
-    const int p = prompt_of_row(tok_offsets, P, seg_lo);
+    const int p = prompt_of_row_wave(tok_offsets, P, seg_lo);
     int seg_hi = (p + 1 < P) ? tok_offsets[p + 1] : rows;   // the last prompt owns every remaining row
     seg_hi = min(max(seg_hi, seg_lo + 1), row_end);
     const int pid = pattern_id[p];
-    const bool valid = pid >= 0 && pid < n_patterns;
-    const float *B = Bbase + (valid ? (size_t)pid * pattern_stride : 0);
-    float acc[4][4] = {};
-    if (valid) {
-      for (int k0 = 0; k0 < K; k0 += TK) {
-        // A tile: 64 rows x 16 k; thread loads 4 elements
-        for (int i = threadIdx.x; i < TM * TK; i += 256) {
-          const int r = i / TK, kk = i % TK;
-          const int gr = min(row0 + r, rows - 1), gk = k0 + kk;
-          As[kk][r] = (gk < K) ? A[(size_t)gr * K + gk] : 0.f;
-        }
-        for (int i = threadIdx.x; i < TN * TK; i += 256) {
-          int c, kk;
-          if (B_NT) { c = i / TK; kk = i % TK; } else { kk = i / TN; c = i % TN; }
-          const int gc = col0 + c, gk = k0 + kk;
-          float v = 0.f;
-          if (gc < N && gk < K) v = B_NT ? B[(size_t)gc * K + gk] : B[(size_t)gk * N + gc];
-          Bs[kk][c] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < TK; ++kk) {
-          float a[4], b[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = row0 + ty * 4 + i;
-      if (r < seg_lo || r >= seg_hi) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = col0 + tx * 4 + j;
-        if (c < N) C[(size_t)r * N + c] = acc[i][j];
-      }
-    }
+    body(pid >= 0 && pid < n_patterns, pid, seg_lo, seg_hi);
     seg_lo = seg_hi;
   }
 }
+
+constexpr int FN_WAVES = 8;          // first product: wavefronts of a workgroup = parts of the reduction
+
+// Z[rows][N] = X[rows][K] * B_p[N][K]^T.  K % 4 == 0.  RT x CT blocks of 16 token rows x 16 ranks per workgroup; a
+// wavefront requests BATCH reduction chunks at a time.
+template <int RT, int CT, int BATCH>
+__global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restrict__ A, const float *__restrict__ Bbase,
+                                                          size_t pattern_stride, int n_patterns, int rows, int N, int K,
+                                                          const int32_t *__restrict__ tok_offsets,
+                                                          const int32_t *__restrict__ pattern_id, int P, float *__restrict__ C) {
+  constexpr int TN = CT * 16;
+  __shared__ float red[FN_WAVES][RT * 16][TN];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * TN;
+  const int chunks = (K + 15) / 16;
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  for_segments(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
+    f32x4 acc[RT][CT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int u = 0; u < CT; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (valid) {
+      const float *arow[RT], *brow[CT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) arow[t] = A + (size_t)min(row0 + t * 16 + i16, rows - 1) * K;
+#pragma unroll
+      for (int u = 0; u < CT; ++u) brow[u] = Bbase + (size_t)pid * pattern_stride + (size_t)min(col0 + u * 16 + i16, N - 1) * K;
+      for (int c0 = wave; c0 < chunks; c0 += FN_WAVES * BATCH) {
+        f32x4 av[BATCH][RT], bv[BATCH][CT];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {                    // chunks past the end are not read (uniform); the last one may be cut
+          const int c = c0 + b * FN_WAVES, k = c * 16 + g * 4;
+          if (c < chunks) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) av[b][t] = k < K ? *reinterpret_cast<const f32x4 *>(arow[t] + k) : zero4;
+#pragma unroll
+            for (int u = 0; u < CT; ++u) bv[b][u] = k < K ? *reinterpret_cast<const f32x4 *>(brow[u] + k) : zero4;
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+          if (c0 + b * FN_WAVES < chunks) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+              for (int u = 0; u < CT; ++u) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[t][u] = mfma_f32_16(av[b][t][e], bv[b][u][e], acc[t][u]);
+              }
+          }
+        }
+      }
+    }
+    __syncthreads();                 // the previous segment's sums have been read
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int u = 0; u < CT; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][t * 16 + g * 4 + r][u * 16 + i16] = acc[t][u][r];
+    __syncthreads();
+#pragma unroll
+    for (int o = threadIdx.x; o < RT * 16 * TN; o += FN_WAVES * 64) {
+      const int r = o / TN, c = o % TN;
+      float s = red[0][r][c];
+#pragma unroll
+      for (int w = 1; w < FN_WAVES; ++w) s += red[w][r][c];
+      if (row0 + r >= lo && row0 + r < hi && col0 + c < N) C[(size_t)(row0 + r) * N + col0 + c] = s;
+    }
+  });
+}
+
+constexpr int FS_WAVES = 4;          // second product: parts of the (short) reduction
+constexpr int FS_TN = 64;            // output columns per workgroup
+constexpr int FS_BATCH = 2;
+
+// Y[rows][N] = Z[rows][K] * B_p[K][N].  N % 4 == 0; K arbitrary (A4: K % 4 == 0, 16-byte loads of Z).  A lane takes 4
+// consecutive columns of a factor row, so the four sub-tiles of a workgroup's 64 columns are interleaved: sub-tile e holds
+// columns 4 i + e, and a lane ends up with 4 consecutive columns of its 4 output rows.
+template <int RT, bool A4>
+__global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restrict__ A, const float *__restrict__ Bbase,
+                                                          size_t pattern_stride, int n_patterns, int rows, int N, int K,
+                                                          const int32_t *__restrict__ tok_offsets,
+                                                          const int32_t *__restrict__ pattern_id, int P, float *__restrict__ C) {
+  __shared__ float4 red[FS_WAVES][RT * 16][FS_TN / 4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int i16 = lane & 15, g = lane >> 4;
+  const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * FS_TN;
+  const int chunks = (K + 15) / 16;
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  for_segments(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
+    f32x4 acc[RT][4];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (valid) {
+      const float *arow[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) arow[t] = A + (size_t)min(row0 + t * 16 + i16, rows - 1) * K;
+      const float *bcol = Bbase + (size_t)pid * pattern_stride + min(col0 + i16 * 4, N - 4);
+      for (int c0 = wave; c0 < chunks; c0 += FS_WAVES * FS_BATCH) {
+        f32x4 av[FS_BATCH][RT], bv[FS_BATCH][4];
+#pragma unroll
+        for (int b = 0; b < FS_BATCH; ++b) {
+          const int c = c0 + b * FS_WAVES, k = c * 16 + g * 4;
+          if (c < chunks) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+              if (A4) av[b][t] = k < K ? *reinterpret_cast<const f32x4 *>(arow[t] + k) : zero4;
+              else av[b][t] = f32x4{k < K ? arow[t][k] : 0.f, k + 1 < K ? arow[t][k + 1] : 0.f, k + 2 < K ? arow[t][k + 2] : 0.f,
+                                     k + 3 < K ? arow[t][k + 3] : 0.f};
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bv[b][e] = k + e < K ? *reinterpret_cast<const f32x4 *>(bcol + (size_t)(k + e) * N) : zero4;
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < FS_BATCH; ++b) {
+          if (c0 + b * FS_WAVES < chunks) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[t][u] = mfma_f32_16(av[b][t][e], bv[b][e][u], acc[t][u]);
+              }
+          }
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        red[wave][t * 16 + g * 4 + r][i16] = float4{acc[t][0][r], acc[t][1][r], acc[t][2][r], acc[t][3][r]};
+    __syncthreads();
+#pragma unroll
+    for (int o = threadIdx.x; o < RT * 16 * (FS_TN / 4); o += FS_WAVES * 64) {
+      const int r = o / (FS_TN / 4), c = o % (FS_TN / 4);
+      float4 s = red[0][r][c];
+#pragma unroll
+      for (int w = 1; w < FS_WAVES; ++w) {
+        const float4 v = red[w][r][c];
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+      }
+      const int col = col0 + c * 4;
+      if (row0 + r >= lo && row0 + r < hi && col < N) *reinterpret_cast<float4 *>(C + (size_t)(row0 + r) * N + col) = s;
+    }
+  });
+}
+
+// 32 token rows per workgroup (every factor operand fetched for twice the products) once 16-row tiles give each compute
+// unit several workgroups anyway
+constexpr int F32_MANY_WGS = 1024;
+// below it (fewer than two 16 x 16 workgroups per compute unit) the first product takes the smallest tiles: twice the units
+// at work and, for n <= 1024, every operand of a wavefront requested at once (256 tokens x 128 ranks: 7.7 us against 10.7 with
+// 16 x 32)
+constexpr int F32_FEW_WGS = 512;
 
 int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, int rows, const int32_t *tok_offsets,
                 const int32_t *pattern_id, int P, float *Y, void *workspace, hipStream_t s) {
   const int gs = L->R / L->G, rS = pt->k * gs;
   float *Z = reinterpret_cast<float *>(workspace);
-  dim3 g1((rows + TM - 1) / TM, (rS + TN - 1) / TN);
-  hipLaunchKernelGGL(sgemm_segments<true>, g1, dim3(256), 0, s, X, (const float *)pt->Vt_S, (size_t)rS * L->n,
-                     pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z);
+  const float *V = (const float *)pt->Vt_S, *U = (const float *)pt->Ut_S;
+  const size_t vs = (size_t)rS * L->n, us = (size_t)rS * L->m;
+  const int t16 = (rows + 15) / 16, t32 = (rows + 31) / 32;
+  const int nb16 = (rS + 15) / 16, nb32 = (rS + 31) / 32, nb2 = (L->m + FS_TN - 1) / FS_TN;
+#define PARSE_NT(RT_, CT_, B_)                                                                                             \
+  hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16), dim3(FN_WAVES * 64), 0, \
+                     s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
+  if ((long long)t16 * nb32 >= F32_MANY_WGS) PARSE_NT(2, 2, 4);
+  else if ((long long)t16 * nb16 >= F32_FEW_WGS) PARSE_NT(1, 2, 4);
+  else PARSE_NT(1, 1, 8);
+#undef PARSE_NT
   PARSE_LAUNCH_CHECK();
-  dim3 g2((rows + TM - 1) / TM, (L->m + TN - 1) / TN);
-  hipLaunchKernelGGL(sgemm_segments<false>, g2, dim3(256), 0, s, Z, (const float *)pt->Ut_S, (size_t)rS * L->m,
-                     pt->n_patterns, rows, L->m, rS, tok_offsets, pattern_id, P, Y);
+  const bool many = (long long)t16 * nb2 >= F32_MANY_WGS, a4 = rS % 4 == 0;
+#define PARSE_NN(RT_, A4_)                                                                                                       \
+  hipLaunchKernelGGL((sgemm_nn<RT_, A4_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
+                     rows, L->m, rS, tok_offsets, pattern_id, P, Y)
+  if (many) { if (a4) PARSE_NN(2, true); else PARSE_NN(2, false); }
+  else { if (a4) PARSE_NN(1, true); else PARSE_NN(1, false); }
+#undef PARSE_NN
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

@@ -1400,3 +1400,28 @@ def test_rank_router_at_its_limits():
             cut = np.sort(S[p])[::-1][K - 1]
             assert len(a) == len(b) and all(abs(S[p][g] - cut) < 1e-5 * np.abs(S).max() for g in a | b), f"prompt {p}"
         assert list(sg[p]) == sorted(set(sg[p]))
+
+
+@pytest.mark.parametrize("n,m,R,G,k,lengths", [
+    (4, 4, 2, 2, 1, [1]),                        # the smallest layer: one partly filled reduction chunk, one rank
+    (520, 516, 200, 8, 3, [7, 1, 33]),           # r_S = 75 (no 16-byte rows of Z), segments inside a 16-row block, ragged edges
+    (1032, 260, 250, 10, 4, [16, 17, 90]),       # n = 64.5 chunks, r_S = 100, a partial column block
+    (256, 4096, 64, 4, 2, [300, 40]),            # second product with 32-row workgroups, K a multiple of 4
+    (2048, 2048, 250, 10, 5, [530, 1, 200]),     # ... with a K that is not, long reductions in the first
+    (64, 64, 2080, 4, 4, [520, 9]),              # first product with 32-row workgroups (many ranks)
+])
+def test_prefill_fp32_edges(n, m, R, G, k, lengths):
+    """fp32 layers at the edges of their tiles, against the oracle (1e-4; measured 1e-6: the products and sums are fp32)."""
+    say(f"prefill fp32 n={n} m={m} R={R} G={G} k={k} lengths={lengths}")
+    if R > min(n, m):
+        rng = np.random.default_rng(971)
+        U0, V = rng.standard_normal((m, R)) / m ** 0.5, rng.standard_normal((R, n)) / n ** 0.5
+        sg = (np.arange(R) + 1.0) ** -0.5
+        lay = si.Layer(n, m, R, G, "f32", U0, sg, V, V.astype(np.float32), np.ascontiguousarray((U0 * sg).T, dtype=np.float32))
+    else:
+        lay = si.make_layer(np.random.default_rng(971), n, m, R, G, "f32", fast=True)
+    rng = np.random.default_rng(972)
+    subs = np.stack([np.sort(rng.choice(G, size=k, replace=False)) for _ in lengths]).astype(np.int32)
+    Yg, Yref, off = _run_prefill(lay, lengths, subs, 973, "f32")
+    for p in range(len(lengths)):
+        assert_close(Yg[off[p]:off[p + 1]], Yref[off[p]:off[p + 1]], TOL_F32, f"prompt {p}")
