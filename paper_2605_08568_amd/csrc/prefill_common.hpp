@@ -27,6 +27,18 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   return x * per + min(x, rem) + i;
 }
 
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit count");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// barrier without the fences of __syncthreads(): those would wait for ALL outstanding loads, also the slices
+// requested ahead.  The explicit vmcnt wait before it covers exactly the slice that is about to be read.
+__device__ __forceinline__ void wg_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 struct PfArgs {
   const uint16_t *X, *Vt_S, *Ut_S;
   uint16_t *Y;

@@ -28,18 +28,6 @@ namespace parse {
 #define PARSE_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 #define PARSE_GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 
-template <int N> __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit count");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// barrier without the fences of __syncthreads(): those would wait for ALL outstanding loads, also the slices
-// requested ahead.  The explicit vmcnt wait before it covers exactly the slice that is about to be read.
-__device__ __forceinline__ void wg_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 constexpr int LG_MAX_LAYERS = 4;
 
 // One product of one layer.  A launch covers up to LG_MAX_LAYERS of them (layers that share their token rows and the

@@ -1425,3 +1425,42 @@ def test_prefill_fp32_edges(n, m, R, G, k, lengths):
     Yg, Yref, off = _run_prefill(lay, lengths, subs, 973, "f32")
     for p in range(len(lengths)):
         assert_close(Yg[off[p]:off[p + 1]], Yref[off[p]:off[p + 1]], TOL_F32, f"prompt {p}")
+
+
+@pytest.mark.parametrize("n,m,R,G,lengths", [
+    (128, 128, 64, 2, [1]),                          # one token, half a rank tile
+    (256, 128, 96, 3, [33, 1, 30, 1]),               # 64 x 64 tiles, a rank tile past the end, prompts inside a token block
+    (128, 256, 2080, 13, [700, 613]),                # 128 x 128 tiles, group borders inside a tile (160 ranks per group)
+    (128, 128, 2048, 64, [3000, 1, 71]),             # 256 x 128 tiles, 64 groups of 32
+])
+def test_router_grad_tiles(n, m, R, G, lengths):
+    """Loss and gradient of parse_router_grad for given outputs, every tile of its paired product, against float64.  The only
+    16-bit rounding inside is that of the residual 2 (y_hat - y), which the reference does too; the rest is fp32 sums (at
+    most 256 products, 160 ranks, 3000 tokens): 2^-24 of their absolute sums per addition, and the differences between the
+    groups' terms cancel them down by up to a hundredfold, hence 1e-4."""
+    say(f"router_grad n={n} m={m} R={R} G={G} lengths={lengths}")
+    rng = np.random.default_rng(1201)
+    off = si.offsets_from_lengths(lengths)
+    rows, P, k, tau, eps = int(off[-1]), len(lengths), 2, 0.5, 1e-6
+    bits = lambda *s: si.f32_to_bf16_bits((rng.standard_normal(s) / 4).astype(np.float32))     # noqa: E731
+    val = lambda b: si.bf16_bits_to_f32(b).astype(np.float64)                                   # noqa: E731
+    Vt, Ut, X, Yh, Yd = bits(R, n), bits(R, m), bits(rows, n), bits(rows, m), bits(rows, m)
+    emb = rng.standard_normal((P, n)).astype(np.float32)
+    scores = rng.standard_normal((P, G)).astype(np.float32)
+    rm = pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, G, pa.PARSE_ROWMAJOR)
+    loss, grad = pa.router_grad(pa.layer_to_mfma16(rm), pa.rankmajor_left_factor(rm), upload_tokens(X, "bf16"), i32(off),
+                                upload_tokens(Yh, "bf16"), upload_tokens(Yd, "bf16"), torch.from_numpy(emb).to(DEV),
+                                torch.from_numpy(scores).to(DEV), k, tau, eps)
+    torch.cuda.synchronize()
+    D = val(Yh) - val(Yd)
+    g = val(si.f32_to_bf16_bits((2.0 * D).astype(np.float32)))
+    prod = ((val(X) @ val(Vt).T) * (g @ val(Ut).T)).reshape(rows, G, R // G).sum(2)
+    dm = np.stack([prod[off[p]:off[p + 1]].sum(0) for p in range(P)])
+    a = 1.0 / (1.0 + np.exp(-scores.astype(np.float64) / tau))
+    A, B = a.sum(1, keepdims=True) + eps, (dm * a).sum(1, keepdims=True)
+    ref = (k * a * (1 - a) / tau * (dm / A - B / A ** 2)).T @ emb.astype(np.float64)
+    err = np.linalg.norm(grad.cpu().numpy() - ref) / np.linalg.norm(ref)
+    lref = np.array([(D[off[p]:off[p + 1]] ** 2).sum() for p in range(P)])
+    say(f"    gradient {err:.2e}, loss {np.abs(loss.cpu().numpy() / lref - 1).max():.2e}")
+    assert err <= 1e-4
+    assert np.allclose(loss.cpu().numpy(), lref, rtol=1e-5)
