@@ -366,10 +366,13 @@ int parse_router_grad(const parse_layer *layer, const void *Ut_rankmajor, const 
  * (equal n; m, R, G and the patterns may differ per layer) take ONE decode step together: the result equals
  * n_layers separate PARSE_DECODE calls, at the launch count of one.
  *   layers, patterns  host arrays [n_layers]; layer l uses patterns[l] (its own subsets, k, n_patterns)
- *   X                 device [rows][n] bf16, one token per sequence (panels of 32 as for PARSE_DECODE)
+ *   X                 device [rows][n] bf16, one token per sequence (any number, as for PARSE_DECODE)
  *   pattern_id        device int32 [rows], shared by all layers (a sequence's cache entry)
  *   Y                 host array [n_layers] of device pointers, Y[l] = [rows][layers[l].m] bf16
- *   workspace         device, >= parse_lowrank_decode_multi_workspace_bytes(layers, n_layers), caller-owned
+ *   workspace         device, >= parse_lowrank_decode_multi_workspace_bytes(layers, n_layers), caller-owned.  The answer covers
+ *                     any number of sequences; a smaller one is accepted down to what one panel of 32 takes
+ *                     (parse_lowrank_decode_planned_workspace_bytes + parse_decode_plan_bytes), and then more than 32
+ *                     sequences go panel after panel, every panel streaming its groups again.
  * Errors as parse_lowrank_forward; nothing is launched on error.  Same inputs, same bits.  (A result may differ in
  * rounding from the single-layer call's: the reduction over n is cut into slices by the size of the whole call.) */
 size_t parse_lowrank_decode_multi_workspace_bytes(const parse_layer *layers, int32_t n_layers);

@@ -35,6 +35,29 @@ int forward_decode_multi_bf16(const parse_layer *layers, const parse_patterns *p
                               int B, const int32_t *pattern_id, uint16_t *const *Y, void *workspace, hipStream_t s);
 int forward_decode_bf16(const parse_layer *L, const parse_patterns *pt, const uint16_t *x, int B,
                         const int32_t *pattern_id, uint16_t *y, void *workspace, hipStream_t s);
+bool decode_wide_supported(const parse_layer *layers, int n_layers);
+size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int rows);
+int forward_decode_wide_bf16(const parse_layer *layers, const parse_patterns *pts, int n_layers, const uint16_t *x, int rows,
+                             const int32_t *pattern_id, void *const *Y, void *workspace, hipStream_t s);
+
+// A decode step of any number of sequences.  More than one panel of 32: all panels together, every group in use streamed
+// once, when the layers and the workspace allow it; else panel after panel (each has its own masks and streams the groups its
+// own sequences selected).  The line lies at the second panel: 33 sequences through the MLP of a 4096 x 11008 block take 75 us
+// together and 104 one panel after the other, 150 take 100 and 313, 64 through 1024 x 2816 layers 40 and 70.
+static int decode_rows(const parse_layer *layers, const parse_patterns *pts, int n_layers, const uint16_t *X, int rows,
+                       const int32_t *pattern_id, void *const *Y, void *workspace, size_t workspace_bytes, hipStream_t s) {
+  if (rows > 32 && decode_wide_supported(layers, n_layers) && workspace_bytes >= decode_wide_workspace_bytes(layers, n_layers, rows))
+    return forward_decode_wide_bf16(layers, pts, n_layers, X, rows, pattern_id, Y, workspace, s);
+  for (int r0 = 0; r0 < rows; r0 += 32) {
+    const int nb = rows - r0 < 32 ? rows - r0 : 32;
+    uint16_t *Yp[4] = {nullptr, nullptr, nullptr, nullptr};
+    for (int l = 0; l < n_layers; ++l) Yp[l] = (uint16_t *)Y[l] + (size_t)r0 * layers[l].m;
+    const int st = forward_decode_multi_bf16(layers, pts, n_layers, X + (size_t)r0 * layers[0].n, nb, pattern_id + r0, Yp,
+                                             workspace, s);
+    if (st != PARSE_OK) return st;
+  }
+  return PARSE_OK;
+}
 }  // namespace parse
 
 using namespace parse;
@@ -51,7 +74,14 @@ static size_t planned_total_bytes(const parse_layer *L, int rows, int P, int k, 
 size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *L, int32_t rows, int32_t k, int32_t P,
                                      int32_t n_patterns) {
   if (!L || rows <= 0 || k <= 0 || L->G <= 0 || L->R <= 0) return 0;
-  if (mode == PARSE_DECODE) return decode_workspace_bytes(L);
+  if (mode == PARSE_DECODE) {
+    size_t need = decode_workspace_bytes(L);
+    if (rows > 32 && decode_wide_supported(L, 1)) {
+      const size_t wide = decode_wide_workspace_bytes(L, 1, rows);
+      if (wide > need) need = wide;
+    }
+    return need;
+  }
   if (L->dtype == PARSE_F32) return round_up((size_t)rows * k * (L->R / L->G) * sizeof(float), 256);
   const int rS = k * (L->R / L->G);
   size_t need = prefill_split_workspace_bytes(rows, rS);
@@ -113,7 +143,8 @@ int parse_lowrank_forward(int32_t mode, const parse_layer *L, const parse_patter
   if (pt->k > L->G || P > rows) return PARSE_ESHAPE;
   if (!aligned16(X) || !aligned16(Y)) return PARSE_EALIGN;
   if (mode == PARSE_DECODE && (L->dtype != PARSE_BF16 || L->layout != PARSE_MFMA16)) return PARSE_ELAYOUT;
-  const size_t need = parse_lowrank_workspace_bytes(mode, L, rows, pt->k, 0, 0);   // the smallest workspace any schedule takes
+  // the smallest workspace any schedule takes
+  const size_t need = mode == PARSE_DECODE ? decode_workspace_bytes(L) : parse_lowrank_workspace_bytes(mode, L, rows, pt->k, 0, 0);
   // bf16 prefill may run without a workspace (fused kernel only); every other mode needs the queried size
   const bool optional_ws = mode == PARSE_PREFILL && L->dtype == PARSE_BF16 && workspace == nullptr;
   if (!optional_ws && need > 0 && (!workspace || workspace_bytes < need)) return PARSE_EWORKSPACE;
@@ -124,15 +155,8 @@ int parse_lowrank_forward(int32_t mode, const parse_layer *L, const parse_patter
   if (mode == PARSE_DECODE) {
     if (!pt->subsets) return PARSE_EINVAL;
     if (rows != P || L->G > 64 || pt->subset_stride < pt->k) return PARSE_ESHAPE;
-    // panels of 32 sequences (the matrix instruction's N side); every panel has its own masks and streams the groups
-    // its own sequences selected
-    for (int r0 = 0; r0 < rows; r0 += 32) {
-      const int nb = rows - r0 < 32 ? rows - r0 : 32;
-      st = forward_decode_bf16(L, pt, (const uint16_t *)X + (size_t)r0 * L->n, nb, pattern_id + r0,
-                               (uint16_t *)Y + (size_t)r0 * L->m, workspace, s);
-      if (st != PARSE_OK) return st;
-    }
-    return PARSE_OK;
+    void *Yd[1] = {Y};
+    return decode_rows(L, pt, 1, (const uint16_t *)X, rows, pattern_id, Yd, workspace, workspace_bytes, s);
   }
 
   if (!tok_offsets || !pt->Vt_S || !pt->Ut_S) return PARSE_EINVAL;
@@ -155,11 +179,21 @@ int parse_lowrank_forward(int32_t mode, const parse_layer *L, const parse_patter
                               workspace_bytes, s);
 }
 
+static size_t decode_panel_bytes(const parse_layer *layers, int n_layers) {
+  return decode_z_bytes(layers, n_layers) + decode_plan_bytes(n_layers);
+}
+
 size_t parse_lowrank_decode_multi_workspace_bytes(const parse_layer *layers, int32_t n_layers) {
   if (!layers || n_layers < 1 || n_layers > 4) return 0;
   for (int l = 0; l < n_layers; ++l)
     if (layers[l].G <= 0 || layers[l].R <= 0) return 0;
-  return decode_z_bytes(layers, n_layers) + decode_plan_bytes(n_layers);   // the call builds its plan behind the intermediates
+  // a panel at a time: the call builds its plan behind the intermediates; several panels at once: as much as a pass takes
+  size_t need = decode_panel_bytes(layers, n_layers);
+  if (decode_wide_supported(layers, n_layers)) {
+    const size_t wide = decode_wide_workspace_bytes(layers, n_layers, INT32_MAX - 31);
+    if (wide > need) need = wide;
+  }
+  return need;
 }
 
 int parse_lowrank_decode_multi(const parse_layer *layers, const parse_patterns *patterns, int32_t n_layers,
@@ -180,21 +214,11 @@ int parse_lowrank_decode_multi(const parse_layer *layers, const parse_patterns *
     if (pt->k > L->G || L->G > 64 || pt->subset_stride < pt->k || L->n != layers[0].n) return PARSE_ESHAPE;
     if (!aligned16(Y[l])) return PARSE_EALIGN;
   }
-  const size_t need = parse_lowrank_decode_multi_workspace_bytes(layers, n_layers);
-  if (!workspace || workspace_bytes < need) return PARSE_EWORKSPACE;
+  if (!workspace || workspace_bytes < decode_panel_bytes(layers, n_layers)) return PARSE_EWORKSPACE;
   if (!aligned16(workspace)) return PARSE_EALIGN;
-  // panels of 32 sequences, as in parse_lowrank_forward(PARSE_DECODE)
-  for (int r0 = 0; r0 < rows; r0 += 32) {
-    const int nb = rows - r0 < 32 ? rows - r0 : 32;
-    uint16_t *Yp[4] = {nullptr, nullptr, nullptr, nullptr};
-    for (int l = 0; l < n_layers; ++l) Yp[l] = (uint16_t *)Y[l] + (size_t)r0 * layers[l].m;
-    const int st = forward_decode_multi_bf16(layers, patterns, n_layers, (const uint16_t *)X + (size_t)r0 * layers[0].n, nb,
-                                             pattern_id + r0, Yp, workspace, (hipStream_t)stream);
-    if (st != PARSE_OK) return st;
-  }
-  return PARSE_OK;
+  return decode_rows(layers, patterns, n_layers, (const uint16_t *)X, rows, pattern_id, Y, workspace, workspace_bytes,
+                     (hipStream_t)stream);
 }
-
 // checks shared by the decode entry points that take several layers
 static int check_decode_layers(const parse_layer *layers, int32_t n_layers) {
   if (!layers || n_layers < 1) return PARSE_EINVAL;

@@ -1464,3 +1464,49 @@ def test_router_grad_tiles(n, m, R, G, lengths):
     say(f"    gradient {err:.2e}, loss {np.abs(loss.cpu().numpy() / lref - 1).max():.2e}")
     assert err <= 1e-4
     assert np.allclose(loss.cpu().numpy(), lref, rtol=1e-5)
+
+
+@pytest.mark.parametrize("n,shapes,rows", [
+    (256, [(64, 256, 8, 3)], 33),                                       # the smallest layer of this path, a panel of one sequence
+    (272, [(32, 288, 3, 2), (4128, 256, 1, 1)], 64),                    # odd numbers of steps, rank and column blocks; two full panels
+    (2048, [(1088, 320, 10, 2), (96, 1024, 16, 5)], 161),               # six panels, several slices of the reduction
+    (4096, [(8224, 256, 2, 1)], 130),                                   # two column blocks per workgroup, eight slices
+    (512, [(16416, 256, 4, 2), (9248, 256, 8, 8)], 200),                # three column blocks; two passes, the last panel 8 sequences
+])
+def test_decode_many_sequences(n, shapes, rows):
+    """More than 32 sequences in one call: every group in use streamed once for all of them.  Against the oracle, with sequences
+    whose pattern id is out of range (zero rows), groups nobody selected, guards around outputs and workspace; and the same
+    call with the workspace of a single panel, which goes panel after panel."""
+    say(f"decode of {rows} sequences: n={n} {shapes}")
+    rng = np.random.default_rng(1301)
+    x = si.make_tokens(rng, rows, n, "bf16")
+    xv = si.bf16_bits_to_f32(x).astype(np.float64)
+    seq_pat = (np.arange(rows) % 4).astype(np.int32)
+    seq_pat[[1, rows - 1]] = [7, -1]
+    ok = (seq_pat >= 0) & (seq_pat < 3)
+    layers, pats, refs = [], [], []
+    for m, R, G, k in shapes:
+        Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((R, n), (R, m)))
+        sub = np.stack([np.sort(rng.choice(G, size=k, replace=False)) for _ in range(3)]).astype(np.int32)
+        mask = np.zeros((rows, R))
+        for s in np.flatnonzero(ok):
+            for g in sub[seq_pat[s]]:
+                mask[s, g * (R // G):(g + 1) * (R // G)] = 1.0
+        V, U = (si.bf16_bits_to_f32(t).astype(np.float64) for t in (Vt, Ut))
+        refs.append(((xv @ V.T) * mask) @ U)
+        layers.append(pa.layer_to_mfma16(pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, G, pa.PARSE_ROWMAJOR)))
+        pats.append(pa.Patterns(k, 3, subsets=i32(sub)))
+    xd, pid = upload_tokens(x, "bf16"), i32(seq_pat)
+    ys = decode_multi_guarded(layers, pats, xd, pid)
+    again = decode_multi_guarded(layers, pats, xd, pid)
+    y1 = forward_guarded(pa.PARSE_DECODE, layers[0], pats[0], xd, None, pid)
+    small = pa.lowrank_decode_planned_workspace_bytes(layers) + 16384
+    panels = [torch.empty_like(y) for y in ys]
+    pa.lowrank_decode_multi(layers, pats, xd, pid, panels, torch.empty(small, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    for l, ref in enumerate(refs):
+        assert torch.equal(ys[l], again[l])
+        for what, y in (("together", ys[l]), ("panel after panel", panels[l])) + ((("one layer", y1),) if l == 0 else ()):
+            yn = y.float().cpu().numpy().astype(np.float64)
+            assert np.all(yn[~ok] == 0.0), f"layer {l}: rows without a pattern are not zero ({what})"
+            assert_close(yn[ok], ref[ok], TOL_BF16, f"layer {l} {what}")
