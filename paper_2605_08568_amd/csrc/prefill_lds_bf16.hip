@@ -61,25 +61,30 @@ struct LgArgs {
 // TROW: token operand 1 = row-major rows looked up through the plan's row map (X, or a row-major intermediate),
 //       0 = operand order over the plan's virtual rows.   OROW: output 1 = row-major through the row map, 0 = operand order.
 // First product: <FORD 0, TROW 1, OROW 0>; second product: <FORD 1, TROW 0, OROW 1>.
+// WK 2: two wavefronts share an output tile, each takes half of the steps of every slice, and the halves are added at the end
+// through LDS: a tile of 128 x 128 or less then still has eight wavefronts, two per SIMD, whose waits cover each other
+// (4096 rows x 1024 ranks of eight patterns, n = 4096, the first product alone: 43 us with four wavefronts, 30 with
+// eight that also take turns).  PING: see there.
 // SPLIT (first product only): the reduction range is cut in a.ks slices, one workgroup each; a workgroup stores its fp32
 // sums as slice s of the partial sums and z_combine adds the slices (in slice order) and rounds -- for launches whose
 // tiles alone would leave most compute units idle (one short prompt).
-template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1, int PING = 0>
+__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
   static_assert(!SPLIT || (FORD == 0 && OROW == 0), "only the first product is split");
-  constexpr int NW = WM * WN;
+  constexpr int NW = WM * WN * WK;
   constexpr int KK = BK / 16;                 // matrix-instruction steps per staged slice
+  constexpr int KW = KK / WK;                 // ... of one wavefront
   constexpr int TB = BM / WM / 32, FB = BN / WN / 32;
   constexpr int F_BYTES = BN * BK * 2, T_BYTES = BM * BK * 2, STAGE_BYTES = F_BYTES + T_BYTES;
   constexpr int NI_F = F_BYTES / 1024, NI_T = T_BYTES / 1024;   // 1 KiB load instructions per slice
   static_assert(NI_F % NW == 0 && NI_T % NW == 0, "the loads of a slice divide evenly over the wavefronts");
-  static_assert(KK == 2 || KK == 4, "register double-buffering assumes an even number of steps");
+  static_assert(KW == 2 || KW == 4, "register double-buffering assumes an even number of steps");
   static_assert(256 % BM == 0, "token tiles subdivide the plan's 256-row tiles");
   constexpr int LF = NI_F / NW, LT = NI_T / NW, L = LF + LT;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wm = wave / WN, wn = wave % WN;
+  const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
   const int j = lane & 31, q = lane >> 5;
 
   // tile of this workgroup: consecutive ids share a die (and its L2); within a locality group the token tile runs fastest
@@ -121,6 +126,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
     }
     return;
   }
+  // the rows of a pattern come first, its padding last: a tile that starts with padding holds nothing else
+  if (BM < 256 && rowmap[tm * BM] < 0) return;
   const uint16_t *Fp = ly.F + (size_t)pat * ly.pattern_stride;
 
   // ---- per-lane global sources of this wavefront's load instructions; they advance by a constant per slice ----
@@ -219,7 +226,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
       for (int e = 0; e < 16; ++e) acc[t][i][e] = 0.f;
 
   u32x4 fr[2][FB], tr[2][TB];
-  auto read_ops = [&](int buf, int stage_buf, int kk) {
+  auto read_ops = [&](int buf, int stage_buf, int step) {
+    const int kk = wk * KW + step;
     const char *base = smem + stage_buf * STAGE_BYTES;
 #pragma unroll
     for (int i = 0; i < FB; ++i) fr[buf][i] = *reinterpret_cast<const u32x4 *>(base + foff[i] + kk * 1024);
@@ -239,6 +247,56 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
     for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[buf][t]));
   };
 
+  if constexpr (PING) {
+    // The two wavefronts of a SIMD (w and w + 4) take turns: while one issues the matrix instructions of two steps, the other
+    // reads its operands of the next two from LDS and requests a slice; a barrier ends every turn.  Wavefronts 4..7 run one
+    // turn behind.  A buffer is requested into again one turn after its last reads have returned (both groups wait for
+    // their LDS reads before the barrier), and slice kt+1 has landed for everybody one turn before it is first read.
+    static_assert(NW == 8 && KW % 2 == 0, "two wavefronts per SIMD");
+    const int grp = wave / 4;
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s)
+      if (s < nk) issue(s);
+    if (nk >= STAGES - 1) wait_vm<(STAGES - 2) * L>(); else wait_vm<0>();
+    wg_barrier();
+    if (grp == 1) wg_barrier();
+    for (int kt = 0; kt < nk; ++kt) {
+      const int sb = kt % STAGES;
+#pragma unroll
+      for (int sub = 0; sub < KW / 2; ++sub) {
+        const bool last = sub == KW / 2 - 1;
+        __builtin_amdgcn_sched_barrier(0);
+        read_ops(0, sb, sub * 2);
+        read_ops(1, sb, sub * 2 + 1);
+        if (sub == 0 && kt + STAGES - 1 < nk) issue((kt + STAGES - 1) % STAGES);
+        __builtin_amdgcn_sched_barrier(0);
+        auto landed = [&]() {
+          const int later = min(kt + STAGES - 1, nk - 1) - (kt + 1);
+          if (later >= STAGES - 2) wait_vm<(STAGES - 2) * L>();
+          else if (STAGES > 3 && later == 1) wait_vm<L>();
+          else wait_vm<0>();
+        };
+        if (last && grp == 1) landed();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wg_barrier();
+        settle(0); settle(1);
+        __builtin_amdgcn_s_setprio(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int i = 0; i < FB; ++i)
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+              acc[t][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[c][i]), as_bf16x8(tr[c][t]), acc[t][i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(0);
+        if (last && grp == 0) landed();
+        wg_barrier();
+      }
+    }
+    if (grp == 0) wg_barrier();
+  } else {
   // prologue: STAGES-1 slices requested, the first one awaited, one more requested
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s)
@@ -251,11 +309,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
   for (int kt = 0; kt < nk; ++kt) {
     const int sb = kt % STAGES;
 #pragma unroll
-    for (int s = 0; s < KK; ++s) {
+    for (int s = 0; s < KW; ++s) {
       const int cur = s & 1;
       settle(cur);
       __builtin_amdgcn_sched_barrier(0);
-      if (s < KK - 1) {
+      if (s < KW - 1) {
         read_ops(cur ^ 1, sb, s + 1);
       } else if (kt + 1 < nk) {
         // hand-over: slice kt+1 must have landed for every wavefront; slice kt's buffer is free after the barrier
@@ -277,6 +335,29 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
     }
   }
 
+  }
+  if constexpr (WK == 2) {
+    // the two halves of the reduction: each takes half of the accumulators over from the other (the staged slices are dead)
+    float *ex = reinterpret_cast<float *>(smem) + (size_t)(wave % (WM * WN)) * (TB * FB * 1024) + lane;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int i = 0; i < FB; ++i)
+        if ((t * FB + i) * 2 / (TB * FB) != wk) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) ex[((t * FB + i) * 16 + e) * 64] = acc[t][i][e];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int i = 0; i < FB; ++i)
+        if ((t * FB + i) * 2 / (TB * FB) == wk) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[t][i][e] += ex[((t * FB + i) * 16 + e) * 64];
+        }
+  }
   // ---- output: lane (j, q) of acc[t][i] holds token t*32+j, factor rows i*32 + 8*band + 4*q + (0..3) ----
 #pragma unroll
   for (int t = 0; t < TB; ++t) {
@@ -286,6 +367,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
 #pragma unroll
     for (int i = 0; i < FB; ++i) {
       const int gb = tn * (BN / 32) + wn * FB + i;     // 32-row factor block of the whole matrix
+      if (WK == 2 && (t * FB + i) * 2 / (TB * FB) != wk) continue;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         if (SPLIT) {   // the same exchange on the fp32 sums: lane (j, q) ends up with the 8 consecutive factor rows of its token
@@ -327,14 +409,18 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lds(LgArgs a) {
 }
 
 // Adds the ks partial sums of every 16-byte piece of Z (8 consecutive ranks of a token) in slice order and rounds to
-// bf16.  One thread per piece, over the plan's virtual rows (pieces of tiles without a pattern hold nothing and are not
-// read by the second product either).
-__global__ __launch_bounds__(256) void z_combine(const float *__restrict__ Pz, int ks, int cap, int M, const int32_t *__restrict__ plan,
-                                                 uint16_t *__restrict__ Z) {
-  const size_t pieces = (size_t)(plan[1] / 32) * (M / 16) * 64;      // virtual rows / 32 token blocks x reduction blocks x lanes
-  const size_t slice = (size_t)cap * 8 * (M / 16) * 512;             // floats per slice
+// bf16.  One thread per piece, over the plan's virtual rows and all layers of the call (grid.y); padding rows hold nothing
+// and are passed over (the second product's results for them are not stored either).
+__global__ __launch_bounds__(256) void z_combine(LgArgs a) {
+  const LgLayer &ly = a.L[blockIdx.y];
+  const int M = ly.M, ks = a.ks;
+  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  const size_t pieces = (size_t)(a.plan[1] / 32) * (M / 16) * 64;    // virtual rows / 32 token blocks x reduction blocks x lanes
+  const size_t slice = (size_t)a.cap * 8 * (M / 16) * 512;           // floats per slice
   for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < pieces; o += (size_t)gridDim.x * 256) {
-    const float *src = Pz + o * 8;
+    const size_t tb = o / ((size_t)(M / 16) * 64);
+    if (rowmap[tb * 32 + (o & 31)] < 0) continue;
+    const float *src = ly.Pz + o * 8;
     float4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < ks; s0 += 4) {      // four slices requested at a time (slices past the last re-read it)
       float4 l4[4], h4[4];
@@ -352,15 +438,16 @@ __global__ __launch_bounds__(256) void z_combine(const float *__restrict__ Pz, i
         }
       }
     }
-    *reinterpret_cast<u32x4 *>(Z + o * 8) =
+    *reinterpret_cast<u32x4 *>(ly.O + o * 8) =
         u32x4{cvt_pk_bf16(lo.x, lo.y), cvt_pk_bf16(lo.z, lo.w), cvt_pk_bf16(hi.x, hi.y), cvt_pk_bf16(hi.z, hi.w)};
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0>
+template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1, int PING = 0>
 static int launch_gemm_lds(LgArgs a, int avg_tiles_per_pattern, hipStream_t s) {
-  constexpr int smem = STAGES * (BM + BN) * BK * 2;
-  auto kern = gemm_lds<BM, BN, WM, WN, BK, STAGES, FORD, TROW, OROW, SPLIT>;
+  constexpr int staged = STAGES * (BM + BN) * BK * 2, sums = WK > 1 ? BM * BN * 4 : 0;
+  constexpr int smem = staged > sums ? staged : sums;
+  auto kern = gemm_lds<BM, BN, WM, WN, BK, STAGES, FORD, TROW, OROW, SPLIT, WK, PING>;
   static bool attr_done[64] = {false};
   int dev = 0;
   PARSE_HIP_TRY(hipGetDevice(&dev));
@@ -378,17 +465,12 @@ static int launch_gemm_lds(LgArgs a, int avg_tiles_per_pattern, hipStream_t s) {
   int gm = avg_tiles_per_pattern * (256 / BM);
   a.gm = gm < 1 ? 1 : (gm > 8 ? 8 : gm);
   a.ngroups = (ntm + a.gm - 1) / a.gm;
-  hipLaunchKernelGGL(kern, dim3(a.ngroups * a.gm * a.ntn * (SPLIT ? a.ks : 1)), dim3(WM * WN * 64), smem, s, a);
+  hipLaunchKernelGGL(kern, dim3(a.ngroups * a.gm * a.ntn * (SPLIT ? a.ks : 1)), dim3(WM * WN * WK * 64), smem, s, a);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
 
-// Z workspace of the planned form: the plan's capacity in virtual rows x rS bf16 (operand order)
-// Slices of the first product's reduction range (1 = no split): only for batches of at most 1024 token rows (16 tiles
-// of 64 tokens: with the eight or so 128-rank tiles of a selection they leave half of the compute units without a
-// workgroup), as many as bring the token tiles x slices to 32, at most 8, at least 8 staged slices of 64 per workgroup.
-// A function of (rows, n) alone, so that a call over several layers splits exactly like its single-layer calls and
-// gives the same bits.
+// Slices of the first product's reduction range that the workspace has room for (1 = no split).
 int prefill_planned_split(int rows, int n) {
   const int tiles = (rows + 63) / 64;
   if (tiles <= 0 || tiles > 16) return 1;
@@ -396,6 +478,15 @@ int prefill_planned_split(int rows, int n) {
   if (ks > 8) ks = 8;
   if (ks > n / 64 / 8) ks = n / 64 / 8;
   return ks < 2 ? 1 : ks;
+}
+// Slices taken: four for up to 256 token rows with a reduction of 4096 or more, where the tiles alone leave the chip idle
+// (77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7 without; 256 rows
+// 26.8 and 31.5; 512 rows 30.8 and 31.4-33.7; n = 1024 19 and 16.6: the second launch costs what the split gains).  A
+// function of (rows, n) alone, so that a call over several layers splits exactly like its single-layer calls and gives
+// the same bits.
+static int split_slices(int rows, int n) {
+  const int room = prefill_planned_split(rows, n);
+  return rows <= 256 && n >= 4096 ? std::min(4, room) : 1;
 }
 // Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
 // partial sums of its ks slices
@@ -416,52 +507,78 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   g1.n_layers = g2.n_layers = n_layers;
   g1.plan = g2.plan = plan;
   g1.cap = g2.cap = cap;
-  long long ct1 = 0, ct2 = 0;                  // 256-wide column tiles of the two products, all layers
+  bool slices64 = true;                        // the second product can take slices of 64
   for (int l = 0; l < n_layers; ++l) {
     if (p[l].sh_ranks % 32 != 0 || p[l].sh_ranks >= p[l].rS) return PARSE_ESHAPE;
     const int own = p[l].rS - p[l].sh_ranks;   // ranks in a pattern's own block
     g1.L[l] = LgLayer{p[l].X, p[l].Vt_S, Z[l], nullptr, (size_t)own * p[l].n, p[l].n, p[l].rS, p[l].Vt_sh, p[l].sh_ranks / 32, 0};
     g2.L[l] = LgLayer{Z[l], p[l].Ut_S, p[l].Y, nullptr, (size_t)own * p[l].m, p[l].rS, p[l].m, p[l].Ut_sh, p[l].sh_ranks / 32, 0};
-    ct1 += (p[l].rS + 255) / 256;
-    ct2 += (p[l].m + 255) / 256;
+    slices64 = slices64 && p[l].sh_ranks == 0 && p[l].rS % 64 == 0;
   }
-  const long long tiles256 = (long long)((p[0].rows + 255) / 256);
+  const int rows = p[0].rows, P = p[0].P;
   const int per_pattern = avg_prompt_rows / 256;
-  // 256 x 256 tiles halve the bytes a compute unit has to take in per flop; they are used when they still give the
-  // chip enough workgroups, 128 x 128 tiles otherwise (config 1's first product: 64 large tiles or 256 small ones)
-  const bool big1 = tiles256 * ct1 >= 192;
-  const bool big2 = tiles256 * ct2 >= 192;
-  // a product that does not even fill the chip with 128 x 128 tiles (one long prompt through a narrow selection:
-  // 2048 tokens x 1024 ranks are 128 tiles for 256 compute units) takes 64-token tiles: more bytes per flop for a unit,
-  // but twice the units at work
-  long long t128 = 0;
-  for (int l = 0; l < n_layers; ++l) t128 += (long long)((p[0].rows + 127) / 128) * ((p[l].rS + 127) / 128);
-  const bool small1 = !big1 && t128 <= 192;
-  const int ks = small1 ? prefill_planned_split(p[0].rows, p[0].n) : 1;
+  // Token tiles of BM rows, as far as the host can tell: a pattern starts on a tile of its own, so prompts whose lengths are
+  // no multiple of BM leave half a tile unused on average.
+  auto token_tiles = [&](int bm) -> long long {
+    if (P <= 1 || (rows % P == 0 && rows / P % bm == 0)) return (rows + bm - 1) / bm;
+    return ((long long)rows * 2 + (long long)P * bm + 2 * bm - 1) / (2 * bm);
+  };
+  auto tiles1 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].rS + bn - 1) / bn; return t * token_tiles(bm); };
+  auto tiles2 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].m + bn - 1) / bn; return t * token_tiles(bm); };
+  auto rounds = [](long long tiles, int slots) { return (double)((tiles + slots - 1) / slots); };
+
+  // First product: the tile with the smallest (rounds of workgroups) x (time of a round), in units of a round of 128 x 128
+  // tiles, one per compute unit (30 us at K = 4096).  The times per round are measured over 16 shapes of 77 to 57 000 rows
+  // and 512 to 3072 ranks: 256 x 256 2.85, 128 x 256 1.57, 64 x 128 0.6 (two per unit 1.13), 64 x 64 0.45 (two per unit 0.69).
+  // E.g. 2048 rows x 2304 ranks, both products, us: 142 / 110 / 121 / 118 / 118 (taken: 128 x 256); 4096 x 1024 136 / 101 / 86 /
+  // 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024 557 / 587 / 654 / 706 / 776.
+  // Up to SHORT_ROWS rows every tile takes the reduction in two halves (WK 2, slices of 64), beyond it none does: which
+  // tile a call takes depends on the layers it fuses, its bits do not.
+  constexpr int SHORT_ROWS = 6144;
+  const int ks = split_slices(rows, p[0].n);
+  int st;
   if (ks > 1) {      // the partial sums follow each layer's Z in the workspace
     g1.ks = ks;
-    for (int l = 0; l < n_layers; ++l)
+    int most = 0;
+    for (int l = 0; l < n_layers; ++l) {
       g1.L[l].Pz = reinterpret_cast<float *>(reinterpret_cast<char *>(Z[l]) + planned_z_only_bytes(cap, p[l].rS));
-  }
-  long long u128 = 0;                          // the same for the second product
-  for (int l = 0; l < n_layers; ++l) u128 += (long long)((p[0].rows + 127) / 128) * ((p[l].m + 127) / 128);
-  const bool small2 = !big2 && u128 <= 192;
-  int st;
-  if (ks > 1) {
-    st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 1>(g1, per_pattern, s);
-    for (int l = 0; l < n_layers && st == PARSE_OK; ++l) {
-      const size_t pieces = (size_t)cap * 8 * (p[l].rS / 16) * 64;
-      hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048)), dim3(256), 0, s, g1.L[l].Pz, ks, cap,
-                         p[l].rS, plan, Z[l]);
-      PARSE_LAUNCH_CHECK();
+      most = std::max(most, p[l].rS);
     }
-  } else if (big1) st = launch_gemm_lds<256, 256, 2, 2, 32, 4, 0, 1, 0>(g1, per_pattern, s);
-  else if (small1) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);
-  else st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);
+    st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g1, per_pattern, s);
+    if (st != PARSE_OK) return st;
+    const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
+    hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), n_layers), dim3(256), 0, s, g1);
+    PARSE_LAUNCH_CHECK();
+  } else {
+    const long long t64x64 = tiles1(64, 64), t64 = tiles1(64, 128), t128 = tiles1(128, 128);
+    const double c256 = 2.85 * rounds(tiles1(256, 256), 256), c128x256 = 1.57 * rounds(tiles1(128, 256), 256), c128 = rounds(t128, 256);
+    if (rows <= SHORT_ROWS) {
+      const double c64 = t64 <= 256 ? 0.6 : 1.13 * std::max(1.0, (double)t64 / 512 + 0.35);
+      const double c64x64 = t64x64 <= 256 ? 0.45 : t64x64 <= 512 ? 0.69 : 1e9;
+      if (c64x64 <= c64 && c64x64 <= c128) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
+      else if (c64 <= c128 && c64 <= c128x256) st = t64 <= 256 ? launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s)
+                                                               : launch_gemm_lds<64, 128, 2, 2, 64, 3, 0, 1, 0, 0, 2>(g1, per_pattern, s);
+      else if (c128 <= c128x256) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
+      else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
+    } else if (c256 <= c128x256 && c256 <= c128) st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g1, per_pattern, s);
+    else if (c128x256 <= c128) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0, 0, 1, 1>(g1, per_pattern, s);
+    else st = launch_gemm_lds<128, 128, 2, 4, 64, 4, 0, 1, 0>(g1, per_pattern, s);
+  }
   if (st != PARSE_OK) return st;
-  if (big2) return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
-  if (small2) return launch_gemm_lds<64, 128, 2, 2, 32, 4, 1, 0, 1>(g2, per_pattern, s);
-  return launch_gemm_lds<128, 128, 2, 2, 32, 4, 1, 0, 1>(g2, per_pattern, s);
+
+  // Second product: 256 x 256 tiles where they fill exactly one round or many; else 128 x 256, two to a compute unit, whose
+  // stores and starts overlap and whose last round is shorter; smaller tiles as these run out (both products, us, 256 x 256 /
+  // 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
+  // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25).
+  const long long u256 = tiles2(256, 256);
+  if ((u256 > 208 && u256 <= 256) || u256 >= 2048) {
+    if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
+    return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
+  }
+  if (tiles2(128, 256) >= 384) return launch_gemm_lds<128, 256, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
+  if (tiles2(128, 128) >= 384) return launch_gemm_lds<128, 128, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
+  if (slices64 && tiles2(64, 128) <= 256) return launch_gemm_lds<64, 64, 2, 2, 64, 4, 1, 0, 1>(g2, per_pattern, s);
+  return launch_gemm_lds<64, 128, 2, 2, 32, 4, 1, 0, 1>(g2, per_pattern, s);
 }
 
 int forward_prefill_planned_bf16(const PfArgs &p, const int32_t *plan, int cap, uint16_t *Z, int avg_prompt_rows,
