@@ -534,7 +534,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   // 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024 557 / 587 / 654 / 706 / 776.
   // Up to SHORT_ROWS rows every tile takes the reduction in two halves (WK 2, slices of 64), beyond it none does: which
   // tile a call takes depends on the layers it fuses, its bits do not.
-  constexpr int SHORT_ROWS = 6144;
+  constexpr int SHORT_ROWS = 4096;
   const int ks = split_slices(rows, p[0].n);
   int st;
   if (ks > 1) {      // the partial sums follow each layer's Z in the workspace
