@@ -54,6 +54,7 @@ struct LgArgs {
   const int32_t *plan;     // header | tile patterns | row map (plan.hip)
   int cap;                 // plan capacity in 256-row tiles (fixes where the row map starts)
   int ntn, gm, ngroups;    // column tiles (all layers), token tiles per locality group, groups
+  int compact;             // the padding tiles are left out of the numbering (plans of at most 256 tiles of BM rows)
   int ks;                  // SPLIT: slices of the reduction range, one workgroup each
 };
 
@@ -92,13 +93,30 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
   // once, the others are renumbered over the REAL count so that every die gets its share.
   const int per = a.gm * a.ntn;
   const int vrows = a.plan[1];
-  const int n_real = ((vrows + BM - 1) / BM + a.gm - 1) / a.gm * per;
+  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  // a.compact: tiles of nothing but padding (the rows of a pattern come first, its padding last: such a tile starts with it)
+  // are left out of the numbering.  Workgroups are dealt to the dies before anything is known of them; with the padding
+  // numbered, one die can get more tiles than it has compute units while another one's leave at once (20 prompts of 30-640
+  // tokens, 220 of 264 tiles real: the launch took two rounds, 118 us against 82).
+  int n_tiles = (vrows + BM - 1) / BM;
+  unsigned long long real[4];                  // bit l of real[u]: tile 64 u + l holds tokens
+  if (BM < 256 && a.compact) {
+    int cnt = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = u * 64 + lane;
+      real[u] = __ballot(t < a.cap * (256 / BM) && rowmap[min(t, a.cap * (256 / BM) - 1) * BM] >= 0 && t < n_tiles);
+      cnt += __popcll(real[u]);
+    }
+    n_tiles = cnt;
+  }
+  const int n_real = (n_tiles + a.gm - 1) / a.gm * per;
   const int ks = SPLIT ? a.ks : 1;
   const int bid = SPLIT ? (int)blockIdx.x / ks : (int)blockIdx.x, sl = SPLIT ? (int)blockIdx.x % ks : 0;
   if (bid >= n_real) return;
   const int tile = xcd_tile(bid, n_real);
   const int g = tile / per, r = tile % per;
-  const int tm = g * a.gm + r % a.gm;
+  int tm = g * a.gm + r % a.gm;
   int tn = r / a.gm;                           // column tile over all layers of the launch
   int li = 0;
 #pragma unroll
@@ -108,9 +126,21 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
   const int K = ly.K, M = ly.M;
   const int kt0 = SPLIT ? (int)(((long long)(K / BK) * sl) / ks) : 0;           // first slice of BK of this workgroup
   const int nk = (SPLIT ? (int)(((long long)(K / BK) * (sl + 1)) / ks) : K / BK) - kt0;
-  if (tm * BM >= vrows) return;                // the last locality group may be partial
+  if (tm >= n_tiles) return;                   // the last locality group may be partial
+  if (BM < 256 && a.compact) {                 // the tm-th tile that holds tokens
+    int at = tm, found = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int n = __popcll(real[u]);
+      if (at >= 0 && at < n) {                 // uniform
+        const bool is = ((real[u] >> lane) & 1ull) && __popcll(real[u] & ((1ull << lane) - 1ull)) == at;
+        found = u * 64 + __ffsll((unsigned long long)__ballot(is)) - 1;
+      }
+      at -= n;
+    }
+    tm = __builtin_amdgcn_readfirstlane(found);
+  }
   const int32_t *tile_pat = a.plan + 16;
-  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
   const int pat = tile_pat[tm * BM / 256];
   if (pat < 0) {
     // prompts without a valid pattern: the first product has nothing to do, the second one writes zero rows
@@ -126,8 +156,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
     }
     return;
   }
-  // the rows of a pattern come first, its padding last: a tile that starts with padding holds nothing else
-  if (BM < 256 && rowmap[tm * BM] < 0) return;
+  if (BM < 256 && !a.compact && rowmap[tm * BM] < 0) return;
   const uint16_t *Fp = ly.F + (size_t)pat * ly.pattern_stride;
 
   // ---- per-lane global sources of this wavefront's load instructions; they advance by a constant per slice ----
@@ -465,6 +494,7 @@ static int launch_gemm_lds(LgArgs a, int avg_tiles_per_pattern, hipStream_t s) {
   int gm = avg_tiles_per_pattern * (256 / BM);
   a.gm = gm < 1 ? 1 : (gm > 8 ? 8 : gm);
   a.ngroups = (ntm + a.gm - 1) / a.gm;
+  a.compact = BM < 256 && ntm <= 256 && a.compact;
   hipLaunchKernelGGL(kern, dim3(a.ngroups * a.gm * a.ntn * (SPLIT ? a.ks : 1)), dim3(WM * WN * WK * 64), smem, s, a);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
@@ -507,6 +537,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   g1.n_layers = g2.n_layers = n_layers;
   g1.plan = g2.plan = plan;
   g1.cap = g2.cap = cap;
+  g1.compact = g2.compact = p[0].P > 1;        // one prompt has less than a 256-row tile of padding
   bool slices64 = true;                        // the second product can take slices of 64
   for (int l = 0; l < n_layers; ++l) {
     if (p[l].sh_ranks % 32 != 0 || p[l].sh_ranks >= p[l].rS) return PARSE_ESHAPE;
@@ -519,8 +550,9 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   const int per_pattern = avg_prompt_rows / 256;
   // Token tiles of BM rows, as far as the host can tell: a pattern starts on a tile of its own, so prompts whose lengths are
   // no multiple of BM leave half a tile unused on average.
+  auto known = [&](int bm) { return P <= 1 || (rows % P == 0 && rows / P % bm == 0); };
   auto token_tiles = [&](int bm) -> long long {
-    if (P <= 1 || (rows % P == 0 && rows / P % bm == 0)) return (rows + bm - 1) / bm;
+    if (known(bm)) return (rows + bm - 1) / bm;
     return ((long long)rows * 2 + (long long)P * bm + 2 * bm - 1) / (2 * bm);
   };
   auto tiles1 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].rS + bn - 1) / bn; return t * token_tiles(bm); };
@@ -566,12 +598,13 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   }
   if (st != PARSE_OK) return st;
 
-  // Second product: 256 x 256 tiles where they fill exactly one round or many; else 128 x 256, two to a compute unit, whose
+  // Second product: 256 x 256 tiles where they fill their rounds (seven eighths of the last one, or there are many); else 128 x 256, two to a compute unit, whose
   // stores and starts overlap and whose last round is shorter; smaller tiles as these run out (both products, us, 256 x 256 /
   // 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
   // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25).
   const long long u256 = tiles2(256, 256);
-  if ((u256 > 208 && u256 <= 256) || u256 >= 2048) {
+  const bool full = known(256) && (double)u256 >= 0.88 * 256 * rounds(u256, 256);
+  if (full || u256 >= 2048) {
     if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
     return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
   }
