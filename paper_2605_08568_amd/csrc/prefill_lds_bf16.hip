@@ -561,7 +561,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
 
   // First product: the tile with the smallest (rounds of workgroups) x (time of a round), in units of a round of 128 x 128
   // tiles, one per compute unit (30 us at K = 4096).  The times per round are measured over 16 shapes of 77 to 57 000 rows
-  // and 512 to 3072 ranks: 256 x 256 2.85, 128 x 256 1.57, 64 x 128 0.6 (two per unit 1.13), 64 x 64 0.45 (two per unit 0.69).
+  // and 512 to 3072 ranks: 256 x 256 2.85, 128 x 256 1.57, 64 x 128 0.6, 64 x 64 0.45 (two per unit 0.69).
   // E.g. 2048 rows x 2304 ranks, both products, us: 142 / 110 / 121 / 118 / 118 (taken: 128 x 256); 4096 x 1024 136 / 101 / 86 /
   // 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024 557 / 587 / 654 / 706 / 776.
   // Up to SHORT_ROWS rows every tile takes the reduction in two halves (WK 2, slices of 64), beyond it none does: which
@@ -584,23 +584,25 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   } else {
     const long long t64x64 = tiles1(64, 64), t64 = tiles1(64, 128), t128 = tiles1(128, 128);
     const double c256 = 2.85 * rounds(tiles1(256, 256), 256), c128x256 = 1.57 * rounds(tiles1(128, 256), 256), c128 = rounds(t128, 256);
+    const double c64 = t64 <= 256 ? 0.6 : 1e9;         // more of them than one round lose to 128 x 256
+    const double c64x64 = t64x64 <= 256 ? 0.45 : t64x64 <= 512 ? 0.69 : 1e9;
+    const bool by64x64 = c64x64 <= std::min(c64, std::min(c128, c128x256)), by64 = c64 <= std::min(c128, c128x256);
     if (rows <= SHORT_ROWS) {
-      const double c64 = t64 <= 256 ? 0.6 : 1.13 * std::max(1.0, (double)t64 / 512 + 0.35);
-      const double c64x64 = t64x64 <= 256 ? 0.45 : t64x64 <= 512 ? 0.69 : 1e9;
-      if (c64x64 <= c64 && c64x64 <= c128) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
-      else if (c64 <= c128 && c64 <= c128x256) st = t64 <= 256 ? launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s)
-                                                               : launch_gemm_lds<64, 128, 2, 2, 64, 3, 0, 1, 0, 0, 2>(g1, per_pattern, s);
+      if (by64x64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
+      else if (by64) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
       else if (c128 <= c128x256) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
       else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
-    } else if (c256 <= c128x256 && c256 <= c128) st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g1, per_pattern, s);
+    } else if (by64x64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);      // many rows, few ranks
+    else if (by64) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);
+    else if (c256 <= c128x256 && c256 <= c128) st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g1, per_pattern, s);
     else if (c128x256 <= c128) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0, 0, 1, 1>(g1, per_pattern, s);
     else st = launch_gemm_lds<128, 128, 2, 4, 64, 4, 0, 1, 0>(g1, per_pattern, s);
   }
   if (st != PARSE_OK) return st;
 
-  // Second product: 256 x 256 tiles where they fill their rounds (seven eighths of the last one, or there are many); else 128 x 256, two to a compute unit, whose
-  // stores and starts overlap and whose last round is shorter; smaller tiles as these run out (both products, us, 256 x 256 /
-  // 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
+  // Second product: 256 x 256 tiles where their number is known and they fill their rounds, or there are many; else 128 x 256,
+  // two to a compute unit, whose stores and starts overlap and whose last round is shorter; smaller tiles as these run out
+  // (both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
   // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25).
   const long long u256 = tiles2(256, 256);
   const bool full = known(256) && (double)u256 >= 0.88 * 256 * rounds(u256, 256);

@@ -1510,3 +1510,64 @@ def test_decode_many_sequences(n, shapes, rows):
             yn = y.float().cpu().numpy().astype(np.float64)
             assert np.all(yn[~ok] == 0.0), f"layer {l}: rows without a pattern are not zero ({what})"
             assert_close(yn[ok], ref[ok], TOL_BF16, f"layer {l} {what}")
+
+
+@pytest.mark.parametrize("n,m,rS,lengths", [
+    # first product up to 4096 rows: 64 x 64, 64 x 128, 128 x 128, 128 x 256 tiles (the second one: 64 x 64, 64 x 128, 128 x 256, 128 x 128)
+    (64, 96, 32, [1]),
+    (192, 512, 256, [40, 1, 64, 90, 65]),
+    (128, 1280, 768, [2048]),
+    (128, 2080, 1024, [700, 1, 129, 1000, 127, 128, 900]),
+    (64, 3072, 2304, [2000]),
+    # ... beyond: 64 x 64, 64 x 128, 128 x 128, 128 x 256, 256 x 256
+    (128, 96, 128, [1500, 2800, 1]),
+    (192, 160, 384, [4200]),
+    (64, 64, 768, [64, 4097, 300]),
+    (64, 64, 1792, [4200]),
+    (128, 64, 2048, [4300]),
+    # second product: 256 x 256 tiles with slices of 64 and of 32
+    (64, 4096, 64, [4096]),
+    (64, 4096, 96, [2048, 2048]),
+    # up to 256 rows with a long reduction: slices, added by a second launch
+    (4096, 128, 96, [77]),
+    (4160, 64, 64, [3, 1, 130]),
+])
+def test_prefill_planned_tiles(n, m, rS, lengths):
+    """Every tile the planned products choose from, with prompts that leave tiles of nothing but padding between them and a prompt
+    without a pattern; and two layers in one call give the bits of their own calls."""
+    say(f"planned tiles n={n} m={m} rS={rS} lengths={lengths}")
+    rng = np.random.default_rng(1401)
+    off = si.offsets_from_lengths(lengths)
+    rows, P = int(off[-1]), len(lengths)
+    bits = lambda r, c, s: si.f32_to_bf16_bits((rng.standard_normal((r, c)) * s).astype(np.float32))      # noqa: E731
+    val = lambda b: si.bf16_bits_to_f32(b).astype(np.float64)                                              # noqa: E731
+    X, pid = bits(rows, n, 1.0), np.arange(P, dtype=np.int32)
+    if P > 2:
+        pid[P - 2] = -1
+    layers, pats, refs = [], [], []
+    for _ in range(2):
+        Vt, Ut = bits(2 * rS, n, n ** -0.5), bits(2 * rS, m, rS ** -0.5)
+        rm = pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, 2 * rS, 2, pa.PARSE_ROWMAJOR)
+        subs = (np.arange(P) % 2).astype(np.int32)[:, None]
+        layer = pa.layer_to_mfma16(rm)
+        Vs, Us = pa.pack_patterns(layer, i32(subs), 1, 1, None, None, P)
+        pats.append(pa.Patterns(1, P, Vs, Us)); layers.append(layer)
+        ref = np.zeros((rows, m))
+        for p in range(P):
+            if pid[p] >= 0:
+                g = slice(int(subs[p, 0]) * rS, (int(subs[p, 0]) + 1) * rS)
+                ref[off[p]:off[p + 1]] = (val(X[off[p]:off[p + 1]]) @ val(Vt[g]).T) @ val(Ut[g])
+        refs.append(ref)
+    Xd, offd, pidd = upload_tokens(X, "bf16"), i32(off), i32(pid)
+    both = prefill_multi_guarded(layers, pats, Xd, offd, pidd)
+    for l in range(2):
+        y = forward_guarded(pa.PARSE_PREFILL, layers[l], pats[l].with_schedule(pa.PARSE_SCHED_PLANNED), Xd, offd, pidd)
+        torch.cuda.synchronize()
+        yn = y.float().cpu().numpy().astype(np.float64)
+        for p in range(P):
+            a, b = off[p], off[p + 1]
+            if pid[p] < 0:
+                assert np.all(yn[a:b] == 0.0)
+            else:
+                assert_close(yn[a:b], refs[l][a:b], TOL_BF16, f"layer {l} prompt {p}")
+        assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in a call of two"
