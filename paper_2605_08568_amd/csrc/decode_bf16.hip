@@ -691,6 +691,172 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// decode_z16 / decode_y16: five to sixteen sequences (a small server), on the 16x16x32 matrix instruction.  The 32-wide
+// kernels leave half of their N side empty there, own 32 ranks or columns per workgroup (too few workgroups: a 4096-column
+// layer has 128 column blocks for 256 units) and stage x through LDS behind barriers.  Here the M side is 16 ranks or
+// columns: in the operand order 16 rows x 32 reduction indices are four runs of 256 bytes, a wavefront instruction reads
+// whole lines, every line once in the launch.  Everything goes straight from memory into registers -- also x, row-major,
+// sixteen rows x 64 bytes per instruction, as many bytes as the factor and mostly from the die's L2 -- the eight wavefronts
+// of a workgroup split the reduction and share nothing until their sums meet in LDS.  No slices of the reduction, so no
+// partial sums in memory and no tickets.  Same rounding points, plan and workspace as the other decode kernels.
+// Bound by what a unit takes in and by the launches' latency.  A 4096 x 11008 block
+// of twelve sequences 93 us a step, 103 with the 32-wide kernels; its MLP of four 61 us, 90 on the vector units.
+typedef __attribute__((ext_vector_type(4))) float f32x4_acc;
+constexpr int D16_WAVES = 8, D16_THREADS = D16_WAVES * 64, D16_MAXB = 16;
+
+// DEPTH: steps of 32 columns a wavefront has in flight -- its whole share where that is up to 16 (n = 4096); requests past the
+// share repeat its last one, so short reductions take fewer (six calls of 1024 columns, twelve sequences: 46 us with 16, 42 with 10)
+template <int DEPTH>
+__global__ __launch_bounds__(D16_THREADS) void decode_z16(DecArgs a) {
+  int li = 0;
+#pragma unroll
+  for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].z_first) ? 1 : 0;
+  const DecLayer &ly = a.L[li];
+  const int b16 = blockIdx.x - ly.z_first;             // 16 ranks = one reduction block of the second product
+  const int n = a.n, B = a.B;
+  const uint32_t mask = (uint32_t)ly.plan[65 + (b16 * 16) / ly.gs];
+  if (mask == 0u) return;
+  __shared__ float red[D16_WAVES][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int r = lane & 15, kq = lane >> 4;             // row of the 16 (rank / sequence), 8 reduction indices of the 32
+  const int nkb = n / 16, steps = (nkb + 1) / 2;
+  const int s0 = (steps * wave) / D16_WAVES, cnt = (steps * (wave + 1)) / D16_WAVES - s0;
+  const char *V = (const char *)ly.Vt + (size_t)(b16 >> 1) * nkb * 1024 + ((kq & 1) * 32 + (b16 & 1) * 16 + r) * 16;
+  const char *X = (const char *)a.x + (size_t)min(r, B - 1) * n * 2 + (kq & 1) * 16;
+  f32x4_acc acc = {0.f, 0.f, 0.f, 0.f};
+  u32x4 vr[DEPTH], xr[DEPTH];
+  auto request = [&](int d, int s) {                   // the second half of an odd last step re-reads the last block
+    const int kb = min((s0 + s) * 2 + (kq >> 1), nkb - 1);
+    vr[d] = *reinterpret_cast<const u32x4 *>(V + (size_t)kb * 1024);
+    xr[d] = *reinterpret_cast<const u32x4 *>(X + (size_t)kb * 32);
+  };
+  auto product = [&](int d, int s) {
+    const u32x4 zero = {0, 0, 0, 0};
+    const bool on = (s0 + s) * 2 + (kq >> 1) < nkb;
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vr[d]), dec_bf16x8(on ? xr[d] : zero), acc, 0, 0, 0);
+  };
+  if (cnt > 0) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) request(d, min(d, cnt - 1));
+    int s = 0;
+    for (; s + DEPTH < cnt; s += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        __builtin_amdgcn_sched_barrier(0);
+        product(d, s + d);
+        request(d, min(s + d + DEPTH, cnt - 1));
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + d < cnt) product(d, s + d);              // uniform
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wave][e][lane] = acc[e];
+  __syncthreads();
+  // lane (sequence c, g) of the sums holds ranks 4g..4g+3; thread (q, j) stores ranks 8q..8q+7 of sequence j, zeros where the
+  // sequence did not select the group
+  if (threadIdx.x < 64) {
+    const int q = lane >> 5, j = lane & 31;
+    u32x4 out = {0, 0, 0, 0};
+    if (j < B && ((mask >> j) & 1u)) {
+      float z[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int ln = (2 * q + (e >> 2)) * 16 + j;
+        z[e] = red[0][e & 3][ln];
+#pragma unroll
+        for (int w = 1; w < D16_WAVES; ++w) z[e] += red[w][e & 3][ln];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = cvt_pk_bf16(z[2 * e], z[2 * e + 1]);
+    }
+    *reinterpret_cast<u32x4 *>((char *)ly.zf + (size_t)b16 * 1024 + lane * 16) = out;
+  }
+}
+
+// NC blocks of 16 columns per workgroup; wavefront w takes every eighth 32-rank block in use.
+template <int NC>
+__global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
+  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : (NC == 4 ? 8 : 6));
+  int li = 0;
+#pragma unroll
+  for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].y_first) ? 1 : 0;
+  const DecLayer &ly = a.L[li];
+  const int B = a.B, m = ly.m;
+  const int c0 = ((int)blockIdx.x - ly.y_first) * NC, ncb = m / 32;
+  __shared__ float red[D16_WAVES][NC][4][64];
+  __shared__ int32_t rb_list[DY_MAXKB / 2];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int r = lane & 15, kq = lane >> 4;
+  const int bpg = ly.gs / 32;
+  const int total = max(0, min(ly.plan[0], ly.G)) * bpg;           // 32-rank blocks in use
+  for (int i = threadIdx.x; i < total; i += D16_THREADS) rb_list[i] = max(ly.plan[1 + i / bpg], 0) * bpg + i % bpg;
+  __syncthreads();
+  const int cnt = (total - wave + D16_WAVES - 1) / D16_WAVES;
+  const char *U = (const char *)ly.Ut + (size_t)(kq >> 1) * ncb * 1024 + ((kq & 1) * 32 + r) * 16;
+  const char *Z = (const char *)ly.zf + (kq >> 1) * 1024 + ((kq & 1) * 32 + r) * 16;
+  int coff[NC];                                                    // blocks past the end re-read the last one (not stored)
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int c = min(c0 + i, ncb * 2 - 1);
+    coff[i] = (c >> 1) * 1024 + (c & 1) * 256;
+  }
+  f32x4_acc acc[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) acc[i] = f32x4_acc{0.f, 0.f, 0.f, 0.f};
+  u32x4 ur[DEPTH][NC], zr[DEPTH];
+  auto request = [&](int d, int s) {
+    const int rb = rb_list[wave + s * D16_WAVES];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) ur[d][i] = *reinterpret_cast<const u32x4 *>(U + (size_t)rb * 2 * ncb * 1024 + coff[i]);
+    zr[d] = *reinterpret_cast<const u32x4 *>(Z + (size_t)rb * 2048);
+  };
+  if (cnt > 0) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) request(d, min(d, cnt - 1));
+    int s = 0;
+    for (; s + DEPTH < cnt; s += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(ur[d][i]), dec_bf16x8(zr[d]), acc[i], 0, 0, 0);
+        request(d, min(s + d + DEPTH, cnt - 1));
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + d < cnt) {                                           // uniform
+#pragma unroll
+        for (int i = 0; i < NC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(ur[d][i]), dec_bf16x8(zr[d]), acc[i], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][i][e][lane] = acc[i][e];
+  __syncthreads();
+  // thread (column block, g, sequence): columns 4g..4g+3, sums in wavefront order
+  for (int t = threadIdx.x; t < NC * 64; t += D16_THREADS) {
+    const int i = t >> 6, ln = t & 63, seq = ln & 15;
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      y[e] = red[0][i][e][ln];
+#pragma unroll
+      for (int w = 1; w < D16_WAVES; ++w) y[e] += red[w][i][e][ln];
+    }
+    if (seq < B && c0 + i < ncb * 2)
+      *reinterpret_cast<u32x2 *>(ly.y + (size_t)seq * m + (c0 + i) * 16 + (ln >> 4) * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
+  }
+}
+
 // workspace of one layer: z in operand order (R/16 operands of 1 KiB), then the partial sums of decode_zr
 static size_t dec_zf_bytes(const parse_layer *L) { return round_up((size_t)(L->R / 16) * 1024, 256); }
 // decode_zr takes reductions of up to DR_MAX_KS slices of 8 * DR_MAXK steps (n <= 65536) and layers of up to DEC_TICKETS
@@ -798,7 +964,13 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   }
   const int nkb = a.n / 16;
   const int NB = B <= 1 ? 1 : (B <= 2 ? 2 : 4);
-  if (B <= DV_MAXB && (size_t)NB * a.n * 2 <= (size_t)DV_XBYTES) {
+  // Which kernel makes z (us a launch, vector / 16-wide / 32-wide).  One sequence: vector.  Two to four: vector while x is short
+  // (2 x 2048: 4.7 / 5.5, 2 x 4096 11.0 / 8.0, 4 x 1024 4.6 / 5.7, 4 x 4096 13.2 / 8.8, 4 x 11008 19 / 14 / 16).  Up to sixteen:
+  // 16-wide, until x, which every workgroup reads whole, outweighs the factor on long reductions (12 x 4096: - / 9.7 / 13.7, 12 x
+  // 1024 - / 6.8 / 7.8, 12 x 11008 - / 18 / 16).
+  const bool zv = B <= DV_MAXB && (size_t)NB * a.n * 2 <= (size_t)DV_XBYTES && (B == 1 || NB * a.n <= 6144);
+  const bool z16 = !zv && B <= D16_MAXB && (a.n <= 4096 || (long long)B * a.n <= 60000);
+  if (zv) {
     // a handful of sequences: eight ranks per workgroup on the vector units, no split of the reduction range
     zb = 0;
     for (int l = 0; l < n_layers; ++l) { a.L[l].z_first = zb; zb += (layers[l].R / 32) * (32 / DV_JW); }
@@ -813,6 +985,14 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
       PARSE_ALLOW_LDS(decode_zv<4>, lds);
       hipLaunchKernelGGL(decode_zv<4>, dim3(zb), dim3(DV_THREADS), lds, s, a);
     }
+  } else if (z16) {
+    zb = 0;
+    for (int l = 0; l < n_layers; ++l) { a.L[l].z_first = zb; zb += layers[l].R / 16; }
+    const int share = ((nkb + 1) / 2 + D16_WAVES - 1) / D16_WAVES;       // steps of a wavefront
+    if (share <= 4) hipLaunchKernelGGL(decode_z16<4>, dim3(zb), dim3(D16_THREADS), 0, s, a);
+    else if (share <= 8) hipLaunchKernelGGL(decode_z16<8>, dim3(zb), dim3(D16_THREADS), 0, s, a);
+    else if (share <= 12) hipLaunchKernelGGL(decode_z16<12>, dim3(zb), dim3(D16_THREADS), 0, s, a);
+    else hipLaunchKernelGGL(decode_z16<16>, dim3(zb), dim3(D16_THREADS), 0, s, a);
   } else {
     const bool two = (nkb + KS - 1) / KS > DR_HALF_KB;     // the longest slice needs two stagings of x
     if (two) hipLaunchKernelGGL(decode_zr<true>, dim3(zb), dim3(DR_THREADS), 0, s, a);
@@ -822,7 +1002,11 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   size_t max_kb = 0;
   for (int l = 0; l < n_layers; ++l) max_kb = std::max(max_kb, (size_t)layers[l].R / 16);
   const size_t zs_bytes = max_kb * 2 * NB * 16;            // z pieces of every reduction block a layer has
-  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES) {
+  // ... and which one y: the vector units up to four sequences while there is little to do (sequences x columns x stored ranks;
+  // 13 M 5.0 / 5.8, 25 M 8.0 / 6.6, 46 M 10.1 / 7.3 vector / 16-wide), 16-wide up to sixteen (4096 columns 6.4, 32-wide 8.1)
+  long long y_work = 0;
+  for (int l = 0; l < n_layers; ++l) y_work += (long long)NB * layers[l].m * layers[l].R;
+  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES && (B == 1 || y_work <= (16ll << 20))) {
     // a handful of sequences: z as a few values per rank in LDS, the launch streams only Ut.  16 columns per workgroup
     // unless that makes more than about four workgroups per compute unit
     int cols = 0;
@@ -839,6 +1023,22 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
     else if (NB == 2) { if (CG == 2) PARSE_YV(2, 2); else PARSE_YV(2, 4); }
     else { if (CG == 2) PARSE_YV(4, 2); else PARSE_YV(4, 4); }
 #undef PARSE_YV
+  } else if (B <= D16_MAXB) {
+    // 16-column blocks per workgroup: the fewest that make one round of workgroups
+    const int choices[] = {1, 2, 3, 4, 6};
+    int nc16 = 6;
+    for (int c : choices) {
+      int wgs = 0;
+      for (int l = 0; l < n_layers; ++l) wgs += (layers[l].m / 16 + c - 1) / c;
+      if (wgs <= n_cu) { nc16 = c; break; }
+    }
+    yb = 0;
+    for (int l = 0; l < n_layers; ++l) { a.L[l].y_first = yb; yb += (layers[l].m / 16 + nc16 - 1) / nc16; }
+    if (nc16 == 1) hipLaunchKernelGGL(decode_y16<1>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else if (nc16 == 2) hipLaunchKernelGGL(decode_y16<2>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else if (nc16 == 3) hipLaunchKernelGGL(decode_y16<3>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else if (nc16 == 4) hipLaunchKernelGGL(decode_y16<4>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else hipLaunchKernelGGL(decode_y16<6>, dim3(yb), dim3(D16_THREADS), 0, s, a);
   } else if (NC == 1) hipLaunchKernelGGL(decode_y<1>, dim3(yb), dim3(DY_THREADS), 0, s, a);
   else if (NC == 2) hipLaunchKernelGGL(decode_y<2>, dim3(yb), dim3(DY_THREADS), 0, s, a);
   else if (NC == 3) hipLaunchKernelGGL(decode_y<3>, dim3(yb), dim3(DY_THREADS), 0, s, a);

@@ -1571,3 +1571,47 @@ def test_prefill_planned_tiles(n, m, rS, lengths):
             else:
                 assert_close(yn[a:b], refs[l][a:b], TOL_BF16, f"layer {l} prompt {p}")
         assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in a call of two"
+
+
+@pytest.mark.parametrize("n,shapes,B", [
+    (16, [(32, 32, 1, 1)], 5),                                       # one reduction step of half an instruction
+    (496, [(64, 96, 3, 2), (416, 256, 4, 3)], 16),                   # odd number of 16-column steps; full instruction
+    (2064, [(1056, 320, 10, 4)], 11),                                # a batch of nine steps; three columns blocks left over
+    (4096, [(4096, 256, 4, 2), (8256, 128, 2, 1)], 3),               # both products 16-wide for three sequences, several blocks per workgroup
+    (4112, [(32, 224, 7, 3)], 14),                                   # more steps than are in flight at once
+    (5648, [(96, 64, 2, 2)], 13),                                    # long reduction: first product 32-wide, second 16-wide
+    (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # first product on the vector units, second 16-wide, six blocks
+])
+def test_decode_few_sequences_tiles(n, shapes, B):
+    """Two to sixteen sequences at the edges of the 16-wide decode kernels and where the choice of kernels changes, against the
+    oracle's product; planned calls over a ready plan give the same bits."""
+    say(f"decode of {B} sequences: n={n} {shapes}")
+    rng = np.random.default_rng(1501)
+    x = si.make_tokens(rng, B, n, "bf16")
+    xv = si.bf16_bits_to_f32(x).astype(np.float64)
+    seq_pat = (np.arange(B) % 3).astype(np.int32)
+    seq_pat[B - 1] = -1
+    layers, pats, refs = [], [], []
+    for m, R, G, k in shapes:
+        Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((R, n), (R, m)))
+        sub = np.stack([np.sort(rng.choice(G, size=k, replace=False)) for _ in range(3)]).astype(np.int32)
+        mask = np.zeros((B, R))
+        for s in range(B - 1):
+            for g in sub[seq_pat[s]]:
+                mask[s, g * (R // G):(g + 1) * (R // G)] = 1.0
+        V, U = (si.bf16_bits_to_f32(t).astype(np.float64) for t in (Vt, Ut))
+        refs.append(((xv @ V.T) * mask) @ U)
+        layers.append(pa.layer_to_mfma16(pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, G, pa.PARSE_ROWMAJOR)))
+        pats.append(pa.Patterns(k, 3, subsets=i32(sub)))
+    xd, pid = upload_tokens(x, "bf16"), i32(seq_pat)
+    ys = decode_multi_guarded(layers, pats, xd, pid)
+    plan = pa.decode_plan(layers, pats, pid)
+    yp = [torch.empty_like(y) for y in ys]
+    pa.lowrank_decode_planned(layers, xd, plan, yp,
+                              torch.empty(pa.lowrank_decode_planned_workspace_bytes(layers), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    for l, ref in enumerate(refs):
+        yn = ys[l].float().cpu().numpy().astype(np.float64)
+        assert np.all(yn[B - 1] == 0.0)
+        assert_close(yn[:B - 1], ref[:B - 1], TOL_BF16, f"layer {l}")
+        assert torch.equal(ys[l].view(torch.int16), yp[l].view(torch.int16))
