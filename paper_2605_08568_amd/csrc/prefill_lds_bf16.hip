@@ -509,14 +509,15 @@ int prefill_planned_split(int rows, int n) {
   if (ks > n / 64 / 8) ks = n / 64 / 8;
   return ks < 2 ? 1 : ks;
 }
-// Slices taken: four for up to 256 token rows with a reduction of 4096 or more, where the tiles alone leave the chip idle
+// Slices taken: up to four for at most 256 token rows with a reduction of 4096 or more, where the tiles alone leave the chip idle
 // (77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7 without; 256 rows
-// 26.8 and 31.5; 512 rows 30.8 and 31.4-33.7; n = 1024 19 and 16.6: the second launch costs what the split gains).  A
+// 26.8 and 31.5; 512 rows 30.8 and 31.4-33.7; n = 1024 19 and 16.6: the second launch costs what the split gains), and up to 512
+// rows with longer ones (488 rows, n = 5632 27 and 40, n = 11008 51 and 70; 640 rows 69 and 70).  A
 // function of (rows, n) alone, so that a call over several layers splits exactly like its single-layer calls and gives
 // the same bits.
 static int split_slices(int rows, int n) {
   const int room = prefill_planned_split(rows, n);
-  return rows <= 256 && n >= 4096 ? std::min(4, room) : 1;
+  return (rows <= 256 && n >= 4096) || (rows <= 512 && n >= 5120) ? std::min(4, room) : 1;
 }
 // Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
 // partial sums of its ks slices
@@ -548,16 +549,23 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   }
   const int rows = p[0].rows, P = p[0].P;
   const int per_pattern = avg_prompt_rows / 256;
-  // Token tiles of BM rows, as far as the host can tell: a pattern starts on a tile of its own, so prompts whose lengths are
-  // no multiple of BM leave half a tile unused on average.
-  auto known = [&](int bm) { return P <= 1 || (rows % P == 0 && rows / P % bm == 0); };
+  // Token tiles of BM rows, as far as the host can tell: a pattern starts on a tile of its own, so patterns whose rows are no
+  // multiple of BM leave half a tile unused on average.  Up to n_patterns prompts may each have their own; more prompts share,
+  // and half of the slots is taken for the number in use.
+  const int groups = P <= p[0].n_patterns ? P : (p[0].n_patterns + 1) / 2;
+  const bool even = rows % P == 0 && groups == P;
   auto token_tiles = [&](int bm) -> long long {
-    if (known(bm)) return (rows + bm - 1) / bm;
-    return ((long long)rows * 2 + (long long)P * bm + 2 * bm - 1) / (2 * bm);
+    if (even) return (long long)P * ((rows / P + bm - 1) / bm);      // prompts of one length, most likely
+    return ((long long)rows * 2 + (long long)groups * bm + 2 * bm - 1) / (2 * bm);
   };
   auto tiles1 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].rS + bn - 1) / bn; return t * token_tiles(bm); };
   auto tiles2 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].m + bn - 1) / bn; return t * token_tiles(bm); };
-  auto rounds = [](long long tiles, int slots) { return (double)((tiles + slots - 1) / slots); };
+  // rounds of workgroups; an estimate that is a tenth of a round over a whole number is taken for it (prompts that share a
+  // pattern leave fewer half tiles)
+  auto rounds = [&](long long tiles, int slots) {
+    const long long slack = even ? 0 : slots / 10;
+    return (double)std::max<long long>(1, (tiles - slack + slots - 1) / slots);
+  };
 
   // First product: the tile with the smallest (rounds of workgroups) x (time of a round), in units of a round of 128 x 128
   // tiles, one per compute unit (30 us at K = 4096).  The times per round are measured over 16 shapes of 77 to 57 000 rows
@@ -600,12 +608,12 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   }
   if (st != PARSE_OK) return st;
 
-  // Second product: 256 x 256 tiles where their number is known and they fill their rounds, or there are many; else 128 x 256,
+  // Second product: 256 x 256 tiles where their number is as good as known and they fill their rounds, or there are many; else 128 x 256,
   // two to a compute unit, whose stores and starts overlap and whose last round is shorter; smaller tiles as these run out
   // (both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
   // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25).
   const long long u256 = tiles2(256, 256);
-  const bool full = known(256) && (double)u256 >= 0.88 * 256 * rounds(u256, 256);
+  const bool full = even && (double)u256 >= 0.88 * 256 * rounds(u256, 256);
   if (full || u256 >= 2048) {
     if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
     return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
