@@ -262,14 +262,14 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *layer, int
  *                  X device [rows][n], Y device [rows][m] (layer dtype), tok_offsets device int32 [P+1],
  *                  pattern_id device int32 [P].
  * PARSE_DECODE   one token per sequence (rows == P, tok_offsets ignored, may be NULL), bf16 PARSE_MFMA16
- *                layers only.  Sequences are taken in panels of 32 (the N side of the matrix instruction): rows > 32
- *                costs one pass over the selected groups per panel, and a group is streamed for a panel only if one
- *                of that panel's sequences selected it.  Per panel: streams every group that some sequence selected exactly
- *                once from the layer's own store (layer->Vt / layer->Ut, not the packed copies) and applies
- *                it to the sequences whose pattern holds it (Sec. 4.3, rank reuse: pattern_id is fixed
- *                at prefill).  Bandwidth-bound.  A panel of one to four sequences is computed on the vector
- *                units with a finer split of the work (same rounding points: z and y to bf16, fp32 sums); a
- *                sequence's result may therefore differ in rounding between a small and a large panel.
+ *                layers only.  Streams every group that some sequence selected from the layer's own store (layer->Vt /
+ *                layer->Ut, not the packed copies) and applies it to the sequences whose pattern holds it (Sec. 4.3, rank
+ *                reuse: pattern_id is fixed at prefill): once for up to 192 sequences when the workspace has the queried
+ *                size, once per panel of 32 sequences (the N side of the matrix instruction) with the workspace of a single
+ *                panel.  Bandwidth-bound.  The kernels are chosen by the number of sequences (vector units for one and some
+ *                calls of two to four, 16-wide matrix instructions up to sixteen, 32-wide beyond, several panels at once
+ *                above 32; same rounding points everywhere: z and y to bf16, fp32 sums), so a sequence's result may differ in
+ *                rounding between a small and a large call.
  * workspace: device, >= parse_lowrank_workspace_bytes(mode, layer, rows, k, P, n_patterns) bytes (optional for
  *            bf16 prefill). */
 int parse_lowrank_forward(int32_t mode, const parse_layer *layer, const parse_patterns *patterns,

@@ -18,9 +18,10 @@
 //              the second product.
 //   decode_y   NC (1..4) 32-column output blocks per workgroup; the eight wavefronts split the used reduction blocks,
 //              all Ut operands requested up front; LDS reduction in wavefront order.
-// A handful of sequences (B <= 4) take decode_zv / decode_yv instead: the same two products on the vector units with a
-// finer split of the work (eight ranks, sixteen or thirty-two columns per workgroup), because one to four sequences
-// leave the matrix instruction's 32-wide N side and most 32-rank workgroups idle.
+// Up to sixteen sequences leave half or more of the 32-wide N side empty and take other kernels with a finer split of the
+// work: decode_z16 / decode_y16 (16 x 16 x 32 matrix instructions, sixteen ranks or columns per workgroup), and one to four
+// sequences with little to do decode_zv / decode_yv on the vector units (eight ranks, sixteen or thirty-two columns).  More than
+// 32 sequences: decode_wide_bf16.hip.
 // Horizontal fusion (Sec. 4.4, Eq. 11-12): up to DEC_MAX_LAYERS layers that read the SAME x (Q/K/V, gate/up) go
 // through the same two launches together -- each launch's grid is the concatenation of the layers' task lists.
 // No floating-point atomics; the summation order is fixed: same inputs, same bits.
