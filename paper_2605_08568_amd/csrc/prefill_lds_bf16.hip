@@ -64,8 +64,8 @@ struct LgArgs {
 // First product: <FORD 0, TROW 1, OROW 0>; second product: <FORD 1, TROW 0, OROW 1>.
 // WK 2: two wavefronts share an output tile, each takes half of the steps of every slice, and the halves are added at the end
 // through LDS: a tile of 128 x 128 or less then still has eight wavefronts, two per SIMD, whose waits cover each other
-// (4096 rows x 1024 ranks of eight patterns, n = 4096, the first product alone: 43 us with four wavefronts, 30 with
-// eight that also take turns).  PING: see there.
+// (4096 rows x 1024 ranks of eight patterns, n = 4096: both products 97 us with four wavefronts, 82-86 with eight that also
+// take turns, inputs hot; inside a step, inputs cold, the first product 43.3 and 40.6 us).  PING: see there.
 // SPLIT (first product only): the reduction range is cut in a.ks slices, one workgroup each; a workgroup stores its fp32
 // sums as slice s of the partial sums and z_combine adds the slices (in slice order) and rounds -- for launches whose
 // tiles alone would leave most compute units idle (one short prompt).
