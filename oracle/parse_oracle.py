@@ -144,7 +144,9 @@ class PatternCache:
     """Embedding -> per-layer subsets; sequential semantics in arrival order.
 
     lookup: nearest neighbour by cosine; the smallest index attaining the maximum wins;
-    a hit needs similarity >= tau.  lookup_or_route: a miss routes every layer's
+    a hit needs similarity >= tau.  An embedding without a direction (zeros, or one that holds an
+    infinity or NaN) has no cosine with anything: as a query it misses, as a stored key it is never
+    the nearest (similarity -inf when nothing else is stored).  lookup_or_route: a miss routes every layer's
     subset, and appends (embedding, subsets) while there is room (no eviction)."""
 
     def __init__(self, capacity: int, d: int, L: int, k: int, n_shared: int = 0):
@@ -168,7 +170,9 @@ class PatternCache:
         """-> (entry or -1, best similarity or -inf, best entry index or -1)."""
         if self.count == 0:
             return -1, float("-inf"), -1
-        c = cosine(e, self.keys)
+        with np.errstate(invalid="ignore", divide="ignore", over="ignore"):
+            c = cosine(e, self.keys)
+        c = np.where(np.isnan(c), -np.inf, c)
         j = int(np.argmax(c))           # numpy returns the first maximum
         return (j if c[j] >= tau else -1), float(c[j]), j
 

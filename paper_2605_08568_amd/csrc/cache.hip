@@ -68,6 +68,12 @@ __global__ __launch_bounds__(256) void cache_sims(const float *__restrict__ E, i
   if (lane == 0) sims[(size_t)p * ld + j] = ab / (sqrtf(aa) * sqrtf(bb));
 }
 
+// Is similarity v nearer than the best so far (bi < 0: none yet)?  A similarity that is no number -- 0/0 of an embedding of
+// zeros, or one that holds an infinity -- is never a candidate, so every lane, wavefront and workgroup that compares the same
+// similarities comes to the same answer, in whatever order it meets them.
+__device__ __forceinline__ bool nearer(float v, float bs, int bi) { return v > bs || (bi < 0 && v == v); }
+
+// Over candidates that nearer() let through.
 __device__ __forceinline__ void wave_argmax(float &bs, int &bi) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -219,7 +225,7 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     int bi = -1;
     for (int j = lane; j < count0; j += 64) {
       const float v = sims[(size_t)q * ld + j];
-      if (bi < 0 || v > bs) { bs = v; bi = j; }
+      if (nearer(v, bs, bi)) { bs = v; bi = j; }
     }
     wave_argmax(bs, bi);
     if (lane == 0) { best_sim[q] = bs; best_idx[q] = bi; }
@@ -228,16 +234,15 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
   if (wave == 0) {
     // The prompts before p only matter for whether they hit: one vote each over the similarities with the peers appended so
     // far (lane i holds the i-th of them).  Which peer is nearest -- larger similarity wins, equal similarity keeps the lower
-    // entry -- is worked out for prompt p itself.  (A first peer without a direction, similarity NaN, shadows the others, as it
-    // does in the arg-max.)  A batch of 8 that hits 7.2 -> 4.7 us a launch, 20 misses 27.2 -> 12.0 us.
+    // entry -- is worked out for prompt p itself.  Vote and arg-max agree because both pass over similarities that are no
+    // numbers.  A batch of 8 that hits 7.2 -> 4.7 us a launch, 20 misses 27.2 -> 12.0 us.
     int n_ins = 0;
     for (int q = 0; q < p; ++q) {
       const float bs = best_sim[q];
       const int bi = best_idx[q];
       const float v = lane < n_ins ? peer[q][ins_list[lane]] : -INFINITY;
-      const bool near = lane < n_ins && v >= tau && (bi < 0 || v > bs);
-      const bool shadow = (__ballot(v != v) & 1ull) != 0ull;
-      const bool h = (bi >= 0 && bs >= tau) || (!shadow && __ballot(near) != 0ull);
+      const bool near = lane < n_ins && v >= tau && nearer(v, bs, bi);
+      const bool h = (bi >= 0 && bs >= tau) || __ballot(near) != 0ull;
       if (!h && count0 + n_ins < capacity) {
         if (lane == 0) ins_list[n_ins] = q;
         ++n_ins;
@@ -247,11 +252,13 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     }
     float bs = best_sim[p];
     int bi = best_idx[p];
-    float ps = lane < n_ins ? peer[p][ins_list[lane]] : -INFINITY;
-    int pi = lane < n_ins ? lane : -1;
+    float ps = -INFINITY;
+    int pi = -1;
+    if (lane < n_ins) {
+      const float v = peer[p][ins_list[lane]];
+      if (nearer(v, ps, pi)) { ps = v; pi = lane; }
+    }
     wave_argmax(ps, pi);
-    ps = __shfl(ps, 0, 64);
-    pi = __shfl(pi, 0, 64);
     int src = -1;
     if (pi >= 0 && (bi < 0 || ps > bs)) { bs = ps; bi = count0 + pi; src = ins_list[pi]; }
     const bool h = bi >= 0 && bs >= tau;

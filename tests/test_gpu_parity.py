@@ -139,6 +139,34 @@ def test_cache_at_the_largest_model_width():
         cache.close()
 
 
+@pytest.mark.parametrize("P,places", [(8, [0]), (8, [1]), (8, [2, 4]), (20, [0, 1, 2]), (20, [1, 3]), (64, [1, 9, 32]), (64, [2])])
+@pytest.mark.parametrize("bad", ["zeros", "infinity"])
+def test_cache_embeddings_without_a_direction(P, places, bad):
+    """A batch with embeddings whose similarities are no numbers, then near-duplicates and new directions in the same and in a
+    second batch: entries, hits and subsets of all the others as the sequential oracle has them, every miss its own entry."""
+    say(f"cache: {P} prompts, {bad} at {places}")
+    d, L, G, k, tau = 256, 3, 8, 3, 0.9
+    E, _, Wr = _cache_inputs(2 * P, d, L, G, max(3, P // 3), 233)
+    for p in places:
+        E[p, 7 if bad == "infinity" else slice(None)] = np.inf if bad == "infinity" else 0.0
+    cache, oc = pa.Cache(2 * P, d, L, k, P), po.PatternCache(2 * P, d, L, k)
+    for b in range(2):
+        q = E[b * P:(b + 1) * P]
+        with np.errstate(invalid="ignore"):
+            e_ref, h_ref, s_ref, sims_ref, rmargin = oc.lookup_or_route(q, tau, Wr, return_detail=True)
+        plain = np.array([b == 1 or p not in places for p in range(P)])
+        finite = np.isfinite(sims_ref)
+        assert np.all(np.abs(sims_ref[finite] - tau) > 1e-3) and np.all(rmargin[plain] > 1e-5), "re-seed"
+        entry, hit, sim, subs = [t.cpu().numpy() for t in cache.lookup_or_route(torch.from_numpy(q).to(DEV), tau, torch.from_numpy(Wr).to(DEV))]
+        assert np.array_equal(entry, e_ref) and np.array_equal(hit, h_ref) and cache.count() == oc.count
+        new = entry[hit == 0]
+        assert len(set(new.tolist())) == len(new)
+        assert np.allclose(sim[finite], sims_ref[finite], atol=2e-5) and np.all(np.isneginf(sim[~finite]))
+        assert np.array_equal(subs[plain], s_ref[plain])
+        assert np.all((subs >= 0) & (subs < G)) and np.all(np.diff(subs, axis=2) > 0)
+    cache.close()
+
+
 def test_cache_empty_full_and_insert():
     say("cache: empty lookup, explicit insert, capacity overflow")
     d, L, G, k = 256, 2, 8, 3

@@ -246,6 +246,20 @@ def test_cache_sequential_semantics_and_capacity():
     assert subs[0, 0].tolist() == po.route(z[None], Wr[0], k)[0][0].tolist()
 
 
+def test_cache_embeddings_without_a_direction_are_near_nothing():
+    """Zeros or an infinity: a miss that takes an entry, and no other prompt's answer changes."""
+    d, L, k = 16, 1, 2
+    Wr = _wr(L, 5, d)
+    a, b, c0, e = np.eye(d)[:4]
+    for bad in (np.zeros(d), np.where(np.arange(d) == 5, np.inf, 1.0)):
+        c = po.PatternCache(16, d, L, k)
+        with np.errstate(invalid="ignore"):
+            entry, hit, _ = c.lookup_or_route(np.stack([a, bad, b, c0, c0 + 0.01 * a, e, bad]), 0.9, Wr)
+        assert entry.tolist() == [0, 1, 2, 3, 3, 4, 5] and hit.tolist() == [0, 0, 0, 0, 1, 0, 0] and c.count == 6
+        ent, sim = c.lookup(np.stack([e, bad]), 0.9)
+        assert ent.tolist() == [4, -1] and np.isneginf(sim[1])
+
+
 def test_cache_hit_returns_route_of_the_key():
     d, L, k = 32, 3, 4
     Wr = _wr(L, 9, d, seed=8)
