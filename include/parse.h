@@ -138,7 +138,8 @@ int parse_route_shared(const void *X, int32_t xdtype, int32_t rows, const int32_
  * library-owned state: keys float [capacity][d], values int32 [capacity][L][k], a device-side
  * entry count, and scratch for one batch of at most max_batch prompts.  A lookup answers with
  * the nearest key by cosine similarity (smallest entry index on equal similarity); it is a hit
- * when the similarity is >= tau.  Calls on one cache must be issued on one stream (or be ordered
+ * when the similarity is >= tau.  An embedding without a direction (zeros, or one that holds an infinity or
+ * NaN) has no similarity with anything: it misses, and an entry it made is never the nearest.  Calls on one cache must be issued on one stream (or be ordered
  * by the caller); calls that overlap on one cache race.
  * create, destroy and count synchronise (count copies to the host); everything else only enqueues, so a whole batch
  * -- explicit inserts included -- can be recorded into a HIP graph. */
@@ -159,7 +160,7 @@ int parse_cache_insert(parse_cache *cache, const float *emb, const int32_t *subs
                        parse_stream stream);
 /* Pure lookup for P <= max_batch embeddings (device float [P][d]).
  *   entry_out  device int32 [P]: the entry that answered, -1 on a miss (also when the cache is empty)
- *   sim_out    device float [P] or NULL: best cosine similarity (-inf if the cache is empty)
+ *   sim_out    device float [P] or NULL: best cosine similarity (-inf if there is none)
  *   subset_out device int32 [P][L][k] or NULL: stored subsets on a hit, untouched on a miss */
 int parse_cache_lookup(parse_cache *cache, const float *emb, int32_t P, float tau,
                        int32_t *entry_out, float *sim_out, int32_t *subset_out,

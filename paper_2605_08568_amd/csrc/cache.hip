@@ -102,7 +102,7 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
     int bi = -1;
     for (int j = lane; j < count0; j += 64) {
       const float s = sims[(size_t)p * ld + j];
-      if (bi < 0 || s > bs) { bs = s; bi = j; }
+      if (nearer(s, bs, bi)) { bs = s; bi = j; }
     }
     wave_argmax(bs, bi);
     if (lane == 0) { best_sim[p] = bs; best_idx[p] = bi; }
@@ -128,9 +128,9 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
     int pi = -1;
     for (int i = lane; i < n_ins; i += 64) {
       const float s = sims[(size_t)p * ld + capacity + ins_list[i]];
-      if (pi < 0 || s > ps) { ps = s; pi = i; }
+      if (nearer(s, ps, pi)) { ps = s; pi = i; }
     }
-    wave_argmax(ps, pi);
+    wave_argmax(ps, pi);            // the same in every lane, and so are the decision and n_ins below
     int src = -1;
     if (pi >= 0 && (bi < 0 || ps > bs)) { bs = ps; bi = count0 + pi; src = ins_list[pi]; }
     const bool h = bi >= 0 && bs >= tau;

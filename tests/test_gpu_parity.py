@@ -139,7 +139,8 @@ def test_cache_at_the_largest_model_width():
         cache.close()
 
 
-@pytest.mark.parametrize("P,places", [(8, [0]), (8, [1]), (8, [2, 4]), (20, [0, 1, 2]), (20, [1, 3]), (64, [1, 9, 32]), (64, [2])])
+@pytest.mark.parametrize("P,places", [(8, [0]), (8, [1]), (8, [2, 4]), (20, [0, 1, 2]), (20, [1, 3]), (64, [1, 9, 32]), (64, [2]),
+                                      (70, [0]), (70, [1, 9, 32])])     # more than 64: another kernel
 @pytest.mark.parametrize("bad", ["zeros", "infinity"])
 def test_cache_embeddings_without_a_direction(P, places, bad):
     """A batch with embeddings whose similarities are no numbers, then near-duplicates and new directions in the same and in a
@@ -164,6 +165,11 @@ def test_cache_embeddings_without_a_direction(P, places, bad):
         assert np.allclose(sim[finite], sims_ref[finite], atol=2e-5) and np.all(np.isneginf(sim[~finite]))
         assert np.array_equal(subs[plain], s_ref[plain])
         assert np.all((subs >= 0) & (subs < G)) and np.all(np.diff(subs, axis=2) > 0)
+    q = np.concatenate([E[P:P + 3], E[places[:1]]])
+    with np.errstate(invalid="ignore"):
+        ent_ref, sim_ref = oc.lookup(q, tau)
+    ent, sim, _ = [t.cpu().numpy() for t in cache.lookup(torch.from_numpy(q).to(DEV), tau)]
+    assert np.array_equal(ent, ent_ref) and np.allclose(sim[:3], sim_ref[:3], atol=2e-5) and np.isneginf(sim[3])
     cache.close()
 
 
