@@ -272,7 +272,7 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *layer, int
  *                above 32; same rounding points everywhere: z and y to bf16, fp32 sums), so a sequence's result may differ in
  *                rounding between a small and a large call.
  * workspace: device, >= parse_lowrank_workspace_bytes(mode, layer, rows, k, P, n_patterns) bytes (optional for
- *            bf16 prefill). */
+ *            bf16 prefill).  For PARSE_DECODE the answer for N rows covers every call of up to N rows. */
 int parse_lowrank_forward(int32_t mode, const parse_layer *layer, const parse_patterns *patterns,
                           const void *X, int32_t rows, const int32_t *tok_offsets,
                           const int32_t *pattern_id, int32_t P, void *Y, void *workspace,

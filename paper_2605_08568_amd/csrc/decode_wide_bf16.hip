@@ -307,9 +307,10 @@ static int wide_slices(const parse_layer *layers, int n_layers) {
   const int nkb = layers[0].n / 16;
   return std::max(1, std::min({DW_UNITS / std::max(units, 1), nkb / 16, DW_MAX_KS}));
 }
+static int panels_of(int rows) { return rows / 32 + (rows % 32 != 0); }
 // panels of one pass over `rows` sequences: the passes cover about the same number each
 static int wide_panels(int rows) {
-  const int panels = (rows + 31) / 32, passes = (panels + DW_MAXP - 1) / DW_MAXP;
+  const int panels = panels_of(rows), passes = (panels + DW_MAXP - 1) / DW_MAXP;
   return (panels + passes - 1) / passes;
 }
 
@@ -323,14 +324,20 @@ bool decode_wide_supported(const parse_layer *layers, int n_layers) {
   return true;
 }
 
-// workspace of a pass over up to `rows` sequences (at most DW_MAXP panels at a time)
-size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int rows) {
-  const size_t nt = (size_t)wide_panels(rows);
+static size_t wide_bytes(const parse_layer *layers, int n_layers, size_t nt) {
   const int ks = wide_slices(layers, n_layers);
   size_t t = round_up((size_t)n_layers * DW_PLAN_WORDS * sizeof(int32_t), 256) + nt * (layers[0].n / 16) * 1024;
   for (int l = 0; l < n_layers; ++l)
     t += nt * (layers[l].R / 16) * 1024 + (ks > 1 ? nt * (layers[l].R / 32) * ks * 4096 : 0);
   return t;
+}
+// What a call of `rows` sequences takes ...
+size_t decode_wide_needed_bytes(const parse_layer *layers, int n_layers, int rows) {
+  return wide_bytes(layers, n_layers, (size_t)wide_panels(rows));
+}
+// ... and what covers every call of up to `rows`: the balanced passes of 193 sequences are shorter than the one pass of 192.
+size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int rows) {
+  return wide_bytes(layers, n_layers, (size_t)std::min(panels_of(rows), DW_MAXP));
 }
 
 static int wide_pass(DwArgs a, hipStream_t s) {

@@ -37,6 +37,7 @@ int forward_decode_bf16(const parse_layer *L, const parse_patterns *pt, const ui
                         const int32_t *pattern_id, uint16_t *y, void *workspace, hipStream_t s);
 bool decode_wide_supported(const parse_layer *layers, int n_layers);
 size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int rows);
+size_t decode_wide_needed_bytes(const parse_layer *layers, int n_layers, int rows);
 int forward_decode_wide_bf16(const parse_layer *layers, const parse_patterns *pts, int n_layers, const uint16_t *x, int rows,
                              const int32_t *pattern_id, void *const *Y, void *workspace, hipStream_t s);
 
@@ -46,7 +47,7 @@ int forward_decode_wide_bf16(const parse_layer *layers, const parse_patterns *pt
 // together and 104 one panel after the other, 150 take 100 and 313, 64 through 1024 x 2816 layers 40 and 70.
 static int decode_rows(const parse_layer *layers, const parse_patterns *pts, int n_layers, const uint16_t *X, int rows,
                        const int32_t *pattern_id, void *const *Y, void *workspace, size_t workspace_bytes, hipStream_t s) {
-  if (rows > 32 && decode_wide_supported(layers, n_layers) && workspace_bytes >= decode_wide_workspace_bytes(layers, n_layers, rows))
+  if (rows > 32 && decode_wide_supported(layers, n_layers) && workspace_bytes >= decode_wide_needed_bytes(layers, n_layers, rows))
     return forward_decode_wide_bf16(layers, pts, n_layers, X, rows, pattern_id, Y, workspace, s);
   for (int r0 = 0; r0 < rows; r0 += 32) {
     const int nb = rows - r0 < 32 ? rows - r0 : 32;
@@ -190,7 +191,7 @@ size_t parse_lowrank_decode_multi_workspace_bytes(const parse_layer *layers, int
   // a panel at a time: the call builds its plan behind the intermediates; several panels at once: as much as a pass takes
   size_t need = decode_panel_bytes(layers, n_layers);
   if (decode_wide_supported(layers, n_layers)) {
-    const size_t wide = decode_wide_workspace_bytes(layers, n_layers, INT32_MAX - 31);
+    const size_t wide = decode_wide_workspace_bytes(layers, n_layers, INT32_MAX);
     if (wide > need) need = wide;
   }
   return need;
@@ -219,6 +220,7 @@ int parse_lowrank_decode_multi(const parse_layer *layers, const parse_patterns *
   return decode_rows(layers, patterns, n_layers, (const uint16_t *)X, rows, pattern_id, Y, workspace, workspace_bytes,
                      (hipStream_t)stream);
 }
+
 // checks shared by the decode entry points that take several layers
 static int check_decode_layers(const parse_layer *layers, int32_t n_layers) {
   if (!layers || n_layers < 1) return PARSE_EINVAL;

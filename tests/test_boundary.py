@@ -306,3 +306,14 @@ def test_plan_entry_points_reject_bad_arguments_and_size_their_buffers():
     assert lib.parse_lowrank_decode_planned_workspace_bytes(big, 1) == 2560 * 64 + 2560 * 128 * 3   # three slices of 229-230 steps
     lib.parse_lowrank_decode_static_capacity.restype = C.c_size_t
     assert lib.parse_lowrank_decode_static_capacity() == 4 << 20
+
+
+def test_decode_workspace_of_a_larger_batch_covers_the_smaller_ones():
+    """A server sizes its workspace once, for its largest batch: no smaller batch may need more (and then go panel after panel)."""
+    lib = pa.lib()
+    L = _layer(n=4096, m=11008, R=2560, G=20, dtype=1, layout=1)
+    q = [lib.parse_lowrank_workspace_bytes(1, C.byref(L), r, 10, r, 4) for r in [*range(1, 600), 4096, 2 ** 31 - 1]]
+    assert all(a <= b for a, b in zip(q, q[1:]))
+    assert q[191] == q[-1]                                        # 192 sequences are the most that go together
+    two = (B._Layer * 2)(L, L)
+    assert lib.parse_lowrank_decode_multi_workspace_bytes(two, 2) > q[-1]
