@@ -732,10 +732,10 @@ __global__ __launch_bounds__(D16_THREADS) void decode_z16(DecArgs a) {
     vr[d] = *reinterpret_cast<const u32x4 *>(V + (size_t)kb * 1024);
     xr[d] = *reinterpret_cast<const u32x4 *>(X + (size_t)kb * 32);
   };
-  auto product = [&](int d, int s) {
+  auto product = [&](int d, int s) {                   // both zero there: an infinite weight times zero is no number
     const u32x4 zero = {0, 0, 0, 0};
     const bool on = (s0 + s) * 2 + (kq >> 1) < nkb;
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vr[d]), dec_bf16x8(on ? xr[d] : zero), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(on ? vr[d] : zero), dec_bf16x8(on ? xr[d] : zero), acc, 0, 0, 0);
   };
   if (cnt > 0) {
 #pragma unroll

@@ -1649,3 +1649,24 @@ def test_decode_few_sequences_tiles(n, shapes, B):
         assert np.all(yn[B - 1] == 0.0)
         assert_close(yn[:B - 1], ref[:B - 1], TOL_BF16, f"layer {l}")
         assert torch.equal(ys[l].view(torch.int16), yp[l].view(torch.int16))
+
+
+@pytest.mark.parametrize("n,B", [(48, 3), (48, 5), (48, 16), (4112, 3), (4112, 5), (4112, 14)])
+def test_decode_of_few_sequences_keeps_infinite_products(n, B):
+    """A weight that overflowed to infinity, in the last column of an odd number of 16-column blocks (half of the 16-wide kernel's
+    last step is past the end): the results are infinities with the signs of the products, and sequences that did not select its
+    group are untouched (within the usual tolerance of the oracle's product)."""
+    say(f"decode with an infinite weight: n={n} {B} sequences")
+    rng = np.random.default_rng(1601)
+    m, R, G = 64, 64, 2
+    Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((R, n), (R, m)))
+    x = si.make_tokens(rng, B, n, "bf16")
+    V, U, xv = (si.bf16_bits_to_f32(t).astype(np.float64) for t in (Vt, Ut, x))
+    Vt[5, n - 1] = 0x7F80
+    layer = pa.layer_to_mfma16(pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, G, pa.PARSE_ROWMAJOR))
+    pid = (np.arange(B) % 2).astype(np.int32)
+    y, = decode_multi_guarded([layer], [pa.Patterns(1, 2, subsets=i32(np.array([[0], [1]], np.int32)))], upload_tokens(x, "bf16"), i32(pid))
+    yn = y.float().cpu().numpy().astype(np.float64)
+    hit, free = np.flatnonzero(pid == 0), np.flatnonzero(pid == 1)
+    assert np.array_equal(yn[hit], np.inf * np.sign(xv[hit, n - 1:] * U[5]))
+    assert_close(yn[free], (xv[free] @ V[32:].T) @ U[32:], TOL_BF16, "the other group")
