@@ -68,12 +68,9 @@ __global__ __launch_bounds__(256) void cache_sims(const float *__restrict__ E, i
   if (lane == 0) sims[(size_t)p * ld + j] = ab / (sqrtf(aa) * sqrtf(bb));
 }
 
-// Is similarity v nearer than the best so far (bi < 0: none yet)?  A similarity that is no number -- 0/0 of an embedding of
-// zeros, or one that holds an infinity -- is never a candidate, so every lane, wavefront and workgroup that compares the same
+// The arg-maxes start from (-infinity, none) and take a similarity by `>`: one that is no number -- 0/0 of an embedding of zeros,
+// or of one that holds an infinity -- is never a candidate, so every lane, wavefront and workgroup that compares the same
 // similarities comes to the same answer, in whatever order it meets them.
-__device__ __forceinline__ bool nearer(float v, float bs, int bi) { return v > bs || (bi < 0 && v == v); }
-
-// Over candidates that nearer() let through.
 __device__ __forceinline__ void wave_argmax(float &bs, int &bi) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -102,7 +99,7 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
     int bi = -1;
     for (int j = lane; j < count0; j += 64) {
       const float s = sims[(size_t)p * ld + j];
-      if (nearer(s, bs, bi)) { bs = s; bi = j; }
+      if (s > bs) { bs = s; bi = j; }
     }
     wave_argmax(bs, bi);
     if (lane == 0) { best_sim[p] = bs; best_idx[p] = bi; }
@@ -128,7 +125,7 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
     int pi = -1;
     for (int i = lane; i < n_ins; i += 64) {
       const float s = sims[(size_t)p * ld + capacity + ins_list[i]];
-      if (nearer(s, ps, pi)) { ps = s; pi = i; }
+      if (s > ps) { ps = s; pi = i; }
     }
     wave_argmax(ps, pi);            // the same in every lane, and so are the decision and n_ins below
     int src = -1;
@@ -225,7 +222,7 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     int bi = -1;
     for (int j = lane; j < count0; j += 64) {
       const float v = sims[(size_t)q * ld + j];
-      if (nearer(v, bs, bi)) { bs = v; bi = j; }
+      if (v > bs) { bs = v; bi = j; }
     }
     wave_argmax(bs, bi);
     if (lane == 0) { best_sim[q] = bs; best_idx[q] = bi; }
@@ -241,7 +238,7 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
       const float bs = best_sim[q];
       const int bi = best_idx[q];
       const float v = lane < n_ins ? peer[q][ins_list[lane]] : -INFINITY;
-      const bool near = lane < n_ins && v >= tau && nearer(v, bs, bi);
+      const bool near = lane < n_ins && v >= tau && v > bs;
       const bool h = (bi >= 0 && bs >= tau) || __ballot(near) != 0ull;
       if (!h && count0 + n_ins < capacity) {
         if (lane == 0) ins_list[n_ins] = q;
@@ -256,7 +253,7 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     int pi = -1;
     if (lane < n_ins) {
       const float v = peer[p][ins_list[lane]];
-      if (nearer(v, ps, pi)) { ps = v; pi = lane; }
+      if (v > ps) { ps = v; pi = lane; }
     }
     wave_argmax(ps, pi);
     int src = -1;
