@@ -190,14 +190,28 @@ __global__ __launch_bounds__(256) void route_or_gather(const float *__restrict__
   }
 }
 
-// Small batches (P <= kSmallBatch): resolve and route_or_gather in one launch.  grid (L, P), block 256.  Every
+// Small batches (P <= kSmallBatch): resolve and route_or_gather in one launch.  grid (L, P), block small_threads().  Every
 // workgroup repeats the (cheap, deterministic) decision walk for prompts 0..p from the similarity matrix, so no
 // workgroup waits for another; it then routes / gathers for its own (layer, prompt).  The entry count is read
 // from count_in and the new one written to count_out (a different word: workgroups still starting must see the
 // old value) by the workgroup of the last prompt, which has walked the whole batch.
-// Latency-bound: a chain of dependent steps on a few values.  Sixteen wavefronts, so that every group of a miss's router has
-// one (sixteen groups, 20 misses of 4096 columns: four wavefronts took 27 us for the launch, see the figures at the walk).
+// Latency-bound while the chip holds the grid: a chain of dependent steps on a few values, and sixteen wavefronts give every
+// group of a miss's router one (20 misses of 4096 columns: four wavefronts took 27 us for the launch, see the figures at the
+// walk).  With more (layer, prompt) workgroups than that, their rounds count, and a workgroup whose prompt hits leaves most of its
+// wavefronts idle: smaller ones.
 constexpr int kSmallBatch = 64, kSmallThreads = 1024;
+// The line by workgroups (whole probe, 1024 columns, us, with 1024 / 512 / 256 threads; misses, then hits):
+//   192 (3 layers x 64): 28 / 30 / 37 and 18 / 21 / 29        256 (32 x 8): 13.4 / 13.7 / 15.7 and 7.5 / 7.3 / 8.1
+//   320 (16 x 20): 22 / 18 / 21 and 12 / 10 / 12              512 (8 x 64): 40 / 31 / 38 and 23 / 22 / 29
+//   640 (32 x 20): 29 / 23 / 21 and 15 / 12 / 12              4480 (224 x 20): 125 / 78 / 49 and 59 / 38 / 25
+// and where few prompts of many layers make a short walk and much reading of routers: 448 (224 x 2, 4096 columns) 32 / 27 / 25
+// and 9 / 7 / 7.
+static int small_threads(int L, int P) {
+  const long long wgs = (long long)L * P;
+  if (wgs <= 256) return kSmallThreads;
+  return wgs <= 512 && P >= 8 ? 512 : 256;
+}
+
 __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     const float *__restrict__ sims, int ld, int capacity, int P, float tau, const int32_t *__restrict__ count_in,
     int32_t *__restrict__ count_out, const float *__restrict__ E, int d, const float *__restrict__ Wr, int G, int L, int k,
@@ -463,8 +477,8 @@ int parse_cache_lookup_or_route(parse_cache *c, const float *emb, int32_t P, flo
     // small batch: every (layer, prompt) workgroup works out the batch's decisions itself, then does its own part;
     // the new entry count goes to the other counter slot, which becomes the live one
     PARSE_ALLOW_LDS(resolve_route_or_gather, (size_t)(c->d + 128) * sizeof(float));
-    hipLaunchKernelGGL(resolve_route_or_gather, dim3(c->L, P), dim3(kSmallThreads), (size_t)(c->d + 128) * sizeof(float), s, c->sims,
-                       ld, c->capacity, P, tau, c->count + c->cur, c->count + (c->cur ^ 1), emb, c->d, Wr, G, c->L, c->k,
+    hipLaunchKernelGGL(resolve_route_or_gather, dim3(c->L, P), dim3(small_threads(c->L, P)), (size_t)(c->d + 128) * sizeof(float), s,
+                       c->sims, ld, c->capacity, P, tau, c->count + c->cur, c->count + (c->cur ^ 1), emb, c->d, Wr, G, c->L, c->k,
                        entry, hit, sim_out, c->keys, c->values, subset_out, c->n_shared);
     PARSE_LAUNCH_CHECK();
     c->cur ^= 1;

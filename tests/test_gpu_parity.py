@@ -173,6 +173,18 @@ def test_cache_embeddings_without_a_direction(P, places, bad):
     cache.close()
 
 
+@pytest.mark.parametrize("L,P", [(4, 64), (5, 52), (16, 32), (300, 2), (9, 57)])
+def test_cache_probe_of_many_layers(L, P):
+    """Either side of the lines where the one-launch probe takes smaller workgroups: 256 (layer, prompt) pairs, 512 of them."""
+    say(f"cache: {L} layers x {P} prompts")
+    d, G, k = 128, 20, 9
+    E, cid, Wr = _cache_inputs(2 * P, d, L, G, 1 + P // 3, 241)
+    cache, oc = pa.Cache(2 * P, d, L, k, P), po.PatternCache(2 * P, d, L, k)
+    for b in range(2):
+        _check_cache_batch(cache, oc, E[b * P:(b + 1) * P], 0.9, Wr)
+    cache.close()
+
+
 def test_cache_empty_full_and_insert():
     say("cache: empty lookup, explicit insert, capacity overflow")
     d, L, G, k = 256, 2, 8, 3
