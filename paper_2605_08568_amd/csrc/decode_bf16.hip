@@ -732,11 +732,8 @@ __global__ __launch_bounds__(D16_THREADS) void decode_z16(DecArgs a) {
     vr[d] = *reinterpret_cast<const u32x4 *>(V + (size_t)kb * 1024);
     xr[d] = *reinterpret_cast<const u32x4 *>(X + (size_t)kb * 32);
   };
-  auto product = [&](int d, int s) {                   // both zero there: an infinite weight times zero is no number
-    const u32x4 zero = {0, 0, 0, 0};
-    const bool on = (s0 + s) * 2 + (kq >> 1) < nkb;
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(on ? vr[d] : zero), dec_bf16x8(on ? xr[d] : zero), acc, 0, 0, 0);
-  };
+  const int half = (nkb & 1) && s0 + cnt == steps ? cnt - 1 : -1;      // that step: always a wavefront's last one
+  auto product = [&](int d) { acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vr[d]), dec_bf16x8(xr[d]), acc, 0, 0, 0); };
   if (cnt > 0) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) request(d, min(d, cnt - 1));
@@ -745,14 +742,17 @@ __global__ __launch_bounds__(D16_THREADS) void decode_z16(DecArgs a) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
         __builtin_amdgcn_sched_barrier(0);
-        product(d, s + d);
+        product(d);
         request(d, min(s + d + DEPTH, cnt - 1));
       }
     }
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
       __builtin_amdgcn_sched_barrier(0);
-      if (s + d < cnt) product(d, s + d);              // uniform
+      if (s + d < cnt) {                               // uniform
+        if (s + d == half && (kq >> 1)) vr[d] = xr[d] = u32x4{0, 0, 0, 0};   // both: an infinite weight times zero is no number
+        product(d);
+      }
     }
   }
 #pragma unroll
