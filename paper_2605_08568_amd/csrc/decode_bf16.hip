@@ -693,7 +693,8 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_z16 / decode_y16: five to sixteen sequences (a small server), on the 16x16x32 matrix instruction.  The 32-wide
+// decode_z16 / decode_y16: up to sixteen sequences (a small server; which calls of two to four come here is decided where the
+// kernels are launched), on the 16x16x32 matrix instruction.  The 32-wide
 // kernels leave half of their N side empty there, own 32 ranks or columns per workgroup (too few workgroups: a 4096-column
 // layer has 128 column blocks for 256 units) and stage x through LDS behind barriers.  Here the M side is 16 ranks or
 // columns: in the operand order 16 rows x 32 reduction indices are four runs of 256 bytes, a wavefront instruction reads
@@ -911,6 +912,29 @@ int build_decode_plan(const parse_layer *layers, const parse_patterns *pts, int 
   return PARSE_OK;
 }
 
+// Which kernel makes z.  One sequence: the vector units.  Two to sixteen: the 16-wide kernel where its workgroups (16 stored
+// ranks each) are many or its wavefronts have their whole share of the reduction in flight (n <= 4096); else the kernel that
+// splits the work more finely: the vector units (eight ranks a workgroup) for two sequences, or for four while x is short,
+// the 32-wide kernel (the reduction cut in slices) otherwise, and wherever x, which every 16-wide workgroup reads whole, outweighs
+// the factor.  us a step of one layer of 4096 columns (two or three patterns of half of the groups), vector / 16-wide / 32-wide, by
+// sequences x n:
+//    512 ranks: 2 x 4608   9.5 / 10.9 / 14.7   4 x 4608 11.4 / 12.1 / 15.6   4 x 8192 14.4 / 12.5 / 16.4   3 x 14336 - / 20 / 17
+//   1024 ranks: 2 x 11008 15.9 / 16.8 / 15.1   5 x 4096 - / 11.0 / 13.9      5 x 11008 - / 19.7 / 17.3     4 x 14336 - / 23 / 18
+//   2048 ranks: 2 x 4608  13.2 / 14.9 / 14.7   5 x 8192 - / 18.9 / 21.9      12 x 4608 - / 18.5 / 16.2     16 x 4608 - / 20 / 16
+//   2560 ranks: 2 x 8192  23 / 18 / 22         5 x 11008 - / 24 / 26         12 x 11008 - / 27 / 25
+//   3 x 2048:   2 x 8192  38 / 34 / 42         4 x 4096 35 / 30 / 30         12 x 2048 - / 20.8 / 20.9     12 x 8192 - / 39 / 41
+static bool z_on_vector_units(int NB, int n, int wgs16) {
+  if (NB == 1 || NB * n <= 6144) return true;
+  return NB == 2 ? wgs16 <= 128 : wgs16 <= 64 && n > 4096 && n <= 6144;
+}
+static bool z_16_wide(int B, int n, int wgs16) {
+  if (n <= 4096) return true;
+  const long long x = (long long)B * n;
+  if (wgs16 >= 160) return x <= 60000;
+  if (wgs16 >= 128) return x <= 50000;
+  return n <= 12288 && (wgs16 < 64 ? x <= 60000 : B <= 4 && x <= 50000);
+}
+
 // n_layers layers that share x (same n); plan = n_layers consecutive layer plans; Y[l] and the z part of layer l in the
 // workspace follow the order of `layers`.
 int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const uint16_t *x, int B, int32_t *plan,
@@ -965,12 +989,10 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   }
   const int nkb = a.n / 16;
   const int NB = B <= 1 ? 1 : (B <= 2 ? 2 : 4);
-  // Which kernel makes z (us a launch, vector / 16-wide / 32-wide).  One sequence: vector.  Two to four: vector while x is short
-  // (2 x 2048: 4.7 / 5.5, 2 x 4096 11.0 / 8.0, 4 x 1024 4.6 / 5.7, 4 x 4096 13.2 / 8.8, 4 x 11008 19 / 14 / 16).  Up to sixteen:
-  // 16-wide, until x, which every workgroup reads whole, outweighs the factor on long reductions (12 x 4096: - / 9.7 / 13.7, 12 x
-  // 1024 - / 6.8 / 7.8, 12 x 11008 - / 18 / 16).
-  const bool zv = B <= DV_MAXB && (size_t)NB * a.n * 2 <= (size_t)DV_XBYTES && (B == 1 || NB * a.n <= 6144);
-  const bool z16 = !zv && B <= D16_MAXB && (a.n <= 4096 || (long long)B * a.n <= 60000);
+  int wgs16 = 0;                                           // workgroups of the 16-wide first product
+  for (int l = 0; l < n_layers; ++l) wgs16 += layers[l].R / 16;
+  const bool zv = B <= DV_MAXB && (size_t)NB * a.n * 2 <= (size_t)DV_XBYTES && z_on_vector_units(NB, a.n, wgs16);
+  const bool z16 = !zv && B <= D16_MAXB && z_16_wide(B, a.n, wgs16);
   if (zv) {
     // a handful of sequences: eight ranks per workgroup on the vector units, no split of the reduction range
     zb = 0;

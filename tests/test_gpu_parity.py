@@ -1627,6 +1627,11 @@ def test_prefill_planned_tiles(n, m, rS, lengths):
     (4112, [(32, 224, 7, 3)], 14),                                   # more steps than are in flight at once
     (5648, [(96, 64, 2, 2)], 13),                                    # long reduction: first product 32-wide, second 16-wide
     (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # first product on the vector units, second 16-wide, six blocks
+    (4624, [(64, 1024, 8, 3)], 4), (4624, [(64, 1056, 11, 3)], 4),   # few workgroups: vector units up to 64 of them, then 16-wide
+    (6160, [(64, 96, 3, 2)], 4), (12304, [(64, 96, 3, 2)], 3),       # ... and only while x is short; past 12288 columns 32-wide
+    (8208, [(64, 2048, 8, 3)], 2), (8208, [(64, 2080, 13, 3)], 2),   # two sequences: vector units up to 128 workgroups
+    (24576, [(32, 64, 2, 1)], 2), (24592, [(32, 64, 2, 1)], 2),      # the longest x the vector units hold, and one longer
+    (8208, [(64, 1024, 8, 3)], 5), (8208, [(64, 992, 31, 9)], 5),    # five: 64 to 127 workgroups go 32-wide
 ])
 def test_decode_few_sequences_tiles(n, shapes, B):
     """Two to sixteen sequences at the edges of the 16-wide decode kernels and where the choice of kernels changes, against the
