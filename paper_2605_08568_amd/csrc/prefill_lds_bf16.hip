@@ -509,16 +509,6 @@ int prefill_planned_split(int rows, int n) {
   if (ks > n / 64 / 8) ks = n / 64 / 8;
   return ks < 2 ? 1 : ks;
 }
-// Slices taken: up to four for at most 256 token rows with a reduction of 4096 or more, where the tiles alone leave the chip idle
-// (77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7 without; 256 rows
-// 26.8 and 31.5; 512 rows 30.8 and 31.4-33.7; n = 1024 19 and 16.6: the second launch costs what the split gains), and up to 512
-// rows with longer ones (488 rows, n = 5632 27 and 40, n = 11008 51 and 70; 640 rows 69 and 70).  A
-// function of (rows, n) alone, so that a call over several layers splits exactly like its single-layer calls and gives
-// the same bits.
-static int split_slices(int rows, int n) {
-  const int room = prefill_planned_split(rows, n);
-  return (rows <= 256 && n >= 4096) || (rows <= 512 && n >= 5120) ? std::min(4, room) : 1;
-}
 // Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
 // partial sums of its ks slices
 static size_t planned_z_only_bytes(int cap_tiles, int rS) { return round_up((size_t)cap_tiles * 256 * rS * sizeof(uint16_t), 256); }
@@ -528,9 +518,67 @@ size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks) {
 
 bool prefill_planned_supported(int n, int m, int rS) { return n % 64 == 0 && rS % 32 == 0 && m % 32 == 0 && n >= 64 && rS >= 32; }
 
+// Token tiles of bm rows, as far as the host can tell: it does not know which prompts share a pattern, and a pattern starts on a
+// tile of its own.  Prompts of one length that are a multiple of bm leave nothing open; otherwise full tiles and one more are
+// taken for the number.  (Half a tile more for every prompt is closer when every prompt has its own pattern, but many prompts of
+// few patterns then get tiles that are far too large: 24 prompts of 20-300 tokens, n = m = 2048, 512 ranks, both products, us:
+// 40.9 against 35.5 with two patterns, 45.9 and 52.3 with 24.  Over 330 batches of 1 to 100 prompts full tiles come closer to the
+// best tile of each: 1 % off it on average, 4 % with the other estimate.)
+static long long token_tiles(int rows, int P, int bm) {
+  if (rows % P == 0 && rows / P % bm == 0) return rows / bm;
+  return (rows + bm - 1) / bm + (P > 1 ? 1 : 0);
+}
+
+// Time of the first product with tile i, in units of a round of 128 x 128 tiles, one per compute unit (30 us at K = 4096).
+// Measured over 16 shapes of 77 to 57 000 rows and 512 to 3072 ranks, further rounds of the small tiles (two workgroups of
+// 64 x 64 per unit) over the batches above.  E.g. 2048 rows x 2304 ranks, both products, us, 256 x 256 / 128 x 256 / 128 x 128 /
+// 64 x 128 / 64 x 64: 142 / 110 / 121 / 118 / 118; 4096 x 1024 136 / 101 / 86 / 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024
+// 557 / 587 / 654 / 706 / 776.
+enum { T64, T64x128, T128, T128x256, T256, N_TILES };
+static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split = 1) {
+  static const int bm[N_TILES] = {64, 64, 128, 128, 256}, bn[N_TILES] = {64, 128, 128, 256, 256};
+  long long t = 0;
+  for (int l = 0; l < n_layers; ++l) t += (p[l]->rS + bn[i] - 1) / bn[i];
+  t *= token_tiles(p[0]->rows, p[0]->P, bm[i]) * split;
+  const double rounds = (double)((t + 255) / 256), two_each = (double)((t + 511) / 512);
+  switch (i) {
+    case T64: return t <= 256 ? 0.45 : (split > 1 ? 0.69 * two_each : 0.69 + 0.9 * (two_each - 1));
+    case T64x128: return rounds - 0.4;
+    case T128: return rounds;
+    case T128x256: return 1.57 * rounds;
+    default: return 2.5 * rounds;
+  }
+}
+constexpr int SHORT_ROWS = 4096;
+static int best_tile(const PfArgs *const *p, int n_layers) {
+  int best = T64;
+  for (int i = 1; i < N_TILES; ++i)
+    if (!(i == T256 && p[0]->rows <= SHORT_ROWS) && tile_rounds(i, p, n_layers) < tile_rounds(best, p, n_layers)) best = i;
+  return best;
+}
+// Slices of one layer's first product: as many (up to four) as pay for the second launch, which adds the fp32 partial sums (2 us
+// and a pass over them).  77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7
+// without; 300 rows x 1024 ranks 24 and 27; 700 x 1024 34 (two) and 31; n = 11008: 534 rows x 384 ranks 33 (three) and 54, 643 x
+// 384 40 (two) and 58, 1024 x 1280 85 (two) and 83; n = 5632, 546 x 640 25.5 (two) and 30.6.  A function of the batch and of this
+// layer alone, so that a call over several layers splits each like its single-layer call and gives the same bits.
+static int split_slices(const PfArgs &p) {
+  const int room = std::min(4, prefill_planned_split(p.rows, p.n));
+  if (p.n < 4096) return 1;
+  const PfArgs *one[1] = {&p};
+  const double round_us = 30.0 * p.n / 4096;
+  int best = 1;
+  double least = tile_rounds(best_tile(one, 1), one, 1) * round_us;
+  for (int ks = 2; ks <= room; ++ks) {
+    const double us = tile_rounds(T64, one, 1, ks) / ks * round_us + 2.0 + 4e-6 * p.rows * p.rS * ks;
+    if (us < least) { least = us; best = ks; }
+  }
+  return best;
+}
+
 // n_layers layers that share X [rows][n] (row-major) and the plan (built for the tok_offsets and pattern ids of these
 // patterns); Z[l] = layer l's intermediate (operand order over the plan's virtual rows); p[l].Y [rows][m_l].
-// Two launches for all layers together: the stacked first product, the batched second product (Sec. 4.4, Eq. 11-12).
+// Two launches for all layers together: the stacked first product, the batched second product (Sec. 4.4, Eq. 11-12); where the
+// first one is split, one more that adds the slices (layers that are split differently: as many of each).
 int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int32_t *plan, int cap, uint16_t *const *Z,
                                        int avg_prompt_rows, hipStream_t s) {
   if (n_layers < 1 || n_layers > LG_MAX_LAYERS) return PARSE_ESHAPE;
@@ -538,7 +586,10 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   g1.n_layers = g2.n_layers = n_layers;
   g1.plan = g2.plan = plan;
   g1.cap = g2.cap = cap;
-  g1.compact = g2.compact = p[0].P > 1;        // one prompt has less than a 256-row tile of padding
+  const int rows = p[0].rows, P = p[0].P;
+  // one prompt has less than a 256-row tile of padding, prompts of one length in whole tiles (most likely) have none: leaving
+  // padding tiles out of the numbering costs a launch 1 us
+  g1.compact = g2.compact = P > 1 && !(rows % P == 0 && rows / P % 256 == 0);
   bool slices64 = true;                        // the second product can take slices of 64
   for (int l = 0; l < n_layers; ++l) {
     if (p[l].sh_ranks % 32 != 0 || p[l].sh_ranks >= p[l].rS) return PARSE_ESHAPE;
@@ -547,80 +598,64 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
     g2.L[l] = LgLayer{Z[l], p[l].Ut_S, p[l].Y, nullptr, (size_t)own * p[l].m, p[l].rS, p[l].m, p[l].Ut_sh, p[l].sh_ranks / 32, 0};
     slices64 = slices64 && p[l].sh_ranks == 0 && p[l].rS % 64 == 0;
   }
-  const int rows = p[0].rows, P = p[0].P;
   const int per_pattern = avg_prompt_rows / 256;
-  // Token tiles of BM rows, as far as the host can tell: a pattern starts on a tile of its own, so patterns whose rows are no
-  // multiple of BM leave half a tile unused on average.  Up to n_patterns prompts may each have their own; more prompts share,
-  // and half of the slots is taken for the number in use.
-  const int groups = P <= p[0].n_patterns ? P : (p[0].n_patterns + 1) / 2;
-  const bool even = rows % P == 0 && groups == P;
-  auto token_tiles = [&](int bm) -> long long {
-    if (even) return (long long)P * ((rows / P + bm - 1) / bm);      // prompts of one length, most likely
-    return ((long long)rows * 2 + (long long)groups * bm + 2 * bm - 1) / (2 * bm);
-  };
-  auto tiles1 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].rS + bn - 1) / bn; return t * token_tiles(bm); };
-  auto tiles2 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].m + bn - 1) / bn; return t * token_tiles(bm); };
-  // rounds of workgroups; an estimate that is a tenth of a round over a whole number is taken for it (prompts that share a
-  // pattern leave fewer half tiles)
-  auto rounds = [&](long long tiles, int slots) {
-    const long long slack = even ? 0 : slots / 10;
-    return (double)std::max<long long>(1, (tiles - slack + slots - 1) / slots);
-  };
-
-  // First product: the tile with the smallest (rounds of workgroups) x (time of a round), in units of a round of 128 x 128
-  // tiles, one per compute unit (30 us at K = 4096).  The times per round are measured over 16 shapes of 77 to 57 000 rows
-  // and 512 to 3072 ranks: 256 x 256 2.85, 128 x 256 1.57, 64 x 128 0.6, 64 x 64 0.45 (two per unit 0.69).
-  // E.g. 2048 rows x 2304 ranks, both products, us: 142 / 110 / 121 / 118 / 118 (taken: 128 x 256); 4096 x 1024 136 / 101 / 86 /
-  // 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024 557 / 587 / 654 / 706 / 776.
-  // Up to SHORT_ROWS rows every tile takes the reduction in two halves (WK 2, slices of 64), beyond it none does: which
-  // tile a call takes depends on the layers it fuses, its bits do not.
-  constexpr int SHORT_ROWS = 4096;
-  const int ks = split_slices(rows, p[0].n);
-  int st;
-  if (ks > 1) {      // the partial sums follow each layer's Z in the workspace
-    g1.ks = ks;
-    int most = 0;
+  // First product, layers of one number of slices together.  Up to SHORT_ROWS rows every tile takes the reduction in two halves
+  // (WK 2, slices of 64), beyond it none does: which tile a call takes depends on the layers it fuses, its bits do not.
+  int slices[LG_MAX_LAYERS];
+  for (int l = 0; l < n_layers; ++l) slices[l] = split_slices(p[l]);
+  for (int ks = 1; ks <= 4; ++ks) {
+    LgArgs g = g1;
+    const PfArgs *lay[LG_MAX_LAYERS];
+    int most = 0, st;
+    g.n_layers = 0;
     for (int l = 0; l < n_layers; ++l) {
-      g1.L[l].Pz = reinterpret_cast<float *>(reinterpret_cast<char *>(Z[l]) + planned_z_only_bytes(cap, p[l].rS));
+      if (slices[l] != ks) continue;
+      lay[g.n_layers] = &p[l];
+      g.L[g.n_layers] = g1.L[l];
+      if (ks > 1)      // the partial sums follow the layer's Z in the workspace
+        g.L[g.n_layers].Pz = reinterpret_cast<float *>(reinterpret_cast<char *>(Z[l]) + planned_z_only_bytes(cap, p[l].rS));
       most = std::max(most, p[l].rS);
+      ++g.n_layers;
     }
-    st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g1, per_pattern, s);
-    if (st != PARSE_OK) return st;
-    const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
-    hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), n_layers), dim3(256), 0, s, g1);
-    PARSE_LAUNCH_CHECK();
-  } else {
-    const long long t64x64 = tiles1(64, 64), t64 = tiles1(64, 128), t128 = tiles1(128, 128);
-    const double c256 = 2.85 * rounds(tiles1(256, 256), 256), c128x256 = 1.57 * rounds(tiles1(128, 256), 256), c128 = rounds(t128, 256);
-    const double c64 = t64 <= 256 ? 0.6 : 1e9;         // more of them than one round lose to 128 x 256
-    const double c64x64 = t64x64 <= 256 ? 0.45 : t64x64 <= 512 ? 0.69 : 1e9;
-    const bool by64x64 = c64x64 <= std::min(c64, std::min(c128, c128x256)), by64 = c64 <= std::min(c128, c128x256);
+    if (g.n_layers == 0) continue;
+    if (ks > 1) {
+      g.ks = ks;
+      st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g, per_pattern, s);
+      if (st != PARSE_OK) return st;
+      const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
+      hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), g.n_layers), dim3(256), 0, s, g);
+      PARSE_LAUNCH_CHECK();
+      continue;
+    }
+    const int tile = best_tile(lay, g.n_layers);
     if (rows <= SHORT_ROWS) {
-      if (by64x64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
-      else if (by64) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g1, per_pattern, s);
-      else if (c128 <= c128x256) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
-      else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2, 1>(g1, per_pattern, s);
-    } else if (by64x64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);      // many rows, few ranks
-    else if (by64) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g1, per_pattern, s);
-    else if (c256 <= c128x256 && c256 <= c128) st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g1, per_pattern, s);
-    else if (c128x256 <= c128) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0, 0, 1, 1>(g1, per_pattern, s);
-    else st = launch_gemm_lds<128, 128, 2, 4, 64, 4, 0, 1, 0>(g1, per_pattern, s);
+      if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
+      else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
+      else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2, 1>(g, per_pattern, s);
+      else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2, 1>(g, per_pattern, s);
+    } else if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);      // many rows, few ranks
+    else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);
+    else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 4, 64, 4, 0, 1, 0>(g, per_pattern, s);
+    else if (tile == T128x256) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0, 0, 1, 1>(g, per_pattern, s);
+    else st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g, per_pattern, s);
+    if (st != PARSE_OK) return st;
   }
-  if (st != PARSE_OK) return st;
 
+  auto tiles2 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].m + bn - 1) / bn; return t * token_tiles(rows, P, bm); };
   // Second product: 256 x 256 tiles where their number is as good as known and they fill their rounds, or there are many; else 128 x 256,
   // two to a compute unit, whose stores and starts overlap and whose last round is shorter; smaller tiles as these run out
   // (both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
-  // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25).
+  // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25; 1533 rows of 40
+  // prompts x 1024 columns 21 / 19 / 16 / 15 / 17).
   const long long u256 = tiles2(256, 256);
-  const bool full = even && (double)u256 >= 0.88 * 256 * rounds(u256, 256);
+  const bool full = rows % P == 0 && rows / P % 256 == 0 && (double)u256 >= 0.88 * 256 * ((u256 + 255) / 256);
   if (full || u256 >= 2048) {
     if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
     return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
   }
   if (tiles2(128, 256) >= 384) return launch_gemm_lds<128, 256, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
   if (tiles2(128, 128) >= 384) return launch_gemm_lds<128, 128, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
-  if (slices64 && tiles2(64, 128) <= 256) return launch_gemm_lds<64, 64, 2, 2, 64, 4, 1, 0, 1>(g2, per_pattern, s);
+  if (slices64 && tiles2(64, 128) <= 160) return launch_gemm_lds<64, 64, 2, 2, 64, 4, 1, 0, 1>(g2, per_pattern, s);
   return launch_gemm_lds<64, 128, 2, 2, 32, 4, 1, 0, 1>(g2, per_pattern, s);
 }
 

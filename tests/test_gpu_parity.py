@@ -1574,9 +1574,24 @@ def test_decode_many_sequences(n, shapes, rows):
     # second product: 256 x 256 tiles with slices of 64 and of 32
     (64, 4096, 64, [4096]),
     (64, 4096, 96, [2048, 2048]),
-    # up to 256 rows with a long reduction: slices, added by a second launch
+    # short batches with a long reduction: slices, added by a second launch
     (4096, 128, 96, [77]),
     (4160, 64, 64, [3, 1, 130]),
+    # the same tiles with reductions of more than twice the stages of their ring, no multiple of them: first products of up to 4096
+    # rows (64 x 64; 64 x 128, in both calls 128 x 128; 128 x 256; 128 x 128, 128 x 256 with padding left out), ...
+    (576, 96, 640, [70, 1]),
+    (704, 512, 768, [2048]),
+    (448, 256, 2304, [2000]),
+    (640, 1280, 1024, [700, 1, 129, 1000, 127, 128, 900]),
+    # ... beyond (64 x 64; 64 x 128, 128 x 128; 128 x 128, 128 x 256; 128 x 256, 256 x 256), ...
+    (576, 96, 128, [1500, 2800, 1]),
+    (576, 96, 256, [1500, 2800, 1]),
+    (640, 64, 768, [64, 4097, 300]),
+    (448, 64, 1792, [4200]),
+    # ... and second products (256 x 256 with slices of 64 and of 32; 128 x 128, 128 x 256)
+    (64, 4096, 320, [4096]),
+    (64, 4096, 352, [2048, 2048]),
+    (64, 2080, 320, [5000]),
 ])
 def test_prefill_planned_tiles(n, m, rS, lengths):
     """Every tile the planned products choose from, with prompts that leave tiles of nothing but padding between them and a prompt
@@ -1687,3 +1702,29 @@ def test_decode_of_few_sequences_keeps_infinite_products(n, B):
     hit, free = np.flatnonzero(pid == 0), np.flatnonzero(pid == 1)
     assert np.array_equal(yn[hit], np.inf * np.sign(xv[hit, n - 1:] * U[5]))
     assert_close(yn[free], (xv[free] @ V[32:].T) @ U[32:], TOL_BF16, "the other group")
+
+
+@pytest.mark.parametrize("n,ranks,rows", [(4096, (96, 1280, 2304), 300), (11008, (128, 1280), 700), (4160, (32, 1056, 96), 1000)])
+def test_prefill_layers_split_differently_in_one_call(n, ranks, rows):
+    """Layers of one call whose first products are cut in different numbers of slices: each gives the bits of its own call."""
+    say(f"planned prefill of {rows} rows: n={n} ranks {ranks} in one call")
+    rng = np.random.default_rng(1701)
+    m, lengths = 64, [rows - 70, 70]
+    off = si.offsets_from_lengths(lengths)
+    X = si.f32_to_bf16_bits(rng.standard_normal((rows, n)).astype(np.float32))
+    xv = si.bf16_bits_to_f32(X).astype(np.float64)
+    layers, pats, refs = [], [], []
+    for rS in ranks:
+        Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((rS, n), (rS, m)))
+        V, U = (si.bf16_bits_to_f32(t).astype(np.float64) for t in (Vt, Ut))
+        refs.append((xv @ V.T) @ U)
+        layer = pa.layer_to_mfma16(pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, rS, 1, pa.PARSE_ROWMAJOR))
+        layers.append(layer)
+        pats.append(pa.Patterns(1, 2, *pa.pack_patterns(layer, i32(np.zeros((2, 1))), 1, 1, None, None, 2)))
+    Xd, offd, pid = upload_tokens(X, "bf16"), i32(off), i32(np.arange(2))
+    both = prefill_multi_guarded(layers, pats, Xd, offd, pid)
+    for l, ref in enumerate(refs):
+        y = forward_guarded(pa.PARSE_PREFILL, layers[l], pats[l].with_schedule(pa.PARSE_SCHED_PLANNED), Xd, offd, pid)
+        torch.cuda.synchronize()
+        assert_close(y.float().cpu().numpy().astype(np.float64), ref, TOL_BF16, f"layer {l}")
+        assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in one call"
