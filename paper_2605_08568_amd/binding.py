@@ -152,10 +152,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # not a public name: the stream object serves without it
+
+
 def _stream():
     """Handle of the current stream of the current device (the number itself: building torch's stream object around it
     takes 1.7 us, several times per step)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def bf16_from_bits(bits: np.ndarray, device="cuda") -> torch.Tensor:

@@ -317,3 +317,12 @@ def test_decode_workspace_of_a_larger_batch_covers_the_smaller_ones():
     assert q[191] == q[-1]                                        # 192 sequences are the most that go together
     two = (B._Layer * 2)(L, L)
     assert lib.parse_lowrank_decode_multi_workspace_bytes(two, 2) > q[-1]
+
+
+def test_stream_handle_without_the_private_name(monkeypatch):
+    """The handle comes from the public stream object where torch does not offer the raw one."""
+    class Stream:
+        cuda_stream = 4711
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
+    assert B._stream() == 4711
