@@ -353,9 +353,9 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_zv: z for a handful of sequences (B <= 4), on the vector units.  With one to four sequences the 32-wide N side
-// of the matrix instruction is almost empty and, worse, a 32-rank block per workgroup leaves most compute units without
-// work (one sequence selects k groups: a 4096x4096 layer with 8 groups of 96 ranks has 24 blocks for 256 units).  Here a
+// decode_zv: z for a handful of sequences (B <= 4; which calls of two to four come here is decided where the kernels are launched),
+// on the vector units.  With one to four sequences the 32-wide N side of the matrix instruction is almost empty and, worse, a
+// 32-rank block per workgroup leaves most compute units without work (one sequence selects k groups: a 4096x4096 layer with 8 groups of 96 ranks has 24 blocks for 256 units).  Here a
 // workgroup owns EIGHT ranks of a block over the whole reduction range: in the operand order the 16-byte pieces of 8
 // consecutive ranks are 128 contiguous bytes, so a wavefront instruction reads 8 such lines (4 reduction steps x 2
 // halves), every line exactly once in the launch.  Lane (step s of 4, half q, rank j of 8) multiplies its 8 factor values
@@ -576,8 +576,8 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_yv: y for a handful of sequences (B <= 4), on the vector units -- the counterpart of decode_zv.  decode_y feeds
-// z to the matrix cores as a 32-sequence operand (1 KiB per reduction block whatever B is) that every workgroup re-reads;
+// decode_yv: y for a handful of sequences (B <= 4, while there is little to do), on the vector units -- the counterpart of
+// decode_zv.  decode_y feeds z to the matrix cores as a 32-sequence operand (1 KiB per reduction block whatever B is) that every workgroup re-reads;
 // here z is a few values per rank: a workgroup copies the B sequences' pieces of the used reduction blocks into LDS once
 // (16 bytes per block half and sequence) and then streams nothing but Ut.  Workgroup = 8 * CG consecutive output columns
 // of one layer (CG = 2 or 4 groups of 8 columns: 128-byte lines of the operand order, each read once in the launch);

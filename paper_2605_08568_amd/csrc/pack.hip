@@ -15,9 +15,13 @@ constexpr size_t kCopyChunk = (size_t)kCopyThreads * kCopyUnroll * 16;  // 32 Ki
 constexpr int kPackWindow = 2048;   // patterns whose work list a workgroup holds in LDS at a time
 
 // Bound by HBM.  The slabs are read with ordinary loads (several patterns of a batch select the same group: the later reads
-// find it in the last-level cache) and the copies, which nothing reads before the next launch and which are larger than any
-// cache on a batch that misses, are written past the caches: 20 patterns of 768 ranks of a 4096 x 4096 layer 78 -> 54 us,
-// the step 276 -> 239 (the other way round, loads past the caches and ordinary stores, it was; ordinary both 262).
+// find it in the last-level cache) and the copies, which nothing reads before the next launch, are written past the caches: 20
+// patterns of 768 ranks of a 4096 x 4096 layer 78 -> 54 us, the step 276 -> 239 (the other way round, loads past the caches and
+// ordinary stores, it was; ordinary both 262).  With few new patterns the copies would still be in the last-level cache for the
+// forward call, so that ordinary stores win by 1-3 us up to about 70 MB of copies and lose beyond.  Aggregation and a forward call of
+// 200-token prompts, us, stores past the caches / ordinary / as it was: 768 ranks of a 4096 x 4096 layer, 1 new pattern 26.2 /
+// 26.8 / 27.6, 2 40.2 / 39.2 / 39.8, 4 49.3 / 47.4 / 52.4, 8 72 / 74 / 77, 16 117 / 143 / 155; 1280 ranks of 4096 x 11008, 1 53.2 / 50.4 /
+// 54.0, 2 86.7 / 85.8 / 88.7, 4 129 / 130 / 139, 24 569 / 606 / 664.
 // A fixed grid walks the work list: every workgroup first lists (in LDS) the patterns that have anything to
 // copy -- a batch whose prompts all hit the cache ends here, after one pass over the hit flags -- then takes
 // every gridDim.x-th task; a task = (listed pattern, one of its 2k slabs, one 32 KiB chunk of the slab).

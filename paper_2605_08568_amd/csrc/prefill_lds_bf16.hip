@@ -649,7 +649,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   // prompts x 1024 columns 21 / 19 / 16 / 15 / 17).
   const long long u256 = tiles2(256, 256);
   const bool full = rows % P == 0 && rows / P % 256 == 0 && (double)u256 >= 0.88 * 256 * ((u256 + 255) / 256);
-  if (full || u256 >= 2048) {
+  if (full || u256 >= 1792) {
     if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
     return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
   }

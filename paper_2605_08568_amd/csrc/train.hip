@@ -335,7 +335,8 @@ extern "C" {
 
 size_t parse_router_grad_workspace_bytes(const parse_layer *L, int32_t rows, int32_t P) {
   if (!L || rows <= 0 || P <= 0 || L->R <= 0 || L->G <= 0 || L->m <= 0) return 0;
-  // (room for two bf16 products over all ranks; their reduced product takes a quarter of it)
+  // (the middle term is room for two bf16 products over all ranks, which callers' sizes count on; their reduced product, the fp32
+  // sums over 8 ranks, takes an eighth of it)
   return round_up((size_t)rows * L->m * 2, 256) + 2 * round_up((size_t)rows * L->R * 2, 256) +
          round_up((size_t)rows * sizeof(float), 256) + round_up((size_t)P * L->G * sizeof(float), 256) + 256;
 }
