@@ -310,9 +310,9 @@ int parse_bucket_and_plan(const int32_t *subset, int32_t P, int32_t k, int32_t s
  * for presence only: everything the kernels need from them is in the plan).
  *   workspace  device, >= parse_lowrank_prefill_planned_workspace_bytes(layer, rows, P, k, n_patterns): the
  *              intermediate of the padded virtual rows, in operand order; for batches of at most 1024 token rows
- *              (n >= 1024) also the fp32 partial sums of the first product, whose reduction over n is then cut in
- *              2..8 slices (one more small launch adds them in slice order; the count depends on rows and n only,
- *              so fused and single-layer calls agree bit for bit). */
+ *              (n >= 1024) also room for the fp32 partial sums of the first product, whose reduction over n may then be cut
+ *              in up to four slices (one more small launch adds them in slice order; the count depends on the batch and the
+ *              layer alone, so fused and single-layer calls agree bit for bit). */
 size_t parse_lowrank_prefill_planned_workspace_bytes(const parse_layer *layer, int32_t rows, int32_t P, int32_t k,
                                                      int32_t n_patterns);
 int parse_lowrank_prefill_planned(const parse_layer *layer, const parse_patterns *patterns, const void *X,
@@ -430,7 +430,8 @@ int parse_lowrank_decode_static(const parse_layer *layer, const parse_patterns *
 
 /* Horizontal fusion for prefill (Sec. 4.4, Eq. 11-12): n_layers (1..4) bf16 PARSE_MFMA16 layers that read the
  * SAME token rows X (equal n) in two launches for all of them -- one stacked first product over the selected
- * ranks of every layer, one batched second product.  patterns[0].schedule chooses for the call:
+ * ranks of every layer, one batched second product (layers of a short batch whose first products are cut in different
+ * numbers of slices: one first product, and one launch that adds the slices, for each number).  patterns[0].schedule chooses for the call:
  *   PARSE_SCHED_AUTO / PARSE_SCHED_PLANNED  the planned tile kernels over one prefill plan built inside the call (one
  *     more small launch; every layer needs the same n_patterns, n % 64 == 0, k*gs % 32 == 0, m % 32 == 0); AUTO falls
  *     back to the two-launch schedule when the shapes or the workspace do not allow it;
