@@ -29,6 +29,7 @@ namespace parse {
 #define PARSE_GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 
 constexpr int LG_MAX_LAYERS = 4;
+typedef __attribute__((ext_vector_type(4))) float f32x4v;
 
 // One product of one layer.  A launch covers up to LG_MAX_LAYERS of them (layers that share their token rows and the
 // plan: the stacked first product and the batched second product of Sec. 4.4, Eq. 11-12): the column tiles of the
@@ -58,47 +59,17 @@ struct LgArgs {
   int ks;                  // SPLIT: slices of the reduction range, one workgroup each
 };
 
-// FORD: factor order, 0 = right factor (operand (rb, kb) at rb*(K/16)+kb), 1 = left factor (operand (kb, cb) at kb*(M/32)+cb).
-// TROW: token operand 1 = row-major rows looked up through the plan's row map (X, or a row-major intermediate),
-//       0 = operand order over the plan's virtual rows.   OROW: output 1 = row-major through the row map, 0 = operand order.
-// First product: <FORD 0, TROW 1, OROW 0>; second product: <FORD 1, TROW 0, OROW 1>.
-// WK 2: two wavefronts share an output tile, each takes half of the steps of every slice, and the halves are added at the end
-// through LDS: a tile of 128 x 128 or less then still has eight wavefronts, two per SIMD, whose waits cover each other
-// (4096 rows x 1024 ranks of eight patterns, n = 4096: both products 97 us with four wavefronts, 82-86 with eight that also
-// take turns, inputs hot; inside a step, inputs cold, the first product 43.3 and 40.6 us).  PING: see there.
-// SPLIT (first product only): the reduction range is cut in a.ks slices, one workgroup each; a workgroup stores its fp32
-// sums as slice s of the partial sums and z_combine adds the slices (in slice order) and rounds -- for launches whose
-// tiles alone would leave most compute units idle (one short prompt).
-template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1, int PING = 0>
-__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
-  static_assert(!SPLIT || (FORD == 0 && OROW == 0), "only the first product is split");
-  constexpr int NW = WM * WN * WK;
-  constexpr int KK = BK / 16;                 // matrix-instruction steps per staged slice
-  constexpr int KW = KK / WK;                 // ... of one wavefront
-  constexpr int TB = BM / WM / 32, FB = BN / WN / 32;
-  constexpr int F_BYTES = BN * BK * 2, T_BYTES = BM * BK * 2, STAGE_BYTES = F_BYTES + T_BYTES;
-  constexpr int NI_F = F_BYTES / 1024, NI_T = T_BYTES / 1024;   // 1 KiB load instructions per slice
-  static_assert(NI_F % NW == 0 && NI_T % NW == 0, "the loads of a slice divide evenly over the wavefronts");
-  static_assert(KW == 2 || KW == 4, "register double-buffering assumes an even number of steps");
-  static_assert(256 % BM == 0, "token tiles subdivide the plan's 256-row tiles");
-  constexpr int LF = NI_F / NW, LT = NI_T / NW, L = LF + LT;
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
-  const int j = lane & 31, q = lane >> 5;
-
-  // tile of this workgroup: consecutive ids share a die (and its L2); within a locality group the token tile runs fastest
-  // The grid is sized for the plan's capacity; the real tile count comes from the plan.  Workgroups past it leave at
-  // once, the others are renumbered over the REAL count so that every die gets its share.
+// Numbering of a launch's tiles: consecutive ids share a die (and its L2); within a locality group the token tile runs fastest.
+// The grid is sized for the plan's capacity; the real tile count comes from the plan.  Workgroups past it leave at once, the others
+// are renumbered over the REAL count so that every die gets its share.  False: nothing to do.
+// a.compact: tiles of nothing but padding (the rows of a pattern come first, its padding last: such a tile starts with it)
+// are left out of the numbering.  Workgroups are dealt to the dies before anything is known of them; with the padding
+// numbered, one die can get more tiles than it has compute units while another one's leave at once (20 prompts of 30-640
+// tokens, 220 of 264 tiles real: the launch took two rounds, 118 us against 82).
+template <int BM>
+__device__ __forceinline__ bool lg_find_tile(const LgArgs &a, const int32_t *rowmap, int bid, int lane, int &tm, int &tn, int &li) {
   const int per = a.gm * a.ntn;
-  const int vrows = a.plan[1];
-  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
-  // a.compact: tiles of nothing but padding (the rows of a pattern come first, its padding last: such a tile starts with it)
-  // are left out of the numbering.  Workgroups are dealt to the dies before anything is known of them; with the padding
-  // numbered, one die can get more tiles than it has compute units while another one's leave at once (20 prompts of 30-640
-  // tokens, 220 of 264 tiles real: the launch took two rounds, 118 us against 82).
-  int n_tiles = (vrows + BM - 1) / BM;
+  int n_tiles = (a.plan[1] + BM - 1) / BM;
   unsigned long long real[4];                  // bit l of real[u]: tile 64 u + l holds tokens
   if (BM < 256 && a.compact) {
     int cnt = 0;
@@ -111,22 +82,16 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
     n_tiles = cnt;
   }
   const int n_real = (n_tiles + a.gm - 1) / a.gm * per;
-  const int ks = SPLIT ? a.ks : 1;
-  const int bid = SPLIT ? (int)blockIdx.x / ks : (int)blockIdx.x, sl = SPLIT ? (int)blockIdx.x % ks : 0;
-  if (bid >= n_real) return;
+  if (bid >= n_real) return false;
   const int tile = xcd_tile(bid, n_real);
   const int g = tile / per, r = tile % per;
-  int tm = g * a.gm + r % a.gm;
-  int tn = r / a.gm;                           // column tile over all layers of the launch
-  int li = 0;
+  tm = g * a.gm + r % a.gm;
+  tn = r / a.gm;                               // column tile over all layers of the launch
+  li = 0;
 #pragma unroll
   for (int i = 1; i < LG_MAX_LAYERS; ++i) li += (i < a.n_layers && tn >= a.L[i].tn_first) ? 1 : 0;
-  const LgLayer &ly = a.L[li];
-  tn -= ly.tn_first;
-  const int K = ly.K, M = ly.M;
-  const int kt0 = SPLIT ? (int)(((long long)(K / BK) * sl) / ks) : 0;           // first slice of BK of this workgroup
-  const int nk = (SPLIT ? (int)(((long long)(K / BK) * (sl + 1)) / ks) : K / BK) - kt0;
-  if (tm >= n_tiles) return;                   // the last locality group may be partial
+  tn -= a.L[li].tn_first;
+  if (tm >= n_tiles) return false;             // the last locality group may be partial
   if (BM < 256 && a.compact) {                 // the tm-th tile that holds tokens
     int at = tm, found = 0;
 #pragma unroll
@@ -140,300 +105,435 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_lds(LgArgs a) {
     }
     tm = __builtin_amdgcn_readfirstlane(found);
   }
-  const int32_t *tile_pat = a.plan + 16;
-  const int pat = tile_pat[tm * BM / 256];
-  if (pat < 0) {
-    // prompts without a valid pattern: the first product has nothing to do, the second one writes zero rows
-    if (OROW == 1 && FORD == 1) {
-      for (int rr = wave; rr < BM; rr += NW) {
-        const int orow = rowmap[tm * BM + rr];
-        if (orow < 0) continue;
-        for (int c = lane * 8; c < BN; c += 512) {
-          const int col = tn * BN + c;
-          if (col < M) *reinterpret_cast<u32x4 *>(ly.O + (size_t)orow * M + col) = u32x4{0, 0, 0, 0};
-        }
-      }
+  return true;
+}
+
+// Rows of a tile whose prompts have no valid pattern: the first product has nothing to do, the second one writes zero rows
+template <int BM, int BN>
+__device__ __forceinline__ void lg_zero_rows(const LgLayer &ly, const int32_t *rowmap, int tm, int tn, int wave, int n_waves, int lane) {
+  for (int rr = wave; rr < BM; rr += n_waves) {
+    const int orow = rowmap[tm * BM + rr];
+    if (orow < 0) continue;
+    for (int c = lane * 8; c < BN; c += 512) {
+      const int col = tn * BN + c;
+      if (col < ly.M) *reinterpret_cast<u32x4 *>(ly.O + (size_t)orow * ly.M + col) = u32x4{0, 0, 0, 0};
     }
+  }
+}
+
+// Lane (j, g) of an accumulator holds factor rows 4 g + (0..3) of token j.  One 16-lane swap of two blocks pairs them up to 8
+// consecutive factor rows, 16 bytes: groups 0 / 2 get rows 0..7 / 8..15 of the first block, groups 1 / 3 of the second.
+__device__ __forceinline__ u32x4 lg_pair(const f32x4v &u, const f32x4v &v) {
+  const u32x2 s0 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(u[0], u[1]), cvt_pk_bf16(v[0], v[1]), false, false);
+  const u32x2 s1 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(u[2], u[3]), cvt_pk_bf16(v[2], v[3]), false, false);
+  return u32x4{s0[0], s1[0], s0[1], s1[1]};
+}
+
+// waits until at most min(later, J) slices of L loads each are outstanding
+template <int J, int L> __device__ __forceinline__ void wait_slices(int later) {
+  if constexpr (J == 0) wait_vm<0>();
+  else if (later >= J) wait_vm<J * L>();
+  else wait_slices<J - 1, L>(later);
+}
+
+// Tile kernel.  What bounds it is power and the issue of loads: a load that writes LDS holds its wavefront until the address unit
+// takes it, so the loads of a slice in a row after the barrier, by every wavefront at once, left the matrix pipes idle for a third
+// of a slice.  Here they are spread between the matrix instructions.  16x16x32 instead of 32x32x16 instructions: twice the
+// reduction per accumulator access, 5-8 % less power (a slice of 64 of a 256 x 256 tile in a loop on normal data, us: matrix
+// instructions and operand reads alone 1.31, loads in a burst 1.60, between the products 1.49, with 16x16x32 1.40).
+//
+// FORD: factor order, 0 = right factor (operand (rb, kb) at rb*(K/16)+kb), 1 = left factor (operand (kb, cb) at kb*(M/32)+cb).
+// TROW: token operand 1 = row-major rows looked up through the plan's row map (X), 0 = operand order over the plan's virtual
+//       rows (Z).   OROW: output 1 = row-major through the row map, 0 = operand order.
+// First product: <FORD 0, TROW 1, OROW 0>, slices of KS = 64 (whole cache lines of a row of X); second product: <1, 0, 1>, KS = 32.
+// A unit of work is 32 reduction indices of a wavefront's share of the tile; its operands are read from LDS into registers during
+// the unit before.  WK 2: two wavefronts share an output tile, each takes one half of every slice, and the halves are added at the
+// end through LDS: a tile of 128 x 128 or less then still has eight wavefronts, two per SIMD, whose waits cover each other.
+// Slice kt + STAGES is requested once slice kt has been read by everybody: from the last unit of slice kt on, whose start has the
+// barrier that also says that slice kt + 1 has landed.
+// SPLIT (first product only): the reduction range is cut in a.ks slices, one workgroup each; a workgroup stores its fp32
+// sums as slice s of the partial sums and z_combine adds the slices (in slice order) and rounds -- for launches whose
+// tiles alone would leave most compute units idle (one short prompt).
+template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1>
+__global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
+  static_assert(!SPLIT || (FORD == 0 && OROW == 0), "only the first product is split");
+  static_assert(WK == 1 || (OROW == 0 && KS == 64), "halves of slices of 64, added for Z");
+  // FORD 1 with a shared head: KS = 32, the head ends between slices
+  static_assert(TROW == 0 || KS == 64, "token rows are swizzled in chunks of 128 bytes");
+  static_assert(256 % BM == 0, "token tiles subdivide the plan's 256-row tiles");
+  constexpr int NW = WM * WN * WK;
+  constexpr int KK = KS / 16;                 // operands of a 32-row block in a slice
+  constexpr int NU = KS / 32 / WK;            // units of a slice
+  constexpr int FB = BN / WN / 16, TB = BM / WM / 16;   // 16-row blocks of a wavefront
+  constexpr int F_BYTES = BN * KS * 2, T_BYTES = BM * KS * 2, STAGE_BYTES = F_BYTES + T_BYTES;
+  constexpr int NI_F = F_BYTES / 1024, NI_T = T_BYTES / 1024;   // 1 KiB load instructions per slice
+  static_assert(NI_F % NW == 0 && NI_T % NW == 0, "the loads of a slice divide evenly over the wavefronts");
+  constexpr int LF = NI_F / NW, LT = NI_T / NW, L = LF + LT, LU = L / NU;
+  static_assert(L % NU == 0 && LU <= FB * TB, "and over the units");
+  static_assert((STAGES - 2) * L + LU < 64, "vmcnt is a 6-bit count");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
+  const int j = lane & 15, g = lane >> 4;
+
+  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  const int ks = SPLIT ? a.ks : 1;
+  const int bid = SPLIT ? (int)blockIdx.x / ks : (int)blockIdx.x, sl = SPLIT ? (int)blockIdx.x % ks : 0;
+  int tm, tn, li;
+  if (!lg_find_tile<BM>(a, rowmap, bid, lane, tm, tn, li)) return;
+  const LgLayer &ly = a.L[li];
+  const int K = ly.K, M = ly.M;
+  const int kt0 = SPLIT ? (int)(((long long)(K / KS) * sl) / ks) : 0;           // first slice of this workgroup
+  const int nk = (SPLIT ? (int)(((long long)(K / KS) * (sl + 1)) / ks) : K / KS) - kt0;
+  const int pat = a.plan[16 + tm * BM / 256];
+  if (pat < 0) {
+    if (OROW == 1) lg_zero_rows<BM, BN>(ly, rowmap, tm, tn, wave, NW, lane);
     return;
   }
   if (BM < 256 && !a.compact && rowmap[tm * BM] < 0) return;
   const uint16_t *Fp = ly.F + (size_t)pat * ly.pattern_stride;
 
-  // ---- per-lane global sources of this wavefront's load instructions; they advance by a constant per slice ----
-  const char *fsrc[LF];
-  const char *fsrc_own[LF];                    // FORD 1 with a shared head: where the pattern's own slices start
-  int fdst[LF];
+  // ---- sources of this wavefront's load instructions; they advance by a constant per slice ----
+  const uint32_t loff = lane * 16;
+  const char *fsrc[LF], *fsrc_own[LF];         // own: FORD 1 with a shared head: where the pattern's own slices start
   const int shb = ly.sh_blocks;
+  const size_t fstep = FORD == 0 ? (size_t)KK * 1024 : (size_t)KK * (M / 32) * 1024;
 #pragma unroll
   for (int i = 0; i < LF; ++i) {
-    const int ins = wave + i * NW;             // instruction id within the factor part, LDS order [fb][kk]
-    const int fb = ins / KK, kk = ins % KK;
-    const int gb = min(tn * (BN / 32) + fb, M / 32 - 1);   // blocks past the end re-read the last one (never stored)
+    const int ins = wave * LF + i, fb = ins / KK, kk = ins % KK;   // LDS order of the factor part: [block of 32][operand]
+    const int gb = min(tn * (BN / 32) + fb, M / 32 - 1);           // blocks past the end re-read the last one (never stored)
     if (FORD == 0) {
-      const char *src = gb < shb ? (const char *)ly.Fsh + (size_t)gb * (K / 16) * 1024
-                                 : (const char *)Fp + (size_t)(gb - shb) * (K / 16) * 1024;
-      fsrc[i] = src + (size_t)kk * 1024 + lane * 16;
+      fsrc[i] = (gb < shb ? (const char *)ly.Fsh + (size_t)gb * (K / 16) * 1024 : (const char *)Fp + (size_t)(gb - shb) * (K / 16) * 1024) +
+                (size_t)kk * 1024 + (SPLIT ? (size_t)kt0 * fstep : 0);
       fsrc_own[i] = fsrc[i];
     } else {
-      fsrc_own[i] = (const char *)Fp + ((size_t)kk * (M / 32) + gb) * 1024 + lane * 16;
-      fsrc[i] = shb > 0 ? (const char *)ly.Fsh + ((size_t)kk * (M / 32) + gb) * 1024 + lane * 16 : fsrc_own[i];
+      fsrc_own[i] = (const char *)Fp + ((size_t)kk * (M / 32) + gb) * 1024;
+      fsrc[i] = shb > 0 ? (const char *)ly.Fsh + ((size_t)kk * (M / 32) + gb) * 1024 : fsrc_own[i];
     }
-    fdst[i] = ins * 1024;
   }
-  const size_t fstep = FORD == 0 ? (size_t)KK * 1024 : (size_t)KK * (M / 32) * 1024;
-  int issued = 0;                              // FORD 1: slices requested so far (a slice of BK = 32 is one 32-rank block)
   const char *tsrc[LT];
-  int tdst[LT];
-  constexpr int CPR = BK * 2 / 16;             // 16-byte chunks per staged X row
 #pragma unroll
   for (int i = 0; i < LT; ++i) {
-    const int ins = wave + i * NW;
-    if (TROW == 0) {
+    const int ins = wave * LT + i;
+    if (TROW == 0) {                           // LDS order: [block of 32][operand]
       const int tb = ins / KK, kk = ins % KK;
-      tsrc[i] = (const char *)ly.Tk + ((size_t)(tm * (BM / 32) + tb) * (K / 16) + kk) * 1024 + lane * 16;
+      tsrc[i] = (const char *)ly.Tk + ((size_t)(tm * (BM / 32) + tb) * (K / 16) + kk) * 1024;
+    } else {                                   // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
+      const int rr = ins * 8 + (lane >> 3);
+      const int row = max(rowmap[tm * BM + rr], 0);                // padding rows read row 0; their results are never stored to Y
+      tsrc[i] = (const char *)ly.Tk + (size_t)row * K * 2 + (((lane & 7) ^ ((rr >> 1) & 7)) * 16) + (SPLIT ? (size_t)kt0 * 128 : 0);
+    }
+  }
+  int issued = 0, dst = 0;                     // slices requested so far; place of the next one
+  auto load = [&](int q) {                     // load q of L of the next slice; the last one moves on
+    if (q < LF) {
+      __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(fsrc[q] + loff), PARSE_LDS_PTR(smem + dst + (wave * LF + q) * 1024), 16, 0, 0);
+      fsrc[q] += fstep;
     } else {
-      constexpr int RPI = 1024 / (BK * 2);     // rows per instruction
-      const int rr = ins * RPI + lane / CPR, cp = lane % CPR;   // LDS position (row, chunk slot)
-      const int sw = CPR == 4 ? ((rr >> 2) & 3) : ((rr >> 1) & 7);
-      const int c = cp ^ sw;                                    // chunk of the row that is stored in that slot
-      int row = rowmap[tm * BM + rr];
-      row = row < 0 ? 0 : row;                 // padding rows read row 0; their results are never stored to Y
-      tsrc[i] = (const char *)ly.Tk + (size_t)row * K * 2 + c * 16;
+      const int i = q - LF;
+      __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(TROW == 0 ? tsrc[i] + loff : tsrc[i]),
+                                       PARSE_LDS_PTR(smem + dst + F_BYTES + (wave * LT + i) * 1024), 16, 0, 0);
+      tsrc[i] += TROW == 0 ? KK * 1024 : KS * 2;
     }
-    tdst[i] = F_BYTES + ins * 1024;
-  }
-  const size_t tstep = TROW == 0 ? (size_t)KK * 1024 : (size_t)BK * 2;
-  if (SPLIT) {
-#pragma unroll
-    for (int i = 0; i < LF; ++i) { fsrc[i] += (size_t)kt0 * fstep; fsrc_own[i] = fsrc[i]; }
-#pragma unroll
-    for (int i = 0; i < LT; ++i) tsrc[i] += (size_t)kt0 * tstep;
-  }
-
-  auto issue = [&](int stage_buf) {
-    char *base = smem + stage_buf * STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < LF; ++i) {
-      __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(fsrc[i]), PARSE_LDS_PTR(base + fdst[i]), 16, 0, 0);
-      fsrc[i] += fstep;
-    }
-#pragma unroll
-    for (int i = 0; i < LT; ++i) {
-      __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(tsrc[i]), PARSE_LDS_PTR(base + tdst[i]), 16, 0, 0);
-      tsrc[i] += tstep;
-    }
-    if (FORD == 1 && BK == 32) {               // the reduction leaves the shared head: continue in the pattern's own block
-      if (++issued == shb) {
+    if (q == L - 1) {
+      dst = dst + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : dst + STAGE_BYTES;
+      ++issued;
+      if (FORD == 1 && issued == shb) {        // the reduction leaves the shared head: continue in the pattern's own block
 #pragma unroll
         for (int i = 0; i < LF; ++i) fsrc[i] = fsrc_own[i];
       }
     }
   };
 
-  // ---- LDS operand addresses (relative to the slice's buffer) ----
-  int foff[FB], toff[TB];
+  // ---- LDS operands: lane (j, g) reads reduction indices 8 g .. 8 g + 7 of row j of a 16-row block ----
+  const int oplane = (g >> 1) * 1024 + (g & 1) * 512 + j * 16;     // in operand order
+  const int f_lane = wn * (FB / 2) * KK * 1024 + oplane;
+  const int t_lane = F_BYTES + (TROW == 0 ? wm * (TB / 2) * KK * 1024 + oplane : wm * TB * 2048 + j * 128 + ((g ^ ((j >> 1) & 7)) * 16));
+  f32x4v acc[FB][TB];
 #pragma unroll
-  for (int i = 0; i < FB; ++i) foff[i] = ((wn * FB + i) * KK) * 1024 + lane * 16;
+  for (int i = 0; i < FB; ++i)
 #pragma unroll
-  for (int t = 0; t < TB; ++t) {
-    if (TROW == 0) toff[t] = F_BYTES + ((wm * TB + t) * KK) * 1024 + lane * 16;
-    else toff[t] = F_BYTES + (wm * TB * 32 + t * 32 + j) * (BK * 2);
-  }
-  auto tchunk = [&](int t, int kk) -> int {    // byte offset of this lane's 16 bytes of token operand (t, kk)
-    if (TROW == 0) return toff[t] + kk * 1024;
-    const int rr = wm * TB * 32 + t * 32 + j;
-    const int sw = CPR == 4 ? ((rr >> 2) & 3) : ((rr >> 1) & 7);
-    return toff[t] + (((kk * 2 + q) ^ sw) * 16);
-  };
-
-  f32x16 acc[TB][FB];
-#pragma unroll
-  for (int t = 0; t < TB; ++t)
-#pragma unroll
-    for (int i = 0; i < FB; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[t][i][e] = 0.f;
-
+    for (int t = 0; t < TB; ++t) acc[i][t] = f32x4v{0.f, 0.f, 0.f, 0.f};
   u32x4 fr[2][FB], tr[2][TB];
-  auto read_ops = [&](int buf, int stage_buf, int step) {
-    const int kk = wk * KW + step;
-    const char *base = smem + stage_buf * STAGE_BYTES;
+  auto read_unit = [&](int buf, int src, int half) {               // half of the slice at src
+    const char *fb = smem + src + f_lane + half * 2048;
 #pragma unroll
-    for (int i = 0; i < FB; ++i) fr[buf][i] = *reinterpret_cast<const u32x4 *>(base + foff[i] + kk * 1024);
+    for (int i = 0; i < FB; ++i) fr[buf][i] = *reinterpret_cast<const u32x4 *>(fb + (i >> 1) * KK * 1024 + (i & 1) * 256);
+    const char *tb = smem + src + (TROW == 0 ? t_lane + half * 2048 : t_lane ^ (half * 64));
 #pragma unroll
-    for (int t = 0; t < TB; ++t) tr[buf][t] = *reinterpret_cast<const u32x4 *>(base + tchunk(t, kk));
+    for (int t = 0; t < TB; ++t)
+      tr[buf][t] = *reinterpret_cast<const u32x4 *>(tb + (TROW == 0 ? (t >> 1) * KK * 1024 + (t & 1) * 256 : t * 2048));
   };
-
   // The compiler treats a load that writes LDS directly like a flat access that may complete out of order with LDS
   // reads, so after one of them every wait it inserts for LDS data is a wait for ALL outstanding LDS reads.  Placed by
-  // the compiler that wait sits between the reads of the next step and the matrix instructions of this step and exposes
-  // the LDS latency once per slice.  Touching this step's operands BEFORE the next step's reads are issued moves the wait
-  // to where nothing is outstanding but reads that had a whole step to finish.
+  // the compiler that wait sits between the reads of the next unit and the matrix instructions of this one and exposes
+  // the LDS latency.  Touching this unit's operands BEFORE the next unit's reads are issued moves the wait
+  // to where nothing is outstanding but reads that had a whole unit to finish.
   auto settle = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < FB; ++i) asm volatile("" ::"v"(fr[buf][i]));
 #pragma unroll
     for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[buf][t]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto products = [&](int buf, int q0, bool more) {                // ... with loads q0 .. q0 + LU - 1 between them
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[buf][i]), as_bf16x8(tr[buf][t]), acc[i][t], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < LU; ++q)
+          if (i * TB + t == (2 * q + 1) * FB * TB / (2 * LU)) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) load(q0 + q);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+      }
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  if constexpr (PING) {
-    // The two wavefronts of a SIMD (w and w + 4) take turns: while one issues the matrix instructions of two steps, the other
-    // reads its operands of the next two from LDS and requests a slice; a barrier ends every turn.  Wavefronts 4..7 run one
-    // turn behind.  A buffer is requested into again one turn after its last reads have returned (both groups wait for
-    // their LDS reads before the barrier), and slice kt+1 has landed for everybody one turn before it is first read.
-    static_assert(NW == 8 && KW % 2 == 0, "two wavefronts per SIMD");
-    const int grp = wave / 4;
+  // prologue: what the units before the first one would have requested
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s)
-      if (s < nk) issue(s);
-    if (nk >= STAGES - 1) wait_vm<(STAGES - 2) * L>(); else wait_vm<0>();
-    wg_barrier();
-    if (grp == 1) wg_barrier();
-    for (int kt = 0; kt < nk; ++kt) {
-      const int sb = kt % STAGES;
+  for (int s = 0; s < STAGES; ++s) {
+    if (s < nk) {
 #pragma unroll
-      for (int sub = 0; sub < KW / 2; ++sub) {
-        const bool last = sub == KW / 2 - 1;
-        __builtin_amdgcn_sched_barrier(0);
-        read_ops(0, sb, sub * 2);
-        read_ops(1, sb, sub * 2 + 1);
-        if (sub == 0 && kt + STAGES - 1 < nk) issue((kt + STAGES - 1) % STAGES);
-        __builtin_amdgcn_sched_barrier(0);
-        auto landed = [&]() {
-          const int later = min(kt + STAGES - 1, nk - 1) - (kt + 1);
-          if (later >= STAGES - 2) wait_vm<(STAGES - 2) * L>();
-          else if (STAGES > 3 && later == 1) wait_vm<L>();
-          else wait_vm<0>();
-        };
-        if (last && grp == 1) landed();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wg_barrier();
-        settle(0); settle(1);
-        __builtin_amdgcn_s_setprio(1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int i = 0; i < FB; ++i)
-#pragma unroll
-            for (int t = 0; t < TB; ++t)
-              acc[t][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[c][i]), as_bf16x8(tr[c][t]), acc[t][i], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
-        if (last && grp == 0) landed();
-        wg_barrier();
-      }
+      for (int q = 0; q < (s == STAGES - 1 ? LU : L); ++q) load(q);
     }
-    if (grp == 0) wg_barrier();
-  } else {
-  // prologue: STAGES-1 slices requested, the first one awaited, one more requested
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nk) issue(s);
-  if (nk >= STAGES - 1) wait_vm<(STAGES - 2) * L>(); else wait_vm<0>();
+  }
+  if (nk >= STAGES) wait_vm<(STAGES - 2) * L + LU>(); else wait_vm<0>();
   wg_barrier();
-  if (STAGES - 1 < nk) issue((STAGES - 1) % STAGES);
-  read_ops(0, 0, 0);
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const int sb = kt % STAGES;
-#pragma unroll
-    for (int s = 0; s < KW; ++s) {
-      const int cur = s & 1;
-      settle(cur);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s < KW - 1) {
-        read_ops(cur ^ 1, sb, s + 1);
-      } else if (kt + 1 < nk) {
-        // hand-over: slice kt+1 must have landed for every wavefront; slice kt's buffer is free after the barrier
-        const int later = min(kt + STAGES - 1, nk - 1) - (kt + 1);   // slices requested after kt+1
-        if (later >= STAGES - 2) wait_vm<(STAGES - 2) * L>();
-        else if (STAGES > 3 && later == 1) wait_vm<L>();
-        else wait_vm<0>();
-        wg_barrier();
-        if (kt + STAGES < nk) issue(sb);
-        read_ops(cur ^ 1, (kt + 1) % STAGES, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < FB; ++i)
-#pragma unroll
-        for (int t = 0; t < TB; ++t)
-          acc[t][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[cur][i]), as_bf16x8(tr[cur][t]), acc[t][i], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+  int src = 0;                                 // place of the slice that is read
+  read_unit(0, src, wk);
+  auto hand_over = [&](bool steady, int kt) {  // slice kt + 1 has landed for everybody, slice kt has been read by everybody
+    if (steady) wait_vm<(STAGES - 2) * L>(); else wait_slices<STAGES - 2, L>(min(kt + STAGES - 1, nk - 1) - (kt + 1));
+    wg_barrier();
+    src = src + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : src + STAGE_BYTES;
+  };
+  // the units of slice kt (NU 1: p its parity); steady: slice kt + STAGES exists.  The loop over those has no branches: between
+  // the barriers of a 128 x 128 tile a wavefront has but sixteen products, and every taken branch delays all eight of them
+  auto slice = [&](bool steady, int p, int kt) {
+    if (NU == 2) {
+      settle(0);
+      read_unit(1, src, 1);
+      products(0, LU, steady || kt - 1 + STAGES < nk);
+      settle(1);
+      if (steady || kt + 1 < nk) { hand_over(steady, kt); read_unit(0, src, 0); }
+      products(1, 0, steady || kt + STAGES < nk);
+    } else {
+      settle(p);
+      if (steady || kt + 1 < nk) { hand_over(steady, kt); read_unit(p ^ 1, src, wk); }
+      products(p, 0, steady || kt + STAGES < nk);
     }
+  };
+  int kt = 0;
+  for (; kt + STAGES + 1 < nk; kt += 2) {
+    slice(true, 0, kt);
+    slice(true, 1, kt + 1);
+  }
+  for (; kt < nk; kt += 2) {
+    slice(false, 0, kt);
+    if (kt + 1 < nk) slice(false, 1, kt + 1);
   }
 
-  }
   if constexpr (WK == 2) {
     // the two halves of the reduction: each takes half of the accumulators over from the other (the staged slices are dead)
-    float *ex = reinterpret_cast<float *>(smem) + (size_t)(wave % (WM * WN)) * (TB * FB * 1024) + lane;
+    float *ex = reinterpret_cast<float *>(smem) + (size_t)(wave % (WM * WN)) * (FB * TB * 256) + lane * 4;
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < TB; ++t)
+    for (int i = 0; i < FB; ++i)
 #pragma unroll
-      for (int i = 0; i < FB; ++i)
-        if ((t * FB + i) * 2 / (TB * FB) != wk) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) ex[((t * FB + i) * 16 + e) * 64] = acc[t][i][e];
-        }
+      for (int t = 0; t < TB; ++t)
+        if (i * 2 / FB != wk) *reinterpret_cast<f32x4v *>(ex + (i * TB + t) * 256) = acc[i][t];
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < TB; ++t)
+    for (int i = 0; i < FB; ++i)
 #pragma unroll
-      for (int i = 0; i < FB; ++i)
-        if ((t * FB + i) * 2 / (TB * FB) == wk) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[t][i][e] += ex[((t * FB + i) * 16 + e) * 64];
-        }
+      for (int t = 0; t < TB; ++t)
+        if (i * 2 / FB == wk) acc[i][t] += *reinterpret_cast<const f32x4v *>(ex + (i * TB + t) * 256);
   }
-  // ---- output: lane (j, q) of acc[t][i] holds token t*32+j, factor rows i*32 + 8*band + 4*q + (0..3) ----
-#pragma unroll
-  for (int t = 0; t < TB; ++t) {
-    const int vrow = tm * BM + (wm * TB + t) * 32 + j;
-    int orow = -1;
-    if (OROW == 1) orow = rowmap[vrow];
+  if (OROW == 0) {                             // Z operands: two token blocks together are one operand, lane's piece at lane * 16
 #pragma unroll
     for (int i = 0; i < FB; ++i) {
-      const int gb = tn * (BN / 32) + wn * FB + i;     // 32-row factor block of the whole matrix
-      if (WK == 2 && (t * FB + i) * 2 / (TB * FB) != wk) continue;
+      const int kb = (tn * BN + wn * FB * 16) / 16 + i;            // 16 factor rows = one operand of the second product
+      if (kb >= M / 16 || (WK == 2 && i * 2 / FB != wk)) continue;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (SPLIT) {   // the same exchange on the fp32 sums: lane (j, q) ends up with the 8 consecutive factor rows of its token
-          float w8[8];
+      for (int t = 0; t < TB; t += 2) {
+        const int tbg = tm * (BM / 32) + (wm * TB + t) / 2;
+        if (SPLIT) {                           // the same exchange on the fp32 sums
+          float *dst8 = ly.Pz + (((size_t)sl * (a.cap * 8) + tbg) * (M / 16) + kb) * 512 + lane * 8;
+          f32x4v lo, hi;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[t][i][(2 * h) * 4 + e]),
-                                                             __float_as_uint(acc[t][i][(2 * h + 1) * 4 + e]), false, false);
-            w8[e] = __uint_as_float(sw[0]); w8[4 + e] = __uint_as_float(sw[1]);
+            const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][t][e]), __float_as_uint(acc[i][t + 1][e]), false, false);
+            lo[e] = __uint_as_float(sw[0]); hi[e] = __uint_as_float(sw[1]);
           }
-          if (gb < M / 32) {
-            const int tbg = tm * (BM / 32) + wm * TB + t;
-            float *dst = ly.Pz + (((size_t)sl * (a.cap * 8) + tbg) * (M / 16) + gb * 2 + h) * 512 + lane * 8;
-            *reinterpret_cast<float4 *>(dst) = float4{w8[0], w8[1], w8[2], w8[3]};
-            *reinterpret_cast<float4 *>(dst + 4) = float4{w8[4], w8[5], w8[6], w8[7]};
-          }
-          continue;
-        }
-        const uint32_t p0x = cvt_pk_bf16(acc[t][i][(2 * h) * 4 + 0], acc[t][i][(2 * h) * 4 + 1]);
-        const uint32_t p0y = cvt_pk_bf16(acc[t][i][(2 * h) * 4 + 2], acc[t][i][(2 * h) * 4 + 3]);
-        const uint32_t p1x = cvt_pk_bf16(acc[t][i][(2 * h + 1) * 4 + 0], acc[t][i][(2 * h + 1) * 4 + 1]);
-        const uint32_t p1y = cvt_pk_bf16(acc[t][i][(2 * h + 1) * 4 + 2], acc[t][i][(2 * h + 1) * 4 + 3]);
-        // the upper 32 lanes of band 2h are exchanged with the lower 32 lanes of band 2h+1: afterwards lane (j, q)
-        // holds the 8 consecutive factor rows gb*32 + 16h + 8q + (0..7) of its token
-        const u32x2 sx = __builtin_amdgcn_permlane32_swap(p0x, p1x, false, false);
-        const u32x2 sy = __builtin_amdgcn_permlane32_swap(p0y, p1y, false, false);
-        const u32x4 w = {sx[0], sy[0], sx[1], sy[1]};
-        if (gb < M / 32) {
-          if (OROW == 0) {   // Z operand (token block, reduction block gb*2 + h), lane's piece at lane*16
-            const int tbg = tm * (BM / 32) + wm * TB + t;
-            *reinterpret_cast<u32x4 *>((char *)ly.O + ((size_t)tbg * (M / 16) + gb * 2 + h) * 1024 + lane * 16) = w;
-          } else if (orow >= 0) {
-            *reinterpret_cast<u32x4 *>(ly.O + (size_t)orow * M + gb * 32 + h * 16 + q * 8) = w;
-          }
+          *reinterpret_cast<f32x4v *>(dst8) = lo;
+          *reinterpret_cast<f32x4v *>(dst8 + 4) = hi;
+        } else {
+          *reinterpret_cast<u32x4 *>((char *)ly.O + ((size_t)tbg * (M / 16) + kb) * 1024 + lane * 16) = lg_pair(acc[i][t], acc[i][t + 1]);
         }
       }
     }
+  } else {                                     // rows of Y: two column blocks together, 64 bytes of a row
+    int orow[TB];
+#pragma unroll
+    for (int t = 0; t < TB; ++t) orow[t] = rowmap[tm * BM + (wm * TB + t) * 16 + j];
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+#pragma unroll
+      for (int i = 0; i < FB; i += 2) {
+        const int cb = (tn * BN + wn * FB * 16) / 32 + i / 2;      // block of 32 columns
+        if (cb < M / 32 && orow[t] >= 0)
+          *reinterpret_cast<u32x4 *>(ly.O + (size_t)orow[t] * M + cb * 32 + (g & 1) * 16 + (g >> 1) * 8) = lg_pair(acc[i][t], acc[i + 1][t]);
+      }
+  }
+}
+
+// First product on 256 x 256 tiles, for launches with many of them.  Slices of 64 of both operands would leave room for two only;
+// here token operands are staged in slices of 64, three of them, and factor operands in halves of 32, four of them: 160 KiB, all of
+// the LDS.  Time h runs the products of half h from registers, reads half h + 1 from LDS and requests factor half h + 4 (into the
+// place of half h, read at time h - 1) and half of the token slice three after the one whose last half was read at time h - 1.  At
+// the start of time h everything requested up to time h - 3 has landed (8 loads a wavefront may be outstanding; fewer are requested
+// near the end), so a load has two halves, 2000 cycles, to arrive.  The sums are those of the other tiles, in the same order.
+// 32768 rows x 1024 ranks of eight patterns, n = m = 4096, both products on large tiles: 526 us with slices of 64, two stages and
+// 32x32x16 instructions, 480 now; 1280 ranks, 11008 columns: 1264 and 1160.
+__global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
+  constexpr int F_HALF = 16384, T_SLICE = 32768, T_BASE = 4 * F_HALF;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;     // 128 token rows x 64 factor rows each
+  const int j = lane & 15, g = lane >> 4;
+  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  int tm, tn, li;
+  if (!lg_find_tile<256>(a, rowmap, blockIdx.x, lane, tm, tn, li)) return;
+  const LgLayer &ly = a.L[li];
+  const int K = ly.K, M = ly.M;
+  const int pat = a.plan[16 + tm];
+  if (pat < 0) return;
+  const int nk = K / 64, nh = nk * 2;
+
+  // ---- sources: wavefront w loads factor block w of a half (two operands) and token rows 32 w .. +31 of a slice ----
+  const int gb = min(tn * 8 + wave, M / 32 - 1);         // blocks past the end re-read the last one (never stored)
+  const int shb = ly.sh_blocks;
+  const char *fsrc = gb < shb ? (const char *)ly.Fsh + (size_t)gb * (K / 16) * 1024
+                              : (const char *)(ly.F + (size_t)pat * ly.pattern_stride) + (size_t)(gb - shb) * (K / 16) * 1024;
+  const uint32_t loff = lane * 16;
+  const char *tsrc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int rr = wave * 32 + i * 8 + (lane >> 3);      // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
+    const int row = max(rowmap[tm * 256 + rr], 0);       // padding rows read row 0; their results are never stored to Y
+    tsrc[i] = (const char *)ly.Tk + (size_t)row * K * 2 + (((lane & 7) ^ ((rr >> 1) & 7)) * 16);
+  }
+  int f_dst = wave * 2048, t_dst = T_BASE + wave * 4096; // place of the next half / slice that is requested
+  auto load_f = [&](int i) {                             // operand i of the next half; i == 1 moves on
+    __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(fsrc + i * 1024 + loff), PARSE_LDS_PTR(smem + f_dst + i * 1024), 16, 0, 0);
+    if (i == 1) {
+      fsrc += 2048;
+      f_dst += F_HALF;
+      if (f_dst >= T_BASE) f_dst -= T_BASE;
+    }
+  };
+  auto load_t = [&](int i) {                             // row group i of the next slice; i == 3 moves on
+    __builtin_amdgcn_global_load_lds(PARSE_GLB_PTR(tsrc[i]), PARSE_LDS_PTR(smem + t_dst + i * 1024), 16, 0, 0);
+    tsrc[i] += 128;
+    if (i == 3) {
+      t_dst += T_SLICE;
+      if (t_dst >= T_BASE + 3 * T_SLICE) t_dst -= 3 * T_SLICE;
+    }
+  };
+
+  // ---- LDS operands: as in gemm_lds ----
+  const int f_lane = wn * 4096 + (g >> 1) * 1024 + (g & 1) * 512 + j * 16;         // half: [block of 32][2 operands]
+  const int t_lane = wm * 16384 + j * 128 + ((g ^ ((j >> 1) & 7)) * 16);
+  f32x4v acc[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[i][t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  u32x4 fr[2][4], tr[2][8];
+  int f_rd = 0, t_rd = T_BASE;                           // places of the half / slice that is read next
+  auto read_half = [&](int buf) {                        // buf = parity of the half
+    const char *fb = smem + f_rd + f_lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fr[buf][i] = *reinterpret_cast<const u32x4 *>(fb + (i >> 1) * 2048 + (i & 1) * 256);
+    const char *tb = smem + t_rd + (t_lane ^ (buf * 64));
+#pragma unroll
+    for (int t = 0; t < 8; ++t) tr[buf][t] = *reinterpret_cast<const u32x4 *>(tb + t * 2048);
+    f_rd += F_HALF;
+    if (f_rd >= T_BASE) f_rd -= T_BASE;
+    if (buf == 1) {
+      t_rd += T_SLICE;
+      if (t_rd >= T_BASE + 3 * T_SLICE) t_rd -= 3 * T_SLICE;
+    }
+  };
+  auto settle = [&](int buf) {                           // as in gemm_lds
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(fr[buf][i]));
+#pragma unroll
+    for (int t = 0; t < 8; ++t) asm volatile("" ::"v"(tr[buf][t]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto products = [&](int p, bool more_f, bool more_t) { // one load after every eight products
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[p][i]), as_bf16x8(tr[p][t]), acc[i][t], 0, 0, 0);
+        if (t == 3) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (i < 2) { if (more_f) load_f(i); }
+          else if (more_t) load_t(p == 0 ? i : i - 2);   // even times: the second half of a slice
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // prologue: T0 F0 | F1 T1 | F2 F3, half of T2
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_t(i);
+  load_f(0); load_f(1);
+  load_f(0); load_f(1);
+  if (nk > 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_t(i);
+    load_f(0); load_f(1);
+    load_f(0); load_f(1);
+  }
+  if (nk > 2) { load_t(0); load_t(1); wait_vm<12>(); } else wait_vm<0>();
+  wg_barrier();
+  read_half(0);
+  auto slice = [&](bool steady, int h) {                 // steady: everything that a slice requests exists
+    settle(0);
+    if (steady || h < nh - 4) wait_vm<8>(); else if (h == nh - 4) wait_vm<6>(); else wait_vm<0>();
+    wg_barrier();
+    read_half(1);
+    products(0, steady || h + 4 < nh, steady || h / 2 + 2 < nk);
+    settle(1);
+    if (steady || h + 2 < nh) {
+      if (steady || h < nh - 5) wait_vm<8>(); else wait_vm<2>();
+      wg_barrier();
+      read_half(0);
+    }
+    products(1, steady || h + 5 < nh, steady || h / 2 + 3 < nk);
+  };
+  int h = 0;
+  for (; h < nh - 6; h += 2) slice(true, h);
+  for (; h < nh; h += 2) slice(false, h);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int kb = tn * 16 + wn * 4 + i;       // 16 factor rows = one operand of the second product
+    if (kb >= M / 16) continue;
+#pragma unroll
+    for (int t = 0; t < 8; t += 2)
+      *reinterpret_cast<u32x4 *>((char *)ly.O + ((size_t)(tm * 8 + wm * 4 + t / 2) * (M / 16) + kb) * 1024 + lane * 16) = lg_pair(acc[i][t], acc[i][t + 1]);
   }
 }
 
@@ -472,12 +572,9 @@ __global__ __launch_bounds__(256) void z_combine(LgArgs a) {
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1, int PING = 0>
-static int launch_gemm_lds(LgArgs a, int avg_tiles_per_pattern, hipStream_t s) {
-  constexpr int staged = STAGES * (BM + BN) * BK * 2, sums = WK > 1 ? BM * BN * 4 : 0;
-  constexpr int smem = staged > sums ? staged : sums;
-  auto kern = gemm_lds<BM, BN, WM, WN, BK, STAGES, FORD, TROW, OROW, SPLIT, WK, PING>;
-  static bool attr_done[64] = {false};
+// kern on tiles of BM x BN: the column tiles of the layers are numbered through, the grid covers what the plan can hold
+template <int BM, int BN>
+static int launch_tiles(void (*kern)(LgArgs), int threads, int smem, bool (&attr_done)[64], LgArgs a, int avg_tiles_per_pattern, int slices, hipStream_t s) {
   int dev = 0;
   PARSE_HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return PARSE_EINVAL;
@@ -495,9 +592,22 @@ static int launch_gemm_lds(LgArgs a, int avg_tiles_per_pattern, hipStream_t s) {
   a.gm = gm < 1 ? 1 : (gm > 8 ? 8 : gm);
   a.ngroups = (ntm + a.gm - 1) / a.gm;
   a.compact = BM < 256 && ntm <= 256 && a.compact;
-  hipLaunchKernelGGL(kern, dim3(a.ngroups * a.gm * a.ntn * (SPLIT ? a.ks : 1)), dim3(WM * WN * WK * 64), smem, s, a);
+  hipLaunchKernelGGL(kern, dim3(a.ngroups * a.gm * a.ntn * slices), dim3(threads), smem, s, a);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
+}
+
+template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1>
+static int launch_gemm_lds(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
+  constexpr int staged = STAGES * (BM + BN) * KS * 2, sums = WK > 1 ? BM * BN * 4 : 0;
+  static bool attr_done[64] = {false};
+  return launch_tiles<BM, BN>(gemm_lds<BM, BN, WM, WN, KS, STAGES, FORD, TROW, OROW, SPLIT, WK>, WM * WN * WK * 64,
+                              staged > sums ? staged : sums, attr_done, a, avg_tiles_per_pattern, SPLIT ? a.ks : 1, s);
+}
+
+static int launch_first256(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
+  static bool attr_done[64] = {false};
+  return launch_tiles<256, 256>(gemm_first256, 512, 160 * 1024, attr_done, a, avg_tiles_per_pattern, 1, s);
 }
 
 // Slices of the first product's reduction range that the workspace has room for (1 = no split).
@@ -631,13 +741,13 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
     if (rows <= SHORT_ROWS) {
       if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
       else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
-      else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2, 1>(g, per_pattern, s);
-      else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2, 1>(g, per_pattern, s);
-    } else if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);      // many rows, few ranks
+      else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
+      else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2>(g, per_pattern, s);
+    } else if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 5, 0, 1, 0>(g, per_pattern, s);      // many rows, few ranks
     else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);
-    else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 4, 64, 4, 0, 1, 0>(g, per_pattern, s);
-    else if (tile == T128x256) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0, 0, 1, 1>(g, per_pattern, s);
-    else st = launch_gemm_lds<256, 256, 2, 4, 64, 2, 0, 1, 0>(g, per_pattern, s);
+    else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 4, 64, 5, 0, 1, 0>(g, per_pattern, s);
+    else if (tile == T128x256) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0>(g, per_pattern, s);
+    else st = launch_first256(g, per_pattern, s);
     if (st != PARSE_OK) return st;
   }
 
@@ -649,10 +759,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   // prompts x 1024 columns 21 / 19 / 16 / 15 / 17).
   const long long u256 = tiles2(256, 256);
   const bool full = rows % P == 0 && rows / P % 256 == 0 && (double)u256 >= 0.88 * 256 * ((u256 + 255) / 256);
-  if (full || u256 >= 1792) {
-    if (slices64) return launch_gemm_lds<256, 256, 2, 4, 64, 2, 1, 0, 1>(g2, per_pattern, s);
-    return launch_gemm_lds<256, 256, 2, 4, 32, 4, 1, 0, 1>(g2, per_pattern, s);
-  }
+  if (full || u256 >= 1792) return launch_gemm_lds<256, 256, 2, 4, 32, 5, 1, 0, 1>(g2, per_pattern, s);
   if (tiles2(128, 256) >= 384) return launch_gemm_lds<128, 256, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
   if (tiles2(128, 128) >= 384) return launch_gemm_lds<128, 128, 2, 2, 32, 3, 1, 0, 1>(g2, per_pattern, s);
   if (slices64 && tiles2(64, 128) <= 160) return launch_gemm_lds<64, 64, 2, 2, 64, 4, 1, 0, 1>(g2, per_pattern, s);
