@@ -12,6 +12,7 @@ constexpr int PF_DEPTH = 8;          // reduction steps of factor operands in fl
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4v;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 // two floats -> packed bfloat16 pair, round to nearest even (hardware conversion)
@@ -30,6 +31,12 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit count");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// waits until at most min(later, J) slices of L loads each are outstanding
+template <int J, int L> __device__ __forceinline__ void wait_slices(int later) {
+  if constexpr (J == 0) wait_vm<0>();
+  else if (later >= J) wait_vm<J * L>();
+  else wait_slices<J - 1, L>(later);
 }
 // barrier without the fences of __syncthreads(): those would wait for ALL outstanding loads, also the slices
 // requested ahead.  The explicit vmcnt wait before it covers exactly the slice that is about to be read.

@@ -29,7 +29,6 @@ namespace parse {
 #define PARSE_GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 
 constexpr int LG_MAX_LAYERS = 4;
-typedef __attribute__((ext_vector_type(4))) float f32x4v;
 
 // One product of one layer.  A launch covers up to LG_MAX_LAYERS of them (layers that share their token rows and the
 // plan: the stacked first product and the batched second product of Sec. 4.4, Eq. 11-12): the column tiles of the
@@ -127,13 +126,6 @@ __device__ __forceinline__ u32x4 lg_pair(const f32x4v &u, const f32x4v &v) {
   const u32x2 s0 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(u[0], u[1]), cvt_pk_bf16(v[0], v[1]), false, false);
   const u32x2 s1 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(u[2], u[3]), cvt_pk_bf16(v[2], v[3]), false, false);
   return u32x4{s0[0], s1[0], s0[1], s1[1]};
-}
-
-// waits until at most min(later, J) slices of L loads each are outstanding
-template <int J, int L> __device__ __forceinline__ void wait_slices(int later) {
-  if constexpr (J == 0) wait_vm<0>();
-  else if (later >= J) wait_vm<J * L>();
-  else wait_slices<J - 1, L>(later);
 }
 
 // Tile kernel.  What bounds it is power and the issue of loads: a load that writes LDS holds its wavefront until the address unit

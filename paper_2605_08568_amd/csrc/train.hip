@@ -58,30 +58,27 @@ __global__ __launch_bounds__(256) void train_residual(const uint16_t *__restrict
 // tile (BM tokens x BN ranks) of both, one after the other through one pipeline, multiplies the two accumulators in
 // registers and writes only the fp32 sums over 8 consecutive ranks, W[R/8][rows]: the two intermediates (2 x rows x R)
 // never exist, are not rounded, and are not read back.
-// Bound by the matrix cores and the load path into LDS.  Both operands are staged in LDS by loads that write LDS directly
-// (factors in operand order, 1 KiB per instruction; token rows row-major with their 16-byte chunks XOR-swizzled on the way
-// in), STAGES slices of BK in rotation, one barrier per slice.  The slices of the second product follow those of the
-// first in the same ring: nothing drains between the two.
+// Bound by power, the issue of loads and the matrix cores, and built like the tile kernel of the prefill (prefill_lds_bf16.hip):
+// both operands staged in LDS by loads that write LDS directly (factors in operand order, 1 KiB per instruction; token rows
+// row-major with their 16-byte chunks XOR-swizzled on the way in), STAGES slices of 64 in rotation, the loads spread between
+// 16x16x32 products, one barrier per slice, no branches in the steady part but the one where the second product's operands begin.
+// The slices of the second product follow those of the first in the same ring: nothing drains between the two.
 // Measured at 4096 rows, n = m = 4096, R = 2048: the two separate products and the pass over their outputs took 90 + 90 +
-// 19 us, this kernel 139-156 us (137 GFLOP).
-typedef __attribute__((ext_vector_type(2))) uint32_t tr_u32x2;
-
-template <int BM, int BN, int WM, int WN, int BK, int STAGES>
-__global__ __launch_bounds__(WM * WN * 64) void train_pair(TrainPair a) {
+// 19 us; this kernel 109-120 us (137 GFLOP), 139-156 with 32x32x16 products and the loads of a slice in a row.
+template <int BM, int BN, int WM, int WN, int STAGES>
+__global__ __launch_bounds__(WM * WN * 64, 2) void train_pair(TrainPair a) {
   constexpr int NW = WM * WN;
-  constexpr int KK = BK / 16;
-  constexpr int TB = BM / WM / 32, FB = BN / WN / 32;
-  constexpr int F_BYTES = BN * BK * 2, T_BYTES = BM * BK * 2, STAGE_BYTES = F_BYTES + T_BYTES;
+  constexpr int FB = BN / WN / 16, TB = BM / WM / 16;          // 16-row blocks of a wavefront
+  constexpr int F_BYTES = BN * 128, T_BYTES = BM * 128, STAGE_BYTES = F_BYTES + T_BYTES;
   constexpr int NI_F = F_BYTES / 1024, NI_T = T_BYTES / 1024;
   static_assert(NI_F % NW == 0 && NI_T % NW == 0, "the loads of a slice divide evenly over the wavefronts");
-  static_assert(KK == 2 || KK == 4, "register double-buffering assumes an even number of steps");
-  constexpr int LF = NI_F / NW, LT = NI_T / NW, L = LF + LT;
-  constexpr int CPR = BK * 2 / 16, RPI = 1024 / (BK * 2);      // 16-byte chunks per staged row, rows per instruction
+  constexpr int LF = NI_F / NW, LT = NI_T / NW, L = LF + LT, LU = L / 2;
+  static_assert(L % 2 == 0 && (STAGES - 2) * L + LU < 64, "and over the two halves; vmcnt is a 6-bit count");
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int j = lane & 31, q = lane >> 5;
+  const int j = lane & 15, g = lane >> 4;
   // up to 8 token tiles run through a rank tile before the next one: a die's consecutive tiles share both operands in its L2
   const int ntm = (a.rows + BM - 1) / BM, ntn = (a.R + BN - 1) / BN;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -90,154 +87,136 @@ __global__ __launch_bounds__(WM * WN * 64) void train_pair(TrainPair a) {
   const int nblk = a.R / 32;
 
   // sources of this wavefront's load instructions in the two products
-  const char *fsrc[LF], *tsrc[LT], *fnext[LF], *tnext[LT];
-  int fdst[LF], tdst[LT];
-#pragma unroll
-  for (int i = 0; i < LF; ++i) {
-    const int ins = wave + i * NW, fb = ins / KK, kk = ins % KK;
-    const int gb = min(tn * (BN / 32) + fb, nblk - 1);         // blocks past the end re-read the last one (never stored)
-    fsrc[i] = (const char *)a.V + ((size_t)gb * (a.n / 16) + kk) * 1024 + lane * 16;
-    fnext[i] = (const char *)a.U + ((size_t)gb * (a.m / 16) + kk) * 1024 + lane * 16;
-    fdst[i] = ins * 1024;
-  }
-#pragma unroll
-  for (int i = 0; i < LT; ++i) {
-    const int ins = wave + i * NW;
-    const int rr = ins * RPI + lane / CPR, cp = lane % CPR;    // LDS position (row, chunk slot)
-    const int sw = CPR == 4 ? ((rr >> 2) & 3) : ((rr >> 1) & 7);
-    const size_t row = min(tm * BM + rr, a.rows - 1);          // rows past the end re-read the last one (never stored)
-    tsrc[i] = (const char *)a.X + row * a.n * 2 + (cp ^ sw) * 16;
-    tnext[i] = (const char *)a.g + row * a.m * 2 + (cp ^ sw) * 16;
-    tdst[i] = F_BYTES + ins * 1024;
-  }
-  const int nk1 = a.n / BK, nk = nk1 + a.m / BK;
-  int issued = 0;
-  auto issue = [&](int stage_buf) {
-    char *base = smem + stage_buf * STAGE_BYTES;
+  const uint32_t loff = lane * 16;
+  const char *fsrc[LF], *tsrc[LT];
+  auto aim = [&](const uint16_t *F, const uint16_t *T, int K) {
 #pragma unroll
     for (int i = 0; i < LF; ++i) {
-      __builtin_amdgcn_global_load_lds(PARSE_TR_GLB_PTR(fsrc[i]), PARSE_TR_LDS_PTR(base + fdst[i]), 16, 0, 0);
-      fsrc[i] += KK * 1024;
+      const int ins = wave * LF + i, fb = ins / 4, kk = ins % 4;
+      const int gb = min(tn * (BN / 32) + fb, nblk - 1);       // blocks past the end re-read the last one (never stored)
+      fsrc[i] = (const char *)F + ((size_t)gb * (K / 16) + kk) * 1024;
     }
 #pragma unroll
-    for (int i = 0; i < LT; ++i) {
-      __builtin_amdgcn_global_load_lds(PARSE_TR_GLB_PTR(tsrc[i]), PARSE_TR_LDS_PTR(base + tdst[i]), 16, 0, 0);
-      tsrc[i] += BK * 2;
-    }
-    if (++issued == nk1) {                                     // uniform: on to the operands of the second product
-#pragma unroll
-      for (int i = 0; i < LF; ++i) fsrc[i] = fnext[i];
-#pragma unroll
-      for (int i = 0; i < LT; ++i) tsrc[i] = tnext[i];
+    for (int i = 0; i < LT; ++i) {                             // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
+      const int rr = (wave * LT + i) * 8 + (lane >> 3);
+      const size_t row = min(tm * BM + rr, a.rows - 1);        // rows past the end re-read the last one (never stored)
+      tsrc[i] = (const char *)T + row * K * 2 + ((lane & 7) ^ ((rr >> 1) & 7)) * 16;
     }
   };
-  int foff[FB], toff[TB], tsw[TB];
-#pragma unroll
-  for (int i = 0; i < FB; ++i) foff[i] = ((wn * FB + i) * KK) * 1024 + lane * 16;
-#pragma unroll
-  for (int t = 0; t < TB; ++t) {
-    const int rr = (wm * TB + t) * 32 + j;
-    toff[t] = F_BYTES + rr * (BK * 2);
-    tsw[t] = CPR == 4 ? ((rr >> 2) & 3) : ((rr >> 1) & 7);
-  }
+  aim(a.V, a.X, a.n);
+  const int nk1 = a.n / 64, nk = nk1 + a.m / 64;
+  int issued = 0, dst = 0;
+  auto load = [&](int q) {                                     // load q of L of the next slice; the last one moves on
+    if (q < LF) {
+      __builtin_amdgcn_global_load_lds(PARSE_TR_GLB_PTR(fsrc[q] + loff), PARSE_TR_LDS_PTR(smem + dst + (wave * LF + q) * 1024), 16, 0, 0);
+      fsrc[q] += 4096;
+    } else {
+      __builtin_amdgcn_global_load_lds(PARSE_TR_GLB_PTR(tsrc[q - LF]), PARSE_TR_LDS_PTR(smem + dst + F_BYTES + (wave * LT + q - LF) * 1024), 16, 0, 0);
+      tsrc[q - LF] += 128;
+    }
+    if (q == L - 1) {
+      dst = dst + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : dst + STAGE_BYTES;
+      if (++issued == nk1) aim(a.U, a.g, a.m);                 // uniform: on to the operands of the second product
+    }
+  };
+  // LDS operands: lane (j, g) reads reduction indices 8 g .. 8 g + 7 of row j of a 16-row block
+  const int f_lane = wn * (FB / 2) * 4096 + (g >> 1) * 1024 + (g & 1) * 512 + j * 16;
+  const int t_lane = F_BYTES + wm * TB * 2048 + j * 128 + (g ^ ((j >> 1) & 7)) * 16;
   u32x4 fr[2][FB], tr[2][TB];
-  auto read_ops = [&](int buf, int stage_buf, int kk) {
-    const char *base = smem + stage_buf * STAGE_BYTES;
+  int src = 0;
+  auto read_half = [&](int half) {
+    const char *fb = smem + src + f_lane + half * 2048, *tb = smem + src + (t_lane ^ (half * 64));
 #pragma unroll
-    for (int i = 0; i < FB; ++i) fr[buf][i] = *reinterpret_cast<const u32x4 *>(base + foff[i] + kk * 1024);
+    for (int i = 0; i < FB; ++i) fr[half][i] = *reinterpret_cast<const u32x4 *>(fb + (i >> 1) * 4096 + (i & 1) * 256);
 #pragma unroll
-    for (int t = 0; t < TB; ++t) tr[buf][t] = *reinterpret_cast<const u32x4 *>(base + toff[t] + (((kk * 2 + q) ^ tsw[t]) * 16));
+    for (int t = 0; t < TB; ++t) tr[half][t] = *reinterpret_cast<const u32x4 *>(tb + t * 2048);
   };
-  // this step's operands are touched before the next step's LDS reads are issued: the wait the compiler places there then
-  // covers reads that had a whole step to finish
-  auto settle = [&](int buf) {
+  // this half's operands are touched before the next half's LDS reads are issued: the wait the compiler places there then
+  // covers reads that had a whole half to finish
+  auto settle = [&](int half) {
 #pragma unroll
-    for (int i = 0; i < FB; ++i) asm volatile("" ::"v"(fr[buf][i]));
+    for (int i = 0; i < FB; ++i) asm volatile("" ::"v"(fr[half][i]));
 #pragma unroll
-    for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[buf][t]));
+    for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[half][t]));
+    __builtin_amdgcn_sched_barrier(0);
   };
-  f32x16 accz[TB][FB], acct[TB][FB];
+  f32x4v accz[FB][TB], acct[FB][TB];
 #pragma unroll
-  for (int t = 0; t < TB; ++t)
+  for (int i = 0; i < FB; ++i)
+#pragma unroll
+    for (int t = 0; t < TB; ++t) accz[i][t] = acct[i][t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  auto products = [&](f32x4v(&acc)[FB][TB], int half, int q0, bool more) {
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < FB; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { accz[t][i][e] = 0.f; acct[t][i][e] = 0.f; }
+      for (int t = 0; t < TB; ++t) {
+        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[half][i]), as_bf16x8(tr[half][t]), acc[i][t], 0, 0, 0);
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
-    if (s < nk) issue(s);
-  if (nk >= STAGES - 1) wait_vm<(STAGES - 2) * L>(); else wait_vm<0>();
-  wg_barrier();
-  if (STAGES - 1 < nk) issue(STAGES - 1);
-  read_ops(0, 0, 0);
-  int sb = 0;
-  auto slices = [&](f32x16(&acc)[TB][FB], int k0, int k1) {
-    for (int kt = k0; kt < k1; ++kt) {
-      const int sn = sb + 1 == STAGES ? 0 : sb + 1;
-#pragma unroll
-      for (int s = 0; s < KK; ++s) {
-        const int cur = s & 1;
-        settle(cur);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s < KK - 1) {
-          read_ops(cur ^ 1, sb, s + 1);
-        } else if (kt + 1 < nk) {
-          // hand-over: slice kt+1 must have landed for every wavefront; slice kt's buffer is free after the barrier
-          const int later = min(kt + STAGES - 1, nk - 1) - (kt + 1);   // slices requested after kt+1
-          if (later >= STAGES - 2) wait_vm<(STAGES - 2) * L>();
-          else if (STAGES > 3 && later == 1) wait_vm<L>();
-          else wait_vm<0>();
-          wg_barrier();
-          if (kt + STAGES < nk) issue(sb);
-          read_ops(cur ^ 1, sn, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < FB; ++i)
-#pragma unroll
-          for (int t = 0; t < TB; ++t)
-            acc[t][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[cur][i]), as_bf16x8(tr[cur][t]), acc[t][i], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int q = 0; q < LU; ++q)
+          if (i * TB + t == (2 * q + 1) * FB * TB / (2 * LU)) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) load(q0 + q);
+            __builtin_amdgcn_sched_barrier(0);
+          }
       }
-      sb = sn;
-    }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  slices(accz, 0, nk1);
-  slices(acct, nk1, nk);
-  // lane (j, q) of acc[t][i] holds token t*32+j, ranks i*32 + 8*band + 4*q + (0..3) of both products
+  // slice kt + STAGES is requested from the second half of slice kt on, whose start has the barrier that says that everybody has read
+  // slice kt and that slice kt + 1 has landed
+  auto slice = [&](f32x4v(&acc)[FB][TB], bool steady, int kt) {
+    settle(0);
+    read_half(1);
+    products(acc, 0, LU, steady || kt - 1 + STAGES < nk);
+    settle(1);
+    if (steady || kt + 1 < nk) {
+      if (steady) wait_vm<(STAGES - 2) * L>(); else wait_slices<STAGES - 2, L>(min(kt + STAGES - 1, nk - 1) - (kt + 1));
+      wg_barrier();
+      src = src + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : src + STAGE_BYTES;
+      read_half(0);
+    }
+    products(acc, 1, 0, steady || kt + STAGES < nk);
+  };
 #pragma unroll
-  for (int t = 0; t < TB; ++t) {
-    const int row = tm * BM + (wm * TB + t) * 32 + j;
+  for (int s = 0; s < STAGES; ++s) {
+    if (s < nk) {
 #pragma unroll
-    for (int i = 0; i < FB; ++i) {
-      const int gb = tn * (BN / 32) + wn * FB + i;
-      float s[4];
+      for (int q = 0; q < (s == STAGES - 1 ? LU : L); ++q) load(q);
+    }
+  }
+  if (nk >= STAGES) wait_vm<(STAGES - 2) * L + LU>(); else wait_vm<0>();
+  wg_barrier();
+  read_half(0);
+  int kt = 0;
+  for (; kt < nk1 && kt + STAGES < nk; ++kt) slice(accz, true, kt);
+  for (; kt < nk1; ++kt) slice(accz, false, kt);
+  for (; kt + STAGES < nk; ++kt) slice(acct, true, kt);
+  for (; kt < nk; ++kt) slice(acct, false, kt);
+  // lane (j, g) of acc[i][t] holds ranks 16 i + 4 g + (0..3) of token 16 t + j of both products; one 16-lane swap of two token blocks
+  // brings the sums over 4 ranks together: groups 0 / 2 get ranks 0..7 / 8..15 of the first block, 1 / 3 of the second
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        s[b] = accz[t][i][b * 4] * acct[t][i][b * 4];
+  for (int i = 0; i < FB; ++i) {
+    const int b16 = (tn * BN + wn * FB * 16) / 16 + i;
 #pragma unroll
-        for (int e = 1; e < 4; ++e) s[b] += accz[t][i][b * 4 + e] * acct[t][i][b * 4 + e];
+    for (int t = 0; t < TB; t += 2) {
+      float s[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        s[u] = accz[i][t + u][0] * acct[i][t + u][0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) s[u] += accz[i][t + u][e] * acct[i][t + u][e];
       }
-      // the two halves of a band: lane (j, 0) ends up with bands 0 and 1, lane (j, 1) with bands 2 and 3
-      float w[2];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const tr_u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[b]), __float_as_uint(s[b + 2]), false, false);
-        w[b] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-      }
-      if (gb < nblk && row < a.rows) {
-        float *dst = a.W + (size_t)(gb * 4 + q * 2) * a.rows + row;
-        dst[0] = w[0];
-        dst[a.rows] = w[1];
-      }
+      const u32x2 sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[0]), __float_as_uint(s[1]), false, false);
+      const int row = tm * BM + (wm * TB + t + (g & 1)) * 16 + j;
+      if (b16 < nblk * 2 && row < a.rows) a.W[(size_t)(b16 * 2 + (g >> 1)) * a.rows + row] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
   }
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int STAGES>
+template <int BM, int BN, int WM, int WN, int STAGES>
 static int launch_train_pair(const TrainPair &a, hipStream_t s) {
-  constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * 2;
-  auto kern = train_pair<BM, BN, WM, WN, BK, STAGES>;
+  constexpr size_t smem = (size_t)STAGES * (BM + BN) * 128;
+  auto kern = train_pair<BM, BN, WM, WN, STAGES>;
   PARSE_ALLOW_LDS(kern, smem);
   const int grid = ((a.rows + BM - 1) / BM) * ((a.R + BN - 1) / BN);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), smem, s, a);
@@ -245,15 +224,15 @@ static int launch_train_pair(const TrainPair &a, hipStream_t s) {
   return PARSE_OK;
 }
 
-// Tile by how many workgroups it gives a launch.  256 x 128 (eight wavefronts, six slices of 32) moves the fewest bytes
-// per flop and wins once it fills the chip; below that the tile that still fills it wins, and 64 x 64 when none does
-// (whole call, us, 256 x 128 / 128 x 128 / 64 x 64: 4096 rows x 2048 ranks 155 / 181 / 218; 3300 x 1024 128 / 95 / 113;
-// 4000 x 768 273 / 190 / 235; 1024 x 2048 204 / 145 / 113; 16 x 1024 111 / 79 / 47).
+// Tile by how many workgroups it gives a launch.  256 x 128 moves the fewest bytes per flop and wins once it fills the chip; below
+// that the tile that still fills it wins, and 64 x 64 when none does
+// (whole call, us, 256 x 128 / 128 x 128 / 64 x 64: 4096 rows x 2048 ranks 134 / 155 / 206; 3300 x 1024 113 / 83 / 119;
+// 4000 x 768 117 / 86 / 101; 1800 x 2048 109 / 81 / 114; 1024 x 2048 99 / 69 / 64; 16 x 1024 87 / 56 / 32).
 static int forward_train_pair(const TrainPair &a, hipStream_t s) {
   auto wgs = [&](int bm, int bn) { return (long long)((a.rows + bm - 1) / bm) * ((a.R + bn - 1) / bn); };
-  if (wgs(256, 128) >= 192) return launch_train_pair<256, 128, 4, 2, 32, 6>(a, s);
-  if (wgs(128, 128) >= 160) return launch_train_pair<128, 128, 2, 2, 64, 4>(a, s);
-  return launch_train_pair<64, 64, 2, 2, 64, 4>(a, s);
+  if (wgs(256, 128) >= 192) return launch_train_pair<256, 128, 4, 2, 3>(a, s);
+  if (wgs(128, 128) >= 160) return launch_train_pair<128, 128, 2, 4, 4>(a, s);
+  return launch_train_pair<64, 64, 2, 2, 4>(a, s);
 }
 
 // Adds W over the group's pieces of 8 ranks and the prompt's tokens.  grid (G + 1, P), block 256; the last column of
