@@ -71,6 +71,24 @@ struct DecPlanArgs {
 
 __device__ __forceinline__ bf16x8 dec_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// The blocks (of 16 or 32 ranks, `per` to a group) of the groups in use, counted through: one load of the plan puts the used ids
+// in a register of the 64 lanes, a block's place follows by arithmetic and a lane read.  A list in LDS put two barriers and two LDS
+// round trips between the plan and the first factor load: decode_y16 5.5 -> 5.0 and 8.4 -> 7.8 us a launch, decode_y the same.
+// (decode_yv asks for the blocks of four lanes' groups at a time; with lane shuffles in place of its list it was 0.6 us slower.)
+struct DecUsed {
+  int ids, count, per;
+  float inv;
+  __device__ __forceinline__ DecUsed(const DecLayer &ly, int lane, int per_group) : per(per_group), inv(1.0f / (float)per_group) {
+    ids = ly.plan[1 + lane];
+    count = max(0, min(ly.plan[0], ly.G)) * per;
+  }
+  // exact: i < 1024, and (i + 1/2) / per is at least 1/2048 off every integer
+  __device__ __forceinline__ int block(int i) const {        // i the same for all lanes, below count
+    const int g = __builtin_amdgcn_readfirstlane((int)(((float)i + 0.5f) * inv));
+    return max(__builtin_amdgcn_readlane(ids, g), 0) * per + i - g * per;
+  }
+};
+
 // grid = layers, one wavefront each: lane b < B looks at its sequence's k group ids and ORs its bit into the groups'
 // masks (LDS, integer OR: order-free); then the used groups are listed in ascending order by a vote.
 __global__ __launch_bounds__(64) void decode_plan_build(DecPlanArgs a) {
@@ -473,27 +491,17 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
   const DecLayer &ly = a.L[li];
   const uint16_t *__restrict__ Ut = ly.Ut;
   const uint16_t *__restrict__ zf = ly.zf;
-  const int32_t *__restrict__ plan = ly.plan;
   uint16_t *__restrict__ y = ly.y;
-  const int B = a.B, m = ly.m, G = ly.G, gs = ly.gs;
+  const int B = a.B, m = ly.m;
   const int bid = blockIdx.x - ly.y_first;
   __shared__ float red[DY_WAVES][16][64];
-  __shared__ int32_t kb_list[DY_MAXKB];
-  __shared__ int32_t used[DEC_MAXG];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int l32 = lane & 31, q = lane >> 5;
   const int ncb = m / 32;
   const int c0 = bid * NC;
   const int nc = min(NC, ncb - c0);
-  // count and ids come from the plan in one round trip (ids past the count are -1 and not used)
-  const int n_used_raw = plan[0];
-  if (threadIdx.x < DEC_MAXG) used[threadIdx.x] = plan[1 + threadIdx.x];
-  const int n_used = max(0, min(n_used_raw, G));
-  __syncthreads();
-  const int kpg = gs / 16;                 // reduction blocks per group
-  const int total_kb = n_used * kpg;       // selected reduction blocks
-  for (int i = threadIdx.x; i < total_kb; i += DY_THREADS) kb_list[i] = max(used[i / kpg], 0) * kpg + i % kpg;
-  __syncthreads();
+  const DecUsed blocks(ly, lane, ly.gs / 16);        // reduction blocks in use
+  const int total_kb = blocks.count;
   const int k0 = (total_kb * wave) / DY_WAVES, k1 = (total_kb * (wave + 1)) / DY_WAVES;
   const int cnt = k1 - k0;
   const uint16_t *ubase = Ut + ((size_t)c0 * 64 + lane) * 8;
@@ -514,7 +522,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
     u32x4 ur[DY_MAXK][NC], zr[DY_MAXK];
 #pragma unroll
     for (int i = 0; i < DY_MAXK; ++i) {
-      const int kb = kb_list[k0 + min(i, cnt - 1)];
+      const int kb = blocks.block(k0 + min(i, cnt - 1));
 #pragma unroll
       for (int j = 0; j < NC; ++j) ur[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
       zr[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
@@ -531,7 +539,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
       u32x4 uu[DEC_CHUNK][NC], zz[DEC_CHUNK];
 #pragma unroll
       for (int i = 0; i < DEC_CHUNK; ++i) {
-        const int kb = kb_list[k0 + min(c + i, cnt - 1)];
+        const int kb = blocks.block(k0 + min(c + i, cnt - 1));
 #pragma unroll
         for (int j = 0; j < NC; ++j) uu[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
         zz[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
@@ -791,13 +799,10 @@ __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
   const int B = a.B, m = ly.m;
   const int c0 = ((int)blockIdx.x - ly.y_first) * NC, ncb = m / 32;
   __shared__ float red[D16_WAVES][NC][4][64];
-  __shared__ int32_t rb_list[DY_MAXKB / 2];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
-  const int bpg = ly.gs / 32;
-  const int total = max(0, min(ly.plan[0], ly.G)) * bpg;           // 32-rank blocks in use
-  for (int i = threadIdx.x; i < total; i += D16_THREADS) rb_list[i] = max(ly.plan[1 + i / bpg], 0) * bpg + i % bpg;
-  __syncthreads();
+  const DecUsed blocks(ly, lane, ly.gs / 32);                      // 32-rank blocks in use
+  const int total = blocks.count;
   const int cnt = (total - wave + D16_WAVES - 1) / D16_WAVES;
   const char *U = (const char *)ly.Ut + (size_t)(kq >> 1) * ncb * 1024 + ((kq & 1) * 32 + r) * 16;
   const char *Z = (const char *)ly.zf + (kq >> 1) * 1024 + ((kq & 1) * 32 + r) * 16;
@@ -812,7 +817,7 @@ __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
   for (int i = 0; i < NC; ++i) acc[i] = f32x4_acc{0.f, 0.f, 0.f, 0.f};
   u32x4 ur[DEPTH][NC], zr[DEPTH];
   auto request = [&](int d, int s) {
-    const int rb = rb_list[wave + s * D16_WAVES];
+    const int rb = blocks.block(wave + s * D16_WAVES);
 #pragma unroll
     for (int i = 0; i < NC; ++i) ur[d][i] = *reinterpret_cast<const u32x4 *>(U + (size_t)rb * 2 * ncb * 1024 + coff[i]);
     zr[d] = *reinterpret_cast<const u32x4 *>(Z + (size_t)rb * 2048);
