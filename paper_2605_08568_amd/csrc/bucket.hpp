@@ -19,10 +19,58 @@ __device__ __forceinline__ void block_scan_inclusive(int32_t *v, int T) {
   }
 }
 
+// Up to 64 prompts: one wavefront, everything in registers (P readings of a lane in place of scans in LDS, some forty barriers in
+// a workgroup of 256): 3.9 -> 2.1 us for four prompts.  All 64 lanes of the wavefront take part.
+__device__ __forceinline__ void bucket_wave(const int32_t *__restrict__ subset, int P, int k, int stride, int32_t *__restrict__ pattern_id,
+                                            int32_t *__restrict__ perm, int32_t *__restrict__ bucket_off,
+                                            int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
+  const int p = threadIdx.x & 63;
+  const int32_t *mine = subset + (size_t)min(p, P - 1) * stride;
+  uint32_t h = 0x9E3779B9u;
+#pragma unroll 8
+  for (int i = 0; i < k; ++i) {
+    h ^= (uint32_t)mine[i];
+    h *= 0xED558CCDu;
+    h ^= h >> 15;
+  }
+  int first = p;                           // the first prompt with the same subset
+  for (int q = 0; q + 1 < P; ++q) {
+    bool same = q < p && first == p && h == (uint32_t)__builtin_amdgcn_readlane((int)h, q);
+    if (__ballot(same) == 0ull) continue;  // uniform
+    for (int i = 0; i < k; ++i) same = same && subset[(size_t)q * stride + i] == mine[i];
+    if (same) first = q;
+  }
+  const unsigned long long reps = __ballot(p < P && first == p);
+  const int npat = __popcll(reps);
+  const int pid = p < P ? __popcll(reps & ((1ull << first) - 1ull)) : 64;      // rank of the representative
+  int below = 0, upto = 0, rank = 0;       // prompts of earlier patterns; of patterns up to number p; earlier ones of this pattern
+  for (int q = 0; q < P; ++q) {
+    const int other = __builtin_amdgcn_readlane(pid, q);
+    below += other < pid ? 1 : 0;
+    upto += other <= p ? 1 : 0;
+    rank += q < p && other == pid ? 1 : 0;
+  }
+  if (p < P) {
+    perm[below + rank] = p;
+    pattern_id[p] = pid;
+    if (first == p) rep[pid] = p;
+    bucket_off[p + 1] = p < npat ? upto : P;
+    if (p >= npat) rep[p] = -1;
+  }
+  if (p == 0) {
+    bucket_off[0] = 0;
+    *n_patterns = npat;
+  }
+}
+
 __device__ __forceinline__ void bucket_body(const int32_t *__restrict__ subset, int P, int k, int stride,
                                                         int32_t *__restrict__ pattern_id, int32_t *__restrict__ perm,
                                                         int32_t *__restrict__ bucket_off,
                                                         int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
+  if (P <= 64) {                           // uniform
+    if (threadIdx.x < 64) bucket_wave(subset, P, k, stride, pattern_id, perm, bucket_off, n_patterns, rep);
+    return;
+  }
   __shared__ unsigned long long sig[1024];
   __shared__ int32_t scan[1024];   // inclusive scan of "is representative", later of the pattern sizes
   __shared__ int32_t pid[1024];

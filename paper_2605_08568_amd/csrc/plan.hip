@@ -27,12 +27,71 @@ static inline int plan_capacity_tiles(int rows, int P, int n_patterns) {
 }
 static inline size_t plan_words(int cap) { return (size_t)PLAN_HDR + (size_t)((cap + 15) / 16 * 16) + (size_t)cap * PLAN_VT; }
 
+// Up to 32 prompts (PLAN_WAVE_P): every wavefront works the tables out in its registers, lane p for prompt p, by P readings of a
+// lane: no LDS, no barrier, one round trip to memory before the rows are written.  With the buckets in the same launch 5.3 -> 2.5 us for one
+// prompt of 77 tokens, 5.8 -> 4.2 for eight of 512, 7.8 both for twenty ragged ones.
+constexpr int PLAN_WAVE_P = 32;
+__device__ __forceinline__ void plan_wave(const int32_t *__restrict__ tok_offsets, const int32_t *__restrict__ pattern_id, int P, int rows,
+                                          int NP, int cap, int32_t *__restrict__ plan, int block, int nblocks) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  int32_t *tile_pat = plan + PLAN_HDR;
+  int32_t *rowmap = plan + PLAN_HDR + (cap + 15) / 16 * 16;
+  const int max_v = cap * PLAN_VT;
+  const int a = tok_offsets[min(lane, P)], b = tok_offsets[min(lane + 1, P)], v = pattern_id[min(lane, P - 1)];
+  const int off = a < 0 ? 0 : (a > rows ? rows : a), end = b < 0 ? 0 : (b > rows ? rows : b);
+  const int len = lane < P ? max(end - off, 0) : 0;
+  const int pid = v >= 0 && v < NP ? v : NP;               // NP: ids out of range, after all patterns
+  int before = 0, all = 0, lead = 1;                       // rows of the pattern's earlier prompts, of all its prompts; first of them?
+  for (int q = 0; q < P; ++q) {
+    const int opid = __builtin_amdgcn_readlane(pid, q), olen = __builtin_amdgcn_readlane(len, q);
+    const bool same = opid == pid;
+    all += same ? olen : 0;
+    before += same && q < lane ? olen : 0;
+    lead = same && q < lane ? 0 : lead;
+  }
+  const int padded = lane < P && lead ? (all + PLAN_VT - 1) / PLAN_VT * PLAN_VT : 0;
+  int base = 0, total = 0;                                 // first virtual row of the pattern
+  for (int q = 0; q < P; ++q) {
+    const int opad = __builtin_amdgcn_readlane(padded, q);
+    base += __builtin_amdgcn_readlane(pid, q) < pid ? opad : 0;
+    total += opad;
+  }
+  total = min(total, max_v);
+  const int gid = block * PLAN_THREADS + tid;
+  if (gid == 0) { plan[0] = total / PLAN_VT; plan[1] = total; plan[2] = PLAN_VT; plan[3] = cap; }
+  else if (gid >= 4 && gid < PLAN_HDR) plan[gid] = 0;
+  // pattern of each tile, and the padding rows at the end of each pattern: the first prompt of the pattern says where
+  for (int q = block; q < P; q += nblocks) {
+    const int n = __builtin_amdgcn_readlane(padded, q);
+    if (n == 0) continue;                                  // uniform
+    const int b0 = __builtin_amdgcn_readlane(base, q), i = __builtin_amdgcn_readlane(pid, q), used = __builtin_amdgcn_readlane(all, q);
+    for (int t = b0 / PLAN_VT + tid; t < (b0 + n) / PLAN_VT; t += PLAN_THREADS)
+      if (t < cap) tile_pat[t] = i < NP ? i : -1;
+    for (int w = b0 + used + tid; w < b0 + n; w += PLAN_THREADS)
+      if (w < max_v) rowmap[w] = -1;
+  }
+  // the rows of this workgroup's share, prompt by prompt
+  const int vstart = base + before;
+  const int r0 = (int)((long long)rows * block / nblocks), r1 = (int)((long long)rows * (block + 1) / nblocks);
+  for (int q = 0; q < P; ++q) {
+    const int s = __builtin_amdgcn_readlane(off, q), e = s + __builtin_amdgcn_readlane(len, q);
+    const int to = __builtin_amdgcn_readlane(vstart, q) - s;
+    if (e <= r0 || s >= r1) continue;                      // uniform
+    for (int r = max(s, r0) + tid; r < min(e, r1); r += PLAN_THREADS)
+      if (to + r < max_v) rowmap[to + r] = r;
+  }
+}
+
 // Every workgroup works out the (small) per-pattern and per-prompt tables in its own LDS -- integer work, the same in
 // every workgroup -- and then fills its share of the row map.
 // (block, nblocks) = this workgroup's place among the workgroups that build the plan.
 __device__ __forceinline__ void plan_body(const int32_t *__restrict__ tok_offsets, const int32_t *__restrict__ pattern_id,
                                           int P, int rows, int NP, int cap, int32_t *__restrict__ plan, int block,
                                           int nblocks) {
+  if (P <= PLAN_WAVE_P) {                            // uniform
+    plan_wave(tok_offsets, pattern_id, P, rows, NP, cap, plan, block, nblocks);
+    return;
+  }
   __shared__ int32_t cnt[PLAN_MAX_PATTERNS + 1];     // rows of each pattern (index NP: invalid ids); later: running fill
   __shared__ int32_t base[PLAN_MAX_PATTERNS + 2];    // first virtual row of each pattern
   __shared__ int32_t vstart[PLAN_MAX_P];             // first virtual row of each prompt

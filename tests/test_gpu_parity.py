@@ -307,6 +307,38 @@ def test_bucket_matches_oracle(P, k, npat, stride):
     assert np.array_equal(rep.cpu().numpy()[:n_r], rep_r) and np.all(rep.cpu().numpy()[n_r:] == -1)
 
 
+@pytest.mark.parametrize("P", [2, 31, 32, 33, 63, 64, 65])
+def test_buckets_and_plan_where_the_register_forms_end(P):
+    """Buckets (in registers up to 64 prompts) and plan (up to 32) on both sides of their limits, bit for bit as the oracle:
+    empty prompts, repeated subsets, ids out of range, patterns of several tiles."""
+    say(f"buckets and plan, register forms, P={P}")
+    rng = np.random.default_rng(340 + P)
+    k, npat, n_slots = 5, max(1, P // 3), 12
+    pats = np.stack([np.sort(rng.choice(24, size=k, replace=False)) for _ in range(npat)]).astype(np.int32)
+    full = pats[rng.integers(0, npat, size=P)]
+    pid_r, perm_r, off_r, n_r, rep_r = po.bucket(full)
+    pid, perm, boff, n, rep = pa.bucket_patterns(i32(full), k, k)
+    lengths = rng.integers(0, 300, size=P)
+    lengths[rng.integers(0, P, size=max(1, P // 8))] = 0
+    lengths[-1] = 513
+    off = si.offsets_from_lengths([int(v) for v in lengths])
+    rows = int(off[-1])
+    entry = rng.integers(-1, n_slots + 1, size=P).astype(np.int32)
+    plan = pa.prefill_plan(i32(off), i32(entry), rows, n_slots)
+    torch.cuda.synchronize()
+    assert int(n.item()) == n_r
+    assert np.array_equal(pid.cpu().numpy(), pid_r) and np.array_equal(perm.cpu().numpy(), perm_r)
+    assert np.array_equal(boff.cpu().numpy()[:n_r + 1], off_r) and np.all(boff.cpu().numpy()[n_r + 1:] == P)
+    assert np.array_equal(rep.cpu().numpy()[:n_r], rep_r) and np.all(rep.cpu().numpy()[n_r:] == -1)
+    words = plan.view(torch.int32).cpu().numpy()
+    rowmap_ref, tpat_ref = po.plan_rows(off, entry, n_slots, 256)
+    nt, cap = int(words[0]), int(words[3])
+    assert nt == len(tpat_ref) and int(words[1]) == nt * 256 and int(words[2]) == 256 and np.all(words[4:16] == 0)
+    assert np.array_equal(words[16:16 + nt], tpat_ref)
+    rm0 = 16 + (cap + 15) // 16 * 16
+    assert np.array_equal(words[rm0:rm0 + nt * 256], rowmap_ref)
+
+
 @pytest.mark.parametrize("P,k,npat,stride,n_slots", [(8, 8, 3, 8, 32), (37, 5, 6, 9, 4), (256, 10, 16, 30, 64), (300, 4, 20, 4, 16), (1, 3, 1, 3, 1)])
 def test_bucket_and_plan_in_one_launch_equal_the_separate_calls(P, k, npat, stride, n_slots):
     """The launch that buckets the prompts and builds the prefill plan: every output against the oracle and, bit for
