@@ -1,18 +1,19 @@
 // a7 for more than 32 sequences (a loaded server): the same two products as decode_bf16.hip over panels of 32 sequences, but a
 // group selected by any sequence of up to DW_MAXP panels is streamed ONCE and applied to all of them, instead of once per
 // panel.  Launches per call:
-//   wide_prepare  the plan (per layer: groups in use, a 32-sequence mask per group and panel) and x in operand order
-//   wide_z        CB rank blocks x a slice of the reduction per workgroup, all panels: fp32 partial sums, or z
+//   wide_prepare  the plan: per layer the groups in use, a 32-sequence mask per group and panel
+//   wide_z        two rank blocks x a slice of the reduction per workgroup, all panels: fp32 partial sums, or z
 //   wide_zsum     adds the slices in slice order, masks, rounds to bf16 (only when the reduction is cut)
 //   wide_y        CB column blocks per workgroup, all used reduction blocks, all panels
-// Both products keep every operand in operand order, so a wavefront loads 1 KiB per instruction straight into registers:
-// per reduction step CB factor operands and NT token operands feed CB * NT matrix instructions.  The four wavefronts of a
-// workgroup take every fourth step and share nothing until their sums meet in LDS: no staging, no barrier in the loop; what
+// wide_z is a tile kernel like the prefill's (see prefill_lds_bf16.hip): both operands staged in LDS, the loads between 16x16x32
+// products; x is read as it is, row-major.  wide_y keeps every operand in operand order, so a wavefront loads 1 KiB per instruction
+// straight into registers: per reduction step CB factor operands and NT token operands feed CB * NT matrix instructions; its four
+// wavefronts take every fourth step and share nothing until their sums meet in LDS: no staging, no barrier in the loop; what
 // is in flight is DEPTH steps per wavefront (about 40 KiB; one wavefront per SIMD, so the registers are there).
-// Bound by HBM for the factors and by what a compute unit can take in: CB + NT KiB per step, of which NT are re-read by every
-// workgroup -- hence the largest CB that still gives every unit one workgroup.
-// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns: wide_z 18-20 us for gate+up and
-// for down, wide_y 28 and 14 us, 100 us a step; five panels one after the other took 313-335 us.
+// Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
+// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns: wide_z 16 us for gate+up and 19 for down
+// (18 and 20 with operands straight into registers, and a launch of 4-6 us that brought x into operand order; 112 us a step against 118):
+// 4.7 us until the first slice is there, the factors at 4 TB/s, 1.6 us for the sums; wide_y 28 and 14 us; five panels one after the other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
 
@@ -36,7 +37,7 @@ struct DwLayer {
   const uint16_t *Vt, *Ut;
   uint16_t *y;
   uint16_t *zf;              // [panel][R/16] operands of 1 KiB
-  float *zpart;              // [R/32][KS][panel][16][64]
+  float *zpart;              // [R/16][KS][16 sequences][64][4]
   int32_t *plan;
   const int32_t *subsets;
   int stride, k, n_patterns;
@@ -47,48 +48,34 @@ struct DwArgs {
   DwLayer L[DW_MAX_LAYERS];
   int n_layers;
   const uint16_t *x;         // [B][n]
-  uint16_t *xo;              // [panel][n/16] operands of 1 KiB
   const int32_t *pattern_id;
   int B, n, KS, panels;
 };
 
-// grid = layers + workgroups that reorder x, 256 threads
+// grid = layers
 __global__ __launch_bounds__(DW_THREADS) void wide_prepare(DwArgs a) {
-  if ((int)blockIdx.x < a.n_layers) {
-    const DwLayer &ly = a.L[blockIdx.x];
-    __shared__ uint32_t gmask[DW_MAXP][DW_MAXG];
-    for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) gmask[i / DW_MAXG][i % DW_MAXG] = 0u;
-    __syncthreads();
-    for (int s = threadIdx.x; s < a.B; s += DW_THREADS) {
-      const int pid = a.pattern_id[s];
-      if (pid < 0 || pid >= ly.n_patterns) continue;
-      for (int i = 0; i < ly.k; ++i) {
-        const int g = ly.subsets[(size_t)pid * ly.stride + i];
-        if (g >= 0 && g < ly.G) atomicOr(&gmask[s >> 5][g], 1u << (s & 31));
-      }
+  const DwLayer &ly = a.L[blockIdx.x];
+  __shared__ uint32_t gmask[DW_MAXP][DW_MAXG];
+  for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) gmask[i / DW_MAXG][i % DW_MAXG] = 0u;
+  __syncthreads();
+  for (int s = threadIdx.x; s < a.B; s += DW_THREADS) {
+    const int pid = a.pattern_id[s];
+    if (pid < 0 || pid >= ly.n_patterns) continue;
+    for (int i = 0; i < ly.k; ++i) {
+      const int g = ly.subsets[(size_t)pid * ly.stride + i];
+      if (g >= 0 && g < ly.G) atomicOr(&gmask[s >> 5][g], 1u << (s & 31));
     }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-      const int lane = threadIdx.x;
-      uint32_t any = 0u;
-      for (int p = 0; p < DW_MAXP; ++p) any |= gmask[p][lane];
-      const unsigned long long votes = __ballot(lane < ly.G && any != 0u);
-      if ((votes >> lane) & 1ull) ly.plan[1 + __popcll(votes & ((1ull << lane) - 1ull))] = lane;
-      if (lane == 0) ly.plan[0] = __popcll(votes);
-    }
-    for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) ly.plan[128 + i] = (int32_t)gmask[i / DW_MAXG][i % DW_MAXG];
-    return;
   }
-  // x in operand order: piece (panel, kb, q, j) = x[panel*32 + j][kb*16 + q*8 ..+7]; sequences past the last give zeros
-  const int nkb = a.n / 16;
-  const int total = a.panels * nkb * 64;
-  for (int o = ((int)blockIdx.x - a.n_layers) * DW_THREADS + threadIdx.x; o < total; o += ((int)gridDim.x - a.n_layers) * DW_THREADS) {
-    // neighbouring threads read neighbouring pieces of a row
-    const int q2 = o % (nkb * 2), row = o / (nkb * 2);
-    u32x4 v = {0, 0, 0, 0};
-    if (row < a.B) v = *reinterpret_cast<const u32x4 *>(a.x + (size_t)row * a.n + q2 * 8);
-    *reinterpret_cast<u32x4 *>((char *)a.xo + (((size_t)(row >> 5) * nkb + (q2 >> 1)) * 64 + (q2 & 1) * 32 + (row & 31)) * 16) = v;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    uint32_t any = 0u;
+    for (int p = 0; p < DW_MAXP; ++p) any |= gmask[p][lane];
+    const unsigned long long votes = __ballot(lane < ly.G && any != 0u);
+    if ((votes >> lane) & 1ull) ly.plan[1 + __popcll(votes & ((1ull << lane) - 1ull))] = lane;
+    if (lane == 0) ly.plan[0] = __popcll(votes);
   }
+  for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) ly.plan[128 + i] = (int32_t)gmask[i / DW_MAXG][i % DW_MAXG];
 }
 
 constexpr int dw_depth(int CB, int NT) { return 40 / (CB + NT) < 4 ? 4 : (40 / (CB + NT) > 8 ? 8 : 40 / (CB + NT)); }
@@ -143,24 +130,32 @@ __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T
   }
 }
 
-// lane (j, q) holds s[e] = ranks 8*(e/4) + 4*q + e%4 of sequence j of rank block rb: mask, round, store as two z operands
-__device__ __forceinline__ void wide_store_z(const float (&s)[16], uint32_t mask, int lane, char *zf, int rb) {
-  const bool member = (mask >> (lane & 31)) & 1u;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    uint32_t w[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] = member ? cvt_pk_bf16(s[h * 8 + 2 * e], s[h * 8 + 2 * e + 1]) : 0u;
-    const u32x2 sx = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
-    const u32x2 sy = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-    *reinterpret_cast<u32x4 *>(zf + (size_t)(rb * 2 + h) * 1024 + lane * 16) = u32x4{sx[0], sy[0], sx[1], sy[1]};
-  }
+// lane (j, g) holds ranks 4 g + (0..3) of sequences j (lo) and 16 + j (hi) of a panel: mask, round, pair, store one z operand
+__device__ __forceinline__ void wide_store_z(const f32x4v &lo, const f32x4v &hi, uint32_t mask, int lane, char *dst) {
+  const u32x2 s0 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(lo[0], lo[1]), cvt_pk_bf16(hi[0], hi[1]), false, false);
+  const u32x2 s1 = __builtin_amdgcn_permlane16_swap(cvt_pk_bf16(lo[2], lo[3]), cvt_pk_bf16(hi[2], hi[3]), false, false);
+  const bool member = (mask >> (lane & 31)) & 1u;      // after the swap the lane's sequence is lane & 31
+  *reinterpret_cast<u32x4 *>(dst + lane * 16) = member ? u32x4{s0[0], s1[0], s0[1], s1[1]} : u32x4{0, 0, 0, 0};
 }
 
-// grid: layers x rank blocks in units of DW_ZCB (numbered over the blocks in use; the rest leaves) x KS slices
+#define PARSE_DW_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+#define PARSE_DW_GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
+
+// Stages of NT panels' slices (8 KiB of factor, 4 KiB of x per panel): all of the LDS, up to eight: there is little to multiply, what
+// counts is how much of the factor stream is on its way.
+constexpr int dw_stages(int NT) { return 160 / (8 + 4 * NT) > 8 ? 8 : 160 / (8 + 4 * NT); }
+constexpr int DWZ_WAVES = 8, DWZ_THREADS = DWZ_WAVES * 64;   // two per SIMD, whose waits cover each other
+
+// grid: layers x rank blocks in units of DW_ZCB (numbered over the blocks in use; the rest leaves) x KS slices.
+// Slices of 64 reduction indices in a ring: slice kt + STAGES is requested once slice kt has been read by everybody.  A wavefront owns
+// 16 of the 64 ranks and half of the panels (the middle one of an odd number twice), so nothing is added between wavefronts.  A last slice of fewer than 64 indices re-reads the
+// last operands in their place, and both are cleared before they are multiplied (an infinite weight times zero is no number).
 template <int NT>
-__global__ __launch_bounds__(DW_THREADS, 1) void wide_z(DwArgs a) {
-  constexpr int CB = DW_ZCB;
+__global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
+  constexpr int CB = DW_ZCB, PW = (NT + 1) / 2, TB = 2 * PW, STAGES = dw_stages(NT);
+  constexpr int F_BYTES = CB * 4096, STAGE_BYTES = F_BYTES + NT * 4096;
+  constexpr int LT = (4 * NT + DWZ_WAVES - 1) / DWZ_WAVES, L = 1 + LT, H = L / 2;   // loads of a wavefront per slice; after its last half
+  static_assert(F_BYTES == DWZ_WAVES * 1024 && (STAGES - 2) * L + H < 64, "vmcnt is a 6-bit count");
   int li = 0;
 #pragma unroll
   for (int i = 1; i < DW_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].z_first) ? 1 : 0;
@@ -170,61 +165,140 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_z(DwArgs a) {
   const int bpg = ly.gs / 32;                          // rank blocks per group
   const int nused = min(max(ly.plan[0], 0), ly.G) * bpg;
   if (i0 >= nused) return;
-  __shared__ float red[2][DW_WAVES][CB][16][64];       // panels alternate: one barrier each
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int nkb = a.n / 16;
-  const int k0 = (int)(((long long)nkb * sl) / KS), k1 = (int)(((long long)nkb * (sl + 1)) / KS);
-  int rb[CB];
-#pragma unroll
-  for (int i = 0; i < CB; ++i) {                       // blocks past the last re-read it (not stored)
+  const int j = lane & 15, g = lane >> 4;
+  const int n = a.n, nkb = n / 16, slices = (n + 63) / 64;
+  const int kt0 = (int)(((long long)slices * sl) / KS), nk = (int)(((long long)slices * (sl + 1)) / KS) - kt0;
+  const bool ragged = (n & 63) != 0 && kt0 + nk == slices;
+  const int wr = wave & 3, p0 = wave >> 2 ? NT - PW : 0;                 // its 16 ranks, its first panel
+  auto rank_block = [&](int i, int &grp) -> int {                        // blocks past the last one re-read it (not stored)
     const int at = min(i0 + i, nused - 1);
-    rb[i] = ly.plan[1 + at / bpg] * bpg + at % bpg;
+    grp = __builtin_amdgcn_readfirstlane(ly.plan[1 + at / bpg]);
+    return grp * bpg + at % bpg;
+  };
+  int grp, lgrp;
+  const int rb = rank_block(wr >> 1, grp), lrb = rank_block(wave >> 2, lgrp);
+
+  // sources: one of the eight factor operands of a slice, and of its groups of 8 rows of x every eighth (the last one again where
+  // they do not divide: the same data to the same place)
+  const uint32_t loff = lane * 16;
+  const char *V = (const char *)ly.Vt + ((size_t)lrb * nkb + kt0 * 4 + wr) * 1024;
+  const char *xs[LT];
+  int chunk[LT], xdst[LT];                             // 16-byte piece of a row's 128 bytes; place of the group in the slice
+#pragma unroll
+  for (int i = 0; i < LT; ++i) {
+    const int grp8 = min(i * DWZ_WAVES + wave, 4 * NT - 1), rr = grp8 * 8 + (lane >> 3);
+    xdst[i] = F_BYTES + grp8 * 1024;
+    chunk[i] = (lane & 7) ^ ((rr >> 1) & 7);           // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
+    xs[i] = (const char *)a.x + (size_t)min(rr, a.B - 1) * n * 2 + (size_t)kt0 * 128;  // rows past the last sequence re-read it
   }
-  const char *V = (const char *)ly.Vt + (size_t)(k0 + wave) * 1024 + lane * 16;
-  const char *X = (const char *)a.xo + (size_t)(k0 + wave) * 1024 + lane * 16;
-  f32x16 acc[CB][NT];
-  wide_loop<CB, NT>(acc, (k1 - k0 - wave + DW_WAVES - 1) / DW_WAVES,
-                    [&](int s, int i) { return V + ((size_t)rb[i] * nkb + s * DW_WAVES) * 1024; },
-                    [&](int s, int p) { return X + ((size_t)p * nkb + s * DW_WAVES) * 1024; });
-#pragma unroll
-  for (int p = 0; p < NT; ++p) {
-#pragma unroll
-    for (int i = 0; i < CB; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) red[p & 1][wave][i][e][lane] = acc[i][p][e];
-    __syncthreads();
-    // the four sums of every value, in wavefront order
-    if (KS > 1) {
-#pragma unroll
-      for (int i = 0; i < CB; ++i) {
-        const int at = min(i0 + i, nused - 1);
-        float *dst = ly.zpart + (((size_t)(ly.plan[1 + at / bpg] * bpg + at % bpg) * KS + sl) * NT + p) * 1024;
-        if (i0 + i < nused) {
-#pragma unroll
-          for (int u = 0; u < 1024 / DW_THREADS; ++u) {
-            const int v = u * DW_THREADS + (int)threadIdx.x;
-            float s = (&red[p & 1][0][i][0][0])[v];
-#pragma unroll
-            for (int w = 1; w < DW_WAVES; ++w) s += (&red[p & 1][w][i][0][0])[v];
-            dst[v] = s;
-          }
-        }
-      }
-    } else if (wave < CB && i0 + wave < nused) {
-      const int g = ly.plan[1 + (i0 + wave) / bpg], myrb = g * bpg + (i0 + wave) % bpg;
-      float s[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[e] = red[p & 1][0][wave][e][lane];
-#pragma unroll
-        for (int w = 1; w < DW_WAVES; ++w) s[e] += red[p & 1][w][wave][e][lane];
-      }
-      wide_store_z(s, (uint32_t)ly.plan[128 + p * 64 + g], lane, (char *)ly.zf + (size_t)p * (ly.R / 16) * 1024, myrb);
+  int issued = 0, dst = 0;
+  auto load = [&](int q, bool steady) {                // load q of L of the next slice; the last one moves on
+    const bool cut = !steady && ragged && issued == nk - 1;              // uniform
+    if (q == 0) {
+      const int over = cut ? max((kt0 + issued) * 4 + wr - (nkb - 1), 0) : 0;
+      __builtin_amdgcn_global_load_lds(PARSE_DW_GLB_PTR(V - over * 1024 + loff), PARSE_DW_LDS_PTR(smem + dst + wave * 1024), 16, 0, 0);
+    } else {
+      const int i = q - 1;
+      const int c = cut ? min(chunk[i], n / 8 - 1 - (kt0 + issued) * 8) : chunk[i];
+      __builtin_amdgcn_global_load_lds(PARSE_DW_GLB_PTR(xs[i] + c * 16), PARSE_DW_LDS_PTR(smem + dst + xdst[i]), 16, 0, 0);
+      xs[i] += 128;
     }
+    if (q == L - 1) {
+      V += 4096;
+      dst = dst + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : dst + STAGE_BYTES;
+      ++issued;
+    }
+  };
+  // LDS operands: lane (j, g) reads reduction indices 8 g .. 8 g + 7 of row j of a 16-row block
+  const int f_lane = (wr >> 1) * 4096 + (g >> 1) * 1024 + (g & 1) * 512 + (wr & 1) * 256 + j * 16;
+  const int t_lane = F_BYTES + p0 * 4096 + j * 128 + ((g ^ ((j >> 1) & 7)) * 16);
+  u32x4 fr[2], tr[2][TB];
+  int src = 0;
+  auto read_half = [&](int half) {
+    fr[half] = *reinterpret_cast<const u32x4 *>(smem + src + f_lane + half * 2048);
+    const char *tb = smem + src + (t_lane ^ (half * 64));
+#pragma unroll
+    for (int t = 0; t < TB; ++t) tr[half][t] = *reinterpret_cast<const u32x4 *>(tb + t * 2048);
+  };
+  auto settle = [&](int half) {                        // the reads have arrived before anything else is issued (see gemm_lds)
+    asm volatile("" ::"v"(fr[half]));
+#pragma unroll
+    for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[half][t]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  f32x4v acc[TB];
+#pragma unroll
+  for (int t = 0; t < TB; ++t) acc[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  auto products = [&](int half, int q0, int q1, bool more, bool steady) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) {
+      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[half]), as_bf16x8(tr[half][t]), acc[t], 0, 0, 0);
+#pragma unroll
+      for (int q = q0; q < q1; ++q)
+        if (t == (q - q0) * TB / (q1 - q0)) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (more) load(q, steady);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto clear_past = [&](int half, int kt) {            // reduction indices past the last one
+    if ((kt0 + kt) * 64 + half * 32 + g * 8 >= n) {
+      fr[half] = u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int t = 0; t < TB; ++t) tr[half][t] = u32x4{0, 0, 0, 0};
+    }
+  };
+  auto slice = [&](bool steady, int kt) {
+    const bool cut = !steady && ragged && kt == nk - 1;
+    settle(0);
+    read_half(1);
+    if (cut) clear_past(0, kt);
+    products(0, H, L, steady || kt - 1 + STAGES < nk, steady);
+    settle(1);
+    if (cut) clear_past(1, kt);
+    if (steady || kt + 1 < nk) {                       // slice kt + 1 has landed for everybody, slice kt has been read by everybody
+      if (steady) wait_vm<(STAGES - 2) * L>(); else wait_slices<STAGES - 2, L>(min(kt + STAGES - 1, nk - 1) - (kt + 1));
+      wg_barrier();
+      src = src + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : src + STAGE_BYTES;
+      read_half(0);
+    }
+    products(1, 0, H, steady || kt + STAGES < nk, steady);
+  };
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s) {
+    if (s < nk) {
+#pragma unroll
+      for (int q = 0; q < (s == STAGES - 1 ? H : L); ++q) load(q, false);
+    }
+  }
+  if (nk >= STAGES) wait_vm<(STAGES - 2) * L + H>(); else wait_vm<0>();
+  wg_barrier();
+  read_half(0);
+  int kt = 0;
+  for (; kt + STAGES + 1 < nk; ++kt) slice(true, kt);  // what it requests are whole slices
+  for (; kt < nk; ++kt) slice(false, kt);
+
+  if (i0 + (wr >> 1) >= nused) return;
+  const int rb16 = rb * 2 + (wr & 1), skip = wave >> 2 ? 2 * PW - NT : 0;        // the other half stores the middle panel
+  if (KS > 1) {
+    float *dst4 = ly.zpart + (((size_t)rb16 * KS + sl) * NT + p0) * 512 + lane * 4;
+#pragma unroll
+    for (int t = 0; t < TB; ++t)
+      if (t >= 2 * skip) *reinterpret_cast<f32x4v *>(dst4 + t * 256) = acc[t];
+  } else {
+#pragma unroll
+    for (int p = 0; p < PW; ++p)
+      if (p >= skip)
+        wide_store_z(acc[2 * p], acc[2 * p + 1], (uint32_t)ly.plan[128 + (p0 + p) * 64 + grp], lane, (char *)ly.zf + ((size_t)(p0 + p) * (ly.R / 16) + rb16) * 1024);
   }
 }
 
-// one wavefront per (used rank block, panel)
+// one wavefront per (16 used ranks, panel)
 __global__ __launch_bounds__(DW_THREADS) void wide_zsum(DwArgs a) {
   const int id = (int)blockIdx.x * DW_WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int li = 0;
@@ -232,22 +306,20 @@ __global__ __launch_bounds__(DW_THREADS) void wide_zsum(DwArgs a) {
   for (int i = 1; i < DW_MAX_LAYERS; ++i) li += (i < a.n_layers && id >= a.L[i].s_first) ? 1 : 0;
   const DwLayer &ly = a.L[li];
   const int at = (id - ly.s_first) / a.panels, p = (id - ly.s_first) % a.panels;
-  const int bpg = ly.gs / 32;
+  const int bpg = ly.gs / 16;
   if (at >= min(max(ly.plan[0], 0), ly.G) * bpg) return;
   const int lane = threadIdx.x & 63;
-  const int g = ly.plan[1 + at / bpg], rb = g * bpg + at % bpg;
+  const int g = ly.plan[1 + at / bpg], rb16 = g * bpg + at % bpg;
   const uint32_t mask = (uint32_t)ly.plan[128 + p * 64 + g];
-  float s[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) s[e] = 0.f;
-  const float *src = ly.zpart + ((size_t)rb * a.KS * a.panels + p) * 1024 + lane;
-  const size_t step = (size_t)a.panels * 1024;
-#pragma unroll 2
+  const size_t step = (size_t)a.panels * 512;
+  const float *src = ly.zpart + (size_t)rb16 * a.KS * step + p * 512 + lane * 4;
+  f32x4v lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
   for (int o = 0; o < a.KS; ++o) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s[e] += src[o * step + e * 64];
+    lo += *reinterpret_cast<const f32x4v *>(src + o * step);
+    hi += *reinterpret_cast<const f32x4v *>(src + o * step + 256);
   }
-  wide_store_z(s, mask, lane, (char *)ly.zf + (size_t)p * (ly.R / 16) * 1024, rb);
+  wide_store_z(lo, hi, mask, lane, (char *)ly.zf + ((size_t)p * (ly.R / 16) + rb16) * 1024);
 }
 
 // grid: layers x column blocks in units of CB
@@ -326,7 +398,7 @@ bool decode_wide_supported(const parse_layer *layers, int n_layers) {
 
 static size_t wide_bytes(const parse_layer *layers, int n_layers, size_t nt) {
   const int ks = wide_slices(layers, n_layers);
-  size_t t = round_up((size_t)n_layers * DW_PLAN_WORDS * sizeof(int32_t), 256) + nt * (layers[0].n / 16) * 1024;
+  size_t t = round_up((size_t)n_layers * DW_PLAN_WORDS * sizeof(int32_t), 256);
   for (int l = 0; l < n_layers; ++l)
     t += nt * (layers[l].R / 16) * 1024 + (ks > 1 ? nt * (layers[l].R / 32) * ks * 4096 : 0);
   return t;
@@ -341,13 +413,12 @@ size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int 
 }
 
 static int wide_pass(DwArgs a, hipStream_t s) {
-  int xwgs = std::min(512, (a.panels * (a.n / 16) * 64 + DW_THREADS - 1) / DW_THREADS);
-  hipLaunchKernelGGL(wide_prepare, dim3(a.n_layers + xwgs), dim3(DW_THREADS), 0, s, a);
+  hipLaunchKernelGGL(wide_prepare, dim3(a.n_layers), dim3(DW_THREADS), 0, s, a);
   PARSE_LAUNCH_CHECK();
   int zw = 0, sw = 0, cols = 0;
   for (int l = 0; l < a.n_layers; ++l) {
     a.L[l].z_first = zw; zw += (a.L[l].R / 32 + DW_ZCB - 1) / DW_ZCB * a.KS;
-    a.L[l].s_first = sw; sw += a.L[l].R / 32 * a.panels;
+    a.L[l].s_first = sw; sw += a.L[l].R / 16 * a.panels;
     cols += a.L[l].m / 32;
   }
   int cb = 1;                                // column blocks per workgroup: the fewest that need one round of workgroups
@@ -357,7 +428,8 @@ static int wide_pass(DwArgs a, hipStream_t s) {
   for (int l = 0; l < a.n_layers; ++l) { a.L[l].y_first = yw; yw += (a.L[l].m / 32 + cb - 1) / cb; }
 #define PARSE_DW(NT_)                                                                              \
   case NT_:                                                                                        \
-    hipLaunchKernelGGL(wide_z<NT_>, dim3(zw), dim3(DW_THREADS), 0, s, a);                          \
+    PARSE_ALLOW_LDS(wide_z<NT_>, dw_stages(NT_) * (8 + 4 * NT_) * 1024);                           \
+    hipLaunchKernelGGL(wide_z<NT_>, dim3(zw), dim3(DWZ_THREADS), dw_stages(NT_) * (8 + 4 * NT_) * 1024, s, a); \
     PARSE_LAUNCH_CHECK();                                                                          \
     if (a.KS > 1) {                                                                                \
       hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a); \
@@ -387,8 +459,6 @@ int forward_decode_wide_bf16(const parse_layer *layers, const parse_patterns *pt
   char *ws = reinterpret_cast<char *>(workspace);
   int32_t *plan = reinterpret_cast<int32_t *>(ws);
   ws += round_up((size_t)n_layers * DW_PLAN_WORDS * sizeof(int32_t), 256);
-  a.xo = reinterpret_cast<uint16_t *>(ws);
-  ws += (size_t)per * (a.n / 16) * 1024;
   for (int l = 0; l < n_layers; ++l) {
     const parse_layer *L = &layers[l];
     DwLayer &d = a.L[l];

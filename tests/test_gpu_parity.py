@@ -1590,6 +1590,19 @@ def test_decode_many_sequences(n, shapes, rows):
             assert_close(yn[ok], ref[ok], TOL_BF16, f"layer {l} {what}")
 
 
+@pytest.mark.parametrize("n,shapes,rows", [
+    (336, [(64, 256, 8, 3)], 97),                     # a last slice of 16 indices, four panels; fewer slices than stages
+    (1056, [(96, 288, 3, 2)], 40),                    # ... of 32, an odd number of rank blocks, two panels
+    (4144, [(64, 512, 16, 4)], 129),                  # ... of 48, the reduction cut in eight, five panels
+    (304, [(64, 8320, 4, 1)], 70),                    # so many ranks that the reduction is not cut, three panels
+    (512, [(64, 8256, 2, 1)], 180),                   # ... six panels
+])
+def test_decode_many_sequences_slices(n, shapes, rows):
+    """The slices of the first product: ragged last ones, more stages than slices, reductions that are not cut, both halves of an
+    odd and an even number of panels."""
+    test_decode_many_sequences(n, shapes, rows)
+
+
 @pytest.mark.parametrize("n,m,rS,lengths", [
     # first product up to 4096 rows: 64 x 64, 64 x 128, 128 x 128, 128 x 256 tiles (the second one: 64 x 64, 64 x 128, 128 x 256, 128 x 128)
     (64, 96, 32, [1]),
