@@ -310,9 +310,10 @@ int parse_bucket_and_plan(const int32_t *subset, int32_t P, int32_t k, int32_t s
  * for presence only: everything the kernels need from them is in the plan).
  *   workspace  device, >= parse_lowrank_prefill_planned_workspace_bytes(layer, rows, P, k, n_patterns): the
  *              intermediate of the padded virtual rows, in operand order; for batches of at most 1024 token rows
- *              (n >= 1024) also room for the fp32 partial sums of the first product, whose reduction over n may then be cut
- *              in up to four slices (one more small launch adds them in slice order; the count depends on the batch and the
- *              layer alone, so fused and single-layer calls agree bit for bit). */
+ *              (n >= 1024), and of at most 4096 on long reductions (n >= 8192), also room for the fp32 partial sums of the
+ *              first product, whose reduction over n may then be cut in up to four slices (one more small launch adds them
+ *              in slice order; the count depends on the batch and the layer alone, so fused and single-layer calls agree
+ *              bit for bit).  Batches of more than 1024 rows also take a workspace without that room, and are not cut then. */
 size_t parse_lowrank_prefill_planned_workspace_bytes(const parse_layer *layer, int32_t rows, int32_t P, int32_t k,
                                                      int32_t n_patterns);
 int parse_lowrank_prefill_planned(const parse_layer *layer, const parse_patterns *patterns, const void *X,

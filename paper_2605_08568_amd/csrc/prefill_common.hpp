@@ -55,6 +55,7 @@ struct PfArgs {
   // per-pattern blocks hold the other rS - sh_ranks; 0 = everything per pattern
   const uint16_t *Vt_sh = nullptr, *Ut_sh = nullptr;
   int sh_ranks = 0;
+  int split_room = 1;      // slices of the first product's reduction that the workspace has room for
 };
 
 

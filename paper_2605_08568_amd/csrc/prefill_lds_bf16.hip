@@ -602,7 +602,7 @@ static int launch_first256(const LgArgs &a, int avg_tiles_per_pattern, hipStream
   return launch_tiles<256, 256>(gemm_first256, 512, 160 * 1024, attr_done, a, avg_tiles_per_pattern, 1, s);
 }
 
-// Slices of the first product's reduction range that the workspace has room for (1 = no split).
+// Slices of the first product's reduction range that the smallest workspace has room for (1 = no split) ...
 int prefill_planned_split(int rows, int n) {
   const int tiles = (rows + 63) / 64;
   if (tiles <= 0 || tiles > 16) return 1;
@@ -610,6 +610,11 @@ int prefill_planned_split(int rows, int n) {
   if (ks > 8) ks = 8;
   if (ks > n / 64 / 8) ks = n / 64 / 8;
   return ks < 2 ? 1 : ks;
+}
+// ... and that the queried one has: also longer batches on long reductions (see split_slices).
+constexpr int SHORT_ROWS = 4096;
+int prefill_planned_room(int rows, int n) {
+  return rows > 1024 && rows <= SHORT_ROWS && n >= 8192 ? 4 : prefill_planned_split(rows, n);
 }
 // Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
 // partial sums of its ks slices
@@ -651,7 +656,6 @@ static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split
     default: return 2.5 * rounds;
   }
 }
-constexpr int SHORT_ROWS = 4096;
 static int best_tile(const PfArgs *const *p, int n_layers) {
   int best = T64;
   for (int i = 1; i < N_TILES; ++i)
@@ -663,9 +667,17 @@ static int best_tile(const PfArgs *const *p, int n_layers) {
 // without; 300 rows x 1024 ranks 24 and 27; 700 x 1024 34 (two) and 31; n = 11008: 534 rows x 384 ranks 33 (three) and 54, 643 x
 // 384 40 (two) and 58, 1024 x 1280 85 (two) and 83; n = 5632, 546 x 640 25.5 (two) and 30.6.  A function of the batch and of this
 // layer alone, so that a call over several layers splits each like its single-layer call and gives the same bits.
+// Batches of more than 1024 rows are split on reductions of 8192 and more, in four slices of 128 x 256 tiles: those move the
+// fewest bytes per flop, and in slices they fill the chip, as long as they are few and the prompts fill them.  n = 11008, both products, us,
+// without / with: 2048 rows x 1024 ranks 96 / 83, 1300 x 1024 91 / 72, 2048 x 640 91 / 68, 2 x 700 rows x 1024 96 / 75, 3 x 1300 x 768 145 / 141;
+// three slices of 100 and 128 tiles 137 / 141 and 195 / 195; 16 x 200 x 1024 169 / 200; n = 8192, 2048 x 1024 77 / 70; n = 5632,
+// 2048 x 512 39 / 44; n = 4096, 2048 x 1024 56 / 62.
 static int split_slices(const PfArgs &p) {
-  const int room = std::min(4, prefill_planned_split(p.rows, p.n));
+  const int room = std::min(4, p.split_room);
   if (p.n < 4096) return 1;
+  if (p.rows > 1024) {
+    return room == 4 && p.rows / p.P >= 384 && token_tiles(p.rows, p.P, 128) * ((p.rS + 255) / 256) <= 96 ? 4 : 1;
+  }
   const PfArgs *one[1] = {&p};
   const double round_us = 30.0 * p.n / 4096;
   int best = 1;
@@ -722,7 +734,8 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
     if (g.n_layers == 0) continue;
     if (ks > 1) {
       g.ks = ks;
-      st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g, per_pattern, s);
+      if (rows > 1024) st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 1, 2>(g, per_pattern, s);
+      else st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g, per_pattern, s);
       if (st != PARSE_OK) return st;
       const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
       hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), g.n_layers), dim3(256), 0, s, g);

@@ -1679,6 +1679,42 @@ def test_prefill_planned_tiles(n, m, rS, lengths):
         assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in a call of two"
 
 
+@pytest.mark.parametrize("n,m,rS,lengths", [
+    (8192, 64, 64, [1025]),                           # the first batch past the short ones, one tile column
+    (8256, 96, 288, [513, 600, 40]),                  # an odd number of slices of 64, a rank block past the last tile, padding tiles
+    (8192, 32, 992, [2048, 1900]),                    # 32 x 4 tiles: too many for slices of these tiles
+    (9024, 32, 768, [2048, 1900]),                    # 32 x 3 tiles in four slices, the most
+    (8192, 32, 64, [300, 383, 400]),                  # prompts too short for these tiles
+])
+def test_prefill_planned_long_reductions(n, m, rS, lengths):
+    """Long reductions of more than 1024 rows are cut in slices: as every other tile, and with the smallest workspace, where they
+    are not cut."""
+    test_prefill_planned_tiles(n, m, rS, lengths)
+    rng = np.random.default_rng(1411)
+    off = si.offsets_from_lengths(lengths)
+    rows, P = int(off[-1]), len(lengths)
+    bf = lambda r, c: torch.from_numpy(rng.standard_normal((r, c)).astype(np.float32)).to(torch.bfloat16).to(DEV)      # noqa: E731
+    layer = pa.Layer(bf(rS, n), bf(rS, m), n, m, rS, 1, pa.PARSE_MFMA16)
+    pt = pa.Patterns(1, P, bf(P * rS, n).view(P, rS, n), bf(P * rS, m).view(P, rS, m))
+    X, offd, pid = bf(rows, n), i32(off), i32(np.arange(P))
+    plan = pa.prefill_plan(offd, pid, rows, P)
+    cap = int(plan.view(torch.int32)[3].item())
+    small = (cap * 256 * rS * 2 + 255) // 256 * 256
+    queried = pa.lowrank_prefill_planned_workspace_bytes(layer, rows, P, 1, P)
+    assert queried > small
+    ys = []
+    for size in (queried, small):
+        whole, ws = guarded_bytes(size)
+        ys.append(torch.full((rows, m), 7.0, dtype=torch.bfloat16, device=DEV))
+        pa.lowrank_prefill_planned(layer, pt, X, offd, pid, plan, ys[-1], ws[:size])
+        torch.cuda.synchronize()
+        check_guards(whole, "planned prefill, long reduction")
+    # both round Z to bf16 once: a value of Z that rounds the other way differs by 2^-8 of itself
+    assert float((ys[0].float() - ys[1].float()).norm() / ys[1].float().norm()) < 2.0 ** -8
+    with pytest.raises(pa.ParseError):
+        pa.lowrank_prefill_planned(layer, pt, X, offd, pid, plan, ys[0], torch.empty(small - 256, dtype=torch.uint8, device=DEV))
+
+
 @pytest.mark.parametrize("n,shapes,B", [
     (16, [(32, 32, 1, 1)], 5),                                       # one reduction step of half an instruction
     (496, [(64, 96, 3, 2), (416, 256, 4, 3)], 16),                   # odd number of 16-column steps; full instruction
