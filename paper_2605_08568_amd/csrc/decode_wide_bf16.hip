@@ -412,7 +412,24 @@ size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int 
   return wide_bytes(layers, n_layers, (size_t)std::min(panels_of(rows), DW_MAXP));
 }
 
+template <int NT>
+static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
+  constexpr int smem = dw_stages(NT) * (8 + 4 * NT) * 1024;
+  static bool attr_done[64] = {false};       // the limit holds for the kernel on a device, not for a launch
+  int dev = 0;
+  PARSE_HIP_TRY(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) return PARSE_EINVAL;
+  if (!attr_done[dev]) {
+    PARSE_HIP_TRY(hipFuncSetAttribute((const void *)wide_z<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    attr_done[dev] = true;
+  }
+  hipLaunchKernelGGL(wide_z<NT>, dim3(wgs), dim3(DWZ_THREADS), smem, s, a);
+  PARSE_LAUNCH_CHECK();
+  return PARSE_OK;
+}
+
 static int wide_pass(DwArgs a, hipStream_t s) {
+  int st;
   hipLaunchKernelGGL(wide_prepare, dim3(a.n_layers), dim3(DW_THREADS), 0, s, a);
   PARSE_LAUNCH_CHECK();
   int zw = 0, sw = 0, cols = 0;
@@ -428,9 +445,8 @@ static int wide_pass(DwArgs a, hipStream_t s) {
   for (int l = 0; l < a.n_layers; ++l) { a.L[l].y_first = yw; yw += (a.L[l].m / 32 + cb - 1) / cb; }
 #define PARSE_DW(NT_)                                                                              \
   case NT_:                                                                                        \
-    PARSE_ALLOW_LDS(wide_z<NT_>, dw_stages(NT_) * (8 + 4 * NT_) * 1024);                           \
-    hipLaunchKernelGGL(wide_z<NT_>, dim3(zw), dim3(DWZ_THREADS), dw_stages(NT_) * (8 + 4 * NT_) * 1024, s, a); \
-    PARSE_LAUNCH_CHECK();                                                                          \
+    st = launch_wide_z<NT_>(a, zw, s);                                                             \
+    if (st != PARSE_OK) return st;                                                                 \
     if (a.KS > 1) {                                                                                \
       hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a); \
       PARSE_LAUNCH_CHECK();                                                                        \
