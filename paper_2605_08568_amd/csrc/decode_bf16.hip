@@ -73,8 +73,8 @@ __device__ __forceinline__ bf16x8 dec_bf16x8(u32x4 v) { return __builtin_bit_cas
 
 // The blocks (of 16 or 32 ranks, `per` to a group) of the groups in use, counted through: one load of the plan puts the used ids
 // in a register of the 64 lanes, a block's place follows by arithmetic and a lane read.  A list in LDS put two barriers and two LDS
-// round trips between the plan and the first factor load: decode_y16 5.5 -> 5.0 and 8.4 -> 7.8 us a launch, decode_y the same.
-// (decode_yv asks for the blocks of four lanes' groups at a time; with lane shuffles in place of its list it was 0.6 us slower.)
+// round trips between the plan and the first factor load: decode_y16 5.5 -> 5.0 and 8.4 -> 7.8 us a launch.  (decode_y keeps its list: the
+// step of 32 sequences was 0.4 us slower without; so does decode_yv, which asks for the blocks of four lanes' groups at a time.)
 struct DecUsed {
   int ids, count, per;
   float inv;
@@ -491,17 +491,27 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
   const DecLayer &ly = a.L[li];
   const uint16_t *__restrict__ Ut = ly.Ut;
   const uint16_t *__restrict__ zf = ly.zf;
+  const int32_t *__restrict__ plan = ly.plan;
   uint16_t *__restrict__ y = ly.y;
-  const int B = a.B, m = ly.m;
+  const int B = a.B, m = ly.m, G = ly.G, gs = ly.gs;
   const int bid = blockIdx.x - ly.y_first;
   __shared__ float red[DY_WAVES][16][64];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  __shared__ int32_t kb_list[DY_MAXKB];
+  __shared__ int32_t used[DEC_MAXG];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, q = lane >> 5;
   const int ncb = m / 32;
   const int c0 = bid * NC;
   const int nc = min(NC, ncb - c0);
-  const DecUsed blocks(ly, lane, ly.gs / 16);        // reduction blocks in use
-  const int total_kb = blocks.count;
+  // count and ids come from the plan in one round trip (ids past the count are -1 and not used)
+  const int n_used_raw = plan[0];
+  if (threadIdx.x < DEC_MAXG) used[threadIdx.x] = plan[1 + threadIdx.x];
+  const int n_used = max(0, min(n_used_raw, G));
+  __syncthreads();
+  const int kpg = gs / 16;                 // reduction blocks per group
+  const int total_kb = n_used * kpg;       // selected reduction blocks
+  for (int i = threadIdx.x; i < total_kb; i += DY_THREADS) kb_list[i] = max(used[i / kpg], 0) * kpg + i % kpg;
+  __syncthreads();
   const int k0 = (total_kb * wave) / DY_WAVES, k1 = (total_kb * (wave + 1)) / DY_WAVES;
   const int cnt = k1 - k0;
   const uint16_t *ubase = Ut + ((size_t)c0 * 64 + lane) * 8;
@@ -522,7 +532,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
     u32x4 ur[DY_MAXK][NC], zr[DY_MAXK];
 #pragma unroll
     for (int i = 0; i < DY_MAXK; ++i) {
-      const int kb = blocks.block(k0 + min(i, cnt - 1));
+      const int kb = kb_list[k0 + min(i, cnt - 1)];
 #pragma unroll
       for (int j = 0; j < NC; ++j) ur[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
       zr[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
@@ -539,7 +549,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
       u32x4 uu[DEC_CHUNK][NC], zz[DEC_CHUNK];
 #pragma unroll
       for (int i = 0; i < DEC_CHUNK; ++i) {
-        const int kb = blocks.block(k0 + min(c + i, cnt - 1));
+        const int kb = kb_list[k0 + min(c + i, cnt - 1)];
 #pragma unroll
         for (int j = 0; j < NC; ++j) uu[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
         zz[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
