@@ -12,8 +12,7 @@
 
 namespace parse {
 
-int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial,
-                         int *Q_out, hipStream_t s);
+int launch_pool(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial, float *emb, hipStream_t s);
 
 constexpr int RK_MAXG = 8192;        // ranks the selection kernel holds in LDS
 constexpr int RK_PB = 8;             // prompts per scoring workgroup
@@ -283,10 +282,7 @@ int parse_route_ranks(const void *X, int32_t xdtype, int32_t rows, const int32_t
   float *emb = emb_out ? emb_out : reinterpret_cast<float *>(ws + pool_bytes);
   float *scores = scores_out ? scores_out
                              : reinterpret_cast<float *>(ws + pool_bytes + round_up((size_t)P * d * sizeof(float), 256));
-  int Q = 0;
-  int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
-  if (st != PARSE_OK) return st;
-  st = launch_pool_finish(partial, Q, rows, d, tok_offsets, P, emb, s);
+  const int st = launch_pool(X, xdtype, rows, tok_offsets, P, d, partial, emb, s);
   if (st != PARSE_OK) return st;
   hipLaunchKernelGGL(rank_scores, dim3((G + RK_ROWS - 1) / RK_ROWS, (P + RK_PB - 1) / RK_PB), dim3(256), 0, s, Wr, emb, G,
                      d, P, scores);

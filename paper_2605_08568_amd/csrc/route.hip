@@ -17,7 +17,8 @@ constexpr int kPoolThreads = 256, kPoolWaves = kPoolThreads / 64;
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-template <bool BF16>
+// WHOLE (Q = 1): the mean itself, no second launch.
+template <bool BF16, bool WHOLE>
 __global__ __launch_bounds__(kPoolThreads) void pool_partial(const void *__restrict__ X, int rows, int d,
                                                              const int32_t *__restrict__ tok_offsets,
                                                              int Q, float *__restrict__ partial) {
@@ -72,6 +73,11 @@ __global__ __launch_bounds__(kPoolThreads) void pool_partial(const void *__restr
     for (int w = 0; w < kPoolWaves - 1; ++w)
 #pragma unroll
       for (int i = 0; i < PER; ++i) acc[i] += red[w][i][lane];
+    if (WHOLE) {
+      const float inv = b > a ? 1.0f / (float)(b - a) : 0.f;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) acc[i] *= inv;
+    }
     float *dst = partial + ((size_t)p * Q + q) * d + c0;
 #pragma unroll
     for (int i = 0; i < PER; i += 4) *reinterpret_cast<float4 *>(dst + i) = float4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
@@ -115,7 +121,11 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__re
 
 // Slices per prompt: about two workgroups per compute unit, a slice of at least 32 rows (8 per wavefront), at most
 // 32 slices.
+// Up to POOL_WHOLE_ROWS rows one slice, which leaves nothing to add: embeddings in one launch (4096 columns, us, one launch / two: 20
+// rows 2.7 / 4.7, 77 3.9 / 5.0, 128 4.3 / 5.6, 180 5.4 / 5.9, 256 6.7 / 4.9; and 2.7 less on the host).
+constexpr int POOL_WHOLE_ROWS = 160;
 static int pool_slices(int rows, int P, int d, bool bf16) {
+  if (rows <= POOL_WHOLE_ROWS) return 1;
   const int per_block = 64 * (bf16 ? 8 : 4);
   const int colblocks = (d + per_block - 1) / per_block;
   long long want = (512 + (long long)P * colblocks - 1) / ((long long)P * colblocks);
@@ -135,9 +145,9 @@ int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok
   const int per_block = 64 * (bf16 ? 8 : 4);
   dim3 grid((d + per_block - 1) / per_block, Q, P);
   if (bf16)
-    hipLaunchKernelGGL(pool_partial<true>, grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
+    hipLaunchKernelGGL((pool_partial<true, false>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
   else
-    hipLaunchKernelGGL(pool_partial<false>, grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
+    hipLaunchKernelGGL((pool_partial<false, false>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
   PARSE_LAUNCH_CHECK();
   *Q_out = Q;
   return PARSE_OK;
@@ -145,6 +155,23 @@ int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok
 
 int launch_pool_finish(const float *partial, int Q, int rows, int d, const int32_t *tok_offsets, int P, float *emb,
                        hipStream_t s);   // with the rank-granular router
+
+// Embeddings of a batch: one launch where the rows of a prompt are one slice
+int launch_pool(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial, float *emb, hipStream_t s) {
+  const bool bf16 = xdtype == PARSE_BF16;
+  if (pool_slices(rows, P, d, bf16) == 1) {
+    const int per_block = 64 * (bf16 ? 8 : 4);
+    const dim3 grid((d + per_block - 1) / per_block, 1, P);
+    if (bf16) hipLaunchKernelGGL((pool_partial<true, true>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, 1, emb);
+    else hipLaunchKernelGGL((pool_partial<false, true>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, 1, emb);
+    PARSE_LAUNCH_CHECK();
+    return PARSE_OK;
+  }
+  int Q = 0;
+  const int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
+  if (st != PARSE_OK) return st;
+  return launch_pool_finish(partial, Q, rows, d, tok_offsets, P, emb, s);
+}
 
 }  // namespace parse
 
@@ -171,10 +198,7 @@ int parse_pool(const void *X, int32_t xdtype, int32_t rows, const int32_t *tok_o
   if (!workspace || workspace_bytes < parse_route_workspace_bytes(rows, P, d)) return PARSE_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   float *partial = reinterpret_cast<float *>(workspace);
-  int Q = 0;
-  const int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
-  if (st != PARSE_OK) return st;
-  return launch_pool_finish(partial, Q, rows, d, tok_offsets, P, emb_out, s);
+  return launch_pool(X, xdtype, rows, tok_offsets, P, d, partial, emb_out, s);
 }
 
 int parse_route(const void *X, int32_t xdtype, int32_t rows, const int32_t *tok_offsets, int32_t P, int32_t d,
