@@ -288,7 +288,7 @@ def bench_prefill(args, torch, pa, si):
         "rank_granular_us": rank_us, "two_batches_in_flight": pipelined,
         # the forward of the timed steps is parse_lowrank_prefill_planned: both products on LDS-staged tiles over the
         # plan, 128 x 128 for the first (256 workgroups), 256 x 256 for the second
-        "roofline": {"bound": "mfma", "kernel": "gemm_lds<128,128,2x2x2,BK64,S4> + gemm_lds<256,256,2x4,BK64,S2> (one planned forward call)",
+        "roofline": {"bound": "mfma", "kernel": "gemm_lds<128,128,2x2x2,KS64,S4> + gemm_lds<256,256,2x4,KS32,S5> (one planned forward call)",
                      "achieved": round(achieved, 2),
                      "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
                      "traffic": traffic_from_profiles("prefill_config1"),
@@ -810,7 +810,7 @@ def main():
                   "ms_per_step_eager": round(p2["ms_per_step"], 4), "step_TFLOPs": round(p2["value"], 1),
                   "rows_us": p2["rows_us"], "forward_in_step_us": p2["roofline"]["launch_us"],
                   "forward_TFLOPs": p2["roofline"]["achieved"], "forward_frac_of_mfma_peak": p2["roofline"]["frac"],
-                  "kernel": "gemm_lds<256,256,2x4,BK64,S2> for both products (one planned forward call)"}
+                  "kernel": "gemm_first256 + gemm_lds<256,256,2x4,KS32,S5> (one planned forward call)"}
         del p2
         torch.cuda.empty_cache()
     if not args.no_decode:
