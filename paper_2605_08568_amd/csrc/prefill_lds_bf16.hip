@@ -1,24 +1,23 @@
 // a6, planned form of the bf16 prefill product (Sec. 4.4, Eq. 10):  launch 1  Z = X Vt_S^T,  launch 2  Y = Z Ut_S,
-// both with ONE tile kernel, `gemm_lds`, over the virtual rows of a prefill plan (plan.hip): a tile of token rows
-// belongs to one pattern, so a workgroup runs one reduction with one factor block, whatever the prompt lengths.
+// both with one tile kernel, `gemm_lds` (first products of many tiles: `gemm_first256`), over the virtual rows of a
+// prefill plan (plan.hip): a tile of token rows belongs to one pattern, so a workgroup runs one reduction with one factor block, whatever the prompt lengths.
 //
 // Data path.  Both operands of a tile are staged in LDS by loads that write LDS directly (no register round trip,
-// 1 KiB per wavefront instruction), STAGES reduction slices of BK deep; the matrix-core operands are then 16-byte
+// 1 KiB per wavefront instruction), STAGES reduction slices of KS deep; the matrix-core operands are then 16-byte
 // LDS reads.  Factor operands are stored in operand order in memory (PARSE_MFMA16), so a 1 KiB load lands as one
 // ready operand and is read back linearly (conflict-free).  The intermediate Z is written by launch 1 in the same
 // operand order (token block x reduction block), so launch 2 stages it exactly like a factor.  Only X is row-major:
 // its rows are loaded 16 bytes per lane, whole cache lines per row, and the 16-byte chunks of a row are XOR-swizzled
 // on the way in (the swizzle is applied to the global address, the LDS write is linear) so that the operand reads --
-// 32 rows x one chunk -- spread over all banks.
-// Pipeline per reduction slice: ... [LDS reads of step s+1 | matrix instructions of step s] ...; in the last step of
-// a slice the wavefront waits for its own loads of the next slice, meets the others at a barrier (so everybody's loads
-// have landed and everybody is done reading the current slice), requests the slice STAGES ahead into the buffer just
-// freed and reads the next slice's first operands -- all of that while its matrix instructions of the last step are
-// still to be issued, so the matrix pipe does not drain at the barrier.
-// Output: the accumulator of the 32x32x16 instruction gives a lane 4 consecutive factor rows (output columns) of one
-// token in each of four 8-row bands; one 32-lane swap pairs the bands up to 8 consecutive columns = 16 bytes, which is
-// one piece of a Z operand (launch 1: stored linearly, 1 KiB per instruction) or a 16-byte store into the token's
-// row of Y (launch 2).
+// 16 rows x four chunks -- spread over all banks.
+// Pipeline: a unit is 32 reduction indices of a wavefront's share of the tile; its operands are read from LDS into
+// registers during the unit before, and the loads of later slices are requested one by one between its matrix
+// instructions.  Before the last unit of a slice the wavefront waits for its own loads of the next slice and meets the
+// others at a barrier (so everybody's loads have landed and everybody has read the current slice); from then on the
+// slice STAGES ahead is requested into the place just freed.
+// Output: the accumulator of the 16x16x32 instruction gives a lane 4 consecutive factor rows (output columns) of one
+// token; one 16-lane swap of two blocks pairs them up to 8 consecutive columns = 16 bytes, which is one piece of a Z
+// operand (launch 1: stored linearly, 1 KiB per instruction) or a 16-byte store into the token's row of Y (launch 2).
 #include <algorithm>
 
 #include "prefill_common.hpp"
@@ -42,7 +41,7 @@ struct LgLayer {
   int K, M;                // reduction length, factor rows (= output columns)
   // shared head (Sec. 4.4: shared experts at the head of memory, stored once): the first sh_blocks 32-rank blocks of
   // every pattern's selection come from Fsh (same operand order, as many rank rows as the head has), the per-pattern
-  // blocks in F hold the rest, renumbered from 0.  FORD 0: the leading factor-row blocks; FORD 1 (BK == 32 only): the
+  // blocks in F hold the rest, renumbered from 0.  FORD 0: the leading factor-row blocks; FORD 1 (KS == 32 only): the
   // leading reduction slices.  0 = everything per pattern.
   const uint16_t *Fsh;
   int sh_blocks;
@@ -137,7 +136,8 @@ __device__ __forceinline__ u32x4 lg_pair(const f32x4v &u, const f32x4v &v) {
 // FORD: factor order, 0 = right factor (operand (rb, kb) at rb*(K/16)+kb), 1 = left factor (operand (kb, cb) at kb*(M/32)+cb).
 // TROW: token operand 1 = row-major rows looked up through the plan's row map (X), 0 = operand order over the plan's virtual
 //       rows (Z).   OROW: output 1 = row-major through the row map, 0 = operand order.
-// First product: <FORD 0, TROW 1, OROW 0>, slices of KS = 64 (whole cache lines of a row of X); second product: <1, 0, 1>, KS = 32.
+// First product: <FORD 0, TROW 1, OROW 0>, slices of KS = 64 (whole cache lines of a row of X); second product: <1, 0, 1>, KS = 32
+// (64 in launches of few tiles without a shared head).
 // A unit of work is 32 reduction indices of a wavefront's share of the tile; its operands are read from LDS into registers during
 // the unit before.  WK 2: two wavefronts share an output tile, each takes one half of every slice, and the halves are added at the
 // end through LDS: a tile of 128 x 128 or less then still has eight wavefronts, two per SIMD, whose waits cover each other.
