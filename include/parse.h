@@ -310,10 +310,12 @@ int parse_bucket_and_plan(const int32_t *subset, int32_t P, int32_t k, int32_t s
  * for presence only: everything the kernels need from them is in the plan).
  *   workspace  device, >= parse_lowrank_prefill_planned_workspace_bytes(layer, rows, P, k, n_patterns): the
  *              intermediate of the padded virtual rows, in operand order; for batches of at most 1024 token rows
- *              (n >= 1024), and of at most 4096 on long reductions (n >= 8192), also room for the fp32 partial sums of the
- *              first product, whose reduction over n may then be cut in up to four slices (one more small launch adds them
- *              in slice order; the count depends on the batch and the layer alone, so fused and single-layer calls agree
- *              bit for bit).  Batches of more than 1024 rows also take a workspace without that room, and are not cut then. */
+ *              (n >= 1024), and of at most 4096 on long reductions (n >= 8192; few prompts of 384 rows and more on average,
+ *              few ranks), also room for the fp32 partial sums of the first product, whose reduction over n may then be cut
+ *              in up to four slices (one more small launch adds them in slice order).  With the queried workspace the count
+ *              depends on the batch and the layer alone, so fused and single-layer calls agree bit for bit.  Batches of
+ *              more than 1024 rows also take a workspace without that room; they are not cut then, and a value of the
+ *              intermediate may round to its other bf16 neighbour. */
 size_t parse_lowrank_prefill_planned_workspace_bytes(const parse_layer *layer, int32_t rows, int32_t P, int32_t k,
                                                      int32_t n_patterns);
 int parse_lowrank_prefill_planned(const parse_layer *layer, const parse_patterns *patterns, const void *X,
@@ -438,7 +440,8 @@ int parse_lowrank_decode_static(const parse_layer *layer, const parse_patterns *
  *     back to the two-launch schedule when the shapes or the workspace do not allow it;
  *   PARSE_SCHED_TILES  the two-launch tile kernels on prompt-order tiles (n and k*gs multiples of 128);
  *   PARSE_SCHED_FUSED  PARSE_EINVAL (the single-launch kernel takes one layer).
- * The result equals n_layers separate PARSE_PREFILL calls under the same schedule, bit for bit.
+ * The result equals n_layers separate PARSE_PREFILL calls under the same schedule, bit for bit, where every call has the
+ * workspace that its query asks for (see parse_lowrank_prefill_planned on smaller ones).
  *   layers, patterns  host arrays [n_layers]; patterns[l] holds layer l's packed factors (Vt_S, Ut_S, k; shared head
  *                     allowed)
  *   X                 device [rows][n] bf16; tok_offsets device int32 [P+1]; pattern_id device int32 [P]

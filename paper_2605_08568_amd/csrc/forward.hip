@@ -1,4 +1,6 @@
 // parse_lowrank_forward: argument checks and dispatch to the fp32 / bf16 prefill kernels and the decode kernels.
+#include <algorithm>
+
 #include "prefill_common.hpp"
 
 namespace parse {
@@ -17,7 +19,8 @@ int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, in
                        int32_t *plan, hipStream_t s);
 size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks);
 int prefill_planned_split(int rows, int n);
-int prefill_planned_room(int rows, int n);
+int prefill_planned_cut_prompts(int rows, int n);
+int prefill_planned_room(int rows, int P, int n, int rS);
 bool prefill_planned_supported(int n, int m, int rS);
 int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int32_t *plan, int cap, uint16_t *const *Z,
                                        int avg_prompt_rows, hipStream_t s);
@@ -69,7 +72,7 @@ extern "C" {
 // workspace of the planned schedule inside parse_lowrank_forward: the intermediate, then the plan
 static size_t planned_total_bytes(const parse_layer *L, int rows, int P, int k, int n_patterns) {
   const int rS = k * (L->R / L->G);
-  return prefill_planned_z_bytes(prefill_plan_capacity(rows, P, n_patterns), rS, prefill_planned_room(rows, L->n)) +
+  return prefill_planned_z_bytes(prefill_plan_capacity(rows, P, n_patterns), rS, prefill_planned_room(rows, P, L->n, rS)) +
          prefill_plan_bytes(rows, P, n_patterns);
 }
 
@@ -99,7 +102,7 @@ size_t parse_lowrank_prefill_planned_workspace_bytes(const parse_layer *L, int32
                                                      int32_t n_patterns) {
   if (!L || rows <= 0 || k <= 0 || P <= 0 || n_patterns <= 0 || L->G <= 0 || L->R <= 0) return 0;
   const int rS = k * (L->R / L->G);
-  return prefill_planned_z_bytes(prefill_plan_capacity(rows, P, n_patterns), rS, prefill_planned_room(rows, L->n));
+  return prefill_planned_z_bytes(prefill_plan_capacity(rows, P, n_patterns), rS, prefill_planned_room(rows, P, L->n, rS));
 }
 
 int parse_lowrank_prefill_planned(const parse_layer *L, const parse_patterns *pt, const void *X, int32_t rows,
@@ -131,7 +134,7 @@ int parse_lowrank_prefill_planned(const parse_layer *L, const parse_patterns *pt
     a.Ut_sh = (const uint16_t *)pt->Ut_shared;
     a.sh_ranks = pt->n_shared * (L->R / L->G);
   }
-  a.split_room = prefill_planned_room(rows, L->n);
+  a.split_room = prefill_planned_room(rows, P, L->n, rS);
   if (workspace_bytes < prefill_planned_z_bytes(cap, rS, a.split_room)) a.split_room = prefill_planned_split(rows, L->n);
   return forward_prefill_planned_bf16(a, (const int32_t *)plan, cap, (uint16_t *)workspace, rows / P, (hipStream_t)stream);
 }
@@ -298,11 +301,15 @@ static bool multi_planned_shapes(const parse_layer *layers, const parse_patterns
   }
   return true;
 }
-// ks: slices of the first product's reduction to make room for
-static size_t multi_planned_bytes(const parse_layer *layers, const parse_patterns *patterns, int n_layers, int rows, int P, int ks) {
+// room: slices of a layer's first product that the queried workspace has room for, else those of the smallest one
+static int multi_slices(const parse_layer &L, const parse_patterns &pt, int rows, int P, bool room) {
+  return room ? prefill_planned_room(rows, P, L.n, pt.k * (L.R / L.G)) : prefill_planned_split(rows, L.n);
+}
+static size_t multi_planned_bytes(const parse_layer *layers, const parse_patterns *patterns, int n_layers, int rows, int P, bool room) {
   const int cap = prefill_plan_capacity(rows, P, patterns[0].n_patterns);
   size_t total = prefill_plan_bytes(rows, P, patterns[0].n_patterns);
-  for (int l = 0; l < n_layers; ++l) total += prefill_planned_z_bytes(cap, patterns[l].k * (layers[l].R / layers[l].G), ks);
+  for (int l = 0; l < n_layers; ++l)
+    total += prefill_planned_z_bytes(cap, patterns[l].k * (layers[l].R / layers[l].G), multi_slices(layers[l], patterns[l], rows, P, room));
   return total;
 }
 
@@ -316,8 +323,9 @@ size_t parse_lowrank_prefill_multi_workspace_bytes(const parse_layer *layers, co
   }
   if (multi_planned_shapes(layers, patterns, n_layers)) {
     const int p_ub = rows < 2048 ? rows : 2048;          // the plan takes at most 2048 prompts
-    const size_t planned = multi_planned_bytes(layers, patterns, n_layers, rows, p_ub, prefill_planned_room(rows, layers[0].n));
-    if (planned > total) total = planned;
+    total = std::max(total, multi_planned_bytes(layers, patterns, n_layers, rows, p_ub, false));
+    for (int P = 1; P <= prefill_planned_cut_prompts(rows, layers[0].n); ++P)      // up to ten; which of them are cut, and what they take
+      total = std::max(total, multi_planned_bytes(layers, patterns, n_layers, rows, P, true));
   }
   return total;
 }
@@ -363,20 +371,18 @@ int parse_lowrank_prefill_multi(const parse_layer *layers, const parse_patterns 
   hipStream_t s = (hipStream_t)stream;
   char *ws = reinterpret_cast<char *>(workspace);
   const bool planned_shapes = multi_planned_shapes(layers, patterns, n_layers) && prefill_plan_supported(P, patterns[0].n_patterns);
-  int ks = prefill_planned_room(rows, layers[0].n);
-  if (planned_shapes && workspace_bytes < multi_planned_bytes(layers, patterns, n_layers, rows, P, ks))
-    ks = prefill_planned_split(rows, layers[0].n);       // the smallest workspace of this schedule
-  const bool can_plan = planned_shapes && workspace != nullptr &&
-                        workspace_bytes >= multi_planned_bytes(layers, patterns, n_layers, rows, P, ks);
+  const bool room = planned_shapes && workspace_bytes >= multi_planned_bytes(layers, patterns, n_layers, rows, P, true);
+  const bool can_plan = planned_shapes && workspace != nullptr &&       // without the room: the smallest workspace of this schedule
+                        (room || workspace_bytes >= multi_planned_bytes(layers, patterns, n_layers, rows, P, false));
   if (schedule == PARSE_SCHED_PLANNED && !can_plan) return planned_shapes ? PARSE_EWORKSPACE : PARSE_ESHAPE;
   if (can_plan && schedule != PARSE_SCHED_TILES) {
     // planned: every layer's padded intermediate, then the plan; one plan launch, then two launches for all layers
     const int cap = prefill_plan_capacity(rows, P, patterns[0].n_patterns);
     uint16_t *Z[4];
     for (int l = 0; l < n_layers; ++l) {
-      args[l].split_room = ks;
+      args[l].split_room = multi_slices(layers[l], patterns[l], rows, P, room);
       Z[l] = reinterpret_cast<uint16_t *>(ws);
-      ws += prefill_planned_z_bytes(cap, args[l].rS, ks);
+      ws += prefill_planned_z_bytes(cap, args[l].rS, args[l].split_room);
     }
     int32_t *plan = reinterpret_cast<int32_t *>(ws);
     int st = build_prefill_plan(tok_offsets, pattern_id, P, rows, patterns[0].n_patterns, plan, s);

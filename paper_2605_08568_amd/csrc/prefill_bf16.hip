@@ -363,7 +363,7 @@ int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, in
                        int32_t *plan, hipStream_t s);
 size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks);
 int prefill_planned_split(int rows, int n);
-int prefill_planned_room(int rows, int n);
+int prefill_planned_room(int rows, int P, int n, int rS);
 bool prefill_planned_supported(int n, int m, int rS);
 int forward_prefill_planned_bf16(const PfArgs &p, const int32_t *plan, int cap, uint16_t *Z, int avg_prompt_rows,
                                  hipStream_t s);
@@ -385,7 +385,7 @@ int forward_prefill_bf16(const parse_layer *L, const parse_patterns *pt, const u
   const bool planned_shapes = a.sh_ranks % 32 == 0 && prefill_plan_supported(P, pt->n_patterns) &&
                               prefill_planned_supported(L->n, L->m, rS);
   const int cap = planned_shapes ? prefill_plan_capacity(rows, P, pt->n_patterns) : 0;
-  a.split_room = prefill_planned_room(rows, L->n);
+  a.split_room = prefill_planned_room(rows, P, L->n, rS);
   size_t zb = planned_shapes ? prefill_planned_z_bytes(cap, rS, a.split_room) : 0;
   if (workspace_bytes < zb + prefill_plan_bytes(rows, P, pt->n_patterns)) {       // the smallest workspace of this schedule
     a.split_room = prefill_planned_split(rows, L->n);

@@ -602,29 +602,6 @@ static int launch_first256(const LgArgs &a, int avg_tiles_per_pattern, hipStream
   return launch_tiles<256, 256>(gemm_first256, 512, 160 * 1024, attr_done, a, avg_tiles_per_pattern, 1, s);
 }
 
-// Slices of the first product's reduction range that the smallest workspace has room for (1 = no split) ...
-int prefill_planned_split(int rows, int n) {
-  const int tiles = (rows + 63) / 64;
-  if (tiles <= 0 || tiles > 16) return 1;
-  int ks = 32 / tiles;
-  if (ks > 8) ks = 8;
-  if (ks > n / 64 / 8) ks = n / 64 / 8;
-  return ks < 2 ? 1 : ks;
-}
-// ... and that the queried one has: also longer batches on long reductions (see split_slices).
-constexpr int SHORT_ROWS = 4096;
-int prefill_planned_room(int rows, int n) {
-  return rows > 1024 && rows <= SHORT_ROWS && n >= 8192 ? 4 : prefill_planned_split(rows, n);
-}
-// Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
-// partial sums of its ks slices
-static size_t planned_z_only_bytes(int cap_tiles, int rS) { return round_up((size_t)cap_tiles * 256 * rS * sizeof(uint16_t), 256); }
-size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks) {
-  return planned_z_only_bytes(cap_tiles, rS) + (ks > 1 ? round_up((size_t)ks * cap_tiles * 256 * rS * sizeof(float), 256) : 0);
-}
-
-bool prefill_planned_supported(int n, int m, int rS) { return n % 64 == 0 && rS % 32 == 0 && m % 32 == 0 && n >= 64 && rS >= 32; }
-
 // Token tiles of bm rows, as far as the host can tell: it does not know which prompts share a pattern, and a pattern starts on a
 // tile of its own.  Prompts of one length that are a multiple of bm leave nothing open; otherwise full tiles and one more are
 // taken for the number.  (Half a tile more for every prompt is closer when every prompt has its own pattern, but many prompts of
@@ -635,6 +612,33 @@ static long long token_tiles(int rows, int P, int bm) {
   if (rows % P == 0 && rows / P % bm == 0) return rows / bm;
   return (rows + bm - 1) / bm + (P > 1 ? 1 : 0);
 }
+
+// Slices of the first product's reduction range that the smallest workspace has room for (1 = no split) ...
+int prefill_planned_split(int rows, int n) {
+  const int tiles = (rows + 63) / 64;
+  if (tiles <= 0 || tiles > 16) return 1;
+  int ks = 32 / tiles;
+  if (ks > 8) ks = 8;
+  if (ks > n / 64 / 8) ks = n / 64 / 8;
+  return ks < 2 ? 1 : ks;
+}
+// ... and that the queried one has: also longer batches on long reductions that are cut (see split_slices), of which few prompts
+// with few tiles are: everybody else is not asked for four fp32 copies of the intermediate (4096 rows of 64 prompts x 1280 ranks:
+// 52 MB with the room left out, 472 MB with it).
+constexpr int SHORT_ROWS = 4096;
+int prefill_planned_cut_prompts(int rows, int n) { return rows > 1024 && rows <= SHORT_ROWS && n >= 8192 ? rows / 384 : 0; }
+int prefill_planned_room(int rows, int P, int n, int rS) {
+  if (P <= prefill_planned_cut_prompts(rows, n) && token_tiles(rows, P, 128) * ((rS + 255) / 256) <= 96) return 4;
+  return prefill_planned_split(rows, n);
+}
+// Z of one layer (bf16, operand order over the plan's capacity), then -- when the first product is split -- the fp32
+// partial sums of its ks slices
+static size_t planned_z_only_bytes(int cap_tiles, int rS) { return round_up((size_t)cap_tiles * 256 * rS * sizeof(uint16_t), 256); }
+size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks) {
+  return planned_z_only_bytes(cap_tiles, rS) + (ks > 1 ? round_up((size_t)ks * cap_tiles * 256 * rS * sizeof(float), 256) : 0);
+}
+
+bool prefill_planned_supported(int n, int m, int rS) { return n % 64 == 0 && rS % 32 == 0 && m % 32 == 0 && n >= 64 && rS >= 32; }
 
 // Time of the first product with tile i, in units of a round of 128 x 128 tiles, one per compute unit (30 us at K = 4096).
 // Measured over 16 shapes of 77 to 57 000 rows and 512 to 3072 ranks, further rounds of the small tiles (two workgroups of
@@ -666,7 +670,8 @@ static int best_tile(const PfArgs *const *p, int n_layers) {
 // and a pass over them).  77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7
 // without; 300 rows x 1024 ranks 24 and 27; 700 x 1024 34 (two) and 31; n = 11008: 534 rows x 384 ranks 33 (three) and 54, 643 x
 // 384 40 (two) and 58, 1024 x 1280 85 (two) and 83; n = 5632, 546 x 640 25.5 (two) and 30.6.  A function of the batch and of this
-// layer alone, so that a call over several layers splits each like its single-layer call and gives the same bits.
+// layer alone, so that a call over several layers splits each like its single-layer call and gives the same bits -- as long as
+// both have their queried workspace: with more than 1024 rows and no room for the partial sums a call is not cut.
 // Batches of more than 1024 rows are split on reductions of 8192 and more, in four slices of 128 x 256 tiles: those move the
 // fewest bytes per flop, and in slices they fill the chip, as long as they are few and the prompts fill them.  n = 11008, both products, us,
 // without / with: 2048 rows x 1024 ranks 96 / 83, 1300 x 1024 91 / 72, 2048 x 640 91 / 68, 2 x 700 rows x 1024 96 / 75, 3 x 1300 x 768 145 / 141;
@@ -675,9 +680,7 @@ static int best_tile(const PfArgs *const *p, int n_layers) {
 static int split_slices(const PfArgs &p) {
   const int room = std::min(4, p.split_room);
   if (p.n < 4096) return 1;
-  if (p.rows > 1024) {
-    return room == 4 && p.rows / p.P >= 384 && token_tiles(p.rows, p.P, 128) * ((p.rS + 255) / 256) <= 96 ? 4 : 1;
-  }
+  if (p.rows > 1024) return room;        // four where prefill_planned_room says so and the workspace is large enough
   const PfArgs *one[1] = {&p};
   const double round_us = 30.0 * p.n / 4096;
   int best = 1;

@@ -319,6 +319,30 @@ def test_decode_workspace_of_a_larger_batch_covers_the_smaller_ones():
     assert lib.parse_lowrank_decode_multi_workspace_bytes(two, 2) > q[-1]
 
 
+def test_prefill_workspace_asks_for_partial_sums_only_where_they_are_used():
+    """More than 1024 rows on reductions of 8192 and more: room for four slices of fp32 sums where the batch is cut (up to ten
+    prompts of 384 rows and more on average, up to 96 tiles of 128 x 256), and for the intermediate alone everywhere else."""
+    lib = pa.lib()
+    up = lambda b: (b + 255) // 256 * 256                                                     # noqa: E731
+    cases = [(4096, 64, 64, 1280, 8192, False),     # prompts too short
+             (4096, 16, 16, 1280, 11008, False),
+             (4096, 10, 10, 768, 8192, False),      # 33 x 3 tiles
+             (4096, 8, 8, 768, 8192, True),         # 32 x 3
+             (3839, 10, 10, 256, 8192, False), (3840, 10, 10, 256, 8192, True),     # 383.9 and 384 rows a prompt
+             (1025, 1, 1, 64, 8192, True), (1025, 1, 1, 64, 8128, False), (4097, 1, 1, 64, 8192, False)]
+    for rows, P, npat, rS, n, cut in cases:
+        L = B._Layer(n, 256, 2 * rS, 2, 1, 1, FAKE.value, FAKE2.value)
+        values = ((rows + 255) // 256 + min(P, npat + 1)) * 256 * rS
+        want = up(values * 2) + (up(4 * values * 4) if cut else 0)
+        assert lib.parse_lowrank_prefill_planned_workspace_bytes(C.byref(L), rows, P, 1, npat) == want, (rows, P, rS, n)
+        # several layers: whatever number of prompts the call has, and no more
+        one = (B._Layer * 1)(L)
+        pats = (B._Patterns * 1)()
+        pats[0].k, pats[0].n_patterns = 1, npat
+        each = [lib.parse_lowrank_workspace_bytes(0, C.byref(L), rows, 1, p, npat) for p in range(1, min(rows, 2048) + 1)]
+        assert lib.parse_lowrank_prefill_multi_workspace_bytes(one, pats, 1, rows) == max(each), (rows, npat, rS, n)
+
+
 def test_stream_handle_without_the_private_name(monkeypatch):
     """The handle comes from the public stream object where torch does not offer the raw one."""
     class Stream:

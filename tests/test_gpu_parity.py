@@ -1679,16 +1679,16 @@ def test_prefill_planned_tiles(n, m, rS, lengths):
         assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in a call of two"
 
 
-@pytest.mark.parametrize("n,m,rS,lengths", [
-    (8192, 64, 64, [1025]),                           # the first batch past the short ones, one tile column
-    (8256, 96, 288, [513, 600, 40]),                  # an odd number of slices of 64, a rank block past the last tile, padding tiles
-    (8192, 32, 992, [2048, 1900]),                    # 32 x 4 tiles: too many for slices of these tiles
-    (9024, 32, 768, [2048, 1900]),                    # 32 x 3 tiles in four slices, the most
-    (8192, 32, 64, [300, 383, 400]),                  # prompts too short for these tiles
+@pytest.mark.parametrize("n,m,rS,lengths,cut", [
+    (8192, 64, 64, [1025], True),                     # the first batch past the short ones, one tile column
+    (8256, 96, 288, [513, 600, 40], True),            # an odd number of slices of 64, a rank block past the last tile, padding tiles
+    (8192, 32, 992, [2048, 1900], False),             # 32 x 4 tiles: too many for slices of these tiles
+    (9024, 32, 768, [2048, 1900], True),              # 32 x 3 tiles in four slices, the most
+    (8192, 32, 64, [300, 383, 400], False),           # prompts too short for these tiles
 ])
-def test_prefill_planned_long_reductions(n, m, rS, lengths):
-    """Long reductions of more than 1024 rows are cut in slices: as every other tile, and with the smallest workspace, where they
-    are not cut."""
+def test_prefill_planned_long_reductions(n, m, rS, lengths, cut):
+    """Long reductions of more than 1024 rows are cut in slices: as every other tile, in a call of two layers, and with the
+    smallest workspace, where they are not cut.  What is cut shows in the partial sums, which lie behind the intermediate."""
     test_prefill_planned_tiles(n, m, rS, lengths)
     rng = np.random.default_rng(1411)
     off = si.offsets_from_lengths(lengths)
@@ -1700,17 +1700,30 @@ def test_prefill_planned_long_reductions(n, m, rS, lengths):
     plan = pa.prefill_plan(offd, pid, rows, P)
     cap = int(plan.view(torch.int32)[3].item())
     small = (cap * 256 * rS * 2 + 255) // 256 * 256
-    queried = pa.lowrank_prefill_planned_workspace_bytes(layer, rows, P, 1, P)
-    assert queried > small
+    sums = 4 * cap * 256 * rS * 4
+    assert pa.lowrank_prefill_planned_workspace_bytes(layer, rows, P, 1, P) == small + (sums if cut else 0)
     ys = []
-    for size in (queried, small):
+    for size in (small + sums, small):
         whole, ws = guarded_bytes(size)
         ys.append(torch.full((rows, m), 7.0, dtype=torch.bfloat16, device=DEV))
         pa.lowrank_prefill_planned(layer, pt, X, offd, pid, plan, ys[-1], ws[:size])
         torch.cuda.synchronize()
         check_guards(whole, "planned prefill, long reduction")
+        assert bool(torch.any(ws[small:] != 0xA5)) == (cut and size > small), "cut where it should not be, or the other way round"
+    if not cut:
+        assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
     # both round Z to bf16 once: a value of Z that rounds the other way differs by 2^-8 of itself
     assert float((ys[0].float() - ys[1].float()).norm() / ys[1].float().norm()) < 2.0 ** -8
+    # two layers in one call, with room for the partial sums of both, and with a little less: the bits of the calls above
+    both = 2 * (small + (sums if cut else 0)) + pa.prefill_plan_bytes(rows, P, P)
+    for size, y in ((both, ys[0]),) + (((both - 256, ys[1]),) if cut else ()):
+        whole, ws = guarded_bytes(size)
+        y2 = [torch.full((rows, m), 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+        pa.lowrank_prefill_multi([layer] * 2, [pt.with_schedule(pa.PARSE_SCHED_PLANNED)] * 2, X, offd, pid, y2, ws)
+        torch.cuda.synchronize()
+        check_guards(whole, "two layers, long reduction")
+        for got in y2:
+            assert torch.equal(got.view(torch.int16), y.view(torch.int16)), f"two layers, {size} of {both} bytes"
     with pytest.raises(pa.ParseError):
         pa.lowrank_prefill_planned(layer, pt, X, offd, pid, plan, ys[0], torch.empty(small - 256, dtype=torch.uint8, device=DEV))
 
