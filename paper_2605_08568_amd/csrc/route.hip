@@ -4,7 +4,8 @@
 //   pool_partial  grid (column blocks of 64 lanes x 16 bytes, Q row slices, P prompts): the rows of a prompt are
 //                 dealt round robin to the wavefronts of its Q workgroups, 16 rows in flight per wavefront; the
 //                 four wavefronts of a workgroup add up through LDS in wavefront order; fp32 partial sums per
-//                 slice, rows streamed once.
+//                 slice, rows streamed once.  Embeddings alone (pool, rank-granular router): where the slices fit in one
+//                 workgroup and pay for it, they are added there, in the same order, and the launch writes the means.
 //   route_finish  one block per prompt: adds the Q partials in slice order, divides by the length,
 //                 scores the G groups (one wavefront per group, butterfly reduction) and selects the
 //                 top k with a rank count inside one wavefront.
@@ -17,14 +18,15 @@ constexpr int kPoolThreads = 256, kPoolWaves = kPoolThreads / 64;
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// WHOLE (Q = 1): the mean itself, no second launch.
-template <bool BF16, bool WHOLE>
-__global__ __launch_bounds__(kPoolThreads) void pool_partial(const void *__restrict__ X, int rows, int d,
+// WHOLE > 0: the workgroup holds all WHOLE slices (= Q, grid.y 1) and writes the mean itself: same sums, same order, no second launch.
+template <bool BF16, int WHOLE>
+__global__ __launch_bounds__(kPoolThreads * (WHOLE > 0 ? WHOLE : 1)) void pool_partial(const void *__restrict__ X, int rows, int d,
                                                              const int32_t *__restrict__ tok_offsets,
                                                              int Q, float *__restrict__ partial) {
   constexpr int PER = BF16 ? 8 : 4;  // columns per lane = 16 bytes
   constexpr int U = 16;              // rows a wavefront has in flight
-  __shared__ float red[kPoolWaves - 1][PER][64];
+  constexpr int NQ = WHOLE > 0 ? WHOLE : 1;    // slices of this workgroup
+  __shared__ float red[NQ * kPoolWaves - 1][PER][64];
   const int p = blockIdx.z, q = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c0 = (blockIdx.x * 64 + lane) * PER;
@@ -73,12 +75,22 @@ __global__ __launch_bounds__(kPoolThreads) void pool_partial(const void *__restr
     for (int w = 0; w < kPoolWaves - 1; ++w)
 #pragma unroll
       for (int i = 0; i < PER; ++i) acc[i] += red[w][i][lane];
+    for (int sl = 1; sl < NQ; ++sl) {
+      const int w0 = sl * kPoolWaves - 1;      // the slice's first wavefront
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        float part = red[w0][i][lane];
+#pragma unroll
+        for (int w = 1; w < kPoolWaves; ++w) part += red[w0 + w][i][lane];
+        acc[i] += part;
+      }
+    }
     if (WHOLE) {
       const float inv = b > a ? 1.0f / (float)(b - a) : 0.f;
 #pragma unroll
       for (int i = 0; i < PER; ++i) acc[i] *= inv;
     }
-    float *dst = partial + ((size_t)p * Q + q) * d + c0;
+    float *dst = partial + ((size_t)p * (WHOLE ? 1 : Q) + q) * d + c0;
 #pragma unroll
     for (int i = 0; i < PER; i += 4) *reinterpret_cast<float4 *>(dst + i) = float4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
   }
@@ -121,11 +133,7 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__re
 
 // Slices per prompt: about two workgroups per compute unit, a slice of at least 32 rows (8 per wavefront), at most
 // 32 slices.
-// Up to POOL_WHOLE_ROWS rows one slice, which leaves nothing to add: embeddings in one launch (4096 columns, us, one launch / two: 20
-// rows 2.7 / 4.7, 77 3.9 / 5.0, 128 4.3 / 5.6, 180 5.4 / 5.9, 256 6.7 / 4.9; and 2.7 less on the host).
-constexpr int POOL_WHOLE_ROWS = 160;
 static int pool_slices(int rows, int P, int d, bool bf16) {
-  if (rows <= POOL_WHOLE_ROWS) return 1;
   const int per_block = 64 * (bf16 ? 8 : 4);
   const int colblocks = (d + per_block - 1) / per_block;
   long long want = (512 + (long long)P * colblocks - 1) / ((long long)P * colblocks);
@@ -137,17 +145,17 @@ static int pool_slices(int rows, int P, int d, bool bf16) {
   return (int)q;
 }
 
-// Launches pool_partial into `partial` ([P][Q][d] floats, Q returned); shared with the rank-granular router.
-int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial,
-                         int *Q_out, hipStream_t s) {
+// Launches pool_partial into `partial` ([P][Q][d] floats, Q returned)
+static int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial,
+                                int *Q_out, hipStream_t s) {
   const bool bf16 = xdtype == PARSE_BF16;
   const int Q = pool_slices(rows, P, d, bf16);
   const int per_block = 64 * (bf16 ? 8 : 4);
   dim3 grid((d + per_block - 1) / per_block, Q, P);
   if (bf16)
-    hipLaunchKernelGGL((pool_partial<true, false>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
+    hipLaunchKernelGGL((pool_partial<true, 0>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
   else
-    hipLaunchKernelGGL((pool_partial<false, false>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
+    hipLaunchKernelGGL((pool_partial<false, 0>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
   PARSE_LAUNCH_CHECK();
   *Q_out = Q;
   return PARSE_OK;
@@ -156,18 +164,31 @@ int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok
 int launch_pool_finish(const float *partial, int Q, int rows, int d, const int32_t *tok_offsets, int P, float *emb,
                        hipStream_t s);   // with the rank-granular router
 
-// Embeddings of a batch: one launch where the rows of a prompt are one slice
+template <int Q>
+static void launch_pool_whole(const void *X, bool bf16, int rows, const int32_t *tok_offsets, int P, int d, float *emb, hipStream_t s) {
+  const int per_block = 64 * (bf16 ? 8 : 4);
+  const dim3 grid((d + per_block - 1) / per_block, 1, P);
+  if (bf16) hipLaunchKernelGGL((pool_partial<true, Q>), grid, dim3(kPoolThreads * Q), 0, s, X, rows, d, tok_offsets, Q, emb);
+  else hipLaunchKernelGGL((pool_partial<false, Q>), grid, dim3(kPoolThreads * Q), 0, s, X, rows, d, tok_offsets, Q, emb);
+}
+
+// Embeddings of a batch, with the bits of the router's: one launch where a prompt is one slice, and for up to POOL_WHOLE_ROWS rows in up
+// to four slices, whose workgroups are one then.  Bound by launches and one or two round trips to memory; bf16, 4096 columns, us, two
+// launches / one: 20 rows 4.7 / 2.8, 64 5.1 / 3.3, 77 5.1 / 3.4, 128 5.7 / 4.7, two prompts of 80 5.4 / 3.4; 256 columns, 77 rows
+// 4.7 / 3.2, 128 5.2 / 4.5 (and a launch less on the host).  The router adds the slices in its second launch, which it needs anyway: there one
+// slice for them all only makes the first launch longer (160 rows 9.6 -> 10.9 us).
+constexpr int POOL_WHOLE_ROWS = 160;
 int launch_pool(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial, float *emb, hipStream_t s) {
   const bool bf16 = xdtype == PARSE_BF16;
-  if (pool_slices(rows, P, d, bf16) == 1) {
-    const int per_block = 64 * (bf16 ? 8 : 4);
-    const dim3 grid((d + per_block - 1) / per_block, 1, P);
-    if (bf16) hipLaunchKernelGGL((pool_partial<true, true>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, 1, emb);
-    else hipLaunchKernelGGL((pool_partial<false, true>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, 1, emb);
+  int Q = pool_slices(rows, P, d, bf16);
+  if (Q == 1 || (Q <= 4 && rows <= POOL_WHOLE_ROWS)) {
+    if (Q == 1) launch_pool_whole<1>(X, bf16, rows, tok_offsets, P, d, emb, s);
+    else if (Q == 2) launch_pool_whole<2>(X, bf16, rows, tok_offsets, P, d, emb, s);
+    else if (Q == 3) launch_pool_whole<3>(X, bf16, rows, tok_offsets, P, d, emb, s);
+    else launch_pool_whole<4>(X, bf16, rows, tok_offsets, P, d, emb, s);
     PARSE_LAUNCH_CHECK();
     return PARSE_OK;
   }
-  int Q = 0;
   const int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
   if (st != PARSE_OK) return st;
   return launch_pool_finish(partial, Q, rows, d, tok_offsets, P, emb, s);

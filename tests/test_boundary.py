@@ -86,6 +86,14 @@ def test_route_rejects_bad_arguments():
     assert pool(ws=None) == -5 and pool(wsb=16) == -5
 
 
+def test_route_workspace_holds_the_slices_of_short_prompts():
+    """One slice for every 32 rows of a prompt, also in small batches: the router's pooling has no other way to fill the chip."""
+    lib = pa.lib()
+    for rows, P, d, slices in [(1, 1, 4096, 1), (63, 1, 4096, 1), (64, 1, 4096, 2), (77, 1, 256, 2), (128, 1, 1024, 4), (160, 1, 4096, 5),
+                               (161, 1, 4096, 5), (160, 2, 4096, 2), (160, 8, 4096, 1), (4096, 8, 4096, 8)]:
+        assert lib.parse_route_workspace_bytes(rows, P, d) == slices * P * d * 4, (rows, P, d)
+
+
 def test_cache_create_rejects_bad_arguments():
     lib = pa.lib()
     h = C.c_void_p()

@@ -62,6 +62,62 @@ def test_route_matches_oracle(dtype, lengths, d, G, k):
     assert torch.equal(emb2, emb) and bool(torch.all(mid[P * d * 4:] == 0xA5))
 
 
+def _pooled_in_order(X, off, Q):
+    """The mean of every prompt's rows, added in float32 in the order that the router documents: rows dealt round robin to the four
+    wavefronts of Q slices, a slice's wavefronts in order, the slices in order."""
+    out = np.zeros((len(off) - 1, X.shape[1]), dtype=np.float32)
+    for p in range(len(off) - 1):
+        total = np.zeros(X.shape[1], dtype=np.float32)
+        for q in range(Q):
+            part = None
+            for w in range(4):
+                acc = np.zeros(X.shape[1], dtype=np.float32)
+                for r in range(off[p] + q * 4 + w, off[p + 1], 4 * Q):
+                    acc += X[r]
+                part = acc if part is None else part + acc
+            total += part
+        if off[p + 1] > off[p]:
+            out[p] = total * (np.float32(1) / np.float32(off[p + 1] - off[p]))
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,lengths,Q", [
+    (1032, [31], 1), (264, [63], 1), (520, [64], 2), (4096, [77], 2), (1024, [96], 3), (256, [127], 3), (4096, [128], 4),
+    (264, [159], 4), (1024, [160], 5), (512, [161], 5), (4096, [1, 130], 2), (512, [40, 0, 120], 1), (1024, [100, 60], 2),
+])
+def test_embeddings_of_short_prompts(dtype, d, lengths, Q):
+    """Embeddings of one to five slices by the embedding-only call, the router and the rank-granular router: the same float32 sums
+    in the same order, bit for bit."""
+    say(f"embeddings dtype={dtype} d={d} lengths={lengths}")
+    rng = np.random.default_rng(103)
+    off, P, G = si.offsets_from_lengths(lengths), len(lengths), 8
+    rows = int(off[-1])
+    X = si.make_tokens(rng, rows, d, dtype)
+    ref = _pooled_in_order(si.bf16_bits_to_f32(X) if dtype == "bf16" else X, off, Q)
+    Xd, offd = upload_tokens(X, dtype), i32(off)
+    Wr = torch.from_numpy(si.make_router(rng, 1, G, d)[0]).to(DEV)
+    assert pa.route_workspace_bytes(rows, P, d) == (P * Q * d * 4 + 255) // 256 * 256
+    got = []
+    for call in range(3):
+        whole, mid = guarded_bytes(P * d * 4)
+        emb = mid[:P * d * 4].view(torch.float32).view(P, d)
+        if call == 0:
+            wholews, ws = guarded_bytes(pa.route_workspace_bytes(rows, P, d))
+            pa.pool(Xd, offd, emb, ws)
+        elif call == 1:
+            wholews, ws = guarded_bytes(pa.route_workspace_bytes(rows, P, d))
+            pa.route(Xd, offd, Wr, 2, emb_out=emb, workspace=ws)
+        else:
+            wholews, ws = guarded_bytes(pa.lib().parse_route_ranks_workspace_bytes(rows, P, d, G))
+            pa.route_ranks(Xd, offd, Wr, 2, emb_out=emb, workspace=ws)
+        torch.cuda.synchronize()
+        check_guards(whole, "embedding"); check_guards(wholews, "workspace")
+        got.append(emb.cpu().numpy())
+    for what, e in zip(("pool", "route", "route_ranks"), got):
+        assert np.array_equal(e.view(np.int32), ref.view(np.int32)), what
+
+
 def test_route_strided_output_and_determinism():
     say("route strided output / repeatability")
     rng = np.random.default_rng(102)
