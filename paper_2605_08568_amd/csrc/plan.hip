@@ -39,46 +39,51 @@ __device__ __forceinline__ void plan_wave(const int32_t *__restrict__ tok_offset
   const int max_v = cap * PLAN_VT;
   const int a = tok_offsets[min(lane, P)], b = tok_offsets[min(lane + 1, P)], v = pattern_id[min(lane, P - 1)];
   const int off = a < 0 ? 0 : (a > rows ? rows : a), end = b < 0 ? 0 : (b > rows ? rows : b);
-  const int len = lane < P ? max(end - off, 0) : 0;
+  const uint32_t len = lane < P ? max(end - off, 0) : 0;
   const int pid = v >= 0 && v < NP ? v : NP;               // NP: ids out of range, after all patterns
-  int before = 0, all = 0, lead = 1;                       // rows of the pattern's earlier prompts, of all its prompts; first of them?
+  // Sums stop at the plan's last row: prompts that overlap (offsets that do not ascend) can claim more rows than an int counts, and
+  // what they claim past the end is not written.
+  const uint32_t most = max_v;
+  uint32_t before = 0, all = 0;                            // rows of the pattern's earlier prompts, of all its prompts
+  bool lead = true;                                        // first of them?
   for (int q = 0; q < P; ++q) {
-    const int opid = __builtin_amdgcn_readlane(pid, q), olen = __builtin_amdgcn_readlane(len, q);
+    const int opid = __builtin_amdgcn_readlane(pid, q);
+    const uint32_t olen = __builtin_amdgcn_readlane(len, q);
     const bool same = opid == pid;
-    all += same ? olen : 0;
-    before += same && q < lane ? olen : 0;
-    lead = same && q < lane ? 0 : lead;
+    all = min(all + (same ? olen : 0u), most);
+    before = min(before + (same && q < lane ? olen : 0u), most);
+    lead = lead && !(same && q < lane);
   }
-  const int padded = lane < P && lead ? (all + PLAN_VT - 1) / PLAN_VT * PLAN_VT : 0;
-  int base = 0, total = 0;                                 // first virtual row of the pattern
+  const uint32_t padded = lane < P && lead ? (all + PLAN_VT - 1) / PLAN_VT * PLAN_VT : 0;
+  uint32_t base = 0, total = 0;                            // first virtual row of the pattern
   for (int q = 0; q < P; ++q) {
-    const int opad = __builtin_amdgcn_readlane(padded, q);
-    base += __builtin_amdgcn_readlane(pid, q) < pid ? opad : 0;
-    total += opad;
+    const uint32_t opad = __builtin_amdgcn_readlane(padded, q);
+    base = min(base + (__builtin_amdgcn_readlane(pid, q) < pid ? opad : 0u), most);
+    total = min(total + opad, most);
   }
-  total = min(total, max_v);
   const int gid = block * PLAN_THREADS + tid;
   if (gid == 0) { plan[0] = total / PLAN_VT; plan[1] = total; plan[2] = PLAN_VT; plan[3] = cap; }
   else if (gid >= 4 && gid < PLAN_HDR) plan[gid] = 0;
   // pattern of each tile, and the padding rows at the end of each pattern: the first prompt of the pattern says where
   for (int q = block; q < P; q += nblocks) {
-    const int n = __builtin_amdgcn_readlane(padded, q);
+    const uint32_t n = __builtin_amdgcn_readlane(padded, q);
     if (n == 0) continue;                                  // uniform
-    const int b0 = __builtin_amdgcn_readlane(base, q), i = __builtin_amdgcn_readlane(pid, q), used = __builtin_amdgcn_readlane(all, q);
-    for (int t = b0 / PLAN_VT + tid; t < (b0 + n) / PLAN_VT; t += PLAN_THREADS)
-      if (t < cap) tile_pat[t] = i < NP ? i : -1;
-    for (int w = b0 + used + tid; w < b0 + n; w += PLAN_THREADS)
-      if (w < max_v) rowmap[w] = -1;
+    const uint32_t b0 = __builtin_amdgcn_readlane(base, q), used = __builtin_amdgcn_readlane(all, q), b1 = min(b0 + n, most);
+    const int i = __builtin_amdgcn_readlane(pid, q);
+    for (uint32_t t = b0 / PLAN_VT + tid; t < b1 / PLAN_VT; t += PLAN_THREADS) tile_pat[t] = i < NP ? i : -1;
+    for (uint32_t w = b0 + used + tid; w < b1; w += PLAN_THREADS) rowmap[w] = -1;
   }
   // the rows of this workgroup's share, prompt by prompt
-  const int vstart = base + before;
+  const uint32_t vstart = min(base + before, most);
   const int r0 = (int)((long long)rows * block / nblocks), r1 = (int)((long long)rows * (block + 1) / nblocks);
   for (int q = 0; q < P; ++q) {
-    const int s = __builtin_amdgcn_readlane(off, q), e = s + __builtin_amdgcn_readlane(len, q);
-    const int to = __builtin_amdgcn_readlane(vstart, q) - s;
+    const int s = __builtin_amdgcn_readlane(off, q), e = s + (int)__builtin_amdgcn_readlane(len, q);
+    const uint32_t to = __builtin_amdgcn_readlane(vstart, q);
     if (e <= r0 || s >= r1) continue;                      // uniform
-    for (int r = max(s, r0) + tid; r < min(e, r1); r += PLAN_THREADS)
-      if (to + r < max_v) rowmap[to + r] = r;
+    for (int r = max(s, r0) + tid; r < min(e, r1); r += PLAN_THREADS) {
+      const uint32_t at = to + (uint32_t)(r - s);
+      if (at < most) rowmap[at] = r;
+    }
   }
 }
 

@@ -438,6 +438,25 @@ def test_bucket_and_plan_in_one_launch_equal_the_separate_calls(P, k, npat, stri
     assert np.array_equal(words[:16 + nt], ref_words[:16 + nt]) and np.array_equal(words[rm0:rm0 + nt * 256], ref_words[rm0:rm0 + nt * 256])
 
 
+@pytest.mark.parametrize("patterns", [1, 3, 32])
+def test_plan_of_overlapping_prompts_stays_inside(patterns):
+    """Offsets that do not ascend: every second prompt claims all of 150 million rows, together more than 2^31.  The plan says no more
+    tiles than it has room for, and nothing is written outside it."""
+    rows, P = 150_000_000, 32
+    say(f"plan of overlapping prompts, {patterns} patterns")
+    off = i32([0, rows] * (P // 2) + [0])
+    pid = i32(np.arange(P) // 2 % patterns)
+    whole, plan = guarded_bytes(pa.prefill_plan_bytes(rows, P, patterns))
+    pa.prefill_plan(off, pid, rows, patterns, plan)
+    check_guards(whole, "plan")
+    words = plan.view(torch.int32)
+    tiles, vrows, _, cap = (int(v) for v in words[:4].cpu())
+    assert tiles == cap == (rows + 255) // 256 + min(P, patterns + 1) and vrows == cap * 256
+    rm0 = 16 + (cap + 15) // 16 * 16
+    assert torch.equal(words[rm0:rm0 + rows], torch.arange(rows, dtype=torch.int32, device=DEV))       # the first prompt's rows
+    assert int(words[rm0:rm0 + vrows].max()) < rows and int(words[16:16 + cap].min()) >= 0 and int(words[16:16 + cap].max()) < patterns
+
+
 # ------------------------------------------------------------------ a4 pack (+ offline reorder)
 @pytest.mark.parametrize("dtype,n,m,R,G,subset", [
     ("f32", 1024, 1024, 256, 8, [1, 2, 5, 7]),
