@@ -7,6 +7,9 @@ namespace parse {
 
 constexpr int kBucketMaxK = 64;
 constexpr int kBucketMaxP = 1024;
+// Up to here buckets and prefill plans are worked out in registers (bucket_wave, plan_wave).  The host chooses: with both forms in one
+// kernel the other one was 0.3-0.6 us slower.
+constexpr int kFewPrompts = 16;
 
 // inclusive scan of v[0..T) in LDS, T = blockDim.x a multiple of 64; every lane takes part
 __device__ __forceinline__ void block_scan_inclusive(int32_t *v, int T) {
@@ -19,8 +22,10 @@ __device__ __forceinline__ void block_scan_inclusive(int32_t *v, int T) {
   }
 }
 
-// Up to 64 prompts: one wavefront, everything in registers (P readings of a lane in place of scans in LDS, some forty barriers in
-// a workgroup of 256): 3.9 -> 2.1 us for four prompts.  All 64 lanes of the wavefront take part.
+// Few prompts: one wavefront, everything in registers (P readings of a lane in place of scans in LDS, some forty barriers
+// in a workgroup of 256).  All 64 lanes of the wavefront take part.  The readings are a chain that grows with P, the scans do not (us, scans /
+// registers, k = 4, all alike and all different: 4 prompts 4.1 / 2.7 and 3.9 / 2.3, 16 4.4 / 4.1 and 5.3 / 3.9, 24 4.5 / 5.1 and 6.3 / 5.0, 64
+// 5.1 / 10.2; k = 64, pairs alike: 16 55.9 / 55.8, 24 80 / 82).
 __device__ __forceinline__ void bucket_wave(const int32_t *__restrict__ subset, int P, int k, int stride, int32_t *__restrict__ pattern_id,
                                             int32_t *__restrict__ perm, int32_t *__restrict__ bucket_off,
                                             int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
@@ -63,11 +68,12 @@ __device__ __forceinline__ void bucket_wave(const int32_t *__restrict__ subset, 
   }
 }
 
+template <bool FEW>
 __device__ __forceinline__ void bucket_body(const int32_t *__restrict__ subset, int P, int k, int stride,
                                                         int32_t *__restrict__ pattern_id, int32_t *__restrict__ perm,
                                                         int32_t *__restrict__ bucket_off,
                                                         int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
-  if (P <= 64) {                           // uniform
+  if constexpr (FEW) {
     if (threadIdx.x < 64) bucket_wave(subset, P, k, stride, pattern_id, perm, bucket_off, n_patterns, rep);
     return;
   }

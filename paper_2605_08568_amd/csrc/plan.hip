@@ -27,10 +27,10 @@ static inline int plan_capacity_tiles(int rows, int P, int n_patterns) {
 }
 static inline size_t plan_words(int cap) { return (size_t)PLAN_HDR + (size_t)((cap + 15) / 16 * 16) + (size_t)cap * PLAN_VT; }
 
-// Up to 32 prompts (PLAN_WAVE_P): every wavefront works the tables out in its registers, lane p for prompt p, by P readings of a
-// lane: no LDS, no barrier, one round trip to memory before the rows are written.  With the buckets in the same launch 5.3 -> 2.5 us for one
-// prompt of 77 tokens, 5.8 -> 4.2 for eight of 512, 7.8 both for twenty ragged ones.
-constexpr int PLAN_WAVE_P = 32;
+// Few prompts: every wavefront works the tables out in its registers, lane p for prompt p, by P readings of a
+// lane: no LDS, no barrier, one round trip to memory before the rows are written.  The readings grow with P (us, tables in LDS / in
+// registers: one prompt of 300 tokens 4.8 / 2.2, eight of 300 5.7 / 4.2, 16 of 300 6.5 / 5.8, 16 of 20 tokens and 4 patterns 6.9 / 7.0, 20 of
+// those 7.5 / 8.3, 20 of 2000 5.7 / 5.8, 32 of 2000 6.5 / 8.0).
 __device__ __forceinline__ void plan_wave(const int32_t *__restrict__ tok_offsets, const int32_t *__restrict__ pattern_id, int P, int rows,
                                           int NP, int cap, int32_t *__restrict__ plan, int block, int nblocks) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -90,10 +90,11 @@ __device__ __forceinline__ void plan_wave(const int32_t *__restrict__ tok_offset
 // Every workgroup works out the (small) per-pattern and per-prompt tables in its own LDS -- integer work, the same in
 // every workgroup -- and then fills its share of the row map.
 // (block, nblocks) = this workgroup's place among the workgroups that build the plan.
+template <bool FEW>
 __device__ __forceinline__ void plan_body(const int32_t *__restrict__ tok_offsets, const int32_t *__restrict__ pattern_id,
                                           int P, int rows, int NP, int cap, int32_t *__restrict__ plan, int block,
                                           int nblocks) {
-  if (P <= PLAN_WAVE_P) {                            // uniform
+  if constexpr (FEW) {
     plan_wave(tok_offsets, pattern_id, P, rows, NP, cap, plan, block, nblocks);
     return;
   }
@@ -191,10 +192,11 @@ __device__ __forceinline__ void plan_body(const int32_t *__restrict__ tok_offset
   }
 }
 
+template <bool FEW>
 __global__ __launch_bounds__(PLAN_THREADS) void plan_build(const int32_t *__restrict__ tok_offsets,
                                                            const int32_t *__restrict__ pattern_id, int P, int rows,
                                                            int NP, int cap, int32_t *__restrict__ plan) {
-  plan_body(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x);
+  plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x);
 }
 
 // The plan and the buckets of a batch in one launch (they depend on the same probe results and not on each other): the
@@ -204,13 +206,14 @@ struct BucketArgs {
   int k, stride;
   int32_t *pattern_id, *perm, *bucket_off, *n_patterns, *rep;
 };
+template <bool FEW>
 __global__ __launch_bounds__(PLAN_THREADS) void bucket_and_plan(BucketArgs b, const int32_t *__restrict__ tok_offsets,
                                                                 const int32_t *__restrict__ pattern_id, int P, int rows,
                                                                 int NP, int cap, int32_t *__restrict__ plan) {
   if (blockIdx.x + 1 == gridDim.x)     // uniform
-    bucket_body(b.subset, P, b.k, b.stride, b.pattern_id, b.perm, b.bucket_off, b.n_patterns, b.rep);
+    bucket_body<FEW>(b.subset, P, b.k, b.stride, b.pattern_id, b.perm, b.bucket_off, b.n_patterns, b.rep);
   else
-    plan_body(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x - 1);
+    plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x - 1);
 }
 
 size_t prefill_plan_bytes(int rows, int P, int n_patterns) {
@@ -228,7 +231,7 @@ int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, in
                        int32_t *plan, hipStream_t s) {
   const int cap = plan_capacity_tiles(rows, P, n_patterns);
   const int grid = plan_grid(rows);
-  hipLaunchKernelGGL(plan_build, dim3(grid), dim3(PLAN_THREADS), 0, s, tok_offsets, pattern_id, P, rows, n_patterns, cap, plan);
+  hipLaunchKernelGGL((P <= kFewPrompts ? plan_build<true> : plan_build<false>), dim3(grid), dim3(PLAN_THREADS), 0, s, tok_offsets, pattern_id, P, rows, n_patterns, cap, plan);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
@@ -272,7 +275,7 @@ int parse_bucket_and_plan(const int32_t *subset, int32_t P, int32_t k, int32_t s
     return build_prefill_plan(tok_offsets, plan_pattern_id, P, rows, n_patterns, (int32_t *)plan, s);
   }
   const BucketArgs b{subset, k, subset_stride, pattern_id_out, perm, bucket_off, n_patterns_out, rep};
-  hipLaunchKernelGGL(bucket_and_plan, dim3(plan_grid(rows) + 1), dim3(PLAN_THREADS), 0, s, b, tok_offsets, plan_pattern_id, P,
+  hipLaunchKernelGGL((P <= kFewPrompts ? bucket_and_plan<true> : bucket_and_plan<false>), dim3(plan_grid(rows) + 1), dim3(PLAN_THREADS), 0, s, b, tok_offsets, plan_pattern_id, P,
                      rows, n_patterns, plan_capacity_tiles(rows, P, n_patterns), (int32_t *)plan);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
