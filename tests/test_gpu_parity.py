@@ -1585,11 +1585,14 @@ def test_prefill_fp32_edges(n, m, R, G, k, lengths):
     (256, 128, 96, 3, [33, 1, 30, 1]),               # 64 x 64 tiles, a rank tile past the end, prompts inside a token block
     (128, 256, 2080, 13, [700, 613]),                # 128 x 128 tiles, group borders inside a tile (160 ranks per group)
     (128, 128, 2048, 64, [3000, 1, 71]),             # 256 x 128 tiles, 64 groups of 32
+    # both larger tiles with two reductions of more than twice the stages of their ring (4 and 3), no multiple of them
+    (640, 896, 2080, 13, [700, 613]),
+    (640, 896, 2048, 64, [3000, 1, 71]),
 ])
 def test_router_grad_tiles(n, m, R, G, lengths):
     """Loss and gradient of parse_router_grad for given outputs, every tile of its paired product, against float64.  The only
     16-bit rounding inside is that of the residual 2 (y_hat - y), which the reference does too; the rest is fp32 sums (at
-    most 256 products, 160 ranks, 3000 tokens): 2^-24 of their absolute sums per addition, and the differences between the
+    most 896 products, 160 ranks, 3000 tokens): 2^-24 of their absolute sums per addition, and the differences between the
     groups' terms cancel them down by up to a hundredfold, hence 1e-4."""
     say(f"router_grad n={n} m={m} R={R} G={G} lengths={lengths}")
     rng = np.random.default_rng(1201)
@@ -1691,7 +1694,7 @@ def test_decode_many_sequences_slices(n, shapes, rows):
     (64, 64, 768, [64, 4097, 300]),
     (64, 64, 1792, [4200]),
     (128, 64, 2048, [4300]),
-    # second product: 256 x 256 tiles with slices of 64 and of 32
+    # second product: 256 x 256 tiles, one and two prompts, two and three slices of 32
     (64, 4096, 64, [4096]),
     (64, 4096, 96, [2048, 2048]),
     # short batches with a long reduction: slices, added by a second launch
@@ -1708,7 +1711,9 @@ def test_decode_many_sequences_slices(n, shapes, rows):
     (576, 96, 256, [1500, 2800, 1]),
     (640, 64, 768, [64, 4097, 300]),
     (448, 64, 1792, [4200]),
-    # ... and second products (256 x 256 with slices of 64 and of 32; 128 x 128, 128 x 256)
+    (704, 96, 128, [1500, 2800, 1]),                 # rings of five stages: 64 x 64 ...
+    (704, 64, 768, [64, 4097, 300]),                 # ... and 128 x 128
+    # ... and second products (256 x 256, ten and eleven slices; 128 x 128, 128 x 256)
     (64, 4096, 320, [4096]),
     (64, 4096, 352, [2048, 2048]),
     (64, 2080, 320, [5000]),
