@@ -391,7 +391,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
 // the start of time h everything requested up to time h - 3 has landed (8 loads a wavefront may be outstanding; fewer are requested
 // near the end), so a load has two halves, 2000 cycles, to arrive.  The sums are those of the other tiles, in the same order.
 // 32768 rows x 1024 ranks of eight patterns, n = m = 4096, both products on large tiles: 526 us with slices of 64, two stages and
-// 32x32x16 instructions, 480 now; 1280 ranks, 11008 columns: 1264 and 1160.
+// 32x32x16 instructions, 462-480 now; 1280 ranks, 11008 columns: 1264 and 1160.
 __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
   constexpr int F_HALF = 16384, T_SLICE = 32768, T_BASE = 4 * F_HALF;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -605,9 +605,9 @@ static int launch_first256(const LgArgs &a, int avg_tiles_per_pattern, hipStream
 // Token tiles of bm rows, as far as the host can tell: it does not know which prompts share a pattern, and a pattern starts on a
 // tile of its own.  Prompts of one length that are a multiple of bm leave nothing open; otherwise full tiles and one more are
 // taken for the number.  (Half a tile more for every prompt is closer when every prompt has its own pattern, but many prompts of
-// few patterns then get tiles that are far too large: 24 prompts of 20-300 tokens, n = m = 2048, 512 ranks, both products, us:
-// 40.9 against 35.5 with two patterns, 45.9 and 52.3 with 24.  Over 330 batches of 1 to 100 prompts full tiles come closer to the
-// best tile of each: 1 % off it on average, 4 % with the other estimate.)
+// few patterns then get tiles that are too large: 24 prompts of 20-300 tokens, n = m = 2048, 512 ranks, both products, us, first one
+// on 64 x 128 / 128 x 128 tiles: 29.8 / 32.4 with two patterns, 44.6 / 38.8 with 24.  Over 70 batches of 1 to 40 prompts the tile chosen is
+// 2.7 % off the best of each on average, 29 % at worst: ragged prompts, nearly every one with its own pattern or nearly none.)
 static long long token_tiles(int rows, int P, int bm) {
   if (rows % P == 0 && rows / P % bm == 0) return rows / bm;
   return (rows + bm - 1) / bm + (P > 1 ? 1 : 0);
@@ -641,10 +641,10 @@ size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks) {
 bool prefill_planned_supported(int n, int m, int rS) { return n % 64 == 0 && rS % 32 == 0 && m % 32 == 0 && n >= 64 && rS >= 32; }
 
 // Time of the first product with tile i, in units of a round of 128 x 128 tiles, one per compute unit (30 us at K = 4096).
-// Measured over 16 shapes of 77 to 57 000 rows and 512 to 3072 ranks, further rounds of the small tiles (two workgroups of
-// 64 x 64 per unit) over the batches above.  E.g. 2048 rows x 2304 ranks, both products, us, 256 x 256 / 128 x 256 / 128 x 128 /
-// 64 x 128 / 64 x 64: 142 / 110 / 121 / 118 / 118; 4096 x 1024 136 / 101 / 86 / 88 / 95; 2048 x 768 108 / 74 / 55 / 48 / 49; 32768 x 1024
-// 557 / 587 / 654 / 706 / 776.
+// Fitted to earlier forms of these kernels, over shapes of 77 to 57 000 rows and 512 to 3072 ranks, and still in their order for the present
+// ones: n = m = 4096, both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: one prompt of 2048 rows x 2304 ranks 115 / 85 /
+// 94 / 95 / 95, x 768 ranks 95 / 62 / 46 / 38 / 42; eight of 512 x 1024 111 / 78 / 68 / 76 / 82, of 1024 x 1024 147 / 124 / 138 / 151 / 161, of 4096 x
+// 1024 462 / 517 / 573 / 651 / 694.
 enum { T64, T64x128, T128, T128x256, T256, N_TILES };
 static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split = 1) {
   static const int bm[N_TILES] = {64, 64, 128, 128, 256}, bn[N_TILES] = {64, 128, 128, 256, 256};
@@ -667,9 +667,9 @@ static int best_tile(const PfArgs *const *p, int n_layers) {
   return best;
 }
 // Slices of one layer's first product: as many (up to four) as pay for the second launch, which adds the fp32 partial sums (2 us
-// and a pass over them).  77 rows, n = 4096, 1024 ranks, both products: 25.4 us with four, 26-28 with two, three or eight, 31.7
-// without; 300 rows x 1024 ranks 24 and 27; 700 x 1024 34 (two) and 31; n = 11008: 534 rows x 384 ranks 33 (three) and 54, 643 x
-// 384 40 (two) and 58, 1024 x 1280 85 (two) and 83; n = 5632, 546 x 640 25.5 (two) and 30.6.  A function of the batch and of this
+// and a pass over them).  77 rows, n = 4096, 1024 ranks, both products: 18.6 us with four, 20.1 and 19.1 with two and three, 22.2
+// without; 300 rows x 1024 ranks 23.4 (two), 25.1 (three) and 24.8; 700 x 1024 32.6 (two) and 28.3; n = 11008: 534 rows x 384 ranks 35.8 (three)
+// and 41.3, 643 x 384 32.1 (two) and 41.6, 1024 x 1280 76 (two) and 63; n = 5632, 546 x 640 27-29 and 27.  A function of the batch and of this
 // layer alone, so that a call over several layers splits each like its single-layer call and gives the same bits -- as long as
 // both have their queried workspace: with more than 1024 rows and no room for the partial sums a call is not cut.
 // Batches of more than 1024 rows are split on reductions of 8192 and more, in four slices of 128 x 256 tiles: those move the
@@ -762,9 +762,9 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
   auto tiles2 = [&](int bm, int bn) { long long t = 0; for (int l = 0; l < n_layers; ++l) t += (p[l].m + bn - 1) / bn; return t * token_tiles(rows, P, bm); };
   // Second product: 256 x 256 tiles where their number is as good as known and they fill their rounds, or there are many; else 128 x 256,
   // two to a compute unit, whose stores and starts overlap and whose last round is shorter; smaller tiles as these run out
-  // (both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: 4096 rows x 4096 columns 83 / 85 / 90 / 94 / 106; 2048 x 12288 125 / 119 / 121 /
-  // 126 / 142; 2048 x 4096 57 / 52 / 50 / 53 / 57; 1100 x 4096 61 / 53 / 51 / 49 / 53; 77 x 4096 44 / 37 / 31 / 27 / 25; 1533 rows of 40
-  // prompts x 1024 columns 21 / 19 / 16 / 15 / 17).
+  // (both products, n = 4096, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: eight prompts of 512 rows x 4096 columns, 1024 ranks 68 / 68 / 70 /
+  // 76 / 87, of 4096 465 / 474 / 487 / 553 / 638; one prompt, 768 ranks: 2048 rows x 12288 columns 69 / 59 / 62 / 69 / 83, 2048 x 4096 45 / 39 / 39 / 40 / 45,
+  // 1100 x 4096 47 / 40 / 40 / 38 / 42; 77 x 4096, 1024 ranks 34 / 27 / 22 / 20 / 18; n = 1024, 1533 rows of 40 prompts x 1024 columns, 512 ranks 32 / 27 / 27 / 26 / 29).
   const long long u256 = tiles2(256, 256);
   const bool full = rows % P == 0 && rows / P % 256 == 0 && (double)u256 >= 0.88 * 256 * ((u256 + 255) / 256);
   if (full || u256 >= 1792) return launch_gemm_lds<256, 256, 2, 4, 32, 5, 1, 0, 1>(g2, per_pattern, s);
