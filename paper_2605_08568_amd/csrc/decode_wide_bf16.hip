@@ -12,7 +12,7 @@
 // is in flight is DEPTH steps per wavefront (about 40 KiB; one wavefront per SIMD, so the registers are there).
 // Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
 // Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns: wide_z 16 us for gate+up and 19 for down
-// (18 and 20 with operands straight into registers, and a launch of 4-6 us that brought x into operand order; 112 us a step against 118):
+// (18 and 20 with operands straight into registers, and a launch of 4-6 us that brought x into operand order; 113 us a step against 118):
 // 4.7 us until the first slice is there, the factors at 4 TB/s, 1.6 us for the sums; wide_y 28 and 14 us; five panels one after the other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
@@ -228,14 +228,17 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
     for (int t = 0; t < TB; ++t) asm volatile("" ::"v"(tr[half][t]));
     __builtin_amdgcn_sched_barrier(0);
   };
-  f32x4v acc[TB];
+  // Four sums of a value, added at the end: the two halves of even and of odd slices.  One alone is farther from the exact value (z rounded
+  // the other way to bf16, 4096 x 4096 ranks: 223 values in a million with one, 129 with four; 0.5 us of 113).
+  f32x4v acc[4][TB];
 #pragma unroll
-  for (int t = 0; t < TB; ++t) acc[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
-  auto products = [&](int half, int q0, int q1, bool more, bool steady) {
+  for (int t = 0; t < TB; ++t) acc[0][t] = acc[1][t] = acc[2][t] = acc[3][t] = f32x4v{0.f, 0.f, 0.f, 0.f};
+  auto products = [&](int odd, int half, int q0, int q1, bool more, bool steady) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < TB; ++t) {
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[half]), as_bf16x8(tr[half][t]), acc[t], 0, 0, 0);
+      f32x4v &sum = acc[odd * 2 + half][t];
+      sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fr[half]), as_bf16x8(tr[half][t]), sum, 0, 0, 0);
 #pragma unroll
       for (int q = q0; q < q1; ++q)
         if (t == (q - q0) * TB / (q1 - q0)) {
@@ -253,12 +256,12 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
       for (int t = 0; t < TB; ++t) tr[half][t] = u32x4{0, 0, 0, 0};
     }
   };
-  auto slice = [&](bool steady, int kt) {
+  auto slice = [&](bool steady, int odd, int kt) {
     const bool cut = !steady && ragged && kt == nk - 1;
     settle(0);
     read_half(1);
     if (cut) clear_past(0, kt);
-    products(0, H, L, steady || kt - 1 + STAGES < nk, steady);
+    products(odd, 0, H, L, steady || kt - 1 + STAGES < nk, steady);
     settle(1);
     if (cut) clear_past(1, kt);
     if (steady || kt + 1 < nk) {                       // slice kt + 1 has landed for everybody, slice kt has been read by everybody
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
       src = src + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : src + STAGE_BYTES;
       read_half(0);
     }
-    products(1, 0, H, steady || kt + STAGES < nk, steady);
+    products(odd, 1, 0, H, steady || kt + STAGES < nk, steady);
   };
 #pragma unroll
   for (int s = 0; s < STAGES; ++s) {
@@ -280,21 +283,29 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
   wg_barrier();
   read_half(0);
   int kt = 0;
-  for (; kt + STAGES + 1 < nk; ++kt) slice(true, kt);  // what it requests are whole slices
-  for (; kt < nk; ++kt) slice(false, kt);
+  for (; kt + STAGES + 2 < nk; kt += 2) {              // what they request are whole slices
+    slice(true, 0, kt);
+    slice(true, 1, kt + 1);
+  }
+  for (; kt < nk; kt += 2) {
+    slice(false, 0, kt);
+    if (kt + 1 < nk) slice(false, 1, kt + 1);
+  }
 
   if (i0 + (wr >> 1) >= nused) return;
+#pragma unroll
+  for (int t = 0; t < TB; ++t) acc[0][t] = (acc[0][t] + acc[1][t]) + (acc[2][t] + acc[3][t]);
   const int rb16 = rb * 2 + (wr & 1), skip = wave >> 2 ? 2 * PW - NT : 0;        // the other half stores the middle panel
   if (KS > 1) {
     float *dst4 = ly.zpart + (((size_t)rb16 * KS + sl) * NT + p0) * 512 + lane * 4;
 #pragma unroll
     for (int t = 0; t < TB; ++t)
-      if (t >= 2 * skip) *reinterpret_cast<f32x4v *>(dst4 + t * 256) = acc[t];
+      if (t >= 2 * skip) *reinterpret_cast<f32x4v *>(dst4 + t * 256) = acc[0][t];
   } else {
 #pragma unroll
     for (int p = 0; p < PW; ++p)
       if (p >= skip)
-        wide_store_z(acc[2 * p], acc[2 * p + 1], (uint32_t)ly.plan[128 + (p0 + p) * 64 + grp], lane, (char *)ly.zf + ((size_t)(p0 + p) * (ly.R / 16) + rb16) * 1024);
+        wide_store_z(acc[0][2 * p], acc[0][2 * p + 1], (uint32_t)ly.plan[128 + (p0 + p) * 64 + grp], lane, (char *)ly.zf + ((size_t)(p0 + p) * (ly.R / 16) + rb16) * 1024);
   }
 }
 
