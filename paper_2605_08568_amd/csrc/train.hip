@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void train_residual(const uint16_t *__restrict
 // 16x16x32 products, one barrier per slice, no branches in the steady part but the one where the second product's operands begin.
 // The slices of the second product follow those of the first in the same ring: nothing drains between the two.
 // Measured at 4096 rows, n = m = 4096, R = 2048: the two separate products and the pass over their outputs took 90 + 90 +
-// 19 us; this kernel 109-120 us (137 GFLOP), 139-156 with 32x32x16 products and the loads of a slice in a row.
+// 19 us; this kernel 109-125 us (137 GFLOP), 139-156 with 32x32x16 products and the loads of a slice in a row.
 template <int BM, int BN, int WM, int WN, int STAGES>
 __global__ __launch_bounds__(WM * WN * 64, 2) void train_pair(TrainPair a) {
   constexpr int NW = WM * WN;
