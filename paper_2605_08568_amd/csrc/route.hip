@@ -1,14 +1,12 @@
 // a1 + a2: prompt pooling and the linear router with top-k (Sec. 4.1, Eq. 5).
 //
-// Two launches, both deterministic:
-//   pool_partial  grid (column blocks of 64 lanes x 16 bytes, Q row slices, P prompts): the rows of a prompt are
-//                 dealt round robin to the wavefronts of its Q workgroups, 16 rows in flight per wavefront; the
-//                 four wavefronts of a workgroup add up through LDS in wavefront order; fp32 partial sums per
-//                 slice, rows streamed once.  Embeddings alone (pool, rank-granular router): where the slices fit in one
-//                 workgroup and pay for it, they are added there, in the same order, and the launch writes the means.
-//   route_finish  one block per prompt: adds the Q partials in slice order, divides by the length,
-//                 scores the G groups (one wavefront per group, butterfly reduction) and selects the
-//                 top k with a rank count inside one wavefront.
+// The rows of a prompt are dealt round robin to 4 Q chains of sums (Q slices of four), the chains of a slice are added in order, then
+// the slices in order; fp32, rows streamed once, the same bits whichever kernel does it:
+//   pool_rows     a workgroup holds all chains of 16 lanes' (or 8, or 32) columns of a prompt and writes the means: one launch
+//   pool_partial  a workgroup is one slice of 64 lanes' columns, its sums go to memory and pool_finish or route_finish adds
+//                 them: long prompts that are too few for one workgroup each to fill the chip
+//   route_finish  one block per prompt: the embedding, or its sum of the Q partials, scores the G groups (one
+//                 wavefront per group, butterfly reduction) and selects the top k with a rank count inside one wavefront.
 #include "common.hpp"
 #include "topk.hpp"
 
@@ -18,15 +16,13 @@ constexpr int kPoolThreads = 256, kPoolWaves = kPoolThreads / 64;
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// WHOLE > 0: the workgroup holds all WHOLE slices (= Q, grid.y 1) and writes the mean itself: same sums, same order, no second launch.
-template <bool BF16, int WHOLE>
-__global__ __launch_bounds__(kPoolThreads * (WHOLE > 0 ? WHOLE : 1)) void pool_partial(const void *__restrict__ X, int rows, int d,
+template <bool BF16, bool MEAN>
+__global__ __launch_bounds__(kPoolThreads) void pool_partial(const void *__restrict__ X, int rows, int d,
                                                              const int32_t *__restrict__ tok_offsets,
                                                              int Q, float *__restrict__ partial) {
   constexpr int PER = BF16 ? 8 : 4;  // columns per lane = 16 bytes
   constexpr int U = 16;              // rows a wavefront has in flight
-  constexpr int NQ = WHOLE > 0 ? WHOLE : 1;    // slices of this workgroup
-  __shared__ float red[NQ * kPoolWaves - 1][PER][64];
+  __shared__ float red[kPoolWaves - 1][PER][64];
   const int p = blockIdx.z, q = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c0 = (blockIdx.x * 64 + lane) * PER;
@@ -75,24 +71,81 @@ __global__ __launch_bounds__(kPoolThreads * (WHOLE > 0 ? WHOLE : 1)) void pool_p
     for (int w = 0; w < kPoolWaves - 1; ++w)
 #pragma unroll
       for (int i = 0; i < PER; ++i) acc[i] += red[w][i][lane];
-    for (int sl = 1; sl < NQ; ++sl) {
-      const int w0 = sl * kPoolWaves - 1;      // the slice's first wavefront
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        float part = red[w0][i][lane];
-#pragma unroll
-        for (int w = 1; w < kPoolWaves; ++w) part += red[w0 + w][i][lane];
-        acc[i] += part;
-      }
-    }
-    if (WHOLE) {
+    if (MEAN) {                                  // Q == 1: the embedding itself
       const float inv = b > a ? 1.0f / (float)(b - a) : 0.f;
 #pragma unroll
       for (int i = 0; i < PER; ++i) acc[i] *= inv;
     }
-    float *dst = partial + ((size_t)p * (WHOLE ? 1 : Q) + q) * d + c0;
+    float *dst = partial + ((size_t)p * Q + q) * d + c0;
 #pragma unroll
     for (int i = 0; i < PER; i += 4) *reinterpret_cast<float4 *>(dst + i) = float4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
+  }
+}
+
+// Workgroup = (prompt, 1 << lwl lanes of 16 bytes of columns, all 4 Q chains): lane l of chain c adds rows c, c + 4 Q, ... of its
+// columns.  Bound by HBM for long prompts, by a round trip to memory and the launch for short ones.
+constexpr int kPoolRowsThreads = 1024;       // the most
+template <bool BF16>
+__global__ __launch_bounds__(kPoolRowsThreads) void pool_rows(const void *__restrict__ X, int rows, int d, const int32_t *__restrict__ tok_offsets,
+                                                              int Q, int lwl, float *__restrict__ emb) {
+  constexpr int PER = BF16 ? 8 : 4;  // columns per lane = 16 bytes
+  constexpr int U = 16;              // rows a lane has in flight
+  extern __shared__ __attribute__((aligned(16))) float red[];      // [chain][column]
+  const int p = blockIdx.y;
+  const int cols = PER << lwl, chains = Q * kPoolWaves;
+  const int chain = (int)threadIdx.x >> lwl, lane = (int)threadIdx.x & ((1 << lwl) - 1);
+  const int c0 = blockIdx.x * cols + lane * PER;
+  const int a = clampi(tok_offsets[p], 0, rows);
+  const int b = clampi(tok_offsets[p + 1], a, rows);
+  float acc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) acc[i] = 0.f;
+  // loads and sums as in pool_partial; U steps of a chain are at most 128 MiB
+  const char *xr = reinterpret_cast<const char *>(X) + ((size_t)(a + chain) * d + min(c0, d - PER)) * (BF16 ? 2 : 4);
+  const uint32_t step = (uint32_t)chains * d * (BF16 ? 2 : 4);
+  for (int left = b - a - chain > 0 ? (b - a - chain - 1) / chains : -1; left >= 0; left -= U) {   // rows of the chain after this one
+    u32x4 v[U];
+    uint32_t at = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = *reinterpret_cast<const u32x4 *>(xr + at);
+      at += u < left ? step : 0u;
+    }
+    xr += (size_t)U * step;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u <= left) {
+        if constexpr (BF16) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            acc[2 * i] += __uint_as_float(v[u][i] << 16);
+            acc[2 * i + 1] += __uint_as_float(v[u][i] & 0xFFFF0000u);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[i] += __uint_as_float(v[u][i]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PER; i += 4)
+    *reinterpret_cast<float4 *>(red + chain * cols + lane * PER + i) = float4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
+  __syncthreads();
+  const float inv = b > a ? 1.0f / (float)(b - a) : 0.f;
+  for (int c = threadIdx.x; c < cols; c += blockDim.x) {
+    if ((int)blockIdx.x * cols + c >= d) break;
+    float total = 0.f;
+#pragma unroll 4
+    for (int q = 0; q < Q; ++q) {
+      const float *s = red + q * kPoolWaves * cols + c;
+      float part = s[0];
+#pragma unroll
+      for (int w = 1; w < kPoolWaves; ++w) part += s[w * cols];
+      total += part;
+    }
+    emb[(size_t)p * d + blockIdx.x * cols + c] = total * inv;
   }
 }
 
@@ -111,7 +164,11 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__re
   const int a = clampi(tok_offsets[p], 0, rows);
   const int b = clampi(tok_offsets[p + 1], a, rows);
   const float inv = (b > a) ? 1.0f / (float)(b - a) : 0.f;
-  // four columns per lane, the Q slice partials added in slice order (independent loads, fixed order of adds)
+  // four columns per lane, the Q slice partials added in slice order (independent loads, fixed order of adds); Q == 0: the embeddings
+  if (Q == 0) {
+    for (int c = threadIdx.x * 4; c < d; c += kFinishThreads * 4)
+      *reinterpret_cast<float4 *>(e + c) = *reinterpret_cast<const float4 *>(partial + (size_t)p * d + c);
+  } else
   for (int c = threadIdx.x * 4; c < d; c += kFinishThreads * 4) {
     const float *src = partial + (size_t)p * Q * d + c;
     float4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -145,51 +202,55 @@ static int pool_slices(int rows, int P, int d, bool bf16) {
   return (int)q;
 }
 
-// Launches pool_partial into `partial` ([P][Q][d] floats, Q returned)
-static int launch_pool_partials(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial,
-                                int *Q_out, hipStream_t s) {
-  const bool bf16 = xdtype == PARSE_BF16;
-  const int Q = pool_slices(rows, P, d, bf16);
+// Launches pool_partial into `partial` ([P][Q][d] floats)
+template <bool MEAN>
+static int launch_pool_partials(const void *X, bool bf16, int rows, const int32_t *tok_offsets, int P, int d, int Q, float *partial, hipStream_t s) {
   const int per_block = 64 * (bf16 ? 8 : 4);
-  dim3 grid((d + per_block - 1) / per_block, Q, P);
-  if (bf16)
-    hipLaunchKernelGGL((pool_partial<true, 0>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
-  else
-    hipLaunchKernelGGL((pool_partial<false, 0>), grid, dim3(kPoolThreads), 0, s, X, rows, d, tok_offsets, Q, partial);
+  hipLaunchKernelGGL((bf16 ? pool_partial<true, MEAN> : pool_partial<false, MEAN>), dim3((d + per_block - 1) / per_block, Q, P), dim3(kPoolThreads),
+                     0, s, X, rows, d, tok_offsets, Q, partial);
   PARSE_LAUNCH_CHECK();
-  *Q_out = Q;
+  return PARSE_OK;
+}
+
+// Lanes (their log2) that a workgroup of pool_rows gives to a row, or -1 where the slices' own launch is faster.  Sixteen lanes read whole lines of a
+// row and make enough workgroups for most batches; eight where they do not, thirty-two where the prompts are long and many.  us, 8 / 16 / 32 /
+// 64 lanes, bf16, 4096 columns: 8 prompts of 512 rows 8.7 / 8.6 / 8.4 / 8.4, 20 of 20-700 12.6 / 12.4 / 12.5 / 14.0, 8 of 4096 43 / 41 / 42 / 42, one of 160
+// 3.3 / 3.6 / 4.1 / 4.1; 1024 columns, 8 of 512 4.7 / 5.6 / 5.5 / 5.6.
+// Embeddings, us, two launches / one: 8 x 512 rows of 4096 columns 10.4 / 8.6, 20 ragged 14.6 / 12.5, one of 77 3.6 / 3.1, of 160 6.1 / 3.3, of 700 7.3 /
+// 4.7, of 2048 9.0 / 8.5, of 4096 11.8 / 12.9, of 16000 31 / 66; 1024 columns, 8 x 512 6.4 / 4.6, one of 2048 6.5 / 5.6, of 4096 8.4 / 9.7; 256 columns, 8 x 4096
+// 9.5 / 11.2; fp32, 1024 columns, 4 x 64 4.7 / 2.8, 4096 columns, one of 16000 54 / 71; one slice, 64 x 20 rows of 4096 columns 4.6 / 5.1.
+// The router's second launch comes either way, and adds the slices of few columns fast: 4096 columns, 8 x 512 15.5 / 14.6, one of 160 9.8 / 8.4, of 2048
+// 15.6 / 13.8; 1024 columns, 8 x 512 9.1 / 9.0, one of 700 9.1 / 8.4, 8 x 4096 19.9 / 21.7; 256 columns, 8 x 512 7.3 / 7.7.
+static int pool_rows_lanes(int rows, int P, int d, bool bf16, int Q, bool router) {
+  if (Q == 1) return -1;
+  const int chains = Q * kPoolWaves, per = bf16 ? 8 : 4;
+  const long long per_chain = rows / P / chains;       // rows
+  auto wgs = [&](int l) { return (long long)P * ((d + (per << l) - 1) / (per << l)); };
+  int l = per_chain > 16 && wgs(5) >= 512 ? 5 : (wgs(4) < 256 ? 3 : 4);
+  while ((chains << l) > kPoolRowsThreads) --l;
+  if (per_chain > 16 && wgs(l) < (per_chain > 64 ? 256 : 128)) return -1;
+  if (router && (d < 512 || (per_chain > 12 && wgs(l) < 256 && Q * d < 65536))) return -1;
+  return l;
+}
+
+static int launch_pool_rows(const void *X, bool bf16, int rows, const int32_t *tok_offsets, int P, int d, int Q, int l, float *emb, hipStream_t s) {
+  const int per = bf16 ? 8 : 4, threads = (Q * kPoolWaves) << l;
+  hipLaunchKernelGGL((bf16 ? pool_rows<true> : pool_rows<false>), dim3((d + (per << l) - 1) / (per << l), P), dim3(threads),
+                     (size_t)threads * per * sizeof(float), s, X, rows, d, tok_offsets, Q, l, emb);
+  PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
 
 int launch_pool_finish(const float *partial, int Q, int rows, int d, const int32_t *tok_offsets, int P, float *emb,
                        hipStream_t s);   // with the rank-granular router
 
-template <int Q>
-static void launch_pool_whole(const void *X, bool bf16, int rows, const int32_t *tok_offsets, int P, int d, float *emb, hipStream_t s) {
-  const int per_block = 64 * (bf16 ? 8 : 4);
-  const dim3 grid((d + per_block - 1) / per_block, 1, P);
-  if (bf16) hipLaunchKernelGGL((pool_partial<true, Q>), grid, dim3(kPoolThreads * Q), 0, s, X, rows, d, tok_offsets, Q, emb);
-  else hipLaunchKernelGGL((pool_partial<false, Q>), grid, dim3(kPoolThreads * Q), 0, s, X, rows, d, tok_offsets, Q, emb);
-}
-
-// Embeddings of a batch, with the bits of the router's: one launch where a prompt is one slice, and for up to POOL_WHOLE_ROWS rows in up
-// to four slices, whose workgroups are one then.  Bound by launches and one or two round trips to memory; bf16, 4096 columns, us, two
-// launches / one: 20 rows 4.7 / 2.8, 64 5.1 / 3.3, 77 5.1 / 3.4, 128 5.7 / 4.7, two prompts of 80 5.4 / 3.4; 256 columns, 77 rows
-// 4.7 / 3.2, 128 5.2 / 4.5 (and a launch less on the host).  The router adds the slices in its second launch, which it needs anyway: there one
-// slice for them all only makes the first launch longer (160 rows 9.6 -> 10.9 us).
-constexpr int POOL_WHOLE_ROWS = 160;
+// Embeddings of a batch, with the bits of the router's.
 int launch_pool(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial, float *emb, hipStream_t s) {
   const bool bf16 = xdtype == PARSE_BF16;
-  int Q = pool_slices(rows, P, d, bf16);
-  if (Q == 1 || (Q <= 4 && rows <= POOL_WHOLE_ROWS)) {
-    if (Q == 1) launch_pool_whole<1>(X, bf16, rows, tok_offsets, P, d, emb, s);
-    else if (Q == 2) launch_pool_whole<2>(X, bf16, rows, tok_offsets, P, d, emb, s);
-    else if (Q == 3) launch_pool_whole<3>(X, bf16, rows, tok_offsets, P, d, emb, s);
-    else launch_pool_whole<4>(X, bf16, rows, tok_offsets, P, d, emb, s);
-    PARSE_LAUNCH_CHECK();
-    return PARSE_OK;
-  }
-  const int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
+  const int Q = pool_slices(rows, P, d, bf16), l = pool_rows_lanes(rows, P, d, bf16, Q, false);
+  if (l >= 0) return launch_pool_rows(X, bf16, rows, tok_offsets, P, d, Q, l, emb, s);
+  if (Q == 1) return launch_pool_partials<true>(X, bf16, rows, tok_offsets, P, d, 1, emb, s);
+  const int st = launch_pool_partials<false>(X, bf16, rows, tok_offsets, P, d, Q, partial, s);
   if (st != PARSE_OK) return st;
   return launch_pool_finish(partial, Q, rows, d, tok_offsets, P, emb, s);
 }
@@ -245,8 +306,16 @@ int parse_route_shared(const void *X, int32_t xdtype, int32_t rows, const int32_
   if (!workspace || workspace_bytes < parse_route_workspace_bytes(rows, P, d)) return PARSE_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   float *partial = reinterpret_cast<float *>(workspace);
-  int Q = 0;
-  const int st = launch_pool_partials(X, xdtype, rows, tok_offsets, P, d, partial, &Q, s);
+  const bool bf16 = xdtype == PARSE_BF16;
+  int Q = pool_slices(rows, P, d, bf16), st;
+  const int l = pool_rows_lanes(rows, P, d, bf16, Q, true);
+  if (l >= 0) {              // the means, where the caller or the second launch wants them
+    if (emb_out) partial = emb_out;
+    st = launch_pool_rows(X, bf16, rows, tok_offsets, P, d, Q, l, partial, s);
+    Q = 0;
+  } else {
+    st = launch_pool_partials<false>(X, bf16, rows, tok_offsets, P, d, Q, partial, s);
+  }
   if (st != PARSE_OK) return st;
   const size_t lds = (size_t)(d + 64) * sizeof(float);
   PARSE_ALLOW_LDS(route_finish, lds);

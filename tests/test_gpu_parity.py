@@ -118,6 +118,37 @@ def test_embeddings_of_short_prompts(dtype, d, lengths, Q):
         assert np.array_equal(e.view(np.int32), ref.view(np.int32)), what
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,lengths", [
+    (264, [163]), (1032, [700]), (4104, [300, 0, 517]), (512, [257] * 9), (4096, [160] * 40), (256, [4000]), (16384, [96, 1]), (520, [2049]),
+])
+def test_embeddings_of_longer_prompts(dtype, d, lengths):
+    """One workgroup for all chains of a prompt's columns (8, 16 and 32 lanes a row, the last ones past the end of it), or slices: the
+    bits of the documented order by every entry point."""
+    say(f"embeddings dtype={dtype} d={d} lengths={lengths}")
+    rng = np.random.default_rng(107)
+    off, P, G = si.offsets_from_lengths(lengths), len(lengths), 8
+    rows, cols = int(off[-1]), 512 if dtype == "bf16" else 256
+    per = P * ((d + cols - 1) // cols)
+    Q = max(1, min(32, (512 + per - 1) // per, max(1, rows // P // 32)))
+    X = si.make_tokens(rng, rows, d, dtype)
+    ref = _pooled_in_order(si.bf16_bits_to_f32(X) if dtype == "bf16" else X, off, Q)
+    Xd, offd = upload_tokens(X, dtype), i32(off)
+    Wr = torch.from_numpy(si.make_router(rng, 1, G, d)[0]).to(DEV)
+    for what in ("pool", "route", "route_ranks"):
+        whole, mid = guarded_bytes(P * d * 4)
+        emb = mid[:P * d * 4].view(torch.float32).view(P, d)
+        if what == "pool":
+            pa.pool(Xd, offd, emb)
+        elif what == "route":
+            pa.route(Xd, offd, Wr, 2, emb_out=emb)
+        else:
+            pa.route_ranks(Xd, offd, Wr, 2, emb_out=emb)
+        torch.cuda.synchronize()
+        check_guards(whole, "embedding")
+        assert np.array_equal(emb.cpu().numpy().view(np.int32), ref.view(np.int32)), what
+
+
 def test_route_strided_output_and_determinism():
     say("route strided output / repeatability")
     rng = np.random.default_rng(102)
