@@ -1,8 +1,8 @@
 // a7 for more than 32 sequences (a loaded server): the same two products as decode_bf16.hip over panels of 32 sequences, but a
 // group selected by any sequence of up to DW_MAXP panels is streamed ONCE and applied to all of them, instead of once per
 // panel.  Launches per call:
-//   wide_prepare  the plan: per layer the groups in use, a 32-sequence mask per group and panel
-//   wide_z        two rank blocks x a slice of the reduction per workgroup, all panels: fp32 partial sums, or z
+//   wide_z        the plan (per layer the groups in use, a 32-sequence mask per group and panel), then two rank blocks x a slice of
+//                 the reduction per workgroup, all panels: fp32 partial sums, or z
 //   wide_zsum     adds the slices in slice order, masks, rounds to bf16 (only when the reduction is cut)
 //   wide_y        CB column blocks per workgroup, all used reduction blocks, all panels
 // wide_z is a tile kernel like the prefill's (see prefill_lds_bf16.hip): both operands staged in LDS, the loads between 16x16x32
@@ -51,32 +51,6 @@ struct DwArgs {
   const int32_t *pattern_id;
   int B, n, KS, panels;
 };
-
-// grid = layers
-__global__ __launch_bounds__(DW_THREADS) void wide_prepare(DwArgs a) {
-  const DwLayer &ly = a.L[blockIdx.x];
-  __shared__ uint32_t gmask[DW_MAXP][DW_MAXG];
-  for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) gmask[i / DW_MAXG][i % DW_MAXG] = 0u;
-  __syncthreads();
-  for (int s = threadIdx.x; s < a.B; s += DW_THREADS) {
-    const int pid = a.pattern_id[s];
-    if (pid < 0 || pid >= ly.n_patterns) continue;
-    for (int i = 0; i < ly.k; ++i) {
-      const int g = ly.subsets[(size_t)pid * ly.stride + i];
-      if (g >= 0 && g < ly.G) atomicOr(&gmask[s >> 5][g], 1u << (s & 31));
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    uint32_t any = 0u;
-    for (int p = 0; p < DW_MAXP; ++p) any |= gmask[p][lane];
-    const unsigned long long votes = __ballot(lane < ly.G && any != 0u);
-    if ((votes >> lane) & 1ull) ly.plan[1 + __popcll(votes & ((1ull << lane) - 1ull))] = lane;
-    if (lane == 0) ly.plan[0] = __popcll(votes);
-  }
-  for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DW_THREADS) ly.plan[128 + i] = (int32_t)gmask[i / DW_MAXG][i % DW_MAXG];
-}
 
 constexpr int dw_depth(int CB, int NT) { return 40 / (CB + NT) < 4 ? 4 : (40 / (CB + NT) > 8 ? 8 : 40 / (CB + NT)); }
 
@@ -145,6 +119,50 @@ __device__ __forceinline__ void wide_store_z(const f32x4v &lo, const f32x4v &hi,
 // counts is how much of the factor stream is on its way.
 constexpr int dw_stages(int NT) { return 160 / (8 + 4 * NT) > 8 ? 8 : 160 / (8 + 4 * NT); }
 constexpr int DWZ_WAVES = 8, DWZ_THREADS = DWZ_WAVES * 64;   // two per SIMD, whose waits cover each other
+static_assert(DW_MAXP * 32 <= 256, "a thread of each 256 looks at one sequence");
+
+// The groups in use and the mask of sequences of every (panel, group), worked out by every workgroup of wide_z in LDS (DW_PREP_BYTES): 1 us of two dependent
+// loads and a vote where a launch of its own took 4-5.  The first workgroup of a layer leaves them in memory for the launches that follow.
+constexpr int DW_PREP_BYTES = (DW_MAXP + 1) * DW_MAXG * 4;
+struct DwUsed {
+  const uint32_t *gmask;     // [DW_MAXP][DW_MAXG]
+  const int32_t *ids;        // ascending
+  int count;
+};
+__device__ __forceinline__ DwUsed wide_used(const DwArgs &a, const DwLayer &ly, char *lds, bool keep) {
+  uint32_t *gmask = reinterpret_cast<uint32_t *>(lds);
+  int32_t *ids = reinterpret_cast<int32_t *>(lds) + DW_MAXP * DW_MAXG;
+  constexpr int PARTS = DWZ_THREADS / 256;             // threads that share a sequence's groups (at most 192 sequences)
+  const int s = threadIdx.x & 255, part = threadIdx.x >> 8, lane = threadIdx.x & 63;
+  const int pid = s < a.B ? a.pattern_id[s] : -1;
+  for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DWZ_THREADS) gmask[i] = 0u;
+  __syncthreads();
+  if (pid >= 0 && pid < ly.n_patterns) {
+    const int32_t *sub = ly.subsets + (size_t)pid * ly.stride;
+    for (int i0 = part; i0 < ly.k; i0 += 8 * PARTS) {
+      int g[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) g[u] = sub[min(i0 + u * PARTS, ly.k - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (i0 + u * PARTS < ly.k && g[u] >= 0 && g[u] < ly.G) atomicOr(&gmask[(s >> 5) * DW_MAXG + g[u]], 1u << (s & 31));
+    }
+  }
+  __syncthreads();
+  uint32_t any = 0u;
+#pragma unroll
+  for (int p = 0; p < DW_MAXP; ++p) any |= gmask[p * DW_MAXG + lane];
+  const unsigned long long votes = __ballot(any != 0u);          // groups below G only
+  const int count = __popcll(votes), at = __popcll(votes & ((1ull << lane) - 1ull));
+  if (threadIdx.x < 64 && any != 0u) ids[at] = lane;
+  if (keep) {
+    if (threadIdx.x < 64 && any != 0u) ly.plan[1 + at] = lane;
+    if (threadIdx.x == 0) ly.plan[0] = count;
+    for (int i = threadIdx.x; i < DW_MAXP * DW_MAXG; i += DWZ_THREADS) ly.plan[128 + i] = (int32_t)gmask[i];
+  }
+  __syncthreads();
+  return DwUsed{gmask, ids, count};
+}
 
 // grid: layers x rank blocks in units of DW_ZCB (numbered over the blocks in use; the rest leaves) x KS slices.
 // Slices of 64 reduction indices in a ring: slice kt + STAGES is requested once slice kt has been read by everybody.  A wavefront owns
@@ -163,9 +181,10 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
   const int KS = a.KS, bid = blockIdx.x - ly.z_first;
   const int sl = bid % KS, i0 = bid / KS * CB;
   const int bpg = ly.gs / 32;                          // rank blocks per group
-  const int nused = min(max(ly.plan[0], 0), ly.G) * bpg;
-  if (i0 >= nused) return;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const DwUsed use = wide_used(a, ly, smem, bid == 0);
+  const int nused = use.count * bpg;
+  if (i0 >= nused) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int j = lane & 15, g = lane >> 4;
   const int n = a.n, nkb = n / 16, slices = (n + 63) / 64;
@@ -174,11 +193,15 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
   const int wr = wave & 3, p0 = wave >> 2 ? NT - PW : 0;                 // its 16 ranks, its first panel
   auto rank_block = [&](int i, int &grp) -> int {                        // blocks past the last one re-read it (not stored)
     const int at = min(i0 + i, nused - 1);
-    grp = __builtin_amdgcn_readfirstlane(ly.plan[1 + at / bpg]);
+    grp = __builtin_amdgcn_readfirstlane(use.ids[at / bpg]);
     return grp * bpg + at % bpg;
   };
   int grp, lgrp;
   const int rb = rank_block(wr >> 1, grp), lrb = rank_block(wave >> 2, lgrp);
+  uint32_t mask[PW];                                   // of its panels, for z that is stored here
+#pragma unroll
+  for (int p = 0; p < PW; ++p) mask[p] = __builtin_amdgcn_readfirstlane(use.gmask[(p0 + p) * DW_MAXG + grp]);
+  __syncthreads();                                     // the lists are read: the stages take their place
 
   // sources: one of the eight factor operands of a slice, and of its groups of 8 rows of x every eighth (the last one again where
   // they do not divide: the same data to the same place)
@@ -305,7 +328,7 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
 #pragma unroll
     for (int p = 0; p < PW; ++p)
       if (p >= skip)
-        wide_store_z(acc[0][2 * p], acc[0][2 * p + 1], (uint32_t)ly.plan[128 + (p0 + p) * 64 + grp], lane, (char *)ly.zf + ((size_t)(p0 + p) * (ly.R / 16) + rb16) * 1024);
+        wide_store_z(acc[0][2 * p], acc[0][2 * p + 1], mask[p], lane, (char *)ly.zf + ((size_t)(p0 + p) * (ly.R / 16) + rb16) * 1024);
   }
 }
 
@@ -440,10 +463,7 @@ static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
 }
 
 static int wide_pass(DwArgs a, hipStream_t s) {
-  int st;
-  hipLaunchKernelGGL(wide_prepare, dim3(a.n_layers), dim3(DW_THREADS), 0, s, a);
-  PARSE_LAUNCH_CHECK();
-  int zw = 0, sw = 0, cols = 0;
+  int st, zw = 0, sw = 0, cols = 0;
   for (int l = 0; l < a.n_layers; ++l) {
     a.L[l].z_first = zw; zw += (a.L[l].R / 32 + DW_ZCB - 1) / DW_ZCB * a.KS;
     a.L[l].s_first = sw; sw += a.L[l].R / 16 * a.panels;
