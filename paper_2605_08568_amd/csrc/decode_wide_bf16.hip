@@ -4,7 +4,7 @@
 //   wide_z        the plan (per layer the groups in use, a 32-sequence mask per group and panel), then two rank blocks x a slice of
 //                 the reduction per workgroup, all panels: fp32 partial sums, or z
 //   wide_zsum     adds the slices in slice order, masks, rounds to bf16 (only when the reduction is cut)
-//   wide_y        CB column blocks per workgroup, all used reduction blocks, all panels
+//   wide_y        CB column blocks x NT panels per workgroup, all used reduction blocks
 // wide_z is a tile kernel like the prefill's (see prefill_lds_bf16.hip): both operands staged in LDS, the loads between 16x16x32
 // products; x is read as it is, row-major.  wide_y keeps every operand in operand order, so a wavefront loads 1 KiB per instruction
 // straight into registers: per reduction step CB factor operands and NT token operands feed CB * NT matrix instructions; its four
@@ -13,7 +13,7 @@
 // Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
 // Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns: wide_z 16 us for gate+up and 19 for down
 // (18 and 20 with operands straight into registers, and a launch of 4-6 us that brought x into operand order; 113 us a step against 118):
-// 4.7 us until the first slice is there, the factors at 4 TB/s, 1.6 us for the sums; wide_y 28 and 14 us; five panels one after the other took 313-335 us.
+// 4.7 us until the first slice is there, the factors at 4 TB/s, 1.6 us for the sums; wide_y 28 and 11 us; five panels one after the other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
 
@@ -50,6 +50,7 @@ struct DwArgs {
   const uint16_t *x;         // [B][n]
   const int32_t *pattern_id;
   int B, n, KS, panels;
+  int groups;                // of panels in wide_y
 };
 
 constexpr int dw_depth(int CB, int NT) { return 40 / (CB + NT) < 4 ? 4 : (40 / (CB + NT) > 8 ? 8 : 40 / (CB + NT)); }
@@ -356,7 +357,9 @@ __global__ __launch_bounds__(DW_THREADS) void wide_zsum(DwArgs a) {
   wide_store_z(lo, hi, mask, lane, (char *)ly.zf + ((size_t)p * (ly.R / 16) + rb16) * 1024);
 }
 
-// grid: layers x column blocks in units of CB
+// grid: layers x groups of NT panels x column blocks in units of CB (their number rounded up to whole rounds of the dies, so that the groups of one
+// column block run on one die and its factor comes from memory once).  The last group of panels ends with the last panel: the ones it shares with the
+// group before are computed by both and stored once.
 template <int CB, int NT>
 __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
   int li = 0;
@@ -370,8 +373,11 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
   const int total = min(max(ly.plan[0], 0), ly.G) * kpg;           // <= R / 16 <= 1024
   for (int i = threadIdx.x; i < total; i += DW_THREADS) kb_list[i] = ly.plan[1 + i / kpg] * kpg + i % kpg;
   __syncthreads();
-  const int c0 = ((int)blockIdx.x - ly.y_first) * CB;
-  const char *U = (const char *)ly.Ut + lane * 16, *Z = (const char *)ly.zf + lane * 16;
+  const int units = (ncb + CB - 1) / CB, units8 = a.groups > 1 ? (units + 7) / 8 * 8 : units;
+  const int unit = ((int)blockIdx.x - ly.y_first) % units8, group = ((int)blockIdx.x - ly.y_first) / units8;
+  const int c0 = unit * CB, p0 = min(group * NT, a.panels - NT), skip = group * NT - p0;
+  if (unit >= units) return;
+  const char *U = (const char *)ly.Ut + lane * 16, *Z = (const char *)ly.zf + (size_t)p0 * (ly.R / 16) * 1024 + lane * 16;
   int cb[CB];
 #pragma unroll
   for (int i = 0; i < CB; ++i) cb[i] = min(c0 + i, ncb - 1);       // blocks past the end re-read the last one (not stored)
@@ -382,6 +388,7 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
                     [&](int s, int p) { return Z + (p * zstep + kb_list[wave + s * DW_WAVES]) * 1024; });
 #pragma unroll
   for (int p = 0; p < NT; ++p) {
+    if (p < skip) continue;                  // uniform
 #pragma unroll
     for (int i = 0; i < CB; ++i)
 #pragma unroll
@@ -390,7 +397,7 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
     // thread = four consecutive columns of a sequence (eight threads a row's 32 columns): sums in wavefront order
 #pragma unroll
     for (int i = 0; i < CB; ++i) {
-      const int quad = threadIdx.x & 7, j = threadIdx.x >> 3, seq = p * 32 + j;
+      const int quad = threadIdx.x & 7, j = threadIdx.x >> 3, seq = (p0 + p) * 32 + j;
       float s[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -463,34 +470,55 @@ static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
 }
 
 static int wide_pass(DwArgs a, hipStream_t s) {
-  int st, zw = 0, sw = 0, cols = 0;
+  int st, zw = 0, sw = 0;
   for (int l = 0; l < a.n_layers; ++l) {
     a.L[l].z_first = zw; zw += (a.L[l].R / 32 + DW_ZCB - 1) / DW_ZCB * a.KS;
     a.L[l].s_first = sw; sw += a.L[l].R / 16 * a.panels;
-    cols += a.L[l].m / 32;
   }
-  int cb = 1;                                // column blocks per workgroup: the fewest that need one round of workgroups
-  const int most = a.panels >= 6 ? 2 : 3;    // what the accumulators leave room for (256 registers per SIMD lane and 256 more)
-  while (cb < most && (cols + cb - 1) / cb > DW_UNITS) ++cb;
+  // Column blocks x panels of a wide_y workgroup: every round of workgroups takes in as many operands a step as their sum; of equals the one with
+  // fewer panels, whose sums meet one after the other at the end.  All panels in each workgroup left half of the units idle where columns are few: 150
+  // sequences through 11008 -> 4096 columns, 2560 ranks, a call, us, column blocks x panels 1 x 5 37.6, 1 x 3 35.2, 2 x 5 41, 2 x 2 35.1;
+  // 1024 -> 448, 2048 ranks, 238 sequences 37.8 (1 x 4), 30.1 (1 x 2); 4096 -> 2 x 11008, 192 sequences 82 (2 x 6), 68 (3 x 3); over 80 calls of nine
+  // forms each the one taken is 0.7 % off the best on average, 11 % at worst (few ranks, where two workgroups a unit run side by side).
+  int cb = 1, nt = a.panels;
+  long long least = 0;
+  for (int c = 1; c <= 3; ++c)
+    for (int g = 1; g <= a.panels; ++g) {
+      const int t = (a.panels + g - 1) / g;
+      if (c * t > 15 || (t * (g - 1) >= a.panels)) continue;       // what the accumulators leave room for
+      long long wgs = 0;
+      for (int l = 0; l < a.n_layers; ++l) wgs += (long long)((a.L[l].m / 32 + c - 1) / c) * g;
+      const long long cost = (wgs + DW_UNITS - 1) / DW_UNITS * (c + t);
+      if (least == 0 || cost < least || (cost == least && t < nt)) { least = cost; cb = c; nt = t; a.groups = g; }
+    }
   int yw = 0;
-  for (int l = 0; l < a.n_layers; ++l) { a.L[l].y_first = yw; yw += (a.L[l].m / 32 + cb - 1) / cb; }
-#define PARSE_DW(NT_)                                                                              \
+  for (int l = 0; l < a.n_layers; ++l) {
+    const int units = (a.L[l].m / 32 + cb - 1) / cb;
+    a.L[l].y_first = yw;
+    yw += (a.groups > 1 ? (units + 7) / 8 * 8 : units) * a.groups;
+  }
+#define PARSE_DWZ(NT_) case NT_: st = launch_wide_z<NT_>(a, zw, s); break
+  switch (a.panels) {
+    PARSE_DWZ(1); PARSE_DWZ(2); PARSE_DWZ(3); PARSE_DWZ(4); PARSE_DWZ(5); PARSE_DWZ(6);
+    default: return PARSE_ESHAPE;
+  }
+#undef PARSE_DWZ
+  if (st != PARSE_OK) return st;
+  if (a.KS > 1) {
+    hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a);
+    PARSE_LAUNCH_CHECK();
+  }
+#define PARSE_DWY(NT_)                                                                             \
   case NT_:                                                                                        \
-    st = launch_wide_z<NT_>(a, zw, s);                                                             \
-    if (st != PARSE_OK) return st;                                                                 \
-    if (a.KS > 1) {                                                                                \
-      hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a); \
-      PARSE_LAUNCH_CHECK();                                                                        \
-    }                                                                                              \
     if (cb == 1) hipLaunchKernelGGL((wide_y<1, NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a);        \
     else if (cb == 2) hipLaunchKernelGGL((wide_y<2, NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a);   \
     else hipLaunchKernelGGL((wide_y<(NT_ < 6 ? 3 : 2), NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a); \
     break
-  switch (a.panels) {
-    PARSE_DW(1); PARSE_DW(2); PARSE_DW(3); PARSE_DW(4); PARSE_DW(5); PARSE_DW(6);
+  switch (nt) {
+    PARSE_DWY(1); PARSE_DWY(2); PARSE_DWY(3); PARSE_DWY(4); PARSE_DWY(5); PARSE_DWY(6);
     default: return PARSE_ESHAPE;
   }
-#undef PARSE_DW
+#undef PARSE_DWY
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

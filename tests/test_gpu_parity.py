@@ -1712,6 +1712,19 @@ def test_decode_many_sequences_slices(n, shapes, rows):
     test_decode_many_sequences(n, shapes, rows)
 
 
+@pytest.mark.parametrize("n,shapes,rows", [
+    (256, [(96, 256, 8, 3), (32, 288, 3, 2)], 192),     # few columns: every panel its own workgroup
+    (272, [(2016, 256, 4, 2)], 150),                    # 63 column blocks, five panels in twos: the middle group shares one
+    (256, [(4000, 256, 4, 2)], 129),                    # 125, five panels in threes
+    (256, [(9632, 256, 4, 2)], 190),                    # 301, three blocks x three of six panels, the last blocks past the end
+    (256, [(7136, 256, 4, 2)], 70),                     # 223 blocks, two x three panels or one x all
+])
+def test_decode_many_sequences_panel_groups(n, shapes, rows):
+    """The second product's column blocks and panels per workgroup: groups of panels that overlap, units that do not fill the
+    rounds of the dies, several layers."""
+    test_decode_many_sequences(n, shapes, rows)
+
+
 def test_decode_many_sequences_precision_of_the_first_product():
     """How far the fp32 sums of z are off shows in how many of its bf16 values fall on the other side of a rounding border than the exact
     ones; with the identity as left factor the output is z.  A sum of N steps wanders in proportion to the root of N: four sums of a
