@@ -258,7 +258,7 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *layer, int
  *                both products on the bf16 matrix cores with fp32 accumulation, the r_S-wide
  *                intermediate rounded to bf16.  Schedules: see parse_prefill_schedule (patterns->schedule).
  *                With workspace == NULL the fused kernel is used.  The planned schedule builds its plan inside the
- *                call (one extra small launch); parse_lowrank_prefill_planned takes a ready plan instead.  f32
+ *                call (one extra small launch; a single prompt needs none); parse_lowrank_prefill_planned takes a ready plan instead.  f32
  *                layers must be PARSE_ROWMAJOR (plain fp32 kernels, intermediate in the workspace).
  *                  X device [rows][n], Y device [rows][m] (layer dtype), tok_offsets device int32 [P+1],
  *                  pattern_id device int32 [P].

@@ -15,6 +15,7 @@ int forward_prefill_split_multi_bf16(const PfArgs *p, int n_layers, uint16_t *co
 size_t prefill_plan_bytes(int rows, int P, int n_patterns);
 int prefill_plan_capacity(int rows, int P, int n_patterns);
 bool prefill_plan_supported(int P, int n_patterns);
+bool prefill_needs_plan(int P);
 int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, int P, int rows, int n_patterns,
                        int32_t *plan, hipStream_t s);
 size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks);
@@ -385,8 +386,8 @@ int parse_lowrank_prefill_multi(const parse_layer *layers, const parse_patterns 
       ws += prefill_planned_z_bytes(cap, args[l].rS, args[l].split_room);
     }
     int32_t *plan = reinterpret_cast<int32_t *>(ws);
-    int st = build_prefill_plan(tok_offsets, pattern_id, P, rows, patterns[0].n_patterns, plan, s);
-    if (st != PARSE_OK) return st;
+    if (!prefill_needs_plan(P)) plan = nullptr;
+    else if (const int st = build_prefill_plan(tok_offsets, pattern_id, P, rows, patterns[0].n_patterns, plan, s)) return st;
     return forward_prefill_planned_multi_bf16(args, n_layers, plan, cap, Z, rows / P, s);
   }
   if (!tiles_ok) return PARSE_ESHAPE;

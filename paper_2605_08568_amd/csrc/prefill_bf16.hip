@@ -359,6 +359,7 @@ int forward_prefill_split_bf16(const PfArgs &p, uint16_t *Z, int avg_prompt_rows
 size_t prefill_plan_bytes(int rows, int P, int n_patterns);
 int prefill_plan_capacity(int rows, int P, int n_patterns);
 bool prefill_plan_supported(int P, int n_patterns);
+bool prefill_needs_plan(int P);
 int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, int P, int rows, int n_patterns,
                        int32_t *plan, hipStream_t s);
 size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks);
@@ -396,8 +397,8 @@ int forward_prefill_bf16(const parse_layer *L, const parse_patterns *pt, const u
   if (schedule == PARSE_SCHED_PLANNED && !can_plan) return planned_shapes ? PARSE_EWORKSPACE : PARSE_ESHAPE;
   if (can_plan && (schedule == PARSE_SCHED_PLANNED || schedule == PARSE_SCHED_AUTO)) {
     int32_t *plan = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(workspace) + zb);
-    int st = build_prefill_plan(tok_offsets, pattern_id, P, rows, pt->n_patterns, plan, s);
-    if (st != PARSE_OK) return st;
+    if (!prefill_needs_plan(P)) plan = nullptr;
+    else if (const int st = build_prefill_plan(tok_offsets, pattern_id, P, rows, pt->n_patterns, plan, s)) return st;
     return forward_prefill_planned_bf16(a, plan, cap, (uint16_t *)workspace, rows / (P > 0 ? P : 1), s);
   }
   // two launches of the register-operand tile kernel

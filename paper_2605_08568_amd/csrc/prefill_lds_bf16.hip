@@ -50,11 +50,37 @@ struct LgLayer {
 struct LgArgs {
   LgLayer L[LG_MAX_LAYERS];
   int n_layers;
-  const int32_t *plan;     // header | tile patterns | row map (plan.hip)
+  const int32_t *plan;     // header | tile patterns | row map (plan.hip); ONE: none
+  const int32_t *tok_offsets, *pattern_id;     // ONE: the prompt
+  int rows, NP;
   int cap;                 // plan capacity in 256-row tiles (fixes where the row map starts)
   int ntn, gm, ngroups;    // column tiles (all layers), token tiles per locality group, groups
   int compact;             // the padding tiles are left out of the numbering (plans of at most 256 tiles of BM rows)
   int ks;                  // SPLIT: slices of the reduction range, one workgroup each
+};
+
+// What a workgroup asks of the plan: read from memory, or (ONE) the same answers for a single prompt, whose virtual rows are its token rows: that saves the
+// plan's own launch where a call makes its plan for itself, and two dependent loads (one prompt of 57 rows, 1024 x 1024, 224 ranks, both products
+// 13.7 -> 10.9 us a call; 34 rows, 4096 x 4096 17.1 -> 14.1; 2048 rows x 1024 ranks, n = 11008, 87 -> 81).  More prompts are not worth it: up to four in scalar registers
+// take 1-2 us of a call's 3 (two launches, all wavefronts), up to 16 by lane readings 2-7.
+template <int ONE>
+struct LgPlan {
+  const LgArgs &a;
+  const int32_t *rowmap;
+  int off, len, pid;                           // first token row, rows, pattern (-1: none)
+  __device__ __forceinline__ explicit LgPlan(const LgArgs &args) : a(args) {
+    if (!ONE) {
+      rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+    } else {
+      const int b = a.tok_offsets[0], e = a.tok_offsets[1], v = a.pattern_id[0];
+      off = b < 0 ? 0 : (b > a.rows ? a.rows : b);
+      len = max((e < 0 ? 0 : (e > a.rows ? a.rows : e)) - off, 0);
+      pid = v >= 0 && v < a.NP ? v : -1;
+    }
+  }
+  __device__ __forceinline__ int virtual_rows() const { return ONE ? (len + 255) / 256 * 256 : a.plan[1]; }
+  __device__ __forceinline__ int pattern(int tile) const { return ONE ? pid : a.plan[16 + tile]; }   // of a 256-row tile below virtual_rows, -1: none
+  __device__ __forceinline__ int token_row(int v) const { return ONE ? (v < len ? off + v : -1) : rowmap[v]; }   // of a virtual row, -1: padding
 };
 
 // Numbering of a launch's tiles: consecutive ids share a die (and its L2); within a locality group the token tile runs fastest.
@@ -64,17 +90,17 @@ struct LgArgs {
 // are left out of the numbering.  Workgroups are dealt to the dies before anything is known of them; with the padding
 // numbered, one die can get more tiles than it has compute units while another one's leave at once (20 prompts of 30-640
 // tokens, 220 of 264 tiles real: the launch took two rounds, 118 us against 82).
-template <int BM>
-__device__ __forceinline__ bool lg_find_tile(const LgArgs &a, const int32_t *rowmap, int bid, int lane, int &tm, int &tn, int &li) {
+template <int BM, int ONE>
+__device__ __forceinline__ bool lg_find_tile(const LgArgs &a, const LgPlan<ONE> &plan, int bid, int lane, int &tm, int &tn, int &li) {
   const int per = a.gm * a.ntn;
-  int n_tiles = (a.plan[1] + BM - 1) / BM;
+  int n_tiles = (plan.virtual_rows() + BM - 1) / BM;
   unsigned long long real[4];                  // bit l of real[u]: tile 64 u + l holds tokens
   if (BM < 256 && a.compact) {
     int cnt = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int t = u * 64 + lane;
-      real[u] = __ballot(t < a.cap * (256 / BM) && rowmap[min(t, a.cap * (256 / BM) - 1) * BM] >= 0 && t < n_tiles);
+      real[u] = __ballot(t < a.cap * (256 / BM) && plan.token_row(min(t, a.cap * (256 / BM) - 1) * BM) >= 0 && t < n_tiles);
       cnt += __popcll(real[u]);
     }
     n_tiles = cnt;
@@ -107,10 +133,10 @@ __device__ __forceinline__ bool lg_find_tile(const LgArgs &a, const int32_t *row
 }
 
 // Rows of a tile whose prompts have no valid pattern: the first product has nothing to do, the second one writes zero rows
-template <int BM, int BN>
-__device__ __forceinline__ void lg_zero_rows(const LgLayer &ly, const int32_t *rowmap, int tm, int tn, int wave, int n_waves, int lane) {
+template <int BM, int BN, int ONE>
+__device__ __forceinline__ void lg_zero_rows(const LgLayer &ly, const LgPlan<ONE> &plan, int tm, int tn, int wave, int n_waves, int lane) {
   for (int rr = wave; rr < BM; rr += n_waves) {
-    const int orow = rowmap[tm * BM + rr];
+    const int orow = plan.token_row(tm * BM + rr);
     if (orow < 0) continue;
     for (int c = lane * 8; c < BN; c += 512) {
       const int col = tn * BN + c;
@@ -146,7 +172,7 @@ __device__ __forceinline__ u32x4 lg_pair(const f32x4v &u, const f32x4v &v) {
 // SPLIT (first product only): the reduction range is cut in a.ks slices, one workgroup each; a workgroup stores its fp32
 // sums as slice s of the partial sums and z_combine adds the slices (in slice order) and rounds -- for launches whose
 // tiles alone would leave most compute units idle (one short prompt).
-template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1>
+template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT, int WK, int ONE>
 __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
   static_assert(!SPLIT || (FORD == 0 && OROW == 0), "only the first product is split");
   static_assert(WK == 1 || (OROW == 0 && KS == 64), "halves of slices of 64, added for Z");
@@ -169,21 +195,21 @@ __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
   const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
   const int j = lane & 15, g = lane >> 4;
 
-  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  const LgPlan<ONE> plan(a);
   const int ks = SPLIT ? a.ks : 1;
   const int bid = SPLIT ? (int)blockIdx.x / ks : (int)blockIdx.x, sl = SPLIT ? (int)blockIdx.x % ks : 0;
   int tm, tn, li;
-  if (!lg_find_tile<BM>(a, rowmap, bid, lane, tm, tn, li)) return;
+  if (!lg_find_tile<BM>(a, plan, bid, lane, tm, tn, li)) return;
   const LgLayer &ly = a.L[li];
   const int K = ly.K, M = ly.M;
   const int kt0 = SPLIT ? (int)(((long long)(K / KS) * sl) / ks) : 0;           // first slice of this workgroup
   const int nk = (SPLIT ? (int)(((long long)(K / KS) * (sl + 1)) / ks) : K / KS) - kt0;
-  const int pat = a.plan[16 + tm * BM / 256];
+  const int pat = plan.pattern(tm * BM / 256);
   if (pat < 0) {
-    if (OROW == 1) lg_zero_rows<BM, BN>(ly, rowmap, tm, tn, wave, NW, lane);
+    if (OROW == 1) lg_zero_rows<BM, BN>(ly, plan, tm, tn, wave, NW, lane);
     return;
   }
-  if (BM < 256 && !a.compact && rowmap[tm * BM] < 0) return;
+  if (BM < 256 && !a.compact && plan.token_row(tm * BM) < 0) return;
   const uint16_t *Fp = ly.F + (size_t)pat * ly.pattern_stride;
 
   // ---- sources of this wavefront's load instructions; they advance by a constant per slice ----
@@ -213,7 +239,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
       tsrc[i] = (const char *)ly.Tk + ((size_t)(tm * (BM / 32) + tb) * (K / 16) + kk) * 1024;
     } else {                                   // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
       const int rr = ins * 8 + (lane >> 3);
-      const int row = max(rowmap[tm * BM + rr], 0);                // padding rows read row 0; their results are never stored to Y
+      const int row = max(plan.token_row(tm * BM + rr), 0);        // padding rows read row 0; their results are never stored to Y
       tsrc[i] = (const char *)ly.Tk + (size_t)row * K * 2 + (((lane & 7) ^ ((rr >> 1) & 7)) * 16) + (SPLIT ? (size_t)kt0 * 128 : 0);
     }
   }
@@ -371,8 +397,9 @@ __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
     }
   } else {                                     // rows of Y: two column blocks together, 64 bytes of a row
     int orow[TB];
+    const LgPlan<ONE> again(a);                // not kept in registers over the reduction
 #pragma unroll
-    for (int t = 0; t < TB; ++t) orow[t] = rowmap[tm * BM + (wm * TB + t) * 16 + j];
+    for (int t = 0; t < TB; ++t) orow[t] = again.token_row(tm * BM + (wm * TB + t) * 16 + j);
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
@@ -392,6 +419,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64, 2) void gemm_lds(LgArgs a) {
 // near the end), so a load has two halves, 2000 cycles, to arrive.  The sums are those of the other tiles, in the same order.
 // 32768 rows x 1024 ranks of eight patterns, n = m = 4096, both products on large tiles: 526 us with slices of 64, two stages and
 // 32x32x16 instructions, 462-480 now; 1280 ranks, 11008 columns: 1264 and 1160.
+template <int ONE>
 __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
   constexpr int F_HALF = 16384, T_SLICE = 32768, T_BASE = 4 * F_HALF;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -399,12 +427,12 @@ __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;     // 128 token rows x 64 factor rows each
   const int j = lane & 15, g = lane >> 4;
-  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
+  const LgPlan<ONE> plan(a);
   int tm, tn, li;
-  if (!lg_find_tile<256>(a, rowmap, blockIdx.x, lane, tm, tn, li)) return;
+  if (!lg_find_tile<256>(a, plan, blockIdx.x, lane, tm, tn, li)) return;
   const LgLayer &ly = a.L[li];
   const int K = ly.K, M = ly.M;
-  const int pat = a.plan[16 + tm];
+  const int pat = plan.pattern(tm);
   if (pat < 0) return;
   const int nk = K / 64, nh = nk * 2;
 
@@ -418,7 +446,7 @@ __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int rr = wave * 32 + i * 8 + (lane >> 3);      // LDS place: row rr, slot lane % 8; it holds chunk slot ^ swizzle of the row
-    const int row = max(rowmap[tm * 256 + rr], 0);       // padding rows read row 0; their results are never stored to Y
+    const int row = max(plan.token_row(tm * 256 + rr), 0);       // padding rows read row 0; their results are never stored to Y
     tsrc[i] = (const char *)ly.Tk + (size_t)row * K * 2 + (((lane & 7) ^ ((rr >> 1) & 7)) * 16);
   }
   int f_dst = wave * 2048, t_dst = T_BASE + wave * 4096; // place of the next half / slice that is requested
@@ -532,15 +560,16 @@ __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
 // Adds the ks partial sums of every 16-byte piece of Z (8 consecutive ranks of a token) in slice order and rounds to
 // bf16.  One thread per piece, over the plan's virtual rows and all layers of the call (grid.y); padding rows hold nothing
 // and are passed over (the second product's results for them are not stored either).
+template <int ONE>
 __global__ __launch_bounds__(256) void z_combine(LgArgs a) {
   const LgLayer &ly = a.L[blockIdx.y];
   const int M = ly.M, ks = a.ks;
-  const int32_t *rowmap = a.plan + 16 + (a.cap + 15) / 16 * 16;
-  const size_t pieces = (size_t)(a.plan[1] / 32) * (M / 16) * 64;    // virtual rows / 32 token blocks x reduction blocks x lanes
+  const LgPlan<ONE> plan(a);
+  const size_t pieces = (size_t)(plan.virtual_rows() / 32) * (M / 16) * 64;    // virtual rows / 32 token blocks x reduction blocks x lanes
   const size_t slice = (size_t)a.cap * 8 * (M / 16) * 512;           // floats per slice
   for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < pieces; o += (size_t)gridDim.x * 256) {
     const size_t tb = o / ((size_t)(M / 16) * 64);
-    if (rowmap[tb * 32 + (o & 31)] < 0) continue;
+    if (plan.token_row((int)(tb * 32 + (o & 31))) < 0) continue;
     const float *src = ly.Pz + o * 8;
     float4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < ks; s0 += 4) {      // four slices requested at a time (slices past the last re-read it)
@@ -589,17 +618,23 @@ static int launch_tiles(void (*kern)(LgArgs), int threads, int smem, bool (&attr
   return PARSE_OK;
 }
 
-template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1>
-static int launch_gemm_lds(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
+template <int ONE, int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT, int WK>
+static int launch_gemm_lds_as(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
   constexpr int staged = STAGES * (BM + BN) * KS * 2, sums = WK > 1 ? BM * BN * 4 : 0;
   static bool attr_done[64] = {false};
-  return launch_tiles<BM, BN>(gemm_lds<BM, BN, WM, WN, KS, STAGES, FORD, TROW, OROW, SPLIT, WK>, WM * WN * WK * 64,
+  return launch_tiles<BM, BN>(gemm_lds<BM, BN, WM, WN, KS, STAGES, FORD, TROW, OROW, SPLIT, WK, ONE>, WM * WN * WK * 64,
                               staged > sums ? staged : sums, attr_done, a, avg_tiles_per_pattern, SPLIT ? a.ks : 1, s);
 }
+template <int BM, int BN, int WM, int WN, int KS, int STAGES, int FORD, int TROW, int OROW, int SPLIT = 0, int WK = 1>
+static int launch_gemm_lds(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
+  return a.plan ? launch_gemm_lds_as<0, BM, BN, WM, WN, KS, STAGES, FORD, TROW, OROW, SPLIT, WK>(a, avg_tiles_per_pattern, s)
+                : launch_gemm_lds_as<1, BM, BN, WM, WN, KS, STAGES, FORD, TROW, OROW, SPLIT, WK>(a, avg_tiles_per_pattern, s);
+}
 
+template <int ONE>
 static int launch_first256(const LgArgs &a, int avg_tiles_per_pattern, hipStream_t s) {
   static bool attr_done[64] = {false};
-  return launch_tiles<256, 256>(gemm_first256, 512, 160 * 1024, attr_done, a, avg_tiles_per_pattern, 1, s);
+  return launch_tiles<256, 256>(gemm_first256<ONE>, 512, 160 * 1024, attr_done, a, avg_tiles_per_pattern, 1, s);
 }
 
 // Token tiles of bm rows, as far as the host can tell: it does not know which prompts share a pattern, and a pattern starts on a
@@ -692,21 +727,27 @@ static int split_slices(const PfArgs &p) {
   return best;
 }
 
-// n_layers layers that share X [rows][n] (row-major) and the plan (built for the tok_offsets and pattern ids of these
+// A call that would make its plan for itself needs none.
+bool prefill_needs_plan(int P) { return P > 1; }
+
+// n_layers layers that share X [rows][n] (row-major) and the plan (none unless prefill_needs_plan; built for the tok_offsets and pattern ids of these
 // patterns); Z[l] = layer l's intermediate (operand order over the plan's virtual rows); p[l].Y [rows][m_l].
 // Two launches for all layers together: the stacked first product, the batched second product (Sec. 4.4, Eq. 11-12); where the
 // first one is split, one more that adds the slices (layers that are split differently: as many of each).
 int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int32_t *plan, int cap, uint16_t *const *Z,
                                        int avg_prompt_rows, hipStream_t s) {
   if (n_layers < 1 || n_layers > LG_MAX_LAYERS) return PARSE_ESHAPE;
-  LgArgs g1{}, g2{};
-  g1.n_layers = g2.n_layers = n_layers;
-  g1.plan = g2.plan = plan;
-  g1.cap = g2.cap = cap;
+  LgArgs g1{};
+  g1.n_layers = n_layers;
+  g1.plan = plan;
+  g1.tok_offsets = p[0].tok_offsets; g1.pattern_id = p[0].pattern_id;
+  g1.rows = p[0].rows; g1.NP = p[0].n_patterns;
+  g1.cap = cap;
   const int rows = p[0].rows, P = p[0].P;
   // one prompt has less than a 256-row tile of padding, prompts of one length in whole tiles (most likely) have none: leaving
   // padding tiles out of the numbering costs a launch 1 us
-  g1.compact = g2.compact = P > 1 && !(rows % P == 0 && rows / P % 256 == 0);
+  g1.compact = P > 1 && !(rows % P == 0 && rows / P % 256 == 0);
+  LgArgs g2 = g1;
   bool slices64 = true;                        // the second product can take slices of 64
   for (int l = 0; l < n_layers; ++l) {
     if (p[l].sh_ranks % 32 != 0 || p[l].sh_ranks >= p[l].rS) return PARSE_ESHAPE;
@@ -741,7 +782,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
       else st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g, per_pattern, s);
       if (st != PARSE_OK) return st;
       const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
-      hipLaunchKernelGGL(z_combine, dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), g.n_layers), dim3(256), 0, s, g);
+      hipLaunchKernelGGL((g.plan ? z_combine<0> : z_combine<1>), dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), g.n_layers), dim3(256), 0, s, g);
       PARSE_LAUNCH_CHECK();
       continue;
     }
@@ -755,7 +796,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
     else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);
     else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 4, 64, 5, 0, 1, 0>(g, per_pattern, s);
     else if (tile == T128x256) st = launch_gemm_lds<128, 256, 2, 4, 64, 3, 0, 1, 0>(g, per_pattern, s);
-    else st = launch_first256(g, per_pattern, s);
+    else st = g.plan ? launch_first256<0>(g, per_pattern, s) : launch_first256<1>(g, per_pattern, s);
     if (st != PARSE_OK) return st;
   }
 

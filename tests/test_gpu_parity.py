@@ -1699,6 +1699,50 @@ def test_decode_many_sequences(n, shapes, rows):
             assert_close(yn[ok], ref[ok], TOL_BF16, f"layer {l} {what}")
 
 
+@pytest.mark.parametrize("n,m,gs,rows,off,pid", [
+    (256, 96, 32, 1, [0, 1], 0),
+    (1024, 1024, 32, 57, [0, 57], 2),
+    (4096, 224, 96, 77, [0, 77], 1),                    # the reduction cut in slices
+    (256, 256, 32, 300, [7, 263], 1),                   # rows outside the prompt stay as they are; one whole tile of 256
+    (256, 256, 32, 300, [5, 262], 0),                   # ... one row more
+    (256, 160, 32, 200, [-3, 900], 1),                  # offsets past the batch
+    (256, 160, 32, 200, [150, 150], 1),                 # no rows
+    (256, 160, 32, 333, [0, 333], 3),                   # no such pattern: zero rows
+    (256, 160, 32, 333, [0, 333], -1),
+    (8192, 128, 32, 1300, [0, 1300], 0),                # four slices of 128 x 256 tiles
+    (256, 4128, 64, 4200, [0, 4200], 1),                # more than 4096 rows
+    (256, 11008, 160, 10500, [0, 10500], 2),            # 256 x 256 tiles in both products
+])
+def test_prefill_of_one_prompt_without_its_plan(n, m, gs, rows, off, pid):
+    """A call that would make the plan of a single prompt for itself works without one: the bits of the planned call, one layer and two."""
+    say(f"prefill of one prompt n={n} m={m} gs={gs} rows={rows} off={off} pid={pid}")
+    gen = torch.Generator(device=DEV); gen.manual_seed(rows + n)
+    G, k, npat = 4, 2, 3
+    R = G * gs
+    layers, pats = [], []
+    for _ in range(2):
+        V, U = ((torch.randn(s, device=DEV, generator=gen) / s[1] ** 0.5).to(torch.bfloat16) for s in ((R, n), (R, m)))
+        layers.append(pa.layer_to_mfma16(pa.Layer(V, U, n, m, R, G, pa.PARSE_ROWMAJOR)))
+        subs = i32(np.array([[0, 2], [1, 3], [2, 3]]))
+        pats.append(pa.Patterns(k, npat, *pa.pack_patterns(layers[-1], subs, k, k, None, None, npat)))
+    X = torch.randn(rows, n, device=DEV, generator=gen).to(torch.bfloat16)
+    offd, pidd = i32(np.array(off)), i32(np.array([pid]))
+    plan = pa.prefill_plan(offd, pidd, rows, npat)
+    ref = []
+    for l, p in zip(layers, pats):
+        Y = torch.full((rows, m), 3.0, dtype=torch.bfloat16, device=DEV)
+        pa.lowrank_prefill_planned(l, p, X, offd, pidd, plan, Y)
+        ref.append(Y)
+    one = torch.full_like(ref[0], 3.0)
+    ws = torch.empty(pa.lowrank_workspace_bytes(pa.PARSE_PREFILL, layers[0], rows, k, 1, npat), dtype=torch.uint8, device=DEV)
+    pa.lowrank_forward(pa.PARSE_PREFILL, layers[0], pats[0], X, offd, pidd, one, ws)
+    both = [torch.full_like(ref[0], 3.0) for _ in range(2)]
+    pa.lowrank_prefill_multi(layers, pats, X, offd, pidd, both)
+    torch.cuda.synchronize()
+    for what, y, r in (("one layer", one, ref[0]), ("two layers, first", both[0], ref[0]), ("two layers, second", both[1], ref[1])):
+        assert torch.equal(y.view(torch.int16), r.view(torch.int16)), what
+
+
 @pytest.mark.parametrize("n,shapes,rows", [
     (336, [(64, 256, 8, 3)], 97),                     # a last slice of 16 indices, four panels; fewer slices than stages
     (1056, [(96, 288, 3, 2)], 40),                    # ... of 32, an odd number of rank blocks, two panels
