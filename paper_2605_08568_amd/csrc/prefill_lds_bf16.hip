@@ -677,13 +677,15 @@ size_t prefill_planned_z_bytes(int cap_tiles, int rS, int ks) {
 bool prefill_planned_supported(int n, int m, int rS) { return n % 64 == 0 && rS % 32 == 0 && m % 32 == 0 && n >= 64 && rS >= 32; }
 
 // Time of the first product with tile i, in units of a round of 128 x 128 tiles, one per compute unit (30 us at K = 4096).
-// Fitted to earlier forms of these kernels, over shapes of 77 to 57 000 rows and 512 to 3072 ranks, and still in their order for the present
-// ones: n = m = 4096, both products, us, 256 x 256 / 128 x 256 / 128 x 128 / 64 x 128 / 64 x 64: one prompt of 2048 rows x 2304 ranks 115 / 85 /
-// 94 / 95 / 95, x 768 ranks 95 / 62 / 46 / 38 / 42; eight of 512 x 1024 111 / 78 / 68 / 76 / 82, of 1024 x 1024 147 / 124 / 138 / 151 / 161, of 4096 x
-// 1024 462 / 517 / 573 / 651 / 694.
-enum { T64, T64x128, T128, T128x256, T256, N_TILES };
+// Fitted to earlier forms of these kernels, over shapes of 77 to 57 000 rows and 512 to 3072 ranks; over 34 calls of 150 to 4096 rows of the present ones
+// the tile taken is 0.4 % off the best of each on average, 16 % at worst (ragged prompts).  n = m = 4096, both products, us, 256 x 256 / 128 x 256 / 128 x 128 /
+// 64 x 128 / 64 x 64: one prompt of 2048 rows x 768 ranks 95 / 62 / 46 / 38 / 42; eight of 512 x 1024 111 / 78 / 68 / 76 / 82, of 1024 x 1024 147 / 124 / 138 / 151 /
+// 161, of 4096 x 1024 462 / 517 / 573 / 651 / 694.  128 x 192 between them, up to SHORT_ROWS, 128 x 256 / 128 x 192 / 128 x 128 / 64 x 128: three layers of
+// 768 ranks that share 2048 rows 93 / 88 / 101 / 101 (192 tiles of three quarters of the work, instead of 144), 2 x 1024 rows 107 / 99 / 112 / 114; n = m = 2048, 3 x 384
+// ranks, 4096 rows 60 / 55.5 / 62 / 63.
+enum { T64, T64x128, T128, T128x192, T128x256, T256, N_TILES };
 static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split = 1) {
-  static const int bm[N_TILES] = {64, 64, 128, 128, 256}, bn[N_TILES] = {64, 128, 128, 256, 256};
+  static const int bm[N_TILES] = {64, 64, 128, 128, 128, 256}, bn[N_TILES] = {64, 128, 128, 192, 256, 256};
   long long t = 0;
   for (int l = 0; l < n_layers; ++l) t += (p[l]->rS + bn[i] - 1) / bn[i];
   t *= token_tiles(p[0]->rows, p[0]->P, bm[i]) * split;
@@ -692,6 +694,7 @@ static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split
     case T64: return t <= 256 ? 0.45 : (split > 1 ? 0.69 * two_each : 0.69 + 0.9 * (two_each - 1));
     case T64x128: return rounds - 0.4;
     case T128: return rounds;
+    case T128x192: return 1.3 * rounds;
     case T128x256: return 1.57 * rounds;
     default: return 2.5 * rounds;
   }
@@ -699,7 +702,7 @@ static double tile_rounds(int i, const PfArgs *const *p, int n_layers, int split
 static int best_tile(const PfArgs *const *p, int n_layers) {
   int best = T64;
   for (int i = 1; i < N_TILES; ++i)
-    if (!(i == T256 && p[0]->rows <= SHORT_ROWS) && tile_rounds(i, p, n_layers) < tile_rounds(best, p, n_layers)) best = i;
+    if (i != (p[0]->rows <= SHORT_ROWS ? T256 : T128x192) && tile_rounds(i, p, n_layers) < tile_rounds(best, p, n_layers)) best = i;
   return best;
 }
 // Slices of one layer's first product: as many (up to four) as pay for the second launch, which adds the fp32 partial sums (2 us
@@ -792,6 +795,7 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
       if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
       else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
       else if (tile == T128) st = launch_gemm_lds<128, 128, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
+      else if (tile == T128x192) st = launch_gemm_lds<128, 192, 2, 2, 64, 4, 0, 1, 0, 0, 2>(g, per_pattern, s);
       else st = launch_gemm_lds<128, 256, 2, 2, 64, 3, 0, 1, 0, 0, 2>(g, per_pattern, s);
     } else if (tile == T64) st = launch_gemm_lds<64, 64, 2, 2, 64, 5, 0, 1, 0>(g, per_pattern, s);      // many rows, few ranks
     else if (tile == T64x128) st = launch_gemm_lds<64, 128, 2, 2, 64, 4, 0, 1, 0>(g, per_pattern, s);

@@ -1871,6 +1871,16 @@ def test_prefill_planned_tiles(n, m, rS, lengths):
         assert torch.equal(y.view(torch.int16), both[l].view(torch.int16)), f"layer {l}: alone and in a call of two"
 
 
+@pytest.mark.parametrize("n,m,rS,lengths", [
+    (64, 64, 2336, [2000]),                             # a last tile of 32 ranks
+    (704, 96, 2304, [700, 1, 129, 1000, 127]),          # eleven slices, padding tiles left out, a prompt without a pattern
+    (192, 64, 2240, [257, 1700]),                       # fewer slices than stages
+])
+def test_prefill_planned_tiles_of_192_ranks(n, m, rS, lengths):
+    """First products whose 128 x 192 tiles are one round of workgroups where 128 x 128 ones are two."""
+    test_prefill_planned_tiles(n, m, rS, lengths)
+
+
 @pytest.mark.parametrize("n,m,rS,lengths,cut", [
     (8192, 64, 64, [1025], True),                     # the first batch past the short ones, one tile column
     (8256, 96, 288, [513, 600, 40], True),            # an odd number of slices of 64, a rank block past the last tile, padding tiles
