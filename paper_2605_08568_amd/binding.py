@@ -1,4 +1,5 @@
-"""ctypes binding of include/parse.h.  Argument marshalling only: names and meaning follow the header."""
+"""Binding of include/parse.h.  Argument marshalling only: names and meaning follow the header.  The calls of a step go through the native
+module _calls (csrc/calls.cpp), which takes tensors, layers and patterns as they are; everything else through ctypes."""
 from __future__ import annotations
 
 import ctypes as C
@@ -135,6 +136,20 @@ def lib():
     return L
 
 
+class _Calls:
+    """Stands for the native module until the first call; fails loudly when it has not been built."""
+
+    def __getattr__(self, name):
+        global _calls
+        lib()
+        from . import _calls as native
+        _calls = native
+        return getattr(native, name)
+
+
+_calls = _Calls()
+
+
 def status_string(status: int) -> str:
     return lib().parse_status_string(status).decode()
 
@@ -150,6 +165,13 @@ def _check(status: int, where: str):
 
 def _ptr(t):
     return None if t is None else t.data_ptr()
+
+
+def _no_more(nl: int, *of_layers):
+    """A list of what the layers have holds no more than there are layers."""
+    for a in of_layers:
+        if len(a) > nl:
+            raise IndexError("invalid index")
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # not a public name: the stream object serves without it
@@ -256,13 +278,11 @@ def route(X, tok_offsets, Wr, k, subset_out=None, subset_stride=None, scores_out
     if workspace is None:
         workspace = torch.empty(max(route_workspace_bytes(rows, P, d), 256), dtype=torch.uint8, device=X.device)
     if n_shared is None:
-        _check(lib().parse_route(_ptr(X), _dtype_code(X), rows, _ptr(tok_offsets), P, d, _ptr(Wr), G, k,
-                                 _ptr(subset_out), stride, _ptr(scores_out), _ptr(emb_out), _ptr(workspace),
-                                 workspace.numel(), _stream()), "parse_route")
+        _check(_calls.parse_route(X, _dtype_code(X), rows, tok_offsets, P, d, Wr, G, k, subset_out, stride, scores_out,
+                                  emb_out, workspace, workspace.numel(), _stream()), "parse_route")
     else:
-        _check(lib().parse_route_shared(_ptr(X), _dtype_code(X), rows, _ptr(tok_offsets), P, d, _ptr(Wr), G, k, n_shared,
-                                        _ptr(subset_out), stride, _ptr(scores_out), _ptr(emb_out), _ptr(workspace),
-                                        workspace.numel(), _stream()), "parse_route_shared")
+        _check(_calls.parse_route_shared(X, _dtype_code(X), rows, tok_offsets, P, d, Wr, G, k, n_shared, subset_out, stride,
+                                         scores_out, emb_out, workspace, workspace.numel(), _stream()), "parse_route_shared")
     return subset_out
 
 
@@ -274,8 +294,8 @@ def pool(X, tok_offsets, emb_out=None, workspace=None):
         emb_out = torch.empty((P, d), dtype=torch.float32, device=X.device)
     if workspace is None:
         workspace = torch.empty(max(route_workspace_bytes(rows, P, d), 256), dtype=torch.uint8, device=X.device)
-    _check(lib().parse_pool(_ptr(X), _dtype_code(X), rows, _ptr(tok_offsets), P, d, _ptr(emb_out), _ptr(workspace),
-                            workspace.numel(), _stream()), "parse_pool")
+    _check(_calls.parse_pool(X, _dtype_code(X), rows, tok_offsets, P, d, emb_out, workspace, workspace.numel(), _stream()),
+                             "parse_pool")
     return emb_out
 
 
@@ -339,8 +359,8 @@ class Cache:
         sim_out = torch.empty(P, dtype=torch.float32, device=dev) if sim_out is None else sim_out
         if subset_out is None:
             subset_out = torch.empty((P, self.L, self.k), dtype=torch.int32, device=dev)
-        _check(lib().parse_cache_lookup_or_route(self._h, _ptr(emb), P, tau, _ptr(Wr), G, _ptr(entry_out),
-                                                 _ptr(hit_out), _ptr(sim_out), _ptr(subset_out), _stream()),
+        _check(_calls.parse_cache_lookup_or_route(None if self._h is None else self._h.value, emb, P, tau, Wr, G, entry_out,
+                                                  hit_out, sim_out, subset_out, _stream()),
                "parse_cache_lookup_or_route")
         return entry_out, hit_out, sim_out, subset_out
 
@@ -355,8 +375,7 @@ def bucket_patterns(subset, k, subset_stride=None, out=None):
                torch.empty(P + 1, dtype=torch.int32, device=dev), torch.empty(1, dtype=torch.int32, device=dev),
                torch.empty(P, dtype=torch.int32, device=dev))
     pid, perm, off, npat, rep = out
-    _check(lib().parse_bucket_patterns(_ptr(subset), P, k, stride, _ptr(pid), _ptr(perm), _ptr(off), _ptr(npat),
-                                       _ptr(rep), _stream()), "parse_bucket_patterns")
+    _check(_calls.parse_bucket_patterns(subset, P, k, stride, pid, perm, off, npat, rep, _stream()), "parse_bucket_patterns")
     return out
 
 
@@ -379,18 +398,16 @@ def pack_patterns(layer: Layer, subset, subset_stride, k, rep, n_patterns, max_p
         Vt_S = torch.empty((max_patterns, k * layer.gs, layer.n), dtype=layer.Vt.dtype, device=layer.Vt.device)
     if Ut_S is None:
         Ut_S = torch.empty((max_patterns, k * layer.gs, layer.m), dtype=layer.Ut.dtype, device=layer.Ut.device)
-    cl = layer.c()
-    _check(lib().parse_pack_patterns(C.byref(cl), _ptr(subset), subset_stride, k, _ptr(rep), _ptr(n_patterns),
-                                     max_patterns, _ptr(Vt_S), _ptr(Ut_S), _stream()), "parse_pack_patterns")
+    _check(_calls.parse_pack_patterns(layer, subset, subset_stride, k, rep, n_patterns, max_patterns, Vt_S, Ut_S, _stream()),
+                                      "parse_pack_patterns")
     return Vt_S, Ut_S
 
 
 def pack_new_entries(layer: Layer, subset, subset_stride, k, entry, hit, Vt_S, Ut_S):
     """parse_pack_new_entries: packs the subsets of this batch's new cache entries into their slots of
     Vt_S [n_slots][k*gs][n] / Ut_S [n_slots][k*gs][m]."""
-    cl = layer.c()
-    _check(lib().parse_pack_new_entries(C.byref(cl), _ptr(subset), subset_stride, k, entry.numel(), _ptr(entry),
-                                        _ptr(hit), Vt_S.shape[0], _ptr(Vt_S), _ptr(Ut_S), _stream()),
+    _check(_calls.parse_pack_new_entries(layer, subset, subset_stride, k, entry.numel(), entry, hit, Vt_S.size(0), Vt_S,
+                                         Ut_S, _stream()),
            "parse_pack_new_entries")
     return Vt_S, Ut_S
 
@@ -410,8 +427,8 @@ def prefill_plan(tok_offsets, pattern_id, rows: int, n_patterns: int, plan=None)
     P = pattern_id.numel()
     if plan is None:
         plan = torch.empty(prefill_plan_bytes(rows, P, n_patterns), dtype=torch.uint8, device=pattern_id.device)
-    _check(lib().parse_prefill_plan(_ptr(tok_offsets), _ptr(pattern_id), P, rows, n_patterns, _ptr(plan), plan.numel(),
-                                    _stream()), "parse_prefill_plan")
+    _check(_calls.parse_prefill_plan(tok_offsets, pattern_id, P, rows, n_patterns, plan, plan.numel(), _stream()),
+                                     "parse_prefill_plan")
     return plan
 
 
@@ -427,9 +444,8 @@ def bucket_and_plan(subset, k, subset_stride, tok_offsets, plan_pattern_id, rows
     if plan is None:
         plan = torch.empty(prefill_plan_bytes(rows, P, n_patterns), dtype=torch.uint8, device=dev)
     pid, perm, off, npat, rep = out
-    _check(lib().parse_bucket_and_plan(_ptr(subset), P, k, stride, _ptr(pid), _ptr(perm), _ptr(off), _ptr(npat), _ptr(rep),
-                                       _ptr(tok_offsets), _ptr(plan_pattern_id), rows, n_patterns, _ptr(plan), plan.numel(),
-                                       _stream()), "parse_bucket_and_plan")
+    _check(_calls.parse_bucket_and_plan(subset, P, k, stride, pid, perm, off, npat, rep, tok_offsets, plan_pattern_id, rows,
+                                        n_patterns, plan, plan.numel(), _stream()), "parse_bucket_and_plan")
     return out, plan
 
 
@@ -440,16 +456,14 @@ def lowrank_prefill_planned_workspace_bytes(layer: Layer, rows: int, P: int, k: 
 
 def lowrank_prefill_planned(layer: Layer, patterns: Patterns, X, tok_offsets, pattern_id, plan, Y=None, workspace=None):
     """parse_lowrank_prefill_planned.  Returns Y [rows][m]."""
-    rows, P = X.shape[0], pattern_id.numel()
+    rows, P = X.size(0), pattern_id.numel()
     if Y is None:
         Y = torch.empty((rows, layer.m), dtype=X.dtype, device=X.device)
     if workspace is None:
         need = lowrank_prefill_planned_workspace_bytes(layer, rows, P, patterns.k, patterns.n_patterns)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    cl, cp = layer.c(), patterns.c()
-    _check(lib().parse_lowrank_prefill_planned(C.byref(cl), C.byref(cp), _ptr(X), rows, _ptr(tok_offsets), _ptr(pattern_id), P,
-                                               _ptr(plan), _ptr(Y),
-                                               _ptr(workspace), workspace.numel(), _stream()),
+    _check(_calls.parse_lowrank_prefill_planned(layer, patterns, X, rows, tok_offsets, pattern_id, P, plan, Y, workspace,
+                                                workspace.numel(), _stream()),
            "parse_lowrank_prefill_planned")
     return Y
 
@@ -461,13 +475,12 @@ def lowrank_forward(mode: int, layer: Layer, patterns: Patterns, X, tok_offsets,
     P = pattern_id.numel()
     if Y is None:
         Y = torch.empty((rows, layer.m), dtype=X.dtype, device=X.device)
-    need = lowrank_workspace_bytes(mode, layer, rows, patterns.k, P, patterns.n_patterns)
-    if workspace is None and need > 0 and not no_workspace:
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
-    cl, cp = layer.c(), patterns.c()
-    _check(lib().parse_lowrank_forward(mode, C.byref(cl), C.byref(cp), _ptr(X), rows, _ptr(tok_offsets),
-                                       _ptr(pattern_id), P, _ptr(Y), _ptr(workspace),
-                                       0 if workspace is None else workspace.numel(), _stream()),
+    if workspace is None and not no_workspace:
+        need = lowrank_workspace_bytes(mode, layer, rows, patterns.k, P, patterns.n_patterns)
+        if need > 0:
+            workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
+    _check(_calls.parse_lowrank_forward(mode, layer, patterns, X, rows, tok_offsets, pattern_id, P, Y, workspace, 0 if
+                                        workspace is None else workspace.numel(), _stream()),
            "parse_lowrank_forward")
     return Y
 
@@ -516,10 +529,9 @@ def lowrank_decode_planned(layers, X, plan, Ys=None, workspace=None):
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
     if workspace is None:
         workspace = torch.empty(max(lowrank_decode_planned_workspace_bytes(layers), 256), dtype=torch.uint8, device=X.device)
-    larr = (_Layer * nl)(*[l.c() for l in layers])
-    yarr = (C.c_void_p * nl)(*[y.data_ptr() for y in Ys])
-    _check(lib().parse_lowrank_decode_planned(larr, nl, _ptr(X), rows, _ptr(plan), yarr, _ptr(workspace),
-                                              workspace.numel(), _stream()), "parse_lowrank_decode_planned")
+    _no_more(nl, Ys)
+    _check(_calls.parse_lowrank_decode_planned(layers, nl, X, rows, plan, Ys, workspace, workspace.numel(), _stream()),
+                                               "parse_lowrank_decode_planned")
     return Ys
 
 
@@ -536,11 +548,9 @@ def lowrank_decode_multi(layers, patterns, X, pattern_id, Ys=None, workspace=Non
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
     if workspace is None:
         workspace = torch.empty(max(lowrank_decode_multi_workspace_bytes(layers), 256), dtype=torch.uint8, device=X.device)
-    larr = (_Layer * nl)(*[l.c() for l in layers])
-    parr = (_Patterns * nl)(*[p.c() for p in patterns])
-    yarr = (C.c_void_p * nl)(*[y.data_ptr() for y in Ys])
-    _check(lib().parse_lowrank_decode_multi(larr, parr, nl, _ptr(X), rows, _ptr(pattern_id), yarr, _ptr(workspace),
-                                            workspace.numel(), _stream()), "parse_lowrank_decode_multi")
+    _no_more(nl, patterns, Ys)
+    _check(_calls.parse_lowrank_decode_multi(layers, patterns, nl, X, rows, pattern_id, Ys, workspace, workspace.numel(),
+                                             _stream()), "parse_lowrank_decode_multi")
     return Ys
 
 
@@ -557,14 +567,12 @@ def lowrank_prefill_multi(layers, patterns, X, tok_offsets, pattern_id, Ys=None,
     P = pattern_id.numel()
     if Ys is None:
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
-    larr = (_Layer * nl)(*[l.c() for l in layers])
-    parr = (_Patterns * nl)(*[p.c() for p in patterns])
     if workspace is None:
-        need = int(lib().parse_lowrank_prefill_multi_workspace_bytes(larr, parr, nl, rows))
+        need = lowrank_prefill_multi_workspace_bytes(layers, patterns, rows)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    yarr = (C.c_void_p * nl)(*[y.data_ptr() for y in Ys])
-    _check(lib().parse_lowrank_prefill_multi(larr, parr, nl, _ptr(X), rows, _ptr(tok_offsets), _ptr(pattern_id), P, yarr,
-                                             _ptr(workspace), workspace.numel(), _stream()), "parse_lowrank_prefill_multi")
+    _no_more(nl, patterns, Ys)
+    _check(_calls.parse_lowrank_prefill_multi(layers, patterns, nl, X, rows, tok_offsets, pattern_id, P, Ys, workspace,
+                                              workspace.numel(), _stream()), "parse_lowrank_prefill_multi")
     return Ys
 
 
@@ -580,9 +588,8 @@ def route_ranks(X, tok_offsets, Wr, K, subset_out=None, subset_stride=None, scor
     if workspace is None:
         need = int(lib().parse_route_ranks_workspace_bytes(rows, P, d, G))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    _check(lib().parse_route_ranks(_ptr(X), _dtype_code(X), rows, _ptr(tok_offsets), P, d, _ptr(Wr), G, K,
-                                   _ptr(subset_out), stride, _ptr(scores_out), _ptr(emb_out), _ptr(workspace),
-                                   workspace.numel(), _stream()), "parse_route_ranks")
+    _check(_calls.parse_route_ranks(X, _dtype_code(X), rows, tok_offsets, P, d, Wr, G, K, subset_out, stride, scores_out,
+                                    emb_out, workspace, workspace.numel(), _stream()), "parse_route_ranks")
     return subset_out
 
 
@@ -593,8 +600,7 @@ def pack_ranks(layer: Layer, subset, K, n_patterns, subset_stride=None, Vt_S=Non
         Vt_S = torch.empty((n_patterns, K, layer.n), dtype=layer.Vt.dtype, device=layer.Vt.device)
     if Ut_S is None:
         Ut_S = torch.empty((n_patterns, K, layer.m), dtype=layer.Ut.dtype, device=layer.Ut.device)
-    cl = layer.c()
-    _check(lib().parse_pack_ranks(C.byref(cl), _ptr(subset), stride, K, n_patterns, _ptr(Vt_S), _ptr(Ut_S), _stream()),
+    _check(_calls.parse_pack_ranks(layer, subset, stride, K, n_patterns, Vt_S, Ut_S, _stream()),
            "parse_pack_ranks")
     return Vt_S, Ut_S
 
@@ -610,13 +616,13 @@ def router_grad(layer: Layer, Ut_rankmajor, X, tok_offsets, Y_hat, Y_dense, emb,
                 workspace=None):
     """parse_router_grad -> (loss [P], grad_Wr [G][d])."""
     rows, P, d = X.shape[0], tok_offsets.numel() - 1, emb.shape[1]
-    cl = layer.c()
     if workspace is None:
+        cl = layer.c()
         need = int(lib().parse_router_grad_workspace_bytes(C.byref(cl), rows, P))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
     loss = torch.empty(P, dtype=torch.float32, device=X.device)
     grad = torch.empty((layer.G, d), dtype=torch.float32, device=X.device)
-    _check(lib().parse_router_grad(C.byref(cl), _ptr(Ut_rankmajor), _ptr(X), rows, _ptr(tok_offsets), P, _ptr(Y_hat),
-                                   _ptr(Y_dense), _ptr(emb), _ptr(scores), d, k, temperature, eps, _ptr(loss), _ptr(grad),
-                                   _ptr(workspace), workspace.numel(), _stream()), "parse_router_grad")
+    _check(_calls.parse_router_grad(layer, Ut_rankmajor, X, rows, tok_offsets, P, Y_hat, Y_dense, emb, scores, d, k,
+                                    temperature, eps, loss, grad, workspace, workspace.numel(), _stream()),
+                                    "parse_router_grad")
     return loss, grad

@@ -1,14 +1,16 @@
-"""Builds libparse.so (the C-ABI library) from the HIP sources with hipcc for gfx950."""
+"""Builds libparse.so (the C-ABI library) from the HIP sources with hipcc for gfx950, and _calls.so (its calls for Python) with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libparse.so")
+CALLS = os.path.join(HERE, "_calls.so")      # CPython module of the step's calls
 SOURCES = ["api.hip", "route.hip", "cache.hip", "pack.hip", "bucket.hip", "forward_f32.hip",
            "prefill_bf16.hip", "prefill_split_bf16.hip", "prefill_lds_bf16.hip", "plan.hip", "decode_bf16.hip", "decode_wide_bf16.hip", "decode_static.hip", "forward.hip", "ranks.hip", "train.hip", "peaks.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-I" + INCLUDE, "-I" + CSRC,
@@ -44,8 +46,16 @@ def build(verbose: bool = True, jobs: int = 8) -> str:
     out = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if out.returncode != 0:
         raise RuntimeError("link failed:\n" + out.stdout)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-I" + INCLUDE,
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L" + HERE, "-l:libparse.so",
+           "-Wl,-rpath,$ORIGIN"]
+    out = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if out.returncode != 0:
+        raise RuntimeError("g++ failed on calls.cpp:\n" + out.stdout)
     if verbose:
-        print("built", LIB)
+        if out.stdout.strip():
+            print(out.stdout)
+        print("built", LIB, CALLS)
     return LIB
 
 

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "parse.h")
@@ -358,3 +359,53 @@ def test_stream_handle_without_the_private_name(monkeypatch):
     monkeypatch.setattr(B, "_raw_stream", None)
     monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
     assert B._stream() == 4711
+
+
+class _Tensor:
+    """Stands for a tensor where only its address is asked for."""
+
+    def __init__(self, address):
+        self.address = address
+
+    def data_ptr(self):
+        return self.address
+
+
+def _module_layer(**kw):
+    a = dict(Vt=_Tensor(4096), Ut=_Tensor(8192), n=64, m=64, R=64, G=2, layout=B.PARSE_MFMA16, dtype=B.PARSE_BF16)
+    a.update(kw)
+    return type("L", (), a)()
+
+
+def test_module_converts_arguments_like_the_structures(monkeypatch):
+    """The native module hands on what the ctypes structures hold: every status below is decided by one converted argument."""
+    calls = B._calls
+    t = _Tensor(1 << 20)
+    pats = B.Patterns(1, 1, t, t, subsets=t)
+    def planned(layer, p=pats, X=t, rows=8, P=1, ws=t, wsb=1 << 40):
+        return calls.parse_lowrank_prefill_planned(layer, p, X, rows, t, t, P, t, t, ws, wsb, None)
+    assert planned(_module_layer(), X=None) == -1                         # PARSE_EINVAL: None is no address
+    assert planned(_module_layer(), rows=0) == -1
+    assert planned(_module_layer(layout=B.PARSE_ROWMAJOR)) == -7          # PARSE_ELAYOUT
+    assert planned(_module_layer(), X=_Tensor((1 << 20) + 8)) == -3       # PARSE_EALIGN
+    assert planned(_module_layer(), P=9) == -2                            # PARSE_ESHAPE: more prompts than rows
+    assert planned(_module_layer(), p=B.Patterns(3, 1, t, t)) == -2       # k > G
+    assert planned(_module_layer(), wsb=16) == -5                         # PARSE_EWORKSPACE
+    assert planned(_module_layer(), ws=None) == -5
+    assert planned(_module_layer(n=np.int64(64)), wsb=np.int32(16)) == -5
+    # sequences: a short one leaves zeros, which the library refuses; more layers than a call takes
+    def multi(layers, p, nl, Ys):
+        return calls.parse_lowrank_decode_multi(layers, p, nl, t, 2, t, Ys, t, 1 << 40, None)
+    two = [_module_layer(), _module_layer()]
+    assert multi(two, [pats], 2, [t, t]) == -1 and multi(tuple(two), (pats, pats), 2, (t,)) == -1
+    assert multi(two * 3, [pats] * 6, 6, [t] * 6) == -2 and multi([], [], 0, []) == -1
+    for bad in (lambda: planned(object()), lambda: planned(_module_layer(n="64")), lambda: planned(_module_layer(), X=3.5),
+                lambda: planned(_module_layer(), rows=1.0), lambda: calls.parse_pool(t), lambda: multi(3, [pats], 1, [t])):
+        with pytest.raises((TypeError, AttributeError)):
+            bad()
+    for extra in (([pats] * 3, [t] * 2), ([pats] * 2, [t] * 3)):
+        with pytest.raises(IndexError):
+            B.lowrank_decode_multi(two, extra[0], torch.zeros(2, 64, dtype=torch.bfloat16), torch.zeros(2, dtype=torch.int32), extra[1], torch.zeros(8))
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    with pytest.raises(B.ParseError, match="-3"):                         # a width of 7: PARSE_EALIGN
+        B.pool(torch.zeros(4, 7), torch.zeros(2, dtype=torch.int32), torch.zeros(1, 7), torch.zeros(8, dtype=torch.uint8))
