@@ -15,9 +15,6 @@ namespace parse {
 int launch_pool(const void *X, int xdtype, int rows, const int32_t *tok_offsets, int P, int d, float *partial, float *emb, hipStream_t s);
 
 constexpr int RK_MAXG = 8192;        // ranks the selection kernel holds in LDS
-constexpr int RK_PB = 8;             // prompts per scoring workgroup
-constexpr int RK_RPW = 2;            // router rows per wavefront
-constexpr int RK_ROWS = 4 * RK_RPW;  // router rows per scoring workgroup
 
 // e[p][:] = (sum of the Q slice partials, in slice order) / prompt length.  grid (ceil(d/1024), P), block 256.
 __global__ __launch_bounds__(256) void pool_finish(const float *__restrict__ partial, int Q, int rows, int d,
@@ -48,44 +45,93 @@ int launch_pool_finish(const float *partial, int Q, int rows, int d, const int32
   return PARSE_OK;
 }
 
-// scores[p][g] = <Wr[g], e_p>.  grid (ceil(G/8), ceil(P/8)), block 256: wavefront w owns rows 2w, 2w+1 of the
-// block for the 8 prompts of the block.  Pure streaming, no LDS and no barrier: a lane reads 16 bytes of each of
-// its two router rows and of the 8 embeddings (cache-resident, 16 KB each) per 256-column step, four steps in
-// flight; every lane keeps 2 x 8 partial sums and the 64 lanes are added at the end (fixed order: same inputs,
-// same bits).
-__global__ __launch_bounds__(256) void rank_scores(const float *__restrict__ Wr, const float *__restrict__ emb, int G,
-                                                   int d, int P, float *__restrict__ scores) {
+// scores[p][g] = <Wr[g], e_p>.  grid (router rows in units of 4 RPW, prompts in units of PB), block 256: wavefront w owns RPW rows
+// for the PB prompts of the block; lane l adds columns 256 i + 4 l .. + 3 for i = 0, 1, ..., and the 64 lanes are added at the end (the
+// same order for all RPW and PB: same inputs, same bits).  Bound by the stream of Wr and, for eight prompts, by the embeddings that come in beside
+// it: parts of RK_PART columns, rows and embeddings of the next ones on their way while one is added up; the embeddings go through LDS,
+// where four wavefronts share them.
+constexpr int RK_PART = 1024, RK_STEPS = RK_PART / 256, RK_AHEAD = 2;
+template <int RPW, int PB>
+__global__ __launch_bounds__(256, 1) void rank_scores(const float *__restrict__ Wr, const float *__restrict__ emb, int G,
+                                                      int d, int P, float *__restrict__ scores) {
+  constexpr int BUFS = RPW == 1 ? 2 : 1;                // one for three workgroups a unit instead of two
+  __shared__ f32x4 es[BUFS][PB][RK_PART / 4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g0 = blockIdx.x * RK_ROWS + wave * RK_RPW, p0 = blockIdx.y * RK_PB;
-  float acc[RK_RPW][RK_PB];
+  const int g0 = (blockIdx.x * 4 + wave) * RPW, p0 = blockIdx.y * PB;
+  float acc[RPW][PB];
 #pragma unroll
-  for (int r = 0; r < RK_RPW; ++r)
+  for (int r = 0; r < RPW; ++r)
 #pragma unroll
-    for (int p = 0; p < RK_PB; ++p) acc[r][p] = 0.f;
-  const float *wrow[RK_RPW], *erow[RK_PB];
+    for (int p = 0; p < PB; ++p) acc[r][p] = 0.f;
+  const float *wrow[RPW], *erow[PB];
 #pragma unroll
-  for (int r = 0; r < RK_RPW; ++r) wrow[r] = Wr + (size_t)min(g0 + r, G - 1) * d;
+  for (int r = 0; r < RPW; ++r) wrow[r] = Wr + (size_t)min(g0 + r, G - 1) * d;
 #pragma unroll
-  for (int p = 0; p < RK_PB; ++p) erow[p] = emb + (size_t)min(p0 + p, P - 1) * d;
-#pragma unroll 4
-  for (int c = lane * 4; c < d; c += 256) {
-    float4 w[RK_RPW], e[RK_PB];
+  for (int p = 0; p < PB; ++p) erow[p] = emb + (size_t)min(p0 + p, P - 1) * d;
+  f32x4 w[RK_AHEAD][RPW][RK_STEPS], e[RK_AHEAD][PB];
+  auto load = [&](int base, f32x4 (&wv)[RPW][RK_STEPS], f32x4 (&ev)[PB]) {   // columns past the end: the last four again, not used
 #pragma unroll
-    for (int r = 0; r < RK_RPW; ++r) w[r] = *reinterpret_cast<const float4 *>(wrow[r] + c);
+    for (int p = 0; p < PB; ++p) ev[p] = *reinterpret_cast<const f32x4 *>(erow[p] + min(base + (int)threadIdx.x * 4, d - 4));
 #pragma unroll
-    for (int p = 0; p < RK_PB; ++p) e[p] = *reinterpret_cast<const float4 *>(erow[p] + c);
+    for (int i = 0; i < RK_STEPS; ++i)
 #pragma unroll
-    for (int p = 0; p < RK_PB; ++p)
+      for (int r = 0; r < RPW; ++r) wv[r][i] = *reinterpret_cast<const f32x4 *>(wrow[r] + min(base + i * 256 + lane * 4, d - 4));
+  };
 #pragma unroll
-      for (int r = 0; r < RK_RPW; ++r) acc[r][p] += w[r].x * e[p].x + w[r].y * e[p].y + w[r].z * e[p].z + w[r].w * e[p].w;
+  for (int u = 0; u < RK_AHEAD; ++u)
+    if (u * RK_PART < d) load(u * RK_PART, w[u], e[u]);
+  int buf = 0;
+  for (int b0 = 0; b0 < d; b0 += RK_AHEAD * RK_PART) {
+#pragma unroll
+    for (int u = 0; u < RK_AHEAD; ++u) {
+      const int base = b0 + u * RK_PART;
+      if (base >= d) break;                            // uniform
+      if (BUFS == 1 && base > 0)                       // the part before is read
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int p = 0; p < PB; ++p) es[buf][p][threadIdx.x] = e[u][p];
+      // everybody's piece is there (of two buffers the other one is read by now).  No fence: loads on their way stay so.
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < RK_STEPS; ++i)
+        if (base + i * 256 + lane * 4 < d) {
+#pragma unroll
+          for (int p = 0; p < PB; ++p) {
+            const f32x4 v = es[buf][p][i * 64 + lane];
+#pragma unroll
+            for (int r = 0; r < RPW; ++r) {
+              const f32x4 x = w[u][r][i];
+              acc[r][p] += x[0] * v[0] + x[1] * v[1] + x[2] * v[2] + x[3] * v[3];
+            }
+          }
+        }
+      buf ^= BUFS - 1;
+      if (base + RK_AHEAD * RK_PART < d) load(base + RK_AHEAD * RK_PART, w[u], e[u]);
+    }
   }
 #pragma unroll
-  for (int r = 0; r < RK_RPW; ++r)
+  for (int r = 0; r < RPW; ++r)
 #pragma unroll
-    for (int p = 0; p < RK_PB; ++p) {
+    for (int p = 0; p < PB; ++p) {
       const float v = wave_sum(acc[r][p]);
       if (lane == 0 && g0 + r < G && p0 + p < P) scores[(size_t)(p0 + p) * G + g0 + r] = v;
     }
+}
+
+// One row a wavefront while every workgroup is at work at once (two a unit), or with so few prompts that the embeddings do not count; else two,
+// which share what they read of LDS, and one buffer, so that three workgroups fit a unit.  The whole routing call, us, the kernel before (no LDS: every
+// wavefront read the embeddings for itself, one load in flight after the other) / one row / two rows, 4096 columns: 2048 ranks x 8 prompts 30.6 / 27.6 /
+// 29.2, x 1 23.2 / 17.5 / 18.0, x 16 29.5 / 31.9 / 28.7, x 20 36.3 / 41.6 / 33.3, 512 x 8 23.3 / 17.5 / 20.5, 8192 x 8 63.0 / 60.9 / 50.0, 8192 x 1 56.7 /
+// 41.7 / 42.8; 1024 columns, 512 x 8 17.8 / 13.9 / 15.7; same bits.
+template <int PB>
+static int launch_rank_scores(const float *Wr, const float *emb, int G, int d, int P, float *scores, hipStream_t s) {
+  const int blocks = (P + PB - 1) / PB;
+  if (PB <= 2 || (long long)((G + 3) / 4) * blocks <= 512)
+    hipLaunchKernelGGL((rank_scores<1, PB>), dim3((G + 3) / 4, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+  else
+    hipLaunchKernelGGL((rank_scores<2, PB>), dim3((G + 7) / 8, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+  PARSE_LAUNCH_CHECK();
+  return PARSE_OK;
 }
 
 // order-preserving map of a float's bits: larger float <=> larger unsigned key (-0 counts as +0)
@@ -282,11 +328,11 @@ int parse_route_ranks(const void *X, int32_t xdtype, int32_t rows, const int32_t
   float *emb = emb_out ? emb_out : reinterpret_cast<float *>(ws + pool_bytes);
   float *scores = scores_out ? scores_out
                              : reinterpret_cast<float *>(ws + pool_bytes + round_up((size_t)P * d * sizeof(float), 256));
-  const int st = launch_pool(X, xdtype, rows, tok_offsets, P, d, partial, emb, s);
+  int st = launch_pool(X, xdtype, rows, tok_offsets, P, d, partial, emb, s);
   if (st != PARSE_OK) return st;
-  hipLaunchKernelGGL(rank_scores, dim3((G + RK_ROWS - 1) / RK_ROWS, (P + RK_PB - 1) / RK_PB), dim3(256), 0, s, Wr, emb, G,
-                     d, P, scores);
-  PARSE_LAUNCH_CHECK();
+  st = P == 1 ? launch_rank_scores<1>(Wr, emb, G, d, P, scores, s) : P == 2 ? launch_rank_scores<2>(Wr, emb, G, d, P, scores, s)
+       : P <= 4 ? launch_rank_scores<4>(Wr, emb, G, d, P, scores, s) : launch_rank_scores<8>(Wr, emb, G, d, P, scores, s);
+  if (st != PARSE_OK) return st;
   hipLaunchKernelGGL(rank_topk, dim3(P), dim3(1024), 0, s, scores, G, K, subset_out, subset_stride);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;

@@ -1357,6 +1357,29 @@ def test_shared_head_planned_on_the_large_tile_path():
         assert_close(yn[rows], Yo, TOL_BF16, f"prompt {p}")
 
 
+@pytest.mark.parametrize("P,d,G", [
+    (1, 264, 37), (2, 1024, 5), (3, 1032, 64), (4, 2056, 4097), (5, 3080, 1003),   # each number of prompts a workgroup takes; part of a part
+    (9, 4104, 1024), (9, 1024, 1027), (17, 2056, 1030),                             # several blocks of prompts: one and two rows a wavefront
+])
+def test_rank_scores_at_the_edges_of_their_tiles(P, d, G):
+    """Scores of the rank-granular router against the same sums in float64 over the embeddings that the call returns."""
+    say(f"rank scores: {P} prompts, {d} columns, {G} ranks")
+    gen = torch.Generator(device=DEV).manual_seed(P * 7 + d + G)
+    X = torch.randn((P * 3, d), device=DEV, generator=gen).to(torch.bfloat16)
+    off = i32(np.arange(P + 1, dtype=np.int32) * 3)
+    Wr = torch.randn((G, d), device=DEV, generator=gen)
+    buf = torch.full((P * G + 128,), 7.0, device=DEV)
+    emb, scores = torch.empty((P, d), device=DEV), buf[64:64 + P * G].view(P, G)
+    pa.route_ranks(X, off, Wr, 1, scores_out=scores, emb_out=emb)
+    torch.cuda.synchronize()
+    w, e = Wr.cpu().numpy().astype(np.float64), emb.cpu().numpy().astype(np.float64)
+    # a lane adds at most ceil(d / 256) terms of four products, then six levels over the lanes
+    bound = (4 + (d + 255) // 256 + 6) * 2.0 ** -24 * (np.abs(e) @ np.abs(w).T)
+    assert (np.abs(scores.cpu().numpy() - e @ w.T) <= bound).all()
+    b = buf.cpu().numpy()
+    assert (b[:64] == 7.0).all() and (b[64 + P * G:] == 7.0).all()
+
+
 def test_rank_granular_route_pack_and_prefill():
     """The paper's own formulation (Sec. 4.1, Eq. 4-5): one expert per rank, router R^d -> R^R, top-K ranks;
     the K scattered rank rows are aggregated into one block (Sec. 4.4) and the prefill kernels run on it."""
