@@ -504,6 +504,27 @@ def test_pack_rowmajor_bytes(dtype, n, m, R, G, subset):
     assert get(Vs).tobytes() == Vr.tobytes() and get(Us).tobytes() == Ur.tobytes()
 
 
+@pytest.mark.parametrize("n,m,gs,G,k,P", [
+    (520, 264, 8, 4, 1, 1),          # one chunk and a part of one (8 KiB chunks: 16.6 KB and 8.4 KB a group)
+    (4096, 2048, 32, 4, 2, 8),       # 256 chunks of 32 KiB: the most that are copied in 8 KiB
+    (4096, 520, 32, 4, 3, 6),        # 288: 32 KiB; groups of the two factors of unlike sizes
+])
+def test_pack_in_chunks_of_either_size(n, m, gs, G, k, P):
+    say(f"pack: {P} patterns of {k} groups of {gs} ranks, {n} x {m}")
+    gen = torch.Generator(device=DEV).manual_seed(n + m)
+    Vt, Ut = (torch.randn((G * gs, w), device=DEV, generator=gen) for w in (n, m))
+    layer = pa.Layer(Vt, Ut, n, m, G * gs, G, pa.PARSE_ROWMAJOR)
+    subs = torch.stack([torch.arange(k, dtype=torch.int32) + p % (G - k + 1) for p in range(P)]).to(DEV)
+    entry, hit = torch.arange(P, dtype=torch.int32, device=DEV).flip(0).contiguous(), torch.zeros(P, dtype=torch.uint8, device=DEV)
+    Vs, Us = (torch.full((P + 1, k * gs, w), 7.0, device=DEV) for w in (n, m))
+    pa.pack_new_entries(layer, subs, k, k, entry, hit, Vs[:P], Us[:P])
+    torch.cuda.synchronize()
+    for p in range(P):
+        for F, S, w in ((Vt, Vs, n), (Ut, Us, m)):
+            assert torch.equal(S[P - 1 - p], F.view(G, gs, w)[subs[p].long()].reshape(k * gs, w)), f"pattern {p}"
+    assert (Vs[P] == 7.0).all() and (Us[P] == 7.0).all()
+
+
 def test_reorder_and_pack_in_operand_order():
     say("offline reorder to operand order + pack of patterns, byte-exact through the documented index map")
     lay = si.small_layer(402, 512, 768, 256, 8, "bf16")
