@@ -22,12 +22,27 @@ __device__ __forceinline__ f32x4 mfma_f32_16(float a, float b, f32x4 c) { return
 template <typename F>
 __device__ __forceinline__ void for_segments(int row0, int row_end, int rows, const int32_t *__restrict__ tok_offsets,
                                              const int32_t *__restrict__ pattern_id, int P, int n_patterns, F body) {
+  // up to 64 prompts: offsets and patterns in one load each, side by side, then by lane, instead of a pattern read once its prompt is known: both
+  // products of 4 x 64 rows of a 1024 x 1024 layer, 128 ranks, 9.7 -> 9.35 us, 1024 rows of 2048 x 2048 31.6 -> 30.8 (same bits)
+  const int lane = threadIdx.x & 63;
+  int off_l = 0x7FFFFFFF, pid_l = -1;
+  if (P <= 64 && lane < P) {
+    off_l = tok_offsets[lane];
+    pid_l = pattern_id[lane];
+  }
   int seg_lo = row0;
   while (seg_lo < row_end) {
-    const int p = prompt_of_row_wave(tok_offsets, P, seg_lo);
-    int seg_hi = (p + 1 < P) ? tok_offsets[p + 1] : rows;   // the last prompt owns every remaining row
+    int p, pid, seg_hi;                                     // the last prompt owns every remaining row
+    if (P <= 64) {
+      p = max(__popcll(__ballot(off_l <= seg_lo)) - 1, 0);
+      pid = __builtin_amdgcn_readlane(pid_l, p);
+      seg_hi = p + 1 < P ? __builtin_amdgcn_readlane(off_l, p + 1) : rows;
+    } else {
+      p = prompt_of_row(tok_offsets, P, seg_lo);
+      pid = pattern_id[p];
+      seg_hi = p + 1 < P ? tok_offsets[p + 1] : rows;
+    }
     seg_hi = min(max(seg_hi, seg_lo + 1), row_end);
-    const int pid = pattern_id[p];
     body(pid >= 0 && pid < n_patterns, pid, seg_lo, seg_hi);
     seg_lo = seg_hi;
   }
