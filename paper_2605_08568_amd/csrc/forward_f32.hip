@@ -7,7 +7,7 @@
 // fetched straight into registers, several 16-deep reduction chunks at a time: lane (i = l % 16, g = l / 16) takes 16
 // bytes of its row at reduction index 4 g, and the four matrix instructions of a chunk use element e of every lane, i.e.
 // reduction indices {e, 4 + e, 8 + e, 12 + e} -- the same for both operands, so the order within a chunk does not matter.
-// Measured at that size: first product 150.7 -> 7.7 us, second 26.9 -> 4.8 us (before: 64 x 64 tiles of plain FMA through
+// Measured at that size: first product 150.7 -> 7 us, second 26.9 -> 4.3 us (before: 64 x 64 tiles of plain FMA through
 // LDS, 8 workgroups for the first product).
 //
 // Each block of token rows is cut into the segments that belong to one prompt, and a segment uses the packed factors of
@@ -202,13 +202,15 @@ __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restric
   });
 }
 
-// 32 token rows per workgroup (every factor operand fetched for twice the products) once 16-row tiles give each compute
-// unit several workgroups anyway
-constexpr int F32_MANY_WGS = 1024;
-// below it (fewer than two 16 x 16 workgroups per compute unit) the first product takes the smallest tiles: twice the units
-// at work and, for n <= 1024, every operand of a wavefront requested at once (256 tokens x 128 ranks: 7.7 us against 10.7 with
-// 16 x 32)
-constexpr int F32_FEW_WGS = 512;
+// First product, tiles: 32 x 32 once 16 x 32 ones are four a unit, 16 x 16 while those are one a unit at most (long reductions) or hardly more (short
+// ones), 16 x 32 between.  Two chunks a wavefront at a time: with four or eight the registers left room for half of the workgroups, which cover each
+// other's waits better than one's own loads do.  Both products, us, the tiles and chunks before / now: 4 x 64 rows, 1024 x 1024, 128 ranks 9.35 / 8.9; 1 x 700,
+// 2048 x 256, 100 20.7 / 16.7; 8 x 128, 2048 x 2048, 100 30.8 / 26.3 (16 x 16: 29.2); 1 x 1000, 520 x 516, 125 12.3 / 11.4; 8 x 512, 1024 x 1024, 128 43.9 / 41.7.
+constexpr int F32_MANY_WGS = 1024, F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 256, F32_LONG = 2048;
+// Second product, 32 rows a workgroup (every factor operand fetched for twice the products) once 16-row ones are four a unit, or seven where single values of
+// Z are loaded (rS not a multiple of 4).  us, 16 / 32 rows: 100 ranks, 4 x 128, 2048 x 2048 (1024 workgroups of 16 rows) 19.6 / 17.1, 8 x 128 (2048) 32.3 / 29.7; 125
+// ranks, 2 x 300, 1032 x 2048 (1216) 22.1 / 24.4, 8 x 100, 256 x 2048 (1600) 23.3 / 25.5.
+constexpr int F32_MANY_WGS_SINGLE = 1792;
 
 int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, int rows, const int32_t *tok_offsets,
                 const int32_t *pattern_id, int P, float *Y, void *workspace, hipStream_t s) {
@@ -221,12 +223,12 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
 #define PARSE_NT(RT_, CT_, B_)                                                                                             \
   hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16), dim3(FN_WAVES * 64), 0, \
                      s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
-  if ((long long)t16 * nb32 >= F32_MANY_WGS) PARSE_NT(2, 2, 4);
-  else if ((long long)t16 * nb16 >= F32_FEW_WGS) PARSE_NT(1, 2, 4);
-  else PARSE_NT(1, 1, 8);
+  if ((long long)t16 * nb32 >= F32_MANY_WGS) PARSE_NT(2, 2, 2);
+  else if ((long long)t16 * nb16 > (L->n >= F32_LONG ? F32_FEW_WGS_LONG : F32_FEW_WGS)) PARSE_NT(1, 2, 2);
+  else PARSE_NT(1, 1, 2);
 #undef PARSE_NT
   PARSE_LAUNCH_CHECK();
-  const bool many = (long long)t16 * nb2 >= F32_MANY_WGS, a4 = rS % 4 == 0;
+  const bool a4 = rS % 4 == 0, many = (long long)t16 * nb2 >= (a4 ? F32_MANY_WGS : F32_MANY_WGS_SINGLE);
 #define PARSE_NN(RT_, A4_)                                                                                                       \
   hipLaunchKernelGGL((sgemm_nn<RT_, A4_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
                      rows, L->m, rS, tok_offsets, pattern_id, P, Y)
