@@ -1,7 +1,7 @@
 // The calls of a step as functions of a CPython module (_calls): the same functions and argument order as in parse.h, without ctypes between them.
 // A step of a short prompt is eight launches of 2 us, and ctypes took as long as they do: 2-3 us to convert sixteen arguments, 1-2 us for
 // every parse_layer / parse_patterns built field by field.  Here an argument is converted by its C type:
-//   pointer          None, an integer, or an object with data_ptr() (a tensor)
+//   pointer          None or an object with data_ptr() (a tensor); an integer only for the two handles, the cache's and (last) the stream's
 //   parse_layer *, parse_patterns *    an object with the structure's fields as attributes, or a sequence of up to four
 //   void *const *    a sequence of up to four pointers
 //   int32_t, size_t  an integer (the low bits, as ctypes does);  float  a number
@@ -32,18 +32,22 @@ bool to_int(PyObject *o, int64_t *v) {
   return !(*v == -1 && PyErr_Occurred());
 }
 
+// Never an integer: a count in the place of a tensor would be read as a device address.
 bool to_pointer(PyObject *o, void **p) {
   if (o == Py_None) { *p = nullptr; return true; }
+  PyObject *r = PyObject_CallMethodNoArgs(o, s_data_ptr);
+  if (!r) return false;
   int64_t v;
-  if (PyLong_Check(o)) {
-    if (!to_int(o, &v)) return false;
-  } else {
-    PyObject *r = PyObject_CallMethodNoArgs(o, s_data_ptr);
-    if (!r) return false;
-    const bool ok = to_int(r, &v);
-    Py_DECREF(r);
-    if (!ok) return false;
-  }
+  const bool ok = to_int(r, &v);
+  Py_DECREF(r);
+  if (ok) *p = (void *)(intptr_t)v;
+  return ok;
+}
+
+bool to_handle(PyObject *o, void **p) {
+  if (o == Py_None) { *p = nullptr; return true; }
+  int64_t v;
+  if (!to_int(o, &v)) return false;
   *p = (void *)(intptr_t)v;
   return true;
 }
@@ -125,13 +129,28 @@ struct Arg<T *> {
   T *get() { return (T *)v; }
 };
 
+struct Handle {
+  void *v;
+  bool set(PyObject *o) { return to_handle(o, &v); }
+  void *get() { return v; }
+};
+template <>
+struct Arg<parse_cache *> {
+  void *v;
+  bool set(PyObject *o) { return to_handle(o, &v); }
+  parse_cache *get() { return (parse_cache *)v; }
+};
+template <size_t I, class... A>              // the last argument of every call is its stream
+using ArgOf = std::conditional_t<I + 1 == sizeof...(A), Handle, Arg<std::tuple_element_t<I, std::tuple<A...>>>>;
+
 template <auto F>
 struct Call;
 template <class... A, int (*F)(A...)>
 struct Call<F> {
   template <size_t... I>
   static PyObject *run(PyObject *const *args, std::index_sequence<I...>) {
-    std::tuple<Arg<A>...> v;
+    static_assert(std::is_same_v<std::tuple_element_t<sizeof...(A) - 1, std::tuple<A...>>, parse_stream>);
+    std::tuple<ArgOf<I, A...>...> v;
     if (!(std::get<I>(v).set(args[I]) && ...)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS

@@ -409,3 +409,42 @@ def test_module_converts_arguments_like_the_structures(monkeypatch):
     monkeypatch.setattr(B, "_stream", lambda: None)
     with pytest.raises(B.ParseError, match="-3"):                         # a width of 7: PARSE_EALIGN
         B.pool(torch.zeros(4, 7), torch.zeros(2, dtype=torch.int32), torch.zeros(1, 7), torch.zeros(8, dtype=torch.uint8))
+
+
+def test_an_integer_is_no_tensor(monkeypatch):
+    """Where a tensor belongs an integer is refused before the library is called: it would be read as a device address.  Counts stand beside
+    tensors in many calls, and one of them is a tensor in one call and a number in others (n_patterns)."""
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    i32 = lambda *shape: torch.zeros(shape, dtype=torch.int32)
+    layer = B.Layer(torch.zeros(64, 64), torch.zeros(64, 64), 64, 64, 64, 2)
+    bad = B.Layer(torch.zeros(64, 64), torch.zeros(64, 64), 64, 64, 64, 2)
+    bad.Vt = 4096
+    subs, rep, X, off = i32(4, 1), i32(4), torch.zeros(8, 64), i32(3)
+    packed = (torch.zeros(4, 32, 64), torch.zeros(4, 32, 64))
+    pats = B.Patterns(1, 1, *packed)
+    for call in (
+        lambda: B.pack_patterns(layer, subs, 1, 1, None, 4, 4),
+        lambda: B.pack_patterns(layer, subs, 1, 1, 0, None, 4),
+        lambda: B.pack_patterns(bad, subs, 1, 1, None, None, 4, *packed),
+        lambda: B.pack_new_entries(layer, subs, 1, 1, rep, 0, *packed),
+        lambda: B.bucket_patterns(subs, 1, out=(16, 32, 48, 64, 80)),
+        lambda: B.bucket_patterns(subs, 1, out=(True, False, True, True, True)),
+        lambda: B.bucket_and_plan(subs, 1, 1, 4096, rep, 8, 4, out=(rep, rep, i32(5), i32(1), rep), plan=i32(4096)),
+        lambda: B.prefill_plan(4096, rep, 8, 4, i32(4096)),
+        lambda: B.route(X, off, torch.zeros(4, 64), 2, scores_out=4096),
+        lambda: B.route(X, off, torch.zeros(4, 64), 2, emb_out=0),
+        lambda: B.route(X, off, torch.zeros(4, 64), 2, subset_out=4096, n_shared=1),
+        lambda: B.route_ranks(X, off, torch.zeros(64, 64), 2, scores_out=4096),
+        lambda: B.pool(X, off, 4096),
+        lambda: B.pack_ranks(layer, 4096, 1, 1),
+        lambda: B.lowrank_forward(B.PARSE_PREFILL, layer, B.Patterns(1, 1, 4096, 4096), X, off, i32(2)),
+        lambda: B.lowrank_forward(B.PARSE_PREFILL, layer, pats, X, off, i32(2), 4096),
+        lambda: B.lowrank_forward(B.PARSE_DECODE, layer, pats, X, np.int64(4096), i32(8)),
+        lambda: B.lowrank_prefill_planned(layer, pats, X, off, i32(2), 4096, X, X),
+        lambda: B.lowrank_prefill_multi([layer], [pats], X, off, i32(2), [4096], X),
+        lambda: B.lowrank_decode_multi([layer], [pats], X, i32(8), [4096], X),
+        lambda: B.lowrank_decode_planned([layer], X, 4096, [X], X),
+        lambda: B.router_grad(layer, 4096, X, off, X, X, torch.zeros(2, 64), torch.zeros(2, 2), 1, 1.0, 1e-6, X),
+    ):
+        with pytest.raises(AttributeError, match="data_ptr"):
+            call()
