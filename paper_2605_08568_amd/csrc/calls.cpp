@@ -2,8 +2,9 @@
 // A step of a short prompt is eight launches of 2 us, and ctypes took as long as they do: 2-3 us to convert sixteen arguments, 1-2 us for
 // every parse_layer / parse_patterns built field by field.  Here an argument is converted by its C type:
 //   pointer          None or an object with data_ptr() (a tensor); an integer only for the two handles, the cache's and (last) the stream's
-//   parse_layer *, parse_patterns *    an object with the structure's fields as attributes, or a sequence of up to four
-//   void *const *    a sequence of up to four pointers
+//   parse_layer *, parse_patterns *    an object with the structure's fields as attributes; in the calls of several layers (SEVERAL) a sequence
+//                    of up to four of them
+//   void *const *    a sequence of up to four tensors
 //   int32_t, size_t  an integer (the low bits, as ctypes does);  float  a number
 // Nothing is kept from one call for the next.  The interpreter's lock is released around the call, as ctypes does.
 #define PY_SSIZE_T_CLEAN
@@ -33,8 +34,7 @@ bool to_int(PyObject *o, int64_t *v) {
 }
 
 // Never an integer: a count in the place of a tensor would be read as a device address.
-bool to_pointer(PyObject *o, void **p) {
-  if (o == Py_None) { *p = nullptr; return true; }
+bool to_tensor(PyObject *o, void **p) {
   PyObject *r = PyObject_CallMethodNoArgs(o, s_data_ptr);
   if (!r) return false;
   int64_t v;
@@ -42,6 +42,11 @@ bool to_pointer(PyObject *o, void **p) {
   Py_DECREF(r);
   if (ok) *p = (void *)(intptr_t)v;
   return ok;
+}
+
+bool to_pointer(PyObject *o, void **p) {
+  if (o == Py_None) { *p = nullptr; return true; }
+  return to_tensor(o, p);
 }
 
 bool to_handle(PyObject *o, void **p) {
@@ -63,11 +68,11 @@ bool int_field(PyObject *o, PyObject *name, int32_t *v) {
 }
 
 template <class T>
-bool pointer_field(PyObject *o, PyObject *name, T **p) {
+bool pointer_field(PyObject *o, PyObject *name, T **p, bool (*to)(PyObject *, void **) = to_pointer) {
   PyObject *a = PyObject_GetAttr(o, name);
   if (!a) return false;
   void *v;
-  const bool ok = to_pointer(a, &v);
+  const bool ok = to(a, &v);
   Py_DECREF(a);
   *p = (T *)v;
   return ok;
@@ -75,7 +80,8 @@ bool pointer_field(PyObject *o, PyObject *name, T **p) {
 
 bool to_struct(PyObject *o, parse_layer *l) {
   return int_field(o, s_n, &l->n) && int_field(o, s_m, &l->m) && int_field(o, s_R, &l->R) && int_field(o, s_G, &l->G) && int_field(o, s_dtype, &l->dtype) &&
-         int_field(o, s_layout, &l->layout) && pointer_field(o, s_Vt, &l->Vt) && pointer_field(o, s_Ut, &l->Ut);
+         int_field(o, s_layout, &l->layout) && pointer_field(o, s_Vt, &l->Vt, to_tensor) &&
+         pointer_field(o, s_Ut, &l->Ut, to_tensor);
 }
 bool to_struct(PyObject *o, parse_patterns *p) {
   return pointer_field(o, s_Vt_S, &p->Vt_S) && pointer_field(o, s_Ut_S, &p->Ut_S) && pointer_field(o, s_subsets, &p->subsets) &&
@@ -83,33 +89,36 @@ bool to_struct(PyObject *o, parse_patterns *p) {
          pointer_field(o, s_Vt_shared, &p->Vt_shared) && pointer_field(o, s_Ut_shared, &p->Ut_shared) && int_field(o, s_n_shared, &p->n_shared) &&
          int_field(o, s_schedule, &p->schedule);
 }
-bool to_struct(PyObject *o, void **p) { return to_pointer(o, p); }
+bool to_struct(PyObject *o, void **p) { return to_tensor(o, p); }
 
 constexpr Py_ssize_t kMost = 4;              // layers of a call
 
 // One argument: what it is converted into, and what is handed to the call.  More than kMost layers reach the library as as many structures
 // as it looks at before it refuses the call.
-template <class T, class = void>
+template <class T, bool SEVERAL, class = void>
 struct Arg;
-template <class T>
-struct Arg<T, std::enable_if_t<std::is_integral_v<T>>> {
+template <class T, bool SEVERAL>
+struct Arg<T, SEVERAL, std::enable_if_t<std::is_integral_v<T>>> {
   T v;
   bool set(PyObject *o) { int64_t w; if (!to_int(o, &w)) return false; v = (T)w; return true; }
   T get() { return v; }
 };
-template <>
-struct Arg<float> {
+template <bool SEVERAL>
+struct Arg<float, SEVERAL> {
   float v;
   bool set(PyObject *o) { const double d = PyFloat_AsDouble(o); v = (float)d; return !(d == -1.0 && PyErr_Occurred()); }
   float get() { return v; }
 };
 template <class T>
+struct One {
+  T v;
+  bool set(PyObject *o) { return to_struct(o, &v); }
+  T *get() { return &v; }
+};
+template <class T>
 struct Many {
   T v[kMost] = {};                           // what a short sequence leaves out is zero, which the library refuses
-  bool none = false;
   bool set(PyObject *o) {
-    if (o == Py_None) { none = true; return true; }
-    if (!PySequence_Check(o)) return to_struct(o, &v[0]);
     PyObject *seq = PySequence_Tuple(o);       // its own: an attribute's getter may change a list
     if (!seq) return false;
     bool ok = true;
@@ -117,40 +126,39 @@ struct Many {
     Py_DECREF(seq);
     return ok;
   }
-  T *get() { return none ? nullptr : v; }
+  T *get() { return v; }
 };
-template <> struct Arg<const parse_layer *> : Many<parse_layer> {};
-template <> struct Arg<const parse_patterns *> : Many<parse_patterns> {};
-template <> struct Arg<void *const *> : Many<void *> {};
-template <class T>
-struct Arg<T *> {
+template <bool SEVERAL> struct Arg<const parse_layer *, SEVERAL> : std::conditional_t<SEVERAL, Many<parse_layer>, One<parse_layer>> {};
+template <bool SEVERAL> struct Arg<const parse_patterns *, SEVERAL> : std::conditional_t<SEVERAL, Many<parse_patterns>, One<parse_patterns>> {};
+template <> struct Arg<void *const *, true> : Many<void *> {};
+template <class T, bool SEVERAL>
+struct Arg<T *, SEVERAL> {
   void *v;
   bool set(PyObject *o) { return to_pointer(o, &v); }
   T *get() { return (T *)v; }
 };
-
 struct Handle {
   void *v;
   bool set(PyObject *o) { return to_handle(o, &v); }
   void *get() { return v; }
 };
-template <>
-struct Arg<parse_cache *> {
+template <bool SEVERAL>
+struct Arg<parse_cache *, SEVERAL> {
   void *v;
   bool set(PyObject *o) { return to_handle(o, &v); }
   parse_cache *get() { return (parse_cache *)v; }
 };
-template <size_t I, class... A>              // the last argument of every call is its stream
-using ArgOf = std::conditional_t<I + 1 == sizeof...(A), Handle, Arg<std::tuple_element_t<I, std::tuple<A...>>>>;
+template <bool SEVERAL, size_t I, class... A>              // the last argument of every call is its stream
+using ArgOf = std::conditional_t<I + 1 == sizeof...(A), Handle, Arg<std::tuple_element_t<I, std::tuple<A...>>, SEVERAL>>;
 
-template <auto F>
+template <auto F, bool SEVERAL>
 struct Call;
-template <class... A, int (*F)(A...)>
-struct Call<F> {
+template <class... A, int (*F)(A...), bool SEVERAL>
+struct Call<F, SEVERAL> {
   template <size_t... I>
   static PyObject *run(PyObject *const *args, std::index_sequence<I...>) {
     static_assert(std::is_same_v<std::tuple_element_t<sizeof...(A) - 1, std::tuple<A...>>, parse_stream>);
-    std::tuple<ArgOf<I, A...>...> v;
+    std::tuple<ArgOf<SEVERAL, I, A...>...> v;
     if (!(std::get<I>(v).set(args[I]) && ...)) return nullptr;
     int status;
     Py_BEGIN_ALLOW_THREADS
@@ -167,12 +175,14 @@ struct Call<F> {
   }
 };
 
-#define CALL(f) {#f, (PyCFunction)(void (*)(void))Call<&f>::py, METH_FASTCALL, nullptr}
+#define CALL_OF(f, several) {#f, (PyCFunction)(void (*)(void))Call<&f, several>::py, METH_FASTCALL, nullptr}
+#define CALL(f) CALL_OF(f, false)
+#define CALL_SEVERAL(f) CALL_OF(f, true)
 PyMethodDef methods[] = {
     CALL(parse_pool), CALL(parse_route), CALL(parse_route_shared), CALL(parse_route_ranks), CALL(parse_cache_lookup_or_route),
     CALL(parse_bucket_patterns), CALL(parse_bucket_and_plan), CALL(parse_prefill_plan), CALL(parse_pack_patterns), CALL(parse_pack_new_entries),
-    CALL(parse_pack_ranks), CALL(parse_lowrank_forward), CALL(parse_lowrank_prefill_planned), CALL(parse_lowrank_prefill_multi),
-    CALL(parse_lowrank_decode_planned), CALL(parse_lowrank_decode_multi), CALL(parse_router_grad),
+    CALL(parse_pack_ranks), CALL(parse_lowrank_forward), CALL(parse_lowrank_prefill_planned), CALL_SEVERAL(parse_lowrank_prefill_multi),
+    CALL_SEVERAL(parse_lowrank_decode_planned), CALL_SEVERAL(parse_lowrank_decode_multi), CALL(parse_router_grad),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

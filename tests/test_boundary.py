@@ -448,3 +448,36 @@ def test_an_integer_is_no_tensor(monkeypatch):
     ):
         with pytest.raises(AttributeError, match="data_ptr"):
             call()
+
+
+def test_one_layer_is_no_list_and_has_its_tensors(monkeypatch):
+    """A list where one layer or its patterns belong is refused, and a layer or an output without its tensor: AttributeError, before the library."""
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    f = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16)
+    i32 = lambda *shape: torch.zeros(shape, dtype=torch.int32)
+    layer, bare = (B.Layer(f(64, 64), f(64, 64), 64, 64, 64, 2, B.PARSE_MFMA16) for _ in range(2))
+    bare.Ut = None
+    Vs, Us, X, subs, pid, off, ws = f(1, 32, 64), f(1, 32, 64), f(2, 64), i32(1, 1), i32(2), torch.arange(3, dtype=torch.int32), torch.zeros(16, dtype=torch.uint8)
+    pats = B.Patterns(1, 1, Vs, Us, subs)
+    for l, p in (([layer], pats), ([], pats), (None, pats), (bare, pats), (layer, [pats]), (layer, None), (f(1, 1), pats)):
+        for call in (
+            lambda: B.lowrank_prefill_planned(l, p, X, off, pid, ws, X, ws),
+            lambda: B.lowrank_forward(B.PARSE_PREFILL, l, p, X, off, pid, X, ws),
+            lambda: B.lowrank_decode_multi([l], [p], X, pid, [X], ws),
+            lambda: B.lowrank_prefill_multi([l], [p], X, off, pid, [X], ws),
+        ):
+            with pytest.raises(AttributeError):
+                call()
+        if p is pats:
+            for call in (
+                lambda: B.pack_patterns(l, subs, 1, 1, None, None, 1, Vs, Us),
+                lambda: B.pack_new_entries(l, subs, 1, 1, i32(1), torch.ones(1, dtype=torch.uint8), Vs, Us),
+                lambda: B.pack_ranks(l, subs, 1, 1, 1, Vs, Us),
+                lambda: B.lowrank_decode_planned([l], X, ws, [X], ws),
+            ):
+                with pytest.raises(AttributeError):
+                    call()
+    for call in (lambda: B.lowrank_decode_multi([layer], [pats], X, pid, [None], ws), lambda: B.lowrank_decode_planned([layer], X, ws, [None], ws),
+                 lambda: B.lowrank_prefill_multi([layer], [pats], X, off, pid, (None,), ws)):
+        with pytest.raises(AttributeError):
+            call()
