@@ -167,11 +167,13 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _no_more(nl: int, *of_layers):
-    """A list of what the layers have holds no more than there are layers."""
-    for a in of_layers:
-        if len(a) > nl:
-            raise IndexError("invalid index")
+def _of_layers(nl: int, a):
+    """What the layers of a call have, out of any iterable (a stacked tensor: its rows), no more than there are layers."""
+    if type(a) is not list and type(a) is not tuple:
+        a = list(a)
+    if len(a) > nl:
+        raise IndexError("invalid index")
+    return a
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # not a public name: the stream object serves without it
@@ -529,9 +531,8 @@ def lowrank_decode_planned(layers, X, plan, Ys=None, workspace=None):
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
     if workspace is None:
         workspace = torch.empty(max(lowrank_decode_planned_workspace_bytes(layers), 256), dtype=torch.uint8, device=X.device)
-    _no_more(nl, Ys)
-    _check(_calls.parse_lowrank_decode_planned(layers, nl, X, rows, plan, Ys, workspace, workspace.numel(), _stream()),
-                                               "parse_lowrank_decode_planned")
+    _check(_calls.parse_lowrank_decode_planned(layers, nl, X, rows, plan, _of_layers(nl, Ys), workspace, workspace.numel(),
+                                               _stream()), "parse_lowrank_decode_planned")
     return Ys
 
 
@@ -548,9 +549,8 @@ def lowrank_decode_multi(layers, patterns, X, pattern_id, Ys=None, workspace=Non
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
     if workspace is None:
         workspace = torch.empty(max(lowrank_decode_multi_workspace_bytes(layers), 256), dtype=torch.uint8, device=X.device)
-    _no_more(nl, patterns, Ys)
-    _check(_calls.parse_lowrank_decode_multi(layers, patterns, nl, X, rows, pattern_id, Ys, workspace, workspace.numel(),
-                                             _stream()), "parse_lowrank_decode_multi")
+    _check(_calls.parse_lowrank_decode_multi(layers, _of_layers(nl, patterns), nl, X, rows, pattern_id, _of_layers(nl, Ys),
+                                             workspace, workspace.numel(), _stream()), "parse_lowrank_decode_multi")
     return Ys
 
 
@@ -567,12 +567,12 @@ def lowrank_prefill_multi(layers, patterns, X, tok_offsets, pattern_id, Ys=None,
     P = pattern_id.numel()
     if Ys is None:
         Ys = [torch.empty((rows, l.m), dtype=X.dtype, device=X.device) for l in layers]
+    patterns = _of_layers(nl, patterns)
     if workspace is None:
         need = lowrank_prefill_multi_workspace_bytes(layers, patterns, rows)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    _no_more(nl, patterns, Ys)
-    _check(_calls.parse_lowrank_prefill_multi(layers, patterns, nl, X, rows, tok_offsets, pattern_id, P, Ys, workspace,
-                                              workspace.numel(), _stream()), "parse_lowrank_prefill_multi")
+    _check(_calls.parse_lowrank_prefill_multi(layers, patterns, nl, X, rows, tok_offsets, pattern_id, P, _of_layers(nl, Ys),
+                                              workspace, workspace.numel(), _stream()), "parse_lowrank_prefill_multi")
     return Ys
 
 

@@ -3,6 +3,7 @@ declares, and rejects bad arguments with the documented status before anything i
 import ctypes as C
 import os
 import re
+from collections import deque
 
 import numpy as np
 import pytest
@@ -481,3 +482,29 @@ def test_one_layer_is_no_list_and_has_its_tensors(monkeypatch):
                  lambda: B.lowrank_prefill_multi([layer], [pats], X, off, pid, (None,), ws)):
         with pytest.raises(AttributeError):
             call()
+
+
+def test_what_the_layers_have_comes_in_any_iterable(monkeypatch):
+    """Layers with a length, patterns and outputs in whatever can be walked, a stacked tensor of outputs row by row: each form reaches the
+    library whole, which then refuses the workspace (-5), and not an argument before it (-1)."""
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    f = lambda *shape: torch.zeros(shape, dtype=torch.bfloat16)
+    layers = [B.Layer(f(64, 64), f(64, 64), 64, 64, 64, 2, B.PARSE_MFMA16) for _ in range(2)]
+    subs = torch.zeros((1, 1), dtype=torch.int32)
+    pats = [B.Patterns(1, 1, f(32, 64), f(32, 64), subs, schedule=B.PARSE_SCHED_PLANNED) for _ in range(2)]
+    X, pid, off, ws = f(2, 64), torch.zeros(2, dtype=torch.int32), torch.arange(3, dtype=torch.int32), torch.zeros(16, dtype=torch.uint8)
+    plan = torch.zeros(1 << 20, dtype=torch.uint8)
+    Ys = lambda: [f(2, 64), f(2, 64)]
+    for L, p, Y in ((layers, pats, Ys()), (tuple(layers), tuple(pats), tuple(Ys())), ({0: layers[0], 1: layers[1]}.values(), iter(pats), f(2, 2, 64)),
+                    (layers, (q for q in pats), iter(Ys())), (layers, dict(enumerate(pats)).values(), dict(enumerate(Ys())).values()),
+                    (deque(layers), deque(pats), deque(Ys()))):
+        once = isinstance(p, type(iter([]))) or hasattr(p, "send")          # walked once: a list of its own for every call
+        for call in (lambda q, y: B.lowrank_decode_multi(L, q, X, pid, y, ws),
+                     lambda q, y: B.lowrank_prefill_multi(L, q, X, off, pid, y, ws),
+                     lambda q, y: B.lowrank_decode_planned(L, X, plan, y, ws)):
+            with pytest.raises(B.ParseError) as e:
+                call(iter(pats) if once else p, iter(Ys()) if hasattr(Y, "__next__") else Y)
+            assert e.value.status == -5
+    for extra in ((iter(pats * 2), Ys()), (pats, f(3, 2, 64))):             # still no more than there are layers
+        with pytest.raises(IndexError):
+            B.lowrank_decode_multi(layers, extra[0], X, pid, extra[1], ws)
