@@ -408,7 +408,7 @@ def pack_patterns(layer: Layer, subset, subset_stride, k, rep, n_patterns, max_p
 def pack_new_entries(layer: Layer, subset, subset_stride, k, entry, hit, Vt_S, Ut_S):
     """parse_pack_new_entries: packs the subsets of this batch's new cache entries into their slots of
     Vt_S [n_slots][k*gs][n] / Ut_S [n_slots][k*gs][m]."""
-    _check(_calls.parse_pack_new_entries(layer, subset, subset_stride, k, entry.numel(), entry, hit, Vt_S.size(0), Vt_S,
+    _check(_calls.parse_pack_new_entries(layer, subset, subset_stride, k, entry.numel(), entry, hit, Vt_S.shape[0], Vt_S,
                                          Ut_S, _stream()),
            "parse_pack_new_entries")
     return Vt_S, Ut_S
@@ -458,7 +458,7 @@ def lowrank_prefill_planned_workspace_bytes(layer: Layer, rows: int, P: int, k: 
 
 def lowrank_prefill_planned(layer: Layer, patterns: Patterns, X, tok_offsets, pattern_id, plan, Y=None, workspace=None):
     """parse_lowrank_prefill_planned.  Returns Y [rows][m]."""
-    rows, P = X.size(0), pattern_id.numel()
+    rows, P = X.shape[0], pattern_id.numel()
     if Y is None:
         Y = torch.empty((rows, layer.m), dtype=X.dtype, device=X.device)
     if workspace is None:

@@ -508,3 +508,17 @@ def test_what_the_layers_have_comes_in_any_iterable(monkeypatch):
     for extra in ((iter(pats * 2), Ys()), (pats, f(3, 2, 64))):             # still no more than there are layers
         with pytest.raises(IndexError):
             B.lowrank_decode_multi(layers, extra[0], X, pid, extra[1], ws)
+
+
+def test_rows_come_from_the_shape(monkeypatch):
+    """Of X and the slots a call needs shape and data_ptr(): whatever has these serves, with size() or without."""
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    class Shaped(_Tensor):
+        shape = (2, 64)
+        def numel(self):
+            return 2
+    t, layer = Shaped(1 << 20), _module_layer()
+    with pytest.raises(B.ParseError, match="-5"):
+        B.lowrank_prefill_planned(layer, B.Patterns(1, 1, t, t), t, t, t, t, t, t)
+    with pytest.raises(B.ParseError, match="-2"):                         # k > G
+        B.pack_new_entries(layer, t, 3, 3, t, t, t, t)
