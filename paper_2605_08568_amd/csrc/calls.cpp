@@ -63,7 +63,7 @@ bool int_field(PyObject *o, PyObject *name, int32_t *v) {
   int64_t w;
   const bool ok = to_int(a, &w);
   Py_DECREF(a);
-  *v = (int32_t)w;
+  if (ok) *v = (int32_t)w;
   return ok;
 }
 
@@ -74,7 +74,7 @@ bool pointer_field(PyObject *o, PyObject *name, T **p, bool (*to)(PyObject *, vo
   void *v;
   const bool ok = to(a, &v);
   Py_DECREF(a);
-  *p = (T *)v;
+  if (ok) *p = (T *)v;
   return ok;
 }
 
