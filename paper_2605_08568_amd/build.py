@@ -1,4 +1,4 @@
-"""Builds libparse.so (the C-ABI library) from the HIP sources with hipcc for gfx950, and _calls.so (its calls for Python) with g++."""
+"""Builds libparse.so (the C-ABI library) from the HIP sources with hipcc for gfx950, and the module _calls (its calls for Python) with g++."""
 from __future__ import annotations
 
 import os
@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libparse.so")
-CALLS = os.path.join(HERE, "_calls.so")      # CPython module of the step's calls
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # CPython module of the step's calls; another Python does not take it
 SOURCES = ["api.hip", "route.hip", "cache.hip", "pack.hip", "bucket.hip", "forward_f32.hip",
            "prefill_bf16.hip", "prefill_split_bf16.hip", "prefill_lds_bf16.hip", "plan.hip", "decode_bf16.hip", "decode_wide_bf16.hip", "decode_static.hip", "forward.hip", "ranks.hip", "train.hip", "peaks.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-I" + INCLUDE, "-I" + CSRC,

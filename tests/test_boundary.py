@@ -3,6 +3,7 @@ declares, and rejects bad arguments with the documented status before anything i
 import ctypes as C
 import os
 import re
+import sysconfig
 from collections import deque
 
 import numpy as np
@@ -522,3 +523,9 @@ def test_rows_come_from_the_shape(monkeypatch):
         B.lowrank_prefill_planned(layer, B.Patterns(1, 1, t, t), t, t, t, t, t, t)
     with pytest.raises(B.ParseError, match="-2"):                         # k > G
         B.pack_new_entries(layer, t, 3, 3, t, t, t, t)
+
+
+def test_module_carries_the_name_of_its_python():
+    """The module uses the whole C API of the Python that it is built with: its file name says which, so that no other one imports it."""
+    B._calls.parse_pool                                                   # imports it
+    assert B._calls.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
