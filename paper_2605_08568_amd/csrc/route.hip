@@ -2,7 +2,7 @@
 //
 // The rows of a prompt are dealt round robin to 4 Q chains of sums (Q slices of four), the chains of a slice are added in order, then
 // the slices in order; fp32, rows streamed once, the same bits whichever kernel does it:
-//   pool_rows     a workgroup holds all chains of 16 lanes' (or 8, or 32) columns of a prompt and writes the means: one launch
+//   pool_rows     a workgroup holds all chains of 16 lanes' (or 8) columns of a prompt and writes the means: one launch
 //   pool_partial  a workgroup is one slice of 64 lanes' columns, its sums go to memory and pool_finish or route_finish adds
 //                 them: long prompts that are too few for one workgroup each to fill the chip
 //   route_finish  one block per prompt: the embedding, or its sum of the Q partials, scores the G groups (one
@@ -151,6 +151,7 @@ __global__ __launch_bounds__(kPoolRowsThreads) void pool_rows(const void *__rest
 
 constexpr int kFinishThreads = 1024;
 
+template <bool MEANS>                       // partial: the embeddings instead of Q slices' sums
 __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__restrict__ partial, int Q, int rows, int d,
                                                                const int32_t *__restrict__ tok_offsets,
                                                                const float *__restrict__ Wr, int G, int k,
@@ -164,8 +165,8 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__re
   const int a = clampi(tok_offsets[p], 0, rows);
   const int b = clampi(tok_offsets[p + 1], a, rows);
   const float inv = (b > a) ? 1.0f / (float)(b - a) : 0.f;
-  // four columns per lane, the Q slice partials added in slice order (independent loads, fixed order of adds); Q == 0: the embeddings
-  if (Q == 0) {
+  // four columns per lane, the Q slice partials added in slice order (independent loads, fixed order of adds)
+  if (MEANS) {
     for (int c = threadIdx.x * 4; c < d; c += kFinishThreads * 4)
       *reinterpret_cast<float4 *>(e + c) = *reinterpret_cast<const float4 *>(partial + (size_t)p * d + c);
   } else
@@ -213,23 +214,32 @@ static int launch_pool_partials(const void *X, bool bf16, int rows, const int32_
 }
 
 // Lanes (their log2) that a workgroup of pool_rows gives to a row, or -1 where the slices' own launch is faster.  Sixteen lanes read whole lines of a
-// row and make enough workgroups for most batches; eight where they do not, thirty-two where the prompts are long and many.  us, 8 / 16 / 32 /
-// 64 lanes, bf16, 4096 columns: 8 prompts of 512 rows 8.7 / 8.6 / 8.4 / 8.4, 20 of 20-700 12.6 / 12.4 / 12.5 / 14.0, 8 of 4096 43 / 41 / 42 / 42, one of 160
-// 3.3 / 3.6 / 4.1 / 4.1; 1024 columns, 8 of 512 4.7 / 5.6 / 5.5 / 5.6.
+// row, eight where that makes fewer workgroups than units.  A workgroup no larger than one of the slices makes as many of them per prompt: taken for up
+// to 24 rows a chain.  A larger one is taken for up to 16, all of which are on their way at once, and while all rows of the batch through its columns are
+// 1 MiB at most (0.5 below 512 columns, where the sums of the slices are next to nothing): the lengths are not known here, and a prompt that holds most of the
+// rows has an eighth to a half of the slices' workgroups.  Half of these rows a chain where rows do not start on a line of 128 bytes: the narrow pieces then take
+// in up to twice their lines.  Over 2528 batches of 1 to 64 prompts of 1 to 4096 rows, 64 to 16384 columns, as long as each other, ragged, or one with half
+// of the rows: 11 % less time than two launches on average, 8 % more at worst (always one launch: 160 % more).
 // Embeddings, us, two launches / one: 8 x 512 rows of 4096 columns 10.4 / 8.6, 20 ragged 14.6 / 12.5, one of 77 3.6 / 3.1, of 160 6.1 / 3.3, of 700 7.3 /
-// 4.7, of 2048 9.0 / 8.5, of 4096 11.8 / 12.9, of 16000 31 / 66; 1024 columns, 8 x 512 6.4 / 4.6, one of 2048 6.5 / 5.6, of 4096 8.4 / 9.7; 256 columns, 8 x 4096
-// 9.5 / 11.2; fp32, 1024 columns, 4 x 64 4.7 / 2.8, 4096 columns, one of 16000 54 / 71; one slice, 64 x 20 rows of 4096 columns 4.6 / 5.1.
-// The router's second launch comes either way, and adds the slices of few columns fast: 4096 columns, 8 x 512 15.5 / 14.6, one of 160 9.8 / 8.4, of 2048
-// 15.6 / 13.8; 1024 columns, 8 x 512 9.1 / 9.0, one of 700 9.1 / 8.4, 8 x 4096 19.9 / 21.7; 256 columns, 8 x 512 7.3 / 7.7.
+// 4.7, of 4096 11.8 / 12.9, of 16000 31 / 66; 1024 columns, 8 x 512 6.4 / 4.6, one of 4096 8.4 / 9.7; fp32, 1024 columns, 4 x 64 4.7 / 2.8; one slice, 64 x 20 rows
+// of 4096 columns 4.6 / 5.1; 19 of 80 columns and 1295 rows on average 7.7 / 5.7, one of them of 12600 12.9 / 24.8; 4488 columns, 8 x 466 9.9 / 11.8.
+// The router's second launch comes either way, and adds the slices of few columns fast (256 columns, 8 x 512 rows 7.3 / 7.7, one of 1050 7.4 / 8.5): not below 1024
+// columns, and for more than eight rows a chain only where the workgroups are half as many as units and rows start on lines.  4096 columns, 8 x 512 15.5 /
+// 14.6, one of 160 9.8 / 8.4; 1024 columns, 8 x 512 9.1 / 9.0; 1120 columns, one of 2152 9.4 / 10.9; 2 % less time on average over the same batches.
 static int pool_rows_lanes(int rows, int P, int d, bool bf16, int Q, bool router) {
   if (Q == 1) return -1;
   const int chains = Q * kPoolWaves, per = bf16 ? 8 : 4;
   const long long per_chain = rows / P / chains;       // rows
+  const bool lines = d % (per * 8) == 0;
   auto wgs = [&](int l) { return (long long)P * ((d + (per << l) - 1) / (per << l)); };
-  int l = per_chain > 16 && wgs(5) >= 512 ? 5 : (wgs(4) < 256 ? 3 : 4);
+  int l = wgs(4) < 256 ? 3 : 4;
   while ((chains << l) > kPoolRowsThreads) --l;
-  if (per_chain > 16 && wgs(l) < (per_chain > 64 ? 256 : 128)) return -1;
-  if (router && (d < 512 || (per_chain > 12 && wgs(l) < 256 && Q * d < 65536))) return -1;
+  if (chains << l <= kPoolThreads) {
+    if (per_chain > (lines ? 24 : 12)) return -1;
+  } else if (per_chain > (lines ? 16 : 8) || (long long)rows * (16 << l) > (d < 512 ? 512 : 1024) * 1024) {
+    return -1;
+  }
+  if (router && (d < 1024 || (per_chain > 8 && (wgs(l) < 128 || !lines)))) return -1;
   return l;
 }
 
@@ -307,19 +317,19 @@ int parse_route_shared(const void *X, int32_t xdtype, int32_t rows, const int32_
   hipStream_t s = (hipStream_t)stream;
   float *partial = reinterpret_cast<float *>(workspace);
   const bool bf16 = xdtype == PARSE_BF16;
-  int Q = pool_slices(rows, P, d, bf16), st;
-  const int l = pool_rows_lanes(rows, P, d, bf16, Q, true);
+  const int Q = pool_slices(rows, P, d, bf16), l = pool_rows_lanes(rows, P, d, bf16, Q, true);
+  int st;
   if (l >= 0) {              // the means, where the caller or the second launch wants them
     if (emb_out) partial = emb_out;
     st = launch_pool_rows(X, bf16, rows, tok_offsets, P, d, Q, l, partial, s);
-    Q = 0;
   } else {
     st = launch_pool_partials<false>(X, bf16, rows, tok_offsets, P, d, Q, partial, s);
   }
   if (st != PARSE_OK) return st;
   const size_t lds = (size_t)(d + 64) * sizeof(float);
-  PARSE_ALLOW_LDS(route_finish, lds);
-  hipLaunchKernelGGL(route_finish, dim3(P), dim3(kFinishThreads), lds, s, partial, Q, rows, d, tok_offsets, Wr, G, k,
+  const auto finish = l >= 0 ? route_finish<true> : route_finish<false>;
+  PARSE_ALLOW_LDS(finish, lds);
+  hipLaunchKernelGGL(finish, dim3(P), dim3(kFinishThreads), lds, s, partial, Q, rows, d, tok_offsets, Wr, G, k,
                      subset_out, subset_stride, scores_out, emb_out, n_shared);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;

@@ -121,9 +121,10 @@ def test_embeddings_of_short_prompts(dtype, d, lengths, Q):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d,lengths", [
     (264, [163]), (1032, [700]), (4104, [300, 0, 517]), (512, [257] * 9), (4096, [160] * 40), (256, [4000]), (16384, [96, 1]), (520, [2049]),
+    (1024, [330] * 63 + [1]),        # more rows of a chain than are on their way at once
 ])
 def test_embeddings_of_longer_prompts(dtype, d, lengths):
-    """One workgroup for all chains of a prompt's columns (8, 16 and 32 lanes a row, the last ones past the end of it), or slices: the
+    """One workgroup for all chains of a prompt's columns (8 and 16 lanes a row, the last ones past the end of it), or slices: the
     bits of the documented order by every entry point."""
     say(f"embeddings dtype={dtype} d={d} lengths={lengths}")
     rng = np.random.default_rng(107)
