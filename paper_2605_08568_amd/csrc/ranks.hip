@@ -118,18 +118,70 @@ __global__ __launch_bounds__(256, 1) void rank_scores(const float *__restrict__ 
     }
 }
 
+// The same sums without LDS: two rows a wavefront, which reads the eight embeddings for itself, four steps of 256 columns on their way.  Many workgroups of
+// few columns hide each other's waits better than loads ahead do, which come in parts of RK_PART and are for nothing past the last column.
+constexpr int RK_ROWS = 8, RK_PB = 8;        // router rows and prompts of a workgroup
+__global__ __launch_bounds__(256) void rank_scores_narrow(const float *__restrict__ Wr, const float *__restrict__ emb, int G,
+                                                          int d, int P, float *__restrict__ scores) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g0 = blockIdx.x * RK_ROWS + wave * 2, p0 = blockIdx.y * RK_PB;
+  float acc[2][RK_PB];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int p = 0; p < RK_PB; ++p) acc[r][p] = 0.f;
+  const float *wrow[2], *erow[RK_PB];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) wrow[r] = Wr + (size_t)min(g0 + r, G - 1) * d;
+#pragma unroll
+  for (int p = 0; p < RK_PB; ++p) erow[p] = emb + (size_t)min(p0 + p, P - 1) * d;
+#pragma unroll 4
+  for (int c = lane * 4; c < d; c += 256) {
+    f32x4 w[2], e[RK_PB];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) w[r] = *reinterpret_cast<const f32x4 *>(wrow[r] + c);
+#pragma unroll
+    for (int p = 0; p < RK_PB; ++p) e[p] = *reinterpret_cast<const f32x4 *>(erow[p] + c);
+#pragma unroll
+    for (int p = 0; p < RK_PB; ++p)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[r][p] += w[r][0] * e[p][0] + w[r][1] * e[p][1] + w[r][2] * e[p][2] + w[r][3] * e[p][3];
+  }
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int p = 0; p < RK_PB; ++p) {
+      const float v = wave_sum(acc[r][p]);
+      if (lane == 0 && g0 + r < G && p0 + p < P) scores[(size_t)(p0 + p) * G + g0 + r] = v;
+    }
+}
+
 // One row a wavefront while every workgroup is at work at once (two a unit), or with so few prompts that the embeddings do not count; else two,
-// which share what they read of LDS, and one buffer, so that three workgroups fit a unit.  The whole routing call, us, the kernel before (no LDS: every
-// wavefront read the embeddings for itself, one load in flight after the other) / one row / two rows, 4096 columns: 2048 ranks x 8 prompts 30.6 / 27.6 /
-// 29.2, x 1 23.2 / 17.5 / 18.0, x 16 29.5 / 31.9 / 28.7, x 20 36.3 / 41.6 / 33.3, 512 x 8 23.3 / 17.5 / 20.5, 8192 x 8 63.0 / 60.9 / 50.0, 8192 x 1 56.7 /
-// 41.7 / 42.8; 1024 columns, 512 x 8 17.8 / 13.9 / 15.7; same bits.
+// which share what they read of LDS, and one buffer, so that three workgroups fit a unit.  The whole routing call, us, the kernel without LDS / one row / two
+// rows, 4096 columns: 2048 ranks x 8 prompts 30.6 / 27.6 / 29.2, x 1 23.2 / 17.5 / 18.0, x 16 29.5 / 31.9 / 28.7, x 20 36.3 / 41.6 / 33.3, 512 x 8 23.3 / 17.5 /
+// 20.5, 8192 x 8 63.0 / 60.9 / 50.0, 8192 x 1 56.7 / 41.7 / 42.8; 1024 columns, 512 x 8 17.8 / 13.9 / 15.7; same bits.
+// Without LDS for more than four prompts and 1024 workgroups of one row where over a fifth of the parts' columns is past the last one: 144 columns, 3576 ranks
+// x 12 prompts 18.7 / 23.9 / 21.9, 1032, 6442 x 8 26.3 / 33.5 / 29.6, 2136, 6311 x 16 43.6 / 57.6 / 45.2; with fewer, 1480 workgroups x 4 prompts of 88 columns 20.2 /
+// 19.2 / 18.8.  Over 300 calls of 32 to 16384 columns, 32 to 8192 ranks and 1 to 64 prompts 18 % less time than without LDS throughout, 8 % more at worst.
 template <int PB>
 static int launch_rank_scores(const float *Wr, const float *emb, int G, int d, int P, float *scores, hipStream_t s) {
-  const int blocks = (P + PB - 1) / PB;
-  if (PB <= 2 || (long long)((G + 3) / 4) * blocks <= 512)
-    hipLaunchKernelGGL((rank_scores<1, PB>), dim3((G + 3) / 4, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
-  else
-    hipLaunchKernelGGL((rank_scores<2, PB>), dim3((G + 7) / 8, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+  const int blocks = (P + PB - 1) / PB, parts = (d + RK_PART - 1) / RK_PART;
+  const long long wgs = (long long)((G + 3) / 4) * blocks;
+  if constexpr (PB == RK_PB) {
+    if (wgs > 1024 && parts * RK_PART * 4 > d * 5) {
+      hipLaunchKernelGGL(rank_scores_narrow, dim3((G + RK_ROWS - 1) / RK_ROWS, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+      PARSE_LAUNCH_CHECK();
+      return PARSE_OK;
+    }
+  }
+  if constexpr (PB > 2) {
+    if (wgs > 512) {
+      hipLaunchKernelGGL((rank_scores<2, PB>), dim3((G + 7) / 8, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+      PARSE_LAUNCH_CHECK();
+      return PARSE_OK;
+    }
+  }
+  hipLaunchKernelGGL((rank_scores<1, PB>), dim3((G + 3) / 4, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

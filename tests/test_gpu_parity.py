@@ -1382,6 +1382,7 @@ def test_shared_head_planned_on_the_large_tile_path():
 @pytest.mark.parametrize("P,d,G", [
     (1, 264, 37), (2, 1024, 5), (3, 1032, 64), (4, 2056, 4097), (5, 3080, 1003),   # each number of prompts a workgroup takes; part of a part
     (9, 4104, 1024), (9, 1024, 1027), (17, 2056, 1030),                             # several blocks of prompts: one and two rows a wavefront
+    (9, 264, 2051), (13, 8, 2305), (17, 1288, 1543),                                # more than 1024 workgroups of few columns: without LDS
 ])
 def test_rank_scores_at_the_edges_of_their_tiles(P, d, G):
     """Scores of the rank-granular router against the same sums in float64 over the embeddings that the call returns."""
