@@ -30,57 +30,19 @@ constexpr int kPackWindow = 2048;   // patterns whose work list a workgroup hold
 // of 256 ranks of a bf16 4096 x 4096 layer (128) 5.25 / 4.5, of 128 of 4096 x 11008 (172) 5.2 / 4.75; of 1024 of 4096 x 4096 (1024) 8.65 / 9.7, eight 34 / 42.
 // The list is in ascending pattern order in every workgroup (a strided walk over lists that differ from
 // workgroup to workgroup would copy some tasks twice and others never).
-struct PackArgs {
-  const char *Vt, *Ut;
-  size_t v_slab, u_slab;       // bytes of a group
-  int G, k;
-  const int32_t *subset;
-  int subset_stride;
-  const int32_t *rep, *slot;
-  char *Vt_S, *Ut_S;
-};
-
-// the tasks of the listed patterns, in chunks of UNROLL pieces of 16 bytes a lane
-template <int UNROLL>
-__device__ __forceinline__ void copy_slabs(const PackArgs &a, const int32_t *act, int n_act) {
-  constexpr size_t CHUNK = (size_t)kCopyThreads * UNROLL * 16;
-  const int chunks = (int)((max(a.v_slab, a.u_slab) + CHUNK - 1) / CHUNK);
-  const long long total = (long long)n_act * 2 * a.k * chunks;
-  for (long long t = blockIdx.x; t < total; t += gridDim.x) {
-    const int c = (int)(t % chunks);
-    const int y = (int)((t / chunks) % (2 * a.k));
-    const int j = act[t / ((long long)chunks * 2 * a.k)];
-    const int row = a.rep ? a.rep[j] : j;
-    const int dst_slot = a.slot ? a.slot[j] : j;
-    const bool is_u = y >= a.k;
-    const int slot_in = is_u ? y - a.k : y;
-    const int g = a.subset[(size_t)row * a.subset_stride + slot_in];
-    if (g < 0 || g >= a.G) continue;
-    const size_t slab = is_u ? a.u_slab : a.v_slab;
-    const size_t base = (size_t)c * CHUNK;
-    if (base >= slab) continue;
-    const char *src = (is_u ? a.Ut : a.Vt) + (size_t)g * slab;
-    char *dst = (is_u ? a.Ut_S : a.Vt_S) + ((size_t)dst_slot * a.k + slot_in) * slab;
-    u32x4 v[UNROLL];
-#pragma unroll
-    for (int i = 0; i < UNROLL; ++i) {
-      const size_t o = base + ((size_t)i * kCopyThreads + threadIdx.x) * 16;
-      if (o < slab) v[i] = *reinterpret_cast<const u32x4 *>(src + o);
-    }
-#pragma unroll
-    for (int i = 0; i < UNROLL; ++i) {
-      const size_t o = base + ((size_t)i * kCopyThreads + threadIdx.x) * 16;
-      if (o < slab) __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>(dst + o));
-    }
-  }
-}
-
-__global__ __launch_bounds__(kCopyThreads) void pack_slabs(PackArgs a, const uint8_t *__restrict__ skip, int n_slots,
-                                                           const int32_t *__restrict__ n_patterns, int max_patterns) {
+__global__ __launch_bounds__(kCopyThreads) void pack_slabs(const char *__restrict__ Vt, const char *__restrict__ Ut,
+                                                           size_t v_slab_bytes, size_t u_slab_bytes, int G, int k,
+                                                           const int32_t *__restrict__ subset, int subset_stride,
+                                                           const int32_t *__restrict__ rep,
+                                                           const int32_t *__restrict__ slot,
+                                                           const uint8_t *__restrict__ skip, int n_slots,
+                                                           const int32_t *__restrict__ n_patterns, int max_patterns,
+                                                           char *__restrict__ Vt_S, char *__restrict__ Ut_S) {
   __shared__ int32_t act[kPackWindow];
   __shared__ int32_t n_act;
   __shared__ int32_t wave_cnt[kCopyThreads / 64];
   const int np = n_patterns ? min(*n_patterns, max_patterns) : max_patterns;
+  const size_t big = v_slab_bytes > u_slab_bytes ? v_slab_bytes : u_slab_bytes;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j0 = 0; j0 < np; j0 += kPackWindow) {
     if (threadIdx.x == 0) n_act = 0;
@@ -91,9 +53,9 @@ __global__ __launch_bounds__(kCopyThreads) void pack_slabs(PackArgs a, const uin
     for (int r0 = j0; r0 < wend; r0 += kCopyThreads) {
       const int j = r0 + (int)threadIdx.x;
       bool on = j < wend && !(skip && skip[j]);
-      if (on && a.rep) on = a.rep[j] >= 0;
+      if (on && rep) on = rep[j] >= 0;
       if (on) {
-        const int d = a.slot ? a.slot[j] : j;
+        const int d = slot ? slot[j] : j;
         on = d >= 0 && d < n_slots;
       }
       const unsigned long long votes = __ballot(on);
@@ -110,9 +72,41 @@ __global__ __launch_bounds__(kCopyThreads) void pack_slabs(PackArgs a, const uin
       }
       __syncthreads();
     }
-    const long long tasks = (long long)n_act * 2 * a.k * ((max(a.v_slab, a.u_slab) + kCopyChunk - 1) / kCopyChunk);
-    if (tasks <= kFewTasks) copy_slabs<kCopyUnroll / 4>(a, act, n_act);
-    else copy_slabs<kCopyUnroll>(a, act, n_act);
+    int chunks = (int)((big + kCopyChunk - 1) / kCopyChunk);
+    size_t chunk = kCopyChunk;
+    if ((long long)n_act * 2 * k * chunks <= kFewTasks) {
+      chunk = kCopyChunk / 4;
+      chunks = (int)((big + kCopyChunk / 4 - 1) / (kCopyChunk / 4));
+    }
+    const long long total = (long long)n_act * 2 * k * chunks;
+    for (long long t = blockIdx.x; t < total; t += gridDim.x) {
+      const int c = (int)(t % chunks);
+      const int y = (int)((t / chunks) % (2 * k));
+      const int j = act[t / ((long long)chunks * 2 * k)];
+      const int row = rep ? rep[j] : j;
+      const int dst_slot = slot ? slot[j] : j;
+      const bool is_u = y >= k;
+      const int slot_in = is_u ? y - k : y;
+      const int g = subset[(size_t)row * subset_stride + slot_in];
+      if (g < 0 || g >= G) continue;
+      const size_t slab = is_u ? u_slab_bytes : v_slab_bytes;
+      const size_t base = (size_t)c * chunk;
+      if (base >= slab) continue;
+      const size_t end = min(base + chunk, slab);
+      const char *src = (is_u ? Ut : Vt) + (size_t)g * slab;
+      char *dst = (is_u ? Ut_S : Vt_S) + ((size_t)dst_slot * k + slot_in) * slab;
+      u32x4 v[kCopyUnroll];
+#pragma unroll
+      for (int i = 0; i < kCopyUnroll; ++i) {
+        const size_t o = base + ((size_t)i * kCopyThreads + threadIdx.x) * 16;
+        if (o < end) v[i] = *reinterpret_cast<const u32x4 *>(src + o);
+      }
+#pragma unroll
+      for (int i = 0; i < kCopyUnroll; ++i) {
+        const size_t o = base + ((size_t)i * kCopyThreads + threadIdx.x) * 16;
+        if (o < end) __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4 *>(dst + o));
+      }
+    }
     __syncthreads();
   }
 }
@@ -159,10 +153,12 @@ static int launch_pack(const parse_layer *L, const int32_t *subset, int subset_s
   const size_t gs = L->R / L->G, es = elem_size(L->dtype);
   const size_t vb = gs * L->n * es, ub = gs * L->m * es;  // multiples of 16 (checked by check_layer)
   const size_t big = vb > ub ? vb : ub;
-  const long long tasks = (long long)((big + kCopyChunk / 4 - 1) / (kCopyChunk / 4)) * 2 * k * max_patterns;
+  long long tasks = (long long)((big + kCopyChunk - 1) / kCopyChunk) * 2 * k * max_patterns;
+  if (tasks <= kFewTasks) tasks = (long long)((big + kCopyChunk / 4 - 1) / (kCopyChunk / 4)) * 2 * k * max_patterns;
   const unsigned grid = (unsigned)(tasks < 1024 ? tasks : 1024);   // four workgroups per compute unit walk the list
-  const PackArgs a{(const char *)L->Vt, (const char *)L->Ut, vb, ub, L->G, k, subset, subset_stride, rep, slot, (char *)Vt_S, (char *)Ut_S};
-  hipLaunchKernelGGL(pack_slabs, dim3(grid), dim3(kCopyThreads), 0, s, a, skip, n_slots, n_patterns, max_patterns);
+  hipLaunchKernelGGL(pack_slabs, dim3(grid), dim3(kCopyThreads), 0, s, (const char *)L->Vt, (const char *)L->Ut, vb, ub,
+                     L->G, k, subset, subset_stride, rep, slot, skip, n_slots, n_patterns, max_patterns, (char *)Vt_S,
+                     (char *)Ut_S);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
