@@ -19,28 +19,29 @@ namespace parse {
 __device__ __forceinline__ f32x4 mfma_f32_16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // one block of token rows: calls body(valid, pattern, seg_lo, seg_hi) for every prompt segment of rows [row0, row_end)
-template <typename F>
+template <bool TABLE, typename F>
 __device__ __forceinline__ void for_segments(int row0, int row_end, int rows, const int32_t *__restrict__ tok_offsets,
                                              const int32_t *__restrict__ pattern_id, int P, int n_patterns, F body) {
-  // up to 64 prompts: offsets and patterns in one load each, side by side, then by lane, instead of a pattern read once its prompt is known: both
-  // products of 4 x 64 rows of a 1024 x 1024 layer, 128 ranks, 9.7 -> 9.35 us, 1024 rows of 2048 x 2048 31.6 -> 30.8 (same bits)
+  // TABLE, up to 64 prompts: offsets and patterns in one load each, side by side, then by lane, instead of a pattern read once its prompt is known: both
+  // products of 4 x 64 rows of a 1024 x 1024 layer, 128 ranks, 9.7 -> 9.35 us, 1024 rows of 2048 x 2048 31.6 -> 30.8 (same bits).  Not for the first product's
+  // large tiles, whose loops it makes slower: 41 prompts, 1189 rows, 3856 x 552, 588 ranks 233.5 / 250 us.
   const int lane = threadIdx.x & 63;
   int off_l = 0x7FFFFFFF, pid_l = -1;
-  if (P <= 64 && lane < P) {
+  if (TABLE && P <= 64 && lane < P) {
     off_l = tok_offsets[lane];
     pid_l = pattern_id[lane];
   }
   int seg_lo = row0;
   while (seg_lo < row_end) {
     int p, pid, seg_hi;                                     // the last prompt owns every remaining row
-    if (P <= 64) {
+    if (TABLE && P <= 64) {
       p = max(__popcll(__ballot(off_l <= seg_lo)) - 1, 0);
       pid = __builtin_amdgcn_readlane(pid_l, p);
       seg_hi = p + 1 < P ? __builtin_amdgcn_readlane(off_l, p + 1) : rows;
     } else {
-      p = prompt_of_row(tok_offsets, P, seg_lo);
-      pid = pattern_id[p];
+      p = TABLE ? prompt_of_row(tok_offsets, P, seg_lo) : prompt_of_row_wave(tok_offsets, P, seg_lo);
       seg_hi = p + 1 < P ? tok_offsets[p + 1] : rows;
+      pid = pattern_id[p];
     }
     seg_hi = min(max(seg_hi, seg_lo + 1), row_end);
     body(pid >= 0 && pid < n_patterns, pid, seg_lo, seg_hi);
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restric
   const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * TN;
   const int chunks = (K + 15) / 16;
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  for_segments(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
+  for_segments<RT == 1>(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
     f32x4 acc[RT][CT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restric
   const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * FS_TN;
   const int chunks = (K + 15) / 16;
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  for_segments(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
+  for_segments<true>(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
     f32x4 acc[RT][4];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -202,15 +203,23 @@ __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restric
   });
 }
 
-// First product, tiles: 32 x 32 once 16 x 32 ones are four a unit, 16 x 16 while those are one a unit at most (long reductions) or hardly more (short
-// ones), 16 x 32 between.  Two chunks a wavefront at a time: with four or eight the registers left room for half of the workgroups, which cover each
-// other's waits better than one's own loads do.  Both products, us, the tiles and chunks before / now: 4 x 64 rows, 1024 x 1024, 128 ranks 9.35 / 8.9; 1 x 700,
-// 2048 x 256, 100 20.7 / 16.7; 8 x 128, 2048 x 2048, 100 30.8 / 26.3 (16 x 16: 29.2); 1 x 1000, 520 x 516, 125 12.3 / 11.4; 8 x 512, 1024 x 1024, 128 43.9 / 41.7.
-constexpr int F32_MANY_WGS = 1024, F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 256, F32_LONG = 2048;
+// First product, tiles: 32 x 32 for more than 1024 columns once 16 x 32 ones are four a unit, prompts are 48 rows on average (24 where the reduction is long: every
+// prompt in a tile takes the whole tile's products) and the ranks leave no more than a sixth of the 32-rank blocks empty; 16 x 16 where they leave a sixth and
+// more, and while those tiles are few: for long reductions hardly more than one a unit (two of prompts of 150 rows on average, which share no tiles), for short ones
+// 400; else 16 x 32.  A wavefront of the small tiles takes two chunks
+// at a time: with four or eight the registers left room for half of the workgroups, which cover each other's waits better than one's own loads do;
+// the large tiles are better off with four.  Both products, us, the tiles and chunks before / now: 4 x 64 rows, 1024 x 1024, 128 ranks 9.35 / 8.9; 1 x 700, 2048 x 256,
+// 100 20.7 / 16.7; 8 x 128, 2048 x 2048, 100 30.8 / 26.3 (16 x 16: 29.2); 1 x 1000, 520 x 516, 125 12.3 / 11.4.  16 x 16 / 16 x 32 / 32 x 32: 26 prompts, 5368 rows, 2256 x
+// 492, 5 ranks 31.6 / 42.0 / 47.7; 24, 5934, 7540 x 184, 153 491 / 390 / 347; 64, 2326, 3372 x 436, 295 279 / 261 / 302; 48, 240, 6936 x 1320, 336 241 / 164 / -; 5, 450, 2824 x
+// 224, 144 29.2 / 34.0 / -.  Over 900 calls of 1 to 100 prompts, 64 to 8192 columns and 4 to 1000 ranks 7 % less time than before, 9 % more at worst, and 0.8 % off
+// the best form of each.
+constexpr int F32_LONG = 2048;                // columns
+constexpr int F32_MANY_WGS = 1024, F32_MANY_ROWS = 48, F32_MANY_ROWS_LONG = 24, F32_MANY_N = 1024;
+constexpr int F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 288, F32_FEW_WGS_LONG_PROMPTS = 512, F32_LONG_PROMPT = 150;
 // Second product, 32 rows a workgroup (every factor operand fetched for twice the products) once 16-row ones are four a unit, or seven where single values of
 // Z are loaded (rS not a multiple of 4).  us, 16 / 32 rows: 100 ranks, 4 x 128, 2048 x 2048 (1024 workgroups of 16 rows) 19.6 / 17.1, 8 x 128 (2048) 32.3 / 29.7; 125
 // ranks, 2 x 300, 1032 x 2048 (1216) 22.1 / 24.4, 8 x 100, 256 x 2048 (1600) 23.3 / 25.5.
-constexpr int F32_MANY_WGS_SINGLE = 1792;
+constexpr int F32_NN_WGS = 1024, F32_NN_WGS_SINGLE = 1792;
 
 int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, int rows, const int32_t *tok_offsets,
                 const int32_t *pattern_id, int P, float *Y, void *workspace, hipStream_t s) {
@@ -223,12 +232,15 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
 #define PARSE_NT(RT_, CT_, B_)                                                                                             \
   hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16), dim3(FN_WAVES * 64), 0, \
                      s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
-  if ((long long)t16 * nb32 >= F32_MANY_WGS) PARSE_NT(2, 2, 2);
-  else if ((long long)t16 * nb16 > (L->n >= F32_LONG ? F32_FEW_WGS_LONG : F32_FEW_WGS)) PARSE_NT(1, 2, 2);
-  else PARSE_NT(1, 1, 2);
+  const int avg = rows / P;
+  const bool long_n = L->n >= F32_LONG;
+  const int few = !long_n ? F32_FEW_WGS : (avg >= F32_LONG_PROMPT ? F32_FEW_WGS_LONG_PROMPTS : F32_FEW_WGS_LONG);
+  if (L->n > F32_MANY_N && (long long)t16 * nb32 >= F32_MANY_WGS && avg >= (long_n ? F32_MANY_ROWS_LONG : F32_MANY_ROWS) && nb32 * 10 <= nb16 * 6) PARSE_NT(2, 2, 4);
+  else if (nb32 * 10 >= nb16 * 6 || (long long)t16 * nb16 <= few) PARSE_NT(1, 1, 2);
+  else PARSE_NT(1, 2, 2);
 #undef PARSE_NT
   PARSE_LAUNCH_CHECK();
-  const bool a4 = rS % 4 == 0, many = (long long)t16 * nb2 >= (a4 ? F32_MANY_WGS : F32_MANY_WGS_SINGLE);
+  const bool a4 = rS % 4 == 0, many = (long long)t16 * nb2 >= (a4 ? F32_NN_WGS : F32_NN_WGS_SINGLE);
 #define PARSE_NN(RT_, A4_)                                                                                                       \
   hipLaunchKernelGGL((sgemm_nn<RT_, A4_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
                      rows, L->m, rS, tok_offsets, pattern_id, P, Y)

@@ -1638,10 +1638,12 @@ def test_rank_router_at_its_limits():
     (1032, 260, 250, 10, 4, [16, 17, 90]),       # n = 64.5 chunks, r_S = 100, a partial column block
     (256, 4096, 64, 4, 2, [300, 40]),            # second product with 32-row workgroups, K a multiple of 4
     (2048, 2048, 250, 10, 5, [530, 1, 200]),     # K not a multiple of 4, long reductions in the first
-    (64, 64, 2080, 4, 4, [520, 9]),              # first product with 32-row workgroups (many ranks)
+    (64, 64, 2080, 4, 4, [520, 9]),              # many ranks
+    (1028, 64, 2080, 4, 4, [520, 9]),            # first product with 32-row workgroups
     (64, 4096, 250, 10, 5, [440, 17]),           # second product with 32-row workgroups, K not a multiple of 4
-    (2048, 64, 250, 10, 5, [500, 40]),           # first product in 16 x 32 tiles: a long reduction
-    (1032, 64, 250, 10, 5, [800, 5]),            # ... a short one
+    (2048, 64, 250, 10, 5, [500, 40]),           # first product in 16 x 16 tiles: a long reduction
+    (2048, 64, 250, 10, 5, [1060, 40]),          # ... in 16 x 32 tiles
+    (1032, 64, 250, 10, 5, [800, 5]),            # ... a short reduction
 ])
 def test_prefill_fp32_edges(n, m, R, G, k, lengths):
     """fp32 layers at the edges of their tiles, against the oracle (1e-4; measured 1e-6: the products and sums are fp32)."""
