@@ -1379,6 +1379,40 @@ def test_shared_head_planned_on_the_large_tile_path():
         assert_close(yn[rows], Yo, TOL_BF16, f"prompt {p}")
 
 
+@pytest.mark.parametrize("n,m,rows", [
+    (256, 160, 77),
+    (4096, 224, 130),        # the reduction cut in slices
+    (256, 4128, 4200),       # more than 4096 rows
+])
+def test_shared_head_of_one_prompt(n, m, rows):
+    """A call that works without a plan, one shared group at the head of the pattern: the bits of the same subset packed whole, alone, with a ready
+    plan and in a call of two layers."""
+    say(f"shared head of one prompt n={n} m={m} rows={rows}")
+    gen = torch.Generator(device=DEV).manual_seed(rows)
+    G, gs, k, ns = 4, 64, 3, 1
+    R = G * gs
+    V, U = ((torch.randn(s, device=DEV, generator=gen) / s[1] ** 0.5).to(torch.bfloat16) for s in ((R, n), (R, m)))
+    dl = pa.layer_to_mfma16(pa.Layer(V, U, n, m, R, G, pa.PARSE_ROWMAJOR))
+    subs = i32(np.array([[0, 2, 3]]))
+    Vsh, Ush = pa.pack_experts(dl, subs[0, :ns])
+    own = subs[:, ns:].contiguous()
+    shared = pa.Patterns(k, 1, *pa.pack_patterns(dl, own, k - ns, k - ns, None, None, 1), Vt_shared=Vsh, Ut_shared=Ush, n_shared=ns,
+                         schedule=pa.PARSE_SCHED_PLANNED)
+    whole = pa.Patterns(k, 1, *pa.pack_patterns(dl, subs, k, k, None, None, 1), schedule=pa.PARSE_SCHED_PLANNED)
+    X = torch.randn(rows, n, device=DEV, generator=gen).to(torch.bfloat16)
+    offd, pid = i32(np.array([0, rows])), i32(np.array([0]))
+    ref = forward_guarded(pa.PARSE_PREFILL, dl, whole, X, offd, pid)
+    alone = forward_guarded(pa.PARSE_PREFILL, dl, shared, X, offd, pid)
+    ready = pa.lowrank_prefill_planned(dl, shared, X, offd, pid, pa.prefill_plan(offd, pid, rows, 1))
+    both = prefill_multi_guarded([dl, dl], [shared, whole], X, offd, pid)
+    torch.cuda.synchronize()
+    for what, y in (("alone", alone), ("ready plan", ready), ("two layers, shared", both[0]), ("two layers, whole", both[1])):
+        assert torch.equal(y.view(torch.int16), ref.view(torch.int16)), what
+    z = (X.double() @ V.double().view(G, gs, n)[subs[0].long()].reshape(k * gs, n).T)
+    want = (z @ U.double().view(G, gs, m)[subs[0].long()].reshape(k * gs, m)).cpu().numpy()
+    assert_close(ref.float().cpu().numpy().astype(np.float64), want, TOL_BF16, "against float64")
+
+
 @pytest.mark.parametrize("P,d,G", [
     (1, 264, 37), (2, 1024, 5), (3, 1032, 64), (4, 2056, 4097), (5, 3080, 1003),   # each number of prompts a workgroup takes; part of a part
     (9, 4104, 1024), (9, 1024, 1027), (17, 2056, 1030),                             # several blocks of prompts: one and two rows a wavefront
@@ -1708,8 +1742,8 @@ def test_router_grad_tiles(n, m, R, G, lengths):
     (256, [(64, 256, 8, 3)], 33),                                       # the smallest layer of this path, a panel of one sequence
     (272, [(32, 288, 3, 2), (4128, 256, 1, 1)], 64),                    # odd numbers of steps, rank and column blocks; two full panels
     (2048, [(1088, 320, 10, 2), (96, 1024, 16, 5)], 161),               # six panels, several slices of the reduction
-    (4096, [(8224, 256, 2, 1)], 130),                                   # two column blocks per workgroup, eight slices
-    (512, [(16416, 256, 4, 2), (9248, 256, 8, 8)], 200),                # three column blocks; two passes, the last panel 8 sequences
+    (4096, [(8224, 256, 2, 1)], 130),                                   # eight slices
+    (512, [(16416, 256, 4, 2), (9248, 256, 8, 8)], 200),                # two passes, the last panel 8 sequences
 ])
 def test_decode_many_sequences(n, shapes, rows):
     """More than 32 sequences in one call: every group in use streamed once for all of them.  Against the oracle, with sequences
@@ -1762,7 +1796,9 @@ def test_decode_many_sequences(n, shapes, rows):
     (256, 160, 32, 333, [0, 333], -1),
     (8192, 128, 32, 1300, [0, 1300], 0),                # four slices of 128 x 256 tiles
     (256, 4128, 64, 4200, [0, 4200], 1),                # more than 4096 rows
-    (256, 11008, 160, 10500, [0, 10500], 2),            # 256 x 256 tiles in both products
+    (256, 11008, 160, 10500, [0, 10500], 2),            # 128 x 128 tiles in the first product, 256 x 256 in the second
+    (128, 96, 1024, 4300, [0, 4300], 1),                # 256 x 256 in the first, 128 x 256 for two layers
+    (192, 96, 1152, 2990, [0, 2990], 0),                # 128 x 256 for a batch that is not cut
 ])
 def test_prefill_of_one_prompt_without_its_plan(n, m, gs, rows, off, pid):
     """A call that would make the plan of a single prompt for itself works without one: the bits of the planned call, one layer and two."""
@@ -1807,16 +1843,36 @@ def test_decode_many_sequences_slices(n, shapes, rows):
     test_decode_many_sequences(n, shapes, rows)
 
 
-@pytest.mark.parametrize("n,shapes,rows", [
-    (256, [(96, 256, 8, 3), (32, 288, 3, 2)], 192),     # few columns: every panel its own workgroup
-    (272, [(2016, 256, 4, 2)], 150),                    # 63 column blocks, five panels in twos: the middle group shares one
-    (256, [(4000, 256, 4, 2)], 129),                    # 125, five panels in threes
-    (256, [(9632, 256, 4, 2)], 190),                    # 301, three blocks x three of six panels, the last blocks past the end
-    (256, [(7136, 256, 4, 2)], 70),                     # 223 blocks, two x three panels or one x all
+def wide_y_form(rows, widths):
+    """Column blocks and panels of a workgroup of the second product, and groups of panels: the rule at its dispatch."""
+    panels, best = (rows + 31) // 32, None
+    for c in (1, 2, 3):
+        for g in range(1, panels + 1):
+            t = -(-panels // g)
+            if c * t > 15 or t * (g - 1) >= panels:
+                continue
+            cost = -(-sum(-(-(m // 32) // c) * g for m in widths) // 256) * (c + t)
+            if best is None or (cost, t) < best[0]:
+                best = (cost, t), (c, t, g)
+    return best[1]
+
+
+@pytest.mark.parametrize("n,shapes,rows,form", [
+    (256, [(96, 256, 8, 3), (32, 288, 3, 2)], 192, (1, 1, 6)),     # few columns: every panel its own workgroup
+    (272, [(2016, 256, 4, 2)], 150, (2, 1, 5)),                    # 63 column blocks in twos, the last one past the end
+    (256, [(4000, 256, 4, 2)], 129, (3, 1, 5)),                    # 125 in threes
+    (256, [(9632, 256, 4, 2)], 190, (3, 3, 2)),                    # 301, two groups of three of six panels
+    (256, [(7136, 256, 4, 2)], 70, (3, 1, 3)),
+    # groups that overlap: the panel they share is computed by both and stored once
+    (256, [(8192, 256, 4, 2)], 70, (2, 2, 2)),                     # three panels in twos
+    (272, [(9216, 256, 4, 2)], 70, (3, 2, 2)),
+    (256, [(2816, 256, 4, 2), (2816, 288, 3, 1)], 150, (3, 2, 3)), # five in twos, two layers: the last group shares one
+    (256, [(8224, 256, 4, 2)], 130, (3, 3, 2)),                    # five in threes
 ])
-def test_decode_many_sequences_panel_groups(n, shapes, rows):
+def test_decode_many_sequences_panel_groups(n, shapes, rows, form):
     """The second product's column blocks and panels per workgroup: groups of panels that overlap, units that do not fill the
     rounds of the dies, several layers."""
+    assert wide_y_form(rows, [m for m, _, _, _ in shapes]) == form
     test_decode_many_sequences(n, shapes, rows)
 
 
@@ -1845,12 +1901,13 @@ def test_decode_many_sequences_precision_of_the_first_product():
 
 
 @pytest.mark.parametrize("n,m,rS,lengths", [
-    # first product up to 4096 rows: 64 x 64, 64 x 128, 128 x 128, 128 x 256 tiles (the second one: 64 x 64, 64 x 128, 128 x 256, 128 x 128)
+    # first product up to 4096 rows: 64 x 64, 64 x 128, 128 x 128, 128 x 192, 128 x 256 tiles (the second one: 64 x 64, 64 x 128, 128 x 256, 128 x 128)
     (64, 96, 32, [1]),
     (192, 512, 256, [40, 1, 64, 90, 65]),
     (128, 1280, 768, [2048]),
     (128, 2080, 1024, [700, 1, 129, 1000, 127, 128, 900]),
     (64, 3072, 2304, [2000]),
+    (64, 64, 2304, [3000]),
     # ... beyond: 64 x 64, 64 x 128, 128 x 128, 128 x 256, 256 x 256
     (128, 96, 128, [1500, 2800, 1]),
     (192, 160, 384, [4200]),
@@ -1864,10 +1921,11 @@ def test_decode_many_sequences_precision_of_the_first_product():
     (4096, 128, 96, [77]),
     (4160, 64, 64, [3, 1, 130]),
     # the same tiles with reductions of more than twice the stages of their ring, no multiple of them: first products of up to 4096
-    # rows (64 x 64; 64 x 128, in both calls 128 x 128; 128 x 256; 128 x 128, 128 x 256 with padding left out), ...
+    # rows (64 x 64; 64 x 128, in both calls 128 x 128; 128 x 192; 128 x 256; 128 x 128, 128 x 256 with padding left out), ...
     (576, 96, 640, [70, 1]),
     (704, 512, 768, [2048]),
     (448, 256, 2304, [2000]),
+    (448, 96, 2304, [2990]),
     (640, 1280, 1024, [700, 1, 129, 1000, 127, 128, 900]),
     # ... beyond (64 x 64; 64 x 128, 128 x 128; 128 x 128, 128 x 256; 128 x 256, 256 x 256), ...
     (576, 96, 128, [1500, 2800, 1]),
