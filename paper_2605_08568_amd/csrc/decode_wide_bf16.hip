@@ -11,9 +11,10 @@
 // wavefronts take every fourth step and share nothing until their sums meet in LDS: no staging, no barrier in the loop; what
 // is in flight is DEPTH steps per wavefront (about 40 KiB; one wavefront per SIMD, so the registers are there).
 // Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
-// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns: wide_z 16 us for gate+up and 19 for down
-// (18 and 20 with operands straight into registers, and a launch of 4-6 us that brought x into operand order; 113 us a step against 118):
-// 4.7 us until the first slice is there, the factors at 4 TB/s, 1.6 us for the sums; wide_y 28 and 11 us; five panels one after the other took 313-335 us.
+// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns, 103 us a step: wide_z 17.5 us for gate+up and 21 for down,
+// 5.7 of them until the first slice is there (1 for the plan; a launch of its own for it and operands straight into registers, with one more launch that
+// brought x into operand order, came to 27-30), the factors at 4 TB/s, 1.6 for the sums; wide_zsum 4.8 each; wide_y 27 and 11 us; five panels one after the
+// other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
 
@@ -122,7 +123,7 @@ constexpr int dw_stages(int NT) { return 160 / (8 + 4 * NT) > 8 ? 8 : 160 / (8 +
 constexpr int DWZ_WAVES = 8, DWZ_THREADS = DWZ_WAVES * 64;   // two per SIMD, whose waits cover each other
 static_assert(DW_MAXP * 32 <= 256, "a thread of each 256 looks at one sequence");
 
-// The groups in use and the mask of sequences of every (panel, group), worked out by every workgroup of wide_z in LDS (DW_PREP_BYTES): 1 us of two dependent
+// The groups in use and the mask of sequences of every (panel, group), worked out by every workgroup of wide_z in LDS: 1 us of two dependent
 // loads and a vote where a launch of its own took 4-5.  The first workgroup of a layer leaves them in memory for the launches that follow.
 constexpr int DW_PREP_BYTES = (DW_MAXP + 1) * DW_MAXG * 4;
 struct DwUsed {
@@ -456,6 +457,7 @@ size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int 
 template <int NT>
 static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
   constexpr int smem = dw_stages(NT) * (8 + 4 * NT) * 1024;
+  static_assert(smem >= DW_PREP_BYTES, "the plan's lists stand where the stages do");
   static bool attr_done[64] = {false};       // the limit holds for the kernel on a device, not for a launch
   int dev = 0;
   PARSE_HIP_TRY(hipGetDevice(&dev));
@@ -477,9 +479,10 @@ static int wide_pass(DwArgs a, hipStream_t s) {
   }
   // Column blocks x panels of a wide_y workgroup: every round of workgroups takes in as many operands a step as their sum; of equals the one with
   // fewer panels, whose sums meet one after the other at the end.  All panels in each workgroup left half of the units idle where columns are few: 150
-  // sequences through 11008 -> 4096 columns, 2560 ranks, a call, us, column blocks x panels 1 x 5 37.6, 1 x 3 35.2, 2 x 5 41, 2 x 2 35.1;
-  // 1024 -> 448, 2048 ranks, 238 sequences 37.8 (1 x 4), 30.1 (1 x 2); 4096 -> 2 x 11008, 192 sequences 82 (2 x 6), 68 (3 x 3); over 80 calls of nine
-  // forms each the one taken is 0.7 % off the best on average, 11 % at worst (few ranks, where two workgroups a unit run side by side).
+  // sequences through 11008 -> 4096 columns, 2560 ranks, a call, us, column blocks x panels 1 x 5 38.5, 2 x 5 40.8 and the equals 1 x 3 35.2, 2 x 2 34.7, 3 x 1
+  // 34.3; 1024 -> 448, 2048 ranks, 238 sequences 37.8 (1 x 4), 30.1 (1 x 2); 4096 -> 2 x 11008, 192 sequences 82 (2 x 6), 68 (3 x 3), 150 sequences 46 (3 x 5),
+  // 52 (3 x 3).  Over 122 calls of up to 17 forms each the one taken is 1 % off the best on average, 10 % at worst (few ranks, where two workgroups a unit run
+  // side by side); in the 21 with equals of unlike panels the one with fewer took 2 % less.
   int cb = 1, nt = a.panels;
   long long least = 0;
   for (int c = 1; c <= 3; ++c)

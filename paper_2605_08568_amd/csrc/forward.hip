@@ -377,7 +377,7 @@ int parse_lowrank_prefill_multi(const parse_layer *layers, const parse_patterns 
                         (room || workspace_bytes >= multi_planned_bytes(layers, patterns, n_layers, rows, P, false));
   if (schedule == PARSE_SCHED_PLANNED && !can_plan) return planned_shapes ? PARSE_EWORKSPACE : PARSE_ESHAPE;
   if (can_plan && schedule != PARSE_SCHED_TILES) {
-    // planned: every layer's padded intermediate, then the plan; one plan launch, then two launches for all layers
+    // planned: every layer's padded intermediate, then the plan; one plan launch (none for a single prompt), then two launches for all layers
     const int cap = prefill_plan_capacity(rows, P, patterns[0].n_patterns);
     uint16_t *Z[4];
     for (int l = 0; l < n_layers; ++l) {
