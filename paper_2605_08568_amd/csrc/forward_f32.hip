@@ -38,8 +38,12 @@ __device__ __forceinline__ void for_segments(int row0, int row_end, int rows, co
       p = max(__popcll(__ballot(off_l <= seg_lo)) - 1, 0);
       pid = __builtin_amdgcn_readlane(pid_l, p);
       seg_hi = p + 1 < P ? __builtin_amdgcn_readlane(off_l, p + 1) : rows;
-    } else {
-      p = TABLE ? prompt_of_row(tok_offsets, P, seg_lo) : prompt_of_row_wave(tok_offsets, P, seg_lo);
+    } else if (TABLE) {
+      p = prompt_of_row(tok_offsets, P, seg_lo);
+      pid = pattern_id[p];
+      seg_hi = p + 1 < P ? tok_offsets[p + 1] : rows;
+    } else {                                                // the pattern last: the loop that follows comes out 7 % faster
+      p = prompt_of_row_wave(tok_offsets, P, seg_lo);
       seg_hi = p + 1 < P ? tok_offsets[p + 1] : rows;
       pid = pattern_id[p];
     }
@@ -203,18 +207,22 @@ __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restric
   });
 }
 
-// First product, tiles: 32 x 32 for more than 1024 columns once 16 x 32 ones are four a unit, prompts are 48 rows on average (24 where the reduction is long: every
-// prompt in a tile takes the whole tile's products) and the ranks leave no more than a sixth of the 32-rank blocks empty; 16 x 16 where they leave a sixth and
-// more, and while those tiles are few: for long reductions hardly more than one a unit (two of prompts of 150 rows on average, which share no tiles), for short ones
-// 400; else 16 x 32.  A wavefront of the small tiles takes two chunks
-// at a time: with four or eight the registers left room for half of the workgroups, which cover each other's waits better than one's own loads do;
-// the large tiles are better off with four.  Both products, us, the tiles and chunks before / now: 4 x 64 rows, 1024 x 1024, 128 ranks 9.35 / 8.9; 1 x 700, 2048 x 256,
-// 100 20.7 / 16.7; 8 x 128, 2048 x 2048, 100 30.8 / 26.3 (16 x 16: 29.2); 1 x 1000, 520 x 516, 125 12.3 / 11.4.  16 x 16 / 16 x 32 / 32 x 32: 26 prompts, 5368 rows, 2256 x
-// 492, 5 ranks 31.6 / 42.0 / 47.7; 24, 5934, 7540 x 184, 153 491 / 390 / 347; 64, 2326, 3372 x 436, 295 279 / 261 / 302; 48, 240, 6936 x 1320, 336 241 / 164 / -; 5, 450, 2824 x
-// 224, 144 29.2 / 34.0 / -.  Over 900 calls of 1 to 100 prompts, 64 to 8192 columns and 4 to 1000 ranks 7 % less time than before, 9 % more at worst, and 0.8 % off
-// the best form of each.
+// First product, tiles (T = 16 x 32 ones):
+//   32 x 32  T at least four a unit and no more than a sixth of the 32-rank blocks empty: every prompt in a tile takes the whole tile's products, so for prompts
+//            that share none (one, or of one length, a multiple of 32), from 512 columns on; for long reductions once prompts are 24 rows on average; else
+//            once they are 100 and T is seven a unit.
+//   16 x 16  a sixth and more of the 32-rank blocks empty, or few of these tiles: up to 400; for long reductions hardly more than one a unit, two where prompts of
+//            150 rows share them
+//   16 x 32  else
+// Two chunks a wavefront at a time: with four or eight the registers left room for half of the workgroups, which cover each other's waits better
+// than one's own loads do; four in the large tiles for long reductions (from 3072 columns on where prompts share none).  Both products, us, the tiles
+// and chunks before / now: 4 x 64 rows, 1024 x 1024, 128 ranks 9.35 / 8.9; 1 x 700, 2048 x 256, 100 20.7 / 16.7; 8 x 128, 2048 x 2048, 100 30.8 / 26.3 (16 x 16:
+// 29.2); 1 x 1000, 520 x 516, 125 12.3 / 11.4; 8 x 512, 1024 x 1024, 128 47.1 / 43.4.  16 x 16 / 16 x 32 / 32 x 32: 26 prompts, 5368 rows, 2256 x 492, 5 ranks
+// 31.6 / 42.0 / 47.7; 24, 5934, 7540 x 184, 153 491 / 390 / 347; 64, 2326, 3372 x 436, 295 279 / 261 / 302; 48, 240, 6936 x 1320, 336 241 / 164 / -; 5, 450, 2824 x 224,
+// 144 29.2 / 34.0 / -; 4 x 512, 1024 x 256, 256 38 / 33 / 28.5; 8, 6049, 420 x 144, 222 - / 48.1 / 47.6.  Over 1300 calls of 1 to 100 prompts, 64 to 8192 columns and 4 to
+// 2000 ranks 6 % less time than before, 3 % more in 13 of them (25 % at worst), and 1 % off the best form of each.
 constexpr int F32_LONG = 2048;                // columns
-constexpr int F32_MANY_WGS = 1024, F32_MANY_ROWS = 48, F32_MANY_ROWS_LONG = 24, F32_MANY_N = 1024;
+constexpr int F32_MANY_WGS = 1024, F32_MANY_N = 512, F32_MANY_ROWS_LONG = 24, F32_MANY_ROWS = 100, F32_MANY_WGS_SHARED = 1792, F32_FOUR_CHUNKS = 3072;
 constexpr int F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 288, F32_FEW_WGS_LONG_PROMPTS = 512, F32_LONG_PROMPT = 150;
 // Second product, 32 rows a workgroup (every factor operand fetched for twice the products) once 16-row ones are four a unit, or seven where single values of
 // Z are loaded (rS not a multiple of 4).  us, 16 / 32 rows: 100 ranks, 4 x 128, 2048 x 2048 (1024 workgroups of 16 rows) 19.6 / 17.1, 8 x 128 (2048) 32.3 / 29.7; 125
@@ -233,18 +241,22 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
   hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16), dim3(FN_WAVES * 64), 0, \
                      s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
   const int avg = rows / P;
-  const bool long_n = L->n >= F32_LONG;
-  const int few = !long_n ? F32_FEW_WGS : (avg >= F32_LONG_PROMPT ? F32_FEW_WGS_LONG_PROMPTS : F32_FEW_WGS_LONG);
-  if (L->n > F32_MANY_N && (long long)t16 * nb32 >= F32_MANY_WGS && avg >= (long_n ? F32_MANY_ROWS_LONG : F32_MANY_ROWS) && nb32 * 10 <= nb16 * 6) PARSE_NT(2, 2, 4);
+  const long long tiles = (long long)t16 * nb32;
+  const bool long_n = L->n >= F32_LONG, apart = P == 1 || (rows % P == 0 && avg % 32 == 0);
+  const int few = !long_n ? F32_FEW_WGS : (!apart && avg >= F32_LONG_PROMPT ? F32_FEW_WGS_LONG_PROMPTS : F32_FEW_WGS_LONG);
+  const bool many = nb32 * 10 <= nb16 * 6 && tiles >= F32_MANY_WGS && L->n >= F32_MANY_N &&
+                    (apart || (long_n ? avg >= F32_MANY_ROWS_LONG : avg >= F32_MANY_ROWS && tiles >= F32_MANY_WGS_SHARED));
+  if (many && L->n >= (apart ? F32_FOUR_CHUNKS : F32_LONG)) PARSE_NT(2, 2, 4);
+  else if (many) PARSE_NT(2, 2, 2);
   else if (nb32 * 10 >= nb16 * 6 || (long long)t16 * nb16 <= few) PARSE_NT(1, 1, 2);
   else PARSE_NT(1, 2, 2);
 #undef PARSE_NT
   PARSE_LAUNCH_CHECK();
-  const bool a4 = rS % 4 == 0, many = (long long)t16 * nb2 >= (a4 ? F32_NN_WGS : F32_NN_WGS_SINGLE);
+  const bool a4 = rS % 4 == 0, rows32 = (long long)t16 * nb2 >= (a4 ? F32_NN_WGS : F32_NN_WGS_SINGLE);
 #define PARSE_NN(RT_, A4_)                                                                                                       \
   hipLaunchKernelGGL((sgemm_nn<RT_, A4_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
                      rows, L->m, rS, tok_offsets, pattern_id, P, Y)
-  if (many) { if (a4) PARSE_NN(2, true); else PARSE_NN(2, false); }
+  if (rows32) { if (a4) PARSE_NN(2, true); else PARSE_NN(2, false); }
   else { if (a4) PARSE_NN(1, true); else PARSE_NN(1, false); }
 #undef PARSE_NN
   PARSE_LAUNCH_CHECK();

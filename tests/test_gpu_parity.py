@@ -1673,7 +1673,9 @@ def test_rank_router_at_its_limits():
     (256, 4096, 64, 4, 2, [300, 40]),            # second product with 32-row workgroups, K a multiple of 4
     (2048, 2048, 250, 10, 5, [530, 1, 200]),     # K not a multiple of 4, long reductions in the first
     (64, 64, 2080, 4, 4, [520, 9]),              # many ranks
-    (1028, 64, 2080, 4, 4, [520, 9]),            # first product with 32-row workgroups
+    (1028, 64, 2080, 4, 4, [520, 9]),            # first product with 32-row workgroups: many ranks
+    (516, 64, 512, 4, 4, [1024]),                # ... one prompt, two chunks at a time
+    (3076, 64, 1024, 4, 2, [64, 1000]),          # ... a long reduction, four
     (64, 4096, 250, 10, 5, [440, 17]),           # second product with 32-row workgroups, K not a multiple of 4
     (2048, 64, 250, 10, 5, [500, 40]),           # first product in 16 x 16 tiles: a long reduction
     (2048, 64, 250, 10, 5, [1060, 40]),          # ... in 16 x 32 tiles
