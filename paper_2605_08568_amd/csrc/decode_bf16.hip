@@ -69,6 +69,9 @@ struct DecPlanArgs {
   int32_t *plan;
 };
 
+// factor operands: each line is read once in the launch, so it goes past the caches (a step of 32 sequences 65.1 -> 61.7 us of kernels, of one 57.4 -> 55.5;
+// the 256-byte pieces of the 16-wide kernels were 0.5 us slower that way, and footprints that stay in the L2 lose 0.1 us a launch)
+__device__ __forceinline__ u32x4 stream_load(const void *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)); }
 __device__ __forceinline__ bf16x8 dec_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // The blocks (of 16 or 32 ranks, `per` to a group) of the groups in use, counted through: one load of the plan puts the used ids
@@ -227,7 +230,7 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
       if (g * 4 < cntAw) {                               // uniform
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii)
-          vr[g * 4 + ii] = *reinterpret_cast<const u32x4 *>(vrow + (size_t)(a0 + min(g * 4 + ii, cntAw - 1)) * 1024 + vlane);
+          vr[g * 4 + ii] = stream_load(vrow + (size_t)(a0 + min(g * 4 + ii, cntAw - 1)) * 1024 + vlane);
       } else {
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) vr[g * 4 + ii] = zero;
@@ -276,11 +279,11 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < HK; ++i)
-      vr[i] = *reinterpret_cast<const u32x4 *>(vrow + (size_t)(a0 + min(i, max(cntAw - 1, 0))) * 1024 + vlane);
+      vr[i] = stream_load(vrow + (size_t)(a0 + min(i, max(cntAw - 1, 0))) * 1024 + vlane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < HK; ++i)
-      vr[HK + i] = *reinterpret_cast<const u32x4 *>(vrow + (size_t)min(cntA + b0 + min(i, max(cntBw - 1, 0)), cnt_wg - 1) * 1024 + vlane);
+      vr[HK + i] = stream_load(vrow + (size_t)min(cntA + b0 + min(i, max(cntBw - 1, 0)), cnt_wg - 1) * 1024 + vlane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < XI; ++u) *reinterpret_cast<u32x4 *>(x_dst(nsegA, u)) = xr[u];
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
     for (int u = 0; u < DV_DEPTH; ++u) {
       if (i0 + u < nw) {                     // uniform
         const int kb = min(((wave + (i0 + u) * DV_WAVES) << 2) + ks, nkb - 1);
-        v[u] = *reinterpret_cast<const u32x4 *>(vbase + (size_t)kb * 1024);
+        v[u] = stream_load(vbase + (size_t)kb * 1024);
       }
     }
   };
@@ -531,11 +534,13 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
   if (cnt > 0) {
     u32x4 ur[DY_MAXK][NC], zr[DY_MAXK];
 #pragma unroll
+    for (int i = 0; i < DY_MAXK; ++i) zr[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb_list[k0 + min(i, cnt - 1)] * 512);
+    __builtin_amdgcn_sched_barrier(0);       // z, which is cached, ahead of the factor: loads come back in order (one column block a workgroup 9.0 -> 8.1 us)
+#pragma unroll
     for (int i = 0; i < DY_MAXK; ++i) {
       const int kb = kb_list[k0 + min(i, cnt - 1)];
 #pragma unroll
-      for (int j = 0; j < NC; ++j) ur[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
-      zr[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
+      for (int j = 0; j < NC; ++j) ur[i][j] = stream_load(ubase + (size_t)kb * ustep + coff[j]);
     }
     __builtin_amdgcn_sched_barrier(0);   // every fetch above is in flight before the first product
 #pragma unroll
@@ -551,7 +556,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
       for (int i = 0; i < DEC_CHUNK; ++i) {
         const int kb = kb_list[k0 + min(c + i, cnt - 1)];
 #pragma unroll
-        for (int j = 0; j < NC; ++j) uu[i][j] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb * ustep + coff[j]);
+        for (int j = 0; j < NC; ++j) uu[i][j] = stream_load(ubase + (size_t)kb * ustep + coff[j]);
         zz[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -653,7 +658,7 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
     for (int u = 0; u < DYV_DEPTH; ++u) {
       if (i0 + u < nw) {                     // uniform
         const int i = min(((part + (i0 + u) * PARTS) << 2) + ks, total_kb - 1);
-        v[u] = *reinterpret_cast<const u32x4 *>(ubase + (size_t)kb_list[i] * ustep);
+        v[u] = stream_load(ubase + (size_t)kb_list[i] * ustep);
       }
     }
   };
