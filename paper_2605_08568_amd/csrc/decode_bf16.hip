@@ -955,6 +955,17 @@ static bool z_16_wide(int B, int n, int wgs16) {
   return n <= 12288 && (wgs16 < 64 ? x <= 60000 : B <= 4 && x <= 50000);
 }
 
+// Factors past the caches: a call whose layers are about a fifth of the last-level cache (256 MiB) or more, since what runs between two of its kind then
+// fills the cache, and each line that it brings in drives out one of another call's.  Smaller calls may belong to a program whose factors
+// all stay in the cache, and there it costs.  us a pass, ordinary loads / past the caches, three states in turn (as in a program
+// of several blocks) and one state again and again: block of one sequence, 4096 x 11008, 54.1 / 47.7 and 45.4 / 46.0; of twelve 84.0 / 76.6 and 76.4 / 76.6; MLP of 32
+// 68.0 / 64.0 and 59.5 / 63.2; block of 32 of 1024 x 2816 (4 to 15 MB a call) 56.7 / 60.6 and 55.8 / 57.4, of 2048 x 5632 61.3 / 66.2 and 61.9 / 65.2.
+bool past_caches(const parse_layer *layers, int n_layers) {
+  size_t bytes = 0;
+  for (int l = 0; l < n_layers; ++l) bytes += (size_t)layers[l].R * ((size_t)layers[l].n + layers[l].m) * 2;
+  return bytes >= (size_t)48 << 20;
+}
+
 // n_layers layers that share x (same n); plan = n_layers consecutive layer plans; Y[l] and the z part of layer l in the
 // workspace follow the order of `layers`.
 int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const uint16_t *x, int B, int32_t *plan,

@@ -23,6 +23,7 @@
 namespace parse {
 
 bool decode_supported(const parse_layer *L);   // what a panel at a time takes
+bool past_caches(const parse_layer *layers, int n_layers);   // whether a call's factors are read past the caches
 
 constexpr int DW_MAXP = 6;                 // panels of 32 sequences a pass covers
 constexpr int DW_MAX_LAYERS = 4;
@@ -58,10 +59,11 @@ constexpr int dw_depth(int CB, int NT) { return 40 / (CB + NT) < 4 ? 4 : (40 / (
 
 // The reduction loop of both products: steps first, first + DW_WAVES, ... (cnt of them); f(step, i) / t(step, p) = address
 // of factor operand i / token operand p.
-template <int CB, int NT, class F, class T>
+template <int CB, int NT, bool PAST, class F, class T>
 __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T t) {
   constexpr int D = dw_depth(CB, NT);
   u32x4 fr[D][CB], tr[D][NT];
+  auto factor = [](const void *p) { return PAST ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)) : *reinterpret_cast<const u32x4 *>(p); };
 #pragma unroll
   for (int i = 0; i < CB; ++i)
 #pragma unroll
@@ -73,7 +75,7 @@ __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T
   for (int d = 0; d < D; ++d) {              // steps past the last re-read it (switched off below)
     const int s = min(d, cnt - 1);
 #pragma unroll
-    for (int i = 0; i < CB; ++i) fr[d][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(f(s, i)));
+    for (int i = 0; i < CB; ++i) fr[d][i] = factor(f(s, i));
 #pragma unroll
     for (int p = 0; p < NT; ++p) tr[d][p] = *reinterpret_cast<const u32x4 *>(t(s, p));
   }
@@ -89,7 +91,7 @@ __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T
           acc[i][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[d][i]), as_bf16x8(tr[d][p]), acc[i][p], 0, 0, 0);
       const int s = min(s0 + d + D, cnt - 1);
 #pragma unroll
-      for (int i = 0; i < CB; ++i) fr[d][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(f(s, i)));
+      for (int i = 0; i < CB; ++i) fr[d][i] = factor(f(s, i));
 #pragma unroll
       for (int p = 0; p < NT; ++p) tr[d][p] = *reinterpret_cast<const u32x4 *>(t(s, p));
     }
@@ -170,7 +172,7 @@ __device__ __forceinline__ DwUsed wide_used(const DwArgs &a, const DwLayer &ly, 
 // Slices of 64 reduction indices in a ring: slice kt + STAGES is requested once slice kt has been read by everybody.  A wavefront owns
 // 16 of the 64 ranks and half of the panels (the middle one of an odd number twice), so nothing is added between wavefronts.  A last slice of fewer than 64 indices re-reads the
 // last operands in their place, and both are cleared before they are multiplied (an infinite weight times zero is no number).
-template <int NT>
+template <int NT, bool PAST>
 __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
   constexpr int CB = DW_ZCB, PW = (NT + 1) / 2, TB = 2 * PW, STAGES = dw_stages(NT);
   constexpr int F_BYTES = CB * 4096, STAGE_BYTES = F_BYTES + NT * 4096;
@@ -219,13 +221,12 @@ __global__ __launch_bounds__(DWZ_THREADS, 2) void wide_z(DwArgs a) {
     xs[i] = (const char *)a.x + (size_t)min(rr, a.B - 1) * n * 2 + (size_t)kt0 * 128;  // rows past the last sequence re-read it
   }
   int issued = 0, dst = 0;
-  // load q of L of the next slice; the last one moves on.  The factor goes past the caches (aux 2), which nobody reads it from again: 19.9 -> 18.7 and 24.9 -> 23.1 us
-  // a launch of 150 sequences
+  // load q of L of the next slice; the last one moves on.  PAST: the factor past the caches (aux 2)
   auto load = [&](int q, bool steady) {
     const bool cut = !steady && ragged && issued == nk - 1;              // uniform
     if (q == 0) {
       const int over = cut ? max((kt0 + issued) * 4 + wr - (nkb - 1), 0) : 0;
-      __builtin_amdgcn_global_load_lds(PARSE_DW_GLB_PTR(V - over * 1024 + loff), PARSE_DW_LDS_PTR(smem + dst + wave * 1024), 16, 0, 2);
+      __builtin_amdgcn_global_load_lds(PARSE_DW_GLB_PTR(V - over * 1024 + loff), PARSE_DW_LDS_PTR(smem + dst + wave * 1024), 16, 0, PAST ? 2 : 0);
     } else {
       const int i = q - 1;
       const int c = cut ? min(chunk[i], n / 8 - 1 - (kt0 + issued) * 8) : chunk[i];
@@ -363,7 +364,7 @@ __global__ __launch_bounds__(DW_THREADS) void wide_zsum(DwArgs a) {
 // grid: layers x groups of NT panels x column blocks in units of CB (their number rounded up to whole rounds of the dies, so that the groups of one
 // column block run on one die and its factor comes from memory once).  The last group of panels ends with the last panel: the ones it shares with the
 // group before are computed by both and stored once.
-template <int CB, int NT>
+template <int CB, int NT, bool PAST>
 __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
   int li = 0;
 #pragma unroll
@@ -386,7 +387,7 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
   for (int i = 0; i < CB; ++i) cb[i] = min(c0 + i, ncb - 1);       // blocks past the end re-read the last one (not stored)
   const size_t zstep = (size_t)(ly.R / 16);
   f32x16 acc[CB][NT];
-  wide_loop<CB, NT>(acc, (total - wave + DW_WAVES - 1) / DW_WAVES,
+  wide_loop<CB, NT, PAST>(acc, (total - wave + DW_WAVES - 1) / DW_WAVES,
                     [&](int s, int i) { return U + ((size_t)kb_list[wave + s * DW_WAVES] * ncb + cb[i]) * 1024; },
                     [&](int s, int p) { return Z + (p * zstep + kb_list[wave + s * DW_WAVES]) * 1024; });
 #pragma unroll
@@ -456,7 +457,7 @@ size_t decode_wide_workspace_bytes(const parse_layer *layers, int n_layers, int 
   return wide_bytes(layers, n_layers, (size_t)std::min(panels_of(rows), DW_MAXP));
 }
 
-template <int NT>
+template <int NT, bool PAST>
 static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
   constexpr int smem = dw_stages(NT) * (8 + 4 * NT) * 1024;
   static_assert(smem >= DW_PREP_BYTES, "the plan's lists stand where the stages do");
@@ -465,15 +466,15 @@ static int launch_wide_z(const DwArgs &a, int wgs, hipStream_t s) {
   PARSE_HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return PARSE_EINVAL;
   if (!attr_done[dev]) {
-    PARSE_HIP_TRY(hipFuncSetAttribute((const void *)wide_z<NT>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    PARSE_HIP_TRY(hipFuncSetAttribute((const void *)wide_z<NT, PAST>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     attr_done[dev] = true;
   }
-  hipLaunchKernelGGL(wide_z<NT>, dim3(wgs), dim3(DWZ_THREADS), smem, s, a);
+  hipLaunchKernelGGL((wide_z<NT, PAST>), dim3(wgs), dim3(DWZ_THREADS), smem, s, a);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
 
-static int wide_pass(DwArgs a, hipStream_t s) {
+static int wide_pass(DwArgs a, bool past, hipStream_t s) {
   int st, zw = 0, sw = 0;
   for (int l = 0; l < a.n_layers; ++l) {
     a.L[l].z_first = zw; zw += (a.L[l].R / 32 + DW_ZCB - 1) / DW_ZCB * a.KS;
@@ -502,7 +503,7 @@ static int wide_pass(DwArgs a, hipStream_t s) {
     a.L[l].y_first = yw;
     yw += (a.groups > 1 ? (units + 7) / 8 * 8 : units) * a.groups;
   }
-#define PARSE_DWZ(NT_) case NT_: st = launch_wide_z<NT_>(a, zw, s); break
+#define PARSE_DWZ(NT_) case NT_: st = past ? launch_wide_z<NT_, true>(a, zw, s) : launch_wide_z<NT_, false>(a, zw, s); break
   switch (a.panels) {
     PARSE_DWZ(1); PARSE_DWZ(2); PARSE_DWZ(3); PARSE_DWZ(4); PARSE_DWZ(5); PARSE_DWZ(6);
     default: return PARSE_ESHAPE;
@@ -513,17 +514,24 @@ static int wide_pass(DwArgs a, hipStream_t s) {
     hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a);
     PARSE_LAUNCH_CHECK();
   }
-#define PARSE_DWY(NT_)                                                                             \
-  case NT_:                                                                                        \
-    if (cb == 1) hipLaunchKernelGGL((wide_y<1, NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a);        \
-    else if (cb == 2) hipLaunchKernelGGL((wide_y<2, NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a);   \
-    else hipLaunchKernelGGL((wide_y<(NT_ < 6 ? 3 : 2), NT_>), dim3(yw), dim3(DW_THREADS), 0, s, a); \
+  // Past the caches only where one group of panels reads a column block: several share what the first one brings into the die's L2.  MLP of 150 sequences, factors
+  // of both products with ordinary loads 104.9 us a step, of the first past the caches 102.5, of the second too where one group reads them 97.3, everywhere 100.6.
+  past = past && a.groups == 1;
+#define PARSE_DWY2(CB_, NT_)                                                                                     \
+  do {                                                                                                           \
+    if (past) hipLaunchKernelGGL((wide_y<CB_, NT_, true>), dim3(yw), dim3(DW_THREADS), 0, s, a);                 \
+    else hipLaunchKernelGGL((wide_y<CB_, NT_, false>), dim3(yw), dim3(DW_THREADS), 0, s, a);                     \
+  } while (0)
+#define PARSE_DWY(NT_)                                                                                           \
+  case NT_:                                                                                                      \
+    if (cb == 1) PARSE_DWY2(1, NT_); else if (cb == 2) PARSE_DWY2(2, NT_); else PARSE_DWY2((NT_ < 6 ? 3 : 2), NT_); \
     break
   switch (nt) {
     PARSE_DWY(1); PARSE_DWY(2); PARSE_DWY(3); PARSE_DWY(4); PARSE_DWY(5); PARSE_DWY(6);
     default: return PARSE_ESHAPE;
   }
 #undef PARSE_DWY
+#undef PARSE_DWY2
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
@@ -557,7 +565,7 @@ int forward_decode_wide_bf16(const parse_layer *layers, const parse_patterns *pt
     a.x = x + (size_t)r0 * a.n;
     a.pattern_id = pattern_id + r0;
     for (int l = 0; l < n_layers; ++l) a.L[l].y = (uint16_t *)Y[l] + (size_t)r0 * a.L[l].m;
-    const int st = wide_pass(a, s);
+    const int st = wide_pass(a, past_caches(layers, n_layers), s);
     if (st != PARSE_OK) return st;
   }
   return PARSE_OK;
