@@ -267,10 +267,10 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *layer, int
  *                layer->Ut, not the packed copies) and applies it to the sequences whose pattern holds it (Sec. 4.3, rank
  *                reuse: pattern_id is fixed at prefill): once for up to 192 sequences when the workspace has the queried
  *                size, once per panel of 32 sequences (the N side of the matrix instruction) with the workspace of a single
- *                panel.  Bandwidth-bound.  The kernels are chosen by the number of sequences (vector units for one and some
- *                calls of two to four, 16-wide matrix instructions up to sixteen, 32-wide beyond, several panels at once
- *                above 32; same rounding points everywhere: z and y to bf16, fp32 sums), so a sequence's result may differ in
- *                rounding between a small and a large call.
+ *                panel.  Bandwidth-bound.  The kernels are chosen by the number of sequences (16-wide matrix instructions up to
+ *                sixteen where x fits the LDS, the vector units in the second product for one and some calls of two to four,
+ *                32-wide beyond, several panels at once above 32; same rounding points everywhere: z and y to bf16, fp32 sums), so
+ *                a sequence's result may differ in rounding between a small and a large call.
  * workspace: device, >= parse_lowrank_workspace_bytes(mode, layer, rows, k, P, n_patterns) bytes (optional for
  *            bf16 prefill).  For PARSE_DECODE the answer for N rows covers every call of up to N rows. */
 int parse_lowrank_forward(int32_t mode, const parse_layer *layer, const parse_patterns *patterns,

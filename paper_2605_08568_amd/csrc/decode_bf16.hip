@@ -19,9 +19,11 @@
 //   decode_y   NC (1..4) 32-column output blocks per workgroup; the eight wavefronts split the used reduction blocks,
 //              all Ut operands requested up front; LDS reduction in wavefront order.
 // Up to sixteen sequences leave half or more of the 32-wide N side empty and take other kernels with a finer split of the
-// work: decode_z16 / decode_y16 (16 x 16 x 32 matrix instructions, sixteen ranks or columns per workgroup), and one to four
-// sequences with little to do decode_zv / decode_yv on the vector units (eight ranks, sixteen or thirty-two columns).  More than
-// 32 sequences: decode_wide_bf16.hip.
+// work: decode_zv / decode_zp (eight ranks a task on the 16 x 16 x 32 matrix instruction) while x fits the LDS, decode_y16 (sixteen columns), and one to
+// four sequences with little to do decode_yv on the vector units (sixteen or thirty-two columns).  More than 32 sequences: decode_wide_bf16.hip.
+// What bounds all of them: HBM, and what a compute unit takes in.  A unit has at most 32 KiB outstanding and gets it back in order, 57 GB/s of a mixture of
+// cached and uncached lines, so every byte of x or z that a workgroup reads again counts like one of the factor; a launch costs 1.9 us, and the plan, the first
+// loads and the sums about 4 more.
 // Horizontal fusion (Sec. 4.4, Eq. 11-12): up to DEC_MAX_LAYERS layers that read the SAME x (Q/K/V, gate/up) go
 // through the same two launches together -- each launch's grid is the concatenation of the layers' task lists.
 // No floating-point atomics; the summation order is fixed: same inputs, same bits.
@@ -69,9 +71,12 @@ struct DecPlanArgs {
   int32_t *plan;
 };
 
-// factor operands: each line is read once in the launch, so it goes past the caches (a step of 32 sequences 65.1 -> 61.7 us of kernels, of one 57.4 -> 55.5;
-// the 256-byte pieces of the 16-wide kernels were 0.5 us slower that way, and footprints that stay in the L2 lose 0.1 us a launch)
-__device__ __forceinline__ u32x4 stream_load(const void *p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)); }
+// Factor operands: each line is read once in the launch.  NT: past the caches (which calls, is decided where the kernels are launched).
+template <bool NT>
+__device__ __forceinline__ u32x4 stream_load(const void *p) {
+  const u32x4 *q = reinterpret_cast<const u32x4 *>(p);
+  return NT ? __builtin_nontemporal_load(q) : *q;
+}
 __device__ __forceinline__ bf16x8 dec_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // The blocks (of 16 or 32 ranks, `per` to a group) of the groups in use, counted through: one load of the plan puts the used ids
@@ -91,6 +96,33 @@ struct DecUsed {
     return max(__builtin_amdgcn_readlane(ids, g), 0) * per + i - g * per;
   }
 };
+
+// A workgroup's task in a first product: 2^shift ranks of a group in use.  The layers take turns and each one's tasks are counted through over its groups in
+// use, so that the workgroups without one are the last of the grid: up to one task a compute unit is then one task a unit (numbered over all groups some
+// units got two and some none: 11008 -> 4096 columns, one sequence, four ranks a workgroup, 11.0 us, 8.5 this way).
+struct DecTask {
+  int layer, unit;             // unit < 0: none
+  uint32_t mask;               // sequences whose pattern holds the unit's group
+};
+__device__ __forceinline__ int dec_layer_of(const DecArgs &a, int bid, int &at) {
+  at = a.n_layers == 1 ? bid : a.n_layers == 2 ? bid >> 1 : a.n_layers == 4 ? bid >> 2 : bid / 3;
+  return bid - at * a.n_layers;
+}
+// ids and masks: the plan's words of the lane
+__device__ __forceinline__ DecTask dec_task(const DecLayer &ly, int used, int ids, int masks, int li, int at, int shift) {
+  const int per = ly.gs >> shift, count = max(0, min(used, ly.G)) * per;
+  // exact: at / per < 64, and (at + 1/2) / per is at least 1/4096 off every integer
+  const int g = min(__builtin_amdgcn_readfirstlane((int)(((float)at + 0.5f) * (1.0f / (float)per))), DEC_MAXG - 1);
+  const int id = min(max(__builtin_amdgcn_readlane(ids, g), 0), ly.G - 1);
+  return DecTask{li, at < count ? id * per + at - g * per : -1, (uint32_t)__builtin_amdgcn_readlane(masks, id)};
+}
+
+// a barrier without the usual one's fence, which waits for every outstanding load: what this wavefront wrote to LDS is there
+__device__ __forceinline__ void dec_lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // grid = layers, one wavefront each: lane b < B looks at its sequence's k group ids and ORs its bit into the groups'
 // masks (LDS, integer OR: order-free); then the used groups are listed in ascending order by a vote.
@@ -167,7 +199,9 @@ __device__ __forceinline__ void dec_store_z_operands(const float (&s)[16], uint3
   }
 }
 
-template <bool TWO>
+// ROWS: 32, or 16 where no more sequences are there: half of x's loads, 15.6 -> 14.5 us for twelve sequences of 11008 columns, 2048 ranks (the upper rows of the
+// staged segments are then whatever was there, and so are the sums of sequences that nobody stores)
+template <bool TWO, int ROWS, bool NT>
 __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
   constexpr int HK = DR_MAXK / 2;            // TWO: operands per half and wavefront
   int li = 0;
@@ -201,10 +235,10 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
   // segment; pieces past the end of the row re-read its last one (their products are switched off below)
   auto stage_x = [&](int s0, int ns) {
 #pragma unroll
-    for (int u = 0; u < DR_MAXSEG * 16 / DR_WAVES; ++u) {
-      const int t = wave + u * DR_WAVES;                 // instruction id: segment t / 16, row pair t % 16
-      if (t < ns * 16) {                                 // uniform
-        const int seg = t >> 4, ins = t & 15;
+    for (int u = 0; u < DR_MAXSEG * ROWS / 2 / DR_WAVES; ++u) {
+      const int t = wave + u * DR_WAVES;                 // instruction id: segment, row pair
+      if (t < ns * (ROWS / 2)) {                         // uniform
+        const int seg = t / (ROWS / 2), ins = t % (ROWS / 2);
         const int r = ins * 2 + (lane >> 5);
         const int piece = min(ks0 * 2 + (s0 + seg) * 32 + ((lane & 31) ^ (r & 15)), last_piece);
         __builtin_amdgcn_global_load_lds(PARSE_DEC_GLB_PTR((const char *)a.x + (size_t)min(r, B - 1) * n * 2 + (size_t)piece * 16),
@@ -230,7 +264,7 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
       if (g * 4 < cntAw) {                               // uniform
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii)
-          vr[g * 4 + ii] = stream_load(vrow + (size_t)(a0 + min(g * 4 + ii, cntAw - 1)) * 1024 + vlane);
+          vr[g * 4 + ii] = stream_load<NT>(vrow + (size_t)(a0 + min(g * 4 + ii, cntAw - 1)) * 1024 + vlane);
       } else {
 #pragma unroll
         for (int ii = 0; ii < 4; ++ii) vr[g * 4 + ii] = zero;
@@ -256,17 +290,17 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
     // the operands of part B are still in flight (it does not do that across loads that write LDS directly).  Every
     // wavefront issues the same number of loads whatever the counts are -- instructions past the end repeat the last
     // one (same data to the same place) -- first half of x, operands of part A, operands of part B ----
-    constexpr int XI = DR_MAXSEG * 16 / DR_WAVES;        // x instructions per wavefront and half
+    constexpr int XI = DR_MAXSEG * 16 / DR_WAVES * ROWS / 32;        // x instructions per wavefront and half
     auto x_src = [&](int s0, int ns, int u) -> const char * {
-      const int t = min(wave + u * DR_WAVES, ns * 16 - 1);
-      const int seg = t >> 4, ins = t & 15;
+      const int t = min(wave + u * DR_WAVES, ns * (ROWS / 2) - 1);
+      const int seg = t / (ROWS / 2), ins = t % (ROWS / 2);
       const int r = ins * 2 + (lane >> 5);
       const int piece = min(ks0 * 2 + (s0 + seg) * 32 + ((lane & 31) ^ (r & 15)), last_piece);
       return (const char *)a.x + (size_t)min(r, B - 1) * n * 2 + (size_t)piece * 16;
     };
     auto x_dst = [&](int ns, int u) -> char * {          // wave-uniform slot + the lane's 16 bytes
-      const int t = min(wave + u * DR_WAVES, ns * 16 - 1);
-      return xs + (t >> 4) * DR_SEG_BYTES + (t & 15) * 1024 + lane * 16;
+      const int t = min(wave + u * DR_WAVES, ns * (ROWS / 2) - 1);
+      return xs + t / (ROWS / 2) * DR_SEG_BYTES + t % (ROWS / 2) * 1024 + lane * 16;
     };
     auto bare_barrier = [&]() {     // the usual barrier comes with a fence that waits for every outstanding load
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -279,11 +313,11 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < HK; ++i)
-      vr[i] = stream_load(vrow + (size_t)(a0 + min(i, max(cntAw - 1, 0))) * 1024 + vlane);
+      vr[i] = stream_load<NT>(vrow + (size_t)(a0 + min(i, max(cntAw - 1, 0))) * 1024 + vlane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < HK; ++i)
-      vr[HK + i] = stream_load(vrow + (size_t)min(cntA + b0 + min(i, max(cntBw - 1, 0)), cnt_wg - 1) * 1024 + vlane);
+      vr[HK + i] = stream_load<NT>(vrow + (size_t)min(cntA + b0 + min(i, max(cntBw - 1, 0)), cnt_wg - 1) * 1024 + vlane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < XI; ++u) *reinterpret_cast<u32x4 *>(x_dst(nsegA, u)) = xr[u];
@@ -374,111 +408,230 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_zv: z for a handful of sequences (B <= 4; which calls of two to four come here is decided where the kernels are launched),
-// on the vector units.  With one to four sequences the 32-wide N side of the matrix instruction is almost empty and, worse, a
+// decode_zv: z for a handful of sequences (B <= 4; which calls of two to four come here is decided where the kernels are launched).
+// With one to four sequences the 32-wide N side of the matrix instruction is almost empty and, worse, a
 // 32-rank block per workgroup leaves most compute units without work (one sequence selects k groups: a 4096x4096 layer with 8 groups of 96 ranks has 24 blocks for 256 units).  Here a
-// workgroup owns EIGHT ranks of a block over the whole reduction range: in the operand order the 16-byte pieces of 8
+// task is EIGHT ranks of a block (or four: JW) over the whole reduction range: in the operand order the 16-byte pieces of 8
 // consecutive ranks are 128 contiguous bytes, so a wavefront instruction reads 8 such lines (4 reduction steps x 2
-// halves), every line exactly once in the launch.  Lane (step s of 4, half q, rank j of 8) multiplies its 8 factor values
-// with the matching 8 values of each sequence's x row (all of x sits in LDS) and keeps one fp32 sum per sequence; the 8
-// lanes of a rank are added by a butterfly, the eight wavefronts through LDS in wavefront order.  No partial sums leave
-// the workgroup.  The result is masked, rounded and stored exactly like decode_zr's (one 16-byte piece per sequence).
+// halves), every line exactly once in the launch.  The 16 x 16 x 32 matrix instruction multiplies them: its sixteen rows are the
+// task's ranks in 16 / JW parts of the reduction range, its sixteen columns the sequences (all of x sits in LDS) in the same parts, and what row and
+// column of one part make is of use.  On the vector units, 36 instructions a load, this was the slower (one sequence, four calls of a 4096 x 11008 block, us:
+// 7.9 + 5.6 + 7.6 + 9.7, with workgroups numbered over all groups; 7.1 + 4.6 + 5.8 + 7.3 now).  Each product is added to its sum by the vector
+// units: chained through the instruction's accumulator z was rounded the other way to bf16 133 times in a million (4096 columns), 110 this way, 97 to 172
+// by the kernels before.  The wavefronts' sums meet in LDS and are added in wavefront order.  No partial sums leave
+// the workgroup.  The result is masked, rounded and stored like decode_zr's.
 constexpr int DV_WAVES = 8, DV_THREADS = DV_WAVES * 64;
-constexpr int DV_JW = 8;                     // ranks per workgroup
-constexpr int DV_DEPTH = 24;                 // factor loads a lane has in flight: reductions of up to 12288 in one batch
 constexpr int DV_XBYTES = 96 * 1024;         // most LDS the x rows may take
 constexpr int DV_MAXB = 4;
 
-template <int NB>
+__device__ __host__ __forceinline__ int dv_xstride(int n) { return n * 2 + ((n & 127) == 0 ? 128 : 0); }   // bytes between x rows in LDS
+
+// XP pieces of x and DEPTH factor operands a lane: what is past the counts repeats the last one, so that no load stands behind a branch (the compiler
+// waits for all loads where the two sides of one meet)
+template <int JW, int XP, int DEPTH, bool NT>
 __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
-  int li = 0;
-#pragma unroll
-  for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].z_first) ? 1 : 0;
-  const DecLayer &ly = a.L[li];
-  const int bid = blockIdx.x - ly.z_first;
-  const int rb = bid / (32 / DV_JW), j0 = (bid % (32 / DV_JW)) * DV_JW;
-  const int n = a.n, B = a.B;
-  const uint32_t mask = (uint32_t)ly.plan[65 + (rb * 32) / ly.gs];
-  if (mask == 0u) return;                    // a block nobody selected is neither read nor written
-  extern __shared__ __attribute__((aligned(16))) char xs[];      // NB * n bf16: several workgroups fit a compute unit
-  __shared__ float red[DV_WAVES][NB][DV_JW];
+  constexpr int C = 16 / JW;                 // parts of an instruction's reduction range
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int jl = lane & 7, q = (lane >> 3) & 1, ks = lane >> 4;
-  const int nkb = n / 16;
-  const int ninstr = (nkb + 3) / 4;                                  // wavefront instructions of the block, 4 steps each
-  const int nw = (ninstr - wave + DV_WAVES - 1) / DV_WAVES;          // ... of this wavefront: wave, wave + 4, ...
-  const char *vbase = (const char *)ly.Vt + (size_t)rb * nkb * 1024 + (q * 32 + j0 + jl) * 16;
-  u32x4 v[DV_DEPTH];
-  auto request = [&](int i0) {               // lanes past the last step re-read it (switched off when used)
+  int at;
+  const int li = dec_layer_of(a, blockIdx.x, at);
+  const DecLayer &ly = a.L[li];
+  // eight ranks; JW == 4: one half of them, the other half (of the same 128-byte lines) goes to a workgroup of the same die
+  const int half = JW == 4 ? (at >> 3) & 1 : 0;
+  const DecTask task = dec_task(ly, ly.plan[0], ly.plan[1 + lane], ly.plan[65 + lane], li, JW == 4 ? (at >> 4) * 8 + (at & 7) : at, 3);
+  if (task.unit < 0) return;
+  const int rb = task.unit >> 2, j0 = (task.unit & 3) * 8 + half * 4;
+  const int n = a.n, B = a.B, nkb = n / 16;
+  extern __shared__ __attribute__((aligned(16))) char xs[];      // B rows of x: several workgroups fit a compute unit
+  __shared__ __attribute__((aligned(16))) float red[DV_WAVES][C][JW][JW];            // [wavefront][part][sequence][rank]
+  const int r = (lane & 15) % JW, part = (lane & 15) / JW, kq = lane >> 4;           // rank and sequence, part, 8 of its 32 reduction indices
+  const int pieces = n / 8, xstride = dv_xstride(n), all = B * pieces;
+  u32x4 xr[XP];
 #pragma unroll
-    for (int u = 0; u < DV_DEPTH; ++u) {
-      if (i0 + u < nw) {                     // uniform
-        const int kb = min(((wave + (i0 + u) * DV_WAVES) << 2) + ks, nkb - 1);
-        v[u] = stream_load(vbase + (size_t)kb * 1024);
-      }
-    }
+  for (int u = 0; u < XP; ++u) xr[u] = *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)min(u * DV_THREADS + (int)threadIdx.x, all - 1) * 16);
+  const char *vbase = (const char *)ly.Vt + (size_t)rb * nkb * 1024 + ((kq & 1) * 32 + j0 + r) * 16;
+  auto step = [&](int i) { return ((wave + i * DV_WAVES) * C + part) * 2 + (kq >> 1); };       // of this wavefront's instruction i, this lane
+  u32x4 v[DEPTH];
+  auto request = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) v[u] = stream_load<NT>(vbase + (size_t)min(step(i0 + u), nkb - 1) * 1024);
   };
+  __builtin_amdgcn_sched_barrier(0);
   request(0);
   __builtin_amdgcn_sched_barrier(0);
-  // the x rows: B * n contiguous bf16, copied as they are; rows B .. NB-1 (never stored) are cleared
-  for (int i = threadIdx.x; i < NB * n / 8; i += DV_THREADS) {
-    u32x4 w = {0, 0, 0, 0};
-    if (i < B * n / 8) w = *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)i * 16);
-    *reinterpret_cast<u32x4 *>(xs + (size_t)i * 16) = w;
+  const float inv = 1.0f / (float)pieces;
+  auto keep = [&](int i, u32x4 w) {          // piece i of the rows; exact: i < 2^14, and (i + 1/2) / pieces is at least 2^-14 off every integer
+    const int row = (int)(((float)i + 0.5f) * inv);
+    *reinterpret_cast<u32x4 *>(xs + row * xstride + (i - row * pieces) * 16) = w;
+  };
+#pragma unroll
+  for (int u = 0; u < XP; ++u) keep(min(u * DV_THREADS + (int)threadIdx.x, all - 1), xr[u]);
+#pragma unroll 1
+  for (int i = XP * DV_THREADS + (int)threadIdx.x; i < all; i += DV_THREADS)
+    keep(i, *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)i * 16));
+  dec_lds_barrier();
+  const char *xrow = xs + min(r, B - 1) * xstride + (kq & 1) * 16;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0;;) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      const int kb = step(i0 + u);
+      const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow + min(kb, nkb - 1) * 32);
+      const bool on = kb < nkb;              // else both are cleared: an infinite weight times zero is no number
+      acc += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(on ? v[u] : u32x4{0, 0, 0, 0}), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+    i0 += DEPTH;
+    if ((wave + i0 * DV_WAVES) * C * 2 >= nkb) break;      // uniform
+    request(i0);
   }
+  // lane (column lane % 16, g) holds rows 4 g .. 4 g + 3: of use where row and column are of the same part
+  if ((kq * 4) / JW == part) *reinterpret_cast<f32x4 *>(&red[wave][part][r][(kq * 4) % JW]) = acc;
   __syncthreads();
-  float acc[NB];
+  if (threadIdx.x < JW * JW) {               // thread (sequence, rank): wavefronts and parts in order
+    const int b = threadIdx.x / JW, e = threadIdx.x % JW;
+    float z = 0.f;
 #pragma unroll
-  for (int b = 0; b < NB; ++b) acc[b] = 0.f;
-  for (int i0 = 0; i0 < nw; i0 += DV_DEPTH) {
+    for (int w = 0; w < DV_WAVES; ++w)
 #pragma unroll
-    for (int u = 0; u < DV_DEPTH; ++u) {
-      if (i0 + u >= nw) break;               // uniform
-      const int kbr = ((wave + (i0 + u) * DV_WAVES) << 2) + ks;
-      const bool on = kbr < nkb;
-      const int kb = min(kbr, nkb - 1);
-      const u32x4 vv = v[u];
+      for (int c = 0; c < C; ++c) z += red[w][c][b][e];
+    const float next = __shfl_down(z, 1, 64);
+    if (b < B && !(e & 1))                   // zeros outside the group's mask
+      *reinterpret_cast<uint32_t *>((char *)ly.zf + (size_t)(rb * 2 + (j0 >> 4)) * 1024 + (((j0 >> 3) & 1) * 32 + b) * 16 + ((j0 & 7) + e) * 2) =
+          ((task.mask >> b) & 1u) ? cvt_pk_bf16(z, next) : 0u;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// decode_zp: decode_zv's tasks of eight ranks for up to sixteen sequences, with x, all of it, staged once per compute unit: one workgroup a unit takes every
+// gridDim-th task.  A task is done in chunks of DEPTH factor operands a wavefront; the next chunk, of this task or the next one, is on its way while
+// one is multiplied.  Bound by what a unit takes in: x once and its share of the factor, where a workgroup of sixteen ranks that reads x for itself takes
+// in as much of x as of the factor and a unit with two of them twice that (twelve sequences, a 4096 x 11008 block, us: q/k/v 14.1 -> 10.5, o 8.2 -> 6.1,
+// gate/up 9.6 -> 9.0; a call of 512 ranks 15.2 (32-wide) / 10.9 / 9.2).
+constexpr int DP_MAXB = 16;
+constexpr int DP_LDS = 160 * 1024 - 512;     // x and the wavefronts' sums
+
+__device__ __host__ constexpr int dp_red_bytes(int NX) { return 2 * DV_WAVES * 2 * NX * 8 * 8 * 4; }
+
+// NX groups of eight sequences, XP pieces of x a thread asks for at once; ONE: a task is one chunk
+template <int NX, int XP, int DEPTH, bool ONE, bool NT>
+__global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int n = a.n, B = a.B, nkb = n / 16;
+  extern __shared__ __attribute__((aligned(16))) char xs[];      // B rows of x
+  __shared__ __attribute__((aligned(16))) float red[2][DV_WAVES][2][NX * 8][8];      // [turn][wavefront][part][sequence][rank]
+  static_assert(sizeof(red) == dp_red_bytes(NX), "");
+  const int r = lane & 7, part = (lane >> 3) & 1, kq = lane >> 4;                    // rank and sequence, part, 8 of its 32 reduction indices
+  const int pieces = n / 8, xstride = dv_xstride(n), all = B * pieces;
+  const int chunks = ONE ? 1 : (nkb + 4 * DV_WAVES * DEPTH - 1) / (4 * DV_WAVES * DEPTH);
+  auto step = [&](int i) { return ((wave + i * DV_WAVES) * 2 + part) * 2 + (kq >> 1); };       // of this wavefront's instruction i of a task, this lane
+  int used[DEC_MAX_LAYERS], ids[DEC_MAX_LAYERS], masks[DEC_MAX_LAYERS];
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const u32x4 xv = *reinterpret_cast<const u32x4 *>(xs + ((size_t)b * n + kb * 16 + q * 8) * 2);
-        float t = 0.f;
+  for (int l = 0; l < DEC_MAX_LAYERS; ++l) { // layers past the last one: that one
+    const int32_t *plan = a.L[0].plan + (size_t)min(l, a.n_layers - 1) * DEC_PLAN_WORDS;
+    used[l] = plan[0];
+    ids[l] = plan[1 + lane];
+    masks[l] = plan[65 + lane];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  struct Task {
+    int unit;                                // < 0: none
+    uint32_t mask;
+    const char *V;                           // this lane's factor; without a task all lanes read the same 16 bytes
+    int stride;
+    uint16_t *zf;
+  };
+  auto task_of = [&](int id) {
+    int at;
+    const int li = dec_layer_of(a, id, at);
+    const DecLayer &ly = a.L[li];
+    auto of = [&](const int (&w)[DEC_MAX_LAYERS]) {
+      int x = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          t += __uint_as_float(vv[e] << 16) * __uint_as_float(xv[e] << 16);
-          t += __uint_as_float(vv[e] & 0xFFFF0000u) * __uint_as_float(xv[e] & 0xFFFF0000u);
-        }
-        acc[b] += on ? t : 0.f;
+      for (int l = 0; l < DEC_MAX_LAYERS; ++l) x |= w[l] & -(int)(li == l);
+      return x;
+    };
+    const DecTask t = dec_task(ly, of(used), of(ids), of(masks), li, at, 3);
+    const bool on = t.unit >= 0;
+    return Task{t.unit, t.mask,
+                on ? (const char *)ly.Vt + (size_t)(t.unit >> 2) * nkb * 1024 + ((kq & 1) * 32 + (t.unit & 3) * 8 + r) * 16 : (const char *)a.x,
+                on ? 1024 : 0, ly.zf};
+  };
+  u32x4 xr[XP], v0[DEPTH], v1[DEPTH];
+  auto request = [&](const Task &t, int chunk, u32x4 (&v)[DEPTH]) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) v[u] = stream_load<NT>(t.V + (size_t)min(step(chunk * DEPTH + u), nkb - 1) * t.stride);
+  };
+  const float inv = 1.0f / (float)pieces;
+  auto keep = [&](int i, u32x4 w) {          // piece i of the rows; exact: i < 2^14, and (i + 1/2) / pieces is at least 2^-14 off every integer
+    const int row = (int)(((float)i + 0.5f) * inv);
+    *reinterpret_cast<u32x4 *>(xs + row * xstride + (i - row * pieces) * 16) = w;
+  };
+#pragma unroll
+  for (int u = 0; u < XP; ++u) xr[u] = *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)min(u * DV_THREADS + (int)threadIdx.x, all - 1) * 16);
+  __builtin_amdgcn_sched_barrier(0);
+  int id = blockIdx.x, chunk = 0;
+  Task task = task_of(id);
+  if (task.unit < 0) return;                 // uniform
+  request(task, 0, v0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < XP; ++u) keep(min(u * DV_THREADS + (int)threadIdx.x, all - 1), xr[u]);
+#pragma unroll 1
+  for (int i = XP * DV_THREADS + (int)threadIdx.x; i < all; i += DV_THREADS)
+    keep(i, *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)i * 16));
+  dec_lds_barrier();
+  const char *xrow[NX];
+  f32x4 acc[NX];
+#pragma unroll
+  for (int h = 0; h < NX; ++h) {
+    xrow[h] = xs + min(h * 8 + r, B - 1) * xstride + (kq & 1) * 16;
+    acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  int which = 0;
+  // multiplies the chunk in v, the next one on its way into w; false after the last task
+  auto turn = [&](const u32x4 (&v)[DEPTH], u32x4 (&w)[DEPTH]) -> bool {
+    const Task now = task;
+    const int c = ONE ? 0 : chunk;
+    if (ONE || ++chunk == chunks) {          // uniform
+      chunk = 0;
+      id += gridDim.x;
+      task = task_of(id);
+    }
+    request(task, ONE ? 0 : chunk, w);
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      const int kb = step(c * DEPTH + u), at = min(kb, nkb - 1) * 32;
+      const bool on = kb < nkb;              // else both are cleared: an infinite weight times zero is no number
+      const u32x4 vv = on ? v[u] : u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int h = 0; h < NX; ++h) {
+        const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow[h] + at);
+        acc[h] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vv), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
       }
     }
-    if (i0 + DV_DEPTH < nw) request(i0 + DV_DEPTH);     // uniform
-  }
-  // the 8 lanes of a rank (4 steps x 2 halves), then the wavefronts
+    if (!ONE && chunk != 0) return true;     // uniform
+    if ((kq >> 1) == part) {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    float t = acc[b];
-    t += __shfl_xor(t, 8, 64);
-    t += __shfl_xor(t, 16, 64);
-    t += __shfl_xor(t, 32, 64);
-    if (lane < DV_JW) red[wave][b][lane] = t;
-  }
-  __syncthreads();
-  if (threadIdx.x < 32) {                    // one 16-byte piece per sequence: its 8 ranks, zeros outside the group's mask
-    const int b = threadIdx.x;
-    u32x4 out = {0, 0, 0, 0};
-    if (b < B && b < NB && ((mask >> b) & 1u)) {
-      float s8[DV_JW];
-#pragma unroll
-      for (int e = 0; e < DV_JW; ++e) {
-        float t = red[0][min(b, NB - 1)][e];
-#pragma unroll
-        for (int w = 1; w < DV_WAVES; ++w) t += red[w][min(b, NB - 1)][e];
-        s8[e] = t;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = cvt_pk_bf16(s8[2 * e], s8[2 * e + 1]);
+      for (int h = 0; h < NX; ++h) *reinterpret_cast<f32x4 *>(&red[which][wave][part][h * 8 + r][(kq & 1) * 4]) = acc[h];
     }
-    *reinterpret_cast<u32x4 *>((char *)ly.zf + (size_t)(rb * 2 + (j0 >> 4)) * 1024 + (((j0 >> 3) & 1) * 32 + b) * 16) = out;
-  }
+    dec_lds_barrier();
+    if (threadIdx.x < NX * 64) {             // thread (sequence, rank): wavefronts and parts in order
+      const int b = threadIdx.x >> 3, e = threadIdx.x & 7;
+      float z = 0.f;
+#pragma unroll
+      for (int q = 0; q < DV_WAVES; ++q)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) z += red[which][q][p][b][e];
+      const float next = __shfl_down(z, 1, 64);
+      if (b < B && !(e & 1))                 // zeros outside the group's mask
+        *reinterpret_cast<uint32_t *>((char *)now.zf + (size_t)(now.unit >> 1) * 1024 + ((now.unit & 1) * 32 + b) * 16 + e * 2) =
+            ((now.mask >> b) & 1u) ? cvt_pk_bf16(z, next) : 0u;
+    }
+    which ^= 1;                              // the other place: this one is read until the next barrier
+#pragma unroll
+    for (int h = 0; h < NX; ++h) acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    return task.unit >= 0;
+  };
+  while (turn(v0, v1) && turn(v1, v0)) {}
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -486,7 +639,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
 // wavefront w owns an eighth of the used reduction blocks for all NC column blocks, so one z operand (cache-resident)
 // feeds NC products; the Ut operands of its first MAXK reduction blocks are requested at once (MAXK sized so that
 // everything stays in registers), the rest is streamed in chunks; the eight wavefronts add up through LDS.
-template <int NC>
+template <int NC, bool NT>
 __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
   int li = 0;
 #pragma unroll
@@ -540,7 +693,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
     for (int i = 0; i < DY_MAXK; ++i) {
       const int kb = kb_list[k0 + min(i, cnt - 1)];
 #pragma unroll
-      for (int j = 0; j < NC; ++j) ur[i][j] = stream_load(ubase + (size_t)kb * ustep + coff[j]);
+      for (int j = 0; j < NC; ++j) ur[i][j] = stream_load<NT>(ubase + (size_t)kb * ustep + coff[j]);
     }
     __builtin_amdgcn_sched_barrier(0);   // every fetch above is in flight before the first product
 #pragma unroll
@@ -556,7 +709,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
       for (int i = 0; i < DEC_CHUNK; ++i) {
         const int kb = kb_list[k0 + min(c + i, cnt - 1)];
 #pragma unroll
-        for (int j = 0; j < NC; ++j) uu[i][j] = stream_load(ubase + (size_t)kb * ustep + coff[j]);
+        for (int j = 0; j < NC; ++j) uu[i][j] = stream_load<NT>(ubase + (size_t)kb * ustep + coff[j]);
         zz[i] = *reinterpret_cast<const u32x4 *>(zbase + (size_t)kb * 512);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -612,7 +765,7 @@ constexpr int DYV_WAVES = 8, DYV_THREADS = DYV_WAVES * 64;
 constexpr int DYV_DEPTH = 16;                // Ut loads a lane has in flight
 constexpr int DYV_ZBYTES = 96 * 1024;        // most LDS the z pieces may take
 
-template <int NB, int CG>
+template <int NB, int CG, bool NT>
 __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
   constexpr int PARTS = DYV_WAVES / CG;      // wavefronts that share a column group
   int li = 0;
@@ -658,7 +811,7 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
     for (int u = 0; u < DYV_DEPTH; ++u) {
       if (i0 + u < nw) {                     // uniform
         const int i = min(((part + (i0 + u) * PARTS) << 2) + ks, total_kb - 1);
-        v[u] = stream_load(ubase + (size_t)kb_list[i] * ustep);
+        v[u] = stream_load<NT>(ubase + (size_t)kb_list[i] * ustep);
       }
     }
   };
@@ -716,97 +869,20 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_z16 / decode_y16: up to sixteen sequences (a small server; which calls of two to four come here is decided where the
-// kernels are launched), on the 16x16x32 matrix instruction.  The 32-wide
-// kernels leave half of their N side empty there, own 32 ranks or columns per workgroup (too few workgroups: a 4096-column
-// layer has 128 column blocks for 256 units) and stage x through LDS behind barriers.  Here the M side is 16 ranks or
+// decode_y16: y for up to sixteen sequences (which calls of two to four come here is decided where the kernels are launched), on the 16x16x32 matrix
+// instruction.  The 32-wide kernel leaves half of its N side empty there and owns 32 columns per workgroup (too few workgroups: a 4096-column
+// layer has 128 column blocks for 256 units).  Here the M side is 16
 // columns: in the operand order 16 rows x 32 reduction indices are four runs of 256 bytes, a wavefront instruction reads
-// whole lines, every line once in the launch.  Everything goes straight from memory into registers -- also x, row-major,
-// sixteen rows x 64 bytes per instruction, as many bytes as the factor and mostly from the die's L2 -- the eight wavefronts
-// of a workgroup split the reduction and share nothing until their sums meet in LDS.  No slices of the reduction, so no
-// partial sums in memory and no tickets.  Same rounding points, plan and workspace as the other decode kernels.
-// Bound by what a unit takes in and by the launches' latency.  A 4096 x 11008 block
-// of twelve sequences 93 us a step, 103 with the 32-wide kernels; its MLP of four 61 us, 90 on the vector units.
+// whole lines, every line once in the launch.  Everything goes straight from memory into registers; the eight wavefronts
+// of a workgroup split the reduction and share nothing until their sums meet in LDS.
+// Same rounding points, plan and workspace as the other decode kernels.  Bound by HBM and by the launch's latency: 5.0 us for 11 MB, 8.8 for 33 MB.
 typedef __attribute__((ext_vector_type(4))) float f32x4_acc;
 constexpr int D16_WAVES = 8, D16_THREADS = D16_WAVES * 64, D16_MAXB = 16;
-
-// DEPTH: steps of 32 columns a wavefront has in flight -- its whole share where that is up to 16 (n = 4096); requests past the
-// share repeat its last one, so short reductions take fewer (six calls of 1024 columns, twelve sequences: 46 us with 16, 42 with 10)
-template <int DEPTH>
-__global__ __launch_bounds__(D16_THREADS) void decode_z16(DecArgs a) {
-  int li = 0;
-#pragma unroll
-  for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].z_first) ? 1 : 0;
-  const DecLayer &ly = a.L[li];
-  const int b16 = blockIdx.x - ly.z_first;             // 16 ranks = one reduction block of the second product
-  const int n = a.n, B = a.B;
-  const uint32_t mask = (uint32_t)ly.plan[65 + (b16 * 16) / ly.gs];
-  if (mask == 0u) return;
-  __shared__ float red[D16_WAVES][4][64];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int r = lane & 15, kq = lane >> 4;             // row of the 16 (rank / sequence), 8 reduction indices of the 32
-  const int nkb = n / 16, steps = (nkb + 1) / 2;
-  const int s0 = (steps * wave) / D16_WAVES, cnt = (steps * (wave + 1)) / D16_WAVES - s0;
-  const char *V = (const char *)ly.Vt + (size_t)(b16 >> 1) * nkb * 1024 + ((kq & 1) * 32 + (b16 & 1) * 16 + r) * 16;
-  const char *X = (const char *)a.x + (size_t)min(r, B - 1) * n * 2 + (kq & 1) * 16;
-  f32x4_acc acc = {0.f, 0.f, 0.f, 0.f};
-  u32x4 vr[DEPTH], xr[DEPTH];
-  auto request = [&](int d, int s) {                   // the second half of an odd last step re-reads the last block
-    const int kb = min((s0 + s) * 2 + (kq >> 1), nkb - 1);
-    vr[d] = *reinterpret_cast<const u32x4 *>(V + (size_t)kb * 1024);
-    xr[d] = *reinterpret_cast<const u32x4 *>(X + (size_t)kb * 32);
-  };
-  const int half = (nkb & 1) && s0 + cnt == steps ? cnt - 1 : -1;      // that step: always a wavefront's last one
-  auto product = [&](int d) { acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vr[d]), dec_bf16x8(xr[d]), acc, 0, 0, 0); };
-  if (cnt > 0) {
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) request(d, min(d, cnt - 1));
-    int s = 0;
-    for (; s + DEPTH < cnt; s += DEPTH) {
-#pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
-        __builtin_amdgcn_sched_barrier(0);
-        product(d);
-        request(d, min(s + d + DEPTH, cnt - 1));
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + d < cnt) {                               // uniform
-        if (s + d == half && (kq >> 1)) vr[d] = xr[d] = u32x4{0, 0, 0, 0};   // both: an infinite weight times zero is no number
-        product(d);
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) red[wave][e][lane] = acc[e];
-  __syncthreads();
-  // lane (sequence c, g) of the sums holds ranks 4g..4g+3; thread (q, j) stores ranks 8q..8q+7 of sequence j, zeros where the
-  // sequence did not select the group
-  if (threadIdx.x < 64) {
-    const int q = lane >> 5, j = lane & 31;
-    u32x4 out = {0, 0, 0, 0};
-    if (j < B && ((mask >> j) & 1u)) {
-      float z[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int ln = (2 * q + (e >> 2)) * 16 + j;
-        z[e] = red[0][e & 3][ln];
-#pragma unroll
-        for (int w = 1; w < D16_WAVES; ++w) z[e] += red[w][e & 3][ln];
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = cvt_pk_bf16(z[2 * e], z[2 * e + 1]);
-    }
-    *reinterpret_cast<u32x4 *>((char *)ly.zf + (size_t)b16 * 1024 + lane * 16) = out;
-  }
-}
 
 // NC blocks of 16 columns per workgroup; wavefront w takes every eighth 32-rank block in use.
 template <int NC>
 __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
-  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : (NC == 4 ? 8 : 6));
+  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : 8);
   int li = 0;
 #pragma unroll
   for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].y_first) ? 1 : 0;
@@ -932,27 +1008,17 @@ int build_decode_plan(const parse_layer *layers, const parse_patterns *pts, int 
   return PARSE_OK;
 }
 
-// Which kernel makes z.  One sequence: the vector units.  Two to sixteen: the 16-wide kernel where its workgroups (16 stored
-// ranks each) are many or its wavefronts have their whole share of the reduction in flight (n <= 4096); else the kernel that
-// splits the work more finely: the vector units (eight ranks a workgroup) for two sequences, or for four while x is short,
-// the 32-wide kernel (the reduction cut in slices) otherwise, and wherever x, which every 16-wide workgroup reads whole, outweighs
-// the factor.  us a step of one layer of 4096 columns (two or three patterns of half of the groups), vector / 16-wide / 32-wide, by
-// sequences x n:
-//    512 ranks: 2 x 4608   9.5 / 10.9 / 14.7   4 x 4608 11.4 / 12.1 / 15.6   4 x 8192 14.4 / 12.5 / 16.4   3 x 14336 - / 20 / 17
-//   1024 ranks: 2 x 11008 15.9 / 16.8 / 15.1   5 x 4096 - / 11.0 / 13.9      5 x 11008 - / 19.7 / 17.3     4 x 14336 - / 23 / 18
-//   2048 ranks: 2 x 4608  13.2 / 14.9 / 14.7   5 x 8192 - / 18.9 / 21.9      12 x 4608 - / 18.5 / 16.2     16 x 4608 - / 20 / 16
-//   2560 ranks: 2 x 8192  23 / 18 / 22         5 x 11008 - / 24 / 26         12 x 11008 - / 27 / 25
-//   3 x 2048:   2 x 8192  38 / 34 / 42         4 x 4096 35 / 30 / 30         12 x 2048 - / 20.8 / 20.9     12 x 8192 - / 39 / 41
-static bool z_on_vector_units(int NB, int n, int wgs16) {
-  if (NB == 1 || NB * n <= 6144) return true;
-  return NB == 2 ? wgs16 <= 128 : wgs16 <= 64 && n > 4096 && n <= 6144;
-}
-static bool z_16_wide(int B, int n, int wgs16) {
-  if (n <= 4096) return true;
-  const long long x = (long long)B * n;
-  if (wgs16 >= 160) return x <= 60000;
-  if (wgs16 >= 128) return x <= 50000;
-  return n <= 12288 && (wgs16 < 64 ? x <= 60000 : B <= 4 && x <= 50000);
+// Which kernel makes z.  Up to sixteen sequences whose x fits the LDS: decode_zv, many small workgroups that each stage x, for one sequence, for so few tasks that
+// none waits for a unit (up to 128 units of eight ranks, which decode_zv halves), or for many tasks of little x; decode_zp, x once per unit, otherwise.
+// The 32-wide kernel where x does not fit.  us a call of one layer with 512 columns of output (two or three patterns of half of the groups), decode_zv /
+// decode_zp / 32-wide, by sequences x n:
+//    512 ranks: 1 x 2816  6.6 / 7.5 / 13.0     4 x 2816  7.7 / 8.3 / 15.1     12 x 2816 - / 8.9 / 15.1
+//   1024 ranks: 2 x 11008 11.2 / 12.5 / 14.2   4 x 5632  10.9 / 11.1 / 13.8   6 x 11008 14.4 / 13.3 / 15.0    12 x 5632 - / 11.6 / 13.3
+//   2048 ranks: 1 x 11008 11.0 / 12.6 / 16.3   2 x 4096  10.5 / 10.0 / 13.3   2 x 11008 17.9 / 14.8 / 18.8    4 x 8192 18.2 / 15.0 / 19.9
+//   2560 ranks: 1 x 11008 13.0 / 13.4 / 16.8   2 x 11008 16.3 / 16.0 / 20.0   4 x 11008 23.2 / 20.9 / 22.2    6 x 11008 23.0 / 18.9 / 19.9
+//   3 x 1536:   1 x 4096  9.9 / 10.5 / 14.5    2 x 4096  11.4 / 11.9 / 15.7   4 x 4096  14.1 / 14.2 / 17.3    12 x 4096 - / 14.0 / 16.2
+static bool z_many_workgroups(int B, int n, int units) {
+  return B == 1 || units <= 128 || (units > 256 && B * n <= 12288);
 }
 
 // Factors past the caches: a call whose layers are about a fifth of the last-level cache (256 MiB) or more, since what runs between two of its kind then
@@ -965,6 +1031,16 @@ bool past_caches(const parse_layer *layers, int n_layers) {
   for (int l = 0; l < n_layers; ++l) bytes += (size_t)layers[l].R * ((size_t)layers[l].n + layers[l].m) * 2;
   return bytes >= (size_t)48 << 20;
 }
+
+// more than 64 KiB of dynamic LDS: the kernel's limit, raised to the most that any call asks for; it holds for the kernel on a device, so once is enough
+#define DEC_ALLOW_LDS(kernel, most, bytes, dev)                                                                                          \
+  do {                                                                                                                                   \
+    static bool done[64] = {false};                                                                                                      \
+    if ((size_t)(bytes) > (size_t)65536 && !done[dev]) {                                                                                 \
+      PARSE_HIP_TRY(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(most)));               \
+      done[dev] = true;                                                                                                                  \
+    }                                                                                                                                    \
+  } while (0)
 
 // n_layers layers that share x (same n); plan = n_layers consecutive layer plans; Y[l] and the z part of layer l in the
 // workspace follow the order of `layers`.
@@ -1020,47 +1096,101 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   }
   const int nkb = a.n / 16;
   const int NB = B <= 1 ? 1 : (B <= 2 ? 2 : 4);
-  int wgs16 = 0;                                           // workgroups of the 16-wide first product
-  for (int l = 0; l < n_layers; ++l) wgs16 += layers[l].R / 16;
-  const bool zv = B <= DV_MAXB && (size_t)NB * a.n * 2 <= (size_t)DV_XBYTES && z_on_vector_units(NB, a.n, wgs16);
-  const bool z16 = !zv && B <= D16_MAXB && z_16_wide(B, a.n, wgs16);
+  const bool nt = past_caches(layers, n_layers);
+  int units = 0;                                           // tasks of eight ranks in the first product
+  for (int l = 0; l < n_layers; ++l) units += layers[l].R / 8;
+  const bool zv = B <= DV_MAXB && (size_t)B * dv_xstride(a.n) <= (size_t)DV_XBYTES && z_many_workgroups(B, a.n, units);
+  const bool zp = !zv && B <= DP_MAXB && (size_t)B * dv_xstride(a.n) + dp_red_bytes(B <= 8 ? 1 : 2) <= (size_t)DP_LDS;
   if (zv) {
-    // a handful of sequences: eight ranks per workgroup on the vector units, no split of the reduction range
-    zb = 0;
-    for (int l = 0; l < n_layers; ++l) { a.L[l].z_first = zb; zb += (layers[l].R / 32) * (32 / DV_JW); }
-    const size_t lds = (size_t)NB * a.n * 2;
-    if (NB == 1) {
-      PARSE_ALLOW_LDS(decode_zv<1>, lds);
-      hipLaunchKernelGGL(decode_zv<1>, dim3(zb), dim3(DV_THREADS), lds, s, a);
-    } else if (NB == 2) {
-      PARSE_ALLOW_LDS(decode_zv<2>, lds);
-      hipLaunchKernelGGL(decode_zv<2>, dim3(zb), dim3(DV_THREADS), lds, s, a);
+    // a handful of sequences: eight ranks per workgroup, four where that leaves units without work
+    const int jw = units <= n_cu ? 4 : 8;
+    int wgs = 0;
+    for (int l = 0; l < n_layers; ++l) wgs = std::max(wgs, jw == 4 ? (layers[l].R / 8 + 7) / 8 * 16 : layers[l].R / 8);
+    wgs *= n_layers;
+    const int share = ((nkb + 32 / jw - 1) / (32 / jw) + DV_WAVES - 1) / DV_WAVES;       // instructions of a wavefront
+    const size_t lds = (size_t)B * dv_xstride(a.n);
+    const int xp = (B * (a.n / 8) + DV_THREADS - 1) / DV_THREADS;                        // pieces of x of a thread
+#define PARSE_ZV(JW_, XP_, D_)                                                                                                              \
+  do {                                                                                                                                     \
+    if (nt) {                                                                                                                              \
+      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, true>), DV_XBYTES, lds, dev);                                                                 \
+      hipLaunchKernelGGL((decode_zv<JW_, XP_, D_, true>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                         \
+    } else {                                                                                                                               \
+      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, false>), DV_XBYTES, lds, dev);                                                                \
+      hipLaunchKernelGGL((decode_zv<JW_, XP_, D_, false>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                        \
+    }                                                                                                                                      \
+  } while (0)
+#define PARSE_ZVX(JW_, D_)                                                                     \
+  do {                                                                                         \
+    if (xp <= 1) PARSE_ZV(JW_, 1, D_);                                                         \
+    else if (xp <= 4) PARSE_ZV(JW_, 4, D_);                                                    \
+    else PARSE_ZV(JW_, 12, D_);                                                                \
+  } while (0)
+    if (jw == 4) { if (share <= 2) PARSE_ZVX(4, 2); else if (share <= 4) PARSE_ZVX(4, 4); else PARSE_ZVX(4, 12); }
+    else { if (share <= 4) PARSE_ZVX(8, 4); else if (share <= 8) PARSE_ZVX(8, 8); else if (share <= 12) PARSE_ZVX(8, 12); else PARSE_ZVX(8, 24); }
+#undef PARSE_ZVX
+#undef PARSE_ZV
+  } else if (zp) {
+    int wgs = 0;
+    for (int l = 0; l < n_layers; ++l) wgs = std::max(wgs, layers[l].R / 8);
+    wgs = std::min(wgs * n_layers, n_cu);
+    const int share = ((nkb + 3) / 4 + DV_WAVES - 1) / DV_WAVES;
+    const size_t lds = (size_t)B * dv_xstride(a.n);
+    const int xp = (B * (a.n / 8) + DV_THREADS - 1) / DV_THREADS;                        // pieces of x of a thread
+#define PARSE_ZP(NX_, XP_, D_, ONE_)                                                                                                        \
+  do {                                                                                                                                     \
+    if (nt) {                                                                                                                              \
+      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, true>), DP_LDS - dp_red_bytes(NX_), lds, dev);                                          \
+      hipLaunchKernelGGL((decode_zp<NX_, XP_, D_, ONE_, true>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                   \
+    } else {                                                                                                                               \
+      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, false>), DP_LDS - dp_red_bytes(NX_), lds, dev);                                         \
+      hipLaunchKernelGGL((decode_zp<NX_, XP_, D_, ONE_, false>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                  \
+    }                                                                                                                                      \
+  } while (0)
+    if (B <= 8) {
+      if (share <= 2) PARSE_ZP(1, 2, 2, true);
+      else if (share <= 4) PARSE_ZP(1, 4, 4, true);
+      else if (share <= 8) PARSE_ZP(1, 8, 8, true);
+      else if (share <= 12) PARSE_ZP(1, 12, 12, true);
+      else PARSE_ZP(1, 16, 8, false);
     } else {
-      PARSE_ALLOW_LDS(decode_zv<4>, lds);
-      hipLaunchKernelGGL(decode_zv<4>, dim3(zb), dim3(DV_THREADS), lds, s, a);
+      if (share <= 2) PARSE_ZP(2, 4, 2, true);
+      else if (share <= 4) PARSE_ZP(2, 8, 4, true);
+      else if (share <= 8 && xp <= 12) PARSE_ZP(2, 12, 8, true);
+      else if (share <= 8) PARSE_ZP(2, 16, 8, true);
+      else if (share <= 12) PARSE_ZP(2, 16, 12, true);
+      else PARSE_ZP(2, 16, 8, false);
     }
-  } else if (z16) {
-    zb = 0;
-    for (int l = 0; l < n_layers; ++l) { a.L[l].z_first = zb; zb += layers[l].R / 16; }
-    const int share = ((nkb + 1) / 2 + D16_WAVES - 1) / D16_WAVES;       // steps of a wavefront
-    if (share <= 4) hipLaunchKernelGGL(decode_z16<4>, dim3(zb), dim3(D16_THREADS), 0, s, a);
-    else if (share <= 8) hipLaunchKernelGGL(decode_z16<8>, dim3(zb), dim3(D16_THREADS), 0, s, a);
-    else if (share <= 12) hipLaunchKernelGGL(decode_z16<12>, dim3(zb), dim3(D16_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(decode_z16<16>, dim3(zb), dim3(D16_THREADS), 0, s, a);
+#undef PARSE_ZP
   } else {
     const bool two = (nkb + KS - 1) / KS > DR_HALF_KB;     // the longest slice needs two stagings of x
-    if (two) hipLaunchKernelGGL(decode_zr<true>, dim3(zb), dim3(DR_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(decode_zr<false>, dim3(zb), dim3(DR_THREADS), 0, s, a);
+#define PARSE_ZR(TWO_, ROWS_)                                                                                     \
+  do {                                                                                                           \
+    if (nt) hipLaunchKernelGGL((decode_zr<TWO_, ROWS_, true>), dim3(zb), dim3(DR_THREADS), 0, s, a);             \
+    else hipLaunchKernelGGL((decode_zr<TWO_, ROWS_, false>), dim3(zb), dim3(DR_THREADS), 0, s, a);               \
+  } while (0)
+    if (B <= 16) { if (two) PARSE_ZR(true, 16); else PARSE_ZR(false, 16); }
+    else { if (two) PARSE_ZR(true, 32); else PARSE_ZR(false, 32); }
+#undef PARSE_ZR
   }
   PARSE_LAUNCH_CHECK();
   size_t max_kb = 0;
   for (int l = 0; l < n_layers; ++l) max_kb = std::max(max_kb, (size_t)layers[l].R / 16);
   const size_t zs_bytes = max_kb * 2 * NB * 16;            // z pieces of every reduction block a layer has
   // ... and which one y: the vector units up to four sequences while there is little to do (sequences x columns x stored ranks;
-  // 13 M 5.0 / 5.8, 25 M 8.0 / 6.6, 46 M 10.1 / 7.3 vector / 16-wide), 16-wide up to sixteen (4096 columns 6.4, 32-wide 8.1)
+  // 13 M 5.0 / 5.8, 25 M 8.0 / 6.6, 46 M 10.1 / 7.3 vector / 16-wide; four sequences, 2048 ranks and few columns 9.1 / 7.5), 16-wide up to sixteen
+  // (4096 columns 6.4, 32-wide 8.1) while up to four blocks a workgroup make one round (2 x 11008 columns, 2048 ranks, four sequences: six blocks 21.7,
+  // 32-wide 20.7)
   long long y_work = 0;
   for (int l = 0; l < n_layers; ++l) y_work += (long long)NB * layers[l].m * layers[l].R;
-  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES && (B == 1 || y_work <= (16ll << 20))) {
+  // 16-column blocks per workgroup: the fewest that make one round of workgroups
+  int nc16 = 1;
+  for (; nc16 <= 4; ++nc16) {
+    int wgs = 0;
+    for (int l = 0; l < n_layers; ++l) wgs += (layers[l].m / 16 + nc16 - 1) / nc16;
+    if (wgs <= n_cu) break;
+  }
+  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES && (B == 1 || (y_work <= (16ll << 20) && (B == 2 || max_kb <= 64)))) {
     // a handful of sequences: z as a few values per rank in LDS, the launch streams only Ut.  16 columns per workgroup
     // unless that makes more than about four workgroups per compute unit
     int cols = 0;
@@ -1068,35 +1198,36 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
     const int CG = cols / 16 > 4 * n_cu ? 4 : 2;
     yb = 0;
     for (int l = 0; l < n_layers; ++l) { a.L[l].y_first = yb; yb += (layers[l].m + 8 * CG - 1) / (8 * CG); }
-#define PARSE_YV(NB_, CG_)                                                                     \
-  do {                                                                                         \
-    PARSE_ALLOW_LDS((decode_yv<NB_, CG_>), zs_bytes);                                          \
-    hipLaunchKernelGGL((decode_yv<NB_, CG_>), dim3(yb), dim3(DYV_THREADS), zs_bytes, s, a);    \
+#define PARSE_YV(NB_, CG_)                                                                                        \
+  do {                                                                                                           \
+    if (nt) {                                                                                                    \
+      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, true>), zs_bytes);                                                    \
+      hipLaunchKernelGGL((decode_yv<NB_, CG_, true>), dim3(yb), dim3(DYV_THREADS), zs_bytes, s, a);              \
+    } else {                                                                                                     \
+      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, false>), zs_bytes);                                                   \
+      hipLaunchKernelGGL((decode_yv<NB_, CG_, false>), dim3(yb), dim3(DYV_THREADS), zs_bytes, s, a);             \
+    }                                                                                                            \
   } while (0)
     if (NB == 1) { if (CG == 2) PARSE_YV(1, 2); else PARSE_YV(1, 4); }
     else if (NB == 2) { if (CG == 2) PARSE_YV(2, 2); else PARSE_YV(2, 4); }
     else { if (CG == 2) PARSE_YV(4, 2); else PARSE_YV(4, 4); }
 #undef PARSE_YV
-  } else if (B <= D16_MAXB) {
-    // 16-column blocks per workgroup: the fewest that make one round of workgroups
-    const int choices[] = {1, 2, 3, 4, 6};
-    int nc16 = 6;
-    for (int c : choices) {
-      int wgs = 0;
-      for (int l = 0; l < n_layers; ++l) wgs += (layers[l].m / 16 + c - 1) / c;
-      if (wgs <= n_cu) { nc16 = c; break; }
-    }
+  } else if (B <= D16_MAXB && nc16 <= 4) {
     yb = 0;
     for (int l = 0; l < n_layers; ++l) { a.L[l].y_first = yb; yb += (layers[l].m / 16 + nc16 - 1) / nc16; }
     if (nc16 == 1) hipLaunchKernelGGL(decode_y16<1>, dim3(yb), dim3(D16_THREADS), 0, s, a);
     else if (nc16 == 2) hipLaunchKernelGGL(decode_y16<2>, dim3(yb), dim3(D16_THREADS), 0, s, a);
     else if (nc16 == 3) hipLaunchKernelGGL(decode_y16<3>, dim3(yb), dim3(D16_THREADS), 0, s, a);
-    else if (nc16 == 4) hipLaunchKernelGGL(decode_y16<4>, dim3(yb), dim3(D16_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(decode_y16<6>, dim3(yb), dim3(D16_THREADS), 0, s, a);
-  } else if (NC == 1) hipLaunchKernelGGL(decode_y<1>, dim3(yb), dim3(DY_THREADS), 0, s, a);
-  else if (NC == 2) hipLaunchKernelGGL(decode_y<2>, dim3(yb), dim3(DY_THREADS), 0, s, a);
-  else if (NC == 3) hipLaunchKernelGGL(decode_y<3>, dim3(yb), dim3(DY_THREADS), 0, s, a);
-  else hipLaunchKernelGGL(decode_y<4>, dim3(yb), dim3(DY_THREADS), 0, s, a);
+    else hipLaunchKernelGGL(decode_y16<4>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+  } else {
+#define PARSE_Y(NC_)                                                                                              \
+  do {                                                                                                           \
+    if (nt) hipLaunchKernelGGL((decode_y<NC_, true>), dim3(yb), dim3(DY_THREADS), 0, s, a);                      \
+    else hipLaunchKernelGGL((decode_y<NC_, false>), dim3(yb), dim3(DY_THREADS), 0, s, a);                        \
+  } while (0)
+    if (NC == 1) PARSE_Y(1); else if (NC == 2) PARSE_Y(2); else if (NC == 3) PARSE_Y(3); else PARSE_Y(4);
+#undef PARSE_Y
+  }
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

@@ -2090,6 +2090,21 @@ def test_decode_few_sequences_tiles(n, shapes, B):
         assert torch.equal(ys[l].view(torch.int16), yp[l].view(torch.int16))
 
 
+@pytest.mark.parametrize("n,shapes,B", [
+    (48, [(32, 64, 2, 1)], 2),                                       # four ranks a workgroup, a last instruction with five eighths past the end
+    (1040, [(64, 4160, 26, 9)], 2),                                  # over 256 tasks of little x: a workgroup each
+    (2064, [(64, 2048, 16, 5)], 4), (8208, [(32, 1088, 34, 9)], 3),  # 129 to 256 tasks: x once per unit; a task in one chunk and in three
+    (4096, [(64, 2112, 33, 8), (32, 96, 3, 2)], 16),                 # x fills the LDS; layers of unlike size take turns
+    (5648, [(64, 1056, 11, 5)], 8), (5632, [(64, 96, 3, 2)], 12),    # twelve instructions a wavefront and task
+    (5632, [(64, 96, 3, 2)], 13),                                    # ... and one sequence more than fits
+    (11024, [(64, 2112, 33, 12)], 6), (11024, [(64, 96, 3, 2)], 7),  # more of x than a thread has on its way at once; all that fits
+    (14352, [(64, 96, 3, 2)], 12), (14352, [(32, 2592, 27, 9)], 11), # 32-wide with half of its rows, x staged once and in halves
+])
+def test_decode_tasks_of_eight_ranks(n, shapes, B):
+    """One to sixteen sequences at the edges of the first product's kernels and of the choice between them, against the oracle's product."""
+    test_decode_few_sequences_tiles(n, shapes, B)
+
+
 @pytest.mark.parametrize("n,B", [(48, 3), (48, 5), (48, 16), (4112, 3), (4112, 5), (4112, 14)])
 def test_decode_of_few_sequences_keeps_infinite_products(n, B):
     """A weight that overflowed to infinity, in the last column of an odd number of 16-column blocks (half of the 16-wide kernel's
