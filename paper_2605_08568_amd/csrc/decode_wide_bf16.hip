@@ -11,10 +11,11 @@
 // wavefronts take every fourth step and share nothing until their sums meet in LDS: no staging, no barrier in the loop; what
 // is in flight is DEPTH steps per wavefront (about 40 KiB; one wavefront per SIMD, so the registers are there).
 // Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
-// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns, 103 us a step: wide_z 17.5 us for gate+up and 21 for down,
-// 5.7 of them until the first slice is there (1 for the plan; a launch of its own for it and operands straight into registers, with one more launch that
-// brought x into operand order, came to 27-30), the factors at 4 TB/s, 1.6 for the sums; wide_zsum 4.8 each; wide_y 27 and 11 us; five panels one after the
-// other took 313-335 us.
+// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns, 91.5 us a step on factors from memory: wide_z 18.7 us for gate+up
+// and 23.2 for down, 5.2 of them until the first slice is there (2.3 for the plan; a launch of its own for it and operands straight into registers, with one more launch
+// that brought x into operand order, came to 27-30), then half a microsecond a slice of 28 KiB, which is what a unit takes in where lines from memory are among
+// those from the L2 (55 GB/s: 32 KiB outstanding, back in order), 1.6 for the sums; wide_zsum 4.8 each; wide_y 34 us, 24 of them the 467 KiB of factor and 778 KiB of z that
+// a unit takes in, and 9.9 us; five panels one after the other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
 
@@ -33,7 +34,8 @@ constexpr int DW_PLAN_WORDS = 128 + DW_MAXP * 64;      // [0] count, [1..64] use
 constexpr int DW_ZCB = 2;                  // rank blocks per wide_z workgroup
 constexpr int DW_UNITS = 256;              // workgroups wanted per launch
 constexpr int DW_MAX_KS = 8;
-constexpr int DW_ESTRIDE = 66;             // floats between accumulator rows in LDS: the row-wise read-out is conflict-free
+// Tiles of wide_y whose sums meet at a time: 16 KiB each, nine where the registers leave room for one workgroup a compute unit only
+constexpr int dw_round(int tiles) { return tiles <= 4 ? tiles : (tiles < 6 ? 4 : (tiles < 9 ? tiles : 9)); }
 
 struct DwLayer {
   const uint16_t *Vt, *Ut;
@@ -57,10 +59,10 @@ struct DwArgs {
 
 constexpr int dw_depth(int CB, int NT) { return 40 / (CB + NT) < 4 ? 4 : (40 / (CB + NT) > 8 ? 8 : 40 / (CB + NT)); }
 
-// The reduction loop of both products: steps first, first + DW_WAVES, ... (cnt of them); f(step, i) / t(step, p) = address
-// of factor operand i / token operand p.
-template <int CB, int NT, bool PAST, class F, class T>
-__device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T t) {
+// The reduction loop of the second product over cnt steps; k(step) = its reduction block, f(block, i) / t(block, p) = address of factor
+// operand i / token operand p.
+template <int CB, int NT, bool PAST, class K, class F, class T>
+__device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, K k, F f, T t) {
   constexpr int D = dw_depth(CB, NT);
   u32x4 fr[D][CB], tr[D][NT];
   auto factor = [](const void *p) { return PAST ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p)) : *reinterpret_cast<const u32x4 *>(p); };
@@ -73,7 +75,7 @@ __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T
   if (cnt <= 0) return;
 #pragma unroll
   for (int d = 0; d < D; ++d) {              // steps past the last re-read it (switched off below)
-    const int s = min(d, cnt - 1);
+    const int s = k(min(d, cnt - 1));
 #pragma unroll
     for (int i = 0; i < CB; ++i) fr[d][i] = factor(f(s, i));
 #pragma unroll
@@ -89,7 +91,7 @@ __device__ __forceinline__ void wide_loop(f32x16 (&acc)[CB][NT], int cnt, F f, T
 #pragma unroll
         for (int p = 0; p < NT; ++p)
           acc[i][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(fr[d][i]), as_bf16x8(tr[d][p]), acc[i][p], 0, 0, 0);
-      const int s = min(s0 + d + D, cnt - 1);
+      const int s = k(min(s0 + d + D, cnt - 1));
 #pragma unroll
       for (int i = 0; i < CB; ++i) fr[d][i] = factor(f(s, i));
 #pragma unroll
@@ -370,13 +372,19 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
 #pragma unroll
   for (int i = 1; i < DW_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].y_first) ? 1 : 0;
   const DwLayer &ly = a.L[li];
-  __shared__ float red[DW_WAVES][CB][16][DW_ESTRIDE];
-  __shared__ int32_t kb_list[1024];
+  constexpr int TILES = CB * NT, ROUND = dw_round(TILES);          // tiles whose sums meet in LDS at a time
+  __shared__ __attribute__((aligned(16))) f32x4v red[ROUND][DW_WAVES][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int kpg = ly.gs / 16, ncb = ly.m / 32, m = ly.m;
+  // the blocks in use, counted through: the ids are a register of the 64 lanes, a block's place follows by arithmetic and a lane read.  Exact: i < 1024, and
+  // (i + 1/2) / kpg is at least 1/2048 off every integer
+  const int ids = ly.plan[1 + lane];
   const int total = min(max(ly.plan[0], 0), ly.G) * kpg;           // <= R / 16 <= 1024
-  for (int i = threadIdx.x; i < total; i += DW_THREADS) kb_list[i] = ly.plan[1 + i / kpg] * kpg + i % kpg;
-  __syncthreads();
+  const float inv = 1.0f / (float)kpg;
+  auto block = [&](int s) {                                        // of step s of this wavefront
+    const int i = wave + s * DW_WAVES, g = __builtin_amdgcn_readfirstlane((int)(((float)i + 0.5f) * inv));
+    return max(__builtin_amdgcn_readlane(ids, g), 0) * kpg + i - g * kpg;
+  };
   const int units = (ncb + CB - 1) / CB, units8 = a.groups > 1 ? (units + 7) / 8 * 8 : units;
   const int unit = ((int)blockIdx.x - ly.y_first) % units8, group = ((int)blockIdx.x - ly.y_first) / units8;
   const int c0 = unit * CB, p0 = min(group * NT, a.panels - NT), skip = group * NT - p0;
@@ -387,33 +395,40 @@ __global__ __launch_bounds__(DW_THREADS, 1) void wide_y(DwArgs a) {
   for (int i = 0; i < CB; ++i) cb[i] = min(c0 + i, ncb - 1);       // blocks past the end re-read the last one (not stored)
   const size_t zstep = (size_t)(ly.R / 16);
   f32x16 acc[CB][NT];
-  wide_loop<CB, NT, PAST>(acc, (total - wave + DW_WAVES - 1) / DW_WAVES,
-                    [&](int s, int i) { return U + ((size_t)kb_list[wave + s * DW_WAVES] * ncb + cb[i]) * 1024; },
-                    [&](int s, int p) { return Z + (p * zstep + kb_list[wave + s * DW_WAVES]) * 1024; });
+  wide_loop<CB, NT, PAST>(acc, (total - wave + DW_WAVES - 1) / DW_WAVES, block,
+                    [&](int b, int i) { return U + ((size_t)b * ncb + cb[i]) * 1024; },
+                    [&](int b, int p) { return Z + (p * zstep + b) * 1024; });
+  // The wavefronts' sums meet in LDS, ROUND tiles at a time, and wavefront w adds and stores every fourth tile (all fifteen of three column blocks and five
+  // panels, panel by panel, took 4.4 us of 36).  Lane (sequence, q) holds columns 8 b + 4 q .. + 3 of band b of its tile.
 #pragma unroll
-  for (int p = 0; p < NT; ++p) {
-    if (p < skip) continue;                  // uniform
+  for (int t0 = 0; t0 < TILES; t0 += ROUND) {
+    if (t0 > 0) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < CB; ++i)
+    for (int t = t0; t < TILES && t < t0 + ROUND; ++t)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) red[wave][i][e][lane] = acc[i][p][e];
-    __syncthreads();
-    // thread = four consecutive columns of a sequence (eight threads a row's 32 columns): sums in wavefront order
-#pragma unroll
-    for (int i = 0; i < CB; ++i) {
-      const int quad = threadIdx.x & 7, j = threadIdx.x >> 3, seq = (p0 + p) * 32 + j;
-      float s[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = (quad >> 1) * 4 + e, ln = (quad & 1) * 32 + j;
-        s[e] = red[0][i][row][ln];
-#pragma unroll
-        for (int w = 1; w < DW_WAVES; ++w) s[e] += red[w][i][row][ln];
+      for (int b = 0; b < 4; ++b) {
+        const f32x16 &v = acc[t % CB][t / CB];
+        red[t - t0][wave][b][lane] = f32x4v{v[b * 4], v[b * 4 + 1], v[b * 4 + 2], v[b * 4 + 3]};
       }
-      if (seq < a.B && c0 + i < ncb)
-        *reinterpret_cast<u32x2 *>(ly.y + (size_t)seq * m + (c0 + i) * 32 + quad * 4) = u32x2{cvt_pk_bf16(s[0], s[1]), cvt_pk_bf16(s[2], s[3])};
-    }
     __syncthreads();
+    for (int t = t0 + wave; t < TILES && t < t0 + ROUND; t += DW_WAVES) {              // uniform
+      const int i = t % CB, p = t / CB, seq = (p0 + p) * 32 + (lane & 31);
+      if (p < skip || c0 + i >= ncb) continue;
+      f32x4v y[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        y[b] = red[t - t0][0][b][lane];
+#pragma unroll
+        for (int w = 1; w < DW_WAVES; ++w) y[b] += red[t - t0][w][b][lane];
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {          // after the swap lane (sequence, q) holds the 8 columns 16 h + 8 q .. + 7
+        const u32x2 x0 = __builtin_amdgcn_permlane32_swap(cvt_pk_bf16(y[2 * h][0], y[2 * h][1]), cvt_pk_bf16(y[2 * h + 1][0], y[2 * h + 1][1]), false, false);
+        const u32x2 x1 = __builtin_amdgcn_permlane32_swap(cvt_pk_bf16(y[2 * h][2], y[2 * h][3]), cvt_pk_bf16(y[2 * h + 1][2], y[2 * h + 1][3]), false, false);
+        if (seq < a.B)
+          *reinterpret_cast<u32x4 *>(ly.y + (size_t)seq * m + (c0 + i) * 32 + h * 16 + (lane >> 5) * 8) = u32x4{x0[0], x1[0], x0[1], x1[1]};
+      }
+    }
   }
 }
 
