@@ -278,13 +278,14 @@ __global__ __launch_bounds__(1024) void rank_topk(const float *__restrict__ scor
 // subset[j*stride + r] of the row-major layer.  Out-of-range ids give zero rows.  Bound by the writes to memory (a pattern's
 // blocks are new memory, the rows are shared by the patterns and stay in the last-level cache).
 
-// One thread per GV_STEPS pieces of consecutive reduction steps: together they take whole 128-byte lines of a row, the
-// stores of a wavefront are 1 KiB each.  1024 of 2048 ranks x 4096 columns for 8 patterns: 22.7 us with one piece per
-// thread, 17-22 with four.
+// A wavefront turns 32 ranks x GV_STEPS reduction steps, 128 bytes of each row: eight lanes take a row's whole line, and the lines come back from LDS
+// as operands (places swizzled by the row), stored in 1 KiB pieces.  Lane by lane in operand order, 32 bytes of 32 rows an instruction, every line was
+// asked for four times, and a unit has 256 lines outstanding at most: 1024 of 2048 ranks of a 4096 x 4096 layer for 8 patterns, both factors, 42.7 -> 38.8 us
+// (stores past the caches: the same, and the products after it 1 to 2 us more; patterns next to each other in the grid: 41.2).
 constexpr int GV_STEPS = 4;
 __device__ __forceinline__ void gather_mfma16_v(int wg, const uint16_t *__restrict__ Vt, int R, int n,
                                                 const int32_t *__restrict__ subset, int stride, int K,
-                                                uint16_t *__restrict__ dst) {
+                                                uint16_t *__restrict__ dst, char *lds) {
   const int nkb = n / 16, nch = (nkb + GV_STEPS - 1) / GV_STEPS;
   const size_t t = ((size_t)wg * 256 + threadIdx.x) >> 6;              // wavefront: (rank block, GV_STEPS reduction steps)
   const int lane = threadIdx.x & 63, j = lane & 31, q = lane >> 5;
@@ -292,16 +293,24 @@ __device__ __forceinline__ void gather_mfma16_v(int wg, const uint16_t *__restri
   const size_t rb = t / nch;
   if (rb >= (size_t)(K / 32)) return;
   const int pat = blockIdx.y;
-  const int row = subset[(size_t)pat * stride + rb * 32 + j];
-  const bool ok = row >= 0 && row < R;
-  const uint16_t *src = Vt + (size_t)(ok ? row : 0) * n + q * 8;
-  u32x4 v[GV_STEPS];
+  const int id = subset[(size_t)pat * stride + rb * 32 + j];
+  char *tile = lds + (threadIdx.x >> 6) * 4096;                        // this wavefront's
+  const int r8 = lane >> 3, c = lane & 7;                              // row of eight, 16-byte piece of its 128
+  u32x4 v[4];
+  bool ok[4];
 #pragma unroll
-  for (int u = 0; u < GV_STEPS; ++u) v[u] = *reinterpret_cast<const u32x4 *>(src + min(kb0 + u, nkb - 1) * 16);
+  for (int u = 0; u < 4; ++u) {
+    const int row = __shfl(id, u * 8 + r8, 64);
+    ok[u] = row >= 0 && row < R;
+    v[u] = *reinterpret_cast<const u32x4 *>(Vt + (size_t)(ok[u] ? row : 0) * n + min(kb0 * 2 + c, nkb * 2 - 1) * 8);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4 *>(tile + (u * 8 + r8) * 128 + ((c ^ r8) * 16)) = ok[u] ? v[u] : u32x4{0, 0, 0, 0};
   char *out = (char *)dst + (size_t)pat * K * n * 2 + (rb * nkb + kb0) * 1024 + lane * 16;
 #pragma unroll
   for (int u = 0; u < GV_STEPS; ++u)
-    if (kb0 + u < nkb) *reinterpret_cast<u32x4 *>(out + (size_t)u * 1024) = ok ? v[u] : u32x4{0, 0, 0, 0};
+    if (kb0 + u < nkb)
+      *reinterpret_cast<u32x4 *>(out + (size_t)u * 1024) = *reinterpret_cast<const u32x4 *>(tile + j * 128 + (((u * 2 + q) ^ (j & 7)) * 16));
 }
 
 // A workgroup turns 16 ranks (one reduction step) x GU_COLS columns: whole pieces of the rank rows go to LDS, and come back
@@ -309,8 +318,7 @@ __device__ __forceinline__ void gather_mfma16_v(int wg, const uint16_t *__restri
 constexpr int GU_COLS = 512, GU_LD = GU_COLS + 8;
 __device__ __forceinline__ void gather_mfma16_u(int wg, const uint16_t *__restrict__ Ut, int R, int m,
                                                 const int32_t *__restrict__ subset, int stride, int K,
-                                                uint16_t *__restrict__ dst) {
-  __shared__ __attribute__((aligned(16))) uint16_t tile[16][GU_LD];
+                                                uint16_t *__restrict__ dst, uint16_t (*tile)[GU_LD]) {
   const int ncc = (m + GU_COLS - 1) / GU_COLS;
   const int kb = wg / ncc, c0 = (wg % ncc) * GU_COLS, cols = min(GU_COLS, m - c0);   // cols: a multiple of 32
   const int pat = blockIdx.y;
@@ -340,12 +348,14 @@ __device__ __forceinline__ void gather_mfma16_u(int wg, const uint16_t *__restri
 }
 
 // Both factors in one launch: each is a chain of two loads and a store, and the workgroups of one cover the waits of the other's.
-// 1024 of 2048 ranks of a 4096 x 4096 layer for 8 patterns: 22 + 20 us as two launches, 37 as one.
+// 1024 of 2048 ranks of a 4096 x 4096 layer for 8 patterns: 22 + 20 us as two launches, 37 as one (with the right factor read lane by lane).
 __global__ __launch_bounds__(256) void gather_mfma16(const uint16_t *__restrict__ Vt, const uint16_t *__restrict__ Ut, int R, int n, int m,
                                                      const int32_t *__restrict__ subset, int stride, int K,
                                                      uint16_t *__restrict__ Vt_S, uint16_t *__restrict__ Ut_S, int v_wgs) {
-  if ((int)blockIdx.x < v_wgs) gather_mfma16_v(blockIdx.x, Vt, R, n, subset, stride, K, Vt_S);      // uniform
-  else gather_mfma16_u(blockIdx.x - v_wgs, Ut, R, m, subset, stride, K, Ut_S);
+  __shared__ __attribute__((aligned(16))) uint16_t tile[16][GU_LD];
+  static_assert(sizeof(tile) >= 4 * 4096, "four wavefronts' tiles of the right factor");
+  if ((int)blockIdx.x < v_wgs) gather_mfma16_v(blockIdx.x, Vt, R, n, subset, stride, K, Vt_S, (char *)tile);      // uniform
+  else gather_mfma16_u(blockIdx.x - v_wgs, Ut, R, m, subset, stride, K, Ut_S, tile);
 }
 
 }  // namespace parse

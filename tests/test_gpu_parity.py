@@ -1645,6 +1645,25 @@ def test_multi_calls_with_four_layers_and_a_shared_head():
                              f"prefill schedule {schedule} layer {li} prompt {p}")
 
 
+@pytest.mark.parametrize("n,m,R,K,P", [(16, 32, 64, 32, 1), (272, 96, 96, 64, 3), (1040, 1056, 512, 160, 2), (4096, 544, 64, 64, 1)])
+def test_rank_gather_at_the_edges_of_its_tiles(n, m, R, K, P):
+    """Rows of one reduction step and of numbers of them that are no multiple of four; an id below and one above the range give zero rows: the bits of
+    the reorder of the gathered rows."""
+    rng = np.random.default_rng(1411)
+    Vt, Ut = (rng.integers(0, 1 << 15, size=(R, w), dtype=np.uint16) for w in (n, m))
+    sub = np.stack([np.sort(rng.choice(R, size=K, replace=False)) for _ in range(P)]).astype(np.int32)
+    sub[0, 0], sub[-1, -1] = -1, R
+    layer = pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, R, pa.PARSE_ROWMAJOR)
+    Vs, Us = (torch.empty((P, K, w), dtype=torch.bfloat16, device=DEV) for w in (n, m))
+    pa.pack_ranks(layer, i32(sub), K, P, K, Vs, Us)
+    torch.cuda.synchronize()
+    for p in range(P):
+        rows = [np.where(((sub[p] >= 0) & (sub[p] < R))[:, None], F[np.clip(sub[p], 0, R - 1)], 0) for F in (Vt, Ut)]
+        ref = pa.layer_to_mfma16(pa.Layer(upload_tokens(rows[0], "bf16"), upload_tokens(rows[1], "bf16"), n, m, K, K // 32, pa.PARSE_ROWMAJOR))
+        for got, want in ((Vs[p], ref.Vt), (Us[p], ref.Ut)):
+            assert torch.equal(got.reshape(-1).view(torch.int16), want.reshape(-1).view(torch.int16)), f"pattern {p}"
+
+
 def test_rank_router_at_its_limits():
     """8192 ranks (the selection kernel's limit), 40 prompts (five scoring blocks), K = 32."""
     say("route_ranks: G=8192, P=40, K=32")
