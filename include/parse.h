@@ -259,7 +259,9 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *layer, int
  *                intermediate rounded to bf16.  Schedules: see parse_prefill_schedule (patterns->schedule).
  *                With workspace == NULL the fused kernel is used.  The planned schedule builds its plan inside the
  *                call (one extra small launch; a single prompt needs none); parse_lowrank_prefill_planned takes a ready plan instead.  f32
- *                layers must be PARSE_ROWMAJOR (plain fp32 kernels, intermediate in the workspace).
+ *                layers must be PARSE_ROWMAJOR (plain fp32 kernels, intermediate in the workspace: rows * r_S floats, and up to
+ *                eight times that for short calls, whose first product is cut into slices; with less room into fewer or none, so
+ *                that a result may differ in rounding.  The answer for N rows covers every call of up to N rows).
  *                  X device [rows][n], Y device [rows][m] (layer dtype), tok_offsets device int32 [P+1],
  *                  pattern_id device int32 [P].
  * PARSE_DECODE   one token per sequence (rows == P, tok_offsets ignored, may be NULL), bf16 PARSE_MFMA16

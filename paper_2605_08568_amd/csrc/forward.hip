@@ -5,7 +5,9 @@
 
 namespace parse {
 int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, int rows, const int32_t *tok_offsets,
-                const int32_t *pattern_id, int P, float *Y, void *workspace, hipStream_t s);
+                const int32_t *pattern_id, int P, float *Y, void *workspace, size_t workspace_bytes, hipStream_t s);
+size_t f32_needed_bytes(int rows, int rS);
+size_t f32_workspace_bytes(int rows, int rS);
 int forward_prefill_bf16(const parse_layer *L, const parse_patterns *pt, const uint16_t *X, int rows,
                          const int32_t *tok_offsets, const int32_t *pattern_id, int P, uint16_t *Y, void *workspace,
                          size_t workspace_bytes, hipStream_t s);
@@ -88,7 +90,7 @@ size_t parse_lowrank_workspace_bytes(int32_t mode, const parse_layer *L, int32_t
     }
     return need;
   }
-  if (L->dtype == PARSE_F32) return round_up((size_t)rows * k * (L->R / L->G) * sizeof(float), 256);
+  if (L->dtype == PARSE_F32) return f32_workspace_bytes(rows, k * (L->R / L->G));
   const int rS = k * (L->R / L->G);
   size_t need = prefill_split_workspace_bytes(rows, rS);
   if (P > 0 && n_patterns > 0 && P <= rows && prefill_plan_supported(P, n_patterns) &&
@@ -152,7 +154,9 @@ int parse_lowrank_forward(int32_t mode, const parse_layer *L, const parse_patter
   if (!aligned16(X) || !aligned16(Y)) return PARSE_EALIGN;
   if (mode == PARSE_DECODE && (L->dtype != PARSE_BF16 || L->layout != PARSE_MFMA16)) return PARSE_ELAYOUT;
   // the smallest workspace any schedule takes
-  const size_t need = mode == PARSE_DECODE ? decode_workspace_bytes(L) : parse_lowrank_workspace_bytes(mode, L, rows, pt->k, 0, 0);
+  const size_t need = mode == PARSE_DECODE       ? decode_workspace_bytes(L)
+                      : L->dtype == PARSE_F32 ? f32_needed_bytes(rows, pt->k * (L->R / L->G))
+                                              : parse_lowrank_workspace_bytes(mode, L, rows, pt->k, 0, 0);
   // bf16 prefill may run without a workspace (fused kernel only); every other mode needs the queried size
   const bool optional_ws = mode == PARSE_PREFILL && L->dtype == PARSE_BF16 && workspace == nullptr;
   if (!optional_ws && need > 0 && (!workspace || workspace_bytes < need)) return PARSE_EWORKSPACE;
@@ -178,7 +182,7 @@ int parse_lowrank_forward(int32_t mode, const parse_layer *L, const parse_patter
   }
   if (L->dtype == PARSE_F32) {
     if (L->layout != PARSE_ROWMAJOR) return PARSE_ELAYOUT;
-    return forward_f32(L, pt, (const float *)X, rows, tok_offsets, pattern_id, P, (float *)Y, workspace, s);
+    return forward_f32(L, pt, (const float *)X, rows, tok_offsets, pattern_id, P, (float *)Y, workspace, workspace_bytes, s);
   }
   if (L->layout != PARSE_MFMA16) return PARSE_ELAYOUT;
   if (rS % 32 != 0) return PARSE_ESHAPE;

@@ -7,11 +7,12 @@
 // fetched straight into registers, several 16-deep reduction chunks at a time: lane (i = l % 16, g = l / 16) takes 16
 // bytes of its row at reduction index 4 g, and the four matrix instructions of a chunk use element e of every lane, i.e.
 // reduction indices {e, 4 + e, 8 + e, 12 + e} -- the same for both operands, so the order within a chunk does not matter.
-// Measured at that size: first product 150.7 -> 7 us, second 26.9 -> 4.3 us (before: 64 x 64 tiles of plain FMA through
-// LDS, 8 workgroups for the first product).
+// Measured at that size: both products 9.2 us (64 x 64 tiles of plain FMA through LDS, 8 workgroups for the first product: 178).
 //
 // Each block of token rows is cut into the segments that belong to one prompt, and a segment uses the packed factors of
 // that prompt's pattern.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace parse {
@@ -56,7 +57,7 @@ __device__ __forceinline__ void for_segments(int row0, int row_end, int rows, co
 constexpr int FN_WAVES = 8;          // first product: wavefronts of a workgroup = parts of the reduction
 
 // Z[rows][N] = X[rows][K] * B_p[N][K]^T.  K % 4 == 0.  RT x CT blocks of 16 token rows x 16 ranks per workgroup; a
-// wavefront requests BATCH reduction chunks at a time.
+// wavefront requests BATCH reduction chunks at a time.  16 x 16 tiles: gridDim.z slices of the reduction, each with its own Z.
 template <int RT, int CT, int BATCH>
 __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restrict__ A, const float *__restrict__ Bbase,
                                                           size_t pattern_stride, int n_patterns, int rows, int N, int K,
@@ -67,7 +68,13 @@ __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restric
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
   const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * TN;
-  const int chunks = (K + 15) / 16;
+  int first = 0, chunks = (K + 15) / 16;
+  if constexpr (RT == 1 && CT == 1) {
+    const int all = chunks;
+    first = all * (int)blockIdx.z / (int)gridDim.z;
+    chunks = all * ((int)blockIdx.z + 1) / (int)gridDim.z;
+    C += (size_t)blockIdx.z * rows * N;
+  }
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
   for_segments<RT == 1>(row0, min(row0 + RT * 16, rows), rows, tok_offsets, pattern_id, P, n_patterns, [&](bool valid, int pid, int lo, int hi) {
     f32x4 acc[RT][CT];
@@ -81,7 +88,7 @@ __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restric
       for (int t = 0; t < RT; ++t) arow[t] = A + (size_t)min(row0 + t * 16 + i16, rows - 1) * K;
 #pragma unroll
       for (int u = 0; u < CT; ++u) brow[u] = Bbase + (size_t)pid * pattern_stride + (size_t)min(col0 + u * 16 + i16, N - 1) * K;
-      for (int c0 = wave; c0 < chunks; c0 += FN_WAVES * BATCH) {
+      for (int c0 = first + wave; c0 < chunks; c0 += FN_WAVES * BATCH) {
         f32x4 av[BATCH][RT], bv[BATCH][CT];
 #pragma unroll
         for (int b = 0; b < BATCH; ++b) {                    // chunks past the end are not read (uniform); the last one may be cut
@@ -132,8 +139,8 @@ constexpr int FS_BATCH = 2;
 
 // Y[rows][N] = Z[rows][K] * B_p[K][N].  N % 4 == 0; K arbitrary (A4: K % 4 == 0, 16-byte loads of Z).  A lane takes 4
 // consecutive columns of a factor row, so the four sub-tiles of a workgroup's 64 columns are interleaved: sub-tile e holds
-// columns 4 i + e, and a lane ends up with 4 consecutive columns of its 4 output rows.
-template <int RT, bool A4>
+// columns 4 i + e, and a lane ends up with 4 consecutive columns of its 4 output rows.  KS slices of Z, added in order where they are read.
+template <int RT, bool A4, int KS>
 __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restrict__ A, const float *__restrict__ Bbase,
                                                           size_t pattern_stride, int n_patterns, int rows, int N, int K,
                                                           const int32_t *__restrict__ tok_offsets,
@@ -163,9 +170,16 @@ __global__ __launch_bounds__(FS_WAVES * 64) void sgemm_nn(const float *__restric
           if (c < chunks) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-              if (A4) av[b][t] = k < K ? *reinterpret_cast<const f32x4 *>(arow[t] + k) : zero4;
-              else av[b][t] = f32x4{k < K ? arow[t][k] : 0.f, k + 1 < K ? arow[t][k + 1] : 0.f, k + 2 < K ? arow[t][k + 2] : 0.f,
-                                     k + 3 < K ? arow[t][k + 3] : 0.f};
+              f32x4 part[KS];
+#pragma unroll
+              for (int o = 0; o < KS; ++o) {
+                const float *z = arow[t] + (size_t)o * rows * K;
+                if (A4) part[o] = k < K ? *reinterpret_cast<const f32x4 *>(z + k) : zero4;
+                else part[o] = f32x4{k < K ? z[k] : 0.f, k + 1 < K ? z[k + 1] : 0.f, k + 2 < K ? z[k + 2] : 0.f, k + 3 < K ? z[k + 3] : 0.f};
+              }
+              av[b][t] = part[0];
+#pragma unroll
+              for (int o = 1; o < KS; ++o) av[b][t] += part[o];
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) bv[b][e] = k + e < K ? *reinterpret_cast<const f32x4 *>(bcol + (size_t)(k + e) * N) : zero4;
@@ -228,17 +242,39 @@ constexpr int F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 288, F32_FEW_WGS_LONG_PROMPT
 // Z are loaded (rS not a multiple of 4).  us, 16 / 32 rows: 100 ranks, 4 x 128, 2048 x 2048 (1024 workgroups of 16 rows) 19.6 / 17.1, 8 x 128 (2048) 32.3 / 29.7; 125
 // ranks, 2 x 300, 1032 x 2048 (1216) 22.1 / 24.4, 8 x 100, 256 x 2048 (1600) 23.3 / 25.5.
 constexpr int F32_NN_WGS = 1024, F32_NN_WGS_SINGLE = 1792;
+// First product of few 16 x 16 tiles: its reduction in 2, 4 or 8 slices, as many as leave a unit one workgroup and a slice sixteen chunks, each with a Z of its own
+// that the second product adds up.  A unit takes in about 50 GB/s, so half as many columns a workgroup take half the time.  Both products, us, one / the slices
+// chosen: 4 x 64 rows, 1024 x 1024, 128 ranks 10.6 / 9.2; 1 x 64 8.9 / 7.3; 1 x 16, 4096 x 1024 19.5 / 9.2; 4 x 16, 8192 x 256 34.2 / 11.7; 4 x 64, 2048 x 2048,
+// 100 ranks 15.1 / 11.8.  Up to two workgroups a unit: 1 x 256, 1024 x 1024 9.0 (one: 8.7), 4 x 64, 2048 x 2048 12.7, 4 x 128, 1024 x 1024 13.9 (13.4); slices of
+// eight chunks: 1 x 64, 1024 x 1024 7.8.  Error against 64 bits, rms, one / the slices chosen: 1024 columns 2.4e-7 / 1.9e-7, 8192 5.9e-7 / 2.4e-7.
+constexpr int F32_SPLIT_WGS = 256, F32_SPLIT_CHUNKS = 16, F32_MAX_SPLIT = 8;
+static int f32_slices(int rows, int rS, int n, int m, size_t workspace_bytes) {
+  const long long t16 = (rows + 15) / 16, wgs = t16 * ((rS + 15) / 16);
+  if (t16 * ((m + FS_TN - 1) / FS_TN) >= F32_NN_WGS) return 1;         // the second product's 32-row form takes one Z
+  int ks = 1;
+  while (ks < F32_MAX_SPLIT && wgs * ks * 2 <= F32_SPLIT_WGS && (n + 15) / 16 >= ks * 2 * F32_SPLIT_CHUNKS &&
+         (size_t)rows * rS * ks * 2 * sizeof(float) <= workspace_bytes)
+    ks *= 2;
+  return ks;
+}
+size_t f32_needed_bytes(int rows, int rS) { return round_up((size_t)rows * rS * sizeof(float), 256); }
+// room for the slices of as many rows or fewer, too
+size_t f32_workspace_bytes(int rows, int rS) {
+  const size_t need = f32_needed_bytes(rows, rS);
+  return std::max(need, std::min(need * F32_MAX_SPLIT, (size_t)F32_SPLIT_WGS * 16 * 16 * sizeof(float)));
+}
 
 int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, int rows, const int32_t *tok_offsets,
-                const int32_t *pattern_id, int P, float *Y, void *workspace, hipStream_t s) {
+                const int32_t *pattern_id, int P, float *Y, void *workspace, size_t workspace_bytes, hipStream_t s) {
   const int gs = L->R / L->G, rS = pt->k * gs;
   float *Z = reinterpret_cast<float *>(workspace);
   const float *V = (const float *)pt->Vt_S, *U = (const float *)pt->Ut_S;
   const size_t vs = (size_t)rS * L->n, us = (size_t)rS * L->m;
   const int t16 = (rows + 15) / 16, t32 = (rows + 31) / 32;
   const int nb16 = (rS + 15) / 16, nb32 = (rS + 31) / 32, nb2 = (L->m + FS_TN - 1) / FS_TN;
+  const int ks = f32_slices(rows, rS, L->n, L->m, workspace_bytes);
 #define PARSE_NT(RT_, CT_, B_)                                                                                             \
-  hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16), dim3(FN_WAVES * 64), 0, \
+  hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16, ks), dim3(FN_WAVES * 64), 0, \
                      s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
   const int avg = rows / P;
   const long long tiles = (long long)t16 * nb32;
@@ -246,18 +282,22 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
   const int few = !long_n ? F32_FEW_WGS : (!apart && avg >= F32_LONG_PROMPT ? F32_FEW_WGS_LONG_PROMPTS : F32_FEW_WGS_LONG);
   const bool many = nb32 * 10 <= nb16 * 6 && tiles >= F32_MANY_WGS && L->n >= F32_MANY_N &&
                     (apart || (long_n ? avg >= F32_MANY_ROWS_LONG : avg >= F32_MANY_ROWS && tiles >= F32_MANY_WGS_SHARED));
-  if (many && L->n >= (apart ? F32_FOUR_CHUNKS : F32_LONG)) PARSE_NT(2, 2, 4);
+  if (ks > 1) PARSE_NT(1, 1, 2);
+  else if (many && L->n >= (apart ? F32_FOUR_CHUNKS : F32_LONG)) PARSE_NT(2, 2, 4);
   else if (many) PARSE_NT(2, 2, 2);
   else if (nb32 * 10 >= nb16 * 6 || (long long)t16 * nb16 <= few) PARSE_NT(1, 1, 2);
   else PARSE_NT(1, 2, 2);
 #undef PARSE_NT
   PARSE_LAUNCH_CHECK();
   const bool a4 = rS % 4 == 0, rows32 = (long long)t16 * nb2 >= (a4 ? F32_NN_WGS : F32_NN_WGS_SINGLE);
-#define PARSE_NN(RT_, A4_)                                                                                                       \
-  hipLaunchKernelGGL((sgemm_nn<RT_, A4_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
+#define PARSE_NN(RT_, A4_, KS_)                                                                                                       \
+  hipLaunchKernelGGL((sgemm_nn<RT_, A4_, KS_>), dim3(RT_ == 2 ? t32 : t16, nb2), dim3(FS_WAVES * 64), 0, s, Z, U, us, pt->n_patterns, \
                      rows, L->m, rS, tok_offsets, pattern_id, P, Y)
-  if (rows32) { if (a4) PARSE_NN(2, true); else PARSE_NN(2, false); }
-  else { if (a4) PARSE_NN(1, true); else PARSE_NN(1, false); }
+  if (rows32) { if (a4) PARSE_NN(2, true, 1); else PARSE_NN(2, false, 1); }
+  else if (ks == 1) { if (a4) PARSE_NN(1, true, 1); else PARSE_NN(1, false, 1); }
+  else if (ks == 2) { if (a4) PARSE_NN(1, true, 2); else PARSE_NN(1, false, 2); }
+  else if (ks == 4) { if (a4) PARSE_NN(1, true, 4); else PARSE_NN(1, false, 4); }
+  else { if (a4) PARSE_NN(1, true, 8); else PARSE_NN(1, false, 8); }
 #undef PARSE_NN
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;

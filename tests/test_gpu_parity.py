@@ -1717,6 +1717,43 @@ def test_prefill_fp32_edges(n, m, R, G, k, lengths):
         assert_close(Yg[off[p]:off[p + 1]], Yref[off[p]:off[p + 1]], TOL_F32, f"prompt {p}")
 
 
+@pytest.mark.parametrize("n,m,R,G,k,lengths", [
+    (508, 64, 64, 4, 2, [20]),                   # 32 chunks, the last one cut: two slices
+    (492, 64, 64, 4, 2, [20]),                   # 31: one
+    (1032, 260, 200, 8, 3, [7, 1, 33]),          # 65: four, r_S = 75 (no 16-byte rows of Z), segments inside a 16-row block
+    (4100, 64, 32, 4, 2, [16, 17, 90]),          # 257: eight
+    (2056, 516, 250, 10, 4, [100, 40]),          # 129: two, 63 tiles
+    (1024, 512, 512, 4, 4, [64]),                # 128 tiles: two
+    (1024, 512, 512, 4, 4, [65]),                # one more row: one
+    (2048, 16384, 32, 4, 2, [64]),               # the second product in 32-row workgroups: one
+])
+def test_prefill_fp32_slices(n, m, R, G, k, lengths):
+    """fp32 layers whose first product is cut into slices, against the oracle (1e-4, the tolerance of every fp32 prefill; each value is the same fp32 products
+    in fewer, shorter sums): with the queried workspace, with room for two slices and for one; a prompt of no valid pattern gives zeros."""
+    say(f"prefill fp32 slices n={n} m={m} R={R} G={G} k={k} lengths={lengths}")
+    lay = si.make_layer(np.random.default_rng(981), n, m, R, G, "f32", fast=True)
+    rng = np.random.default_rng(982)
+    lengths = lengths + [3] if lengths[-1] % 16 not in (0, 1) else lengths
+    P, off = len(lengths), si.offsets_from_lengths(lengths)
+    subs = np.stack([np.sort(rng.choice(G, size=k, replace=False)) for _ in lengths]).astype(np.int32)
+    X = si.make_tokens(rng, int(off[-1]), n, "f32")
+    Yref = po.forward(*oracle_factors(lay), lay.gs, X.astype(np.float64), off, subs)
+    dl, sd = upload_layer(lay), i32(subs)
+    pid, perm, boff, npat, rep = pa.bucket_patterns(sd, k)
+    Vs, Us = pa.pack_patterns(dl, sd, k, k, rep, npat, P)
+    if P > 1:
+        pid = pid.clone()
+        pid[P - 1] = -1
+        Yref[off[P - 1]:] = 0.0
+    one = (int(off[-1]) * k * lay.gs * 4 + 255) // 256 * 256
+    for size in (pa.lowrank_workspace_bytes(pa.PARSE_PREFILL, dl, int(off[-1]), k, P, P), 2 * one, one):
+        ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device=DEV)       # not numbers
+        Y = pa.lowrank_forward(pa.PARSE_PREFILL, dl, pa.Patterns(k, P, Vs, Us), upload_tokens(X, "f32"), i32(off), pid, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert (ws[size:] == 0xFF).all(), "written past the workspace"
+        assert_close(Y.cpu().numpy().astype(np.float64), Yref, TOL_F32, f"workspace of {size} bytes")
+
+
 @pytest.mark.parametrize("n,m,R,G,lengths", [
     (128, 128, 64, 2, [1]),                          # one token, half a rank tile
     (256, 128, 96, 3, [33, 1, 30, 1]),               # 64 x 64 tiles, a rank tile past the end, prompts inside a token block
