@@ -45,33 +45,35 @@ int launch_pool_finish(const float *partial, int Q, int rows, int d, const int32
   return PARSE_OK;
 }
 
-// scores[p][g] = <Wr[g], e_p>.  grid (router rows in units of 4 RPW, prompts in units of PB), block 256: wavefront w owns RPW rows
+// scores[p][g] = <Wr[g], e_p>.  grid (router rows in units of WAVES RPW, prompts in units of PB), block 64 WAVES: wavefront w owns RPW rows
 // for the PB prompts of the block; lane l adds columns 256 i + 4 l .. + 3 for i = 0, 1, ..., and the 64 lanes are added at the end (the
 // same order for all RPW and PB: same inputs, same bits).  Bound by the stream of Wr and, for eight prompts, by the embeddings that come in beside
 // it: parts of RK_PART columns, rows and embeddings of the next ones on their way while one is added up; the embeddings go through LDS,
-// where four wavefronts share them.
+// where the wavefronts share them.
 constexpr int RK_PART = 1024, RK_STEPS = RK_PART / 256, RK_AHEAD = 2;
-template <int RPW, int PB>
-__global__ __launch_bounds__(256, 1) void rank_scores(const float *__restrict__ Wr, const float *__restrict__ emb, int G,
-                                                      int d, int P, float *__restrict__ scores) {
+template <int RPW, int PB, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 1) void rank_scores(const float *__restrict__ Wr, const float *__restrict__ emb, int G,
+                                                              int d, int P, float *__restrict__ scores) {
   constexpr int BUFS = RPW == 1 ? 2 : 1;                // one for three workgroups a unit instead of two
   __shared__ f32x4 es[BUFS][PB][RK_PART / 4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g0 = (blockIdx.x * 4 + wave) * RPW, p0 = blockIdx.y * PB;
+  const int g0 = (blockIdx.x * WAVES + wave) * RPW, p0 = blockIdx.y * PB;
+  constexpr int EP = PB * 4 / WAVES;                    // embeddings of a thread: e0, e0 + WAVES / 4, ...
+  const int e0 = threadIdx.x >> 8, ec = threadIdx.x & 255;
   float acc[RPW][PB];
 #pragma unroll
   for (int r = 0; r < RPW; ++r)
 #pragma unroll
     for (int p = 0; p < PB; ++p) acc[r][p] = 0.f;
-  const float *wrow[RPW], *erow[PB];
+  const float *wrow[RPW], *erow[EP];
 #pragma unroll
   for (int r = 0; r < RPW; ++r) wrow[r] = Wr + (size_t)min(g0 + r, G - 1) * d;
 #pragma unroll
-  for (int p = 0; p < PB; ++p) erow[p] = emb + (size_t)min(p0 + p, P - 1) * d;
-  f32x4 w[RK_AHEAD][RPW][RK_STEPS], e[RK_AHEAD][PB];
-  auto load = [&](int base, f32x4 (&wv)[RPW][RK_STEPS], f32x4 (&ev)[PB]) {   // columns past the end: the last four again, not used
+  for (int i = 0; i < EP; ++i) erow[i] = emb + (size_t)min(p0 + e0 + i * (WAVES / 4), P - 1) * d;
+  f32x4 w[RK_AHEAD][RPW][RK_STEPS], e[RK_AHEAD][EP];
+  auto load = [&](int base, f32x4 (&wv)[RPW][RK_STEPS], f32x4 (&ev)[EP]) {   // columns past the end: the last four again, not used
 #pragma unroll
-    for (int p = 0; p < PB; ++p) ev[p] = *reinterpret_cast<const f32x4 *>(erow[p] + min(base + (int)threadIdx.x * 4, d - 4));
+    for (int i = 0; i < EP; ++i) ev[i] = *reinterpret_cast<const f32x4 *>(erow[i] + min(base + ec * 4, d - 4));
 #pragma unroll
     for (int i = 0; i < RK_STEPS; ++i)
 #pragma unroll
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(256, 1) void rank_scores(const float *__restrict__ 
       if (BUFS == 1 && base > 0)                       // the part before is read
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-      for (int p = 0; p < PB; ++p) es[buf][p][threadIdx.x] = e[u][p];
+      for (int i = 0; i < EP; ++i) es[buf][e0 + i * (WAVES / 4)][ec] = e[u][i];
       // everybody's piece is there (of two buffers the other one is read by now).  No fence: loads on their way stay so.
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
@@ -160,6 +162,9 @@ __global__ __launch_bounds__(256) void rank_scores_narrow(const float *__restric
 // which share what they read of LDS, and one buffer, so that three workgroups fit a unit.  The whole routing call, us, the kernel without LDS / one row / two
 // rows, 4096 columns: 2048 ranks x 8 prompts 30.6 / 27.6 / 29.2, x 1 23.2 / 17.5 / 18.0, x 16 29.5 / 31.9 / 28.7, x 20 36.3 / 41.6 / 33.3, 512 x 8 23.3 / 17.5 /
 // 20.5, 8192 x 8 63.0 / 60.9 / 50.0, 8192 x 1 56.7 / 41.7 / 42.8; 1024 columns, 512 x 8 17.8 / 13.9 / 15.7; same bits.
+// Eight prompts and two workgroups of four wavefronts on some units: one of eight, and the embeddings come in once a unit.  The call, 256 workgroups of four / of
+// eight: 4096 columns, 2048 ranks x 8 prompts 23.9 / 22.6, 1040 x 8 21.8 / 20.3, 1024 x 16 21.5 / 20.3; 2048 columns, 2048 x 8 19.0 / 18.6; 512 columns 14.7 /
+// 14.5; with a unit to each of four the same.
 // Without LDS for more than four prompts and 1024 workgroups of one row where over a fifth of the parts' columns is past the last one: 144 columns, 3576 ranks
 // x 12 prompts 18.7 / 23.9 / 21.9, 1032, 6442 x 8 26.3 / 33.5 / 29.6, 2136, 6311 x 16 43.6 / 57.6 / 45.2; with fewer, 1480 workgroups x 4 prompts of 88 columns 20.2 /
 // 19.2 / 18.8.  Over 300 calls of 32 to 16384 columns, 32 to 8192 ranks and 1 to 64 prompts 18 % less time than without LDS throughout, 8 % more at worst.
@@ -176,12 +181,19 @@ static int launch_rank_scores(const float *Wr, const float *emb, int G, int d, i
   }
   if constexpr (PB > 2) {
     if (wgs > 512) {
-      hipLaunchKernelGGL((rank_scores<2, PB>), dim3((G + 7) / 8, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+      hipLaunchKernelGGL((rank_scores<2, PB, 4>), dim3((G + 7) / 8, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
       PARSE_LAUNCH_CHECK();
       return PARSE_OK;
     }
   }
-  hipLaunchKernelGGL((rank_scores<1, PB>), dim3((G + 3) / 4, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
+  if constexpr (PB == RK_PB) {
+    if (wgs > 256) {
+      hipLaunchKernelGGL((rank_scores<1, PB, 8>), dim3((G + 7) / 8, blocks), dim3(512), 0, s, Wr, emb, G, d, P, scores);
+      PARSE_LAUNCH_CHECK();
+      return PARSE_OK;
+    }
+  }
+  hipLaunchKernelGGL((rank_scores<1, PB, 4>), dim3((G + 3) / 4, blocks), dim3(256), 0, s, Wr, emb, G, d, P, scores);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

@@ -1437,6 +1437,12 @@ def test_rank_scores_at_the_edges_of_their_tiles(P, d, G):
     assert (b[:64] == 7.0).all() and (b[64 + P * G:] == 7.0).all()
 
 
+@pytest.mark.parametrize("P,d,G", [(5, 1032, 1025), (8, 2056, 2045), (6, 264, 1031), (9, 4104, 516), (16, 1288, 1021)])
+def test_rank_scores_of_eight_wavefronts(P, d, G):
+    """Workgroups of eight rows: the last one not full, part of a part of the columns, a second block of prompts with one."""
+    test_rank_scores_at_the_edges_of_their_tiles(P, d, G)
+
+
 def test_rank_granular_route_pack_and_prefill():
     """The paper's own formulation (Sec. 4.1, Eq. 4-5): one expert per rank, router R^d -> R^R, top-K ranks;
     the K scattered rank rows are aggregated into one block (Sec. 4.4) and the prefill kernels run on it."""
