@@ -57,8 +57,8 @@ __device__ __forceinline__ void for_segments(int row0, int row_end, int rows, co
 constexpr int FN_WAVES = 8;          // first product: wavefronts of a workgroup = parts of the reduction
 
 // Z[rows][N] = X[rows][K] * B_p[N][K]^T.  K % 4 == 0.  RT x CT blocks of 16 token rows x 16 ranks per workgroup; a
-// wavefront requests BATCH reduction chunks at a time.  16 x 16 tiles: gridDim.z slices of the reduction, each with its own Z.
-template <int RT, int CT, int BATCH>
+// wavefront requests BATCH reduction chunks at a time.  KS slices of the reduction (blockIdx.z), each with its own Z.
+template <int RT, int CT, int BATCH, int KS>
 __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restrict__ A, const float *__restrict__ Bbase,
                                                           size_t pattern_stride, int n_patterns, int rows, int N, int K,
                                                           const int32_t *__restrict__ tok_offsets,
@@ -69,10 +69,10 @@ __global__ __launch_bounds__(FN_WAVES * 64) void sgemm_nt(const float *__restric
   const int i16 = lane & 15, g = lane >> 4;
   const int row0 = blockIdx.x * RT * 16, col0 = blockIdx.y * TN;
   int first = 0, chunks = (K + 15) / 16;
-  if constexpr (RT == 1 && CT == 1) {
+  if constexpr (KS > 1) {
     const int all = chunks;
-    first = all * (int)blockIdx.z / (int)gridDim.z;
-    chunks = all * ((int)blockIdx.z + 1) / (int)gridDim.z;
+    first = all * (int)blockIdx.z / KS;
+    chunks = all * ((int)blockIdx.z + 1) / KS;
     C += (size_t)blockIdx.z * rows * N;
   }
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -244,9 +244,11 @@ constexpr int F32_FEW_WGS = 400, F32_FEW_WGS_LONG = 288, F32_FEW_WGS_LONG_PROMPT
 constexpr int F32_NN_WGS = 1024, F32_NN_WGS_SINGLE = 1792;
 // First product of few 16 x 16 tiles: its reduction in 2, 4 or 8 slices, as many as leave a unit one workgroup and a slice sixteen chunks, each with a Z of its own
 // that the second product adds up.  A unit takes in about 50 GB/s, so half as many columns a workgroup take half the time.  Both products, us, one / the slices
-// chosen: 4 x 64 rows, 1024 x 1024, 128 ranks 10.6 / 9.2; 1 x 64 8.9 / 7.3; 1 x 16, 4096 x 1024 19.5 / 9.2; 4 x 16, 8192 x 256 34.2 / 11.7; 4 x 64, 2048 x 2048,
+// chosen: 4 x 64 rows, 1024 x 1024, 128 ranks 10.6 / 9.2; 1 x 64 8.9 / 7.3; 1 x 16, 4096 x 1024 19.5 / 9.1; 4 x 16, 8192 x 256 34.2 / 11.7; 4 x 64, 2048 x 2048,
 // 100 ranks 15.1 / 11.8.  Up to two workgroups a unit: 1 x 256, 1024 x 1024 9.0 (one: 8.7), 4 x 64, 2048 x 2048 12.7, 4 x 128, 1024 x 1024 13.9 (13.4); slices of
 // eight chunks: 1 x 64, 1024 x 1024 7.8.  Error against 64 bits, rms, one / the slices chosen: 1024 columns 2.4e-7 / 1.9e-7, 8192 5.9e-7 / 2.4e-7.
+// KS is a template argument because gridDim is not an argument of the launch but read from memory of its own: a routed pass of 4 x 64 rows, launched call by
+// call, 24.7 unsplit, 27.1 with gridDim.z slices, 23.5 with KS.
 constexpr int F32_SPLIT_WGS = 256, F32_SPLIT_CHUNKS = 16, F32_MAX_SPLIT = 8;
 static int f32_slices(int rows, int rS, int n, int m, size_t workspace_bytes) {
   const long long t16 = (rows + 15) / 16, wgs = t16 * ((rS + 15) / 16);
@@ -273,8 +275,8 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
   const int t16 = (rows + 15) / 16, t32 = (rows + 31) / 32;
   const int nb16 = (rS + 15) / 16, nb32 = (rS + 31) / 32, nb2 = (L->m + FS_TN - 1) / FS_TN;
   const int ks = f32_slices(rows, rS, L->n, L->m, workspace_bytes);
-#define PARSE_NT(RT_, CT_, B_)                                                                                             \
-  hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16, ks), dim3(FN_WAVES * 64), 0, \
+#define PARSE_NT(RT_, CT_, B_, KS_)                                                                                             \
+  hipLaunchKernelGGL((sgemm_nt<RT_, CT_, B_, KS_>), dim3(RT_ == 2 ? t32 : t16, CT_ == 2 ? nb32 : nb16, KS_), dim3(FN_WAVES * 64), 0, \
                      s, X, V, vs, pt->n_patterns, rows, rS, L->n, tok_offsets, pattern_id, P, Z)
   const int avg = rows / P;
   const long long tiles = (long long)t16 * nb32;
@@ -282,11 +284,13 @@ int forward_f32(const parse_layer *L, const parse_patterns *pt, const float *X, 
   const int few = !long_n ? F32_FEW_WGS : (!apart && avg >= F32_LONG_PROMPT ? F32_FEW_WGS_LONG_PROMPTS : F32_FEW_WGS_LONG);
   const bool many = nb32 * 10 <= nb16 * 6 && tiles >= F32_MANY_WGS && L->n >= F32_MANY_N &&
                     (apart || (long_n ? avg >= F32_MANY_ROWS_LONG : avg >= F32_MANY_ROWS && tiles >= F32_MANY_WGS_SHARED));
-  if (ks > 1) PARSE_NT(1, 1, 2);
-  else if (many && L->n >= (apart ? F32_FOUR_CHUNKS : F32_LONG)) PARSE_NT(2, 2, 4);
-  else if (many) PARSE_NT(2, 2, 2);
-  else if (nb32 * 10 >= nb16 * 6 || (long long)t16 * nb16 <= few) PARSE_NT(1, 1, 2);
-  else PARSE_NT(1, 2, 2);
+  if (ks == 8) PARSE_NT(1, 1, 2, 8);
+  else if (ks == 4) PARSE_NT(1, 1, 2, 4);
+  else if (ks == 2) PARSE_NT(1, 1, 2, 2);
+  else if (many && L->n >= (apart ? F32_FOUR_CHUNKS : F32_LONG)) PARSE_NT(2, 2, 4, 1);
+  else if (many) PARSE_NT(2, 2, 2, 1);
+  else if (nb32 * 10 >= nb16 * 6 || (long long)t16 * nb16 <= few) PARSE_NT(1, 1, 2, 1);
+  else PARSE_NT(1, 2, 2, 1);
 #undef PARSE_NT
   PARSE_LAUNCH_CHECK();
   const bool a4 = rS % 4 == 0, rows32 = (long long)t16 * nb2 >= (a4 ? F32_NN_WGS : F32_NN_WGS_SINGLE);
