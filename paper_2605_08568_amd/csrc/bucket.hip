@@ -16,7 +16,7 @@ __global__ __launch_bounds__(FEW ? 64 : 1024) void bucket_patterns(const int32_t
                                                         int32_t *__restrict__ pattern_id, int32_t *__restrict__ perm,
                                                         int32_t *__restrict__ bucket_off,
                                                         int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
-  bucket_body<FEW>(subset, P, k, stride, pattern_id, perm, bucket_off, n_patterns, rep);
+  bucket_body<FEW>(subset, P, k, stride, pattern_id, perm, bucket_off, n_patterns, rep, (P + 63) / 64 * 64);
 }
 
 }  // namespace parse

@@ -1,4 +1,4 @@
-// Body of the bucketing kernel (one workgroup, blockDim.x >= P a multiple of 64), shared by the stand-alone launch and
+// Body of the bucketing kernel (one workgroup of T >= P lanes, a multiple of 64), shared by the stand-alone launch and
 // the launch that also builds the prefill plan.
 #pragma once
 #include "common.hpp"
@@ -11,7 +11,7 @@ constexpr int kBucketMaxP = 1024;
 // kernel the other one was 0.3-0.6 us slower.
 constexpr int kFewPrompts = 16;
 
-// inclusive scan of v[0..T) in LDS, T = blockDim.x a multiple of 64; every lane takes part
+// inclusive scan of v[0..T) in LDS, T the workgroup's lanes, a multiple of 64; every lane takes part
 __device__ __forceinline__ void block_scan_inclusive(int32_t *v, int T) {
   const int p = threadIdx.x;
   for (int o = 1; o < T; o <<= 1) {
@@ -72,7 +72,7 @@ template <bool FEW>
 __device__ __forceinline__ void bucket_body(const int32_t *__restrict__ subset, int P, int k, int stride,
                                                         int32_t *__restrict__ pattern_id, int32_t *__restrict__ perm,
                                                         int32_t *__restrict__ bucket_off,
-                                                        int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep) {
+                                                        int32_t *__restrict__ n_patterns, int32_t *__restrict__ rep, int T) {
   if constexpr (FEW) {
     if (threadIdx.x < 64) bucket_wave(subset, P, k, stride, pattern_id, perm, bucket_off, n_patterns, rep);
     return;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void bucket_body(const int32_t *__restrict__ subset, 
   __shared__ int32_t scan[1024];   // inclusive scan of "is representative", later of the pattern sizes
   __shared__ int32_t pid[1024];
   __shared__ int32_t cnt[1025];
-  const int p = threadIdx.x, T = blockDim.x;
+  const int p = threadIdx.x;
   const int32_t *mine = subset + (size_t)min(p, P - 1) * stride;
   unsigned long long h = 0x9E3779B97F4A7C15ull;
   for (int i = 0; i < k; ++i) {   // independent loads, then a sequential mix

@@ -88,11 +88,12 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
                                                 float tau, int sequential, int32_t *__restrict__ count,
                                                 int32_t *__restrict__ entry_out, uint8_t *__restrict__ hit_out,
                                                 float *__restrict__ sim_out, int32_t *__restrict__ src_out) {
+  constexpr int threads = 1024;
   extern __shared__ float lds_f[];
   float *best_sim = lds_f;                                         // [P]
   int32_t *best_idx = reinterpret_cast<int32_t *>(lds_f + P);      // [P]
   int32_t *ins_list = best_idx + P;                                // [P]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = threads >> 6;
   const int count0 = *count;
   for (int p = wave; p < P; p += nwaves) {
     float bs = -INFINITY;
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(1024) void resolve(const float *__restrict__ sims, 
   }
   __syncthreads();
   if (!sequential) {
-    for (int p = threadIdx.x; p < P; p += blockDim.x) {
+    for (int p = threadIdx.x; p < P; p += threads) {
       const bool h = best_idx[p] >= 0 && best_sim[p] >= tau;
       entry_out[p] = h ? best_idx[p] : -1;
       hit_out[p] = h ? 1 : 0;
@@ -173,13 +174,13 @@ __global__ __launch_bounds__(256) void route_or_gather(const float *__restrict__
   if (!do_route) return;
   const int from = h ? src[p] : p;  // the embedding that defines the key of the answering entry
   const bool owner = !h && ent >= 0;   // this prompt's miss created entry `ent`
-  for (int c = threadIdx.x; c < d; c += blockDim.x) {
+  for (int c = threadIdx.x; c < d; c += 256) {
     const float v = E[(size_t)from * d + c];
     e[c] = v;
     if (l == 0 && owner) keys[(size_t)ent * d + c] = v;
   }
   __syncthreads();
-  block_router_scores(Wr + (size_t)l * G * d, e, d, G, s);
+  block_router_scores(Wr + (size_t)l * G * d, e, d, G, s, 256 / 64);
   int32_t *sel = reinterpret_cast<int32_t *>(s + 64);  // [64] after the scores
   if (threadIdx.x < 64) wave_topk_ascending(s, G, k, sel, n_shared);
   __syncthreads();
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
     const float *__restrict__ sims, int ld, int capacity, int P, float tau, const int32_t *__restrict__ count_in,
     int32_t *__restrict__ count_out, const float *__restrict__ E, int d, const float *__restrict__ Wr, int G, int L, int k,
     int32_t *__restrict__ entry_out, uint8_t *__restrict__ hit_out, float *__restrict__ sim_out,
-    float *__restrict__ keys, int32_t *__restrict__ values, int32_t *__restrict__ subset_out, int n_shared) {
+    float *__restrict__ keys, int32_t *__restrict__ values, int32_t *__restrict__ subset_out, int n_shared, int threads) {
   extern __shared__ float lds[];
   float *e = lds, *s = lds + d;
   __shared__ float best_sim[kSmallBatch];
@@ -224,10 +225,10 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
   __shared__ int32_t my_ent, my_src, my_hit, total_ins;
   __shared__ float peer[kSmallBatch][kSmallBatch + 1];   // peer[q][i] = similarity of prompt q with earlier prompt i
   const int l = blockIdx.x, p = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = threads >> 6;
   const int count0 = min(*count_in, capacity);
   // the walk below is sequential: everything it reads is fetched here, all at once
-  for (int t = threadIdx.x; t < (p + 1) * P; t += blockDim.x) {
+  for (int t = threadIdx.x; t < (p + 1) * P; t += threads) {
     const int q = t / P, i = t - q * P;
     if (i < q) peer[q][i] = sims[(size_t)q * ld + capacity + i];
   }
@@ -296,13 +297,13 @@ __global__ __launch_bounds__(kSmallThreads) void resolve_route_or_gather(
   }
   const int from = h ? my_src : p;     // the embedding that defines the key of the answering entry
   const bool owner = !h && ent >= 0;   // this prompt's miss created entry `ent`
-  for (int c = threadIdx.x; c < d; c += blockDim.x) {
+  for (int c = threadIdx.x; c < d; c += threads) {
     const float v = E[(size_t)from * d + c];
     e[c] = v;
     if (l == 0 && owner) keys[(size_t)ent * d + c] = v;
   }
   __syncthreads();
-  block_router_scores(Wr + (size_t)l * G * d, e, d, G, s);
+  block_router_scores(Wr + (size_t)l * G * d, e, d, G, s, nwaves);
   int32_t *sel = reinterpret_cast<int32_t *>(s + 64);  // [64] after the scores
   if (threadIdx.x < 64) wave_topk_ascending(s, G, k, sel, n_shared);
   __syncthreads();
@@ -321,8 +322,8 @@ __global__ void append_entry(const float *__restrict__ emb, const int32_t *__res
     if (threadIdx.x == 0) *dropped += 1;
     return;
   }
-  for (int c = threadIdx.x; c < d; c += blockDim.x) keys[(size_t)ent * d + c] = emb[c];
-  for (int i = threadIdx.x; i < Lk; i += blockDim.x) values[(size_t)ent * Lk + i] = subsets[i];
+  for (int c = threadIdx.x; c < d; c += 256) keys[(size_t)ent * d + c] = emb[c];
+  for (int i = threadIdx.x; i < Lk; i += 256) values[(size_t)ent * Lk + i] = subsets[i];
   __syncthreads();   // one workgroup: every lane has read *count before it changes
   if (threadIdx.x == 0) *count = ent + 1;
 }
@@ -479,7 +480,7 @@ int parse_cache_lookup_or_route(parse_cache *c, const float *emb, int32_t P, flo
     PARSE_ALLOW_LDS(resolve_route_or_gather, (size_t)(c->d + 128) * sizeof(float));
     hipLaunchKernelGGL(resolve_route_or_gather, dim3(c->L, P), dim3(small_threads(c->L, P)), (size_t)(c->d + 128) * sizeof(float), s,
                        c->sims, ld, c->capacity, P, tau, c->count + c->cur, c->count + (c->cur ^ 1), emb, c->d, Wr, G, c->L, c->k,
-                       entry, hit, sim_out, c->keys, c->values, subset_out, c->n_shared);
+                       entry, hit, sim_out, c->keys, c->values, subset_out, c->n_shared, small_threads(c->L, P));
     PARSE_LAUNCH_CHECK();
     c->cur ^= 1;
     return PARSE_OK;

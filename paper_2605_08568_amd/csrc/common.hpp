@@ -53,6 +53,9 @@ void set_hip_error(hipError_t e, const char *where);
       PARSE_HIP_TRY(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes))); \
   } while (0)
 
+// Kernels are told their grid and block sizes or work them out: gridDim and blockDim are no arguments of the launch but another 256 bytes that the runtime writes
+// for each launch, and the kernel reads them from there.  Five processes each, with / without, launched call by call: a step of one prompt of 77 tokens (eight launches)
+// 34.3 to 38.4 us / 34.1 to 35.6, a routed fp32 pass (six) 24.7 to 25.9 / 23.4 to 24.8.
 #define PARSE_LAUNCH_CHECK()                        \
   do {                                              \
     hipError_t _e = hipGetLastError();              \

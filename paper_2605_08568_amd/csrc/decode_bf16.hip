@@ -61,6 +61,7 @@ struct DecArgs {
   const uint16_t *x;
   int B, n;
   int KS;                      // decode_zr: slices of the reduction range
+  int wgs;                     // decode_zp: workgroups
 };
 
 struct DecPlanArgs {
@@ -502,7 +503,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
 
 // ---------------------------------------------------------------------------------------------------------
 // decode_zp: decode_zv's tasks of eight ranks for up to sixteen sequences, with x, all of it, staged once per compute unit: one workgroup a unit takes every
-// gridDim-th task.  A task is done in chunks of DEPTH factor operands a wavefront; the next chunk, of this task or the next one, is on its way while
+// wgs-th task.  A task is done in chunks of DEPTH factor operands a wavefront; the next chunk, of this task or the next one, is on its way while
 // one is multiplied.  Bound by what a unit takes in: x once and its share of the factor, where a workgroup of sixteen ranks that reads x for itself takes
 // in as much of x as of the factor and a unit with two of them twice that (twelve sequences, a 4096 x 11008 block, us: q/k/v 14.1 -> 10.5, o 8.2 -> 6.1,
 // gate/up 9.6 -> 9.0; a call of 512 ranks 15.2 (32-wide) / 10.9 / 9.2).
@@ -593,7 +594,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
     const int c = ONE ? 0 : chunk;
     if (ONE || ++chunk == chunks) {          // uniform
       chunk = 0;
-      id += gridDim.x;
+      id += a.wgs;
       task = task_of(id);
     }
     request(task, ONE ? 0 : chunk, w);
@@ -1134,6 +1135,7 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
     int wgs = 0;
     for (int l = 0; l < n_layers; ++l) wgs = std::max(wgs, layers[l].R / 8);
     wgs = std::min(wgs * n_layers, n_cu);
+    a.wgs = wgs;
     const int share = ((nkb + 3) / 4 + DV_WAVES - 1) / DV_WAVES;
     const size_t lds = (size_t)B * dv_xstride(a.n);
     const int xp = (B * (a.n / 8) + DV_THREADS - 1) / DV_THREADS;                        // pieces of x of a thread

@@ -25,7 +25,7 @@ constexpr int kPackWindow = 2048;   // patterns whose work list a workgroup hold
 // 54.0, 2 86.7 / 85.8 / 88.7, 4 129 / 130 / 139, 24 569 / 606 / 664.
 // A fixed grid walks the work list: every workgroup first lists (in LDS) the patterns that have anything to
 // copy -- a batch whose prompts all hit the cache ends here, after one pass over the hit flags -- then takes
-// every gridDim.x-th task; a task = (listed pattern, one of its 2k slabs, one chunk of the slab): 32 KiB, or 8 KiB where those
+// every wgs-th task; a task = (listed pattern, one of its 2k slabs, one chunk of the slab): 32 KiB, or 8 KiB where those
 // would be one task a unit at most.  us, 32 KiB / 8 KiB: four patterns of 128 ranks of an fp32 1024 x 1024 layer (128 tasks of 32 KiB) 5.1 / 4.3, one 4.65 / 3.65; one
 // of 256 ranks of a bf16 4096 x 4096 layer (128) 5.25 / 4.5, of 128 of 4096 x 11008 (172) 5.2 / 4.75; of 1024 of 4096 x 4096 (1024) 8.65 / 9.7, eight 34 / 42.
 // The list is in ascending pattern order in every workgroup (a strided walk over lists that differ from
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kCopyThreads) void pack_slabs(const char *__restric
                                                            const int32_t *__restrict__ slot,
                                                            const uint8_t *__restrict__ skip, int n_slots,
                                                            const int32_t *__restrict__ n_patterns, int max_patterns,
-                                                           char *__restrict__ Vt_S, char *__restrict__ Ut_S) {
+                                                           char *__restrict__ Vt_S, char *__restrict__ Ut_S, int wgs) {
   __shared__ int32_t act[kPackWindow];
   __shared__ int32_t n_act;
   __shared__ int32_t wave_cnt[kCopyThreads / 64];
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kCopyThreads) void pack_slabs(const char *__restric
       chunks = (int)((big + kCopyChunk / 4 - 1) / (kCopyChunk / 4));
     }
     const long long total = (long long)n_act * 2 * k * chunks;
-    for (long long t = blockIdx.x; t < total; t += gridDim.x) {
+    for (long long t = blockIdx.x; t < total; t += wgs) {
       const int c = (int)(t % chunks);
       const int y = (int)((t / chunks) % (2 * k));
       const int j = act[t / ((long long)chunks * 2 * k)];
@@ -158,7 +158,7 @@ static int launch_pack(const parse_layer *L, const int32_t *subset, int subset_s
   const unsigned grid = (unsigned)(tasks < 1024 ? tasks : 1024);   // four workgroups per compute unit walk the list
   hipLaunchKernelGGL(pack_slabs, dim3(grid), dim3(kCopyThreads), 0, s, (const char *)L->Vt, (const char *)L->Ut, vb, ub,
                      L->G, k, subset, subset_stride, rep, slot, skip, n_slots, n_patterns, max_patterns, (char *)Vt_S,
-                     (char *)Ut_S);
+                     (char *)Ut_S, (int)grid);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

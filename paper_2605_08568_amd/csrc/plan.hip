@@ -195,8 +195,8 @@ __device__ __forceinline__ void plan_body(const int32_t *__restrict__ tok_offset
 template <bool FEW>
 __global__ __launch_bounds__(PLAN_THREADS) void plan_build(const int32_t *__restrict__ tok_offsets,
                                                            const int32_t *__restrict__ pattern_id, int P, int rows,
-                                                           int NP, int cap, int32_t *__restrict__ plan) {
-  plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x);
+                                                           int NP, int cap, int32_t *__restrict__ plan, int wgs) {
+  plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, wgs);
 }
 
 // The plan and the buckets of a batch in one launch (they depend on the same probe results and not on each other): the
@@ -209,11 +209,11 @@ struct BucketArgs {
 template <bool FEW>
 __global__ __launch_bounds__(PLAN_THREADS) void bucket_and_plan(BucketArgs b, const int32_t *__restrict__ tok_offsets,
                                                                 const int32_t *__restrict__ pattern_id, int P, int rows,
-                                                                int NP, int cap, int32_t *__restrict__ plan) {
-  if (blockIdx.x + 1 == gridDim.x)     // uniform
-    bucket_body<FEW>(b.subset, P, b.k, b.stride, b.pattern_id, b.perm, b.bucket_off, b.n_patterns, b.rep);
+                                                                int NP, int cap, int32_t *__restrict__ plan, int wgs) {
+  if ((int)blockIdx.x + 1 == wgs)      // uniform
+    bucket_body<FEW>(b.subset, P, b.k, b.stride, b.pattern_id, b.perm, b.bucket_off, b.n_patterns, b.rep, PLAN_THREADS);
   else
-    plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, gridDim.x - 1);
+    plan_body<FEW>(tok_offsets, pattern_id, P, rows, NP, cap, plan, blockIdx.x, wgs - 1);
 }
 
 size_t prefill_plan_bytes(int rows, int P, int n_patterns) {
@@ -231,7 +231,7 @@ int build_prefill_plan(const int32_t *tok_offsets, const int32_t *pattern_id, in
                        int32_t *plan, hipStream_t s) {
   const int cap = plan_capacity_tiles(rows, P, n_patterns);
   const int grid = plan_grid(rows);
-  hipLaunchKernelGGL((P <= kFewPrompts ? plan_build<true> : plan_build<false>), dim3(grid), dim3(PLAN_THREADS), 0, s, tok_offsets, pattern_id, P, rows, n_patterns, cap, plan);
+  hipLaunchKernelGGL((P <= kFewPrompts ? plan_build<true> : plan_build<false>), dim3(grid), dim3(PLAN_THREADS), 0, s, tok_offsets, pattern_id, P, rows, n_patterns, cap, plan, grid);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }
@@ -276,7 +276,7 @@ int parse_bucket_and_plan(const int32_t *subset, int32_t P, int32_t k, int32_t s
   }
   const BucketArgs b{subset, k, subset_stride, pattern_id_out, perm, bucket_off, n_patterns_out, rep};
   hipLaunchKernelGGL((P <= kFewPrompts ? bucket_and_plan<true> : bucket_and_plan<false>), dim3(plan_grid(rows) + 1), dim3(PLAN_THREADS), 0, s, b, tok_offsets, plan_pattern_id, P,
-                     rows, n_patterns, plan_capacity_tiles(rows, P, n_patterns), (int32_t *)plan);
+                     rows, n_patterns, plan_capacity_tiles(rows, P, n_patterns), (int32_t *)plan, plan_grid(rows) + 1);
   PARSE_LAUNCH_CHECK();
   return PARSE_OK;
 }

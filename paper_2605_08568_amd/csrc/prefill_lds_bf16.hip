@@ -562,13 +562,13 @@ __global__ __launch_bounds__(512) void gemm_first256(LgArgs a) {
 // bf16.  One thread per piece, over the plan's virtual rows and all layers of the call (grid.y); padding rows hold nothing
 // and are passed over (the second product's results for them are not stored either).
 template <int ONE>
-__global__ __launch_bounds__(256) void z_combine(LgArgs a) {
+__global__ __launch_bounds__(256) void z_combine(LgArgs a, int wgs) {
   const LgLayer &ly = a.L[blockIdx.y];
   const int M = ly.M, ks = a.ks;
   const LgPlan<ONE> plan(a);
   const size_t pieces = (size_t)(plan.virtual_rows() / 32) * (M / 16) * 64;    // virtual rows / 32 token blocks x reduction blocks x lanes
   const size_t slice = (size_t)a.cap * 8 * (M / 16) * 512;           // floats per slice
-  for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < pieces; o += (size_t)gridDim.x * 256) {
+  for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < pieces; o += (size_t)wgs * 256) {
     const size_t tb = o / ((size_t)(M / 16) * 64);
     if (plan.token_row((int)(tb * 32 + (o & 31))) < 0) continue;
     const float *src = ly.Pz + o * 8;
@@ -786,7 +786,8 @@ int forward_prefill_planned_multi_bf16(const PfArgs *p, int n_layers, const int3
       else st = launch_gemm_lds<64, 64, 2, 2, 64, 4, 0, 1, 0, 1, 2>(g, per_pattern, s);
       if (st != PARSE_OK) return st;
       const size_t pieces = (size_t)cap * 8 * (most / 16) * 64;
-      hipLaunchKernelGGL((g.plan ? z_combine<0> : z_combine<1>), dim3((unsigned)std::min<size_t>((pieces + 255) / 256, 2048), g.n_layers), dim3(256), 0, s, g);
+      const int wgs = (int)std::min<size_t>((pieces + 255) / 256, 2048);
+      hipLaunchKernelGGL((g.plan ? z_combine<0> : z_combine<1>), dim3(wgs, g.n_layers), dim3(256), 0, s, g, wgs);
       PARSE_LAUNCH_CHECK();
       continue;
     }

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kPoolRowsThreads) void pool_rows(const void *__rest
     *reinterpret_cast<float4 *>(red + chain * cols + lane * PER + i) = float4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]};
   __syncthreads();
   const float inv = b > a ? 1.0f / (float)(b - a) : 0.f;
-  for (int c = threadIdx.x; c < cols; c += blockDim.x) {
+  for (int c = threadIdx.x; c < cols; c += chains << lwl) {
     if ((int)blockIdx.x * cols + c >= d) break;
     float total = 0.f;
 #pragma unroll 4
@@ -183,9 +183,9 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish(const float *__re
     if (emb_out) *reinterpret_cast<float4 *>(emb_out + (size_t)p * d + c) = acc;
   }
   __syncthreads();
-  block_router_scores(Wr, e, d, G, s);
+  block_router_scores(Wr, e, d, G, s, kFinishThreads / 64);
   if (scores_out)
-    for (int g = threadIdx.x; g < G; g += blockDim.x) scores_out[(size_t)p * G + g] = s[g];
+    for (int g = threadIdx.x; g < G; g += kFinishThreads) scores_out[(size_t)p * G + g] = s[g];
   if (threadIdx.x < 64) wave_topk_ascending(s, G, k, subset_out + (size_t)p * subset_stride, n_shared);
 }
 

@@ -5,11 +5,11 @@
 namespace parse {
 
 // Scores s_g = <Wr[g], e> for g in [0, G): e lives in LDS (d floats, d % 4 == 0), each of the block's
-// wavefronts takes every nwaves-th group and reduces across its 64 lanes.  Result in s_lds[G]; ends
+// nwaves wavefronts takes every nwaves-th group and reduces across its 64 lanes (told, not read from blockDim).  Result in s_lds[G]; ends
 // with a barrier.
 __device__ __forceinline__ void block_router_scores(const float *__restrict__ Wr, const float *e_lds,
-                                                    int d, int G, float *s_lds) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
+                                                    int d, int G, float *s_lds, int nwaves) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int g = wave; g < G; g += nwaves) {
     const float4 *w4 = reinterpret_cast<const float4 *>(Wr + (size_t)g * d);
     const float4 *e4 = reinterpret_cast<const float4 *>(e_lds);

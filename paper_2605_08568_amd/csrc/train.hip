@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void train_pair(TrainPair a) {
   const int j = lane & 15, g = lane >> 4;
   // up to 8 token tiles run through a rank tile before the next one: a die's consecutive tiles share both operands in its L2
   const int ntm = (a.rows + BM - 1) / BM, ntn = (a.R + BN - 1) / BN;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tile = xcd_tile(blockIdx.x, ((a.rows + BM - 1) / BM) * ((a.R + BN - 1) / BN));
   const int grp = tile / (8 * ntn), first = grp * 8, gm = min(8, ntm - first), r = tile - grp * 8 * ntn;
   const int tm = first + r % gm, tn = r / gm;
   const int nblk = a.R / 32;
