@@ -30,6 +30,7 @@
 #include <algorithm>
 
 #include "prefill_common.hpp"
+#include "decode_tasks.hpp"
 
 namespace parse {
 
@@ -37,7 +38,6 @@ constexpr int DY_WAVES = 8, DY_THREADS = DY_WAVES * 64;
 constexpr int DEC_MAXG = 64;
 constexpr int DY_CHUNK = 4;                // decode_y: operands per chunk after the first block
 constexpr int DY_MAXKB = 1024;             // selected reduction blocks a decode_y workgroup can list
-constexpr int DEC_MAX_LAYERS = 4;
 constexpr int DEC_TICKETS = 512;           // 32-rank blocks of the largest layer (R = 16384)
 constexpr int DEC_PLAN_WORDS = 192 + DEC_TICKETS;   // per layer: [0] count, [1..64] used group ids, [65..128] sequence masks,
                                                     // [192..) arrival counters of the split reduction (zero between calls)
@@ -53,7 +53,8 @@ struct DecLayer {
   float *zpart;                // workspace: partial sums of z, [R/32][KS][16][64] floats (KS > 1)
   int32_t *ticket;             // [DEC_TICKETS] arrival counters in the plan, one per 32-rank block
   int R, G, gs, m;
-  int z_first, y_first;        // first workgroup of this layer in decode_zr / decode_y
+  int z_first, y_first;        // first workgroup of this layer in decode_zr and decode_zp / decode_y
+  int z_wgs;                   // decode_zp: workgroups of this layer
 };
 struct DecArgs {
   DecLayer L[DEC_MAX_LAYERS];
@@ -61,7 +62,6 @@ struct DecArgs {
   const uint16_t *x;
   int B, n;
   int KS;                      // decode_zr: slices of the reduction range
-  int wgs;                     // decode_zp: workgroups
 };
 
 struct DecPlanArgs {
@@ -98,11 +98,12 @@ struct DecUsed {
   }
 };
 
-// A workgroup's task in a first product: 2^shift ranks of a group in use.  The layers take turns and each one's tasks are counted through over its groups in
-// use, so that the workgroups without one are the last of the grid: up to one task a compute unit is then one task a unit (numbered over all groups some
-// units got two and some none: 11008 -> 4096 columns, one sequence, four ranks a workgroup, 11.0 us, 8.5 this way).
+// A task of a first product: 2^shift ranks of a group in use.  Each layer's tasks are counted through over its groups in use.  decode_zv, a workgroup a task:
+// the layers take turns, so that the workgroups without one are the last of the grid (of layers with equally many): up to one task a compute unit is then one task a
+// unit (numbered over all groups some units got two and some none: 11008 -> 4096 columns, one sequence, four ranks a workgroup, 11.0 us, 8.5 this way).
+// decode_zp, several tasks a workgroup: each layer has workgroups of its own (dec_share).
 struct DecTask {
-  int layer, unit;             // unit < 0: none
+  int unit;                    // unit < 0: none
   uint32_t mask;               // sequences whose pattern holds the unit's group
 };
 __device__ __forceinline__ int dec_layer_of(const DecArgs &a, int bid, int &at) {
@@ -110,12 +111,11 @@ __device__ __forceinline__ int dec_layer_of(const DecArgs &a, int bid, int &at) 
   return bid - at * a.n_layers;
 }
 // ids and masks: the plan's words of the lane
-__device__ __forceinline__ DecTask dec_task(const DecLayer &ly, int used, int ids, int masks, int li, int at, int shift) {
+__device__ __forceinline__ DecTask dec_task(const DecLayer &ly, int used, int ids, int masks, int at, int shift) {
   const int per = ly.gs >> shift, count = max(0, min(used, ly.G)) * per;
-  // exact: at / per < 64, and (at + 1/2) / per is at least 1/4096 off every integer
-  const int g = min(__builtin_amdgcn_readfirstlane((int)(((float)at + 0.5f) * (1.0f / (float)per))), DEC_MAXG - 1);
+  const int g = min(__builtin_amdgcn_readfirstlane(dec_group_of(at, per)), DEC_MAXG - 1);
   const int id = min(max(__builtin_amdgcn_readlane(ids, g), 0), ly.G - 1);
-  return DecTask{li, at < count ? id * per + at - g * per : -1, (uint32_t)__builtin_amdgcn_readlane(masks, id)};
+  return DecTask{at < count ? id * per + at - g * per : -1, (uint32_t)__builtin_amdgcn_readlane(masks, id)};
 }
 
 // a barrier without the usual one's fence, which waits for every outstanding load: what this wavefront wrote to LDS is there
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
   const DecLayer &ly = a.L[li];
   // eight ranks; JW == 4: one half of them, the other half (of the same 128-byte lines) goes to a workgroup of the same die
   const int half = JW == 4 ? (at >> 3) & 1 : 0;
-  const DecTask task = dec_task(ly, ly.plan[0], ly.plan[1 + lane], ly.plan[65 + lane], li, JW == 4 ? (at >> 4) * 8 + (at & 7) : at, 3);
+  const DecTask task = dec_task(ly, ly.plan[0], ly.plan[1 + lane], ly.plan[65 + lane], JW == 4 ? (at >> 4) * 8 + (at & 7) : at, 3);
   if (task.unit < 0) return;
   const int rb = task.unit >> 2, j0 = (task.unit & 3) * 8 + half * 4;
   const int n = a.n, B = a.B, nkb = n / 16;
@@ -502,8 +502,8 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// decode_zp: decode_zv's tasks of eight ranks for up to sixteen sequences, with x, all of it, staged once per compute unit: one workgroup a unit takes every
-// wgs-th task.  A task is done in chunks of DEPTH factor operands a wavefront; the next chunk, of this task or the next one, is on its way while
+// decode_zp: decode_zv's tasks of eight ranks for up to sixteen sequences, with x, all of it, staged once per compute unit: one workgroup a unit takes
+// tasks of its layer in turn.  A task is done in chunks of DEPTH factor operands a wavefront; the next chunk, of this task or the next one, is on its way while
 // one is multiplied.  Bound by what a unit takes in: x once and its share of the factor, where a workgroup of sixteen ranks that reads x for itself takes
 // in as much of x as of the factor and a unit with two of them twice that (twelve sequences, a 4096 x 11008 block, us: q/k/v 14.1 -> 10.5, o 8.2 -> 6.1,
 // gate/up 9.6 -> 9.0; a call of 512 ranks 15.2 (32-wide) / 10.9 / 9.2).
@@ -524,37 +524,24 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
   const int pieces = n / 8, xstride = dv_xstride(n), all = B * pieces;
   const int chunks = ONE ? 1 : (nkb + 4 * DV_WAVES * DEPTH - 1) / (4 * DV_WAVES * DEPTH);
   auto step = [&](int i) { return ((wave + i * DV_WAVES) * 2 + part) * 2 + (kq >> 1); };       // of this wavefront's instruction i of a task, this lane
-  int used[DEC_MAX_LAYERS], ids[DEC_MAX_LAYERS], masks[DEC_MAX_LAYERS];
+  int li = 0;
 #pragma unroll
-  for (int l = 0; l < DEC_MAX_LAYERS; ++l) { // layers past the last one: that one
-    const int32_t *plan = a.L[0].plan + (size_t)min(l, a.n_layers - 1) * DEC_PLAN_WORDS;
-    used[l] = plan[0];
-    ids[l] = plan[1 + lane];
-    masks[l] = plan[65 + lane];
-  }
+  for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].z_first) ? 1 : 0;
+  const DecLayer &ly = a.L[li];
+  const int used = ly.plan[0], ids = ly.plan[1 + lane], masks = ly.plan[65 + lane];
   __builtin_amdgcn_sched_barrier(0);
   struct Task {
     int unit;                                // < 0: none
     uint32_t mask;
     const char *V;                           // this lane's factor; without a task all lanes read the same 16 bytes
     int stride;
-    uint16_t *zf;
   };
-  auto task_of = [&](int id) {
-    int at;
-    const int li = dec_layer_of(a, id, at);
-    const DecLayer &ly = a.L[li];
-    auto of = [&](const int (&w)[DEC_MAX_LAYERS]) {
-      int x = 0;
-#pragma unroll
-      for (int l = 0; l < DEC_MAX_LAYERS; ++l) x |= w[l] & -(int)(li == l);
-      return x;
-    };
-    const DecTask t = dec_task(ly, of(used), of(ids), of(masks), li, at, 3);
+  auto task_of = [&](int at) {
+    const DecTask t = dec_task(ly, used, ids, masks, at, 3);
     const bool on = t.unit >= 0;
     return Task{t.unit, t.mask,
                 on ? (const char *)ly.Vt + (size_t)(t.unit >> 2) * nkb * 1024 + ((kq & 1) * 32 + (t.unit & 3) * 8 + r) * 16 : (const char *)a.x,
-                on ? 1024 : 0, ly.zf};
+                on ? 1024 : 0};
   };
   u32x4 xr[XP], v0[DEPTH], v1[DEPTH];
   auto request = [&](const Task &t, int chunk, u32x4 (&v)[DEPTH]) {
@@ -569,9 +556,9 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
 #pragma unroll
   for (int u = 0; u < XP; ++u) xr[u] = *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)min(u * DV_THREADS + (int)threadIdx.x, all - 1) * 16);
   __builtin_amdgcn_sched_barrier(0);
-  int id = blockIdx.x, chunk = 0;
-  Task task = task_of(id);
-  if (task.unit < 0) return;                 // uniform
+  int at = (int)blockIdx.x - ly.z_first, chunk = 0;
+  Task task = task_of(at);
+  if (task.unit < 0) return;                 // uniform; no later place has a task either
   request(task, 0, v0);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -594,18 +581,18 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
     const int c = ONE ? 0 : chunk;
     if (ONE || ++chunk == chunks) {          // uniform
       chunk = 0;
-      id += a.wgs;
-      task = task_of(id);
+      at += ly.z_wgs;
+      task = task_of(at);
     }
     request(task, ONE ? 0 : chunk, w);
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
-      const int kb = step(c * DEPTH + u), at = min(kb, nkb - 1) * 32;
+      const int kb = step(c * DEPTH + u), xat = min(kb, nkb - 1) * 32;
       const bool on = kb < nkb;              // else both are cleared: an infinite weight times zero is no number
       const u32x4 vv = on ? v[u] : u32x4{0, 0, 0, 0};
 #pragma unroll
       for (int h = 0; h < NX; ++h) {
-        const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow[h] + at);
+        const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow[h] + xat);
         acc[h] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vv), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
       }
     }
@@ -624,7 +611,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
         for (int p = 0; p < 2; ++p) z += red[which][q][p][b][e];
       const float next = __shfl_down(z, 1, 64);
       if (b < B && !(e & 1))                 // zeros outside the group's mask
-        *reinterpret_cast<uint32_t *>((char *)now.zf + (size_t)(now.unit >> 1) * 1024 + ((now.unit & 1) * 32 + b) * 16 + e * 2) =
+        *reinterpret_cast<uint32_t *>((char *)ly.zf + (size_t)(now.unit >> 1) * 1024 + ((now.unit & 1) * 32 + b) * 16 + e * 2) =
             ((now.mask >> b) & 1u) ? cvt_pk_bf16(z, next) : 0u;
     }
     which ^= 1;                              // the other place: this one is read until the next barrier
@@ -1132,10 +1119,10 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
 #undef PARSE_ZVX
 #undef PARSE_ZV
   } else if (zp) {
-    int wgs = 0;
-    for (int l = 0; l < n_layers; ++l) wgs = std::max(wgs, layers[l].R / 8);
-    wgs = std::min(wgs * n_layers, n_cu);
-    a.wgs = wgs;
+    int tasks[DEC_MAX_LAYERS], share_of[DEC_MAX_LAYERS], first = 0;
+    for (int l = 0; l < n_layers; ++l) tasks[l] = layers[l].R / 8;
+    const int wgs = dec_share(tasks, n_layers, n_cu, share_of);
+    for (int l = 0; l < n_layers; ++l) { a.L[l].z_first = first; a.L[l].z_wgs = share_of[l]; first += share_of[l]; }
     const int share = ((nkb + 3) / 4 + DV_WAVES - 1) / DV_WAVES;
     const size_t lds = (size_t)B * dv_xstride(a.n);
     const int xp = (B * (a.n / 8) + DV_THREADS - 1) / DV_THREADS;                        // pieces of x of a thread

@@ -3,6 +3,7 @@ declares, and rejects bad arguments with the documented status before anything i
 import ctypes as C
 import os
 import re
+import subprocess
 import sysconfig
 from collections import deque
 
@@ -529,3 +530,49 @@ def test_module_carries_the_name_of_its_python():
     """The module uses the whole C API of the Python that it is built with: its file name says which, so that no other one imports it."""
     B._calls.parse_pool                                                   # imports it
     assert B._calls.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+SHARE = r"""
+#include "decode_tasks.hpp"
+#include <vector>
+// a call's workgroups walk over the tasks in use, of `most` in each layer at most: tasks that are not taken exactly once; -1: more workgroups than units
+extern "C" int walk(int units, int n_layers, const int *most, const int *in_use) {
+  int wgs[4], wrong = 0;
+  const int all = parse::dec_share(most, n_layers, units, wgs);
+  for (int l = 0, sum = 0; l < n_layers; ++l) {
+    sum += wgs[l];
+    if (wgs[l] < 1 || (l == n_layers - 1 && sum != all) || (units >= n_layers && all > units)) return -1;
+    std::vector<int> taken(in_use[l]);
+    for (int w = 0; w < wgs[l]; ++w)
+      for (int at = w; at < in_use[l]; at += wgs[l]) ++taken[at];
+    for (int t : taken) wrong += t != 1;
+  }
+  return wrong;
+}
+extern "C" int groups(int per) {                       // a layer has up to 64 groups and 2048 tasks
+  int wrong = 0;
+  for (int at = 0; at < 64 * per && at < 2048; ++at) wrong += parse::dec_group_of(at, per) != at / per;
+  return wrong;
+}
+"""
+
+
+def test_every_task_of_a_decode_call_is_taken_once(tmp_path):
+    """Shares of a first product's workgroups among one to four layers, and their walk over tasks whose numbers differ as the layers' sizes and groups in use do."""
+    src, so = tmp_path / "share.cpp", tmp_path / "share.so"
+    src.write_text(SHARE)
+    csrc = os.path.join(ROOT, "paper_2605_08568_amd", "csrc")
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-D__device__=", "-D__host__=", "-I" + csrc, str(src), "-o", str(so)], check=True)
+    lib = C.CDLL(str(so))
+    rng = np.random.default_rng(71)
+    # q of 1536 ranks with k and v of 512, 14 groups of 16 in use; three layers of 2048 ranks with 8, 16 and 16; long layer in the middle and last; the least and the most
+    cases = [([192, 64, 64], [168, 56, 56]), ([64, 192, 64], [56, 168, 56]), ([64, 64, 192], [56, 56, 168]), ([256, 256, 256], [128, 256, 256]),
+             ([2048, 4, 2048, 2048], [2048, 4, 0, 2048]), ([4], [4]), ([2048], [2048]), ([4, 4, 4, 4], [0, 4, 0, 4])]
+    for _ in range(300):
+        most = rng.integers(1, 513, size=rng.integers(1, 5)) * 4 // rng.choice([1, 8, 64], size=1) // 4 * 4 + 4
+        cases.append((most.clip(4, 2048).tolist(), [int(rng.integers(0, m + 1)) for m in most.clip(4, 2048)]))
+    for most, in_use in cases:
+        for units in (256, 304, 32, 4, 1):
+            n = len(most)
+            assert lib.walk(units, n, (C.c_int * n)(*most), (C.c_int * n)(*in_use)) == 0, (units, most, in_use)
+    assert all(lib.groups(per) == 0 for per in range(1, 2049))

@@ -2167,6 +2167,40 @@ def test_decode_tasks_of_eight_ranks(n, shapes, B):
     test_decode_few_sequences_tiles(n, shapes, B)
 
 
+GQA = [(96, 1536, 16, 8), (64, 512, 16, 8), (64, 512, 16, 8)]        # q, k, v: a third of the ranks in k and in v
+
+
+@pytest.mark.parametrize("n,shapes,B", [
+    (4096, GQA, 4), (4096, GQA, 12), (4096, GQA, 16),                # the long layer first, ...
+    (4096, GQA[1:] + GQA[:1], 12), (4096, [GQA[1], GQA[0], GQA[2]], 16),                                                  # ... last and in the middle
+    (2064, [(64, 2048, 16, 8), (64, 2048, 16, 16), (64, 2048, 16, 16)], 5),                                               # alike, unlike numbers of groups in use
+    (1040, [(32, 3072, 16, 3), (32, 64, 2, 1), (32, 2048, 16, 12), (32, 96, 3, 3)], 6),                                   # four layers
+    (8208, [(64, 1280, 20, 17), (32, 256, 4, 1), (32, 1600, 25, 25)], 4),                                                 # three chunks a task
+    (8192, [(64, 2560, 20, 19)], 5), (7184, [(64, 2560, 20, 19)], 9),                                                     # two
+])
+def test_decode_layers_of_unlike_numbers_of_tasks(n, shapes, B):
+    """Several tasks a workgroup, layers of unlike numbers of them: against the oracle's product, and the same bits whatever the workspace held."""
+    test_decode_few_sequences_tiles(n, shapes, B)
+    rng = np.random.default_rng(1502)
+    layers, pats = [], []
+    for m, R, G, k in shapes:
+        Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((R, n), (R, m)))
+        sub = np.sort(rng.choice(G, size=k, replace=False))[None].repeat(2, 0)       # one subset: exactly k groups in use
+        layers.append(pa.layer_to_mfma16(pa.Layer(upload_tokens(Vt, "bf16"), upload_tokens(Ut, "bf16"), n, m, R, G, pa.PARSE_ROWMAJOR)))
+        pats.append(pa.Patterns(k, 2, subsets=i32(sub)))
+    x, pid = upload_tokens(si.make_tokens(rng, B, n, "bf16"), "bf16"), i32(np.arange(B) % 2)
+    plan = pa.decode_plan(layers, pats, pid)
+    need = pa.lowrank_decode_planned_workspace_bytes(layers)
+    runs = []
+    for byte in (0x00, 0xFF):                                        # zeros; no numbers
+        ys = [torch.empty((B, l.m), dtype=torch.bfloat16, device=DEV) for l in layers]
+        pa.lowrank_decode_planned(layers, x, plan, ys, torch.full((need,), byte, dtype=torch.uint8, device=DEV))
+        runs.append(ys)
+    torch.cuda.synchronize()
+    for l, (a, b) in enumerate(zip(*runs)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)), f"layer {l}: the workspace shows through"
+
+
 @pytest.mark.parametrize("n,B", [(48, 3), (48, 5), (48, 16), (4112, 3), (4112, 5), (4112, 14)])
 def test_decode_of_few_sequences_keeps_infinite_products(n, B):
     """A weight that overflowed to infinity, in the last column of an odd number of 16-column blocks (half of the 16-wide kernel's
