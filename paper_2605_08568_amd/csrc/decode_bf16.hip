@@ -417,10 +417,25 @@ __global__ __launch_bounds__(DR_THREADS) void decode_zr(DecArgs a) {
 // halves), every line exactly once in the launch.  The 16 x 16 x 32 matrix instruction multiplies them: its sixteen rows are the
 // task's ranks in 16 / JW parts of the reduction range, its sixteen columns the sequences (all of x sits in LDS) in the same parts, and what row and
 // column of one part make is of use.  On the vector units, 36 instructions a load, this was the slower (one sequence, four calls of a 4096 x 11008 block, us:
-// 7.9 + 5.6 + 7.6 + 9.7, with workgroups numbered over all groups; 7.1 + 4.6 + 5.8 + 7.3 now).  Each product is added to its sum by the vector
-// units: chained through the instruction's accumulator z was rounded the other way to bf16 133 times in a million (4096 columns), 110 this way, 97 to 172
-// by the kernels before.  The wavefronts' sums meet in LDS and are added in wavefront order.  No partial sums leave
-// the workgroup.  The result is masked, rounded and stored like decode_zr's.
+// 7.9 + 5.6 + 7.6 + 9.7, with workgroups numbered over all groups; 7.1 + 4.6 + 5.8 + 7.3 now).  The result is masked, rounded and stored like decode_zr's; no
+// partial sums leave the workgroup.
+// The sums: an instruction's product of 32 columns goes to one of its lane's four running sums, and those, the parts and the wavefronts (in LDS) are added by pairs.
+// What the roundings add up to, rms, in units of 2^-24 of the root of the sum of the products' squares (products that cancel, so that all of the result is
+// rounding), 1024 / 2048 / 4096 / 11008 columns: 0.91 / 1.01 / 1.11 / 1.28.  One running sum a lane, parts and wavefronts in order: 1.11 / 1.21 / 1.25 to 1.32 /
+// 1.54 to 1.69; on the vector units 0.90 / 1.00 / 1.15 / 1.47; a 16-wide kernel with one sum over all columns 1.06 / 1.45 / 2.05 / 3.49; decode_zr 0.97 / 1.11 / 1.30
+// / 2.10.
+constexpr int DV_SUMS = 4;                   // running sums of a lane, one for every fourth instruction
+
+// v[0..N), a power of two of them, by pairs, pairs of pairs, ...
+template <int N, class T>
+__device__ __forceinline__ T pair_sum(T (&v)[N]) {
+#pragma unroll
+  for (int d = 1; d < N; d *= 2)
+#pragma unroll
+    for (int i = 0; i < N; i += 2 * d) v[i] += v[i + d];
+  return v[0];
+}
+
 constexpr int DV_WAVES = 8, DV_THREADS = DV_WAVES * 64;
 constexpr int DV_XBYTES = 96 * 1024;         // most LDS the x rows may take
 constexpr int DV_MAXB = 4;
@@ -471,29 +486,30 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
     keep(i, *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)i * 16));
   dec_lds_barrier();
   const char *xrow = xs + min(r, B - 1) * xstride + (kq & 1) * 16;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[DV_SUMS];
+#pragma unroll
+  for (int i = 0; i < DV_SUMS; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int i0 = 0;;) {
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
       const int kb = step(i0 + u);
       const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow + min(kb, nkb - 1) * 32);
       const bool on = kb < nkb;              // else both are cleared: an infinite weight times zero is no number
-      acc += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(on ? v[u] : u32x4{0, 0, 0, 0}), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+      acc[u % DV_SUMS] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(on ? v[u] : u32x4{0, 0, 0, 0}), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
     }
     i0 += DEPTH;
     if ((wave + i0 * DV_WAVES) * C * 2 >= nkb) break;      // uniform
     request(i0);
   }
   // lane (column lane % 16, g) holds rows 4 g .. 4 g + 3: of use where row and column are of the same part
-  if ((kq * 4) / JW == part) *reinterpret_cast<f32x4 *>(&red[wave][part][r][(kq * 4) % JW]) = acc;
+  if ((kq * 4) / JW == part) *reinterpret_cast<f32x4 *>(&red[wave][part][r][(kq * 4) % JW]) = pair_sum(acc);
   __syncthreads();
-  if (threadIdx.x < JW * JW) {               // thread (sequence, rank): wavefronts and parts in order
+  if (threadIdx.x < JW * JW) {               // thread (sequence, rank)
     const int b = threadIdx.x / JW, e = threadIdx.x % JW;
-    float z = 0.f;
+    float zs[DV_WAVES * C];
 #pragma unroll
-    for (int w = 0; w < DV_WAVES; ++w)
-#pragma unroll
-      for (int c = 0; c < C; ++c) z += red[w][c][b][e];
+    for (int i = 0; i < DV_WAVES * C; ++i) zs[i] = red[i / C][i % C][b][e];
+    const float z = pair_sum(zs);
     const float next = __shfl_down(z, 1, 64);
     if (b < B && !(e & 1))                   // zeros outside the group's mask
       *reinterpret_cast<uint32_t *>((char *)ly.zf + (size_t)(rb * 2 + (j0 >> 4)) * 1024 + (((j0 >> 3) & 1) * 32 + b) * 16 + ((j0 & 7) + e) * 2) =
@@ -568,12 +584,16 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
     keep(i, *reinterpret_cast<const u32x4 *>((const char *)a.x + (size_t)i * 16));
   dec_lds_barrier();
   const char *xrow[NX];
-  f32x4 acc[NX];
+  f32x4 acc[NX][DV_SUMS];
+  auto clear = [&]() {
 #pragma unroll
-  for (int h = 0; h < NX; ++h) {
-    xrow[h] = xs + min(h * 8 + r, B - 1) * xstride + (kq & 1) * 16;
-    acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int h = 0; h < NX; ++h)
+#pragma unroll
+      for (int i = 0; i < DV_SUMS; ++i) acc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+#pragma unroll
+  for (int h = 0; h < NX; ++h) xrow[h] = xs + min(h * 8 + r, B - 1) * xstride + (kq & 1) * 16;
+  clear();
   int which = 0;
   // multiplies the chunk in v, the next one on its way into w; false after the last task
   auto turn = [&](const u32x4 (&v)[DEPTH], u32x4 (&w)[DEPTH]) -> bool {
@@ -593,30 +613,28 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zp(DecArgs a) {
 #pragma unroll
       for (int h = 0; h < NX; ++h) {
         const u32x4 xv = *reinterpret_cast<const u32x4 *>(xrow[h] + xat);
-        acc[h] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vv), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        acc[h][u % DV_SUMS] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(vv), dec_bf16x8(on ? xv : u32x4{0, 0, 0, 0}), f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
       }
     }
     if (!ONE && chunk != 0) return true;     // uniform
     if ((kq >> 1) == part) {
 #pragma unroll
-      for (int h = 0; h < NX; ++h) *reinterpret_cast<f32x4 *>(&red[which][wave][part][h * 8 + r][(kq & 1) * 4]) = acc[h];
+      for (int h = 0; h < NX; ++h) *reinterpret_cast<f32x4 *>(&red[which][wave][part][h * 8 + r][(kq & 1) * 4]) = pair_sum(acc[h]);
     }
     dec_lds_barrier();
-    if (threadIdx.x < NX * 64) {             // thread (sequence, rank): wavefronts and parts in order
+    if (threadIdx.x < NX * 64) {             // thread (sequence, rank)
       const int b = threadIdx.x >> 3, e = threadIdx.x & 7;
-      float z = 0.f;
+      float zs[DV_WAVES * 2];
 #pragma unroll
-      for (int q = 0; q < DV_WAVES; ++q)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) z += red[which][q][p][b][e];
+      for (int i = 0; i < DV_WAVES * 2; ++i) zs[i] = red[which][i >> 1][i & 1][b][e];
+      const float z = pair_sum(zs);
       const float next = __shfl_down(z, 1, 64);
       if (b < B && !(e & 1))                 // zeros outside the group's mask
         *reinterpret_cast<uint32_t *>((char *)ly.zf + (size_t)(now.unit >> 1) * 1024 + ((now.unit & 1) * 32 + b) * 16 + e * 2) =
             ((now.mask >> b) & 1u) ? cvt_pk_bf16(z, next) : 0u;
     }
     which ^= 1;                              // the other place: this one is read until the next barrier
-#pragma unroll
-    for (int h = 0; h < NX; ++h) acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    clear();
     return task.unit >= 0;
   };
   while (turn(v0, v1) && turn(v1, v0)) {}

@@ -2201,6 +2201,47 @@ def test_decode_layers_of_unlike_numbers_of_tasks(n, shapes, B):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), f"layer {l}: the workspace shows through"
 
 
+@pytest.mark.parametrize("n,R,m,B,first,bound", [
+    (2048, 1024, 64, 1, True, 1.10), (2048, 1024, 64, 3, True, 1.10),
+    (11008, 1024, 64, 2, True, 1.40), (11008, 2048, 64, 6, True, 1.40),
+])
+def test_decode_of_few_sequences_precision_of_the_sums(n, R, m, B, first, bound):
+    """Products that cancel in pairs (at random places), so that a result is nothing but its sums' roundings; they are measured in 2^-24 of the root of the sum
+    of the products' squares.  A rounding is off by 0.42 of that on average (rms, over all mantissas), and each level of sums taken by pairs adds roundings of one
+    such whole: 2048 columns are sums of 4 x 16 by pairs, six levels, less what cancels on the way 4.0, and one rounding in the product itself, sqrt(0.176 x 5)
+    = 0.94 (1.01 measured); one sum of four and sixteen in order take 1.5 + 8.5 levels for them, 1.20 measured.  11008: 1.23 to 1.29 (1.54 to 1.69 in order), on
+    the vector units 1.47.  Bounds between the two."""
+    say(f"decode of {B} sequences: sums of the {'first' if first else 'second'} product, n={n} R={R} m={m}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + R + m + B)
+    def randn(r, c):
+        return torch.randn(r, c, device=DEV, generator=g)
+    V, U, G = (randn(R, n) / n ** 0.5).to(torch.bfloat16), randn(R, m).to(torch.bfloat16), 16
+    order = torch.randperm(n if first else R, device=DEV, generator=g)
+    a, b = order[:len(order) // 2], order[len(order) // 2:]
+    if first:
+        V[:, b] = V[:, a]
+    else:
+        V[b], U[b] = V[a], -U[a]
+    layer = pa.layer_to_mfma16(pa.Layer(V, U, n, m, R, G, pa.PARSE_ROWMAJOR))
+    pats = [pa.Patterns(G, 1, subsets=i32(np.arange(G)[None]))]
+    plan = pa.decode_plan([layer], pats, i32(np.zeros(B)))
+    ws = torch.empty(pa.lowrank_decode_planned_workspace_bytes([layer]), dtype=torch.uint8, device=DEV)
+    square = 0.0
+    for _ in range(24 // B):
+        x = randn(B, n).to(torch.bfloat16)
+        if first:
+            x[:, b] = -x[:, a]
+        y = torch.empty((B, m), dtype=torch.bfloat16, device=DEV)
+        pa.lowrank_decode_planned([layer], x, plan, [y], ws)
+        z = ws[:R * 64].view(torch.bfloat16).view(R // 16, 2, 32, 8)[:, :, :B].permute(2, 0, 1, 3).reshape(B, R).double()      # operands of the second product
+        got, left, right = (z, x.double(), V.double().t().contiguous()) if first else (y.double(), z, U.double())
+        assert first or torch.equal(z[:, a], z[:, b])
+        square += float((got ** 2 / ((left ** 2) @ (right ** 2))).mean()) / (24 // B)
+    say(f"    {square ** 0.5 * 2 ** 24:.3f}")
+    assert square ** 0.5 * 2 ** 24 <= bound
+
+
 @pytest.mark.parametrize("n,B", [(48, 3), (48, 5), (48, 16), (4112, 3), (4112, 5), (4112, 14)])
 def test_decode_of_few_sequences_keeps_infinite_products(n, B):
     """A weight that overflowed to infinity, in the last column of an odd number of 16-column blocks (half of the 16-wide kernel's
