@@ -882,13 +882,16 @@ __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
 // whole lines, every line once in the launch.  Everything goes straight from memory into registers; the eight wavefronts
 // of a workgroup split the reduction and share nothing until their sums meet in LDS.
 // Same rounding points, plan and workspace as the other decode kernels.  Bound by HBM and by the launch's latency: 5.0 us for 11 MB, 8.8 for 33 MB.
+// A wavefront's steps take SUMS running sums in turn, those and the wavefronts are added by pairs: roundings as above, 512 / 1024 / 1536 / 2048 ranks 0.77 / 0.90 / 1.00 /
+// 1.05 (two blocks and more a workgroup 1.18), one sum a wavefront and wavefronts in order 0.80 / 1.05 / 1.24 / 1.44, decode_yv 0.76 / 0.90 / 0.98 / 1.05; no more
+// than 0.1 us of 5.
 typedef __attribute__((ext_vector_type(4))) float f32x4_acc;
 constexpr int D16_WAVES = 8, D16_THREADS = D16_WAVES * 64, D16_MAXB = 16;
 
 // NC blocks of 16 columns per workgroup; wavefront w takes every eighth 32-rank block in use.
 template <int NC>
 __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
-  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : 8);
+  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : 8), SUMS = NC == 3 ? 2 : 4;
   int li = 0;
 #pragma unroll
   for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].y_first) ? 1 : 0;
@@ -909,9 +912,9 @@ __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
     const int c = min(c0 + i, ncb * 2 - 1);
     coff[i] = (c >> 1) * 1024 + (c & 1) * 256;
   }
-  f32x4_acc acc[NC];
+  f32x4_acc acc0[NC], acc1[NC], acc2[NC], acc3[NC];                // arrays of their own: one of all of them is moved about as a whole at every branch
 #pragma unroll
-  for (int i = 0; i < NC; ++i) acc[i] = f32x4_acc{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NC; ++i) acc0[i] = acc1[i] = acc2[i] = acc3[i] = f32x4_acc{0.f, 0.f, 0.f, 0.f};
   u32x4 ur[DEPTH][NC], zr[DEPTH];
   auto request = [&](int d, int s) {
     const int rb = blocks.block(wave + s * D16_WAVES);
@@ -919,42 +922,53 @@ __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
     for (int i = 0; i < NC; ++i) ur[d][i] = *reinterpret_cast<const u32x4 *>(U + (size_t)rb * 2 * ncb * 1024 + coff[i]);
     zr[d] = *reinterpret_cast<const u32x4 *>(Z + (size_t)rb * 2048);
   };
+  auto multiply = [&](int d, f32x4_acc (&acc)[NC]) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(ur[d][i]), dec_bf16x8(zr[d]), acc[i], 0, 0, 0);
+  };
+  auto in_turn = [&](auto f) {                                     // f(step, running sum) of all DEPTH steps
+#pragma unroll
+    for (int d = 0; d < DEPTH; d += SUMS) {
+      f(d, acc0);
+      f(d + 1, acc1);
+      if constexpr (SUMS == 4) {
+        f(d + 2, acc2);
+        f(d + 3, acc3);
+      }
+    }
+  };
   if (cnt > 0) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) request(d, min(d, cnt - 1));
     int s = 0;
-    for (; s + DEPTH < cnt; s += DEPTH) {
-#pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
+    for (; s + DEPTH < cnt; s += DEPTH)
+      in_turn([&](int d, f32x4_acc (&acc)[NC]) {
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(ur[d][i]), dec_bf16x8(zr[d]), acc[i], 0, 0, 0);
+        multiply(d, acc);
         request(d, min(s + d + DEPTH, cnt - 1));
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
+      });
+    in_turn([&](int d, f32x4_acc (&acc)[NC]) {
       __builtin_amdgcn_sched_barrier(0);
-      if (s + d < cnt) {                                           // uniform
-#pragma unroll
-        for (int i = 0; i < NC; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dec_bf16x8(ur[d][i]), dec_bf16x8(zr[d]), acc[i], 0, 0, 0);
-      }
-    }
+      if (s + d < cnt) multiply(d, acc);                           // uniform
+    });
   }
 #pragma unroll
-  for (int i = 0; i < NC; ++i)
+  for (int i = 0; i < NC; ++i) {
+    const f32x4_acc sum = (acc0[i] + acc1[i]) + (acc2[i] + acc3[i]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[wave][i][e][lane] = acc[i][e];
+    for (int e = 0; e < 4; ++e) red[wave][i][e][lane] = sum[e];
+  }
   __syncthreads();
-  // thread (column block, g, sequence): columns 4g..4g+3, sums in wavefront order
+  // thread (column block, g, sequence): columns 4g..4g+3
   for (int t = threadIdx.x; t < NC * 64; t += D16_THREADS) {
     const int i = t >> 6, ln = t & 63, seq = ln & 15;
     float y[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      y[e] = red[0][i][e][ln];
+      float ys[D16_WAVES];
 #pragma unroll
-      for (int w = 1; w < D16_WAVES; ++w) y[e] += red[w][i][e][ln];
+      for (int w = 0; w < D16_WAVES; ++w) ys[w] = red[w][i][e][ln];
+      y[e] = pair_sum(ys);
     }
     if (seq < B && c0 + i < ncb * 2)
       *reinterpret_cast<u32x2 *>(ly.y + (size_t)seq * m + (c0 + i) * 16 + (ln >> 4) * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};

@@ -2204,13 +2204,14 @@ def test_decode_layers_of_unlike_numbers_of_tasks(n, shapes, B):
 @pytest.mark.parametrize("n,R,m,B,first,bound", [
     (2048, 1024, 64, 1, True, 1.10), (2048, 1024, 64, 3, True, 1.10),
     (11008, 1024, 64, 2, True, 1.40), (11008, 2048, 64, 6, True, 1.40),
+    (64, 2048, 2048, 3, False, 1.25), (64, 2048, 4096, 12, False, 1.25),
 ])
 def test_decode_of_few_sequences_precision_of_the_sums(n, R, m, B, first, bound):
     """Products that cancel in pairs (at random places), so that a result is nothing but its sums' roundings; they are measured in 2^-24 of the root of the sum
     of the products' squares.  A rounding is off by 0.42 of that on average (rms, over all mantissas), and each level of sums taken by pairs adds roundings of one
     such whole: 2048 columns are sums of 4 x 16 by pairs, six levels, less what cancels on the way 4.0, and one rounding in the product itself, sqrt(0.176 x 5)
     = 0.94 (1.01 measured); one sum of four and sixteen in order take 1.5 + 8.5 levels for them, 1.20 measured.  11008: 1.23 to 1.29 (1.54 to 1.69 in order), on
-    the vector units 1.47.  Bounds between the two."""
+    the vector units 1.47.  The second product of 2048 ranks, eight wavefronts of eight: 1.05 (1.44 in order, 1.05 on the vector units).  Bounds between the two."""
     say(f"decode of {B} sequences: sums of the {'first' if first else 'second'} product, n={n} R={R} m={m}")
     g = torch.Generator(device=DEV)
     g.manual_seed(n + R + m + B)
