@@ -318,6 +318,9 @@ __device__ __forceinline__ void gather_mfma16_v(int wg, const uint16_t *__restri
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) *reinterpret_cast<u32x4 *>(tile + (u * 8 + r8) * 128 + ((c ^ r8) * 16)) = ok[u] ? v[u] : u32x4{0, 0, 0, 0};
+  // other lanes' pieces from here on: this wavefront's writes stay ahead of its reads (LDS serves them in order, so nothing is waited for)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
   char *out = (char *)dst + (size_t)pat * K * n * 2 + (rb * nkb + kb0) * 1024 + lane * 16;
 #pragma unroll
   for (int u = 0; u < GV_STEPS; ++u)
