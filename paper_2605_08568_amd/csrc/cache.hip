@@ -201,6 +201,7 @@ __global__ __launch_bounds__(256) void route_or_gather(const float *__restrict__
 // walk).  With more (layer, prompt) workgroups than that, their rounds count, and a workgroup whose prompt hits leaves most of its
 // wavefronts idle: smaller ones.
 constexpr int kSmallBatch = 64, kSmallThreads = 1024;
+constexpr size_t kSmallLds = (3 * kSmallBatch + 4 + kSmallBatch * (kSmallBatch + 1)) * 4;     // resolve_route_or_gather's own arrays
 // The line by workgroups (whole probe, 1024 columns, us, with 1024 / 512 / 256 threads; misses, then hits):
 //   192 (3 layers x 64): 28 / 30 / 37 and 18 / 21 / 29        256 (32 x 8): 13.4 / 13.7 / 15.7 and 7.5 / 7.3 / 8.1
 //   320 (16 x 20): 22 / 18 / 21 and 12 / 10 / 12              512 (8 x 64): 40 / 31 / 38 and 23 / 22 / 29
@@ -477,7 +478,7 @@ int parse_cache_lookup_or_route(parse_cache *c, const float *emb, int32_t P, flo
   if (P <= kSmallBatch) {
     // small batch: every (layer, prompt) workgroup works out the batch's decisions itself, then does its own part;
     // the new entry count goes to the other counter slot, which becomes the live one
-    PARSE_ALLOW_LDS(resolve_route_or_gather, (size_t)(c->d + 128) * sizeof(float));
+    PARSE_ALLOW_LDS(resolve_route_or_gather, kSmallLds, (size_t)(c->d + 128) * sizeof(float));
     hipLaunchKernelGGL(resolve_route_or_gather, dim3(c->L, P), dim3(small_threads(c->L, P)), (size_t)(c->d + 128) * sizeof(float), s,
                        c->sims, ld, c->capacity, P, tau, c->count + c->cur, c->count + (c->cur ^ 1), emb, c->d, Wr, G, c->L, c->k,
                        entry, hit, sim_out, c->keys, c->values, subset_out, c->n_shared, small_threads(c->L, P));
@@ -488,7 +489,7 @@ int parse_cache_lookup_or_route(parse_cache *c, const float *emb, int32_t P, flo
   hipLaunchKernelGGL(resolve, dim3(1), dim3(1024), (size_t)P * 12, s, c->sims, ld, c->capacity, P, tau, 1, c->count + c->cur,
                      entry, hit, sim_out, c->src);
   PARSE_LAUNCH_CHECK();
-  PARSE_ALLOW_LDS(route_or_gather, (size_t)(c->d + 128) * sizeof(float));
+  PARSE_ALLOW_LDS(route_or_gather, 0, (size_t)(c->d + 128) * sizeof(float));
   hipLaunchKernelGGL(route_or_gather, dim3(c->L, P), dim3(256), (size_t)(c->d + 128) * sizeof(float), s, emb, c->d, Wr,
                      G, c->L, c->k, c->capacity, 1, entry, hit, c->src, c->keys, c->values, subset_out, c->n_shared);
   PARSE_LAUNCH_CHECK();

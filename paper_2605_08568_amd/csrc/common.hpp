@@ -45,11 +45,11 @@ void set_hip_error(hipError_t e, const char *where);
     }                                               \
   } while (0)
 
-// A launch with more than 64 KiB of dynamic LDS needs the kernel's limit raised first (gfx950 has 160 KiB per CU).
-// Only the rare large shapes take this path, so the attribute is simply set again on each such call.
-#define PARSE_ALLOW_LDS(kernel, bytes)                                                                            \
+// A launch with more than 64 KiB of LDS, the dynamic part and the `own` bytes of the kernel's arrays together, needs the dynamic part's limit raised first
+// (gfx950 has 160 KiB per CU).  Only the rare large shapes take this path, so the attribute is simply set again on each such call.
+#define PARSE_ALLOW_LDS(kernel, own, bytes)                                                                       \
   do {                                                                                                            \
-    if ((size_t)(bytes) > (size_t)65536)                                                                          \
+    if ((size_t)(own) + (size_t)(bytes) > (size_t)65536)                                                          \
       PARSE_HIP_TRY(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes))); \
   } while (0)
 

@@ -439,6 +439,7 @@ __device__ __forceinline__ T pair_sum(T (&v)[N]) {
 constexpr int DV_WAVES = 8, DV_THREADS = DV_WAVES * 64;
 constexpr int DV_XBYTES = 96 * 1024;         // most LDS the x rows may take
 constexpr int DV_MAXB = 4;
+constexpr int dv_red_bytes(int JW) { return DV_WAVES * 16 * JW * 4; }       // the wavefronts' sums
 
 __device__ __host__ __forceinline__ int dv_xstride(int n) { return n * 2 + ((n & 127) == 0 ? 128 : 0); }   // bytes between x rows in LDS
 
@@ -459,6 +460,7 @@ __global__ __launch_bounds__(DV_THREADS) void decode_zv(DecArgs a) {
   const int n = a.n, B = a.B, nkb = n / 16;
   extern __shared__ __attribute__((aligned(16))) char xs[];      // B rows of x: several workgroups fit a compute unit
   __shared__ __attribute__((aligned(16))) float red[DV_WAVES][C][JW][JW];            // [wavefront][part][sequence][rank]
+  static_assert(sizeof(red) == dv_red_bytes(JW), "");
   const int r = (lane & 15) % JW, part = (lane & 15) / JW, kq = lane >> 4;           // rank and sequence, part, 8 of its 32 reduction indices
   const int pieces = n / 8, xstride = dv_xstride(n), all = B * pieces;
   u32x4 xr[XP];
@@ -770,6 +772,7 @@ __global__ __launch_bounds__(DY_THREADS) void decode_y(DecArgs a) {
 constexpr int DYV_WAVES = 8, DYV_THREADS = DYV_WAVES * 64;
 constexpr int DYV_DEPTH = 16;                // Ut loads a lane has in flight
 constexpr int DYV_ZBYTES = 96 * 1024;        // most LDS the z pieces may take
+constexpr int dyv_own_bytes(int NB) { return (DY_MAXKB + DEC_MAXG + DYV_WAVES * NB * 8) * 4; }         // the kernel's own arrays
 
 template <int NB, int CG, bool NT>
 __global__ __launch_bounds__(DYV_THREADS) void decode_yv(DecArgs a) {
@@ -1052,11 +1055,11 @@ bool past_caches(const parse_layer *layers, int n_layers) {
   return bytes >= (size_t)48 << 20;
 }
 
-// more than 64 KiB of dynamic LDS: the kernel's limit, raised to the most that any call asks for; it holds for the kernel on a device, so once is enough
-#define DEC_ALLOW_LDS(kernel, most, bytes, dev)                                                                                          \
+// PARSE_ALLOW_LDS, raised to the most that any call asks for: it holds for the kernel on a device, so once is enough
+#define DEC_ALLOW_LDS(kernel, own, most, bytes, dev)                                                                                     \
   do {                                                                                                                                   \
     static bool done[64] = {false};                                                                                                      \
-    if ((size_t)(bytes) > (size_t)65536 && !done[dev]) {                                                                                 \
+    if ((size_t)(own) + (size_t)(bytes) > (size_t)65536 && !done[dev]) {                                                                 \
       PARSE_HIP_TRY(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(most)));               \
       done[dev] = true;                                                                                                                  \
     }                                                                                                                                    \
@@ -1133,10 +1136,10 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
 #define PARSE_ZV(JW_, XP_, D_)                                                                                                              \
   do {                                                                                                                                     \
     if (nt) {                                                                                                                              \
-      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, true>), DV_XBYTES, lds, dev);                                                                 \
+      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, true>), dv_red_bytes(JW_), DV_XBYTES, lds, dev);                                             \
       hipLaunchKernelGGL((decode_zv<JW_, XP_, D_, true>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                         \
     } else {                                                                                                                               \
-      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, false>), DV_XBYTES, lds, dev);                                                                \
+      DEC_ALLOW_LDS((decode_zv<JW_, XP_, D_, false>), dv_red_bytes(JW_), DV_XBYTES, lds, dev);                                            \
       hipLaunchKernelGGL((decode_zv<JW_, XP_, D_, false>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                        \
     }                                                                                                                                      \
   } while (0)
@@ -1161,10 +1164,10 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
 #define PARSE_ZP(NX_, XP_, D_, ONE_)                                                                                                        \
   do {                                                                                                                                     \
     if (nt) {                                                                                                                              \
-      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, true>), DP_LDS - dp_red_bytes(NX_), lds, dev);                                          \
+      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, true>), dp_red_bytes(NX_), DP_LDS - dp_red_bytes(NX_), lds, dev);                        \
       hipLaunchKernelGGL((decode_zp<NX_, XP_, D_, ONE_, true>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                   \
     } else {                                                                                                                               \
-      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, false>), DP_LDS - dp_red_bytes(NX_), lds, dev);                                         \
+      DEC_ALLOW_LDS((decode_zp<NX_, XP_, D_, ONE_, false>), dp_red_bytes(NX_), DP_LDS - dp_red_bytes(NX_), lds, dev);                       \
       hipLaunchKernelGGL((decode_zp<NX_, XP_, D_, ONE_, false>), dim3(wgs), dim3(DV_THREADS), lds, s, a);                                  \
     }                                                                                                                                      \
   } while (0)
@@ -1222,10 +1225,10 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
 #define PARSE_YV(NB_, CG_)                                                                                        \
   do {                                                                                                           \
     if (nt) {                                                                                                    \
-      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, true>), zs_bytes);                                                    \
+      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, true>), dyv_own_bytes(NB_), zs_bytes);                                \
       hipLaunchKernelGGL((decode_yv<NB_, CG_, true>), dim3(yb), dim3(DYV_THREADS), zs_bytes, s, a);              \
     } else {                                                                                                     \
-      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, false>), zs_bytes);                                                   \
+      PARSE_ALLOW_LDS((decode_yv<NB_, CG_, false>), dyv_own_bytes(NB_), zs_bytes);                               \
       hipLaunchKernelGGL((decode_yv<NB_, CG_, false>), dim3(yb), dim3(DYV_THREADS), zs_bytes, s, a);             \
     }                                                                                                            \
   } while (0)

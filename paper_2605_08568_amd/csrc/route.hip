@@ -328,7 +328,7 @@ int parse_route_shared(const void *X, int32_t xdtype, int32_t rows, const int32_
   if (st != PARSE_OK) return st;
   const size_t lds = (size_t)(d + 64) * sizeof(float);
   const auto finish = l >= 0 ? route_finish<true> : route_finish<false>;
-  PARSE_ALLOW_LDS(finish, lds);
+  PARSE_ALLOW_LDS(finish, 0, lds);
   hipLaunchKernelGGL(finish, dim3(P), dim3(kFinishThreads), lds, s, partial, Q, rows, d, tok_offsets, Wr, G, k,
                      subset_out, subset_stride, scores_out, emb_out, n_shared);
   PARSE_LAUNCH_CHECK();

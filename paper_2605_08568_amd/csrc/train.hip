@@ -217,7 +217,7 @@ template <int BM, int BN, int WM, int WN, int STAGES>
 static int launch_train_pair(const TrainPair &a, hipStream_t s) {
   constexpr size_t smem = (size_t)STAGES * (BM + BN) * 128;
   auto kern = train_pair<BM, BN, WM, WN, STAGES>;
-  PARSE_ALLOW_LDS(kern, smem);
+  PARSE_ALLOW_LDS(kern, 0, smem);
   const int grid = ((a.rows + BM - 1) / BM) * ((a.R + BN - 1) / BN);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WM * WN * 64), smem, s, a);
   PARSE_LAUNCH_CHECK();

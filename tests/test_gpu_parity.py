@@ -2161,6 +2161,8 @@ def test_decode_few_sequences_tiles(n, shapes, B):
     (5632, [(64, 96, 3, 2)], 13),                                    # ... and one sequence more than fits
     (11024, [(64, 2112, 33, 12)], 6), (11024, [(64, 96, 3, 2)], 7),  # more of x than a thread has on its way at once; all that fits
     (14352, [(64, 96, 3, 2)], 12), (14352, [(32, 2592, 27, 9)], 11), # 32-wide with half of its rows, x staged once and in halves
+    (4096, [(64, 2112, 33, 8)], 7), (4096, [(64, 2112, 33, 8)], 8),  # x and the sums: 65 KiB of LDS, 57 of them x; x alone 65
+    (2048, [(64, 2112, 33, 8)], 11), (2048, [(64, 2112, 33, 8)], 13), (2048, [(64, 2112, 33, 8)], 15),                    # 61, 70 and 78 KiB, 45, 54 and 62 of them x
 ])
 def test_decode_tasks_of_eight_ranks(n, shapes, B):
     """One to sixteen sequences at the edges of the first product's kernels and of the choice between them, against the oracle's product."""
