@@ -1044,11 +1044,18 @@ static bool z_many_workgroups(int B, int n, int units) {
   return B == 1 || units <= 128 || (units > 256 && B * n <= 12288);
 }
 
-// Factors past the caches: a call whose layers are about a fifth of the last-level cache (256 MiB) or more, since what runs between two of its kind then
-// fills the cache, and each line that it brings in drives out one of another call's.  Smaller calls may belong to a program whose factors
-// all stay in the cache, and there it costs.  us a pass, ordinary loads / past the caches, three states in turn (as in a program
-// of several blocks) and one state again and again: block of one sequence, 4096 x 11008, 54.1 / 47.7 and 45.4 / 46.0; of twelve 84.0 / 76.6 and 76.4 / 76.6; MLP of 32
-// 68.0 / 64.0 and 59.5 / 63.2; block of 32 of 1024 x 2816 (4 to 15 MB a call) 56.7 / 60.6 and 55.8 / 57.4, of 2048 x 5632 61.3 / 66.2 and 61.9 / 65.2.
+// Factors past the caches: a call whose layers are about a fifth of the last-level cache (256 MiB) or more.  What a call cannot see is whether the program's
+// factors all stay in that cache: then it costs, and beyond it gains.  A program with calls of this size fits the cache only if it has no more than five of them, so the
+// line is drawn for those that do not.  It goes by what is stored: the groups in use are known on the device only.  us a pass, ordinary loads / as chosen, the factors
+// of one state again and again, of three and of 32 (seven gigabytes) in turn, 4096 x 11008:
+//   block (273 MiB)   1 sequence  49.5 / 48.8   55.2 / 52.7   57.7 / 55.5        MLP (221 MiB)   1  34.7 / 35.7   39.8 / 36.1    40.6 / 38.0
+//                    12           82.0 / 81.5   88.8 / 82.7   88.6 / 86.8                       12  55.6 / 59.2   64.2 / 59.1    64.0 / 61.8
+//                    32          100.5 / 101.1 108.0 / 100.6 107.7 / 105.6                      32  62.1 / 66.6   71.7 / 66.6    71.4 / 66.4
+//   MLP              64           68.0 / 74.2   79.2 / 71.7   78.9 / 75.8                       96  76.0 / 85.0   92.0 / 81.1    92.0 / 88.0
+//                   128           79.0 / 82.9   97.3 / 94.7   97.3 / 94.2                      150  87.4 / 90.1  106.5 / 103.9  106.0 / 103.5
+// Smaller calls are those of programs that may fit the cache.  Ordinary / past the caches for all calls, one state, three, as many as make 0.9 to 1.5 gigabytes:
+//   block of 2048 x 5632 (61 MiB)    1 sequence  34.2 / 33.5  35.6 / 36.1  41.5 / 37.2    32  64.8 / 66.6  65.1 / 70.4  72.1 / 70.5
+//   block of 1024 x 2816 (19 MiB)    1           28.7 / 28.7  31.2 / 30.4  36.8 / 32.9    32  58.1 / 59.6  60.2 / 63.5  66.2 / 65.1
 bool past_caches(const parse_layer *layers, int n_layers) {
   size_t bytes = 0;
   for (int l = 0; l < n_layers; ++l) bytes += (size_t)layers[l].R * ((size_t)layers[l].n + layers[l].m) * 2;

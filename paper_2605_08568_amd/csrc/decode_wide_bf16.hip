@@ -34,6 +34,7 @@ constexpr int DW_PLAN_WORDS = 128 + DW_MAXP * 64;      // [0] count, [1..64] use
 constexpr int DW_ZCB = 2;                  // rank blocks per wide_z workgroup
 constexpr int DW_UNITS = 256;              // workgroups wanted per launch
 constexpr int DW_MAX_KS = 8;
+constexpr int DWY_PAST = 3;                // most panels of a wide_y workgroup that reads its factor past the caches
 // Tiles of wide_y whose sums meet at a time: 16 KiB each, nine where the registers leave room for one workgroup a compute unit only
 constexpr int dw_round(int tiles) { return tiles <= 4 ? tiles : (tiles < 6 ? 4 : (tiles < 9 ? tiles : 9)); }
 
@@ -529,12 +530,17 @@ static int wide_pass(DwArgs a, bool past, hipStream_t s) {
     hipLaunchKernelGGL(wide_zsum, dim3((sw + DW_WAVES - 1) / DW_WAVES), dim3(DW_THREADS), 0, s, a);
     PARSE_LAUNCH_CHECK();
   }
-  // Past the caches only where one group of panels reads a column block: several share what the first one brings into the die's L2.  MLP of 150 sequences, factors
-  // of both products with ordinary loads 104.9 us a step, of the first past the caches 102.5, of the second too where one group reads them 97.3, everywhere 100.6.
-  past = past && a.groups == 1;
+  // Past the caches where one group of panels reads a column block (several share what the first one brings into the die's L2) and has up to three panels:
+  // a workgroup of more takes in more z than factor.  MLP of 4096 x 11008, us a step, ordinary loads / first product past the caches / both, by states in turn:
+  //    64 sequences  one 68.3 / 68.5 / 71.6   three 78.6 / 77.4 / 71.8    32 78.9 / 77.0 / 75.6
+  //    96            one 74.2 / 77.9 / 82.2   three 91.5 / 89.6 / 83.0    32 92.2 / 90.1 / 89.0
+  //   128            one 76.7 / 80.7 / 88.2   three 97.4 / 94.5 / 88.6    32 97.3 / 94.4 / 95.3
+  //   150            one 91.0 / 89.0 / 99.9   three 107.3 / 105.4 / 99.9  32 106.7 / 104.6 / 107.9
+  // (of few states a part stays in the last-level cache when nothing drives it out, which a program of tens of layers, or with other work in between, does not see).
+  past = past && a.groups == 1 && nt <= DWY_PAST;
 #define PARSE_DWY2(CB_, NT_)                                                                                     \
   do {                                                                                                           \
-    if (past) hipLaunchKernelGGL((wide_y<CB_, NT_, true>), dim3(yw), dim3(DW_THREADS), 0, s, a);                 \
+    if (past) hipLaunchKernelGGL((wide_y<CB_, NT_, (NT_ <= DWY_PAST)>), dim3(yw), dim3(DW_THREADS), 0, s, a);    \
     else hipLaunchKernelGGL((wide_y<CB_, NT_, false>), dim3(yw), dim3(DW_THREADS), 0, s, a);                     \
   } while (0)
 #define PARSE_DWY(NT_)                                                                                           \
