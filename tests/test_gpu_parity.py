@@ -857,13 +857,13 @@ def test_prefill_config1_full_size_sampled():
     (512, 32768, 96, 3, 2, 9, 3, 0),       # four column blocks per workgroup
     (2048, 2048, 2048, 64, 20, 32, 4, 0),  # the most groups a layer may have (64 of 32 ranks): quads span four groups
     (8192, 512, 256, 8, 3, 32, 4, 0),      # a long reduction over few rank blocks: 16 slices, two stagings of x each
-    (4096, 4096, 1536, 16, 8, 1, 1, 0),    # one sequence: eight ranks per workgroup on the vector units
+    (4096, 4096, 1536, 16, 8, 1, 1, 0),    # one sequence: four ranks a workgroup in the first product, the second on the vector units
     (11008, 4096, 2048, 16, 8, 1, 1, 0),   # ... a reduction whose step count is no multiple of four (688 steps, 3 batches of loads)
     (1040, 512, 256, 8, 3, 2, 2, 0),       # two sequences, 65 reduction steps (a ragged last instruction)
     (2752, 1024, 640, 20, 10, 3, 2, 0),    # three sequences (computed as four)
     (512, 256, 256, 8, 3, 4, 4, 0),        # four sequences, four patterns
     (32, 64, 32, 1, 1, 1, 1, 0),           # a tiny layer: two reduction steps, one instruction, three idle wavefronts
-    (16384, 256, 64, 2, 1, 4, 2, 0),       # four sequences whose x rows do not fit the small-batch staging: the matrix path
+    (16384, 256, 64, 2, 1, 4, 2, 0),       # four sequences whose x rows are more than a workgroup of one task stages: once per unit
 ])
 def test_decode_matches_oracle_and_prefill(n, m, R, G, k, B, npat, schedule):
     say(f"decode n={n} m={m} R={R} G={G} k={k} B={B} patterns={npat} schedule={schedule}")
@@ -2107,15 +2107,15 @@ def test_prefill_planned_long_reductions(n, m, rS, lengths, cut):
     (16, [(32, 32, 1, 1)], 5),                                       # one reduction step of half an instruction
     (496, [(64, 96, 3, 2), (416, 256, 4, 3)], 16),                   # odd number of 16-column steps; full instruction
     (2064, [(1056, 320, 10, 4)], 11),                                # a batch of nine steps; three columns blocks left over
-    (4096, [(4096, 256, 4, 2), (8256, 128, 2, 1)], 3),               # both products 16-wide for three sequences, several blocks per workgroup
-    (4112, [(32, 224, 7, 3)], 14),                                   # more steps than are in flight at once
-    (5648, [(96, 64, 2, 2)], 13),                                    # long reduction: first product 32-wide, second 16-wide
-    (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # first product on the vector units, second 16-wide, six blocks
-    (4624, [(64, 1024, 8, 3)], 4), (4624, [(64, 1056, 11, 3)], 4),   # few workgroups: vector units up to 64 of them, then 16-wide
-    (6160, [(64, 96, 3, 2)], 4), (12304, [(64, 96, 3, 2)], 3),       # ... and only while x is short; past 12288 columns 32-wide
-    (8208, [(64, 2048, 8, 3)], 2), (8208, [(64, 2080, 13, 3)], 2),   # two sequences: vector units up to 128 workgroups
-    (24576, [(32, 64, 2, 1)], 2), (24592, [(32, 64, 2, 1)], 2),      # the longest x the vector units hold, and one longer
-    (8208, [(64, 1024, 8, 3)], 5), (8208, [(64, 992, 31, 9)], 5),    # five: 64 to 127 workgroups go 32-wide
+    (4096, [(4096, 256, 4, 2), (8256, 128, 2, 1)], 3),               # two unlike layers, a task a workgroup; the second product's 32 columns a workgroup
+    (4112, [(32, 224, 7, 3)], 14),                                   # 28 tasks
+    (5648, [(96, 64, 2, 2)], 13),                                    # x and the sums all but fill the LDS
+    (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # more columns than four 16-column blocks a workgroup: second product 32-wide
+    (4624, [(64, 1024, 8, 3)], 4), (4624, [(64, 1056, 11, 3)], 4),   # 128 tasks: a workgroup each, second product on the vector units; 132: neither
+    (6160, [(64, 96, 3, 2)], 4), (12304, [(64, 96, 3, 2)], 3),       # few tasks of long x
+    (8208, [(64, 2048, 8, 3)], 2), (8208, [(64, 2080, 13, 3)], 2),   # two sequences, 256 tasks, 260 of them with over 12288 columns in all
+    (24576, [(32, 64, 2, 1)], 2), (24592, [(32, 64, 2, 1)], 2),      # x longer than a workgroup of one task stages
+    (8208, [(64, 1024, 8, 3)], 5), (8208, [(64, 992, 31, 9)], 5),    # five: x once per unit however few the tasks
 ])
 def test_decode_few_sequences_tiles(n, shapes, B):
     """Two to sixteen sequences at the edges of the 16-wide decode kernels and where the choice of kernels changes, against the
@@ -2125,13 +2125,13 @@ def test_decode_few_sequences_tiles(n, shapes, B):
     x = si.make_tokens(rng, B, n, "bf16")
     xv = si.bf16_bits_to_f32(x).astype(np.float64)
     seq_pat = (np.arange(B) % 3).astype(np.int32)
-    seq_pat[B - 1] = -1
+    seq_pat[B - 1] = -1 if B > 1 else 0
     layers, pats, refs = [], [], []
     for m, R, G, k in shapes:
         Vt, Ut = (si.f32_to_bf16_bits((rng.standard_normal(s) / s[1] ** 0.5).astype(np.float32)) for s in ((R, n), (R, m)))
         sub = np.stack([np.sort(rng.choice(G, size=k, replace=False)) for _ in range(3)]).astype(np.int32)
         mask = np.zeros((B, R))
-        for s in range(B - 1):
+        for s in np.flatnonzero(seq_pat >= 0):
             for g in sub[seq_pat[s]]:
                 mask[s, g * (R // G):(g + 1) * (R // G)] = 1.0
         V, U = (si.bf16_bits_to_f32(t).astype(np.float64) for t in (Vt, Ut))
@@ -2147,9 +2147,47 @@ def test_decode_few_sequences_tiles(n, shapes, B):
     torch.cuda.synchronize()
     for l, ref in enumerate(refs):
         yn = ys[l].float().cpu().numpy().astype(np.float64)
-        assert np.all(yn[B - 1] == 0.0)
-        assert_close(yn[:B - 1], ref[:B - 1], TOL_BF16, f"layer {l}")
+        on = seq_pat >= 0
+        assert np.all(yn[~on] == 0.0)
+        assert_close(yn[on], ref[on], TOL_BF16, f"layer {l}")
         assert torch.equal(ys[l].view(torch.int16), yp[l].view(torch.int16))
+
+
+def few_sequences_forms(n, shapes, B):
+    """Kernels of the first and of the second product of one to sixteen sequences: the rules at their dispatch (256 units)."""
+    units, x = sum(R for _, R, _, _ in shapes) // 8, B * (2 * n + (128 if n % 128 == 0 else 0))          # tasks of eight ranks, bytes of x in LDS
+    if B <= 4 and x <= 96 * 1024 and (B == 1 or units <= 128 or (units > 256 and B * n <= 12288)):
+        first = "zv4" if units <= 256 else "zv8"                     # ranks a workgroup
+    elif x + (8192 if B <= 8 else 16384) <= 160 * 1024 - 512:
+        first = "zp"
+    else:
+        first = "zr"
+    nb, most = (1, 2, 4, 4)[min(B, 4) - 1], max(R for _, R, _, _ in shapes) // 16
+    work = sum(nb * m * R for m, R, _, _ in shapes)
+    if B <= 4 and most * nb * 32 <= 96 * 1024 and (B == 1 or (work <= 16 << 20 and (B == 2 or most <= 64))):
+        return first, "yv"
+    return first, "y16" if sum(-(-m // 16 // 4) for m, _, _, _ in shapes) <= 256 else "y"
+
+
+@pytest.mark.parametrize("n,shapes,B,first,second", [
+    (2064, [(64, 1024, 16, 8)], 4, "zv4", "yv"), (2064, [(64, 1056, 33, 16)], 4, "zp", "y16"),        # 128 and 132 tasks; 64 and 66 blocks
+    (2064, [(64, 2048, 64, 30)], 1, "zv4", "yv"), (2064, [(64, 2080, 13, 6)], 1, "zv8", "yv"),   # 256 and 260 tasks of one sequence
+    (4096, [(64, 2048, 16, 8)], 3, "zp", "y16"), (4096, [(64, 2080, 13, 7)], 3, "zv8", "y16"),        # ... of three with 12288 columns in all
+    (4112, [(64, 2080, 13, 7)], 3, "zp", "y16"),                                                      # and with 48 more
+    (2048, [(64, 1536, 16, 8), (32, 512, 16, 8), (32, 512, 16, 5)], 4, "zv8", "y16"),                 # three unlike layers, a task a workgroup
+    # the most of x that a workgroup of one task stages (96 KiB), and 16 columns more
+    (49136, [(32, 64, 2, 1)], 1, "zv4", "yv"), (49152, [(32, 64, 2, 1)], 1, "zp", "yv"),
+    (24560, [(32, 64, 2, 1)], 2, "zv4", "yv"), (24576, [(32, 2080, 13, 6)], 2, "zp", "yv"),
+    (16368, [(32, 64, 2, 1)], 3, "zv4", "yv"), (16384, [(32, 64, 2, 1)], 3, "zp", "yv"),
+    (12272, [(32, 64, 2, 1)], 4, "zv4", "yv"), (12288, [(32, 64, 2, 1)], 4, "zp", "yv"),
+    (11024, [(64, 96, 3, 2)], 8, "zr", "y16"),                                                        # one sequence more than the LDS holds
+    (256, [(8192, 1024, 16, 8)], 2, "zv4", "yv"), (256, [(8224, 1024, 16, 8)], 2, "zv4", "y16"),      # columns x ranks x sequences: 16 M
+    (256, [(16384, 64, 2, 1)], 5, "zp", "y16"), (256, [(16416, 64, 2, 1)], 5, "zp", "y"),             # 256 workgroups of four 16-column blocks
+])
+def test_decode_few_sequences_at_the_lines_between_kernels(n, shapes, B, first, second):
+    """Either side of each line at which calls of one to sixteen sequences change kernels, against the oracle's product."""
+    assert few_sequences_forms(n, shapes, B) == (first, second)
+    test_decode_few_sequences_tiles(n, shapes, B)
 
 
 @pytest.mark.parametrize("n,shapes,B", [
