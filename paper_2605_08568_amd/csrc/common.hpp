@@ -53,9 +53,10 @@ void set_hip_error(hipError_t e, const char *where);
       PARSE_HIP_TRY(hipFuncSetAttribute((const void *)(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(bytes))); \
   } while (0)
 
-// Kernels are told their grid and block sizes or work them out: gridDim and blockDim are no arguments of the launch but another 256 bytes that the runtime writes
-// for each launch, and the kernel reads them from there.  Five processes each, with / without, launched call by call: a step of one prompt of 77 tokens (eight launches)
-// 34.3 to 38.4 us / 34.1 to 35.6, a routed fp32 pass (six) 24.7 to 25.9 / 23.4 to 24.8.
+// Kernels are told their grid and block sizes or work them out where a step launches them one after another: gridDim and blockDim are no arguments of the launch but
+// another 256 bytes that the runtime writes for each launch, and the kernel reads them from there.  No more than the spread of such a step (a routed fp32 pass of six
+// launches, five processes each, 24.7 to 25.9 us with, 23.4 to 24.8 without; one prompt of 77 tokens 34.3 to 38.4, 34.1 to 35.6).  One-time reorders, the probes and the
+// prefill kernels of one launch or two read them.
 #define PARSE_LAUNCH_CHECK()                        \
   do {                                              \
     hipError_t _e = hipGetLastError();              \

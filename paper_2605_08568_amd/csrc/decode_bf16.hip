@@ -160,8 +160,8 @@ __global__ __launch_bounds__(64) void decode_plan_build(DecPlanArgs a) {
 // ---------------------------------------------------------------------------------------------------------
 // decode_zr.  Workgroup = (layer, 32-rank block, slice s of KS of the reduction range).  A slice is at most 256 reduction steps (4096 columns): each of the eight wavefronts
 // owns an eighth of it and requests ALL its Vt operands at once, straight into registers (1 KiB coalesced per
-// instruction, up to 32 of them): the registers of the eight wavefronts are the staging buffer -- 256 KiB of factor
-// stream in flight per compute unit, several times what LDS staging can hold, which is what a stream from HBM needs.
+// instruction, up to 32 of them): the registers of the eight wavefronts are the staging buffer.  Up to 256 KiB are asked for, of which a
+// unit has 32 KiB on their way; the others wait in its queue, so that it never runs dry, and LDS is left to x.
 // The x rows of the slice are staged in LDS (loads that write LDS directly; 512-byte row segments, 16-byte pieces
 // XOR-swizzled by the row so that an operand read -- 32 rows x the same piece -- spreads over the banks), at most 128
 // steps at a time.  TWO == false (slices of up to 128 steps): one wait, one barrier, then the products run from registers
@@ -1033,13 +1033,15 @@ int build_decode_plan(const parse_layer *layers, const parse_patterns *pts, int 
 
 // Which kernel makes z.  Up to sixteen sequences whose x fits the LDS: decode_zv, many small workgroups that each stage x, for one sequence, for so few tasks that
 // none waits for a unit (up to 128 units of eight ranks, which decode_zv halves), or for many tasks of little x; decode_zp, x once per unit, otherwise.
-// The 32-wide kernel where x does not fit.  us a call of one layer with 512 columns of output (two or three patterns of half of the groups), decode_zv /
-// decode_zp / 32-wide, by sequences x n:
-//    512 ranks: 1 x 2816  6.6 / 7.5 / 13.0     4 x 2816  7.7 / 8.3 / 15.1     12 x 2816 - / 8.9 / 15.1
-//   1024 ranks: 2 x 11008 11.2 / 12.5 / 14.2   4 x 5632  10.9 / 11.1 / 13.8   6 x 11008 14.4 / 13.3 / 15.0    12 x 5632 - / 11.6 / 13.3
-//   2048 ranks: 1 x 11008 11.0 / 12.6 / 16.3   2 x 4096  10.5 / 10.0 / 13.3   2 x 11008 17.9 / 14.8 / 18.8    4 x 8192 18.2 / 15.0 / 19.9
-//   2560 ranks: 1 x 11008 13.0 / 13.4 / 16.8   2 x 11008 16.3 / 16.0 / 20.0   4 x 11008 23.2 / 20.9 / 22.2    6 x 11008 23.0 / 18.9 / 19.9
-//   3 x 1536:   1 x 4096  9.9 / 10.5 / 14.5    2 x 4096  11.4 / 11.9 / 15.7   4 x 4096  14.1 / 14.2 / 17.3    12 x 4096 - / 14.0 / 16.2
+// The 32-wide kernel where x does not fit.  us a call of one layer (or three) with 512 columns of output, half of the groups in up to three patterns, over layers of 0.7
+// gigabytes in turn, decode_zv / decode_zp / 32-wide, by sequences x columns (decode_zv takes four sequences):
+//    512 ranks: 1 x 2816  6.7 / 7.6 / 13.1     4 x 2816   7.8 / 8.4 / 15.1     4 x 11008 13.2 / 14.6 / 17.8    12 x 2816  - / 9.2 / 15.7
+//   1024 ranks: 1 x 2816  7.4 / 8.1 / 10.8     2 x 11008 13.1 / 14.4 / 15.7    4 x 5632  12.4 / 12.4 / 15.2    4 x 11008 14.2 / 15.5 / 16.8
+//               6 x 11008  - / 15.3 / 16.7     12 x 5632   - / 13.2 / 15.1
+//   2048 ranks: 1 x 4096  9.0 / 9.2 / 12.6     2 x 4096  12.1 / 11.4 / 14.3    4 x 4096  12.3 / 11.4 / 14.9    12 x 4096  - / 12.5 / 15.2
+//               1 x 11008 12.1 / 13.8 / 17.2   2 x 11008 19.4 / 16.2 / 19.5    4 x 8192  18.5 / 15.3 / 19.2
+//   2560 ranks: 1 x 11008 12.9 / 13.1 / 17.0   2 x 11008 17.3 / 16.1 / 19.8    4 x 11008 22.8 / 19.9 / 19.7    6 x 11008  - / 19.8 / 19.7
+//   3 x 1536:   1 x 4096  11.3 / 11.4 / 15.7   2 x 4096  13.1 / 13.3 / 17.3    4 x 4096  15.0 / 14.7 / 17.8    12 x 4096  - / 15.5 / 18.0
 static bool z_many_workgroups(int B, int n, int units) {
   return B == 1 || units <= 128 || (units > 256 && B * n <= 12288);
 }
