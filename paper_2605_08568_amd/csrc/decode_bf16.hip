@@ -1058,6 +1058,7 @@ static bool z_many_workgroups(int B, int n, int units) {
 // Smaller calls are those of programs that may fit the cache.  Ordinary / past the caches for all calls, one state, three, as many as make 0.9 to 1.5 gigabytes:
 //   block of 2048 x 5632 (61 MiB)    1 sequence  34.2 / 33.5  35.6 / 36.1  41.5 / 37.2    32  64.8 / 66.6  65.1 / 70.4  72.1 / 70.5
 //   block of 1024 x 2816 (19 MiB)    1           28.7 / 28.7  31.2 / 30.4  36.8 / 32.9    32  58.1 / 59.6  60.2 / 63.5  66.2 / 65.1
+// decode_y16 keeps ordinary loads in either: 32 states, without / with, block of 4 78.6 / 79.0, of 12 86.9 / 87.0, MLP of 12 61.8 / 59.7.
 bool past_caches(const parse_layer *layers, int n_layers) {
   size_t bytes = 0;
   for (int l = 0; l < n_layers; ++l) bytes += (size_t)layers[l].R * ((size_t)layers[l].n + layers[l].m) * 2;

@@ -11,11 +11,11 @@
 // wavefronts take every fourth step and share nothing until their sums meet in LDS: no staging, no barrier in the loop; what
 // is in flight is DEPTH steps per wavefront (about 40 KiB; one wavefront per SIMD, so the registers are there).
 // Bound by HBM for the factors and by what a compute unit can take in: the token operands are re-read by every workgroup.
-// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns, 91.5 us a step on factors from memory: wide_z 18.7 us for gate+up
-// and 23.2 for down, 5.2 of them until the first slice is there (2.3 for the plan; a launch of its own for it and operands straight into registers, with one more launch
+// Measured, MLP of a 4096 x 11008 block (20 groups of 128 ranks), 150 sequences, six patterns, 100 us a step, three states in turn: wide_z 19.3 us for gate+up
+// and 24.0 for down, 5.2 of them until the first slice is there (2.3 for the plan; a launch of its own for it and operands straight into registers, with one more launch
 // that brought x into operand order, came to 27-30), then half a microsecond a slice of 28 KiB, which is what a unit takes in where lines from memory are among
 // those from the L2 (55 GB/s: 32 KiB outstanding, back in order), 1.6 for the sums; wide_zsum 4.8 each; wide_y 34 us, 24 of them the 467 KiB of factor and 778 KiB of z that
-// a unit takes in, and 9.9 us; five panels one after the other took 313-335 us.
+// a unit takes in, and 13.6 us; five panels one after the other took 313-335 us.
 // No atomics on floating point; fixed order of all sums: same inputs, same bits.
 #include <algorithm>
 
