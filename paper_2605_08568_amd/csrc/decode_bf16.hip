@@ -894,7 +894,7 @@ constexpr int D16_WAVES = 8, D16_THREADS = D16_WAVES * 64, D16_MAXB = 16;
 // NC blocks of 16 columns per workgroup; wavefront w takes every eighth 32-rank block in use.
 template <int NC>
 __global__ __launch_bounds__(D16_THREADS) void decode_y16(DecArgs a) {
-  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : 8), SUMS = NC == 3 ? 2 : 4;
+  constexpr int DEPTH = NC <= 2 ? 12 : (NC == 3 ? 10 : (NC == 4 ? 8 : 6)), SUMS = NC == 3 || NC == 6 ? 2 : 4;
   int li = 0;
 #pragma unroll
   for (int i = 1; i < DEC_MAX_LAYERS; ++i) li += (i < a.n_layers && (int)blockIdx.x >= a.L[i].y_first) ? 1 : 0;
@@ -1213,18 +1213,26 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   const size_t zs_bytes = max_kb * 2 * NB * 16;            // z pieces of every reduction block a layer has
   // ... and which one y: the vector units up to four sequences while there is little to do (sequences x columns x stored ranks;
   // 13 M 5.0 / 5.8, 25 M 8.0 / 6.6, 46 M 10.1 / 7.3 vector / 16-wide; four sequences, 2048 ranks and few columns 9.1 / 7.5), 16-wide up to sixteen
-  // (4096 columns 6.4, 32-wide 8.1) while up to four blocks a workgroup make one round (2 x 11008 columns, 2048 ranks, four sequences: six blocks 21.7,
-  // 32-wide 20.7)
+  // (4096 columns 6.4, 32-wide 8.1) while up to four blocks a workgroup make one round.  Beyond, six blocks a workgroup or 32-wide (us a call of 512 columns of input, three or
+  // twelve sequences, factors from memory, six / 32-wide, by columns x ranks): while six make one round, up to 45 M (columns x ranks) 17408 x 64 6.5 / 9.1,
+  // 2 x 9920 x 512 11.6 / 13.7, 24576 x 1536 18.1 / 18.9; 24576 x 2048 23.2 / 22.8, 2 x 11008 x 2048 26.9 / 26.2; while four 32-wide ones do and six not, up to
+  // 6 M only, 28672 x 64 8.4 / 9.4, x 128 9.8 / 10.4, x 192 12.2 / 12.2, x 256 13.6 / 12.7, x 1024 19.7 / 15.7; where neither does always, 36864 x 64 8.5 / 14.0, 40960 x 1024 21.0 / 24.6,
+  // 49152 x 2048 32.3 / 36.7, 65536 x 256 18.5 / 20.3, x 2048 41.7 / 40.7.
   long long y_work = 0;
-  for (int l = 0; l < n_layers; ++l) y_work += (long long)NB * layers[l].m * layers[l].R;
+  for (int l = 0; l < n_layers; ++l) y_work += (long long)layers[l].m * layers[l].R;
   // 16-column blocks per workgroup: the fewest that make one round of workgroups
-  int nc16 = 1;
-  for (; nc16 <= 4; ++nc16) {
+  auto rounds = [&](int columns) {
     int wgs = 0;
-    for (int l = 0; l < n_layers; ++l) wgs += (layers[l].m / 16 + nc16 - 1) / nc16;
-    if (wgs <= n_cu) break;
+    for (int l = 0; l < n_layers; ++l) wgs += (layers[l].m + columns - 1) / columns;
+    return (wgs + n_cu - 1) / n_cu;
+  };
+  int nc16 = 1;
+  while (nc16 <= 4 && rounds(nc16 * 16) > 1) ++nc16;
+  if (nc16 > 4) {
+    const bool one6 = rounds(96) == 1, one32 = rounds(128) == 1;
+    nc16 = (one6 ? y_work <= 45000000 : one32 ? y_work <= 6000000 : true) ? 6 : 0;                 // 0: 32-wide
   }
-  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES && (B == 1 || (y_work <= (16ll << 20) && (B == 2 || max_kb <= 64)))) {
+  if (B <= DV_MAXB && zs_bytes <= (size_t)DYV_ZBYTES && (B == 1 || (NB * y_work <= (16ll << 20) && (B == 2 || max_kb <= 64)))) {
     // a handful of sequences: z as a few values per rank in LDS, the launch streams only Ut.  16 columns per workgroup
     // unless that makes more than about four workgroups per compute unit
     int cols = 0;
@@ -1246,13 +1254,14 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
     else if (NB == 2) { if (CG == 2) PARSE_YV(2, 2); else PARSE_YV(2, 4); }
     else { if (CG == 2) PARSE_YV(4, 2); else PARSE_YV(4, 4); }
 #undef PARSE_YV
-  } else if (B <= D16_MAXB && nc16 <= 4) {
+  } else if (B <= D16_MAXB && nc16 > 0) {
     yb = 0;
     for (int l = 0; l < n_layers; ++l) { a.L[l].y_first = yb; yb += (layers[l].m / 16 + nc16 - 1) / nc16; }
     if (nc16 == 1) hipLaunchKernelGGL(decode_y16<1>, dim3(yb), dim3(D16_THREADS), 0, s, a);
     else if (nc16 == 2) hipLaunchKernelGGL(decode_y16<2>, dim3(yb), dim3(D16_THREADS), 0, s, a);
     else if (nc16 == 3) hipLaunchKernelGGL(decode_y16<3>, dim3(yb), dim3(D16_THREADS), 0, s, a);
-    else hipLaunchKernelGGL(decode_y16<4>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else if (nc16 == 4) hipLaunchKernelGGL(decode_y16<4>, dim3(yb), dim3(D16_THREADS), 0, s, a);
+    else hipLaunchKernelGGL(decode_y16<6>, dim3(yb), dim3(D16_THREADS), 0, s, a);
   } else {
 #define PARSE_Y(NC_)                                                                                              \
   do {                                                                                                           \

@@ -2110,7 +2110,7 @@ def test_prefill_planned_long_reductions(n, m, rS, lengths, cut):
     (4096, [(4096, 256, 4, 2), (8256, 128, 2, 1)], 3),               # two unlike layers, a task a workgroup; the second product's 32 columns a workgroup
     (4112, [(32, 224, 7, 3)], 14),                                   # 28 tasks
     (5648, [(96, 64, 2, 2)], 13),                                    # x and the sums all but fill the LDS
-    (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # more columns than four 16-column blocks a workgroup: second product 32-wide
+    (1024, [(16448, 1024, 16, 5), (16448, 64, 2, 1)], 2),            # more columns than a round of workgroups of either kernel: six 16-column blocks each
     (4624, [(64, 1024, 8, 3)], 4), (4624, [(64, 1056, 11, 3)], 4),   # 128 tasks: a workgroup each, second product on the vector units; 132: neither
     (6160, [(64, 96, 3, 2)], 4), (12304, [(64, 96, 3, 2)], 3),       # few tasks of long x
     (8208, [(64, 2048, 8, 3)], 2), (8208, [(64, 2080, 13, 3)], 2),   # two sequences, 256 tasks, 260 of them with over 12288 columns in all
@@ -2163,26 +2163,35 @@ def few_sequences_forms(n, shapes, B):
     else:
         first = "zr"
     nb, most = (1, 2, 4, 4)[min(B, 4) - 1], max(R for _, R, _, _ in shapes) // 16
-    work = sum(nb * m * R for m, R, _, _ in shapes)
-    if B <= 4 and most * nb * 32 <= 96 * 1024 and (B == 1 or (work <= 16 << 20 and (B == 2 or most <= 64))):
+    work = sum(m * R for m, R, _, _ in shapes)
+    if B <= 4 and most * nb * 32 <= 96 * 1024 and (B == 1 or (nb * work <= 16 << 20 and (B == 2 or most <= 64))):
         return first, "yv"
-    return first, "y16" if sum(-(-m // 16 // 4) for m, _, _, _ in shapes) <= 256 else "y"
+    one = lambda columns: sum(-(-m // columns) for m, _, _, _ in shapes) <= 256  # noqa: E731  (one round of workgroups)
+    for c in (1, 2, 3, 4):
+        if one(16 * c):
+            return first, f"y16<{c}>"
+    return first, "y16<6>" if (work <= 45000000 if one(96) else work <= 6000000 if one(128) else True) else "y"
 
 
 @pytest.mark.parametrize("n,shapes,B,first,second", [
-    (2064, [(64, 1024, 16, 8)], 4, "zv4", "yv"), (2064, [(64, 1056, 33, 16)], 4, "zp", "y16"),        # 128 and 132 tasks; 64 and 66 blocks
-    (2064, [(64, 2048, 64, 30)], 1, "zv4", "yv"), (2064, [(64, 2080, 13, 6)], 1, "zv8", "yv"),   # 256 and 260 tasks of one sequence
-    (4096, [(64, 2048, 16, 8)], 3, "zp", "y16"), (4096, [(64, 2080, 13, 7)], 3, "zv8", "y16"),        # ... of three with 12288 columns in all
-    (4112, [(64, 2080, 13, 7)], 3, "zp", "y16"),                                                      # and with 48 more
-    (2048, [(64, 1536, 16, 8), (32, 512, 16, 8), (32, 512, 16, 5)], 4, "zv8", "y16"),                 # three unlike layers, a task a workgroup
+    (2064, [(64, 1024, 16, 8)], 4, "zv4", "yv"), (2064, [(64, 1056, 33, 16)], 4, "zp", "y16<1>"),     # 128 and 132 tasks; 64 and 66 blocks
+    (2064, [(64, 2048, 64, 30)], 1, "zv4", "yv"), (2064, [(64, 2080, 13, 6)], 1, "zv8", "yv"),        # 256 and 260 tasks of one sequence
+    (4096, [(64, 2048, 16, 8)], 3, "zp", "y16<1>"), (4096, [(64, 2080, 13, 7)], 3, "zv8", "y16<1>"),  # ... of three with 12288 columns in all
+    (4112, [(64, 2080, 13, 7)], 3, "zp", "y16<1>"),                                                   # and with 48 more
+    (2048, [(64, 1536, 16, 8)] * 2 + [(32, 1536, 16, 5)], 4, "zv8", "y16<1>"),                        # three alike with unlike patterns
     # the most of x that a workgroup of one task stages (96 KiB), and 16 columns more
     (49136, [(32, 64, 2, 1)], 1, "zv4", "yv"), (49152, [(32, 64, 2, 1)], 1, "zp", "yv"),
     (24560, [(32, 64, 2, 1)], 2, "zv4", "yv"), (24576, [(32, 2080, 13, 6)], 2, "zp", "yv"),
     (16368, [(32, 64, 2, 1)], 3, "zv4", "yv"), (16384, [(32, 64, 2, 1)], 3, "zp", "yv"),
     (12272, [(32, 64, 2, 1)], 4, "zv4", "yv"), (12288, [(32, 64, 2, 1)], 4, "zp", "yv"),
-    (11024, [(64, 96, 3, 2)], 8, "zr", "y16"),                                                        # one sequence more than the LDS holds
-    (256, [(8192, 1024, 16, 8)], 2, "zv4", "yv"), (256, [(8224, 1024, 16, 8)], 2, "zv4", "y16"),      # columns x ranks x sequences: 16 M
-    (256, [(16384, 64, 2, 1)], 5, "zp", "y16"), (256, [(16416, 64, 2, 1)], 5, "zp", "y"),             # 256 workgroups of four 16-column blocks
+    (11024, [(64, 96, 3, 2)], 8, "zr", "y16<1>"),                                                     # one sequence more than the LDS holds
+    (256, [(8192, 1024, 16, 8)], 2, "zv4", "yv"), (256, [(8224, 1024, 16, 8)], 2, "zv4", "y16<3>"),   # columns x ranks x sequences: 16 M
+    (256, [(16384, 64, 2, 1)], 5, "zp", "y16<4>"), (256, [(16416, 64, 2, 1)], 5, "zp", "y16<6>"),     # 256 workgroups of four 16-column blocks
+    (48, [(16416, 2720, 17, 6)], 6, "zp", "y16<6>"), (48, [(16416, 2752, 43, 16)], 6, "zp", "y"),     # of six, 45 M
+    (48, [(24576, 1536, 48, 47)], 16, "zp", "y16<6>"),                                                # 48 blocks: six a wavefront, all that is on its way at once; 47
+    (256, [(24608, 224, 7, 3)], 11, "zp", "y16<6>"), (256, [(24608, 256, 8, 3)], 5, "zp", "y"),       # more than one round of six, 6 M
+    (256, [(32768, 192, 6, 3)], 9, "zp", "y"), (256, [(32800, 192, 6, 3)], 9, "zp", "y16<6>"),        # of four 32-wide blocks
+    (272, [(9696, 512, 16, 3)] * 3 + [(9632, 544, 17, 9)], 4, "zp", "y16<6>"),                        # four layers, whose last workgroups have one block of six and two
 ])
 def test_decode_few_sequences_at_the_lines_between_kernels(n, shapes, B, first, second):
     """Either side of each line at which calls of one to sixteen sequences change kernels, against the oracle's product."""
