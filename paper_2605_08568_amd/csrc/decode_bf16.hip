@@ -1042,7 +1042,11 @@ int build_decode_plan(const parse_layer *layers, const parse_patterns *pts, int 
 //               1 x 11008 12.1 / 13.8 / 17.2   2 x 11008 19.4 / 16.2 / 19.5    4 x 8192  18.5 / 15.3 / 19.2
 //   2560 ranks: 1 x 11008 12.9 / 13.1 / 17.0   2 x 11008 17.3 / 16.1 / 19.8    4 x 11008 22.8 / 19.9 / 19.7    6 x 11008  - / 19.8 / 19.7
 //   3 x 1536:   1 x 4096  11.3 / 11.4 / 15.7   2 x 4096  13.1 / 13.3 / 17.3    4 x 4096  15.0 / 14.7 / 17.8    12 x 4096  - / 15.5 / 18.0
-static bool z_many_workgroups(int B, int n, int units) {
+// Unlike layers: decode_zv's take turns, so beyond the shorter ones' ends only every second to fourth workgroup has a task, and the dispatcher hands those
+// to a half or a quarter of the units.  decode_zv / decode_zp, one sequence x columns, tasks of the layers: x 12624, 24 + 16 + 32 + 176 24.8 / 13.9; x 12832, 192 + 64 19.7 / 14.6;
+// x 8592, 128 + 152 + 176 + 80 26.0 / 17.8; x 4096, 192 + 64 + 64 11.2 / 10.4; x 4096, 256 + 64 10.5 / 11.0; x 5504, 80 + 96 + 64 9.8 / 10.3.
+static bool z_many_workgroups(int B, int n, int n_layers, int units, int most) {
+  if (most * n_layers != units && ((n_layers > 2 && units > 256) || most * n_layers * (units <= 256 ? 2 : 1) > 640)) return false;
   return B == 1 || units <= 128 || (units > 256 && B * n <= 12288);
 }
 
@@ -1055,7 +1059,8 @@ static bool z_many_workgroups(int B, int n, int units) {
 //                    32          100.5 / 101.1 108.0 / 100.6 107.7 / 105.6                      32  62.1 / 66.6   71.7 / 66.6    71.4 / 66.4
 //   MLP              64           68.0 / 74.2   79.2 / 71.7   78.9 / 75.8                       96  76.0 / 85.0   92.0 / 81.1    92.0 / 88.0
 //                   128           79.0 / 82.9   97.3 / 94.7   97.3 / 94.2                      150  87.4 / 90.1  106.5 / 103.9  106.0 / 103.5
-// Smaller calls are those of programs that may fit the cache.  Ordinary / past the caches for all calls, one state, three, as many as make 0.9 to 1.5 gigabytes:
+// 83 random calls above the line (one to 200 sequences) take 0.83 to 1.02 of the time beyond the cache, 0.95 in the middle, one 1.05; one call repeated, its factors in
+// the cache, 1.05 in the middle, up to 1.28, one 1.45.  Smaller calls are those of programs that may fit the cache.  Ordinary / past the caches for all calls, one state, three, as many as make 0.9 to 1.5 gigabytes:
 //   block of 2048 x 5632 (61 MiB)    1 sequence  34.2 / 33.5  35.6 / 36.1  41.5 / 37.2    32  64.8 / 66.6  65.1 / 70.4  72.1 / 70.5
 //   block of 1024 x 2816 (19 MiB)    1           28.7 / 28.7  31.2 / 30.4  36.8 / 32.9    32  58.1 / 59.6  60.2 / 63.5  66.2 / 65.1
 // decode_y16 keeps ordinary loads in either: 32 states, without / with, block of 4 78.6 / 79.0, of 12 86.9 / 87.0, MLP of 12 61.8 / 59.7.
@@ -1130,9 +1135,9 @@ int forward_decode_planned_bf16(const parse_layer *layers, int n_layers, const u
   const int nkb = a.n / 16;
   const int NB = B <= 1 ? 1 : (B <= 2 ? 2 : 4);
   const bool nt = past_caches(layers, n_layers);
-  int units = 0;                                           // tasks of eight ranks in the first product
-  for (int l = 0; l < n_layers; ++l) units += layers[l].R / 8;
-  const bool zv = B <= DV_MAXB && (size_t)B * dv_xstride(a.n) <= (size_t)DV_XBYTES && z_many_workgroups(B, a.n, units);
+  int units = 0, most = 0;                                 // tasks of eight ranks in the first product, of all layers and of the largest
+  for (int l = 0; l < n_layers; ++l) { units += layers[l].R / 8; most = std::max(most, layers[l].R / 8); }
+  const bool zv = B <= DV_MAXB && (size_t)B * dv_xstride(a.n) <= (size_t)DV_XBYTES && z_many_workgroups(B, a.n, n_layers, units, most);
   const bool zp = !zv && B <= DP_MAXB && (size_t)B * dv_xstride(a.n) + dp_red_bytes(B <= 8 ? 1 : 2) <= (size_t)DP_LDS;
   if (zv) {
     // a handful of sequences: eight ranks per workgroup, four where that leaves units without work

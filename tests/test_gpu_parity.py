@@ -2155,8 +2155,10 @@ def test_decode_few_sequences_tiles(n, shapes, B):
 
 def few_sequences_forms(n, shapes, B):
     """Kernels of the first and of the second product of one to sixteen sequences: the rules at their dispatch (256 units)."""
-    units, x = sum(R for _, R, _, _ in shapes) // 8, B * (2 * n + (128 if n % 128 == 0 else 0))          # tasks of eight ranks, bytes of x in LDS
-    if B <= 4 and x <= 96 * 1024 and (B == 1 or units <= 128 or (units > 256 and B * n <= 12288)):
+    tasks, x = [R // 8 for _, R, _, _ in shapes], B * (2 * n + (128 if n % 128 == 0 else 0))             # of eight ranks; bytes of x in LDS
+    units, slots = sum(tasks), max(tasks) * len(tasks)
+    turns = slots == units or not ((len(tasks) > 2 and units > 256) or slots * (2 if units <= 256 else 1) > 640)
+    if B <= 4 and x <= 96 * 1024 and turns and (B == 1 or units <= 128 or (units > 256 and B * n <= 12288)):
         first = "zv4" if units <= 256 else "zv8"                     # ranks a workgroup
     elif x + (8192 if B <= 8 else 16384) <= 160 * 1024 - 512:
         first = "zp"
@@ -2178,6 +2180,11 @@ def few_sequences_forms(n, shapes, B):
     (2064, [(64, 2048, 64, 30)], 1, "zv4", "yv"), (2064, [(64, 2080, 13, 6)], 1, "zv8", "yv"),        # 256 and 260 tasks of one sequence
     (4096, [(64, 2048, 16, 8)], 3, "zp", "y16<1>"), (4096, [(64, 2080, 13, 7)], 3, "zv8", "y16<1>"),  # ... of three with 12288 columns in all
     (4112, [(64, 2080, 13, 7)], 3, "zp", "y16<1>"),                                                   # and with 48 more
+    # unlike layers: three of 256 tasks and of 264, two with as many workgroups as are let take turns and with more
+    (2064, [(64, 768, 24, 8), (32, 640, 20, 8), (32, 640, 5, 4)], 1, "zv4", "yv"),
+    (2064, [(64, 768, 24, 8), (32, 672, 21, 8), (32, 672, 7, 4)], 1, "zp", "yv"),
+    (2064, [(64, 1280, 20, 8), (64, 256, 8, 3)], 1, "zv4", "yv"), (2064, [(64, 1312, 41, 8), (64, 256, 8, 3)], 1, "zp", "yv"),
+    (2064, [(64, 2560, 20, 8), (64, 256, 8, 3)], 4, "zv8", "y16<1>"), (2064, [(64, 2592, 27, 8), (64, 256, 8, 3)], 4, "zp", "y16<1>"),
     (2048, [(64, 1536, 16, 8)] * 2 + [(32, 1536, 16, 5)], 4, "zv8", "y16<1>"),                        # three alike with unlike patterns
     # the most of x that a workgroup of one task stages (96 KiB), and 16 columns more
     (49136, [(32, 64, 2, 1)], 1, "zv4", "yv"), (49152, [(32, 64, 2, 1)], 1, "zp", "yv"),
